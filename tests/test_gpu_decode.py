@@ -67,6 +67,22 @@ def test_ragged_sizes(orc, lane_syms, n):
     assert np.array_equal(got, _oracle_expected(orc, x))
 
 
+@pytest.mark.parametrize("lane_syms,cap", [(32, 0), (64, 0), (128, 0), (32, 15), (64, 10), (64, 15), (128, 10), (128, 15)])
+def test_ragged_last_chunk(orc, lane_syms, cap):
+    """The last chunk is cut inside a 16-byte piece, at a piece, at a lane, inside the forward and the backward run, with
+    nothing but one symbol in it, behind 0 .. 600 whole chunks (few and many per workgroup, in turn to each wave)."""
+    chunk = 64 * lane_syms
+    for whole in (0, 1, 7, 8, 15, 24, 600):
+        for part in (1, 15, 16, 17, 1023, 1025, chunk // 2 - 1, chunk // 2 + 16, chunk - 1024 - 5, chunk - 1):
+            n = whole * chunk + part
+            x = _rand_bytes(n, n + cap, conc=0.15 if part % 2 else 5.0)
+            blob = ecf8.ecf8_encode(x, 1, n, lane_syms=lane_syms, max_code_len=cap, table_mode=1 + (whole % 2))
+            got, guards = _gpu_decode_guarded(blob.numpy(), blob.header)
+            assert guards, (whole, part)
+            assert np.array_equal(got, x), (whole, part)         # the codec's definition; the oracle agrees on a sample
+    assert np.array_equal(x, _oracle_expected(orc, x))
+
+
 def _special_cases():
     fib = [1, 1]
     while len(fib) < 16:
