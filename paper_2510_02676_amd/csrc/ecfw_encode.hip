@@ -285,7 +285,7 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, const ecfw_
     hipLaunchKernelGGL(w_header_kernel, dim3(1), dim3(128), 0, s, blob, ha);
     const uint32_t chunk_blocks = (uint32_t)((h.n_chunks + 3) / 4);
     hipLaunchKernelGGL(w_lane_bits_kernel<FMT>, dim3(chunk_blocks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, blob + h.off_chunk_bit, h.n_chunks);
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, blob + h.off_chunk_bit, h.n_chunks, blob + h.off_stream);
     // span of a chunk: at most 64 N lmax bits plus the bits before it in its first dword
     const uint32_t need_dw = (64u * N * h.max_code_len + 31) / 32 + 2;
     const int pg = grid_for_bytes(chunk_blocks, 1);

@@ -75,6 +75,13 @@ def test_seeded_sweep_of_shapes_and_options(orc, block):
                     table_mode=int(rng.choice([1, 2])))
 
 
+@pytest.mark.parametrize("extra", [-2048, 0, 1, 2048 * 1024 + 7])
+def test_more_chunks_than_a_round_of_the_prefix_sum(orc, extra):
+    """The chunk totals are summed 8192 at a time; the last round has one chunk less, none, one symbol, 1024 chunks more."""
+    x = _rand_bytes(8192 * 2048 + extra, 91 + extra % 5)
+    _check_same(orc, x, 1, x.size, oracle_read=False, lane_syms=32, max_code_len=15 if extra else 0)
+
+
 def test_special_histograms(orc):
     fib = [1, 1]
     while len(fib) < 16:
