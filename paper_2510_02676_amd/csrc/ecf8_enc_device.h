@@ -56,6 +56,51 @@ __global__ __launch_bounds__(1024) void scan_kernel(uint64_t chunk_bit_, uint64_
     }
 }
 
+// Where chunk c's pieces lie: piece q of lane l starts at element base + q * stride + lane_off(l) (see the container's layouts).
+struct ChunkPlace {
+    uint64_t base, stride, lane_off;
+};
+
+// The 16 bytes at byte e of a tensor of n bytes, zeros from its end on.
+__device__ __forceinline__ u32x4 load_cut(const GLOBAL uint8_t *x, uint64_t e, uint64_t n)
+{
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const uint64_t d = e + 4 * k;
+        if (d + 4 <= n) w[k] = *(const GLOBAL uint32_t *)(x + d);
+        else
+#pragma unroll
+            for (int b = 0; b < 3; b++)
+                if (d + b < n) w[k] |= (uint32_t)x[d + b] << (8 * b);
+    }
+    return u32x4{w[0], w[1], w[2], w[3]};
+}
+
+// A lane's string of bits on its way into the chunk's span in LDS (zeroed before): whole dwords are ORed in as they fill.
+struct LanePacker {
+    uint32_t *d;
+    uint32_t fill, acc = 0;
+
+    __device__ __forceinline__ LanePacker(uint32_t *stage, uint32_t at) : d(stage + (at >> 5)), fill(at & 31) {}
+    __device__ __forceinline__ void put(uint32_t bits, uint32_t nb)          // nb <= 32, bits above nb clear
+    {
+        const uint64_t t = (uint64_t)bits << fill;
+        acc |= (uint32_t)t;
+        fill += nb;
+        if (fill >= 32) {
+            __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            d++;
+            fill -= 32;
+            acc = (uint32_t)(t >> 32);
+        }
+    }
+    __device__ __forceinline__ void finish()
+    {
+        if (fill) __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+};
+
 // A chunk's span of the stream, assembled in LDS (`stage` = the 16-byte unit that holds stream bit b0, on), to its place:
 // whole units by 16-byte stores, the units at the ends dword by dword; the first and the last dword may hold bits of
 // other chunks, were zeroed by scan_kernel (or, the stream's last one, with the padding) and are ORed into.
@@ -81,17 +126,6 @@ __device__ __forceinline__ void copy_span(const uint32_t *stage, GLOBAL uint32_t
         }
     }
 }
-
-[[maybe_unused]] int grid_for_bytes(uint64_t work_items, int per_block)
-{
-    int cus = device_cus();
-    if (cus <= 0) return -1;
-    uint64_t want = (work_items + per_block - 1) / per_block;
-    uint64_t cap = (uint64_t)cus * 8;
-    uint64_t g = want < cap ? want : cap;
-    return (int)(g ? g : 1);
-}
-
 
 } // namespace
 

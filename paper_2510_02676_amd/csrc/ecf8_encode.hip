@@ -28,11 +28,6 @@ struct EncArgs {
     uint32_t code[16], rcode[16];
 };
 
-// Where chunk c's pieces lie: piece q of lane l starts at element base + q * stride + lane_off(l) (see the container's layouts).
-struct ChunkPlace {
-    uint64_t base, stride, lane_off;
-};
-
 template <int N>
 __device__ __forceinline__ ChunkPlace place_of(const EncArgs &a, uint64_t c, uint32_t lane)
 {
@@ -46,22 +41,6 @@ __device__ __forceinline__ ChunkPlace place_of(const EncArgs &a, uint64_t c, uin
     const uint64_t w = c & (a.group - 1);
     if (c < grouped) return {(c - w) * E + w * 1024, (uint64_t)a.group * 1024, lane * 16ull};
     return {c * E, 1024, lane * 16ull};
-}
-
-// The 16 bytes at element e of a piece that reaches past the tensor's end, zeros from there on.
-__device__ __forceinline__ u32x4 load_cut(const GLOBAL uint8_t *x, uint64_t e, uint64_t n)
-{
-    uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const uint64_t d = e + 4 * k;
-        if (d + 4 <= n) w[k] = *(const GLOBAL uint32_t *)(x + d);
-        else
-#pragma unroll
-            for (int b = 0; b < 3; b++)
-                if (d + b < n) w[k] |= (uint32_t)x[d + b] << (8 * b);
-    }
-    return u32x4{w[0], w[1], w[2], w[3]};
 }
 
 // A lane's pieces of a chunk; `whole`: the chunk lies entirely inside the tensor (the same for every lane).
@@ -265,19 +244,7 @@ __global__ __launch_bounds__(256) void pack_kernel(EncArgs a)
         for (uint32_t u = lane; u < n_units && u < (uint32_t)STAGE / 4; u += 64) *(u32x4 *)(stage + 4 * u) = u32x4{0, 0, 0, 0};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const uint32_t at = (uint32_t)(b0 & 127) + (wave_incl_scan(lb) - lb);     // stage bit of the lane's first bit
-        uint32_t *d = stage + (at >> 5);
-        uint32_t fill = at & 31, acc = 0;
-        auto put = [&](uint32_t bits, uint32_t nb) {          // nb <= 30, bits above nb clear
-            const uint64_t t = (uint64_t)bits << fill;
-            acc |= (uint32_t)t;
-            fill += nb;
-            if (fill >= 32) {
-                __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                d++;
-                fill -= 32;
-                acc = (uint32_t)(t >> 32);
-            }
-        };
+        LanePacker out(stage, at);
         // the four symbols of dword w, in order (BWD = false) or in reverse
         auto put4 = [&](auto bwd, uint32_t w) {
             constexpr bool BWD = decltype(bwd)::value;
@@ -287,10 +254,10 @@ __global__ __launch_bounds__(256) void pack_kernel(EncArgs a)
             if (BWD) { const Entry x = ea; ea = eb; eb = x; }
             if constexpr (CAP7) {
                 const uint32_t la = ea >> LEN_AT, lb2 = eb >> LEN_AT;
-                put((ea & ((1u << LEN_AT) - 1u)) | ((eb & ((1u << LEN_AT) - 1u)) << la), la + lb2);
+                out.put((ea & ((1u << LEN_AT) - 1u)) | ((eb & ((1u << LEN_AT) - 1u)) << la), la + lb2);
             } else {
-                put((uint32_t)ea, (uint32_t)(ea >> LEN_AT));
-                put((uint32_t)eb, (uint32_t)(eb >> LEN_AT));
+                out.put((uint32_t)ea, (uint32_t)(ea >> LEN_AT));
+                out.put((uint32_t)eb, (uint32_t)(eb >> LEN_AT));
             }
         };
         if (whole) {
@@ -310,7 +277,7 @@ __global__ __launch_bounds__(256) void pack_kernel(EncArgs a)
                     const uint32_t j = back ? 15 - k : k, w = j < 8 ? (j < 4 ? piece.x : piece.y) : (j < 12 ? piece.z : piece.w);
                     const uint32_t s = j < have ? (w >> (8 * (j & 3) + 3)) & 15u : 16u;
                     const uint32_t e = s_one[back][s];
-                    put(e & 0xffffu, e >> 16);
+                    out.put(e & 0xffffu, e >> 16);
                 }
             };
             const uint64_t e0 = p.base + p.lane_off;
@@ -319,7 +286,7 @@ __global__ __launch_bounds__(256) void pack_kernel(EncArgs a)
 #pragma unroll
             for (int q = N / 16 - 1; q >= N / 32; q--) put_piece(true, v[q], piece_len(e0 + q * p.stride, a.n));
         }
-        if (fill) __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        out.finish();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         copy_span(stage, (GLOBAL uint32_t *)(a.blob + a.off_st), b0, b1, lane);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -82,6 +82,24 @@ def test_more_chunks_than_a_round_of_the_prefix_sum(orc, extra):
     _check_same(orc, x, 1, x.size, oracle_read=False, lane_syms=32, max_code_len=15 if extra else 0)
 
 
+@pytest.mark.parametrize("opts", [dict(lane_syms=128, table_mode=1), dict(lane_syms=64, table_mode=2, max_code_len=15), dict(lane_syms=32, table_mode=1, group_chunks=1),
+                                  dict(lane_syms=64, tile_rows=16, table_mode=2)])
+def test_every_byte_of_the_blob_is_written(opts):
+    """Into a poisoned buffer: the padding between sections, the plane past a ragged end and the dwords of the stream
+    that chunks share hold what the CPU encoder's container holds, and nothing behind the blob is touched."""
+    rows = 16 if "tile_rows" in opts else 1
+    for n in ([4096, 16 * 4096] if rows == 16 else [1, 33, 2047, 8192, 8192 * 33 + 5, 300_001]):
+        x = _rand_bytes(n, n + 5)
+        want = ecf8.ecf8_encode(x, rows, n // rows, **opts)
+        buf = torch.full((want.size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+        hdr, _ = ecf8.ecf8_encode_gpu(torch.from_numpy(x).to(DEV), rows, n // rows, d_blob=buf, **opts)
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        assert bytes(hdr) == bytes(want.header)
+        assert np.array_equal(got[:want.size], want.numpy()), n
+        assert (got[want.size:] == 0xA5).all(), n
+
+
 def test_special_histograms(orc):
     fib = [1, 1]
     while len(fib) < 16:
