@@ -94,42 +94,44 @@ struct ChunkMap {
 // starting at the deepest level, the items of a level are paired into packages
 // that join the next level's coins; the 2m-2 cheapest items of the top level say
 // how many levels each symbol was taken at = its code length.
+// Only the weights are carried from level to level, and per level which item is a coin: coins and packages are each in
+// order, so the K items taken at a level are its first a coins and first K - a packages, and those packages are the first
+// 2 (K - a) items one level down.  Walking down from the top, every symbol below a gets one level longer.  (With the
+// taken coins counted inside every item this was 45 us of a device encode of BF16, all of it with the GPU idle.)
 bool capped_lengths(const uint64_t *freq, uint32_t A, uint32_t lmax, uint8_t *len)
 {
-    std::vector<uint32_t> sym;
-    for (uint32_t s = 0; s < A; s++) { len[s] = 0; if (freq[s]) sym.push_back(s); }
-    const size_t m = sym.size();
+    struct Coin { uint64_t w; uint32_t s; };
+    Coin coin[256];
+    uint32_t m = 0;
+    for (uint32_t s = 0; s < A; s++) { len[s] = 0; if (freq[s]) coin[m++] = {freq[s], s}; }
     if (m == 0 || lmax < 1 || lmax > ECFW_MAX_CODE_LEN || (uint64_t)m > (1ull << lmax)) return false;
-    if (m == 1) { len[sym[0]] = 1; return true; }
-    std::stable_sort(sym.begin(), sym.end(), [&](uint32_t a, uint32_t b) { return freq[a] < freq[b]; });
-    struct Item { uint64_t w; std::vector<uint8_t> taken; };   // taken[i]: how often coin i is inside
-    std::vector<Item> coins(m);
-    for (size_t i = 0; i < m; i++) {
-        coins[i].w = freq[sym[i]];
-        coins[i].taken.assign(m, 0);
-        coins[i].taken[i] = 1;
-    }
-    std::vector<Item> cur = coins;
+    if (m == 1) { len[coin[0].s] = 1; return true; }
+    std::sort(coin, coin + m, [](const Coin &a, const Coin &b) { return a.w != b.w ? a.w < b.w : a.s < b.s; });
+    uint64_t w[2][512];                                   // a level has at most m coins and m - 1 packages
+    bool is_coin[ECFW_MAX_CODE_LEN][512];
+    uint32_t n = m;
+    for (uint32_t i = 0; i < m; i++) { w[0][i] = coin[i].w; is_coin[0][i] = true; }
     for (uint32_t level = 1; level < lmax; level++) {
-        std::vector<Item> packages;
-        for (size_t i = 0; i + 1 < cur.size(); i += 2) {
-            Item p{cur[i].w + cur[i + 1].w, cur[i].taken};
-            for (size_t j = 0; j < m; j++) p.taken[j] = (uint8_t)(p.taken[j] + cur[i + 1].taken[j]);
-            packages.push_back(std::move(p));
+        const uint64_t *below = w[(level - 1) & 1];
+        uint64_t *here = w[level & 1];
+        const uint32_t packages = n / 2;
+        uint32_t a = 0, b = 0;
+        n = 0;
+        while (a < m || b < packages) {
+            const uint64_t pw = b < packages ? below[2 * b] + below[2 * b + 1] : 0;
+            const bool c = b >= packages || (a < m && coin[a].w <= pw);       // a coin goes before a package of its weight
+            is_coin[level][n] = c;
+            here[n++] = c ? coin[a].w : pw;
+            if (c) a++; else b++;
         }
-        std::vector<Item> merged;
-        merged.reserve(m + packages.size());
-        size_t a = 0, b = 0;
-        while (a < m || b < packages.size()) {
-            if (b >= packages.size() || (a < m && coins[a].w <= packages[b].w)) merged.push_back(coins[a++]);
-            else merged.push_back(std::move(packages[b++]));
-        }
-        cur.swap(merged);
     }
-    std::vector<uint32_t> total(m, 0);
-    for (size_t i = 0; i < 2 * m - 2; i++)
-        for (size_t j = 0; j < m; j++) total[j] += cur[i].taken[j];
-    for (size_t j = 0; j < m; j++) len[sym[j]] = (uint8_t)total[j];
+    uint32_t taken = 2 * m - 2;
+    for (uint32_t level = lmax; level-- > 0 && taken;) {
+        uint32_t a = 0;
+        for (uint32_t i = 0; i < taken; i++) a += is_coin[level][i];
+        for (uint32_t i = 0; i < a; i++) len[coin[i].s]++;
+        taken = 2 * (taken - a);
+    }
     return true;
 }
 
