@@ -582,6 +582,16 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_raw_kernel(GArgs a)
 // the A operands of a chunk are fetched from X (L2-resident: M x K bytes) one chunk ahead, like
 // the chunk's payload.  Same decode, same MFMA order inside a chunk, same reduction.
 
+// The table's set-up out of line (APART), for the kernels that walk over several matrices: inlined there, its registers
+// cost the decode loop spills (eight experts 113.8 us inlined, 109.6 called; kernels of one matrix have the registers and
+// save the call's 1 us).
+template <int NW>
+__device__ __noinline__ void build_pair_table_apart(uint64_t len_lo, uint64_t len_hi, uint8_t *smem, int lane, int wave)
+{
+    using C = GCfg<1, NW, 64>;
+    build_pair_table<NW>(len_lo, len_hi, (uint16_t *)(smem + C::OFF_TBL), (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
+}
+
 template <int MT, int N>
 struct XPieces { u32x4 v[MT][N / 16]; };
 
@@ -616,7 +626,7 @@ struct Walk {
 // The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units
 // of them), table set-up included.  `parity` says which of the two reduction buffers comes next and is
 // carried on to the caller's next matrix.
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0>
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0, bool APART = false>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint64_t unit_stride,
                                           uint64_t my_units, uint32_t &parity)
 {
@@ -721,7 +731,8 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         for (int i = tid; i < TBL_ENTRIES * 2 / 16; i += NW * 64) ((u32x4 *)tbl)[i] = src[i];
         __syncthreads();
     } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
+        if constexpr (APART) build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
+        else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
     }
 
     for (uint64_t b = 0; b < my_blocks; b++) {            // uniform for the workgroup: one barrier per block
@@ -942,7 +953,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
         __syncthreads();                                // the last matrix's table and reduction buffers are out of use
         if (b0 < b1) {
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
-            else anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
+            else anyk_walk<MT, NW, N, SC, false, 0, true>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
         }
         pos = it.first_work + n_blocks * kchunks;       // on to the next matrix (or past `end`)
     }
