@@ -6,20 +6,17 @@
 // one backward), finished 16-byte pieces held in registers and stored in one
 // burst, persistent workgroups over contiguous chunk ranges with an LDS ticket
 // counter among their waves.  What differs:
-//  * the lookup table has 2^12 16-bit entries and resolves ONE codeword per
-//    lookup (with up to 256 symbols a pair table would not fit LDS); an entry is
-//    the exponent field already shifted to its place in the output element, plus
-//    the codeword's length.  One 32-bit window serves two lookups;
-//  * under the encoder's default cap of 12 bits every codeword is a table hit
-//    (FAST kernels: straight-line code); longer codes (cap 13..16) fall to a
-//    canonical first-code comparison per length, in a rarely taken branch;
+//  * under the encoder's default cap of 12 bits (ecfw_decode_kernel) one lookup resolves TWO codewords, as there: a
+//    pair table is built from a 2^12-entry table of single codewords, with entries that fit the format (see Pairs);
+//    pairs that do not fit it take a branch-free second level.  The launch of a layer of seven matrices (218 M elements)
+//    with one codeword per lookup and the lanes' bits moved to bank-private LDS columns first took 107.5 us for E5M2,
+//    bound by LDS and vector work; now 90 (376 MB: 4.2 TB/s, two thirds of what is left is vector work).  BF16
+//    was and is at the memory wall: 140.5 -> 138.7 us (735 MB: 5.3 TB/s);
+//  * codes with longer codewords (cap 13..16, ecfw_long_decode_kernel) keep one codeword per lookup and
+//    a canonical first-code comparison per length, in a rarely taken branch;
 //  * the remaining bits come from planes laid out so that whole output words are
 //    merged with a few bit selects (BF16: a byte per element in the order
 //    0 2 1 3; E5M2: mantissas sliced by output word, signs as a bit mask);
-//  * these kernels are bound by the LDS, not by HBM, unless the window reads are
-//    kept off each other's banks: the FAST kernels move every lane's bits from
-//    the linear image of the span into a column of its own before decoding
-//    (dword r of lane l at row r, column l), see WCfg;
 //  * one launch may cover many tensors (ecfw_decode_batched): a workgroup's
 //    range of chunks runs through the batch and the code is set up again where
 //    it crosses into another tensor.
@@ -28,8 +25,7 @@
 #include "ecf8_device.h"
 
 #include <cstring>
-
-#include <cstdlib>
+#include <type_traits>
 
 namespace {
 
@@ -55,20 +51,15 @@ template <> struct Fmt<ECFW_FMT_BF16> {
     static constexpr int SYM_SHIFT = 7, LEN_SHIFT = 0;     // entry = exponent << 7 | length
 };
 
-// COLS: after the chunk's span has landed in LDS, every lane copies the dwords of its own bits into a
-// column of its own (dword r of lane l at row r, column l: bank l % 32), so that the two window
-// reads of every decode step are free of bank conflicts; the copy reads each dword once instead.
-template <int FMT, int N, int WAVES, bool COLS>
+// The kernel for codes with codewords of more than 12 bits (ecfw_long_decode_kernel).
+template <int FMT, int N, int WAVES>
 struct WCfg {
     using F = Fmt<FMT>;
     static constexpr int PIECES = N / F::P;                 // 16-byte pieces per lane
     // span of a chunk whose codewords average AVG bits: uniformly random exponent fields still fit
-    static constexpr int AVG = COLS ? (FMT == ECFW_FMT_BF16 ? 8 : 5) : 8;
+    static constexpr int AVG = 8;
     static constexpr int STAGE = 8 * AVG * N + 64;
     static constexpr int SEGS = (STAGE / 16 + 63) / 64;
-    // rows of a lane's column: its bits at up to AVG + 1/2 bits per codeword, the dword before, the
-    // dword after, and the misalignment of its first bit
-    static constexpr int ROWS = COLS ? ((2 * AVG + 1) * N / 64 + 3) : 0;
     static constexpr int OFF_TBL = 0;
     static constexpr int OFF_WCNT = OFF_TBL + (2 << WTB);   // symbols per (wavefront, length) while the code is set up
     static constexpr int OFF_SORTED = OFF_WCNT + 320;       // symbols ordered by (length, symbol)
@@ -76,10 +67,8 @@ struct WCfg {
     static constexpr int OFF_FIRST = OFF_CNT + 80;
     static constexpr int OFF_OFFS = OFF_FIRST + 80;
     static constexpr int OFF_TICKET = OFF_OFFS + 80;
-    static constexpr int OFF_STAGE = OFF_TICKET + 16 + 16;  // one spare slot below: a column's first row is the dword
-                                                            // before the lane's first one
-    static constexpr int OFF_COLS = OFF_STAGE + WAVES * STAGE;
-    static constexpr int TOTAL = OFF_COLS + WAVES * ROWS * 256;
+    static constexpr int OFF_STAGE = OFF_TICKET + 16;
+    static constexpr int TOTAL = OFF_STAGE + WAVES * STAGE;
     static_assert(STAGE % 16 == 0 && OFF_STAGE % 16 == 0, "16-byte LDS stores");
     static_assert(PIECES % 2 == 0, "two runs of whole pieces");
     static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
@@ -95,61 +84,59 @@ struct CodeArrays {
 // (count, first code, offset into the list of symbols sorted by (length, symbol))
 // and the lookup table.  All threads of the workgroup call it; it needs at least
 // four wavefronts.  Symbols are ranked with wave ballots (wavefront w holds symbols
-// 64w..64w+63), so nothing here loops over the alphabet.
+// 64w..64w+63); in every wavefront lane l stands for length l, so that first codes and offsets are two
+// wave prefix sums, and an entry's length is the number of lengths whose codes all lie below its index.
 template <int FMT>
-__device__ void build_code(const GLOBAL uint8_t *code_len, uint32_t *wavecnt, uint8_t *sorted, uint32_t *cnt,
+__device__ void build_code(uint32_t my_len, uint32_t *wavecnt, uint8_t *sorted, uint32_t *cnt,
                            uint32_t *first, uint32_t *offs, uint16_t *tbl, int tid, int nthreads)
 {
     using F = Fmt<FMT>;
     constexpr int L = (int)ECFW_MAX_CODE_LEN;
-    const int lane = tid & 63, wave = tid >> 6;
-    uint32_t my_len = 0, my_rank = 0;
-    if (tid < 256) {
-        my_len = tid < F::A ? code_len[tid] : 0;
-        if (my_len > (uint32_t)L) my_len = 0;
+    const int lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
+    uint32_t my_rank = 0;
+    if (wave < 4) {
         const uint64_t below = ((uint64_t)1 << lane) - 1;
+        uint32_t count = 0;                                         // lane l: symbols of length l in this wavefront
 #pragma unroll
         for (int l = 1; l <= L; l++) {
             const uint64_t m = __ballot(my_len == (uint32_t)l);
             if (my_len == (uint32_t)l) my_rank = (uint32_t)__popcll(m & below);
-            if (lane == 0) wavecnt[wave * 20 + l] = (uint32_t)__popcll(m);
+            if (lane == l) count = (uint32_t)__popcll(m);
         }
+        if (lane <= L) wavecnt[wave * 20 + lane] = count;
     }
     __syncthreads();
-    // every thread keeps the canonical arrays of the lengths the table covers in registers
-    uint32_t r_first[WTB + 1], r_offs[WTB + 1], r_limit[WTB + 1];   // limit: first code of the next length, left-aligned
-    {
-        uint32_t code = 0, off = 0, prev = 0;
+    // lane l = 1 .. L: symbols of length l, offset of the first one in `sorted`, its code
+    uint32_t c[4], total = 0;
 #pragma unroll
-        for (int l = 1; l <= L; l++) {
-            const uint32_t c = wavecnt[l] + wavecnt[20 + l] + wavecnt[40 + l] + wavecnt[60 + l];
-            code = (code + prev) << 1;
-            if (l <= WTB) {
-                r_first[l] = code;
-                r_offs[l] = off;
-                r_limit[l] = (code + c) << (WTB - l);
-            }
-            if (tid == 0) { cnt[l] = c; first[l] = code; offs[l] = off; }
-            if (my_len == (uint32_t)l) {
-                uint32_t before = 0;
-#pragma unroll
-                for (int w = 0; w < 4; w++) before += w < wave ? wavecnt[w * 20 + l] : 0;
-                my_rank += off + before;
-            }
-            off += c;
-            prev = c;
-        }
+    for (int w = 0; w < 4; w++) {
+        c[w] = lane >= 1 && lane <= L ? wavecnt[w * 20 + lane] : 0u;
+        total += c[w];
     }
-    if (tid < 256 && my_len) sorted[my_rank] = (uint8_t)tid;
+    const uint32_t space = lane >= 1 && lane <= L ? total << (L - lane) : 0u;      // of the 2^L units of code space
+    const uint32_t used = wave_incl_scan(space), off = wave_incl_scan(total) - total;
+    const uint32_t code1 = lane >= 1 && lane <= L ? (used - space) >> (L - lane) : 0u;
+    if (wave == 0 && lane <= L) { cnt[lane] = total; first[lane] = code1; offs[lane] = off; }
+    if (wave < 4) {
+        uint32_t before = off;
+#pragma unroll
+        for (int w = 0; w < 3; w++) before += w < wave ? c[w] : 0u;
+        my_rank += (uint32_t)__builtin_amdgcn_ds_bpermute((int)(my_len * 4), (int)before);
+        if (my_len) sorted[my_rank] = (uint8_t)tid;
+    }
+    uint32_t limit[WTB + 1];                                        // first 12-bit index past the codes of length l and below
+#pragma unroll
+    for (int l = 1; l <= WTB; l++) limit[l] = (uint32_t)__builtin_amdgcn_readlane((int)used, l) >> (L - WTB);
     __syncthreads();
     // entry i: the codeword spelled by the bits of i, bit 0 first
     for (int i = tid; i < (1 << WTB); i += nthreads) {
         const uint32_t v = __brev((uint32_t)i) >> (32 - WTB);       // the 12 bits, first bit most significant
-        uint32_t e = 0;
+        uint32_t l = 1;
 #pragma unroll
-        for (int l = WTB; l >= 1; l--)                              // the smallest length whose codes reach past v
-            if (v < r_limit[l]) e = ((uint32_t)l << 16) | (r_offs[l] + (v >> (WTB - l)) - r_first[l]);
-        if (e) e = ((uint32_t)sorted[e & 0xffffu] << F::SYM_SHIFT) | ((e >> 16) << F::LEN_SHIFT);
+        for (int k = 1; k < WTB; k++) l += v >= limit[k];
+        const uint32_t at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(l * 4), (int)(off - code1)) + (v >> (WTB - l));
+        uint32_t e = 0;
+        if (v < limit[WTB]) e = ((uint32_t)sorted[at & 255u] << F::SYM_SHIFT) | (l << F::LEN_SHIFT);
         tbl[i] = (uint16_t)e;
     }
     __syncthreads();
@@ -178,11 +165,11 @@ __device__ __noinline__ uint32_t long_code(uint32_t bits, const uint8_t *sorted,
     return e;
 }
 
-template <int FMT, bool FAST>
+template <int FMT>
 __device__ __forceinline__ uint32_t decode_entry(uint32_t bits, const CodeArrays &ca)
 {
     uint32_t e = ca.tbl[bits & ((1u << WTB) - 1)];
-    if (!FAST && __builtin_expect(e == 0, 0)) e = long_code<FMT>(bits, ca.sorted, ca.cnt, ca.first, ca.offs);
+    if (__builtin_expect(e == 0, 0)) e = long_code<FMT>(bits, ca.sorted, ca.cnt, ca.first, ca.offs);
     return e;
 }
 
@@ -190,18 +177,14 @@ __device__ __forceinline__ uint32_t decode_entry(uint32_t bits, const CodeArrays
 // pb = (one past the next bit of the backward run) - 31 as absolute LDS bit
 // addresses: the windows read there are the stream bits shifted left by one,
 // which masked is the byte offset of a table entry.
-// COLS: pa and pb count bits inside the lane's column (row = bit / 32), `smem` points at the lane's
-// slot of row 0, and consecutive dwords of the lane lie 256 bytes apart.
-template <int FMT, bool FAST, bool COLS>
+template <int FMT>
 __device__ __forceinline__ void pair_step(const uint8_t *smem, const CodeArrays &ca, uint32_t &pa, uint32_t &pb,
                                           uint32_t &eA0, uint32_t &eA1, uint32_t &eB0, uint32_t &eB1)
 {
-    static_assert(!COLS || FAST, "the long-code branch reads windows from the linear stage");
     const uint8_t *tb = (const uint8_t *)ca.tbl;
-    constexpr uint32_t NEXT = COLS ? 256 : 4;
-    const uint32_t aA = COLS ? (pa >> 5) << 8 : (pa >> 3) & ~3u, aB = COLS ? (pb >> 5) << 8 : (pb >> 3) & ~3u;
-    const uint32_t wA = __builtin_amdgcn_alignbit(*(const uint32_t *)(smem + aA + NEXT), *(const uint32_t *)(smem + aA), pa);
-    const uint32_t wB = __brev(__builtin_amdgcn_alignbit(*(const uint32_t *)(smem + aB + NEXT), *(const uint32_t *)(smem + aB), pb));
+    const uint32_t aA = (pa >> 3) & ~3u, aB = (pb >> 3) & ~3u;
+    const uint32_t wA = __builtin_amdgcn_alignbit(*(const uint32_t *)(smem + aA + 4), *(const uint32_t *)(smem + aA), pa);
+    const uint32_t wB = __brev(__builtin_amdgcn_alignbit(*(const uint32_t *)(smem + aB + 4), *(const uint32_t *)(smem + aB), pb));
     eA0 = *(const uint16_t *)(tb + (wA & WMASK2));
     eB0 = *(const uint16_t *)(tb + (wB & WMASK2));
     uint32_t lA0 = entry_len<FMT>(eA0), lB0 = entry_len<FMT>(eB0);
@@ -209,15 +192,15 @@ __device__ __forceinline__ void pair_step(const uint8_t *smem, const CodeArrays 
     eB1 = *(const uint16_t *)(tb + ((wB >> lB0) & WMASK2));
     uint32_t lA1 = entry_len<FMT>(eA1), lB1 = entry_len<FMT>(eB1);
     // a miss leaves the length 0, so the second lookup repeats the first: testing the second covers both
-    if (!FAST && __builtin_expect(eA1 == 0 || eB1 == 0, 0)) {
+    if (__builtin_expect(eA1 == 0 || eB1 == 0, 0)) {
         if (eA1 == 0) {
             if (eA0 == 0) { eA0 = long_code<FMT>(wA >> 1, ca.sorted, ca.cnt, ca.first, ca.offs); lA0 = entry_len<FMT>(eA0); }
-            eA1 = decode_entry<FMT, false>(lds_window<+1>(smem, pa + 1 + lA0), ca);
+            eA1 = decode_entry<FMT>(lds_window<+1>(smem, pa + 1 + lA0), ca);
             lA1 = entry_len<FMT>(eA1);
         }
         if (eB1 == 0) {
             if (eB0 == 0) { eB0 = long_code<FMT>(wB >> 1, ca.sorted, ca.cnt, ca.first, ca.offs); lB0 = entry_len<FMT>(eB0); }
-            eB1 = decode_entry<FMT, false>(lds_window<-1>(smem, pb + 31 - lB0), ca);
+            eB1 = decode_entry<FMT>(lds_window<-1>(smem, pb + 31 - lB0), ca);
             lB1 = entry_len<FMT>(eB1);
         }
     }
@@ -245,7 +228,7 @@ __device__ __forceinline__ u32x4 merge_bf16(const uint32_t e[8], u32x2 pl)
     return d;
 }
 
-// E5M2: e[0..15]; mant = the piece's mantissa word, sign = its 16 sign bits.
+// E5M2: e[0..15]: entries of the 12-bit table; mant = the piece's mantissa word, sign = its 16 sign bits.
 __device__ __forceinline__ u32x4 merge_e5m2(const uint32_t e[16], uint32_t mant, uint32_t sign)
 {
     uint32_t out[4];
@@ -261,13 +244,133 @@ __device__ __forceinline__ u32x4 merge_e5m2(const uint32_t e[16], uint32_t mant,
     return u32x4{out[0], out[1], out[2], out[3]};
 }
 
-template <int FMT, int N, int WAVES, bool FAST>
-__global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
+// The item of a batched launch that holds chunk g: a 64-way search, one round trip to memory per level (lane l probes the
+// l-th of 64 evenly spaced items; first_chunk is increasing, so the lanes that pass form a prefix), then the item's 16
+// words by one load of 16 lanes into scalar registers.
+__device__ __forceinline__ WArgs find_item(const BArgs &b, uint64_t g, int lane)
 {
-    constexpr bool COLS = FAST;
-    using C = WCfg<FMT, N, WAVES, COLS>;
+    if (!b.items) return b.single;
+    uint32_t lo = 0, n = b.n_items;
+    while (n > 1) {
+        const uint32_t stride = (n + 63) / 64;
+        const uint32_t at = (uint32_t)lane * stride;
+        const bool pass = at < n && b.items[lo + at].first_chunk <= g;
+        const uint32_t k = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pass));
+        const uint32_t step = k ? (k - 1) * stride : 0;
+        lo += step;
+        n = n - step < stride ? n - step : stride;
+    }
+    static_assert(sizeof(WArgs) == 128, "sixteen words");
+    const uint64_t word = ((const GLOBAL uint64_t *)(b.items + lo))[lane & 15];
+    WArgs a;
+    uint64_t *dst = (uint64_t *)&a;
+#pragma unroll
+    for (int i = 0; i < 16; i++)
+        dst[i] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, i) |
+                 ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), i) << 32);
+    return a;
+}
+
+// contiguous range of a launch's chunks for this workgroup, cut at multiples of 64 or 8 chunks where that leaves every
+// workgroup at least 16 such units, so that the waves of a workgroup share the interleaved groups of the layout
+__device__ __forceinline__ void share_of(const BArgs &b, uint64_t &g, uint64_t &g_end)
+{
+    const uint64_t NWG = gridDim.x, wg = blockIdx.x;
+    const uint64_t unit = b.total_chunks >= NWG * 1024 ? 64 : b.total_chunks >= NWG * 128 ? 8 : 1;
+    const uint64_t units = (b.total_chunks + unit - 1) / unit;
+    g = units * wg / NWG * unit;                      // chunk numbers run through the whole batch
+    g_end = units * (wg + 1) / NWG * unit;
+    if (g_end > b.total_chunks) g_end = b.total_chunks;
+}
+
+// Element layout: piece q of lane l of chunk c starts at element base(c) + q * stride(c) + l * P.
+template <int FMT, int N>
+struct Place {
+    static constexpr uint64_t E = 64ull * N, P = Fmt<FMT>::P;
+    uint64_t group, whole;                            // whole: chunks inside complete groups (group is a power of two)
+    __device__ __forceinline__ Place(const WArgs &a) : group(a.group_chunks), whole((a.n_elem / E) & ~(a.group_chunks - 1)) {}
+    __device__ __forceinline__ uint64_t base(uint64_t c) const
+    {
+        const uint64_t w = c & (group - 1);
+        return c < whole ? (c - w) * E + w * (64 * P) : c * E;
+    }
+    __device__ __forceinline__ uint32_t stride(uint64_t c) const { return c < whole ? (uint32_t)(group * (64 * P)) : (uint32_t)(64 * P); }
+};
+
+struct Meta { uint64_t b0, b1; uint32_t lb; };
+
+__device__ __forceinline__ Meta load_meta(const WArgs &a, uint64_t c, int lane)
+{
+    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(a.d_blob + a.off_chunk_bit);
+    Meta m;
+    m.b0 = chunk_bit[c];
+    m.b1 = chunk_bit[c + 1];
+    m.lb = ((const GLOBAL uint16_t *)(a.d_blob + a.off_lane_bits))[c * 64 + lane];
+    return m;
+}
+
+// A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead) from its two start bits: the same in every
+// lane, so the arithmetic is done once, in scalar registers.
+__device__ __forceinline__ uint64_t span_of(const WArgs &a, const Meta &m, uint64_t &byte0)
+{
+    const uint64_t b0 = uniform64(m.b0), b1 = uniform64(m.b1);
+    uint64_t byte_end = ((b1 + 7) >> 3) + 8;
+    if (byte_end > a.stream_bytes) byte_end = a.stream_bytes;
+    byte0 = (b0 >> 3) & ~15ull;
+    if (byte0 > byte_end) byte0 = byte_end;
+    return byte_end - byte0;
+}
+
+// The careful way, one symbol at a time with windows straight from HBM: chunks whose span does not fit the stage.
+template <int FMT, int N>
+__device__ __forceinline__ void symbol_pass(const WArgs &a, const CodeArrays &ca, uint64_t c, int lane)
+{
+    constexpr int P = Fmt<FMT>::P;
+    const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
+    const GLOBAL uint8_t *stream = blob + a.off_stream, *plane = blob + a.off_plane, *signs = blob + a.off_sign;
+    GLOBAL uint8_t *out = (GLOBAL uint8_t *)a.d_out;
+    const Place<FMT, N> place(a);
+    const Meta m = load_meta(a, c, lane);
+    const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
+    const uint64_t limit = a.stream_bytes * 8 - 64;
+    uint64_t posA = m.b0 + rel, posB = posA + m.lb;
+    const uint64_t e0 = place.base(c) + (uint64_t)lane * P, stride = place.stride(c);
+#pragma unroll 1
+    for (int k = 0; k < N; k++) {
+        const uint64_t e = e0 + (uint64_t)(k / P) * stride + (uint32_t)(k % P);
+        if (e >= a.n_elem) continue;
+        uint32_t en;
+        if (k < N / 2) {
+            if (posA > limit) posA = limit;
+            en = decode_entry<FMT>(global_window<+1>(stream, posA), ca);
+            posA += entry_len<FMT>(en);
+        } else {
+            if (posB > limit) posB = limit;
+            en = decode_entry<FMT>(global_window<-1>(stream, posB), ca);
+            const uint32_t l = entry_len<FMT>(en);
+            posB = posB >= l ? posB - l : 0;
+        }
+        if (FMT == ECFW_FMT_BF16) {
+            const uint32_t swap = (0x3120u >> (4 * (uint32_t)(e & 3))) & 3u;      // 0 2 1 3
+            const uint32_t r = plane[(e & ~3ull) + swap];
+            ((GLOBAL uint16_t *)out)[e] = (uint16_t)(((r & 0x80u) << 8) | (en & 0x7f80u) | (r & 0x7fu));
+        } else {
+            const uint32_t j = (uint32_t)(e & 3), d = (uint32_t)(e >> 2) & 3;
+            const uint32_t mw = ((const GLOBAL uint32_t *)plane)[e / 16];
+            const uint32_t sw = ((const GLOBAL uint16_t *)signs)[e / 16];
+            out[e] = (uint8_t)((((sw >> (e & 15)) & 1u) << 7) | (en & 0x7cu) | ((mw >> (8 * j + 2 * d)) & 3u));
+        }
+    }
+}
+
+// Codes with codewords of more than 12 bits (caps 13 .. 16): one codeword per lookup, the longer ones by a canonical
+// first-code comparison in a rarely taken branch.
+template <int FMT, int N, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
+{
+    using C = WCfg<FMT, N, WAVES>;
     using F = Fmt<FMT>;
-    constexpr int PIECES = C::PIECES, SEGS = C::SEGS, STAGE = C::STAGE, P = F::P, ROWS = C::ROWS;
+    constexpr int PIECES = C::PIECES, SEGS = C::SEGS, STAGE = C::STAGE, P = F::P;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
     uint32_t *s_ticket = (uint32_t *)(smem + C::OFF_TICKET);
@@ -277,58 +380,28 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t stage_off = C::OFF_STAGE + wave * STAGE;
     uint8_t *stage = smem + stage_off;
-    uint8_t *column = smem + C::OFF_COLS + wave * (ROWS * 256) + lane * 4;      // this lane's slot of row 0
-
-    // contiguous range of chunks for this workgroup, cut at multiples of 64 chunks when there is
-    // enough work so that the waves of a workgroup share the interleaved groups of the layout
-    const uint64_t NWG = gridDim.x, wg = blockIdx.x;
-    const uint64_t unit = b.total_chunks >= NWG * 1024 ? 64 : b.total_chunks >= NWG * 128 ? 8 : 1;   // >= 16 units each: shares differ by 1/16 at most
-    const uint64_t units = (b.total_chunks + unit - 1) / unit;
-    uint64_t g = units * wg / NWG * unit;              // chunk numbers run through the whole batch
-    uint64_t g_end = units * (wg + 1) / NWG * unit;
-    if (g_end > b.total_chunks) g_end = b.total_chunks;
+    uint64_t g, g_end;
+    share_of(b, g, g_end);
 
     while (g < g_end) {                                // one round per tensor the range touches (uniform)
-    WArgs a;
-    if (b.items) {
-        uint32_t lo = 0, hi = b.n_items - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (uniform64(b.items[mid].first_chunk) <= g) lo = mid; else hi = mid - 1;
-        }
-        // the item is the same for every lane: say so, or its fields (and all the address arithmetic
-        // on them) would live in vector registers
-        const GLOBAL uint64_t *src = (const GLOBAL uint64_t *)(b.items + lo);
-        uint64_t *dst = (uint64_t *)&a;
-#pragma unroll
-        for (int i = 0; i < (int)(sizeof(WArgs) / 8); i++) dst[i] = uniform64(src[i]);
-    } else {
-        a = b.single;
-    }
+    const WArgs a = find_item(b, g, lane);
     const uint64_t c_begin = g - a.first_chunk;        // chunk numbers inside the tensor
     const uint64_t c_end = g_end - a.first_chunk < a.n_chunks ? g_end - a.first_chunk : a.n_chunks;
+    if (c_end <= c_begin) break;                       // the item table does not cover chunk g: stop rather than spin
     const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
-    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(blob + a.off_chunk_bit);
-    const GLOBAL uint16_t *lane_bits = (const GLOBAL uint16_t *)(blob + a.off_lane_bits);
     const GLOBAL uint8_t *stream = blob + a.off_stream;
     const GLOBAL uint8_t *plane = blob + a.off_plane;
     const GLOBAL uint8_t *signs = blob + a.off_sign;
     GLOBAL uint8_t *out = (GLOBAL uint8_t *)a.d_out;
-
+    const Place<FMT, N> place(a);
 
     if (tid == 0) *s_ticket = 0;
     static_assert(WAVES >= 4, "the code set-up ranks 256 symbols with four wavefronts");
-    build_code<FMT>(blob + a.off_code_len, (uint32_t *)(smem + C::OFF_WCNT), smem + C::OFF_SORTED, (uint32_t *)(smem + C::OFF_CNT),
+    uint32_t my_len = tid < F::A ? (blob + a.off_code_len)[tid] : 0u;
+    if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;
+    build_code<FMT>(my_len, (uint32_t *)(smem + C::OFF_WCNT), smem + C::OFF_SORTED, (uint32_t *)(smem + C::OFF_CNT),
                     (uint32_t *)(smem + C::OFF_FIRST), (uint32_t *)(smem + C::OFF_OFFS), tbl, tid, WAVES * 64);
 
-    const uint64_t E = 64ull * N;
-    const uint64_t whole = a.n_elem / (a.group_chunks * E) * a.group_chunks;     // chunks inside complete groups
-    auto chunk_base = [&](uint64_t c) -> uint64_t {
-        return c < whole ? (c - c % a.group_chunks) * E + (c % a.group_chunks) * (64 * P) : c * E;
-    };
-    auto chunk_stride = [&](uint64_t c) -> uint64_t { return c < whole ? (uint64_t)a.group_chunks * (64 * P) : 64ull * P; };
-
-    struct Meta { uint64_t b0, b1; uint32_t lb; };
     struct Payload {
         u32x4 seg[SEGS];
         u32x2 pl[FMT == ECFW_FMT_BF16 ? PIECES : 1];
@@ -340,24 +413,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         if (lane == 0) t = atomicAdd(s_ticket, 1u);
         return c_begin + uniform32(t);
     };
-    auto load_meta = [&](uint64_t c) {
-        Meta m;
-        m.b0 = chunk_bit[c];
-        m.b1 = chunk_bit[c + 1];
-        m.lb = lane_bits[c * 64 + lane];
-        return m;
-    };
-    auto span_of = [&](const Meta &m, uint64_t &byte0) -> uint64_t {
-        uint64_t byte_end = ((m.b1 + 7) >> 3) + 8;
-        if (byte_end > a.stream_bytes) byte_end = a.stream_bytes;
-        byte0 = (m.b0 >> 3) & ~15ull;
-        if (byte0 > byte_end) byte0 = byte_end;
-        return byte_end - byte0;
-    };
     auto load_payload = [&](uint64_t c, const Meta &m, Payload &p) {
         uint64_t byte0;
-        const uint64_t span = span_of(m, byte0);
-        const uint64_t e0 = chunk_base(c) + (uint64_t)lane * P, stride = chunk_stride(c);
+        const uint64_t span = span_of(a, m, byte0);
+        const uint64_t e0 = place.base(c) + (uint64_t)lane * P, stride = place.stride(c);
 #pragma unroll
         for (int q = 0; q < PIECES; q++) {
             const uint64_t e = e0 + q * stride;
@@ -377,61 +436,24 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         }
     };
 
-    // The careful way, one symbol at a time with windows straight from HBM: the ragged last
-    // chunk, and chunks whose span does not fit the stage (codewords averaging over 8 bits).
-    auto symbol_pass = [&](uint64_t c, const Meta &m) {
-        const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
-        const uint64_t limit = a.stream_bytes * 8 - 64;
-        uint64_t posA = m.b0 + rel, posB = posA + m.lb;
-        const uint64_t e0 = chunk_base(c) + (uint64_t)lane * P, stride = chunk_stride(c);
-#pragma unroll 1
-        for (int k = 0; k < N; k++) {
-            const uint64_t e = e0 + (uint64_t)(k / P) * stride + (uint32_t)(k % P);
-            if (e >= a.n_elem) continue;
-            uint32_t en;
-            if (k < N / 2) {
-                if (posA > limit) posA = limit;
-                en = decode_entry<FMT, false>(global_window<+1>(stream, posA), ca);
-                posA += entry_len<FMT>(en);
-            } else {
-                if (posB > limit) posB = limit;
-                en = decode_entry<FMT, false>(global_window<-1>(stream, posB), ca);
-                const uint32_t l = entry_len<FMT>(en);
-                posB = posB >= l ? posB - l : 0;
-            }
-            if (FMT == ECFW_FMT_BF16) {
-                const uint32_t swap = (0x3120u >> (4 * (uint32_t)(e & 3))) & 3u;      // 0 2 1 3
-                const uint32_t r = plane[(e & ~3ull) + swap];
-                ((GLOBAL uint16_t *)out)[e] = (uint16_t)(((r & 0x80u) << 8) | (en & 0x7f80u) | (r & 0x7fu));
-            } else {
-                const uint32_t j = (uint32_t)(e & 3), d = (uint32_t)(e >> 2) & 3;
-                const uint32_t mw = ((const GLOBAL uint32_t *)plane)[e / 16];
-                const uint32_t sw = ((const GLOBAL uint16_t *)signs)[e / 16];
-                out[e] = (uint8_t)((((sw >> (e & 15)) & 1u) << 7) | (en & 0x7cu) | ((mw >> (8 * j + 2 * d)) & 3u));
-            }
-        }
-    };
-
     uint64_t cur = draw();
     Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
     Payload p_cur;
     if (cur < c_end) {
-        m_cur = load_meta(cur);
+        m_cur = load_meta(a, cur, lane);
         load_payload(cur, m_cur, p_cur);
     }
     uint64_t nxt = draw();
-    if (nxt < c_end) m_next = load_meta(nxt);
+    if (nxt < c_end) m_next = load_meta(a, nxt, lane);
 
     while (cur < c_end) {
         const Meta m = m_cur;
         uint64_t byte0;
-        const uint64_t span = span_of(m, byte0);
+        const uint64_t span = span_of(a, m, byte0);
         const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
         const uint64_t start = uniform64(m.b0);
         const uint32_t first_bit = (uint32_t)(start - byte0 * 8) + rel;           // this lane's first bit, counted from byte0
-        // COLS: rows this lane's bits take (with the dword before and the one after), and the most any lane takes
-        const uint32_t rows_used = COLS ? wave_max(((32 + (first_bit & 31) + m.lb) >> 5) + 2) : 0;
-        const bool careful = span > (uint64_t)STAGE || (cur + 1) * E > a.n_elem || rows_used > (uint32_t)ROWS;    // uniform
+        const bool careful = span > (uint64_t)STAGE || (cur + 1) * place.E > a.n_elem;    // uniform
         if (!careful) {
 #pragma unroll
             for (int k = 0; k < SEGS; k++) {
@@ -452,25 +474,15 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         if (nxt < c_end) {
             load_payload(nxt, m_next, p_cur);
             nn = draw();
-            if (nn < c_end) m_next2 = load_meta(nn);
+            if (nn < c_end) m_next2 = load_meta(a, nn, lane);
         }
         if (careful) {
-            symbol_pass(cur, m);
+            symbol_pass<FMT, N>(a, ca, cur, lane);
         } else {
             uint32_t pa = stage_off * 8 + first_bit - 1;    // one bit off, see pair_step
-            if constexpr (COLS) {
-                // row r of the column = dword (first_bit / 32) - 1 + r of the stage (row 0 of a lane that starts in the
-                // stage's first dword is the spare slot below the stage)
-                const uint8_t *src = stage + ((first_bit >> 5) << 2) - 4;
-#pragma unroll
-                for (int r = 0; r < ROWS; r++)
-                    if ((uint32_t)r < rows_used) *(uint32_t *)(column + r * 256) = *(const uint32_t *)(src + r * 4);
-                pa = 32 + (first_bit & 31) - 1;
-            }
             uint32_t pb = pa + m.lb - 30;
-            const uint8_t *bits = COLS ? column : smem;
-            GLOBAL uint8_t *dst = out + (chunk_base(cur) + (uint64_t)lane * P) * F::ELEM;
-            const uint64_t stride_bytes = chunk_stride(cur) * F::ELEM;
+            GLOBAL uint8_t *dst = out + (place.base(cur) + (uint64_t)lane * P) * F::ELEM;
+            const uint64_t stride_bytes = (uint64_t)place.stride(cur) * F::ELEM;
             // finished pieces wait in registers and leave in bursts of eight (8 KiB per wavefront)
             constexpr int BURST = PIECES / 2 < 4 ? PIECES / 2 : 4;
             static_assert((PIECES / 2) % BURST == 0, "whole bursts");
@@ -483,7 +495,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                     uint32_t eA[P], eB[P];
 #pragma unroll
                     for (int t = 0; t < P / 2; t++)
-                        pair_step<FMT, FAST, COLS>(bits, ca, pa, pb, eA[2 * t], eA[2 * t + 1], eB[2 * t], eB[2 * t + 1]);
+                        pair_step<FMT>(smem, ca, pa, pb, eA[2 * t], eA[2 * t + 1], eB[2 * t], eB[2 * t + 1]);
                     if constexpr (FMT == ECFW_FMT_BF16) {
                         pieceA[i] = merge_bf16(eA, pl[q]);
                         pieceB[i] = merge_bf16(eB, pl[q + PIECES / 2]);
@@ -511,28 +523,401 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
     }
 }
 
-template <int FMT, int N, int WAVES, bool FAST>
-int launch_as(const BArgs &a, uint32_t max_workgroups, hipStream_t stream)
+// ---- codes of at most 12 bits: two codewords per lookup ----
+
+// Pair table, indexed by the next BITS stream bits: the exponent fields of the first two codewords and the bits both
+// consume, 0 if that is more than BITS.
+//  * BF16: 2^13 entries of 32 bits, the fields where an output word has them (bits 7..14 of both halves), i.e. one look-up
+//    per output word; the length in bits 0..4, which the merge masks off.  (2^14 entries: no faster, these launches
+//    are at the memory wall.)
+//  * E5M2: 2^15 entries of 16 bits: fields at 2..6 and 7..11, the length in the upper four bits.  Fifteen bits leave pairs
+//    that do not fit to one step of a wave in six; thirteen, in 32-bit entries of the same size, to two in three.
+// In an entry without a pair the second field's place has the first codeword's length.
+template <int FMT> struct Pairs;
+template <> struct Pairs<ECFW_FMT_E5M2> {
+    typedef uint16_t Entry;
+    static constexpr int BITS = 15, OFF = 1;               // OFF: log2 of an entry's size
+    static constexpr uint32_t SYM1 = 0x7cu;
+    static constexpr int SYM2_AT = 5, FIRST_AT = 7, LEN_AT = 12;       // second field: the single table's entry << SYM2_AT
+    static __device__ __forceinline__ uint32_t len(uint32_t e) { return e >> LEN_AT; }
+};
+template <> struct Pairs<ECFW_FMT_BF16> {
+    typedef uint32_t Entry;
+    static constexpr int BITS = 13, OFF = 2;
+    static constexpr uint32_t SYM1 = 0x7f80u;
+    static constexpr int SYM2_AT = 16, FIRST_AT = 23, LEN_AT = 0;
+    static __device__ __forceinline__ uint32_t len(uint32_t e) { return e & 31u; }
+};
+
+// From the table of single codewords: the codeword at the low 12 bits of the index, then the one that many bits on (zeros
+// shifted in at the top can only lengthen a codeword that does not fit anyway).  A thread keeps the low bits and
+// walks over the others.
+template <int FMT>
+__device__ __forceinline__ void build_pairs(const uint16_t *tbl, typename Pairs<FMT>::Entry *pairs, int tid, int nthreads)
+{
+    using PT = Pairs<FMT>;
+    constexpr uint32_t M = (1u << WTB) - 1;
+    for (uint32_t lo = tid; lo <= M; lo += nthreads) {
+        const uint32_t t1 = tbl[lo], l1 = entry_len<FMT>(t1), base = t1 & PT::SYM1;
+#pragma unroll
+        for (uint32_t hi = 0; hi < 1u << (PT::BITS - WTB); hi++) {
+            const uint32_t t2 = tbl[((lo | (hi << WTB)) >> l1) & M], l2 = entry_len<FMT>(t2), n = l1 + l2;
+            const bool pair = l1 != 0 && l2 != 0 && n <= (uint32_t)PT::BITS;
+            pairs[lo | (hi << WTB)] = (typename PT::Entry)(base + (pair ? ((t2 & PT::SYM1) << PT::SYM2_AT) + (n << PT::LEN_AT) : l1 << PT::FIRST_AT));
+        }
+    }
+    __syncthreads();
+}
+
+// Four codewords of each run: two lookups.  pa = (next bit of the forward run) - OFF and pb = (one past the next bit of the
+// backward run) - (32 - OFF) as LDS bit addresses: the windows read there are the stream bits shifted left by OFF, which
+// masked is the byte offset of a table entry.  A pair that does not fit the table sends the wave through a branch-free
+// second level: the pair's other codeword is the one that many bits on, and the second pair starts where the first
+// now ends; 64-bit windows reach that far.
+template <int FMT>
+__device__ __forceinline__ void quad_step(const uint8_t *smem, const uint8_t *pairs, const uint8_t *tbl, uint32_t &pa, uint32_t &pb, uint32_t &eA1,
+                                          uint32_t &eA2, uint32_t &eB1, uint32_t &eB2)
+{
+    using PT = Pairs<FMT>;
+    auto at = [&](uint32_t w) -> uint32_t { return *(const typename PT::Entry *)(pairs + (w & (((1u << PT::BITS) - 1) << PT::OFF))); };
+    const uint32_t aA = (pa >> 3) & ~3u, aB = (pb >> 3) & ~3u;
+    const uint32_t dA0 = *(const uint32_t *)(smem + aA), dA1 = *(const uint32_t *)(smem + aA + 4);
+    const uint32_t dB0 = *(const uint32_t *)(smem + aB), dB1 = *(const uint32_t *)(smem + aB + 4);
+    const uint32_t wA = __builtin_amdgcn_alignbit(dA1, dA0, pa);
+    const uint32_t wB = __brev(__builtin_amdgcn_alignbit(dB1, dB0, pb));
+    eA1 = at(wA);
+    eB1 = at(wB);
+    uint32_t nA1 = PT::len(eA1), nB1 = PT::len(eB1);
+    eA2 = at(wA >> nA1);                          // OFF + 2 BITS <= 32 valid bits in the window
+    eB2 = at(wB >> nB1);
+    uint32_t nA2 = PT::len(eA2), nB2 = PT::len(eB2);
+    // n1 == 0 makes the second lookup repeat the first, so n2 == 0 covers both pairs of a run
+    if (__builtin_expect(nA2 == 0 || nB2 == 0, 0)) {
+        const uint32_t dA2 = *(const uint32_t *)(smem + aA + 8), dBm = *(const uint32_t *)(smem + aB - 4);
+        const uint64_t WA = wA | ((uint64_t)__builtin_amdgcn_alignbit(dA2, dA1, pa) << 32);
+        const uint64_t WB = wB | ((uint64_t)__brev(__builtin_amdgcn_alignbit(dB0, dBm, pb)) << 32);
+        auto join = [&](uint64_t W, uint32_t from, uint32_t &e, uint32_t &n) {       // e: the entry at bit `from` of W
+            const uint32_t l = (e >> PT::FIRST_AT) & 15u;                            // of use only where n == 0
+            const uint32_t x = *(const uint16_t *)(tbl + (((uint32_t)(W >> (from + l)) >> (PT::OFF - 1)) & WMASK2));
+            if (n == 0) {
+                e = (e & PT::SYM1) | ((x & PT::SYM1) << PT::SYM2_AT);
+                n = l + entry_len<FMT>(x);
+            }
+        };
+        join(WA, 0, eA1, nA1);                    // first pairs: at most 24 bits
+        join(WB, 0, eB1, nB1);
+        eA2 = at((uint32_t)(WA >> nA1));
+        eB2 = at((uint32_t)(WB >> nB1));
+        nA2 = PT::len(eA2);
+        nB2 = PT::len(eB2);
+        join(WA, nA1, eA2, nA2);                  // at most OFF + 24 + 15 + 12 bits from the windows' start
+        join(WB, nB1, eB2, nB2);
+    }
+    pa += nA1 + nA2;
+    pb = pb - nB1 - nB2;
+}
+
+template <int FMT, int N, int WAVES>
+struct PCfg {
+    using F = Fmt<FMT>;
+    static constexpr int PIECES = N / F::P;                 // 16-byte pieces per lane
+    // span of a chunk whose codewords average AVG bits: uniformly random exponent fields still fit
+    static constexpr int AVG = FMT == ECFW_FMT_BF16 ? 8 : 5;
+    static constexpr int STAGE = 8 * AVG * N + 64;
+    static constexpr int SEGS = (STAGE / 16 + 63) / 64;
+    static constexpr int LIST_MAX = 60;                     // oversize chunks remembered per (workgroup, tensor)
+    static constexpr int OFF_PAIRS = 0;
+    static constexpr int OFF_TBL = OFF_PAIRS + ((int)sizeof(typename Pairs<FMT>::Entry) << Pairs<FMT>::BITS);
+    static constexpr int OFF_WCNT = OFF_TBL + (2 << WTB);
+    static constexpr int OFF_SORTED = OFF_WCNT + 320;
+    static constexpr int OFF_CNT = OFF_SORTED + 256;
+    static constexpr int OFF_FIRST = OFF_CNT + 80;
+    static constexpr int OFF_OFFS = OFF_FIRST + 80;
+    static constexpr int OFF_CTL = OFF_OFFS + 80;           // ticket counter, oversize count, tail flag, oversize list
+    static constexpr int OFF_STAGE = OFF_CTL + 16 + 4 * LIST_MAX;
+    // a lane of a ragged last chunk reads up to N / 2 codewords past its bits
+    static constexpr int TOTAL = OFF_STAGE + WAVES * STAGE + N / 2 * WTB / 8 + 32;
+    static_assert(STAGE % 16 == 0 && OFF_STAGE % 16 == 0, "16-byte LDS stores");
+    static_assert(PIECES % 4 == 0, "two runs of whole pieces, in half bursts");
+    static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
+    static_assert(WAVES >= 4, "the code set-up ranks 256 symbols with four wavefronts");
+};
+
+// The loop of the E4M3 decoder (ecf8_decode.hip) over these tables: metadata two chunks ahead, payload one chunk ahead in
+// registers refilled in place, full chunks only, so that the stores of a chunk are unconditional and the wait for a
+// prefetch never drains them; HALF: pieces leave in two bursts, else in one.
+template <int FMT, int N, int WAVES, bool HALF>
+__global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
+{
+    using C = PCfg<FMT, N, WAVES>;
+    using F = Fmt<FMT>;
+    constexpr int PIECES = C::PIECES, SEGS = C::SEGS, STAGE = C::STAGE, P = F::P;
+    constexpr bool BF = FMT == ECFW_FMT_BF16;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
+    uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
+    uint32_t *s_ticket = (uint32_t *)(smem + C::OFF_CTL);
+    uint32_t *s_oversize = s_ticket + 1;                  // number of oversize chunks met in the loop
+    uint32_t *s_tail = s_ticket + 2;                      // set: the ragged last chunk is left to the symbol pass
+    uint32_t *s_list = s_ticket + 4;                      // oversize chunks, relative to c_begin
+    const CodeArrays ca{tbl, smem + C::OFF_SORTED, (const uint32_t *)(smem + C::OFF_CNT),
+                        (const uint32_t *)(smem + C::OFF_FIRST), (const uint32_t *)(smem + C::OFF_OFFS)};
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
+    const uint32_t stage_off = C::OFF_STAGE + wave * STAGE, lane16 = (uint32_t)lane * 16;
+    uint8_t *stage = smem + stage_off;
+    uint64_t g, g_end;
+    share_of(b, g, g_end);
+
+    while (g < g_end) {                                // one round per tensor the range touches (uniform)
+        const WArgs a = find_item(b, g, lane);
+        const uint64_t c_begin = g - a.first_chunk;    // chunk numbers inside the tensor
+        const uint64_t c_end = g_end - a.first_chunk < a.n_chunks ? g_end - a.first_chunk : a.n_chunks;
+        if (c_end <= c_begin) break;                   // the item table does not cover chunk g: stop rather than spin
+        const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
+        const GLOBAL uint8_t *stream = blob + a.off_stream, *plane = blob + a.off_plane, *signs = blob + a.off_sign;
+        GLOBAL uint8_t *out = (GLOBAL uint8_t *)a.d_out;
+        const Place<FMT, N> place(a);
+        const bool ragged_tail = c_end == a.n_chunks && a.n_elem % place.E != 0;
+        const uint64_t fast_end = ragged_tail ? c_end - 1 : c_end;
+
+        __syncthreads();                               // every wave is done with the previous tensor's tables
+        if (tid == 0) { *s_ticket = 2 * WAVES; *s_oversize = 0; *s_tail = 0; }
+
+        auto draw = [&]() -> uint64_t {
+            uint32_t t = 0;
+            if (lane == 0) t = __hip_atomic_fetch_add(s_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            return c_begin + uniform32(t);
+        };
+        // the span's 16-byte units; those beyond it keep what they held
+        auto load_stream = [&](const Meta &m, u32x4 (&seg)[SEGS]) {
+            uint64_t byte0;
+            const uint64_t span64 = span_of(a, m, byte0);
+            const uint32_t span = span64 <= (uint64_t)STAGE ? (uint32_t)span64 : 0u;
+            const GLOBAL uint8_t *sp = stream + byte0;
+#pragma unroll
+            for (int k = 0; k < SEGS; k++) {
+                const uint32_t i = lane16 + 1024 * k;
+                if (i < span) seg[k] = __builtin_nontemporal_load((const GLOBAL u32x4 *)(sp + i));
+            }
+        };
+        // what a piece's elements have besides their exponents: BF16 eight bytes, E5M2 a word of mantissas and 16 signs
+        struct Rest { u32x2 v; };
+        auto load_rest = [&](uint64_t e) {
+            Rest r;
+            if constexpr (BF) r.v = __builtin_nontemporal_load((const GLOBAL u32x2 *)(plane + e));
+            else r.v = u32x2{__builtin_nontemporal_load((const GLOBAL uint32_t *)(plane + e / 4)), __builtin_nontemporal_load((const GLOBAL uint16_t *)(signs + e / 8))};
+            return r;
+        };
+
+        // the first two chunks of a wave are fixed, later ones are drawn
+        uint64_t cur = c_begin + wave, nxt = cur + WAVES, nn = fast_end;
+        Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
+        u32x4 seg[SEGS];
+        Rest rest[PIECES];
+#pragma unroll
+        for (int k = 0; k < SEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < PIECES; q++) rest[q].v = u32x2{0, 0};
+        uint32_t my_len = tid < F::A ? (blob + a.off_code_len)[tid] : 0u;
+        auto load_first = [&](uint64_t c) {
+            m_cur = load_meta(a, c, lane);
+            m_next = m_cur;
+            if (nxt < fast_end) m_next = load_meta(a, nxt, lane);
+            const uint64_t e0 = place.base(c) + (uint64_t)lane * P;
+#pragma unroll
+            for (int q = 0; q < PIECES; q++) rest[q] = load_rest(e0 + q * (uint64_t)place.stride(c));
+            load_stream(m_cur, seg);
+        };
+        // the ragged last chunk goes first, to the wave it would fall to in turn, its stores cut at the tensor's end
+        const bool tail_here = ragged_tail && (uint32_t)wave == (uint32_t)((c_end - 1 - c_begin) % WAVES);
+        if (tail_here) load_first(c_end - 1);
+        else if (cur < fast_end) load_first(cur);
+        if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;
+        build_code<FMT>(my_len, (uint32_t *)(smem + C::OFF_WCNT), smem + C::OFF_SORTED, (uint32_t *)(smem + C::OFF_CNT),
+                        (uint32_t *)(smem + C::OFF_FIRST), (uint32_t *)(smem + C::OFF_OFFS), tbl, tid, WAVES * 64);
+        build_pairs<FMT>(tbl, (typename Pairs<FMT>::Entry *)(smem + C::OFF_PAIRS), tid, WAVES * 64);
+
+        // One chunk from LDS bit `first_bit` on.  The pieces of `rest` give their registers to the chunk whose first
+        // element in this lane is next_e (RELOAD); CUT: the chunk reaches past the tensor's end.
+        auto decode_store = [&](auto reload, auto cut, uint32_t first_bit, uint32_t lb, uint64_t e0, uint32_t stride, uint64_t next_e,
+                                uint32_t next_stride) {
+            constexpr bool RELOAD = decltype(reload)::value, CUT = decltype(cut)::value;
+            uint32_t pa = first_bit - Pairs<FMT>::OFF, pb = first_bit + lb - (32 - Pairs<FMT>::OFF);                 // see quad_step
+            auto piece = [&](const uint32_t (&x)[4], const Rest &r) {
+                u32x4 d;
+                if constexpr (BF) {
+                    d.x = bit_sel(0x7f807f80u, x[0], bit_sel(0x80008000u, r.v.x << 8, r.v.x));
+                    d.y = bit_sel(0x7f807f80u, x[1], bit_sel(0x80008000u, r.v.x, r.v.x >> 8));
+                    d.z = bit_sel(0x7f807f80u, x[2], bit_sel(0x80008000u, r.v.y << 8, r.v.y));
+                    d.w = bit_sel(0x7f807f80u, x[3], bit_sel(0x80008000u, r.v.y, r.v.y >> 8));
+                } else {
+                    uint32_t o[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        // four sign bits -> bit 0 of each byte (the partial products do not overlap), then up to bit 7
+                        const uint32_t sp = __umul24(__builtin_amdgcn_ubfe(r.v.y, 4 * k, 4), 0x204081u) << 7;
+                        o[k] = bit_sel(0x7c7c7c7cu, x[k], bit_sel(0x80808080u, sp, r.v.x >> (2 * k)));
+                    }
+                    d = u32x4{o[0], o[1], o[2], o[3]};
+                }
+                return d;
+            };
+            auto store_at = [&](u32x4 v, uint64_t e) {
+                GLOBAL uint8_t *to = out + e * F::ELEM;
+                if (!CUT || e + P <= a.n_elem) {
+                    __builtin_nontemporal_store(v, (GLOBAL u32x4 *)to);
+                    return;
+                }
+#pragma unroll 1
+                for (uint64_t i = e; i < a.n_elem; i++, to += F::ELEM) {
+                    if constexpr (BF) *(GLOBAL uint16_t *)to = (uint16_t)v.x;
+                    else *to = (uint8_t)v.x;
+                    v.x = __builtin_amdgcn_alignbit(v.y, v.x, 8 * F::ELEM);
+                    v.y = __builtin_amdgcn_alignbit(v.z, v.y, 8 * F::ELEM);
+                    v.z = __builtin_amdgcn_alignbit(v.w, v.z, 8 * F::ELEM);
+                    v.w >>= 8 * F::ELEM;
+                }
+            };
+            constexpr int H = PIECES / 2, BURST = CUT ? 1 : HALF ? (H < 2 ? H : 2) : H;
+#pragma unroll
+            for (int q0 = 0; q0 < H; q0 += BURST) {
+                u32x4 oA[BURST], oB[BURST];
+#pragma unroll
+                for (int i = 0; i < BURST; i++) {
+                    const int q = q0 + i;
+                    uint32_t xA[4], xB[4];
+#pragma unroll
+                    for (int t = 0; t < (BF ? 2 : 4); t++) {
+                        uint32_t eA1, eA2, eB1, eB2;
+                        quad_step<FMT>(smem, smem + C::OFF_PAIRS, smem + C::OFF_TBL, pa, pb, eA1, eA2, eB1, eB2);
+                        if constexpr (BF) {
+                            xA[2 * t] = eA1; xA[2 * t + 1] = eA2;
+                            xB[2 * t] = eB1; xB[2 * t + 1] = eB2;
+                        } else {
+                            const uint32_t tA = __builtin_amdgcn_perm(eA2, eA1, 0x05040100u), tB = __builtin_amdgcn_perm(eB2, eB1, 0x05040100u);
+                            xA[t] = bit_sel(0x007c007cu, tA, tA << 3);
+                            xB[t] = bit_sel(0x007c007cu, tB, tB << 3);
+                        }
+                    }
+                    oA[i] = piece(xA, rest[q]);
+                    oB[i] = piece(xB, rest[q + H]);
+                    if constexpr (RELOAD) {
+                        rest[q] = load_rest(next_e + q * (uint64_t)next_stride);
+                        rest[q + H] = load_rest(next_e + (q + H) * (uint64_t)next_stride);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < BURST; i++) store_at(oA[i], e0 + (q0 + i) * (uint64_t)stride);
+#pragma unroll
+                for (int i = 0; i < BURST; i++) store_at(oB[i], e0 + (q0 + i + H) * (uint64_t)stride);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+
+        if (tail_here) {
+            uint64_t byte0;
+            const uint64_t span64 = span_of(a, m_cur, byte0);
+            if (span64 <= (uint64_t)STAGE) {
+                const uint32_t rel = wave_incl_scan(m_cur.lb) - m_cur.lb;
+#pragma unroll
+                for (int k = 0; k < SEGS; k++)
+                    if (lane16 + 1024 * k < (uint32_t)span64) *(u32x4 *)(stage + lane16 + 1024 * k) = seg[k];
+                decode_store(std::false_type{}, std::true_type{}, stage_off * 8 + (uint32_t)(uniform64(m_cur.b0) - byte0 * 8) + rel, m_cur.lb,
+                             place.base(c_end - 1) + (uint64_t)lane * P, place.stride(c_end - 1), 0, 0);
+            } else if (lane == 0) {
+                *s_tail = 1;
+            }
+            if (cur < fast_end) load_first(cur);
+        }
+        if (cur < fast_end) {
+            // drain the prologue's loads here (vmcnt(0)), so that the wait at the loop head is decided by the back edge
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            for (;;) {
+                uint64_t byte0;
+                const uint64_t span64 = span_of(a, m_cur, byte0);
+                const bool staged = __builtin_amdgcn_readfirstlane((uint32_t)(span64 <= (uint64_t)STAGE)) != 0;
+                const uint32_t rel = wave_incl_scan(m_cur.lb) - m_cur.lb;
+                const uint32_t bit_in = (uint32_t)(uniform64(m_cur.b0) - byte0 * 8) + rel;     // this lane's first bit from byte0
+#pragma unroll
+                for (int k = 0; k < SEGS; k++)
+                    if (lane16 + 1024 * k < (uint32_t)STAGE) *(u32x4 *)(stage + lane16 + 1024 * k) = seg[k];
+                const bool has_next = nxt < fast_end;
+                Meta m_next2 = m_next;
+                if (has_next) {
+                    load_stream(m_next, seg);
+                    nn = draw();
+                    if (nn < fast_end) m_next2 = load_meta(a, nn, lane);
+                }
+                if (!staged && lane == 0) {
+                    const uint32_t at = __hip_atomic_fetch_add(s_oversize, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = (uint32_t)(cur - c_begin);
+                }
+                // a chunk that was not staged decodes stale bits (redone after the loop), its runs pinned to the stage's start
+                const uint64_t c_rest = has_next ? nxt : cur;          // after the last chunk: its own rest again, not a branch
+                decode_store(std::true_type{}, std::false_type{}, stage_off * 8 + (staged ? bit_in : 64u), staged ? m_cur.lb : 0u,
+                             place.base(cur) + (uint64_t)lane * P, place.stride(cur), place.base(c_rest) + (uint64_t)lane * P, place.stride(c_rest));
+                if (!has_next) break;
+                m_cur = m_next;
+                m_next = m_next2;
+                cur = nxt;
+                nxt = nn;
+            }
+        }
+        // Chunks whose span did not fit a stage, and a ragged last one of that kind: symbol by symbol.  The loop stored
+        // garbage for them, from whichever wave drew them: every such store lands before any store of this pass.
+        __syncthreads();
+        const uint32_t n_over = *s_oversize;
+        const bool tail_left = *s_tail != 0;
+        if (n_over != 0 || tail_left) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __syncthreads();
+            const bool listed = n_over <= (uint32_t)C::LIST_MAX;
+            const uint64_t count = listed ? n_over + (tail_left ? 1u : 0u) : c_end - c_begin;
+#pragma unroll 1
+            for (uint64_t k = wave; k < count; k += WAVES) {
+                const uint64_t c = !listed ? c_begin + k : k < n_over ? c_begin + uniform32(s_list[k]) : c_end - 1;
+                if (!listed) {
+                    uint64_t byte0;
+                    const bool over = c >= fast_end ? tail_left : span_of(a, load_meta(a, c, lane), byte0) > (uint64_t)STAGE;
+                    if (!__builtin_amdgcn_readfirstlane((uint32_t)over)) continue;
+                }
+                symbol_pass<FMT, N>(a, ca, c, lane);
+            }
+        }
+        g = a.first_chunk + c_end;
+    }
+}
+
+template <int WAVES, class K>
+int launch_as(K kernel, const BArgs &a, uint32_t max_workgroups, hipStream_t stream)
 {
     int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
     uint64_t grid = (uint64_t)cus;
     if (max_workgroups && max_workgroups < grid) grid = max_workgroups;
     if (grid > a.total_chunks) grid = a.total_chunks;
-    hipLaunchKernelGGL((ecfw_decode_kernel<FMT, N, WAVES, FAST>), dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, a);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 
 template <int FMT>
-int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, hipStream_t stream)
+int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, hipStream_t s)
 {
-    // the branch-free kernels at N = 64 need under 128 registers: 16 wavefronts hide more of the LDS latency
-    if (N == 64 && fast) return launch_as<FMT, 64, 16, true>(a, max_workgroups, stream);
-    if (N == 64) return launch_as<FMT, 64, 8, false>(a, max_workgroups, stream);
-    // E5M2 at N = 128 needs under 170 registers: three wavefronts per SIMD
-    if constexpr (FMT == ECFW_FMT_E5M2)
-        if (fast) return launch_as<FMT, 128, 12, true>(a, max_workgroups, stream);
-    return fast ? launch_as<FMT, 128, 8, true>(a, max_workgroups, stream) : launch_as<FMT, 128, 8, false>(a, max_workgroups, stream);
+    if (!fast)
+        return N == 64 ? launch_as<8>(ecfw_long_decode_kernel<FMT, 64, 8>, a, max_workgroups, s)
+                       : launch_as<8>(ecfw_long_decode_kernel<FMT, 128, 8>, a, max_workgroups, s);
+    // Waves per workgroup and bursts, measured on a layer of seven matrices (218 M elements):
+    //   BF16, N = 64   8 waves, a chunk's pieces in one burst 139.0 us; 10 waves 139.6, 12 waves 140.6, 6 waves 150.7; in two
+    //                  bursts 8 waves 144.8, 12 waves 145, 16 waves 149
+    //   E5M2, N = 128  12 waves, two bursts 90.0 us; 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
+    // i.e. BF16 is at the memory wall and wants its stores together, E5M2 wants the waves to hide its look-ups.
+    if constexpr (FMT == ECFW_FMT_BF16)
+        return N == 64 ? launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, false>, a, max_workgroups, s)
+                       : launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, true>, a, max_workgroups, s);
+    else
+        return N == 64 ? launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, false>, a, max_workgroups, s)
+                       : launch_as<12>(ecfw_decode_kernel<FMT, 128, 12, true>, a, max_workgroups, s);
 }
 
 int launch(const BArgs &a, uint32_t fmt, uint32_t N, uint32_t max_code_len, uint32_t max_workgroups, void *stream)

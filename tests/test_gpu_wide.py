@@ -127,6 +127,36 @@ def test_islands_of_long_codes(orc, lane_syms):
     assert (np.diff(cb.astype(np.int64)) // 8 > 64 * lane_syms * 12 // 8 + 64).sum() == 4     # the islands are oversize
 
 
+@pytest.mark.parametrize("cap", [8, 12])
+@pytest.mark.parametrize("lane_syms", [64, 128])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_pairs_of_codewords_that_do_not_fit_the_table(fmt, lane_syms, cap):
+    """Four frequent exponents and twenty rare ones whose codewords crowd under the cap: pairs of up to 24 bits in the
+    first and in the second lookup of a step, in both runs, strewn and in one stretch of 70 chunks.  Under the cap of 12 the
+    stretch's chunks do not fit a wave's stage, and they are more than one workgroup keeps a list of.  The tensor ends inside a piece."""
+    rng = np.random.default_rng(cap + lane_syms)
+    chunk = 64 * lane_syms
+    n = chunk * 2800 + 8 * 64 + 3
+    s = rng.choice(4, size=n, p=[0.4, 0.3, 0.2, 0.1])
+    rare = rng.random(n) < 0.003
+    s[rare] = rng.integers(4, 24, int(rare.sum()))
+    s[n // 3:n // 3 + 70 * chunk] = rng.integers(4, 24, 70 * chunk)
+    if fmt == BF16:
+        x = ((s + 100).astype(np.uint16) << 7) | rng.integers(0, 128, n).astype(np.uint16) | (rng.integers(0, 2, n).astype(np.uint16) << 15)
+    else:
+        x = ((s + 4).astype(np.uint8) << 2) | rng.integers(0, 4, n).astype(np.uint8) | (rng.integers(0, 2, n).astype(np.uint8) << 7)
+    for group, workgroups in ((1, 1), (32, 0)):
+        blob = ecfw.ecfw_encode(fmt, x, 1, n, lane_syms=lane_syms, max_code_len=cap, group_chunks=group)
+        h = blob.header
+        starts = blob.numpy()[h.off_chunk_bit:h.off_chunk_bit + 8 * (h.n_chunks + 1)].view(np.uint64).astype(np.int64)
+        stage = (8 if fmt == BF16 else 5) * 8 * lane_syms + 64
+        assert cap == 8 or group != 1 or int((np.diff(starts) // 8 > stage).sum()) > 60
+        assert h.max_code_len <= cap
+        got, guards = _gpu_decode_guarded(blob, max_workgroups=workgroups)
+        assert guards
+        assert np.array_equal(got, x)                      # the codec's definition
+
+
 @pytest.mark.parametrize("fmt", [E5M2, BF16])
 def test_few_workgroups_and_caller_buffer(orc, fmt):
     x = _rand_elems(fmt, 64 * 128 * 50 + 9, 3)
