@@ -207,10 +207,16 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             const uint64_t w = cl & (group - 1);
             return cl < grouped ? (cl - w) * (64ull * N) + w * 1024 : cl * (64ull * N);
         };
-        auto chunk_stride = [&](uint64_t cl) -> uint32_t {
+        // What a lane stores (and the nibbles it merges): piece q at chunk_base + lane_off + q * chunk_stride.  That is where the
+        // lane's symbols are, except in the TILED kernel, whose decoded exponents change lanes first: there a lane
+        // holds 16 columns of row 4 q + l / 16 of the block.
+        typedef typename std::conditional<TILED, uint64_t, uint32_t>::type stride_t;
+        auto chunk_stride = [&](uint64_t cl) -> stride_t {
+            if constexpr (TILED) return 4 * tcols;
             return tcols ? 64u : cl < grouped ? (uint32_t)group * 1024u : 1024u;
         };
-        const uint64_t lane_off = tcols ? (uint64_t)(lane & 15) * tcols + (uint64_t)(lane >> 4) * 16 : (uint64_t)lane * 16;
+        const uint64_t symbol_off = tcols ? (uint64_t)(lane & 15) * tcols + (uint64_t)(lane >> 4) * 16 : (uint64_t)lane * 16;
+        const uint64_t lane_off = TILED ? (uint64_t)(lane >> 4) * tcols + (uint64_t)(lane & 15) * 16 : symbol_off;
 
         __syncthreads(); // every wave is done with the previous tensor's table and its scratch
         // the first two chunks of a wave are fixed (c + wave, c + WAVES + wave); later ones are drawn
@@ -305,7 +311,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             if (cg1 < fast_end) m_next = load_meta(cg1 - first_chunk);
             load_stream(m_cur, seg);
             const GLOBAL uint8_t *pp = plane_of(ck - first_chunk);
-            const uint32_t pstride = chunk_stride(ck - first_chunk) / 2;
+            const stride_t pstride = chunk_stride(ck - first_chunk) / 2;
 #pragma unroll
             for (int j = 0; j < C::PIECES; j++) pl[j] = LD_STREAM((const GLOBAL u32x2 *)(pp + j * pstride));
         };
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // registers, once merged, to the same piece of the chunk whose plane starts at next_pl.  With `cut` set the
         // chunk is a ragged last one: its stores end where the tensor does.
         auto decode_store = [&](auto reload, auto cut, uint32_t first_bit, uint32_t lb, u32x2 (&pl)[C::PIECES], GLOBAL uint8_t *out_c,
-                                uint32_t ostride, const GLOBAL uint8_t *next_pl, uint32_t next_pstride) {
+                                stride_t ostride, const GLOBAL uint8_t *next_pl, stride_t next_pstride) {
             constexpr bool RELOAD = decltype(reload)::value, CUT = decltype(cut)::value;
             auto store_cut = [&](u32x4 v, uint32_t at) {
                 const uint64_t el = (uint64_t)(out_c - out) + at;
@@ -369,6 +375,11 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                     if constexpr (PAIRFIT) quad_step_held(smem, tbl, runs, dwA[t], dwB[t]);
                     else quad_step2<PAIRFIT, LONG>(smem, tbl, s_len, s_code, bpA, bpB, dwA[t], dwB[t]);
                 }
+                if constexpr (TILED) {      // exponents only; merged after they have changed lanes
+                    ov[Q] = u32x4{dwA[0], dwA[1], dwA[2], dwA[3]};
+                    ov[Q + C::PIECES / 2] = u32x4{dwB[0], dwB[1], dwB[2], dwB[3]};
+                    continue;
+                }
                 const u32x4 oA = merge_piece(dwA, pl[Q]);
                 const u32x4 oB = merge_piece(dwB, pl[Q + C::PIECES / 2]);
                 if constexpr (RELOAD) {
@@ -400,20 +411,25 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             }
             if constexpr (CUT) {
             } else if constexpr (TILED) {
-                // Row-tiled blob: lane (r = l % 16, g = l / 16) holds columns 64 Q + 16 g of row r, so a store of
-                // piece Q as it is would cover 16 rows x 64 bytes.  Through the wave's tile the pieces become whole
-                // row segments: store j covers rows 4 j .. 4 j + 3 x 256 bytes, lane l row 4 j + l / 16, columns
-                // 16 (l % 16).  The 16-byte units of a row are swizzled by the row number against bank conflicts.
+                // Row-tiled blob: lane (r = l % 16, g = l / 16) holds the exponents of columns 64 Q + 16 g of row r; stored
+                // as they are a piece would cover 16 rows x 64 bytes, and its nibbles 16 rows x 32.  Through the wave's
+                // tile the exponents become whole row segments (lane l: row 4 j + l / 16, columns 16 (l % 16)), are merged
+                // with nibbles that were loaded in that order (4 rows x 128 bytes per instruction) and leave as 4 rows x 256
+                // bytes.  The 16-byte units of a row are swizzled by the row number against bank conflicts.
                 uint8_t *tile = smem + C::OFF_TILE + wave * C::TILE_BYTES;
                 const uint32_t r = lane & 15, g = lane >> 4;
 #pragma unroll
                 for (int Q = 0; Q < C::PIECES; Q++) *(u32x4 *)(tile + r * 256 + (((4 * Q + g) ^ r) & 15) * 16) = ov[Q];
-                GLOBAL uint8_t *out_t = out_c - lane_off + (uint64_t)g * tcols + r * 16;       // row l / 16, columns 16 (l % 16)
 #pragma unroll
-                for (int j = 0; j < 4; j++) ov[j] = *(const u32x4 *)(tile + (4 * j + g) * 256 + ((r ^ (4 * j + g)) & 15) * 16);
+                for (int j = 0; j < 4; j++) {
+                    const u32x4 e = *(const u32x4 *)(tile + (4 * j + g) * 256 + ((r ^ (4 * j + g)) & 15) * 16);
+                    const uint32_t dw[4] = {e.x, e.y, e.z, e.w};
+                    ov[j] = merge_piece(dw, pl[j]);
+                    if constexpr (RELOAD) pl[j] = LD_STREAM((const GLOBAL u32x2 *)(next_pl + j * next_pstride));
+                }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int j = 0; j < 4; j++) ST_STREAM(ov[j], (GLOBAL u32x4 *)(out_t + (uint64_t)(4 * j) * tcols));
+                for (int j = 0; j < 4; j++) ST_STREAM(ov[j], (GLOBAL u32x4 *)(out_c + j * ostride));
                 __builtin_amdgcn_sched_barrier(0);
             } else if constexpr (BURST == 1) {
                 __builtin_amdgcn_sched_barrier(0);   // keep the stores together, after the decode
@@ -453,7 +469,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             for (;;) {
                 const uint64_t cl = cg - first_chunk;            // chunk index inside the tensor
                 GLOBAL uint8_t *out_c = out + chunk_base(cl) + lane_off;   // this lane's piece 0
-                const uint32_t ostride = chunk_stride(cl);
+                const stride_t ostride = chunk_stride(cl);
                 const uint64_t b0 = uniform64(m_cur.b0);
                 uint64_t byte0;
                 const uint64_t span64 = span_of(m_cur, byte0);
@@ -534,7 +550,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                         if (span <= (uint64_t)C::SLOT) {          // else: a corrupt blob, left as decoded in the loop
                             u32x2 pl_s[C::PIECES];
                             const GLOBAL uint8_t *plane_c = plane_of(cl);
-                            const uint32_t pstride = chunk_stride(cl) / 2;
+                            const stride_t pstride = chunk_stride(cl) / 2;
 #pragma unroll
                             for (int j = 0; j < C::PIECES; j++) pl_s[j] = *(const GLOBAL u32x2 *)(plane_c + j * pstride);
                             const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
@@ -562,14 +578,14 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 const bool redo = (tail_left && cg2 >= fast_end) || (span64 > (uint64_t)C::STAGE && (PAIRFIT || n_over > (uint32_t)C::LIST_MAX));
                 if (!__builtin_amdgcn_readfirstlane((uint32_t)redo)) continue;
                 const uint64_t elem0 = chunk_base(cl);
-                const uint32_t estride = chunk_stride(cl);
+                const uint64_t estride = TILED ? 64 : chunk_stride(cl);
                 const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
                 const GLOBAL uint8_t *sp = stream + byte0;
                 uint64_t bA = (m.b0 - byte0 * 8) + rel;   // forward run: next bit
                 uint64_t bB = bA + m.lb;                  // backward run: one past the next bit
 #pragma unroll 1
                 for (int Q = 0; Q < C::PIECES; Q++) {
-                    const uint64_t o = elem0 + (uint64_t)Q * estride + lane_off;
+                    const uint64_t o = elem0 + (uint64_t)Q * estride + symbol_off;
                     const bool fwd = Q < C::PIECES / 2;
 #pragma unroll 1
                     for (uint32_t i = 0; i < 16 && o + i < n_elem; i++) {
@@ -620,8 +636,11 @@ int dispatch(const KArgs &a, uint32_t lane_syms, hipStream_t s)
         if (pairfit) return launch_as<32, 16, true>(a, 1, s);
         return lng ? launch_as<32, 16, false, false, true, 0>(a, 1, s) : launch_as<32, 16, false, false, false, 0>(a, 1, s);
     case 64:
-        // the fused GEMM's blobs (row-tiled, capped codes): decoded chunks leave as whole row segments
-        if (pairfit && a.row_tiled) return launch_as<64, 16, true, true>(a, 1, s);
+        // the fused GEMM's blobs (row-tiled, capped codes): decoded chunks leave as whole row segments.  8 waves: a layer of
+        // seven matrices (418 MB) takes 87.4 us, with 10 waves 88.5, 12 88.8, 16 91.5 (merged before the exponents
+        // changed lanes, nibbles read as 16 rows x 32 bytes: 16 waves 108); in the linear layout without groups, which
+        // this layout cannot have, 84
+        if (pairfit && a.row_tiled) return launch_as<64, 8, true, true>(a, 1, s);
         if (pairfit) return launch_as<64, 12, true>(a, 1, s);
         return lng ? launch_as<64, 12, false, false, true, 1>(a, 1, s) : launch_as<64, 12, false, false, false, 1>(a, 1, s);
     case 128:
