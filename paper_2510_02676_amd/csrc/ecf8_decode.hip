@@ -304,7 +304,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // its stores cut at the tensor's end.  (Read symbol by symbol from HBM after the loop it was a chain of N
         // round trips at the end of every such launch: 2047 x 2049 weights 55.7 -> 11.1 us, 8 x 256 22.8 -> 9.1 us.)
         // Not inside the loop: a store under a condition there would make the wait for a prefetch drain the stores.
-        const bool tail_here = fast_end != seg_end && (uint32_t)wave == (uint32_t)((seg_end - 1 - c) % WAVES);
+        const bool tail_here = fast_end != seg_end && (uint32_t)wave == (uint32_t)(seg_end - 1 - c) % WAVES;
         auto load_first = [&](uint64_t ck) {
             m_cur = load_meta(ck - first_chunk);
             m_next = m_cur;

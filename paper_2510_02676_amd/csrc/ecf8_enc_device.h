@@ -14,24 +14,55 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint64_t dst, uint64_t b
         p[i] = u32x4{0, 0, 0, 0};
 }
 
-// In-place inclusive prefix sum of chunk_bit[1 .. n_chunks], one workgroup, 8192 chunks a round: row k of a round is 1024
-// chunks side by side, scanned by the waves; the 128 (row, wave) totals are scanned once more by every wave.  Sums of a
-// round fit 32 bits (chunks of at most 2^17 bits), the carry has 64.  Where a chunk starts inside a dword of the stream,
-// that dword holds bits of two chunks or more: it is zeroed here, and the packing kernels OR into it.
-// 7168 chunks: 7.0 us (1024 a round 6.4 .. 11.8 us; eight neighbouring chunks per thread, uncoalesced, 11.5 us).
+// chunk_bit[1 .. n_chunks] on the way from chunk totals to stream positions.  The metadata kernels leave a chunk's total
+// (at most 2^17 bits) in the upper bits of its entry; the prefix sum puts the position below it.
+//  * Up to SLICED chunks, a workgroup per 1024 of them: each adds up the totals in front of its slice by itself (512 KiB at the
+//    most) and scans the slice.  No workgroup waits for another: an entry reads the same from before and after its
+//    update, because the total stays in it, and the packing kernels mask it off and write the plain position back.
+//  * Above that one workgroup goes through all of them, 8192 a round: row k of a round is 1024 chunks side by side, scanned
+//    by the waves, and the 128 (row, wave) totals are scanned once more by every wave.
+// Where a chunk starts inside a dword of the stream, that dword holds bits of two chunks or more: it is zeroed here, and the
+// packing kernels OR into it.  (One workgroup for everything: 7.0 us for 7168 chunks and 14 for 14336, half of it these
+// scattered stores from one compute unit; sliced 3 .. 4 us.)
+constexpr int TOTAL_AT = 46;
+constexpr uint64_t SLICED = 1 << 16;
+__host__ __device__ inline uint64_t position_mask(uint64_t n_chunks) { return n_chunks <= SLICED ? (1ull << TOTAL_AT) - 1 : ~0ull; }
+
 __global__ __launch_bounds__(1024) void scan_kernel(uint64_t chunk_bit_, uint64_t n_chunks, uint64_t stream_)
 {
     constexpr int ROWS = 8;
     __shared__ uint32_t totals[2][ROWS * 16];
+    __shared__ uint64_t before_s[16];
     GLOBAL uint64_t *cb = (GLOBAL uint64_t *)chunk_bit_;
     GLOBAL uint32_t *stream = (GLOBAL uint32_t *)stream_;
     const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
+    if (n_chunks <= SLICED) {
+        const uint64_t first = 1 + 1024ull * blockIdx.x, i = first + tid;
+        const uint32_t mine = i <= n_chunks ? (uint32_t)(cb[i] >> TOTAL_AT) : 0u;
+        uint32_t front = 0;                               // at most 64 totals
+#pragma unroll 8
+        for (uint32_t k = 0; k < blockIdx.x; k++) front += (uint32_t)(cb[1 + tid + 1024ull * k] >> TOTAL_AT);
+        const uint32_t incl = wave_incl_scan(mine), f = wave_incl_scan(front);      // 64 x 64 totals: 2^29
+        if (lane == 63) {
+            totals[0][wave] = incl;
+            before_s[wave] = f;
+        }
+        __syncthreads();
+        uint64_t at = incl;
+#pragma unroll
+        for (int w = 0; w < 16; w++) at += before_s[w] + (w < wave ? totals[0][w] : 0u);
+        if (i <= n_chunks) {
+            cb[i] = at | ((uint64_t)mine << TOTAL_AT);
+            if (i < n_chunks && (at & 31)) stream[at >> 5] = 0;
+        }
+        return;
+    }
     uint64_t carry = 0;
     int parity = 0;
     for (uint64_t base = 1; base <= n_chunks; base += 1024 * ROWS, parity ^= 1) {
         uint32_t v[ROWS];
 #pragma unroll
-        for (int k = 0; k < ROWS; k++) v[k] = base + 1024 * k + tid <= n_chunks ? (uint32_t)cb[base + 1024 * k + tid] : 0u;
+        for (int k = 0; k < ROWS; k++) v[k] = base + 1024 * k + tid <= n_chunks ? (uint32_t)(cb[base + 1024 * k + tid] >> TOTAL_AT) : 0u;
 #pragma unroll
         for (int k = 0; k < ROWS; k++) {
             v[k] = wave_incl_scan(v[k]);
@@ -54,6 +85,20 @@ __global__ __launch_bounds__(1024) void scan_kernel(uint64_t chunk_bit_, uint64_
         }
         carry += (uint32_t)__builtin_amdgcn_readlane((int)s1, 63);
     }
+}
+
+inline void launch_scan(uint64_t chunk_bit, uint64_t n_chunks, uint64_t stream, hipStream_t s)
+{
+    const uint32_t grid = n_chunks <= SLICED ? (uint32_t)((n_chunks + 1023) / 1024) : 1u;
+    hipLaunchKernelGGL(scan_kernel, dim3(grid), dim3(1024), 0, s, chunk_bit, n_chunks, stream);
+}
+
+// The positions of chunk c's first and last bit, the latter written back plain.
+__device__ __forceinline__ void chunk_positions(GLOBAL uint64_t *cb, uint64_t c, uint64_t mask, int lane, uint64_t &b0, uint64_t &b1)
+{
+    b0 = uniform64(cb[c]) & mask;
+    b1 = uniform64(cb[c + 1]) & mask;
+    if (~mask && lane == 0) cb[c + 1] = b1;
 }
 
 // Where chunk c's pieces lie: piece q of lane l starts at element base + q * stride + lane_off(l) (see the container's layouts).

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void meta_kernel(EncArgs a, ecf8_header h, uin
     }
     ((GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane] = (uint16_t)lb;
     const uint32_t total = wave_incl_scan(lb);
-    if (lane == 63) ((GLOBAL uint64_t *)(a.blob + a.off_cb))[c + 1] = total;
+    if (lane == 63) ((GLOBAL uint64_t *)(a.blob + a.off_cb))[c + 1] = (uint64_t)total << TOTAL_AT;
 }
 
 // Stream: one wave per chunk.  A lane's bits are one string, the forward run's codewords in order and then the backward
@@ -232,13 +232,15 @@ __global__ __launch_bounds__(256) void pack_kernel(EncArgs a)
     }
     __syncthreads();
     uint32_t *stage = stage_all[wave];
-    const GLOBAL uint64_t *cb = (const GLOBAL uint64_t *)(a.blob + a.off_cb);
+    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(a.blob + a.off_cb);
+    const uint64_t mask = position_mask(a.n_chunks);
     for (uint64_t c = (uint64_t)blockIdx.x * 4 + wave; c < a.n_chunks; c += (uint64_t)gridDim.x * 4) {       // the same for the whole wave
         const bool whole = (c + 1) * (64ull * N) <= a.n;
         const ChunkPlace p = place_of<N>(a, c, lane);
         u32x4 v[N / 16];
         load_pieces<N>(a, p, whole, v);
-        const uint64_t b0 = uniform64(cb[c]), b1 = uniform64(cb[c + 1]);
+        uint64_t b0, b1;
+        chunk_positions(cb, c, mask, lane, b0, b1);
         const uint32_t lb = ((const GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane];
         const uint32_t n_units = (uint32_t)(((b1 + 127) >> 7) - (b0 >> 7));
         for (uint32_t u = lane; u < n_units && u < (uint32_t)STAGE / 4; u += 64) *(u32x4 *)(stage + 4 * u) = u32x4{0, 0, 0, 0};
@@ -301,7 +303,7 @@ int launch_pass2(const EncArgs &a, const ecf8_header &h, uint32_t lmax, hipStrea
     const uint32_t parts = h.table_bits ? 64 : 1;
     const uint64_t chunk_blocks = (h.n_chunks + 3) / 4;
     hipLaunchKernelGGL(meta_kernel<N>, dim3((uint32_t)chunk_blocks + parts), dim3(256), 0, s, a, h, parts);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a.blob + a.off_cb, h.n_chunks, a.blob + a.off_st);
+    launch_scan(a.blob + a.off_cb, h.n_chunks, a.blob + a.off_st, s);
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);
     if (lmax <= 7) hipLaunchKernelGGL((pack_kernel<N, true>), dim3(pg), dim3(256), 0, s, a);

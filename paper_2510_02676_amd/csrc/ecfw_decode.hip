@@ -729,7 +729,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
             load_stream(m_cur, seg);
         };
         // the ragged last chunk goes first, to the wave it would fall to in turn, its stores cut at the tensor's end
-        const bool tail_here = ragged_tail && (uint32_t)wave == (uint32_t)((c_end - 1 - c_begin) % WAVES);
+        const bool tail_here = ragged_tail && (uint32_t)wave == (uint32_t)(c_end - 1 - c_begin) % WAVES;
         if (tail_here) load_first(c_end - 1);
         else if (cur < fast_end) load_first(cur);
         if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;

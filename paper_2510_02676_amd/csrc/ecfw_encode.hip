@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void w_meta_kernel(WEncArgs a, WHeadArgs ha)
     }
     ((GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane] = (uint16_t)lb;
     const uint32_t total = wave_incl_scan(lb);
-    if (lane == 63) ((GLOBAL uint64_t *)(a.blob + a.off_cb))[c + 1] = total;
+    if (lane == 63) ((GLOBAL uint64_t *)(a.blob + a.off_cb))[c + 1] = (uint64_t)total << TOTAL_AT;
 }
 
 // Stream: one wave per chunk, as in the E4M3 encoder (a lane's bits are one string: the forward run's codewords in order,
@@ -255,13 +255,15 @@ __global__ __launch_bounds__(256) void w_pack_kernel(WEncArgs a, WCodeArgs ca)
     if (tid < 2) s_code[tid][A] = 0;
     __syncthreads();
     uint32_t *stage = stage_all[wave];
-    const GLOBAL uint64_t *cb = (const GLOBAL uint64_t *)(a.blob + a.off_cb);
+    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(a.blob + a.off_cb);
+    const uint64_t mask = position_mask(a.n_chunks);
     for (uint64_t c = (uint64_t)blockIdx.x * 4 + wave; c < a.n_chunks; c += (uint64_t)gridDim.x * 4) {   // the same for the whole wave
         const bool whole = (c + 1) * (64ull * N) <= a.n;
         const ChunkPlace p = place_of<FMT, N>(a, c, lane);
         u32x4 v[N / P];
         load_pieces<FMT, N>(a, p, whole, v);
-        const uint64_t b0 = uniform64(cb[c]), b1 = uniform64(cb[c + 1]);
+        uint64_t b0, b1;
+        chunk_positions(cb, c, mask, lane, b0, b1);
         const uint32_t lb = ((const GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane];
         const uint32_t n_units = (uint32_t)(((b1 + 127) >> 7) - (b0 >> 7));
         for (uint32_t u = lane; u < n_units && u < (uint32_t)STAGE / 4; u += 64) *(u32x4 *)(stage + 4 * u) = u32x4{0, 0, 0, 0};
@@ -315,7 +317,7 @@ int launch_pass2(const WEncArgs &a, const WHeadArgs &ha, const WCodeArgs &ca, hi
     if (cus <= 0) return ECF8_E_HIP;
     const uint64_t chunk_blocks = (a.n_chunks + 3) / 4;
     hipLaunchKernelGGL((w_meta_kernel<FMT, N>), dim3((uint32_t)chunk_blocks + 1), dim3(256), 0, s, a, ha);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a.blob + a.off_cb, a.n_chunks, a.blob + a.off_st);
+    launch_scan(a.blob + a.off_cb, a.n_chunks, a.blob + a.off_st, s);
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);
     if (ha.h.max_code_len <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_pack_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(pg), dim3(256), 0, s, a, ca);

@@ -75,11 +75,18 @@ def test_seeded_sweep_of_shapes_and_options(orc, block):
                     table_mode=int(rng.choice([1, 2])))
 
 
-@pytest.mark.parametrize("extra", [-2048, 0, 1, 2048 * 1024 + 7])
-def test_more_chunks_than_a_round_of_the_prefix_sum(orc, extra):
-    """The chunk totals are summed 8192 at a time; the last round has one chunk less, none, one symbol, 1024 chunks more."""
-    x = _rand_bytes(8192 * 2048 + extra, 91 + extra % 5)
-    _check_same(orc, x, 1, x.size, oracle_read=False, lane_syms=32, max_code_len=15 if extra else 0)
+@pytest.mark.parametrize("chunks,extra", [(1024, 0), (1024, 1), (2048, -1), (8192, 7), (65536, 0), (65536, 1), (65536 + 8192, 5)])
+def test_many_chunks(chunks, extra):
+    """The chunk totals are summed 1024 per workgroup up to 65536 of them, beyond that by one workgroup 8192 at a time:
+    whole and nearly whole slices and rounds, one chunk more, the first sizes past the limit."""
+    n = chunks * 2048 + extra
+    x = np.resize(_rand_bytes((1 << 20) + 12345, chunks + extra), n)
+    opts = dict(lane_syms=32, max_code_len=15 if extra else 0)
+    want = ecf8.ecf8_encode(x, 1, n, **opts)
+    hdr, d_blob = ecf8.ecf8_encode_gpu(torch.from_numpy(x).to(DEV), 1, n, **opts)
+    torch.cuda.synchronize()
+    assert bytes(hdr) == bytes(want.header)
+    assert torch.equal(d_blob.cpu(), torch.from_numpy(want.numpy()))
 
 
 @pytest.mark.parametrize("opts", [dict(lane_syms=128, table_mode=1), dict(lane_syms=64, table_mode=2, max_code_len=15), dict(lane_syms=32, table_mode=1, group_chunks=1),
