@@ -165,47 +165,48 @@ __device__ __attribute__((unused)) void build_tables(uint64_t len_lo, uint64_t l
 // What bounds it: instruction issue, once per workgroup and tensor.  Under the cap an entry is the sum of two parts, the
 // codeword at its low 7 bits and the codeword that many bits on, so a table of the 128 short indices gives both: lane t
 // keeps the parts of the low bits 2t and 2t + 1 in registers and walks over the high 7 bits, one look-up per entry.
-// About 550 vector operations per thread of an 8-wave workgroup: a single decode of 256 x 256 weights 14.4 -> 8.7 us
-// against the general builder below, the fused product with a 240 x 768 matrix 11.3 -> 8.4 us per call.
+// The codeword of a short index is found by its place in the code space: symbols in canonical order begin at sums of
+// 2^(7 - length), and an index belongs to the last one that begins at or before it.
+// About 270 vector operations per thread of an 8-wave workgroup: a single decode of 256 x 256 weights 14.4 -> 8.1 us against
+// the general builder below (8.7 with every symbol matched against every index), the fused product with a 240 x 768 matrix
+// 11.3 -> 8.1 us per call.
 template <int NW>
 __device__ __forceinline__ void build_pair_table(uint64_t len_lo, uint64_t len_hi, uint16_t *tbl, uint32_t *tmp, int lane, int wave)
 {
     constexpr uint32_t H = TB / 2;
-    // lane s < 16 of every wave: codeword s, first bit lowest
-    const uint32_t len = len_of(len_lo, len_hi, lane & 15);
-    uint32_t code = 0;
+    // lane s < 16 of every wave: symbol s, its rank in canonical order (absent symbols last) and where its codes begin
+    const uint32_t len = lane < 16 ? len_of(len_lo, len_hi, lane & 15) : 0u;
+    const uint32_t key = lane < 16 ? ((len ? len : 15u) << 4) | (uint32_t)lane : 0u;
+    uint32_t before = 0;                      // begin in the low half, rank in the high half
 #pragma unroll
     for (int j = 0; j < 16; j++) {
         const uint32_t lj = len_of(len_lo, len_hi, j);
-        if (lj != 0 && lj < len) code += 1u << (len - lj);
-        else if (lj == len && j < (lane & 15)) code += 1;
+        before += (((lj ? lj : 15u) << 4) | (uint32_t)j) < key ? (lj ? 1u << ((H - lj) & 31u) : 0u) + 0x10000u : 0u;
     }
-    const uint32_t rcode = len ? __brev(code) >> (32 - len) : 0u;
-    // the codeword at the low bits of 2t and of 2t + 1: symbol and length
-    uint32_t s0 = 0, l0 = 0, s1 = 0, l1 = 0;
+    const uint32_t begin = len ? before & 0xffffu : 255u;
+    // the symbol of rank r to lane r: symbol | length << 8
+    const uint32_t ranked = (uint32_t)__builtin_amdgcn_ds_permute((int)((lane < 16 ? before >> 16 : (uint32_t)lane) * 4), (int)((uint32_t)lane | (len << 8)));
+    const uint32_t x0 = __brev(2u * lane) >> (32 - H), x1 = x0 + (1u << (H - 1));     // the short indices, first bit most significant
+    uint32_t r0 = 0, r1 = 0;
 #pragma unroll
     for (int s = 0; s < 16; s++) {
-        const uint32_t ls = (uint32_t)__builtin_amdgcn_readlane((int)len, s), rs = (uint32_t)__builtin_amdgcn_readlane((int)rcode, s);
-        const uint32_t mask = (1u << ls) - 1u;
-        const bool h0 = ls != 0 && ((2u * lane) & mask) == rs, h1 = ls != 0 && ((2u * lane + 1u) & mask) == rs;
-        s0 = h0 ? (uint32_t)s : s0;
-        l0 = h0 ? ls : l0;
-        s1 = h1 ? (uint32_t)s : s1;
-        l1 = h1 ? ls : l1;
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)begin, s);
+        r0 += at <= x0;
+        r1 += at <= x1;
     }
-    if (wave == 0) {                      // as the second codeword of an entry: symbol << 11 | length << 7, 0 = none
-        tmp[2 * lane] = l0 ? (s0 << 11) | (l0 << 7) : 0u;
-        tmp[2 * lane + 1] = l1 ? (s1 << 11) | (l1 << 7) : 0u;
+    const uint32_t c0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(r0 * 4 - 4), (int)ranked), c1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(r1 * 4 - 4), (int)ranked);
+    const uint32_t l0 = c0 >> 8, l1 = c1 >> 8, s0 = c0 & 15u, s1 = c1 & 15u;
+    if (wave == 0) {                          // as the second codeword of an entry
+        tmp[2 * lane] = (s0 << 11) | (l0 << 7);
+        tmp[2 * lane + 1] = (s1 << 11) | (l1 << 7);
     }
     __syncthreads();
-    const uint32_t e0 = l0 ? (s0 << 3) | l0 : 0u, e1 = l1 ? (s1 << 3) | l1 : 0u;
-    const uint32_t f0 = e0 + (l0 << 7), f1 = e1 + (l1 << 7);
+    const uint32_t f0 = (s0 << 3) | l0 | (l0 << 7), f1 = (s1 << 3) | l1 | (l1 << 7);       // as the first one
     const uint32_t at0 = ((2u * lane) >> l0) << 2, at1 = ((2u * lane + 1u) >> l1) << 2;    // byte offsets into tmp
 #pragma unroll 4
     for (uint32_t hi = (uint32_t)wave; hi < (1u << H); hi += NW) {
-        const uint32_t b0 = *(const uint32_t *)((const uint8_t *)tmp + ((at0 | (hi << (H + 2 - l0))) & (((1u << H) - 1) << 2)));
-        const uint32_t b1 = *(const uint32_t *)((const uint8_t *)tmp + ((at1 | (hi << (H + 2 - l1))) & (((1u << H) - 1) << 2)));
-        const uint32_t v0 = (l0 && b0) ? f0 + b0 : e0, v1 = (l1 && b1) ? f1 + b1 : e1;
+        const uint32_t v0 = f0 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l0)) & (((1u << H) - 1) << 2)) | at0));
+        const uint32_t v1 = f1 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l1)) & (((1u << H) - 1) << 2)) | at1));
         ((uint32_t *)tbl)[(hi << (H - 1)) + lane] = v0 | (v1 << 16);
     }
     __syncthreads();
