@@ -172,6 +172,14 @@ __device__ __forceinline__ void copy_span(const uint32_t *stage, GLOBAL uint32_t
     }
 }
 
+// The encoders' one synchronisation: the histogram back to the host, when everything queued on `s` so far is done.  The
+// call returns with the bytes in place; an asynchronous copy to pageable memory waits just as long, and the
+// hipStreamSynchronize it needs for that to be certain adds a second round trip to the device.
+inline bool read_back(void *host, uint64_t device, uint64_t bytes, hipStream_t s)
+{
+    return hipMemcpyWithStream(host, (const void *)(uintptr_t)device, bytes, hipMemcpyDeviceToHost, s) == hipSuccess;
+}
+
 } // namespace
 
 #endif

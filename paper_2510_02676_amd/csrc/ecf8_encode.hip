@@ -343,9 +343,7 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
     hipLaunchKernelGGL(histogram_kernel, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s, x, n,
                        blob + 128);
     uint64_t freq[16];
-    if (hipMemcpyAsync(freq, (const uint8_t *)d_blob + 128, sizeof(freq), hipMemcpyDeviceToHost, s) != hipSuccess)
-        return ECF8_E_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return ECF8_E_HIP;
+    if (!read_back(freq, blob + 128, sizeof(freq), s)) return ECF8_E_HIP;
 
     ecf8_internal::Plan plan;
     rc = ecf8_internal::plan_encode(freq, rows, cols, opts, &plan);

@@ -344,9 +344,7 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     hipLaunchKernelGGL(w_histogram_kernel<FMT>, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s,
                        x, n, blob + off_freq);
     uint64_t freq[256] = {};
-    if (hipMemcpyAsync(freq, (const uint8_t *)d_blob + off_freq, 8ull * A, hipMemcpyDeviceToHost, s) != hipSuccess)
-        return ECF8_E_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return ECF8_E_HIP;
+    if (!read_back(freq, blob + off_freq, 8ull * A, s)) return ECF8_E_HIP;
 
     ecfw_internal::WPlan plan;
     int rc = ecfw_internal::plan_encode(freq, FMT, rows, cols, N, group, lmax, &plan);

@@ -134,6 +134,26 @@ def test_config0_and_a_full_size_matrix(orc):
     assert torch.equal(ecf8.ecf8_decode(hdr, d_blob), wd)
 
 
+def test_on_a_side_stream():
+    """The histogram is read back behind work that is still queued on the caller's stream, which is not the default one."""
+    x = torch.from_numpy(_rand_bytes(2_000_001, 3)).to(DEV)
+    y = torch.from_numpy(_rand_bytes(2_000_001, 4, conc=3.0)).to(DEV)
+    m = torch.randn(4096, 4096, device=DEV)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        z = x.clone()
+        for _ in range(8):
+            m = m @ m * 1e-3
+        z.copy_(y)                                             # after milliseconds of products
+        hdr, d_blob = ecf8.ecf8_encode_gpu(z, 1, z.numel())
+        z.copy_(x)                                             # behind the encode on the same stream
+    torch.cuda.synchronize()
+    want = ecf8.ecf8_encode(y.cpu(), 1, y.numel())
+    assert bytes(hdr) == bytes(want.header)
+    assert torch.equal(d_blob.cpu(), torch.from_numpy(want.numpy()))
+
+
 def test_argument_errors():
     d_x = torch.zeros(4096, dtype=torch.uint8, device=DEV)
     with pytest.raises(ecf8.Ecf8Error) as e:
