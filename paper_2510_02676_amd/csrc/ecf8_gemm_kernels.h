@@ -118,6 +118,25 @@ __device__ __forceinline__ void load_x_slice(const GArgs &a, int tid,
             }
 }
 
+// The pair table the encoder embedded, if it did, on its way from the blob to LDS.
+template <int NW> constexpr int TABLE_UNITS = (TBL_ENTRIES * 2 / 16 + NW * 64 - 1) / (NW * 64);     // 16-byte units per thread
+template <int NW>
+__device__ __forceinline__ void load_table(const GArgs &a, int tid, u32x4 (&tv)[TABLE_UNITS<NW>])
+{
+    static_assert(TABLE_UNITS<NW> * NW * 64 * 16 == TBL_ENTRIES * 2, "whole rounds");
+    if (!a.off_tbl) return;
+    const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
+#pragma unroll
+    for (int j = 0; j < TABLE_UNITS<NW>; j++) tv[j] = src[tid + j * NW * 64];
+}
+template <int NW>
+__device__ __forceinline__ void store_table(uint16_t *tbl, int tid, const u32x4 (&tv)[TABLE_UNITS<NW>])
+{
+#pragma unroll
+    for (int j = 0; j < TABLE_UNITS<NW>; j++) ((u32x4 *)tbl)[tid + j * NW * 64] = tv[j];
+    __syncthreads();
+}
+
 // The sums of one chunk (16 rows x 256 columns).  Without scales a chunk adds straight into the block's
 // accumulators.  With scales its two 128-column halves -- exactly its forward and its backward run --
 // are summed by the matrix cores apart and enter the block's sum through one multiply-add each, with
@@ -418,28 +437,26 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
+    // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
+    // table first, since it is what the workgroup meets for.
+    u32x4 tv[TABLE_UNITS<NW>];
+    load_table<NW>(a, tid, tv);
     if (n_steps > 0) {
         m_cur = load_meta(0);
         m_next = load_meta(n_steps > 1 ? 1 : 0);
-        load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(0);
 #pragma unroll
         for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * q));
     }
-
     u32x4 areg[MT][KPW][GPIECES];
     load_x_slice<MT, NW, N>(a, tid, areg);
+    if (n_steps > 0) load_stream(m_cur, seg);
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
     __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) {
-        const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
-        for (int i = tid; i < TBL_ENTRIES * 2 / 16; i += NW * 64) ((u32x4 *)tbl)[i] = src[i];
-        __syncthreads();
-    } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
-    }
+    if (a.off_tbl) store_table<NW>(tbl, tid, tv);
+    else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
 
     uint32_t parity = 0;
     for (uint64_t s0 = 0; s0 < n_steps; s0 += KPW) {
@@ -712,28 +729,25 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
     XPieces<MT, N> x_cur;
+    u32x4 tv[TABLE_UNITS<NW>];
+    load_table<NW>(a, tid, tv);                           // see ecf8_gemm_kernel for the order
     if (valid(cur)) {
         m_cur = load_meta(cur);
         m_next = m_cur;
         if (valid(next_of(cur))) m_next = load_meta(next_of(cur));
-        load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(cur) + lane_plane;
 #pragma unroll
         for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * q));
         load_x_chunk<MT, N>(a, lane, kc_of(cur), x_cur);
     }
+    if (valid(cur)) load_stream(m_cur, seg);
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
     __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) {
-        const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
-        for (int i = tid; i < TBL_ENTRIES * 2 / 16; i += NW * 64) ((u32x4 *)tbl)[i] = src[i];
-        __syncthreads();
-    } else {
-        if constexpr (APART) build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
-        else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
-    }
+    if (a.off_tbl) store_table<NW>(tbl, tid, tv);
+    else if constexpr (APART) build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
+    else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
 
     for (uint64_t b = 0; b < my_blocks; b++) {            // uniform for the workgroup: one barrier per block
         f32x4 acc[MT];
