@@ -644,7 +644,15 @@ int dispatch(const KArgs &a, uint32_t lane_syms, hipStream_t s)
         if (pairfit) return launch_as<64, 12, true>(a, 1, s);
         return lng ? launch_as<64, 12, false, false, true, 1>(a, 1, s) : launch_as<64, 12, false, false, false, 1>(a, 1, s);
     case 128:
-        if (pairfit) return launch_as<128, 8, true>(a, 1, s);
+        if (pairfit) {
+            // Nine to eleven chunks per compute unit leave 8 waves a second round that is nearly empty: 12 waves take them in
+            // one, without registers for a burst (8.5 chunks 11.7 us against 12.8, 10 chunks 12.8 against 14.6, 11 chunks
+            // 13.6 against 14.0, but 12 chunks 14.3 against 14.2 and 18 chunks 18.7 against 17.9: the burst counts for more).
+            const int cus = device_cus();
+            const uint64_t each = cus > 0 ? (a.total_chunks + cus - 1) / cus : 0;
+            if (each > 8 && each <= 11) return launch_as<128, 12, true, false, false, 0>(a, 1, s);
+            return launch_as<128, 8, true>(a, 1, s);
+        }
         return lng ? launch_as<128, 12, false, false, true, 2>(a, 1, s) : launch_as<128, 12, false, false, false, 2>(a, 1, s);
     default: return ECF8_E_ARG;
     }

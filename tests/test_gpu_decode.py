@@ -83,6 +83,24 @@ def test_ragged_last_chunk(orc, lane_syms, cap):
     assert np.array_equal(x, _oracle_expected(orc, x))
 
 
+@pytest.mark.parametrize("per_cu", [8, 8.004, 9.5, 11, 11.004])
+def test_sizes_around_one_round_of_waves(per_cu):
+    """8, just over 8, up to 11 and just over 11 chunks of 128 symbols per lane and compute unit: either side of the rule
+    that picks 12 waves; whole chunks and a ragged end, one tensor and a batch of two."""
+    chunks = int(per_cu * torch.cuda.get_device_properties(0).multi_processor_count)
+    for extra in (0, -5000):
+        n = chunks * 8192 + extra
+        d_x = synth.make_weight(1, n, 1.8, 0.02, chunks, scaling="tensor", device=DEV).reshape(-1)
+        hdr, d_blob = ecf8.ecf8_encode_gpu(d_x, 1, n)
+        assert torch.equal(ecf8.ecf8_decode(hdr, d_blob).reshape(-1), d_x)
+        cut = (n // 3 + 255) // 256 * 256
+        parts = [d_x[:cut].clone(), d_x[cut:].clone()]
+        enc = [ecf8.ecf8_encode_gpu(p, 1, p.numel()) for p in parts]
+        out = torch.full((n + 512,), 0xA5, dtype=torch.uint8, device=DEV)
+        ecf8.ecf8_decode_batched(ecf8.Batch([h for h, _ in enc], [b for _, b in enc], [out[:cut], out[cut:n]]))
+        assert torch.equal(out[:n], d_x) and bool((out[n:] == 0xA5).all())
+
+
 def _special_cases():
     fib = [1, 1]
     while len(fib) < 16:
