@@ -328,33 +328,34 @@ __device__ __forceinline__ void quad_step2(const uint8_t *smem, const uint16_t *
     outB = __builtin_amdgcn_perm(eB2, eB1, 0x05040100u);
 }
 
-// The two runs of a lane with their windows held in registers: three consecutive dwords of the LDS image per run
-// (the two a window is made of and the one the run moves into next).  A step then has two LDS round trips on
-// its critical path, the two table lookups, instead of three: the dword that refills the spare is fetched at the
-// end of a step and first needed at the end of the next one.  Positions are kept one bit off as in quad_step2.
+// The two runs of a lane with their windows held in registers: the two dwords of the LDS image that a window is made of, per
+// run.  A step moves a run by at most 28 bits, so by at most one dword; the dword it may move into is fetched inside
+// the step, behind the first two table lookups and in their shadow, so that a step has two LDS round trips on
+// its critical path, the lookups.  Positions are kept one bit off as in quad_step2, the backward run's another 32 bits
+// down, so that the address of its window's dwords is also that of the dword below them.
 struct HeldRuns {
-    uint32_t pa, pb;           // forward run: next bit - 1; backward run: one past its next bit - 31
-    uint32_t a0, a1, a2;       // dwords at A, A + 4, A + 8 with A = (pa / 8) & ~3
-    uint32_t bm, b0, b1;       // dwords at B - 4, B, B + 4 with B = (pb / 8) & ~3
+    uint32_t pa, pb;           // forward run: next bit - 1; backward run: one past its next bit - 63
+    uint32_t A, B;             // (pa / 8) & ~3, (pb / 8) & ~3
+    uint32_t a0, a1;           // dwords at A, A + 4
+    uint32_t b0, b1;           // dwords at B + 4, B + 8
 
+    // pb_: one past the backward run's next bit - 31, as in quad_step2
     __device__ __forceinline__ void begin(const uint8_t *smem, uint32_t pa_, uint32_t pb_)
     {
         pa = pa_;
-        pb = pb_;
-        const uint32_t A = (pa >> 3) & ~3u, B = (pb >> 3) & ~3u;
+        pb = pb_ - 32;
+        A = (pa >> 3) & ~3u;
+        B = (pb >> 3) & ~3u;
         a0 = *(const uint32_t *)(smem + A);
         a1 = *(const uint32_t *)(smem + A + 4);
-        a2 = *(const uint32_t *)(smem + A + 8);
-        bm = *(const uint32_t *)(smem + B - 4);
-        b0 = *(const uint32_t *)(smem + B);
-        b1 = *(const uint32_t *)(smem + B + 4);
+        b0 = *(const uint32_t *)(smem + B + 4);
+        b1 = *(const uint32_t *)(smem + B + 8);
     }
 };
 
 // quad_step2 over held windows, for launches whose pairs always fit the table (PAIRFIT; with a second level in
-// the way the general kernels measured faster on windows fetched per step).  A step moves a run by at most 28 bits,
-// so by at most one dword: bit 5 of the position tells.  The refill reads past the stage of the last wave by up to
-// 8 bytes and before the first one by up to 4: the caller's LDS map has something there.
+// the way the general kernels measured faster on windows fetched per step).  It reads up to 8 bytes past the dwords of a
+// window and 4 before them: the caller's LDS map has something there.
 __device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint16_t *tbl, HeldRuns &r, uint32_t &outA, uint32_t &outB)
 {
     constexpr uint32_t OFF_MASK = TBL_MASK << 1;
@@ -363,23 +364,23 @@ __device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint16
     const uint32_t wB = __brev(__builtin_amdgcn_alignbit(r.b1, r.b0, r.pb));
     const uint32_t eA1 = *(const uint16_t *)(tb + (wA & OFF_MASK));
     const uint32_t eB1 = *(const uint16_t *)(tb + (wB & OFF_MASK));
+    __builtin_amdgcn_sched_barrier(0x7f);       // anything but LDS accesses may move: the lookups stay in front
+    const uint32_t a2 = *(const uint32_t *)(smem + r.A + 8);
+    const uint32_t bm = *(const uint32_t *)(smem + r.B);
     const uint32_t nA1 = (eA1 >> 7) & 15u;
     const uint32_t nB1 = (eB1 >> 7) & 15u;
     const uint32_t eA2 = *(const uint16_t *)(tb + ((wA >> nA1) & OFF_MASK));    // >= 17 valid bits left in the window
     const uint32_t eB2 = *(const uint16_t *)(tb + ((wB >> nB1) & OFF_MASK));
-    const uint32_t pa = r.pa + nA1 + ((eA2 >> 7) & 15u);
-    const uint32_t pb = r.pb - nB1 - ((eB2 >> 7) & 15u);
-    const uint32_t ldA = *(const uint32_t *)(smem + ((pa >> 3) & ~3u) + 8);
-    const uint32_t ldB = *(const uint32_t *)(smem + ((pb >> 3) & ~3u) - 4);
-    const bool upA = ((pa ^ r.pa) & 32u) != 0, downB = ((pb ^ r.pb) & 32u) != 0;
+    r.pa += nA1 + ((eA2 >> 7) & 15u);
+    r.pb -= nB1 + ((eB2 >> 7) & 15u);
+    const uint32_t A = (r.pa >> 3) & ~3u, B = (r.pb >> 3) & ~3u;
+    const bool upA = A != r.A, downB = B != r.B;
     r.a0 = upA ? r.a1 : r.a0;
-    r.a1 = upA ? r.a2 : r.a1;
-    r.a2 = ldA;                     // the dword at the new A + 8 either way
+    r.a1 = upA ? a2 : r.a1;
     r.b1 = downB ? r.b0 : r.b1;
-    r.b0 = downB ? r.bm : r.b0;
-    r.bm = ldB;
-    r.pa = pa;
-    r.pb = pb;
+    r.b0 = downB ? bm : r.b0;
+    r.A = A;
+    r.B = B;
     outA = __builtin_amdgcn_perm(eA2, eA1, 0x05040100u);
     outB = __builtin_amdgcn_perm(eB2, eB1, 0x05040100u);
 }
