@@ -438,25 +438,34 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
     // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
-    // table first, since it is what the workgroup meets for.
+    // table first, since it is what the workgroup meets for (M = 16: 21.9 -> 21.45 us).  Not with four tiles of X and no
+    // scales, where X alone takes half of the registers and the metadata come first (30.8 us; in this order 31.4).
+    constexpr bool EARLY = !(MT == 4 && SC == 0);
     u32x4 tv[TABLE_UNITS<NW>];
-    load_table<NW>(a, tid, tv);
+    if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (n_steps > 0) {
         m_cur = load_meta(0);
         m_next = load_meta(n_steps > 1 ? 1 : 0);
+        if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(0);
 #pragma unroll
         for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * q));
     }
     u32x4 areg[MT][KPW][GPIECES];
     load_x_slice<MT, NW, N>(a, tid, areg);
-    if (n_steps > 0) load_stream(m_cur, seg);
+    if constexpr (EARLY) {
+        if (n_steps > 0) load_stream(m_cur, seg);
+    }
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
     __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) store_table<NW>(tbl, tid, tv);
-    else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
+    if (a.off_tbl) {
+        if constexpr (!EARLY) load_table<NW>(a, tid, tv);
+        store_table<NW>(tbl, tid, tv);
+    } else {
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
+    }
 
     uint32_t parity = 0;
     for (uint64_t s0 = 0; s0 < n_steps; s0 += KPW) {
@@ -729,25 +738,36 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
     XPieces<MT, N> x_cur;
+    // The order of ecf8_gemm_kernel, but for groups with scales and two tiles of X: six experts, M = 20, 119.7 us with the
+    // metadata first and 124.8 in this order, which gains 1.5 .. 3 % everywhere else.
+    constexpr bool EARLY = !(APART && MT == 2 && SC == 1);
     u32x4 tv[TABLE_UNITS<NW>];
-    load_table<NW>(a, tid, tv);                           // see ecf8_gemm_kernel for the order
+    if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (valid(cur)) {
         m_cur = load_meta(cur);
         m_next = m_cur;
         if (valid(next_of(cur))) m_next = load_meta(next_of(cur));
+        if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(cur) + lane_plane;
 #pragma unroll
         for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * q));
         load_x_chunk<MT, N>(a, lane, kc_of(cur), x_cur);
     }
-    if (valid(cur)) load_stream(m_cur, seg);
+    if constexpr (EARLY) {
+        if (valid(cur)) load_stream(m_cur, seg);
+    }
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
     __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) store_table<NW>(tbl, tid, tv);
-    else if constexpr (APART) build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
-    else build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
+    if (a.off_tbl) {
+        if constexpr (!EARLY) load_table<NW>(a, tid, tv);
+        store_table<NW>(tbl, tid, tv);
+    } else if constexpr (APART) {
+        build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
+    } else {
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
+    }
 
     for (uint64_t b = 0; b < my_blocks; b++) {            // uniform for the workgroup: one barrier per block
         f32x4 acc[MT];
