@@ -330,7 +330,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             // than the copy does (a layer of seven matrices, 80.6 -> 83.8 us)
             build_pair_table<WAVES>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_WAVES), lane, wave);
         } else {
-            build_tables(len_lo, len_hi, tbl, s_len, s_code, (uint16_t *)(smem + C::OFF_WAVES), tid, WAVES * 64);
+            build_tables<WAVES * 64>(len_lo, len_hi, tbl, s_len, s_code, (uint16_t *)(smem + C::OFF_WAVES), tid);
         }
 
         // Decode of one full chunk whose span sits in LDS from bit `first_bit` (smem-relative) on,
