@@ -156,14 +156,14 @@ __device__ __forceinline__ void write_fixed(const EncArgs &a, const ecf8_header 
 // 89 MB it reads and writes, i.e. a copy's rate (metadata and plane each in a kernel of its own, 15 + 8 .. 14 us, after a
 // zero fill of the whole blob, 10 us, and the pair table by one workgroup, 8 us).
 template <int N>
-__global__ __launch_bounds__(256) void meta_kernel(EncArgs a, ecf8_header h, uint32_t parts)
+__global__ __launch_bounds__(256) void meta_kernel(EncArgs a, ecf8_header h, uint32_t parts, uint64_t first_block)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     if (blockIdx.x < parts) {
         write_fixed(a, h, blockIdx.x, parts, tid);
         return;
     }
-    const uint64_t c = (uint64_t)(blockIdx.x - parts) * 4 + uniform32((uint32_t)tid >> 6);
+    const uint64_t c = (first_block + (blockIdx.x - parts)) * 4 + uniform32((uint32_t)tid >> 6);
     if (c >= a.n_chunks) return;
     uint32_t len_bytes[4];                   // code lengths of symbols 4i .. 4i + 3
 #pragma unroll
@@ -302,7 +302,12 @@ int launch_pass2(const EncArgs &a, const ecf8_header &h, uint32_t lmax, hipStrea
     if (cus <= 0) return ECF8_E_HIP;
     const uint32_t parts = h.table_bits ? 64 : 1;
     const uint64_t chunk_blocks = (h.n_chunks + 3) / 4;
-    hipLaunchKernelGGL(meta_kernel<N>, dim3((uint32_t)chunk_blocks + parts), dim3(256), 0, s, a, h, parts);
+    for (uint64_t b = 0; b < chunk_blocks; b += META_BLOCKS) {
+        const uint32_t fixed = b == 0 ? parts : 0, blocks = (uint32_t)(chunk_blocks - b < META_BLOCKS ? chunk_blocks - b : META_BLOCKS);
+        hipLaunchKernelGGL(meta_kernel<N>, dim3(blocks + fixed), dim3(256), 0, s, a, h, fixed, b);
+    }
+    // the kernels behind it store where the metadata say: not without them
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     launch_scan(a.blob + a.off_cb, h.n_chunks, a.blob + a.off_st, s);
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);

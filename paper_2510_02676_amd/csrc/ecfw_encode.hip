@@ -174,18 +174,18 @@ __device__ __forceinline__ void write_fixed(const WEncArgs &a, const WHeadArgs &
 // the scan); the chunk's planes, zeros where the last chunk reaches past the tensor.  One wave per chunk; the
 // first workgroup writes the fixed parts instead.  The code lengths sit in 256 bytes of LDS: 64 dwords, one per bank.
 template <int FMT, int N>
-__global__ __launch_bounds__(256) void w_meta_kernel(WEncArgs a, WHeadArgs ha)
+__global__ __launch_bounds__(256) void w_meta_kernel(WEncArgs a, WHeadArgs ha, uint32_t parts, uint64_t first_block)
 {
     using F = EFmt<FMT>;
     constexpr int P = F::P;
     __shared__ uint32_t s_len4[64];
     const uint8_t *s_len = (const uint8_t *)s_len4;
     const int tid = threadIdx.x, lane = tid & 63;
-    if (blockIdx.x == 0) {
+    if (blockIdx.x < parts) {
         write_fixed(a, ha, tid);
         return;
     }
-    const uint64_t c = (uint64_t)(blockIdx.x - 1) * 4 + uniform32((uint32_t)tid >> 6);
+    const uint64_t c = (first_block + (blockIdx.x - parts)) * 4 + uniform32((uint32_t)tid >> 6);
     const bool here = c < a.n_chunks;
     const bool whole = (c + 1) * (64ull * N) <= a.n;
     const ChunkPlace p = place_of<FMT, N>(a, c, lane);
@@ -316,7 +316,12 @@ int launch_pass2(const WEncArgs &a, const WHeadArgs &ha, const WCodeArgs &ca, hi
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
     const uint64_t chunk_blocks = (a.n_chunks + 3) / 4;
-    hipLaunchKernelGGL((w_meta_kernel<FMT, N>), dim3((uint32_t)chunk_blocks + 1), dim3(256), 0, s, a, ha);
+    for (uint64_t b = 0; b < chunk_blocks; b += META_BLOCKS) {
+        const uint32_t fixed = b == 0 ? 1 : 0, blocks = (uint32_t)(chunk_blocks - b < META_BLOCKS ? chunk_blocks - b : META_BLOCKS);
+        hipLaunchKernelGGL((w_meta_kernel<FMT, N>), dim3(blocks + fixed), dim3(256), 0, s, a, ha, fixed, b);
+    }
+    // the kernels behind it store where the metadata say: not without them
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     launch_scan(a.blob + a.off_cb, a.n_chunks, a.blob + a.off_st, s);
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);

@@ -107,6 +107,55 @@ def test_every_byte_of_the_blob_is_written(opts):
         assert (got[want.size:] == 0xA5).all(), n
 
 
+def _rows_equal(t, row):
+    """Is every row of the flat tensor t (a whole number of rows) this row?  In pieces: t may be tens of GB."""
+    n = row.numel()
+    step = max(1, (1 << 28) // n) * n
+    return all(bool((t[i:i + step].view(-1, n) == row).all()) for i in range(0, t.numel(), step))
+
+
+@pytest.mark.parametrize("groups", [(1 << 17) + 3, (1 << 21) + 3])
+def test_more_chunks_than_one_launch_takes(groups):
+    """8.6 GB and 137 GB of weights, 32 symbols per lane: 2^22 and 2^26 chunks and some.  The metadata pass takes one launch per
+    2^20 workgroups; as a single launch the larger one has more than the 2^32 work-items a launch can have.  Every group of 32 chunks
+    holds the same weights, whose code bits are a whole number of 16-byte units, so each section of the container is the CPU
+    encoder's for one group over and over."""
+    period = 32 * 2048
+    n = groups * period
+    rng = np.random.default_rng(1)
+    e = np.full(period, 7, np.uint8)
+    e[rng.choice(period, 4096, replace=False)] = np.repeat([8, 3], 2048)
+    x = (e << 3) | (rng.integers(0, 256, period, dtype=np.uint8) & 0x87)
+    opts = dict(lane_syms=32, table_mode=2)
+    one = ecf8.ecf8_encode(x, 1, period, **opts)
+    h1, b1 = one.header, torch.from_numpy(one.numpy().copy()).to(DEV)
+    assert h1.stream_bits == period + 4096 and h1.stream_bits % 128 == 0
+    size = n // period * (h1.stream_bits // 8 + h1.plane_bytes + 32 * 136) + (1 << 12)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < n + size + (4 << 30):
+        pytest.skip("needs %d GB of device memory" % ((n + size) >> 30))
+    d_x = torch.empty(n, dtype=torch.uint8, device=DEV)
+    d_x[:period] = torch.from_numpy(x).to(DEV)
+    done = period
+    while done < n:
+        more = min(done, n - done)
+        d_x[done:done + more] = d_x[:more]
+        done += more
+    d_blob = torch.empty(size, dtype=torch.uint8, device=DEV)
+    hdr, _ = ecf8.ecf8_encode_gpu(d_x, 1, n, d_blob=d_blob, **opts)
+    torch.cuda.synchronize()
+    assert list(hdr.code_len) == list(h1.code_len) and hdr.stream_bits == groups * h1.stream_bits and hdr.n_chunks == 32 * groups
+    cb = d_blob[hdr.off_chunk_bit:hdr.off_chunk_bit + 8 * hdr.n_chunks].view(torch.int64).view(groups, 32)
+    cb1 = b1[h1.off_chunk_bit:h1.off_chunk_bit + 8 * 32].view(torch.int64)
+    assert torch.equal(cb, torch.arange(groups, device=DEV)[:, None] * h1.stream_bits + cb1)
+    assert int(d_blob[hdr.off_chunk_bit + 8 * hdr.n_chunks:][:8].view(torch.int64)) == hdr.stream_bits
+    for at, at1, nbytes in ((hdr.off_lane_bits, h1.off_lane_bits, 128 * 32), (hdr.off_stream, h1.off_stream, h1.stream_bits // 8),
+                            (hdr.off_plane, h1.off_plane, h1.plane_bytes)):
+        assert _rows_equal(d_blob[at:at + groups * nbytes], b1[at1:at1 + nbytes]), at
+    del d_x, d_blob, cb
+    torch.cuda.empty_cache()
+
+
 def test_special_histograms(orc):
     fib = [1, 1]
     while len(fib) < 16:

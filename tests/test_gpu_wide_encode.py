@@ -104,6 +104,38 @@ def test_full_size_matrix(orc, fmt):
     _same_as_cpu(orc, fmt, x, 14336, 4096, oracle_read=False)
 
 
+def test_more_chunks_than_one_launch_takes():
+    """17 GB of E5M2, 64 symbols per lane: 2^22 chunks and some.  The metadata pass takes one launch per 2^20 workgroups.  Every group
+    of 32 chunks holds the same elements, whose code bits are a whole number of 16-byte units, so each section of the
+    container is the CPU encoder's for one group over and over."""
+    groups, period = (1 << 17) + 3, 32 * 4096
+    n = groups * period
+    rng = np.random.default_rng(1)
+    e = np.full(period, 15, np.uint8)
+    e[rng.choice(period, 8192, replace=False)] = np.repeat([16, 9], 4096)
+    x = (e << 2) | (rng.integers(0, 256, period, dtype=np.uint8) & 0x83)
+    one = ecfw.ecfw_encode(E5M2, x, 1, period, lane_syms=64)
+    h1, b1 = one.header, torch.from_numpy(one.numpy().copy()).to(DEV)
+    assert h1.stream_bits == period + 8192 and h1.stream_bits % 128 == 0
+    size = groups * (h1.stream_bits // 8 + h1.plane_bytes + h1.sign_bytes + 32 * 136) + (1 << 13)
+    torch.cuda.empty_cache()
+    d_x = torch.from_numpy(x).to(DEV).repeat(groups)
+    d_blob = torch.empty(size, dtype=torch.uint8, device=DEV)
+    hdr, _ = ecfw.ecfw_encode_gpu(E5M2, d_x, 1, n, lane_syms=64, d_blob=d_blob)
+    torch.cuda.synchronize()
+    assert hdr.stream_bits == groups * h1.stream_bits and hdr.n_chunks == 32 * groups
+    cb = d_blob[hdr.off_chunk_bit:hdr.off_chunk_bit + 8 * hdr.n_chunks].view(torch.int64).view(groups, 32)
+    cb1 = b1[h1.off_chunk_bit:h1.off_chunk_bit + 8 * 32].view(torch.int64)
+    assert torch.equal(cb, torch.arange(groups, device=DEV)[:, None] * h1.stream_bits + cb1)
+    for at, at1, nbytes in ((hdr.off_code_len, h1.off_code_len, 256), (hdr.off_lane_bits, h1.off_lane_bits, 128 * 32),
+                            (hdr.off_stream, h1.off_stream, h1.stream_bits // 8), (hdr.off_plane, h1.off_plane, h1.plane_bytes),
+                            (hdr.off_sign, h1.off_sign, h1.sign_bytes)):
+        rows = d_blob[at:at + (1 if nbytes == 256 else groups) * nbytes].view(-1, nbytes)
+        assert all(bool((r == b1[at1:at1 + nbytes]).all()) for r in rows.split(1 << 13)), at
+    del d_x, d_blob, cb, rows
+    torch.cuda.empty_cache()
+
+
 def test_argument_errors():
     x = torch.zeros(10000, dtype=torch.int16, device=DEV)
     with pytest.raises(ecf8.Ecf8Error) as e:
