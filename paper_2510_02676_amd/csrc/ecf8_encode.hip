@@ -306,9 +306,10 @@ int launch_pass2(const EncArgs &a, const ecf8_header &h, uint32_t lmax, hipStrea
         const uint32_t fixed = b == 0 ? parts : 0, blocks = (uint32_t)(chunk_blocks - b < META_BLOCKS ? chunk_blocks - b : META_BLOCKS);
         hipLaunchKernelGGL(meta_kernel<N>, dim3(blocks + fixed), dim3(256), 0, s, a, h, fixed, b);
     }
-    // the kernels behind it store where the metadata say: not without them
+    // prefix sum and packing store where the metadata say: neither without what it reads
     if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     launch_scan(a.blob + a.off_cb, h.n_chunks, a.blob + a.off_st, s);
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);
     if (lmax <= 7) hipLaunchKernelGGL((pack_kernel<N, true>), dim3(pg), dim3(256), 0, s, a);

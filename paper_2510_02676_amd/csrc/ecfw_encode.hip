@@ -320,9 +320,10 @@ int launch_pass2(const WEncArgs &a, const WHeadArgs &ha, const WCodeArgs &ca, hi
         const uint32_t fixed = b == 0 ? 1 : 0, blocks = (uint32_t)(chunk_blocks - b < META_BLOCKS ? chunk_blocks - b : META_BLOCKS);
         hipLaunchKernelGGL((w_meta_kernel<FMT, N>), dim3(blocks + fixed), dim3(256), 0, s, a, ha, fixed, b);
     }
-    // the kernels behind it store where the metadata say: not without them
+    // prefix sum and packing store where the metadata say: neither without what it reads
     if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     launch_scan(a.blob + a.off_cb, a.n_chunks, a.blob + a.off_st, s);
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     const uint64_t most = (uint64_t)cus * 8;
     const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);
     if (ha.h.max_code_len <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_pack_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(pg), dim3(256), 0, s, a, ca);
