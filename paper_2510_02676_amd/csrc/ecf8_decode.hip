@@ -621,6 +621,28 @@ int launch_as(const KArgs &a, int wgs_per_cu, hipStream_t s)
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 
+// Capped codes at N = 128: 8 waves that store a chunk in one burst, or 12 that store piece by piece (no registers for a
+// burst).  Up to 8 chunks per workgroup are one round of 8 waves, whose tables are smaller; beyond that 12 waves pay where they
+// save a round (one instead of two; on half of the compute units two instead of three), or where the launch is confined
+// to so few compute units that HBM is not the bound (not for 13 .. 16 chunks,
+// two rounds either way).  Measured, us with 8 / with 12 waves, by workgroups: chunks per workgroup
+//   256: 1 8.7 / 9.2, 9 13.3 / 12.1, 10 13.8 / 13.1, 11 13.7 / 13.8, 12 14.1 / 14.3, 16 16.8 / 17.5, 104 76.5 / 88.7
+//   192: 11 13.3 / 12.8, 13 14.5 / 14.8, 15 14.9 / 15.5, 64 42.0 / 44.7
+//   128: 14 15.2 / 15.5, 16 14.3 / 14.6, 18 16.0 / 15.8, 22 18.4 / 17.9, 24 18.8 / 18.4, 96 51.5 / 51.4, 208 100.8 / 102.4
+//    96: 6 10.0 / 10.3, 19 16.9 / 16.4, 32 22.0 / 20.3, 43 28.0 / 28.3, 277 129.6 / 126.5;  64: 40 25.0 / 22.4, 416 186 / 171
+//    32: 16 14.0 / 14.2, 48 29.2 / 26.5, 832 357 / 299
+int pairfit_128(const KArgs &a, hipStream_t s)
+{
+    const int cus = device_cus();
+    if (cus <= 0) return ECF8_E_HIP;
+    const uint64_t wgs = a.max_workgroups && a.max_workgroups < (uint32_t)cus ? a.max_workgroups : (uint64_t)cus;
+    const uint64_t each = (a.total_chunks + wgs - 1) / wgs;
+    const bool few = 8 * wgs <= 3 * (uint64_t)cus, half = 2 * wgs <= (uint64_t)cus;
+    if (each > 8 && (each <= 11 || (half && each > 16 && each <= 24) || (few && (each == 12 || each > 16))))
+        return launch_as<128, 12, true, false, false, 0>(a, 1, s);
+    return launch_as<128, 8, true>(a, 1, s);
+}
+
 // Workgroup shapes.  PAIRFIT kernels: N = 128 runs 8 waves of ~200 VGPRs, which is what holding a chunk's 8
 // output pieces for the store burst takes; it has compute to spare (6 waves measured the same, 4 a sixth slower);
 // N = 64 runs 12 waves (2 % faster than 16).  General kernels: 12 waves, the most that
@@ -644,15 +666,7 @@ int dispatch(const KArgs &a, uint32_t lane_syms, hipStream_t s)
         if (pairfit) return launch_as<64, 12, true>(a, 1, s);
         return lng ? launch_as<64, 12, false, false, true, 1>(a, 1, s) : launch_as<64, 12, false, false, false, 1>(a, 1, s);
     case 128:
-        if (pairfit) {
-            // Nine to eleven chunks per compute unit leave 8 waves a second round that is nearly empty: 12 waves take them in
-            // one, without registers for a burst (8.5 chunks 11.7 us against 12.8, 10 chunks 12.8 against 14.6, 11 chunks
-            // 13.6 against 14.0, but 12 chunks 14.3 against 14.2 and 18 chunks 18.7 against 17.9: the burst counts for more).
-            const int cus = device_cus();
-            const uint64_t each = cus > 0 ? (a.total_chunks + cus - 1) / cus : 0;
-            if (each > 8 && each <= 11) return launch_as<128, 12, true, false, false, 0>(a, 1, s);
-            return launch_as<128, 8, true>(a, 1, s);
-        }
+        if (pairfit) return pairfit_128(a, s);
         return lng ? launch_as<128, 12, false, false, true, 2>(a, 1, s) : launch_as<128, 12, false, false, false, 2>(a, 1, s);
     default: return ECF8_E_ARG;
     }

@@ -101,6 +101,25 @@ def test_sizes_around_one_round_of_waves(per_cu):
         assert torch.equal(out[:n], d_x) and bool((out[n:] == 0xA5).all())
 
 
+@pytest.mark.parametrize("per_wg,share", [(8, 0.75), (9.5, 0.75), (11.01, 0.75), (16, 0.5), (16.01, 0.5), (24.01, 0.5), (7, 0.375), (8.5, 0.375), (14, 0.375), (30, 0.375), (30, 0.38)])
+def test_sizes_around_the_rounds_of_a_confined_launch(per_wg, share):
+    """A launch confined to a part of the compute units, on either side of the rules that pick 12 waves: 8 to 11 chunks of 128
+    symbols per lane and workgroup anywhere, 17 to 24 on half of the compute units, 9 to 12 and any number above 16 on three eighths;
+    whole chunks and a ragged end, a batch of two."""
+    wgs = int(share * torch.cuda.get_device_properties(0).multi_processor_count)
+    chunks = int(per_wg * wgs)
+    for extra in (0, -5000):
+        n = chunks * 8192 + extra
+        d_x = synth.make_weight(1, n, 1.8, 0.02, chunks, scaling="tensor", device=DEV).reshape(-1)
+        cut = (n // 3 + 255) // 256 * 256
+        enc = [ecf8.ecf8_encode_gpu(p.clone(), 1, p.numel()) for p in (d_x[:cut], d_x[cut:])]
+        out = torch.full((n + 512,), 0xA5, dtype=torch.uint8, device=DEV)
+        batch = ecf8.Batch([h for h, _ in enc], [b for _, b in enc], [out[:cut], out[cut:n]])
+        batch.info.max_workgroups = wgs
+        ecf8.ecf8_decode_batched(batch)
+        assert torch.equal(out[:n], d_x) and bool((out[n:] == 0xA5).all())
+
+
 def _special_cases():
     fib = [1, 1]
     while len(fib) < 16:
