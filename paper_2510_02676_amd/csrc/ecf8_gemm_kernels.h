@@ -438,8 +438,8 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
     // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
-    // table first, since it is what the workgroup meets for (M = 16: 21.9 -> 21.45 us).  Not with four tiles of X and no
-    // scales, where X alone takes half of the registers and the metadata come first (30.8 us; in this order 31.4).
+    // table first, since it is what the workgroup meets for (M = 16: 21.0 -> 20.7 us; M = 32 25.5 -> 25.2, M = 64 with scales of W
+    // 34.4 -> 34.2).  Not with four tiles of X and no scales, where the metadata come first (30.0 us; in this order 30.7).
     constexpr bool EARLY = !(MT == 4 && SC == 0);
     u32x4 tv[TABLE_UNITS<NW>];
     if constexpr (EARLY) load_table<NW>(a, tid, tv);
@@ -738,9 +738,11 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
     XPieces<MT, N> x_cur;
-    // The order of ecf8_gemm_kernel, but for groups with scales and two tiles of X: six experts, M = 20, 119.7 us with the
-    // metadata first and 124.8 in this order, which gains 1.5 .. 3 % everywhere else.
-    constexpr bool EARLY = !(APART && MT == 2 && SC == 1);
+    // The order of ecf8_gemm_kernel, but not in groups with two tiles of X and scales of W or with two or four and no scales.
+    // Metadata first / this order, us: six experts, M = 20 and scales of W 117.7 / 123.4, no scales 112.0 / 114.0; M = 32 and no scales
+    // 124.8 / 131.7, M = 48 163.3 / 169.3.  Elsewhere this order: M = 48 and scales of W 188.7 / 181.7, M = 32 and scales of W and X 159.9 / 153.0,
+    // M = 4 84.0 / 83.3; 512 x 7168 split in K, M = 16 and all scales 14.1 / 14.0.
+    constexpr bool EARLY = !(APART && ((MT == 2 && SC == 1) || (MT > 1 && SC == 0)));
     u32x4 tv[TABLE_UNITS<NW>];
     if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (valid(cur)) {
