@@ -441,6 +441,9 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     // table first, since it is what the workgroup meets for (M = 16: 21.0 -> 20.7 us; M = 32 25.5 -> 25.2, M = 64 with scales of W
     // 34.4 -> 34.2).  Not with four tiles of X and no scales, where the metadata come first (30.0 us; in this order 30.7).
     constexpr bool EARLY = !(MT == 4 && SC == 0);
+    // lookups in front of the fetch behind them (quad_step_held): M = 16 20.7 against 21.0 us, but two tiles of X with scales of W
+    // 29.1 against 26.7
+    constexpr bool PINNED = !(MT == 2 && SC == 1);
     u32x4 tv[TABLE_UNITS<NW>];
     if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (n_steps > 0) {
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
             for (int Q = 0; Q < GPIECES / 2; Q++) {
                 uint32_t dwA[4], dwB[4];
 #pragma unroll
-                for (int t = 0; t < 4; t++) quad_step_held(smem, tbl, runs, dwA[t], dwB[t]);
+                for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
                 // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
                 const u32x4 wA = merge_piece(dwA, pl[Q]);
                 pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * Q));
@@ -652,7 +655,7 @@ struct Walk {
 // The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units
 // of them), table set-up included.  `parity` says which of the two reduction buffers comes next and is
 // carried on to the caller's next matrix.
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0, bool APART = false>
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0, bool APART = false, bool PINNED = true>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint64_t unit_stride,
                                           uint64_t my_units, uint32_t &parity)
 {
@@ -812,7 +815,7 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             for (int Q = 0; Q < GPIECES / 2; Q++) {
                 uint32_t dwA[4], dwB[4];
 #pragma unroll
-                for (int t = 0; t < 4; t++) quad_step_held(smem, tbl, runs, dwA[t], dwB[t]);
+                for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
                 // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
                 const u32x4 wA = merge_piece(dwA, pl[Q]);
                 pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * Q));
@@ -840,13 +843,13 @@ __device__ __forceinline__ uint64_t units_of_workgroup(uint64_t n_units)
     return blockIdx.x < n_units ? (n_units - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
 }
 
-template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0>
+template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, bool PINNED = true>
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::TOTAL];
     __shared__ uint32_t s_flag;                   // split K: the arrival count this workgroup drew
     uint32_t parity = 0;
-    anyk_walk<MT, NW, N, SC, SPLIT, ACC>(a, smem, &s_flag, blockIdx.x, gridDim.x,
+    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, PINNED>(a, smem, &s_flag, blockIdx.x, gridDim.x,
                                     units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)), parity);
 }
 
@@ -989,7 +992,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
         __syncthreads();                                // the last matrix's table and reduction buffers are out of use
         if (b0 < b1) {
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
-            else anyk_walk<MT, NW, N, SC, false, 0, true>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
+            else anyk_walk<MT, NW, N, SC, false, 0, true, !(MT == 4 && SC == 2)>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);     // M = 64: 297 us, pinned 306
         }
         pos = it.first_work + n_blocks * kchunks;       // on to the next matrix (or past `end`)
     }
@@ -1089,7 +1092,18 @@ int launch_fused(const GArgs &a, void *stream)
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
         if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // X pieces of two chunks: 8 waves' worth of registers
-        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
+        else {
+            // Four tiles of X with a scale per row and 128 columns crowd the registers: pinning the lookups (quad_step_held) pays only
+            // from seven chunks of a block per wave on, and with two blocks of rows or more per workgroup from four, or for two nearly
+            // full rounds.  us pinned / not, 14336 rows, M = 64: K = 1024 26.0 / 23.7, 2048 39.8 / 38.8, 3072 55.5 / 54.9, 3584 63.0 / 65.1,
+            // 4096 68.0 / 70.2, 4608 78.3 / 75.1, 5120 84.3 / 82.2, 6144 97.3 / 97.5, 8192 120.8 / 123.8, 11264 157.5 / 164.5, 16384 222.8 / 228.8;
+            // 4096 rows, M = 48: 1024 10.8 / 10.0, 4096 18.8 / 18.4, 5120 22.9 / 21.5, 8192 31.3 / 30.9, 14336 49.8 / 49.8; M = 64: 14336 55.8 / 56.6.
+            const uint64_t kchunks = a.K / 256;
+            const bool pinned = SCALED != 2 || ACC != 0 || kchunks >= 56 ||
+                                (a.rows / BLOCK_ROWS >= 2 * (uint64_t)grid && (kchunks >= 32 || (kchunks >= 14 && kchunks <= 16)));
+            if (pinned) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
+            else if constexpr (SCALED == 2 && ACC == 0) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC, false>), dim3(grid), dim3(8 * 64), 0, s, a);
+        }
         return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
     }
     if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_kernel<1, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);

@@ -329,6 +329,30 @@ def test_any_k_against_oracle(orc, rows, K, M):
     assert np.array_equal(y2.cpu().numpy().astype(np.float64), yref2)
 
 
+@pytest.mark.parametrize("rows,K", [(256, 3328), (256, 13824), (256, 14336), (8176, 3584), (8192, 3328), (8192, 3584), (8192, 4096), (8192, 4352), (8192, 7936),
+                                    (8192, 8192)])
+def test_four_tiles_of_x_with_group_scales(orc, rows, K):
+    """M > 32 with a scale per row and 128 columns of X, on either side of the sizes where the kernel with pinned lookups takes
+    over: 56 chunks of a block, and with two blocks per workgroup 14 to 16 or 32.  Bit for bit the twin on uncompressed weights; sampled
+    outputs against the oracle."""
+    M = 41
+    w = synth.make_weight(rows, K, 1.7, 0.02, 12, device=DEV)
+    x = synth.activations(M, K, seed=rows + K, device=DEV)
+    rng = np.random.default_rng(K)
+    ws = np.exp(rng.normal(0.0, 0.7, size=(rows // 128 + (rows % 128 != 0), K // 128))).astype(np.float32)
+    xs = np.exp(rng.normal(0.0, 0.5, size=(M, K // 128))).astype(np.float32)
+    d_ws, d_xs = torch.from_numpy(ws).to(DEV), torch.from_numpy(xs).to(DEV)
+    hdr, d_blob = ecf8.ecf8_encode_gpu(w, lane_syms=64, tile_rows=16)
+    fused = ecf8.ecf8_gemm_fp8_scaled(hdr, d_blob, x, d_ws, d_xs)
+    raw = ecf8.ecf8_gemm_fp8_raw_scaled(w, x, d_ws, d_xs)
+    torch.cuda.synchronize()
+    assert torch.equal(fused, raw)
+    wh, xh = w.cpu().numpy(), x.cpu().numpy()
+    for n in (0, 17, rows - 1):
+        yj, aj = orc.gemm_ref_scaled(xh, wh[n:n + 1], ws[n // 128:n // 128 + 1], xs)
+        _check(fused.cpu().numpy()[:, n:n + 1], yj, aj, "row %d of %dx%d" % (n, rows, K))
+
+
 @pytest.mark.parametrize("M", [3, 40])
 def test_any_k_block_scaled_and_full_size(orc, M):
     """The down projection of the 8B-class stack (4096 x 14336) with block scales: fused equals the twin on
