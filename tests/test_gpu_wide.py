@@ -157,6 +157,40 @@ def test_pairs_of_codewords_that_do_not_fit_the_table(fmt, lane_syms, cap):
         assert np.array_equal(got, x)                      # the codec's definition
 
 
+@pytest.mark.parametrize("share,cut,two", [(96, 0, False), (128, 0, False), (128, 1, False), (128, 3003, True), (160, 0, True), (1024, 4095, True), (1056, 0, False)])
+@pytest.mark.parametrize("lane_syms", [64, 128])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_shares_begun_in_turn(fmt, lane_syms, share, cut, two):
+    """Equal shares of a multiple of 32 chunks, 128 or more (64 of them from 1024 on), are begun one group of 32 later by each
+    workgroup; others are not.  Whole tensors and a ragged last chunk in the last share, one tensor and a batch of two whose border
+    lies inside a share, and chunks that do not fit a wave's stage before and behind the place where a share is begun."""
+    rng = np.random.default_rng(share + cut)
+    chunk, wgs = 64 * lane_syms, 5 if share < 1000 else 2
+    n = chunk * share * wgs - cut
+    s = rng.choice(4, size=n, p=[0.4, 0.3, 0.2, 0.1])
+    rare = rng.random(n) < 0.002
+    s[rare] = rng.integers(4, 24, int(rare.sum()))
+    for c in (3, share + 31, share + 33, 2 * share - 2):
+        s[c * chunk:(c + 1) * chunk] = rng.integers(4, 24, chunk)
+    if fmt == BF16:
+        x = ((s + 100).astype(np.uint16) << 7) | rng.integers(0, 128, n).astype(np.uint16) | (rng.integers(0, 2, n).astype(np.uint16) << 15)
+    else:
+        x = ((s + 4).astype(np.uint8) << 2) | rng.integers(0, 4, n).astype(np.uint8) | (rng.integers(0, 2, n).astype(np.uint8) << 7)
+    border = chunk * (share + share // 2) if two else n
+    blobs = [ecfw.ecfw_encode(fmt, p, 1, p.size, lane_syms=lane_syms, group_chunks=1) for p in (x[:border], x[border:]) if p.size]
+    h = blobs[0].header
+    starts = blobs[0].numpy()[h.off_chunk_bit:h.off_chunk_bit + 8 * (h.n_chunks + 1)].view(np.uint64).astype(np.int64)
+    assert (np.diff(starts) // 8 > (8 if fmt == BF16 else 5) * 8 * lane_syms + 64).any() and h.max_code_len <= 12
+    want = torch.from_numpy(x.view(np.uint8)).to(DEV)
+    out = torch.full((x.nbytes + 512,), 0xA5, dtype=torch.uint8, device=DEV)
+    at = border * x.itemsize
+    batch = ecfw.WBatch([b.header for b in blobs], [b.to(DEV) for b in blobs], [out[:at], out[at:x.nbytes]][:len(blobs)])
+    batch.info.max_workgroups = wgs
+    assert batch.info.total_chunks == share * wgs
+    ecfw.ecfw_decode_batched(batch)
+    assert torch.equal(out[:x.nbytes], want) and bool((out[x.nbytes:] == 0xA5).all())
+
+
 @pytest.mark.parametrize("fmt", [E5M2, BF16])
 def test_few_workgroups_and_caller_buffer(orc, fmt):
     x = _rand_elems(fmt, 64 * 128 * 50 + 9, 3)
