@@ -638,7 +638,7 @@ struct PCfg {
     // a lane of a ragged last chunk reads up to N / 2 codewords past its bits
     static constexpr int TOTAL = OFF_STAGE + WAVES * STAGE + N / 2 * WTB / 8 + 32;
     static_assert(STAGE % 16 == 0 && OFF_STAGE % 16 == 0, "16-byte LDS stores");
-    static_assert(PIECES % 4 == 0, "two runs of whole pieces, in half bursts");
+    static_assert(PIECES % 4 == 0, "two runs of whole pieces, in bursts of two or more");
     static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
     static_assert(WAVES >= 4, "the code set-up ranks 256 symbols with four wavefronts");
 };
@@ -650,8 +650,8 @@ constexpr uint32_t TURN_CHUNKS = 32;
 
 // The loop of the E4M3 decoder (ecf8_decode.hip) over these tables: metadata two chunks ahead, payload one chunk ahead in
 // registers refilled in place, full chunks only, so that the stores of a chunk are unconditional and the wait for a
-// prefetch never drains them; HALF: pieces leave in two bursts, else in one.
-template <int FMT, int N, int WAVES, bool HALF, bool TURN>
+// prefetch never drains them; PER: pieces of each run that leave together.
+template <int FMT, int N, int WAVES, int PER, bool TURN>
 __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
 {
     using C = PCfg<FMT, N, WAVES>;
@@ -789,7 +789,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                     v.w >>= 8 * F::ELEM;
                 }
             };
-            constexpr int H = PIECES / 2, BURST = CUT ? 1 : HALF ? (H < 2 ? H : 2) : H;
+            constexpr int H = PIECES / 2, BURST = CUT ? 1 : PER;
+            static_assert(H % PER == 0, "whole bursts");
 #pragma unroll
             for (int q0 = 0; q0 < H; q0 += BURST) {
                 u32x4 oA[BURST], oB[BURST];
@@ -901,17 +902,24 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
     }
 }
 
+// one per compute unit, fewer where the caller or the number of chunks says so; 0: no device
+uint64_t workgroups(const BArgs &a, uint32_t max_workgroups)
+{
+    const int cus = device_cus();
+    if (cus <= 0) return 0;
+    uint64_t grid = (uint64_t)cus;
+    if (max_workgroups && max_workgroups < grid) grid = max_workgroups;
+    return grid < a.total_chunks ? grid : a.total_chunks;
+}
+
 // The share from which TURN pays, its multiple, and what it gives (matrices of 14336 x 4096, us without / with): BF16, 224 chunks per
 // workgroup 151.7 / 145.6, 448 294.5 / 278.5, 896 588.7 / 562.5, layout without groups 448 331 / 320; E5M2, 224 177.0 / 171.3, 448 342 / 326.
 // Not for others: BF16, 56 chunks 42.3 / 44.4, 64 (8192 x 8192) 49.1 / 51.1, 67.5 (5120 x 13824) 48.8 / 53.1, 504 314.2 / 317.6.
 template <int WAVES, class K>
 int launch_as(K kernel, const BArgs &a, uint32_t max_workgroups, hipStream_t stream, K turned = nullptr)
 {
-    int cus = device_cus();
-    if (cus <= 0) return ECF8_E_HIP;
-    uint64_t grid = (uint64_t)cus;
-    if (max_workgroups && max_workgroups < grid) grid = max_workgroups;
-    if (grid > a.total_chunks) grid = a.total_chunks;
+    const uint64_t grid = workgroups(a, max_workgroups);
+    if (grid == 0) return ECF8_E_HIP;
     const uint64_t share = a.total_chunks / grid;
     if (turned && share * grid == a.total_chunks && share >= 4 * TURN_CHUNKS && share % (share >= 1024 ? 64 : TURN_CHUNKS) == 0) kernel = turned;
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, a);
@@ -929,12 +937,17 @@ int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, h
     //                  bursts 8 waves 144.8, 12 waves 145, 16 waves 149
     //   E5M2, N = 128  12 waves, two bursts 90.0 us; 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
     // i.e. BF16 is at the memory wall and wants its stores together, E5M2 wants the waves to hide its look-ups.
-    if constexpr (FMT == ECFW_FMT_BF16)
-        return N == 64 ? launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, false, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 8, false, true>)
-                       : launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, true, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 8, true, true>);
-    else
-        return N == 64 ? launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, false, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 12, false, true>)
-                       : launch_as<12>(ecfw_decode_kernel<FMT, 128, 12, true, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 12, true, true>);
+    if constexpr (FMT == ECFW_FMT_BF16) {
+        // N = 128 has registers for two bursts of a chunk, which pay from the third round of chunks on.  Four bursts / two, us, by chunks per
+        // workgroup: 8 19.3 / 19.5, 16 27.9 / 28.6, 17 32.7 / 32.4, 25 44.6 / 42.6, 48 75.3 / 73.3, 104 147.3 / 139.9 (one burst, eight matrices 296.9 / 295.0)
+        const uint64_t wgs = workgroups(a, max_workgroups), each = wgs ? (a.total_chunks + wgs - 1) / wgs : 0;
+        if (N == 64) return launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 8, 4, true>);
+        if (each <= 16) return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 2, false>, a, max_workgroups, s);
+        return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 8, 4, true>);
+    } else {
+        return N == 64 ? launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 2, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 12, 2, true>)
+                       : launch_as<12>(ecfw_decode_kernel<FMT, 128, 12, 2, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 12, 2, true>);
+    }
 }
 
 int launch(const BArgs &a, uint32_t fmt, uint32_t N, uint32_t max_code_len, uint32_t max_workgroups, void *stream)

@@ -191,6 +191,19 @@ def test_shares_begun_in_turn(fmt, lane_syms, share, cut, two):
     assert torch.equal(out[:x.nbytes], want) and bool((out[x.nbytes:] == 0xA5).all())
 
 
+@pytest.mark.parametrize("per_wg", [8, 9, 12, 13, 16, 17, 24, 25, 30, 31])
+@pytest.mark.parametrize("lane_syms", [64, 128])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_rounds_of_chunks(fmt, lane_syms, per_wg):
+    """Few chunks per workgroup, on either side of the sizes where another number of waves or of bursts takes over; whole
+    chunks and a ragged end."""
+    for cut in (0, 777):
+        x = _rand_elems(fmt, 64 * lane_syms * per_wg * 3 - cut, per_wg + cut)
+        blob = ecfw.ecfw_encode(fmt, x, 1, x.size, lane_syms=lane_syms)
+        got, guards = _gpu_decode_guarded(blob, max_workgroups=3)
+        assert guards and np.array_equal(got, x)                      # the codec's definition
+
+
 @pytest.mark.parametrize("fmt", [E5M2, BF16])
 def test_few_workgroups_and_caller_buffer(orc, fmt):
     x = _rand_elems(fmt, 64 * 128 * 50 + 9, 3)
