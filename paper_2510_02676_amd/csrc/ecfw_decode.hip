@@ -941,6 +941,10 @@ int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, h
         // N = 128 has registers for two bursts of a chunk, which pay from the third round of chunks on.  Four bursts / two, us, by chunks per
         // workgroup: 8 19.3 / 19.5, 16 27.9 / 28.6, 17 32.7 / 32.4, 25 44.6 / 42.6, 48 75.3 / 73.3, 104 147.3 / 139.9 (one burst, eight matrices 296.9 / 295.0)
         const uint64_t wgs = workgroups(a, max_workgroups), each = wgs ? (a.total_chunks + wgs - 1) / wgs : 0;
+        // N = 64: 12 waves where they save one of the first four rounds of chunks.  8 / 12 waves, us, by chunks per workgroup: 9 15.9 / 13.7,
+        // 12 17.0 / 15.7, 13 17.6 / 17.7, 16 19.1 / 19.6, 17 21.3 / 20.4, 20 21.3 / 21.0, 24 23.0 / 23.1, 25 24.6 / 23.7, 28 26.6 / 25.9, 30 27.5 / 27.1,
+        // 32 27.7 / 27.9, 52 39.3 / 40.1
+        if (N == 64 && each <= 30 && (each + 11) / 12 < (each + 7) / 8) return launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 4, false>, a, max_workgroups, s);
         if (N == 64) return launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 8, 4, true>);
         if (each <= 16) return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 2, false>, a, max_workgroups, s);
         return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 8, 4, true>);
