@@ -104,6 +104,22 @@ def test_full_size_matrix(orc, fmt):
     _same_as_cpu(orc, fmt, x, 14336, 4096, oracle_read=False)
 
 
+@pytest.mark.parametrize("chunks,extra", [(1024, 0), (1024, 1), (2048, -1), (65536, 0), (65536, 1), (65536 + 8192, 5)])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_many_chunks(fmt, chunks, extra):
+    """The chunk totals are summed 1024 per workgroup up to 65536 of them, beyond that by one workgroup 8192 at a time, and lie in
+    chunk_bit in another way: whole and nearly whole slices, one chunk more, the first sizes past the limit."""
+    n = chunks * 4096 + extra
+    x = np.resize(_rand_elems(fmt, (1 << 20) + 12345, chunks + extra), n)
+    opts = dict(lane_syms=64, max_code_len=16 if extra else 0)
+    want = ecfw.ecfw_encode(fmt, x, 1, n, **opts)
+    buf = torch.full((want.size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+    hdr, d_blob = ecfw.ecfw_encode_gpu(fmt, _to_dev(fmt, x), 1, n, d_blob=buf, **opts)
+    torch.cuda.synchronize()
+    assert bytes(hdr) == bytes(want.header) and hdr.n_chunks == chunks + (extra > 0)
+    assert torch.equal(d_blob.cpu(), torch.from_numpy(want.numpy())) and bool((buf[want.size:] == 0xA5).all())
+
+
 def test_more_chunks_than_one_launch_takes():
     """17 GB of E5M2, 64 symbols per lane: 2^22 chunks and some.  The metadata pass takes one launch per 2^20 workgroups.  Every group
     of 32 chunks holds the same elements, whose code bits are a whole number of 16-byte units, so each section of the
