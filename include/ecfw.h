@@ -9,9 +9,10 @@
  *   ECFW_FMT_BF16  2 bytes / element: sign(1) exponent(8) mantissa(7), 256 symbols
  * (BF16 elements are little-endian 16-bit words.)  With these alphabets plain
  * Huffman codes grow past the 16 bits Section 3.1 allows a codeword, so the code
- * is the cheapest one under a cap (package-merge); with the default cap of 12,
- * the index width of the decoder's lookup table, every codeword resolves in one
- * lookup (measured cost on synthetic weights: 0.004 bits per element).
+ * is the cheapest one under a cap (package-merge); under the default cap of 12 the
+ * decoder resolves two codewords in one lookup, or, where the two are too long
+ * for its table together, in two (measured cost of the cap on synthetic weights:
+ * 0.004 bits per element).
  *
  * E5M2, second way of storing it (declared here, implemented by ecf8.h): the FP8
  * container of ecf8.h never interprets its bytes -- it codes bits 6..3 of a byte and
@@ -20,10 +21,11 @@
  * coded symbol and the sign, the lowest exponent bit and the mantissa in the raw
  * nibble; ecf8_decode / ecf8_decode_batched return the exact bytes.  One exponent
  * bit goes uncoded (0.750 of the raw size against 0.726 for ECFW_FMT_E5M2 on the
- * synthetic weights), and the decoder is the pair-table one of ecf8.h, two symbols
- * per lookup, which this chip runs about 1.4 x faster than the one-symbol-per-lookup
- * decoder a 32-symbol alphabet needs.  Use ECFW_FMT_E5M2 for the smaller blob, the
- * FP8 container for the faster decode.
+ * synthetic weights), and the decoder is that of ecf8.h, whose capped codes always
+ * have two symbols in one lookup: one launch over eight 14336 x 4096 matrices takes
+ * 153 us against 178 us for ECFW_FMT_E5M2, 1.16 x as fast.  Use ECFW_FMT_E5M2 for the
+ * smaller blob, the FP8 container for the somewhat faster decode and for what only
+ * ecf8.h has (the fused products).
  *
  * Boundary rules are those of ecf8.h: plain pointers and sizes, "host" = CPU
  * memory, "device" = HIP memory of the current device owned by the caller, no
@@ -157,7 +159,8 @@ int ecfw_blob_validate(const void *blob_host, uint64_t size);
 /*
  * ecfw_decode (Section 3.2 / Algorithm 1 for the formats above, restructured as in
  * ecf8_decode: one wavefront per chunk, stream staged in LDS, two independent runs
- * per lane, one 12-bit lookup per codeword, 16-byte stores).
+ * per lane, two codewords per lookup for codes of at most 12 bits and one for
+ * longer ones, 16-byte stores).
  * d_blob: DEVICE copy of the whole blob, 256-byte aligned.  hdr: HOST header of
  * that blob (from ecfw_blob_describe).  d_out: DEVICE buffer of out_capacity
  * bytes >= n_elem * bytes per element, 16-byte aligned; receives the exact

@@ -104,8 +104,7 @@ __device__ __forceinline__ void pair_second_level(uint32_t bits, uint32_t &e, ui
     n = l1 + (r2 >> 8);
 }
 
-// Builds the pair table and the per-symbol (length, code) arrays in LDS from
-// the 16 code lengths.  `tmp` is TBL_ENTRIES u16 of scratch LDS.
+// The per-symbol (length, code) arrays in LDS from the 16 code lengths: canonical codewords, first bit most significant.
 __device__ __forceinline__ void build_symbol_arrays(uint64_t len_lo, uint64_t len_hi, uint32_t *s_len,
                                                     uint32_t *s_code, int tid)
 {
@@ -123,9 +122,10 @@ __device__ __forceinline__ void build_symbol_arrays(uint64_t len_lo, uint64_t le
     }
 }
 
-// Any code, NT threads.  `tmp` first receives the table of first codewords: every index whose low bits spell a codeword, as
-// the entry it has without a second one (0 where none of at most TB bits does), scattered symbol by symbol with lengths and
-// codes in scalar registers; an entry's other half is then the first codeword that many bits on.
+// The pair table and the symbol arrays of any code, NT threads.  `tmp` is TBL_ENTRIES u16 of scratch LDS.  It first receives
+// the table of first codewords: every index whose low bits spell a codeword, as the entry it has without a second one (0 where
+// none of at most TB bits does), scattered symbol by symbol with lengths and codes in scalar registers; an entry's other half is
+// then the first codeword that many bits on.
 // 256 x 256 weights, codewords of up to 15 bits: 14.6 us with entries one by one (two dependent reads and some 25 operations each), 12.6 now;
 // with the loop over the symbols rolled, 13.5.
 template <int NT>
@@ -168,7 +168,7 @@ __device__ __forceinline__ void build_tables(uint64_t len_lo, uint64_t len_hi, u
 // The codeword of a short index is found by its place in the code space: symbols in canonical order begin at sums of
 // 2^(7 - length), and an index belongs to the last one that begins at or before it.
 // About 270 vector operations per thread of an 8-wave workgroup: a single decode of 256 x 256 weights 14.4 -> 8.1 us against
-// the general builder below (8.7 with every symbol matched against every index), the fused product with a 240 x 768 matrix
+// the general builder above (8.7 with every symbol matched against every index), the fused product with a 240 x 768 matrix
 // 11.3 -> 8.1 us per call.
 template <int NW>
 __device__ __forceinline__ void build_pair_table(uint64_t len_lo, uint64_t len_hi, uint16_t *tbl, uint32_t *tmp, int lane, int wave)

@@ -6,8 +6,8 @@
 //   fill 0 (256 bytes) -> histogram -> [host: 128 bytes back, code + layout]
 //   -> metadata and plane (one wave per chunk: lane_bits, the chunk's total, its nibble plane; the first
 //   workgroups write the header, the pair table and the padding between sections) -> prefix sum of the
-//   totals (one workgroup) -> stream (one wave per chunk assembles its span in LDS and copies it out; the two
-//   dwords a span may share with its neighbours go out with atomic OR).
+//   totals (a workgroup per 1024 chunks; one in all above 65536 of them) -> stream (one wave per chunk assembles its span
+//   in LDS and copies it out; the two dwords a span may share with its neighbours go out with atomic OR).
 // The input is read three times (histogram, metadata, stream), the last two mostly from the memory-side cache.
 // No scratch memory: the histogram is counted into the header's freq[] field and the chunk
 // totals into chunk_bit[], both part of the output.

@@ -11,7 +11,7 @@
 //    pairs that do not fit it take a branch-free second level.  The launch of a layer of seven matrices (218 M elements)
 //    with one codeword per lookup and the lanes' bits moved to bank-private LDS columns first took 107.5 us for E5M2,
 //    bound by LDS and vector work; now 90 (376 MB: 4.2 TB/s, two thirds of what is left is vector work).  BF16
-//    was and is at the memory wall: 140.5 -> 138.7 us (735 MB: 5.3 TB/s);
+//    was and is at the memory wall, 139 .. 141 us (735 MB: 5.3 TB/s);
 //  * codes with longer codewords (cap 13..16, ecfw_long_decode_kernel) keep one codeword per lookup and
 //    a canonical first-code comparison per length, in a rarely taken branch;
 //  * the remaining bits come from planes laid out so that whole output words are
