@@ -643,15 +643,10 @@ struct PCfg {
     static_assert(WAVES >= 4, "the code set-up ranks 256 symbols with four wavefronts");
 };
 
-// Equal shares of a multiple of 32 chunks lie a multiple of 256 KiB of output apart, and workgroups in step with each other then
-// meet in the same memory channels.  In such launches (TURN, see launch_as) every workgroup begins its share one group of
-// 32 chunks later than the one before it, and goes round the share's end.
-constexpr uint32_t TURN_CHUNKS = 32;
-
 // The loop of the E4M3 decoder (ecf8_decode.hip) over these tables: metadata two chunks ahead, payload one chunk ahead in
 // registers refilled in place, full chunks only, so that the stores of a chunk are unconditional and the wait for a
 // prefetch never drains them; PER: pieces of each run that leave together.
-template <int FMT, int N, int WAVES, int PER, bool TURN>
+template <int FMT, int N, int WAVES, int PER>
 __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
 {
     using C = PCfg<FMT, N, WAVES>;
@@ -684,12 +679,6 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         const Place<FMT, N> place(a);
         const bool ragged_tail = c_end == a.n_chunks && a.n_elem % place.E != 0;
         const uint64_t fast_end = ragged_tail ? c_end - 1 : c_end;
-        // the chunk whose turn is c's
-        const uint32_t n_fast = (uint32_t)(fast_end - c_begin), turn = TURN && n_fast ? uniform32(blockIdx.x * TURN_CHUNKS % n_fast) : 0u;
-        auto chunk_of = [&](uint64_t c) -> uint64_t {
-            if constexpr (!TURN) return c;
-            return c + turn < fast_end ? c + turn : c + turn - n_fast;
-        };
 
         __syncthreads();                               // every wave is done with the previous tensor's tables
         if (tid == 0) { *s_ticket = 2 * WAVES; *s_oversize = 0; *s_tail = 0; }
@@ -733,7 +722,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         auto load_first = [&](uint64_t c) {
             m_cur = load_meta(a, c, lane);
             m_next = m_cur;
-            if (nxt < fast_end) m_next = load_meta(a, chunk_of(nxt), lane);
+            if (nxt < fast_end) m_next = load_meta(a, nxt, lane);
             const uint64_t e0 = place.base(c) + (uint64_t)lane * P;
 #pragma unroll
             for (int q = 0; q < PIECES; q++) rest[q] = load_rest(e0 + q * (uint64_t)place.stride(c));
@@ -742,7 +731,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         // the ragged last chunk goes first, to the wave it would fall to in turn, its stores cut at the tensor's end
         const bool tail_here = ragged_tail && (uint32_t)wave == (uint32_t)(c_end - 1 - c_begin) % WAVES;
         if (tail_here) load_first(c_end - 1);
-        else if (cur < fast_end) load_first(chunk_of(cur));
+        else if (cur < fast_end) load_first(cur);
         if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;
         build_code<FMT>(my_len, (uint32_t *)(smem + C::OFF_WCNT), smem + C::OFF_SORTED, (uint32_t *)(smem + C::OFF_CNT),
                         (uint32_t *)(smem + C::OFF_FIRST), (uint32_t *)(smem + C::OFF_OFFS), tbl, tid, WAVES * 64);
@@ -840,7 +829,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
             } else if (lane == 0) {
                 *s_tail = 1;
             }
-            if (cur < fast_end) load_first(chunk_of(cur));
+            if (cur < fast_end) load_first(cur);
         }
         if (cur < fast_end) {
             // drain the prologue's loads here (vmcnt(0)), so that the wait at the loop head is decided by the back edge
@@ -855,21 +844,20 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                 for (int k = 0; k < SEGS; k++)
                     if (lane16 + 1024 * k < (uint32_t)STAGE) *(u32x4 *)(stage + lane16 + 1024 * k) = seg[k];
                 const bool has_next = nxt < fast_end;
-                const uint64_t c_cur = chunk_of(cur);
                 Meta m_next2 = m_next;
                 if (has_next) {
                     load_stream(m_next, seg);
                     nn = draw();
-                    if (nn < fast_end) m_next2 = load_meta(a, chunk_of(nn), lane);
+                    if (nn < fast_end) m_next2 = load_meta(a, nn, lane);
                 }
                 if (!staged && lane == 0) {
                     const uint32_t at = __hip_atomic_fetch_add(s_oversize, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = (uint32_t)(c_cur - c_begin);
+                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = (uint32_t)(cur - c_begin);
                 }
                 // a chunk that was not staged decodes stale bits (redone after the loop), its runs pinned to the stage's start
-                const uint64_t c_rest = has_next ? chunk_of(nxt) : c_cur;          // after the last chunk: its own rest again, not a branch
+                const uint64_t c_rest = has_next ? nxt : cur;          // after the last chunk: its own rest again, not a branch
                 decode_store(std::true_type{}, std::false_type{}, stage_off * 8 + (staged ? bit_in : 64u), staged ? m_cur.lb : 0u,
-                             place.base(c_cur) + (uint64_t)lane * P, place.stride(c_cur), place.base(c_rest) + (uint64_t)lane * P, place.stride(c_rest));
+                             place.base(cur) + (uint64_t)lane * P, place.stride(cur), place.base(c_rest) + (uint64_t)lane * P, place.stride(c_rest));
                 if (!has_next) break;
                 m_cur = m_next;
                 m_next = m_next2;
@@ -912,16 +900,11 @@ uint64_t workgroups(const BArgs &a, uint32_t max_workgroups)
     return grid < a.total_chunks ? grid : a.total_chunks;
 }
 
-// The share from which TURN pays, its multiple, and what it gives (matrices of 14336 x 4096, us without / with): BF16, 224 chunks per
-// workgroup 151.7 / 145.6, 448 294.5 / 278.5, 896 588.7 / 562.5, layout without groups 448 331 / 320; E5M2, 224 177.0 / 171.3, 448 342 / 326.
-// Not for others: BF16, 56 chunks 42.3 / 44.4, 64 (8192 x 8192) 49.1 / 51.1, 67.5 (5120 x 13824) 48.8 / 53.1, 504 314.2 / 317.6.
 template <int WAVES, class K>
-int launch_as(K kernel, const BArgs &a, uint32_t max_workgroups, hipStream_t stream, K turned = nullptr)
+int launch_as(K kernel, const BArgs &a, uint32_t max_workgroups, hipStream_t stream)
 {
     const uint64_t grid = workgroups(a, max_workgroups);
     if (grid == 0) return ECF8_E_HIP;
-    const uint64_t share = a.total_chunks / grid;
-    if (turned && share * grid == a.total_chunks && share >= 4 * TURN_CHUNKS && share % (share >= 1024 ? 64 : TURN_CHUNKS) == 0) kernel = turned;
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, a);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
@@ -938,19 +921,19 @@ int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, h
     //   E5M2, N = 128  12 waves, two bursts 90.0 us; 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
     // i.e. BF16 is at the memory wall and wants its stores together, E5M2 wants the waves to hide its look-ups.
     if constexpr (FMT == ECFW_FMT_BF16) {
-        // N = 128 has registers for two bursts of a chunk, which pay from the third round of chunks on.  Four bursts / two, us, by chunks per
-        // workgroup: 8 19.3 / 19.5, 16 27.9 / 28.6, 17 32.7 / 32.4, 25 44.6 / 42.6, 48 75.3 / 73.3, 104 147.3 / 139.9 (one burst, eight matrices 296.9 / 295.0)
         const uint64_t wgs = workgroups(a, max_workgroups), each = wgs ? (a.total_chunks + wgs - 1) / wgs : 0;
         // N = 64: 12 waves where they save one of the first four rounds of chunks.  8 / 12 waves, us, by chunks per workgroup: 9 15.9 / 13.7,
         // 12 17.0 / 15.7, 13 17.6 / 17.7, 16 19.1 / 19.6, 17 21.3 / 20.4, 20 21.3 / 21.0, 24 23.0 / 23.1, 25 24.6 / 23.7, 28 26.6 / 25.9, 30 27.5 / 27.1,
         // 32 27.7 / 27.9, 52 39.3 / 40.1
-        if (N == 64 && each <= 30 && (each + 11) / 12 < (each + 7) / 8) return launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 4, false>, a, max_workgroups, s);
-        if (N == 64) return launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 8, 4, true>);
-        if (each <= 16) return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 2, false>, a, max_workgroups, s);
-        return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 4, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 8, 4, true>);
+        if (N == 64 && each <= 30 && (each + 11) / 12 < (each + 7) / 8) return launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 4>, a, max_workgroups, s);
+        if (N == 64) return launch_as<8>(ecfw_decode_kernel<FMT, 64, 8, 4>, a, max_workgroups, s);
+        // N = 128 has registers for two bursts of a chunk, which pay from the third round of chunks on.  Four bursts / two, us, by chunks
+        // per workgroup: 8 19.3 / 19.5, 16 27.9 / 28.6, 17 32.7 / 32.4, 25 44.6 / 42.6, 48 75.3 / 73.3, 104 147.3 / 139.9
+        if (each <= 16) return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 2>, a, max_workgroups, s);
+        return launch_as<8>(ecfw_decode_kernel<FMT, 128, 8, 4>, a, max_workgroups, s);
     } else {
-        return N == 64 ? launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 2, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 64, 12, 2, true>)
-                       : launch_as<12>(ecfw_decode_kernel<FMT, 128, 12, 2, false>, a, max_workgroups, s, ecfw_decode_kernel<FMT, 128, 12, 2, true>);
+        return N == 64 ? launch_as<12>(ecfw_decode_kernel<FMT, 64, 12, 2>, a, max_workgroups, s)
+                       : launch_as<12>(ecfw_decode_kernel<FMT, 128, 12, 2>, a, max_workgroups, s);
     }
 }
 

@@ -160,10 +160,9 @@ def test_pairs_of_codewords_that_do_not_fit_the_table(fmt, lane_syms, cap):
 @pytest.mark.parametrize("share,cut,two", [(96, 0, False), (128, 0, False), (128, 1, False), (128, 3003, True), (160, 0, True), (1024, 4095, True), (1056, 0, False)])
 @pytest.mark.parametrize("lane_syms", [64, 128])
 @pytest.mark.parametrize("fmt", [E5M2, BF16])
-def test_shares_begun_in_turn(fmt, lane_syms, share, cut, two):
-    """Equal shares of a multiple of 32 chunks, 128 or more (64 of them from 1024 on), are begun one group of 32 later by each
-    workgroup; others are not.  Whole tensors and a ragged last chunk in the last share, one tensor and a batch of two whose border
-    lies inside a share, and chunks that do not fit a wave's stage before and behind the place where a share is begun."""
+def test_shares_of_many_chunks(fmt, lane_syms, share, cut, two):
+    """96 to 1056 chunks per workgroup: whole tensors and a ragged last chunk in the last share, one tensor and a batch of two whose
+    border lies inside a share, and chunks that do not fit a wave's stage near the borders of the shares."""
     rng = np.random.default_rng(share + cut)
     chunk, wgs = 64 * lane_syms, 5 if share < 1000 else 2
     n = chunk * share * wgs - cut
