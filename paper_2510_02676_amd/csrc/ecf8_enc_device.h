@@ -93,8 +93,8 @@ inline void launch_scan(uint64_t chunk_bit, uint64_t n_chunks, uint64_t stream, 
     hipLaunchKernelGGL(scan_kernel, dim3(grid), dim3(1024), 0, s, chunk_bit, n_chunks, stream);
 }
 
-// The metadata kernels take a workgroup per four chunks, and a launch must stay below 2^32 work-items in all: from 2^26 chunks
-// on (2^37 weights at 32 symbols per lane) they take several launches, each of at most this many workgroups of 256 threads.
+// The metadata kernels take a workgroup of 256 threads per four chunks.  A launch must stay below 2^32 work-items, which a single one
+// would pass at 2^26 chunks (2^37 weights at 32 symbols per lane): they take as many as they need, of at most this many workgroups.
 constexpr uint64_t META_BLOCKS = 1 << 20;
 
 // The positions of chunk c's first and last bit, the latter written back plain.
