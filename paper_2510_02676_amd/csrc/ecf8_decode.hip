@@ -611,9 +611,10 @@ int launch_as(const KArgs &a, int wgs_per_cu, hipStream_t s)
     if (cus <= 0) return ECF8_E_HIP;
     // Few chunks are spread over the compute units, a workgroup each: a wave alone on its compute unit gets through a
     // chunk's steps faster, and the chunks' loads start at more places (128 chunks of 128 symbols per lane: 16 full
-    // workgroups 9.8 us, 128 workgroups with one chunk each 8.4; 1024 chunks 9.1 / 8.3).  Beside a consumer on another stream too, 24
-    // layers of 128 chunks decoded ahead: beside copies 825 / 753 us, 4096^3 products 2797 / 2741, products with one weight matrix 853 / 807;
-    // layers of 512 .. 1024 chunks 858 / 791, 2811 / 2833, 881 / 887.
+    // workgroups 9.8 us, 128 workgroups with one chunk each 8.4; 1024 chunks 9.1 / 8.3).  Beside a consumer on another stream, 24
+    // layers decoded ahead, means of five runs, full workgroups / a chunk each: 128 chunks beside copies 823 / 752 us, 4096^3 products
+    // 2832 / 2776, one product with a weight matrix 798 / 789; 512 chunks 851 / 787, 2845 / 2865, 873 / 881; 1024 chunks 867 / 817,
+    // 2843 / 2872, 881 / 906.  It costs up to 3 % there beside products and gives 6 .. 9 % beside copies.
     uint64_t want = a.total_chunks;
     uint64_t cap = (uint64_t)cus * wgs_per_cu;
     if (a.max_workgroups && a.max_workgroups < cap) cap = a.max_workgroups;

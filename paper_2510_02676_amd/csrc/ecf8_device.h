@@ -357,8 +357,9 @@ struct HeldRuns {
 // the way the general kernels measured faster on windows fetched per step).  It reads up to 8 bytes past the dwords of a
 // window and 4 before them: the caller's LDS map has something there.
 // PINNED: no LDS access moves across the first lookups, which keeps them in front of the next dwords' fetch; without it the
-// scheduler places that fetch among the products' other work.  Worth up to 3 % to the row-tiled decode and the fused
-// products, nothing measurable to a layer in the linear layout; where it costs instead, the kernel says so.
+// scheduler places that fetch among the products' other work.  Worth 1 .. 4 % to some fused products (14336 x 4096, M = 16: 21.0 -> 20.8 us;
+// 14336 x 11264, M = 64, group scales: 164.8 -> 157.7) and nothing to the decode (a layer 78.1 us, row-tiled 83.8, with and
+// without); where it costs instead, the kernel says so.
 template <bool PINNED = true>
 __device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint16_t *tbl, HeldRuns &r, uint32_t &outA, uint32_t &outB)
 {
