@@ -39,8 +39,11 @@ struct GCfg {
     static constexpr int BPB = (MT == 1 && KPW == 1) ? 4 : 1;
     static constexpr int RED_BUFS = BPB == 1 ? 2 : BPB;
     static constexpr int TOTAL = OFF_RED + RED_BUFS * RED_BYTES;
+    // The any-K kernels give all that is left of the LDS to slots of 16 x 16 MT partial sums (see anyk_walk).
+    static constexpr uint32_t SLOTS = (160 * 1024 - 64 - OFF_RED) / (MT * 1024);
+    static constexpr int ANYK_TOTAL = OFF_RED + (int)SLOTS * MT * 1024;
     static_assert(NW * STAGE >= 512, "table-build scratch");
-    static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
+    static_assert(TOTAL <= 160 * 1024 && SLOTS >= NW, "LDS of one gfx950 CU");
 };
 
 struct GArgs {
@@ -253,6 +256,31 @@ __device__ __forceinline__ void reduce_parked(const f32x4 *red, const GArgs &a, 
 #pragma unroll
         for (int w = 0; w < NW; w++) sum += ((const float *)&red[(j * NW + w) * 64 + l])[r];
         const uint32_t m = 4 * (l >> 4) + r;
+        if (m < a.M) {
+            if (SCALED && a.d_xs && a.xs_cols == 1) sum *= ((const GLOBAL float *)a.d_xs)[m];
+            Y[(uint64_t)m * a.rows + (first + j * stride) * BLOCK_ROWS + (l & 15)] = sum;
+        }
+    }
+}
+
+// reduce_block for a batch of `count` blocks of rows first, first + stride, ...: the waves have parked block j's partial sums in
+// slots slots * j, slots * j + 1, ... of `red`, one per place of a chunk in the deal (its number modulo NW), whoever had it; the
+// caller's barriers lie around this.  Summed in that order, which is reduce_block's.
+template <int MT, int NW, bool SCALED>
+__device__ __forceinline__ void reduce_batch(const f32x4 *red, const GArgs &a, uint64_t first, uint64_t stride, uint32_t count, uint32_t slots, int tid)
+{
+    GLOBAL float *Y = (GLOBAL float *)a.d_y;
+    for (uint32_t o = tid; o < count * (MT * 256); o += NW * 64) {
+        const uint32_t j = o / (MT * 256), mt = (o >> 8) % MT, l = (o >> 2) & 63, r = o & 3;
+        const float *p = (const float *)&red[(j * slots * MT + mt) * 64 + l] + r;
+        float sum = 0.f;
+        if (slots == NW) {
+#pragma unroll
+            for (int w = 0; w < NW; w++) sum += p[w * (MT * 256)];
+        } else {
+            for (uint32_t w = 0; w < slots; w++) sum += p[w * (MT * 256)];
+        }
+        const uint32_t m = 16 * mt + 4 * (l >> 4) + r;
         if (m < a.M) {
             if (SCALED && a.d_xs && a.xs_cols == 1) sum *= ((const GLOBAL float *)a.d_xs)[m];
             Y[(uint64_t)m * a.rows + (first + j * stride) * BLOCK_ROWS + (l & 15)] = sum;
@@ -642,28 +670,47 @@ __device__ __forceinline__ void load_x_chunk(const GArgs &a, int lane, uint32_t 
 
 #define ECF8_MFMA_XPIECE(acc, xp, p, W_PIECE) ECF8_MFMA_OPERANDS(acc, xp.v[mt_][p], W_PIECE)
 
-// Position of a wave in its sequence of chunks: its i-th chunk of its workgroup's b-th unit.  A unit
-// is a block of 16 rows of W, or with split K one of the `slices` equal parts of its chunks: `block`
-// is the unit's block of rows, k0 its first chunk.
-struct Walk {
-    uint64_t b;
-    uint32_t i;
-    uint64_t block;
-    uint32_t k0;
+// Position of a wave in its sequence of chunks.  A unit is a block of 16 rows of W, or with split K one of the `slices` equal
+// parts of its chunks.
+struct Place {
+    uint32_t b, kc;             // the workgroup's b-th unit, its kc-th chunk
+    uint32_t block;             // the unit's block of rows
+    uint32_t c;                 // the chunk's number in the blob (row-tiled blobs have at most 2^28)
 };
 
-// The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units
-// of them), table set-up included.  `parity` says which of the two reduction buffers comes next and is
-// carried on to the caller's next matrix.
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0, bool APART = false, bool PINNED = true>
-__device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint64_t unit_stride,
-                                          uint64_t my_units, uint32_t &parity)
+// Chunks of a block whose share of X a wave keeps in registers for the whole matrix (0: it fetches X chunk by chunk).  One tile
+// of X only: two chunks of it are 32 registers, and with more tiles or chunks they are not there.  Two pay from the second block of
+// rows on; a workgroup with one (1024 x 7168, M = 16: 13.9 us) only waits longer for its first look-up (14.8).
+template <int MT, int NW>
+__host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t blocks)
+{
+    return MT != 1 ? 0u : kchunks <= NW ? 1u : kchunks <= 2 * NW && blocks > 1 ? 2u : 0u;
+}
+
+// The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units of them), table
+// set-up included.  At a block's end a wave parks its sum in LDS and goes on; the workgroup meets once per batch, as many
+// blocks as there are slots for.  Which of a block's chunks are summed together (those NW apart) and in which order the sums are
+// added does not depend on which wave has them, so every way below gives the same bits.
+//  * KRES = 1, 2 (see resident_chunks): wave w has the chunks w, w + NW of every block and keeps their X; where a block has at
+//    most NW / 2 chunks the waves form groups with a block each.  That leaves waves idle at times (28 chunks on 16 waves: an
+//    eighth), which costs little beside the others' work.
+//  * KRES = 0: the units' chunks form one sequence, and wave w takes every NW-th of it from the w-th on, across the units'
+//    borders; batches are rounded down to whole rounds of the waves.
+// What bounds it: the requests for the blob's bytes, the look-ups and the vector operations about equally (eight experts, M = 4: without
+// nibble loads 87 us, without stream loads 87, without look-ups 92, all 97).  Eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W,
+// M = 4 / 16 / 64: block by block with a barrier each and X fetched for every chunk 106 / 126 / 294 us, in one sequence 106 / 127 / 269,
+// now 97 / 103 / 269.
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, bool PINNED, int KRES>
+__device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
+                                          uint32_t my_units)
 {
     constexpr bool SCALED = SC != 0;
     using C = GCfg<MT, NW, N>;
     constexpr int BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES, GSTAGE = C::STAGE, GSEGS = C::SEGS;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
+    static_assert((NW & (NW - 1)) == 0, "places in the deal are chunk numbers modulo NW");
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
+    f32x4 *red = (f32x4 *)(smem + C::OFF_RED);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = (int)uniform32((uint32_t)tid >> 6);           // the same for every lane: what follows from it stays in scalar registers
     const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
@@ -675,50 +722,69 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
     const uint64_t lane_elem = (uint64_t)(lane & 15) * a.K + (uint64_t)(lane >> 4) * 16;
     const uint32_t kchunks = (uint32_t)(a.K / BLOCK_COLS);
-    const uint32_t unit_chunks = SPLIT ? kchunks / a.slices : kchunks;                                     // chunks of K per unit
-    const Deal deal = deal_chunks<NW>(unit_chunks, SPLIT, wave);
-    const uint32_t my_chunks = deal.my_chunks;                                                             // wave-uniform
-    const uint64_t my_blocks = (my_units + deal.groups - 1) / deal.groups;                                 // units of `groups` blocks
+    const uint32_t unit_chunks = SPLIT ? kchunks / a.slices : kchunks;
+    // split K: the grid is the units, each workgroup has one
+    const uint32_t k0 = SPLIT ? (uint32_t)first_unit % a.slices * unit_chunks : 0u;
+    const uint32_t block0 = SPLIT ? (uint32_t)first_unit / a.slices : (uint32_t)first_unit;
 
     struct Meta { uint64_t b0, b1; uint32_t lb; };
-    auto at_unit = [&](uint64_t b) {
-        Walk w{b, 0, first_unit + (b * deal.groups + deal.gi) * unit_stride, 0};
-        if constexpr (SPLIT) {
-            const uint32_t u = (uint32_t)w.block;            // units < 2^31, checked on the host
-            w.block = u / a.slices;
-            w.k0 = (u % a.slices) * unit_chunks;
+    // NW chunks on: over at most this many units and so many chunks more
+    const uint32_t hop = (uint32_t)NW / unit_chunks, hop_kc = (uint32_t)NW % unit_chunks;
+    const uint32_t skip = (unit_stride - 1) * unit_chunks;         // the other workgroups' chunks between one unit and the next
+    const uint32_t groups = KRES && 2 * unit_chunks <= (uint32_t)NW ? (uint32_t)NW / unit_chunks : 1u, per_group = (uint32_t)NW / groups;
+    const uint32_t kw = (uint32_t)wave % per_group;
+    const bool two = KRES && kw + NW < unit_chunks;
+    auto first_place = [&]() {
+        Place w;
+        if constexpr (KRES != 0) {
+            w.b = (uint32_t)wave / per_group;
+            w.kc = kw;
+            if (kw >= unit_chunks || w.b >= groups) w.b = my_units;              // a wave with nothing to do
+        } else {
+            w.b = (uint32_t)wave / unit_chunks;
+            w.kc = (uint32_t)wave % unit_chunks;
         }
+        w.block = block0 + w.b * unit_stride;
+        w.c = w.block * kchunks + k0 + w.kc;
         return w;
     };
-    auto block_of = [&](const Walk &w) -> uint64_t { return w.block; };
-    auto kc_of = [&](const Walk &w) -> uint32_t { return w.k0 + deal.kw + deal.wpb * w.i; };
-    auto valid = [&](const Walk &w) { return my_chunks != 0 && w.b * deal.groups + deal.gi < my_units; };
-    auto next_of = [&](Walk w) { if (++w.i == my_chunks) w = at_unit(w.b + 1); return w; };
-    auto load_meta = [&](const Walk &w) {
-        const uint64_t c = block_of(w) * kchunks + kc_of(w);
+    auto next_of = [&](Place w) {
+        uint32_t kc, units;
+        if constexpr (KRES != 0) {
+            const bool over = w.kc + NW >= unit_chunks;
+            units = over ? groups : 0u;
+            kc = over ? kw : w.kc + NW;
+            w.c += units * unit_stride * unit_chunks + kc - w.kc;
+        } else {
+            const bool over = w.kc + hop_kc >= unit_chunks;        // never past the one unit that split K has but at its end
+            units = hop + (over ? 1u : 0u);
+            kc = over ? w.kc + hop_kc - unit_chunks : w.kc + hop_kc;
+            w.c += NW + units * skip;
+        }
+        w.kc = kc;
+        w.b += units;
+        w.block += units * unit_stride;
+        return w;
+    };
+    auto valid = [&](const Place &w) { return w.b < my_units; };
+    auto load_meta = [&](const Place &w) {
         Meta m;
-        m.b0 = chunk_bit[c];
-        m.b1 = chunk_bit[c + 1];
-        m.lb = lane_bits[c * 64 + lane];
+        m.b0 = chunk_bit[w.c];
+        m.b1 = chunk_bit[w.c + 1];
+        m.lb = lane_bits[(uint64_t)w.c * 64 + lane];
         return m;
     };
     // A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead), from the chunk's two start
     // bits: values every lane holds alike, so the arithmetic is done once, in scalar registers.
-    auto span_of = [&](const Meta &m, uint64_t &byte0) {
-        const uint64_t b0 = uniform64(m.b0), b1 = uniform64(m.b1);
-        uint64_t byte_end = ((b1 + 7) >> 3) + 8;
-        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
-        byte0 = (b0 >> 3) & ~15ull;
-        if (byte0 > byte_end) byte0 = byte_end;
-        return byte_end - byte0;
-    };
     // The span's 16-byte units into `seg` (unit lane + 64 k into seg[k]); units beyond the span keep what they
     // held: the lanes' codewords never reach into them.
     const uint32_t lane16 = (uint32_t)lane * 16;
     auto load_stream = [&](const Meta &m, u32x4 (&seg)[GSEGS], bool wanted = true) {
-        uint64_t byte0;
-        const uint32_t whole = (uint32_t)span_of(m, byte0);         // at most GSTAGE under the cap on codewords
-        const uint32_t span = wanted ? whole : 0u;
+        const uint64_t b0 = uniform64(m.b0), b1 = uniform64(m.b1);
+        uint64_t byte_end = ((b1 + 7) >> 3) + 8, byte0 = (b0 >> 3) & ~15ull;
+        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
+        if (byte0 > byte_end) byte0 = byte_end;
+        const uint32_t span = wanted ? (uint32_t)(byte_end - byte0) : 0u;      // at most GSTAGE under the cap on codewords
         const GLOBAL uint8_t *sp = stream + byte0;
 #pragma unroll
         for (int k = 0; k < GSEGS; k++) {
@@ -726,13 +792,14 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             if (i < (uint32_t)GSTAGE && i < span) seg[k] = __builtin_nontemporal_load((const GLOBAL u32x4 *)(sp + i));
         }
     };
-    // nibble plane of a chunk: piece q of this lane at plane_of(w) + lane_plane + 32 q
+    // nibble plane of a chunk: piece q of this lane at plane_of(w) + lane_plane + 32 q.  Block and column of chunk c begin at
+    // element 256 * (16 * block * kchunks + k), k = c - block * kchunks.
     const uint64_t lane_plane = lane_elem / 2;
-    auto plane_of = [&](const Walk &w) -> const GLOBAL uint8_t * {
-        return plane + (block_of(w) * BLOCK_ROWS * a.K + kc_of(w) * (uint64_t)BLOCK_COLS) / 2;
+    auto plane_of = [&](const Place &w) -> const GLOBAL uint8_t * {
+        return plane + ((uint64_t)(16 * w.c - 15 * (k0 + w.kc)) << 7);
     };
 
-    Walk cur = at_unit(0);
+    Place cur = first_place();
     Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
     u32x4 seg[GSEGS];
     u32x2 pl[GPIECES];
@@ -740,7 +807,7 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
 #pragma unroll
     for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
-    XPieces<MT, N> x_cur;
+    XPieces<MT, N> x_cur[KRES > 1 ? KRES : 1];
     // The order of ecf8_gemm_kernel, but not in groups with two tiles of X and scales of W or with two or four and no scales.
     // Metadata first / this order, us: six experts, M = 20 and scales of W 117.7 / 123.4, no scales 112.0 / 114.0; M = 32 and no scales
     // 124.8 / 131.7, M = 48 163.3 / 169.3.  Elsewhere this order: M = 48 and scales of W 188.7 / 181.7, M = 32 and scales of W and X 159.9 / 153.0,
@@ -751,16 +818,18 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     if (valid(cur)) {
         m_cur = load_meta(cur);
         m_next = m_cur;
-        if (valid(next_of(cur))) m_next = load_meta(next_of(cur));
+        const Place nxt = next_of(cur);
+        if (valid(nxt)) m_next = load_meta(nxt);
         if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(cur) + lane_plane;
 #pragma unroll
         for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * q));
-        load_x_chunk<MT, N>(a, lane, kc_of(cur), x_cur);
+        load_x_chunk<MT, N>(a, lane, k0 + cur.kc, x_cur[0]);
     }
     if constexpr (EARLY) {
         if (valid(cur)) load_stream(m_cur, seg);
     }
+    if constexpr (KRES > 1) load_x_chunk<MT, N>(a, lane, two ? kw + NW : kw, x_cur[1]);
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
@@ -774,66 +843,100 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
     }
 
-    for (uint64_t b = 0; b < my_blocks; b++) {            // uniform for the workgroup: one barrier per block
-        f32x4 acc[MT];
+    // slots of a block, blocks of a batch: whole rounds of the waves where there are slots for NW / gcd(NW, chunks) blocks
+    const uint32_t slots = unit_chunks < (uint32_t)NW ? unit_chunks : (uint32_t)NW;
+    const uint32_t low = unit_chunks & (0u - unit_chunks), whole = low < (uint32_t)NW ? (uint32_t)NW / low : 1u;
+    uint32_t batch = SPLIT ? 1u : C::SLOTS / slots;
+    if (batch >= whole) batch &= 0u - whole;
+
+    f32x4 acc[MT];
+    auto clear = [&]() {
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const uint32_t n_mine = valid(at_unit(b)) ? my_chunks : 0;       // the sequence may end inside the last unit
-#pragma unroll 1
-        for (uint32_t i = 0; i < n_mine; i++) {
-            const Meta m = m_cur;
-            uint64_t byte0;
-            span_of(m, byte0);
-            const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
-            const uint64_t start = uniform64(m.b0);
+    };
+    // One chunk: decoded and multiplied by x; the wave's next one is fetched meanwhile, its share of X by fetch_x.
+    auto chunk = [&](const XPieces<MT, N> &x, auto fetch_x) {
+        const Meta m = m_cur;
+        const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
+        const uint32_t start = uniform32((uint32_t)m.b0) & 127u;           // of the chunk's first bit in its image
 #pragma unroll
-            for (int k = 0; k < GSEGS; k++) {
-                const uint32_t j = lane16 + 1024 * k;
-                if (j < (uint32_t)GSTAGE) *(u32x4 *)(stage + j) = seg[k];
-            }
-            const XPieces<MT, N> x = x_cur;
-            ChunkSums<MT, SC> sums;
-            sums.begin(a, block_of(cur), kc_of(cur));
-            // The stream registers are free: fetch the next chunk's span and its share of X, and the metadata of the
-            // chunk after it.
-            const Walk nxt = next_of(cur);
-            const bool more = valid(nxt);
-            Meta m_next2 = m_next;
-            if (more) {
-                load_stream(m_next, seg);
-                load_x_chunk<MT, N>(a, lane, kc_of(nxt), x_cur);
-                if (valid(next_of(nxt))) m_next2 = load_meta(next_of(nxt));
-            }
-            // after the last chunk the plane pieces are fetched from the plane's first chunk (every wave's last fetch: cached)
-            const GLOBAL uint8_t *pp = (more ? plane_of(nxt) : plane) + lane_plane;
-            const uint32_t bpA = stage_off * 8 + (uint32_t)(start - byte0 * 8) + rel - 1;   // one bit off, see quad_step2
-            HeldRuns runs;
-            runs.begin(smem, bpA, bpA + m.lb - 30);
-            auto &dstA = sums.first(acc);
-            auto &dstB = sums.second(acc);
-#pragma unroll
-            for (int Q = 0; Q < GPIECES / 2; Q++) {
-                uint32_t dwA[4], dwB[4];
-#pragma unroll
-                for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
-                // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
-                const u32x4 wA = merge_piece(dwA, pl[Q]);
-                pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * Q));
-                ECF8_MFMA_XPIECE(dstA, x, Q, wA);
-                const u32x4 wB = merge_piece(dwB, pl[Q + GPIECES / 2]);
-                pl[Q + GPIECES / 2] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * (Q + GPIECES / 2)));
-                ECF8_MFMA_XPIECE(dstB, x, Q + GPIECES / 2, wB);
-            }
-            sums.end(acc, a, lane);
-            cur = nxt;
-            m_cur = m_next;
-            m_next = m_next2;
+        for (int k = 0; k < GSEGS; k++) {
+            const uint32_t j = lane16 + 1024 * k;
+            if (j < (uint32_t)GSTAGE) *(u32x4 *)(stage + j) = seg[k];
         }
-        f32x4 *red = (f32x4 *)(smem + C::OFF_RED + parity * C::RED_BYTES);
-        const Walk unit = at_unit(b);
-        if constexpr (SPLIT) reduce_split<MT, NW, SCALED>(red, s_flag, a, (uint32_t)unit.block, unit.k0 / unit_chunks, tid, acc);
-        else reduce_groups<MT, NW, SCALED>(red, a, first_unit, unit_stride, b * deal.groups, my_units, deal, tid, acc);
-        parity ^= 1;
+        ChunkSums<MT, SC> sums;
+        sums.begin(a, cur.block, k0 + cur.kc);
+        // The stream registers are free: fetch the next chunk's span and its share of X, and the metadata of the
+        // chunk after it.
+        const Place nxt = next_of(cur);
+        const bool more = valid(nxt);
+        Meta m_next2 = m_next;
+        if (more) {
+            load_stream(m_next, seg);
+            fetch_x(nxt);
+            const Place nxt2 = next_of(nxt);
+            if (valid(nxt2)) m_next2 = load_meta(nxt2);
+        }
+        // after the last chunk the plane pieces are fetched from the plane's first chunk (every wave's last fetch: cached)
+        const GLOBAL uint8_t *pp = (more ? plane_of(nxt) : plane) + lane_plane;
+        const uint32_t bpA = stage_off * 8 + start + rel - 1;      // one bit off, see quad_step2
+        HeldRuns runs;
+        runs.begin(smem, bpA, bpA + m.lb - 30);
+        auto &dstA = sums.first(acc);
+        auto &dstB = sums.second(acc);
+#pragma unroll
+        for (int Q = 0; Q < GPIECES / 2; Q++) {
+            uint32_t dwA[4], dwB[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
+            // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
+            const u32x4 wA = merge_piece(dwA, pl[Q]);
+            pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * Q));
+            ECF8_MFMA_XPIECE(dstA, x, Q, wA);
+            const u32x4 wB = merge_piece(dwB, pl[Q + GPIECES / 2]);
+            pl[Q + GPIECES / 2] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * (Q + GPIECES / 2)));
+            ECF8_MFMA_XPIECE(dstB, x, Q + GPIECES / 2, wB);
+        }
+        sums.end(acc, a, lane);
+        m_cur = m_next;
+        m_next = m_next2;
+        return nxt;
+    };
+    auto park = [&](uint32_t j, uint32_t place) {                  // the wave's last chunk of the batch's j-th block is done
+        f32x4 *slot = red + (j * slots + place) * (MT * 64) + lane;
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) slot[mt * 64] = acc[mt];
+    };
+    clear();
+    for (uint32_t b0 = 0; b0 < my_units; b0 += batch) {            // uniform for the workgroup: its barriers
+        const uint32_t b1 = my_units - b0 < batch ? my_units : b0 + batch;
+        if constexpr (KRES != 0) {
+            while (cur.b < b1) {
+                const uint32_t j = cur.b - b0, place = cur.kc;
+                clear();
+                cur = chunk(x_cur[0], [](const Place &) {});
+                if (KRES > 1 && two) cur = chunk(x_cur[KRES - 1], [](const Place &) {});
+                park(j, place);
+            }
+        } else {
+#pragma unroll 1
+            while (cur.b < b1) {
+                const XPieces<MT, N> x = x_cur[0];
+                const Place nxt = chunk(x, [&](const Place &w) { load_x_chunk<MT, N>(a, lane, k0 + w.kc, x_cur[0]); });
+                if (!SPLIT && nxt.b != cur.b) {
+                    park(cur.b - b0, cur.kc & (NW - 1));
+                    clear();
+                }
+                cur = nxt;
+            }
+        }
+        if constexpr (SPLIT) {
+            reduce_split<MT, NW, SCALED>(red, s_flag, a, block0, k0 / unit_chunks, tid, acc);
+        } else {
+            __syncthreads();
+            reduce_batch<MT, NW, SCALED>(red, a, first_unit + (uint64_t)b0 * unit_stride, unit_stride, b1 - b0, slots, tid);
+            if (b1 < my_units) __syncthreads();                    // the slots are free again
+        }
     }
 }
 
@@ -843,15 +946,23 @@ __device__ __forceinline__ uint64_t units_of_workgroup(uint64_t n_units)
     return blockIdx.x < n_units ? (n_units - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
 }
 
-template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, bool PINNED = true>
+template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, bool PINNED = true, int KRES = 0>
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::TOTAL];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::ANYK_TOTAL];
     __shared__ uint32_t s_flag;                   // split K: the arrival count this workgroup drew
-    uint32_t parity = 0;
-    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, PINNED>(a, smem, &s_flag, blockIdx.x, gridDim.x,
-                                    units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)), parity);
+    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, PINNED, KRES>(a, smem, &s_flag, blockIdx.x, gridDim.x,
+                                                              (uint32_t)units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)));
 }
+
+// Position of a wave in its sequence of chunks of uncompressed W: its i-th chunk of its workgroup's b-th unit.  `block` is the
+// unit's block of rows, k0 its first chunk.
+struct Walk {
+    uint64_t b;
+    uint32_t i;
+    uint64_t block;
+    uint32_t k0;
+};
 
 // The any-K GEMM on uncompressed W: same deal of chunks, same order of accumulation.
 template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0>
@@ -965,7 +1076,7 @@ template <int MT, int NW, int N, int SC, bool RAW>
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
 {
     using C = GCfg<MT, NW, N>;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[RAW ? 2 * C::RED_BYTES : C::TOTAL];
+    __shared__ __attribute__((aligned(16))) uint8_t smem[RAW ? 2 * C::RED_BYTES : C::ANYK_TOTAL];
     __shared__ uint32_t s_flag;
     constexpr uint32_t WORDS = sizeof(ecf8_gemm_group_item) / 8;
     const GLOBAL uint64_t *items = (const GLOBAL uint64_t *)g.d_items;
@@ -973,12 +1084,18 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
     uint64_t pos = g.total_work * blockIdx.x / gridDim.x;
     const uint64_t end = g.total_work * (blockIdx.x + 1) / gridDim.x;
     uint32_t parity = 0;
-    while (pos < end) {                                 // one round per matrix the share touches (uniform)
-        uint32_t lo = 0, hi = g.n_items - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (uniform64(items[(uint64_t)mid * WORDS]) <= pos) lo = mid; else hi = mid - 1;
-        }
+    // The matrix that holds pos: lane l probes the l-th of 64 evenly spaced items, one round trip to memory for up to 64 of
+    // them (a binary search took five for 24, at the start and again wherever a share crosses into the next matrix, which is
+    // simply the next item).
+    uint32_t lo = 0;
+    for (uint32_t n = g.n_items; n > 1;) {
+        const uint32_t step = (n + 63) / 64, at = (threadIdx.x & 63) * step;
+        const bool begun = at < n && items[(uint64_t)(lo + (at < n ? at : 0u)) * WORDS] <= pos;
+        const uint32_t k = ((uint32_t)__popcll(__ballot(begun)) - 1u) * step;       // the first one has begun
+        lo += k;
+        n = n - k < step ? n - k : step;
+    }
+    for (; pos < end; lo++) {                           // one round per matrix the share touches (uniform)
         GItem it;
         {
             uint64_t *dst = (uint64_t *)&it;
@@ -992,7 +1109,13 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
         __syncthreads();                                // the last matrix's table and reduction buffers are out of use
         if (b0 < b1) {
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
-            else anyk_walk<MT, NW, N, SC, false, 0, true, !(MT == 4 && SC == 2)>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);     // M = 64: 297 us, pinned 306
+            else {
+                constexpr bool PINNED = !(MT == 4 && SC == 2);      // M = 64: 297 us, pinned 306
+                const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW>(kchunks, n);
+                if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
+                else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
+                else anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, 0>(it.a, smem, &s_flag, b0, 1, n);
+            }
         }
         pos = it.first_work + n_blocks * kchunks;       // on to the next matrix (or past `end`)
     }
@@ -1090,7 +1213,10 @@ int launch_fused(const GArgs &a, void *stream)
     // at M > 32: beside four tiles of X in registers the scales do not fit (93 us against 83 at M = 64)
     // ... and on the F16 matrix cores at M > 16, where X in registers and the converted operands do not fit together
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
+        const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
+        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
+        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, 2>), dim3(grid), dim3(16 * 64), 0, s, a);
+        else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // X pieces of two chunks: 8 waves' worth of registers
         else {
             // Four tiles of X with a scale per row and 128 columns crowd the registers: pinning the lookups (quad_step_held) pays only

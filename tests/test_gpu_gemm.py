@@ -618,6 +618,26 @@ def test_grouped_gemm_equals_the_single_calls(orc, name, scale_mode):
     _check(ys[-1].cpu().numpy(), yref, mag, "grouped, last member")
 
 
+@pytest.mark.parametrize("M", [4, 16, 24, 64])
+def test_deals_of_chunks_to_waves(M):
+    """Either side of every border of the any-K deal: as many chunks per block as fall to half the waves, one wave or two each and one
+    more, odd counts, one block per workgroup and several, batches that end inside; alone and in a group of more matrices than one probe
+    of its items covers.  Bit for bit the twin on uncompressed weights, which is dealt block by block, and the single calls."""
+    shapes = [(16 * b, 256 * k) for k in (1, 3, 7, 8, 9, 15, 17, 28, 31, 32, 33, 57) for b in (1, 5)] + [(16 * 700, 256 * k) for k in (3, 9, 17, 33)]
+    members, single = [], []
+    for i, (rows, K) in enumerate(shapes):
+        w = synth.make_weight(rows, K, 1.7, 0.02, 29, i, "block128", DEV)
+        x = synth.activations(M, K, 290 + i, DEV)
+        hdr, blob = ecf8.ecf8_encode_gpu(w, lane_syms=64, tile_rows=16, table_mode=1 + i % 2)
+        members.append({"hdr": hdr, "blob": blob, "x": x})
+        single.append(_single_call(members[-1]))
+        assert torch.equal(single[-1], ecf8.ecf8_gemm_fp8_raw(w, x)), (rows, K)
+    order = (list(range(len(shapes))) * 3)[:65 + M]
+    group = ecf8.GemmGroup([members[i] for i in order])
+    for i, y in zip(order, ecf8.ecf8_gemm_fp8_grouped(group)):
+        assert torch.equal(y, single[i]), (i, shapes[i])
+
+
 def test_grouped_gemm_argument_errors():
     shapes, Ms = GROUPS["mid_M"]
     fused = _group_members(shapes, Ms, seed=3)
