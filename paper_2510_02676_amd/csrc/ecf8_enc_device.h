@@ -6,103 +6,18 @@
 
 namespace {
 
+// The workgroups' shares of chunk_bit[] are zeroed by the histogram kernels, which run before anything reads them.
+__device__ __forceinline__ void zero_chunk_bits(uint64_t chunk_bit, uint64_t n_chunks, uint32_t tid, uint32_t threads)
+{
+    for (uint64_t i = (uint64_t)blockIdx.x * threads + tid; i <= n_chunks; i += (uint64_t)gridDim.x * threads) ((GLOBAL uint64_t *)chunk_bit)[i] = 0;
+}
+
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint64_t dst, uint64_t bytes)   // bytes % 16 == 0
 {
     GLOBAL u32x4 *p = (GLOBAL u32x4 *)dst;
     const uint64_t n16 = bytes / 16;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (uint64_t)gridDim.x * blockDim.x)
         p[i] = u32x4{0, 0, 0, 0};
-}
-
-// chunk_bit[1 .. n_chunks] on the way from chunk totals to stream positions.  The metadata kernels leave a chunk's total
-// (at most 2^17 bits) in the upper bits of its entry; the prefix sum puts the position below it.
-//  * Up to SLICED chunks, a workgroup per 1024 of them: each adds up the totals in front of its slice by itself (512 KiB at the
-//    most) and scans the slice.  No workgroup waits for another: an entry reads the same from before and after its
-//    update, because the total stays in it, and the packing kernels mask it off and write the plain position back.
-//  * Above that one workgroup goes through all of them, 8192 a round: row k of a round is 1024 chunks side by side, scanned
-//    by the waves, and the 128 (row, wave) totals are scanned once more by every wave.
-// Where a chunk starts inside a dword of the stream, that dword holds bits of two chunks or more: it is zeroed here, and the
-// packing kernels OR into it.  (One workgroup for everything: 7.0 us for 7168 chunks and 14 for 14336, half of it these
-// scattered stores from one compute unit; sliced 3 .. 4 us.)
-constexpr int TOTAL_AT = 46;
-constexpr uint64_t SLICED = 1 << 16;
-__host__ __device__ inline uint64_t position_mask(uint64_t n_chunks) { return n_chunks <= SLICED ? (1ull << TOTAL_AT) - 1 : ~0ull; }
-
-__global__ __launch_bounds__(1024) void scan_kernel(uint64_t chunk_bit_, uint64_t n_chunks, uint64_t stream_)
-{
-    constexpr int ROWS = 8;
-    __shared__ uint32_t totals[2][ROWS * 16];
-    __shared__ uint64_t before_s[16];
-    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)chunk_bit_;
-    GLOBAL uint32_t *stream = (GLOBAL uint32_t *)stream_;
-    const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
-    if (n_chunks <= SLICED) {
-        const uint64_t first = 1 + 1024ull * blockIdx.x, i = first + tid;
-        const uint32_t mine = i <= n_chunks ? (uint32_t)(cb[i] >> TOTAL_AT) : 0u;
-        uint32_t front = 0;                               // at most 64 totals
-#pragma unroll 8
-        for (uint32_t k = 0; k < blockIdx.x; k++) front += (uint32_t)(cb[1 + tid + 1024ull * k] >> TOTAL_AT);
-        const uint32_t incl = wave_incl_scan(mine), f = wave_incl_scan(front);      // 64 x 64 totals: 2^29
-        if (lane == 63) {
-            totals[0][wave] = incl;
-            before_s[wave] = f;
-        }
-        __syncthreads();
-        uint64_t at = incl;
-#pragma unroll
-        for (int w = 0; w < 16; w++) at += before_s[w] + (w < wave ? totals[0][w] : 0u);
-        if (i <= n_chunks) {
-            cb[i] = at | ((uint64_t)mine << TOTAL_AT);
-            if (i < n_chunks && (at & 31)) stream[at >> 5] = 0;
-        }
-        return;
-    }
-    uint64_t carry = 0;
-    int parity = 0;
-    for (uint64_t base = 1; base <= n_chunks; base += 1024 * ROWS, parity ^= 1) {
-        uint32_t v[ROWS];
-#pragma unroll
-        for (int k = 0; k < ROWS; k++) v[k] = base + 1024 * k + tid <= n_chunks ? (uint32_t)(cb[base + 1024 * k + tid] >> TOTAL_AT) : 0u;
-#pragma unroll
-        for (int k = 0; k < ROWS; k++) {
-            v[k] = wave_incl_scan(v[k]);
-            if (lane == 63) totals[parity][k * 16 + wave] = v[k];
-        }
-        __syncthreads();                                  // the other buffer is free again once everyone is here
-        const uint32_t t0 = totals[parity][lane], t1 = totals[parity][64 + lane];
-        const uint32_t s0 = wave_incl_scan(t0), half = (uint32_t)__builtin_amdgcn_readlane((int)s0, 63);
-        const uint32_t s1 = half + wave_incl_scan(t1);
-        const uint32_t x0 = s0 - t0, x1 = s1 - t1;        // totals before (row, wave)
-#pragma unroll
-        for (int k = 0; k < ROWS; k++) {
-            const uint64_t i = base + 1024 * k + tid;
-            const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(k < 4 ? x0 : x1), (k & 3) * 16 + wave);
-            const uint64_t at = carry + before + v[k];
-            if (i <= n_chunks) {
-                cb[i] = at;
-                if (i < n_chunks && (at & 31)) stream[at >> 5] = 0;
-            }
-        }
-        carry += (uint32_t)__builtin_amdgcn_readlane((int)s1, 63);
-    }
-}
-
-inline void launch_scan(uint64_t chunk_bit, uint64_t n_chunks, uint64_t stream, hipStream_t s)
-{
-    const uint32_t grid = n_chunks <= SLICED ? (uint32_t)((n_chunks + 1023) / 1024) : 1u;
-    hipLaunchKernelGGL(scan_kernel, dim3(grid), dim3(1024), 0, s, chunk_bit, n_chunks, stream);
-}
-
-// The metadata kernels take a workgroup of 256 threads per four chunks.  A launch must stay below 2^32 work-items, which a single one
-// would pass at 2^26 chunks (2^37 weights at 32 symbols per lane): they take as many as they need, of at most this many workgroups.
-constexpr uint64_t META_BLOCKS = 1 << 20;
-
-// The positions of chunk c's first and last bit, the latter written back plain.
-__device__ __forceinline__ void chunk_positions(GLOBAL uint64_t *cb, uint64_t c, uint64_t mask, int lane, uint64_t &b0, uint64_t &b1)
-{
-    b0 = uniform64(cb[c]) & mask;
-    b1 = uniform64(cb[c + 1]) & mask;
-    if (~mask && lane == 0) cb[c + 1] = b1;
 }
 
 // Where chunk c's pieces lie: piece q of lane l starts at element base + q * stride + lane_off(l) (see the container's layouts).
@@ -113,6 +28,7 @@ struct ChunkPlace {
 // The 16 bytes at byte e of a tensor of n bytes, zeros from its end on.
 __device__ __forceinline__ u32x4 load_cut(const GLOBAL uint8_t *x, uint64_t e, uint64_t n)
 {
+    if (e + 16 <= n) return *(const GLOBAL u32x4 *)(x + e);
     uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -150,30 +66,273 @@ struct LanePacker {
     }
 };
 
-// A chunk's span of the stream, assembled in LDS (`stage` = the 16-byte unit that holds stream bit b0, on), to its place:
-// whole units by 16-byte stores, the units at the ends dword by dword; the first and the last dword may hold bits of
-// other chunks, were zeroed by scan_kernel (or, the stream's last one, with the padding) and are ORed into.
-__device__ __forceinline__ void copy_span(const uint32_t *stage, GLOBAL uint32_t *stream, uint64_t b0, uint64_t b1, int lane)
+// ---- the container behind the code: one pass over the weights ----
+// A wave takes a few chunks in a row, a workgroup as many times its waves, a tile.  Chunk by chunk the wave counts the code bits,
+// writes the planes and packs the bits into its image in LDS, one chunk behind the other; where they go is only known when
+// everything before them has been counted.  That the workgroups find out from one another, once per tile, and then copy the
+// images to the stream, shifted into place.  Tiles are drawn from a counter, so that a workgroup waits only for tiles
+// that were drawn before its own; these wait for earlier ones only, so every wait ends whatever part of the grid is running.
+//
+// The exchange goes through chunk_bit[], which the histogram kernel has zeroed.  Of the entries of tile t, which has T chunks,
+//   [T t]      holds the tile's first bit once the tile before has written it, plain and for good (it is not 0: a chunk has a bit
+//              per weight at least, and tile 0's entry is not read);
+//   [T t + 1]  holds what the tile before has to say, until tile t replaces it by its plain value: SAID_TOTAL and its length from bit 32
+//              on as soon as the code bits of its chunks are counted, SAID_TAIL and its last 32 bits once they are packed.
+//              An entry that has been replaced reads as not said; then the first bit of tile t + 1 is on its way, and is what ends the wait.
+// What bounds it: the exchange costs a tile 3 to 5 us, round trips through the memory side and waiting for the slowest wave, and the compute unit
+// has nothing else to do meanwhile; hence tiles as large as the LDS holds, and one per compute unit where that is enough.
+// 58.7 M E4M3 weights: tiles of eight chunks, two workgroups per compute unit, 52 us; of 16 chunks 42; of 32, one per compute unit, 32.
+constexpr uint64_t SAID_TOTAL = 1ull << 63, SAID_TAIL = 1ull << 62;
+constexpr int LATE_DWORDS = 68;             // end of an image: one lane's bits of a chunk that does not fit into the rest
+constexpr int LATE_LANES = 16;              // such a chunk goes out by so many lanes at a time, whose bits fit whatever they are
+
+__device__ __forceinline__ uint64_t agent_load(GLOBAL uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void agent_store(GLOBAL uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// One wave: the first bit of tile t, by adding up what the tiles before have said back to the nearest one whose first bit is known.
+// WINDOWS x 64 tiles are asked for at a time, about as many as there are workgroups on the chip.
+__device__ __forceinline__ uint64_t tile_begin(GLOBAL uint64_t *cb, uint32_t T, uint32_t t, int lane)
 {
-    const uint64_t unit0 = b0 >> 7;
-    const uint32_t n_units = (uint32_t)(((b1 + 127) >> 7) - unit0);
-    const uint64_t dw0 = b0 >> 5, dw1 = (b1 + 31) >> 5;                 // dwords [dw0, dw1) hold the span
-    for (uint32_t u = lane; u < n_units; u += 64) {
-        const u32x4 v = *(const u32x4 *)(stage + 4 * u);
-        if (u != 0 && u + 1 != n_units) {
-            *(GLOBAL u32x4 *)(stream + 4 * (unit0 + u)) = v;
-            continue;
-        }
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    constexpr int WINDOWS = 4;
+    uint64_t between = 0;
+    for (uint32_t s0 = t;;) {
+        uint64_t at[WINDOWS], said[WINDOWS];                    // of tile s0 - 64 k - lane
 #pragma unroll
-        for (int k = 0; k < 4; k++) {
-            const uint64_t d = 4 * (unit0 + u) + k;
-            if (d < dw0 || d >= dw1) continue;
-            const bool shared = (d == dw0 && (b0 & 31)) || (d + 1 == dw1 && (b1 & 31));
-            if (!shared) stream[d] = w[k];
-            else if (w[k]) atomicOr((unsigned int *)(stream + d), w[k]);
+        for (int k = 0; k < WINDOWS; k++) {
+            at[k] = said[k] = 0;
+            if ((uint32_t)lane + 64 * k < s0) {
+                GLOBAL uint64_t *e = cb + (uint64_t)T * (s0 - 64 * k - lane);
+                at[k] = agent_load(e);
+                said[k] = agent_load(e + 1);
+            }
+        }
+        bool again = false;
+#pragma unroll
+        for (int k = 0; k < WINDOWS; k++) {
+            if (again) break;
+            const uint64_t known = __ballot((uint32_t)lane >= s0 || at[k] != 0), there = __ballot(said[k] >> 63);
+            const uint32_t f = known ? (uint32_t)__builtin_ctzll(known) : 64u;
+            const uint64_t need = f < 64 ? (1ull << f) - 1 : ~0ull;
+            if ((there & need) != need) {
+                again = true;                                   // from this window on
+                break;
+            }
+            const uint32_t sum = wave_incl_scan((uint32_t)lane < f ? (uint32_t)(said[k] >> 32) & 0x3fffffffu : 0u);      // at most 64 x 2^25, see tile_chunks
+            between += (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
+            if (f < 64)
+                return between + ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(at[k] >> 32), (int)f) << 32 |
+                                  (uint32_t)__builtin_amdgcn_readlane((int)at[k], (int)f));
+            s0 -= 64;
+        }
+        if (again) __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+// What the waves of a workgroup tell one another about the tile they are at, in two buffers used in turn.
+constexpr int WMAX = 16;                    // waves of a workgroup at the most
+struct TileShared {
+    uint64_t begin;
+    uint64_t counted[2];                    // code bits of the waves that have counted theirs, from bit 40 on how many have
+    uint32_t drawn[2];                      // the tile after it
+    uint32_t total[2][WMAX], tail[2][WMAX]; // bits of a wave's chunks, the last 32 of them
+};
+
+// `bits` bits in front of bit number `bits` of an image: the last 32 of them, for bits >= 32.
+__device__ __forceinline__ uint32_t last32(const uint32_t *image, uint32_t bits)
+{
+    return bits >= 32 ? __builtin_amdgcn_alignbit(image[bits >> 5], image[(bits >> 5) - 1], bits & 31) : 0u;
+}
+
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
+
+// An image's bits to bits [b0, b1) of the stream: the dwords from the one that holds the first bit, whose lower bits are the last
+// ones of image[-1], to the last one that the bits fill, `all`: to the last one that they reach.  `skip`: not the first one.
+__device__ __forceinline__ void copy_bits(const uint32_t *image, GLOBAL uint32_t *stream, uint64_t b0, uint64_t b1, bool all, bool skip, int lane)
+{
+    const uint32_t n = (uint32_t)((b1 >> 5) - (b0 >> 5)) + (all && (b1 & 31) ? 1u : 0u), shift = (uint32_t)b0 & 31;
+    GLOBAL uint32_t *out = stream + (b0 >> 5);
+    for (uint32_t j = 4 * lane; j < n; j += 256) {
+        const u32x4 w = *(const u32x4 *)(image + j);
+        const uint32_t below = image[(int)j - 1];
+        u32x4a v = {w.x, w.y, w.z, w.w};
+        if (shift)
+            v = u32x4a{__builtin_amdgcn_alignbit(w.x, below, 32 - shift), __builtin_amdgcn_alignbit(w.y, w.x, 32 - shift),
+                       __builtin_amdgcn_alignbit(w.z, w.y, 32 - shift), __builtin_amdgcn_alignbit(w.w, w.z, 32 - shift)};
+        if (j + 4 <= n && (j || !skip)) {
+            *(GLOBAL u32x4a *)(out + j) = v;
+        } else {
+            if (j || !skip) out[j] = v.x;
+            if (j + 1 < n) out[j + 1] = v.y;
+            if (j + 2 < n) out[j + 2] = v.z;
+            if (j + 3 < n) out[j + 3] = v.w;
         }
     }
+}
+
+struct TileArgs {
+    uint64_t n_chunks;
+    uint32_t per_wave;                      // chunks of a wave per tile, at most 16
+    const uint32_t *header;                 // the blob's first 256 bytes
+};
+
+// The tiles of one workgroup.  K is a codec's chunk.  For chunks that lie entirely inside the tensor, fetch(c) asks for the weights, count(c) gives
+// the lane's code bits and writes the planes, pack(image, at, c, refill) packs the lane's bits from image bit `at` on and asks for the weights of
+// chunk c + 1 piece by piece as those of c are used up.  slow_count and slow_pack do the same for any chunk, from memory and rolled
+// up: the code of the common way has to stay well inside the instruction cache (with the ragged chunk's code woven in, 118 KB, it took
+// twice as long).  `image` is the wave's, K::AREA dwords, and image[-1] is there to be written.
+template <class K>
+__device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *image, const TileArgs &ta, GLOBAL uint8_t *blob, uint64_t off_cb,
+                                             uint64_t off_lb, uint64_t off_st, int lane, int wave)
+{
+    constexpr uint32_t ROOM = (uint32_t)(K::AREA - LATE_DWORDS - 2) * 32;       // bits an image takes, zeros behind them
+    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(blob + off_cb);
+    GLOBAL uint16_t *lane_bits = (GLOBAL uint16_t *)(blob + off_lb);
+    GLOBAL uint32_t *stream = (GLOBAL uint32_t *)(blob + off_st);
+    const uint32_t W = blockDim.x >> 6, T = W * ta.per_wave, n_tiles = (uint32_t)((ta.n_chunks + T - 1) / T);
+    // The counter is the header's first dword, 0 from before the histogram; whoever draws last writes the header.
+    uint32_t drawn = 0;
+    auto draw = [&]() {
+        if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add((GLOBAL uint32_t *)blob, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto first_chunk = [&](uint32_t t) { return (uint64_t)T * t + (uint64_t)ta.per_wave * wave; };
+    auto fetch_first = [&](uint32_t t) {
+        if (t < n_tiles && k.whole(first_chunk(t))) k.fetch(first_chunk(t));
+    };
+    auto zero = [&](uint32_t dwords) {
+        for (uint32_t u = lane; u * 4 < dwords; u += 64) *(u32x4 *)(image + 4 * u) = u32x4{0, 0, 0, 0};
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    draw();
+    if (threadIdx.x == 0) {
+        sh.drawn[1] = drawn;
+        sh.counted[0] = sh.counted[1] = 0;
+    }
+    __syncthreads();
+    uint32_t t = uniform32(sh.drawn[1]);
+    fetch_first(t);
+    for (uint32_t parity = 0; t < n_tiles; parity ^= 1) {
+        const uint64_t first = (uint64_t)T * t, c0 = first_chunk(t);
+        const bool followed = first + T < ta.n_chunks;
+        const uint32_t count = c0 < ta.n_chunks ? (uint32_t)(ta.n_chunks - c0 < ta.per_wave ? ta.n_chunks - c0 : ta.per_wave) : 0u;
+        uint32_t total = 0, used = 0, kept = 0, upto = 0, late_bits = 0;         // upto: lane i, bits up to the end of chunk i
+        zero(K::AREA);
+#pragma unroll 1
+        for (uint32_t i = 0; i < count; i++) {
+            const uint64_t c = c0 + i;
+            const bool whole = k.whole(c);
+            const uint32_t lb = whole ? k.count(c) : k.slow_count(c, true);
+            lane_bits[c * 64 + lane] = (uint16_t)lb;
+            const uint32_t incl = wave_incl_scan(lb), bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            total += bits;
+            upto = (uint32_t)lane == i ? total : upto;
+            // not before: a workgroup that draws twice before others have drawn at all takes their tile from them
+            if (i + 1 == count) draw();
+            if (i + 1 == count && lane == 0) {
+                // the last wave of the workgroup to have counted its chunks tells the next tile
+                sh.total[parity][wave] = total;
+                const uint64_t now = atomicAdd((unsigned long long *)&sh.counted[parity], (1ull << 40) + total) + (1ull << 40) + total;
+                if ((now >> 40) == W && followed)
+                    __hip_atomic_fetch_add(cb + first + T + 1, SAID_TOTAL | (now & ((1ull << 40) - 1)) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            // A chunk that does not fit behind the others is packed when its place is known; of the last one the last bits are needed before.
+            const bool fits = kept == i && used + bits <= ROOM, refill = fits && i + 1 < count && k.whole(c + 1);
+            if (fits && whole) k.pack(image, used + incl - lb, c, refill);
+            else if (fits || (i + 1 == count && lane == 63)) k.slow_pack(image + (fits ? 0 : K::AREA - LATE_DWORDS), fits ? used + incl - lb : 0u, c);
+            if (i + 1 < count && !refill && k.whole(c + 1)) k.fetch(c + 1);
+            late_bits = (uint32_t)__builtin_amdgcn_readlane((int)lb, 63);
+            kept += fits ? 1u : 0u;
+            used += fits ? bits : 0u;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane == 0) {
+            sh.tail[parity][wave] = kept == count ? last32(image, total) : last32(image + K::AREA - LATE_DWORDS, late_bits);
+            if (wave == 0) sh.drawn[parity] = drawn;
+        }
+        __syncthreads();
+        const uint32_t next = uniform32(sh.drawn[parity]);
+        uint32_t before = 0, all = 0;
+        for (uint32_t w = 0; w < W; w++) {
+            const uint32_t v = sh.total[parity][w];
+            before += w < (uint32_t)wave ? v : 0u;
+            all += v;
+        }
+        if (wave == 0) {
+            if (lane == 0) {
+                sh.counted[parity] = 0;
+                if (followed) __hip_atomic_fetch_add(cb + first + T + 1, SAID_TAIL | sh.tail[parity][W - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const uint64_t begin = tile_begin(cb, T, t, lane);
+            if (lane == 0) {
+                if (followed) agent_store(cb + first + T, begin + all);
+                sh.begin = begin;
+            }
+        }
+        fetch_first(next);
+        __syncthreads();
+        if (count) {
+            const uint64_t b0 = uniform64(sh.begin) + before;
+            const uint32_t shift = (uint32_t)b0 & 31;
+            const bool skip = wave == 0 && shift;               // the tile's first dword comes last: it needs the end of the tile before
+            if (lane == 0 && wave != 0) image[-1] = sh.tail[parity][wave - 1];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            copy_bits(image, stream, b0, b0 + used, kept == count && c0 + count == ta.n_chunks, skip, lane);
+            uint32_t tail = wave ? sh.tail[parity][wave - 1] : 0u;
+            if (wave == 0 && t != 0) {
+                uint64_t said;                                  // all of it, before the entry is replaced
+                while (((said = agent_load(cb + first + 1)) & (SAID_TOTAL | SAID_TAIL)) != (SAID_TOTAL | SAID_TAIL)) __builtin_amdgcn_s_sleep(1);
+                tail = uniform32((uint32_t)said);
+                if (skip && lane == 0 && (b0 >> 5 != (b0 + used) >> 5 || (kept == count && c0 + count == ta.n_chunks)))
+                    stream[b0 >> 5] = __builtin_amdgcn_alignbit(image[0], tail, 32 - shift);
+            }
+            // all but the first bit of the tile behind, which the first wave has written
+            if ((uint32_t)lane < count && !(followed && wave + 1 == (int)W && (uint32_t)lane + 1 == count)) agent_store(cb + c0 + lane + 1, b0 + upto);
+            if (kept < count) {
+                uint64_t at = b0 + used;
+                if (kept) tail = last32(image, used);
+                for (uint32_t i = kept; i < count; i++) {
+                    const uint64_t c = c0 + i;
+                    const uint32_t lb = k.slow_count(c, false), incl = wave_incl_scan(lb);
+                    for (int l0 = 0; l0 < 64; l0 += LATE_LANES) {
+                        const uint32_t from = l0 ? (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 - 1) : 0u;
+                        const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 + LATE_LANES - 1) - from;
+                        zero(K::AREA);
+                        if (lane == 0) image[-1] = tail;
+                        if (lane >= l0 && lane < l0 + LATE_LANES) k.slow_pack(image, incl - lb - from, c);
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        const bool end = c + 1 == ta.n_chunks && l0 + LATE_LANES == 64;
+                        copy_bits(image, stream, at, at + bits, end, false, lane);
+                        if (bits >= 32) tail = last32(image, bits);
+                        else if (bits) tail = (uint32_t)((((uint64_t)image[0] << 32 | tail) >> bits));
+                        at += bits;
+                    }
+                }
+            }
+        }
+        t = next;
+    }
+    if (t == n_tiles + gridDim.x - 1 && threadIdx.x < 64)
+        __hip_atomic_store((GLOBAL uint32_t *)blob + threadIdx.x, ta.header[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waves per workgroup, chunks per wave and tile, workgroups, for a stream of `bits` bits: a chunk on as many compute units as there are
+// chunks; then more waves, up to WMAX; then as many chunks per wave as gives every compute unit the same number of tiles, up to what
+// their images hold (with 15 % to spare: a chunk that does not fit is read and packed a second time).
+struct TilePlan {
+    uint32_t waves, per_wave, grid;
+};
+template <int AREA>
+inline TilePlan plan_tiles(uint64_t n_chunks, uint64_t bits, uint32_t cus)
+{
+    TilePlan p;
+    p.waves = n_chunks <= 4ull * cus ? 4u : n_chunks <= 8ull * cus ? 8u : (uint32_t)WMAX;
+    const uint64_t each = (n_chunks + (uint64_t)p.waves * cus - 1) / ((uint64_t)p.waves * cus), mean = bits / n_chunks + 1;
+    uint64_t hold = (uint64_t)(AREA - LATE_DWORDS - 2) * 32 * 100 / (115 * mean);
+    hold = hold < 1 ? 1 : hold > 16 ? 16 : hold;
+    const uint64_t rounds = (each + hold - 1) / hold;
+    p.per_wave = (uint32_t)((each + rounds - 1) / rounds);
+    const uint64_t tiles = (n_chunks + (uint64_t)p.waves * p.per_wave - 1) / ((uint64_t)p.waves * p.per_wave);
+    p.grid = (uint32_t)(tiles < cus ? tiles : cus);
+    return p;
 }
 
 // The encoders' one synchronisation: the histogram back to the host, when everything queued on `s` so far is done.  The

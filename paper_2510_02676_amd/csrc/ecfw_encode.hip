@@ -2,13 +2,10 @@
 // for 5- and 8-bit exponent fields.  Writes exactly the container ecfw_encode writes, byte for byte:
 // the code and the layout come from the same host routine, fed with the device histogram.
 //
-//   fill 0 (header, code lengths, freq) -> histogram -> [host: the histogram back, code + layout]
-//   -> metadata and planes (one wave per chunk: lane_bits, the chunk's total, the remaining bits of its elements; the
-//   first workgroup writes header, code lengths and the padding between sections) -> prefix sum of the
-//   totals -> stream (one wave per chunk assembles its span in LDS and copies it out; the two dwords a span may share
-//   with its neighbours go out with atomic OR).
-// No scratch memory: the histogram is counted into the freq section and the chunk totals into
-// chunk_bit[], both part of the output.
+//   fill 0 (header, code lengths, freq) -> histogram (and zeros in chunk_bit[]) -> [host: the histogram back, code + layout]
+//   -> everything else in one pass over the elements, as in the E4M3 encoder (encode_tiles).
+// No scratch memory: the histogram is counted into the freq section, tiles are drawn from the header's first dword, and what the
+// workgroups tell one another goes through chunk_bit[], all of them part of the output.
 #include "ecfw.h"
 
 #include "ecf8_enc_device.h"
@@ -44,27 +41,13 @@ __device__ __forceinline__ ChunkPlace place_of(const WEncArgs &a, uint64_t c, ui
     return {c * E, 64 * P, lane * P};
 }
 
-// A lane's pieces of a chunk; `whole`: the chunk lies entirely inside the tensor (the same for every lane).
-template <int FMT, int N>
-__device__ __forceinline__ void load_pieces(const WEncArgs &a, const ChunkPlace &p, bool whole, u32x4 (&v)[N / EFmt<FMT>::P])
-{
-    constexpr int ELEM = EFmt<FMT>::ELEM;
-    const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x;
-    const uint64_t e0 = (p.base + p.lane_off) * ELEM;
-#pragma unroll
-    for (int q = 0; q < N / EFmt<FMT>::P; q++) {
-        const uint64_t e = e0 + q * p.stride * ELEM;
-        v[q] = whole || e + 16 <= a.n * ELEM ? *(const GLOBAL u32x4 *)(x + e) : load_cut(x, e, a.n * ELEM);
-    }
-}
-
 // Histogram of the exponent field into A u64 counters, one workgroup of 16 waves per compute unit.
 //  * E5M2: bit planes.  32 elements are turned into five 32-bit words, one per exponent bit, and each of the 32 exponents
 //    is one AND and one population count that also adds: four vector operations per element, no LDS.
 //  * BF16: LDS counters in 64 copies, lane l of every wave in copy l = bank l, so that the lanes of a wave, most of which
 //    hold one of a handful of exponents, never meet.  58.7 M elements: 21 us, 5.5 TB/s (16 copies: 47 us).
 template <int FMT>
-__global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t n, uint64_t counters_)
+__global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t n, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks)
 {
     constexpr int A = EFmt<FMT>::A, COPIES = FMT == ECFW_FMT_BF16 ? 64 : 1;
     __shared__ uint32_t s_cnt[A * COPIES];
@@ -72,6 +55,7 @@ __global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t
     GLOBAL unsigned long long *counters = (GLOBAL unsigned long long *)counters_;
     const int tid = threadIdx.x, lane = tid & 63;
     for (int i = tid; i < A * COPIES; i += 1024) s_cnt[i] = 0;
+    zero_chunk_bits(chunk_bit, n_chunks, (uint32_t)tid, 1024);
     __syncthreads();
     // a wave takes 4 KiB per step: four loads of 1 KiB, of which a lane keeps the 16 bytes at 16 * lane
     constexpr uint64_t PER = 4096 / EFmt<FMT>::ELEM;
@@ -140,194 +124,190 @@ __global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t
     }
 }
 
-struct WHeadArgs {
-    ecfw_header h;
-    uint8_t len[256];
-};
-
 struct WCodeArgs {
+    ecfw_header h;
     uint16_t code[256];                   // canonical codewords, first bit most significant
     uint8_t len[256];
 };
 
-// Everything of the container that is neither chunk data nor stream (the freq section already holds the histogram):
-// header, code lengths, zeros in the gaps between sections and in the dwords of the stream section from the one that
-// holds its last bit on.
-__device__ __forceinline__ void write_fixed(const WEncArgs &a, const WHeadArgs &ha, int tid)
+// What of the container is neither chunk data nor stream, but for the header, by the first workgroup (the freq section already
+// holds the histogram): code lengths, zeros in the gaps between sections and behind the last dword of the stream.
+__device__ __forceinline__ void write_fixed(const WEncArgs &a, const WCodeArgs &ca)
 {
+    if (blockIdx.x != 0) return;
+    const uint32_t tid = threadIdx.x;
     GLOBAL uint8_t *blob = (GLOBAL uint8_t *)a.blob;
-    const ecfw_header &h = ha.h;
-    if (tid < 64) ((GLOBAL uint32_t *)blob)[tid] = ((const uint32_t *)&h)[tid];
-    if ((uint32_t)tid * 4 < h.n_alphabet) *(GLOBAL uint32_t *)(blob + a.off_len + 4 * tid) = ((const uint32_t *)ha.len)[tid];
-    if (tid == 0) *(GLOBAL uint64_t *)(blob + a.off_cb) = 0;
+    const ecfw_header &h = ca.h;
+    if (tid * 4 < h.n_alphabet) *(GLOBAL uint32_t *)(blob + a.off_len + 4 * tid) = ((const uint32_t *)ca.len)[tid];
     auto zero = [&](uint64_t from, uint64_t to) {       // multiples of four
-        for (uint64_t i = from + 4 * tid; i < to; i += 1024) *(GLOBAL uint32_t *)(blob + i) = 0;
+        for (uint64_t i = from + 4 * tid; i < to; i += 4 * blockDim.x) *(GLOBAL uint32_t *)(blob + i) = 0;
     };
     zero(a.off_cb + 8 * (a.n_chunks + 1), a.off_lb);
     zero(a.off_lb + 128 * a.n_chunks, a.off_st);
-    zero(a.off_st + (h.stream_bits >> 5) * 4, a.off_pl);
+    zero(a.off_st + ((h.stream_bits + 31) >> 5) * 4, a.off_pl);
     zero(a.off_pl + h.plane_bytes, h.sign_bytes ? a.off_sg : h.total_size);
     if (h.sign_bytes) zero(a.off_sg + h.sign_bytes, h.total_size);
 }
 
-// lane_bits[c][l] = code bits of the lane's symbols; chunk_bit[c + 1] = bits of chunk c (turned into stream positions by
-// the scan); the chunk's planes, zeros where the last chunk reaches past the tensor.  One wave per chunk; the
-// first workgroup writes the fixed parts instead.  The code lengths sit in 256 bytes of LDS: 64 dwords, one per bank.
-template <int FMT, int N>
-__global__ __launch_bounds__(256) void w_meta_kernel(WEncArgs a, WHeadArgs ha, uint32_t parts, uint64_t first_block)
-{
+// A chunk on its way through encode_tiles, as in the E4M3 encoder.  The codewords come from the host with the launch; symbols are looked up
+// one by one (256 of them would make a pair table of 256 KiB), codeword and length in one dword, and packed two at a time.
+// LMAX: the longest codeword in use is at most this.
+template <int FMT, int N, int LMAX>
+struct Chunk {
     using F = EFmt<FMT>;
-    constexpr int P = F::P;
-    __shared__ uint32_t s_len4[64];
-    const uint8_t *s_len = (const uint8_t *)s_len4;
-    const int tid = threadIdx.x, lane = tid & 63;
-    if (blockIdx.x < parts) {
-        write_fixed(a, ha, tid);
-        return;
+    static constexpr int P = F::P, A = F::A, PIECES = N / P;
+    static constexpr int AREA = ((160 * 1024 - 1024 - 8 * (A + 1) - 256) / (4 * WMAX) - 4) / 4 * 4;
+    static_assert(N * LMAX < 32 * LATE_DWORDS && N * LMAX * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
+
+    const WEncArgs &a;
+    const uint32_t (*code)[A + 1];          // code | length << 16, first bit lowest / highest; A = no symbol
+    const uint8_t *len;
+    int lane;
+    u32x4 v[PIECES];
+
+    __device__ __forceinline__ bool whole(uint64_t c) const { return (c + 1) * (64ull * N) <= a.n; }
+    __device__ __forceinline__ void fetch(uint64_t c)
+    {
+        const ChunkPlace p = place_of<FMT, N>(a, c, lane);
+        const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x + (p.base + p.lane_off) * F::ELEM;
+#pragma unroll
+        for (int q = 0; q < PIECES; q++) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
     }
-    const uint64_t c = (first_block + (blockIdx.x - parts)) * 4 + uniform32((uint32_t)tid >> 6);
-    const bool here = c < a.n_chunks;
-    const bool whole = (c + 1) * (64ull * N) <= a.n;
-    const ChunkPlace p = place_of<FMT, N>(a, c, lane);
-    u32x4 v[N / P];
-    if (here) load_pieces<FMT, N>(a, p, whole, v);
-    if (tid < 64) s_len4[tid] = ((const uint32_t *)ha.len)[tid];
-    __syncthreads();
-    if (!here) return;
-    uint32_t lb = 0;
-    GLOBAL uint8_t *plane = (GLOBAL uint8_t *)(a.blob + a.off_pl), *signs = (GLOBAL uint8_t *)(a.blob + a.off_sg);
-#pragma unroll
-    for (int q = 0; q < N / P; q++) {
-        const uint64_t e = p.base + p.lane_off + q * p.stride;
-        const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-        if (whole) {
-#pragma unroll
-            for (int j = 0; j < P; j++) lb += s_len[F::sym(w, j)];
-        } else {
-            const uint32_t have = e + P <= a.n ? (uint32_t)P : e < a.n ? (uint32_t)(a.n - e) : 0u;
-#pragma unroll
-            for (int j = 0; j < P; j++) lb += (uint32_t)j < have ? s_len[F::sym(w, j)] : 0u;
-        }
+    // the planes of the piece at element e
+    __device__ __forceinline__ void planes(uint64_t e, const u32x4 &w) const
+    {
+        GLOBAL uint8_t *plane = (GLOBAL uint8_t *)(a.blob + a.off_pl), *signs = (GLOBAL uint8_t *)(a.blob + a.off_sg);
         if constexpr (FMT == ECFW_FMT_BF16) {
             // sign << 7 | mantissa in bytes 0 and 2 of a dword's two elements; the bytes of four elements in the order 0 2 1 3
-            uint32_t r[4];
-#pragma unroll
-            for (int k = 0; k < 4; k++) r[k] = bit_select(0x007f007fu, w[k], w[k] >> 8);
-            *(GLOBAL u32x2 *)(plane + e) = u32x2{bit_select(0x00ff00ffu, r[0], r[1] << 8), bit_select(0x00ff00ffu, r[2], r[3] << 8)};
+            const uint32_t r0 = bit_select(0x007f007fu, w.x, w.x >> 8), r1 = bit_select(0x007f007fu, w.y, w.y >> 8);
+            const uint32_t r2 = bit_select(0x007f007fu, w.z, w.z >> 8), r3 = bit_select(0x007f007fu, w.w, w.w >> 8);
+            *(GLOBAL u32x2 *)(plane + e) = u32x2{bit_select(0x00ff00ffu, r0, r1 << 8), bit_select(0x00ff00ffu, r2, r3 << 8)};
         } else {
             // mantissa of element 4d + j in bits 8j + 2d; sign of element i in bit i
-            const uint32_t m01 = bit_select(0x03030303u, w[0], w[1] << 2), m23 = bit_select(0x03030303u, w[2], w[3] << 2);
-            uint32_t s = 0;
-#pragma unroll
-            for (int d = 0; d < 4; d++) {
-                uint32_t y = (w[d] >> 7) & 0x01010101u;
+            const uint32_t m01 = bit_select(0x03030303u, w.x, w.y << 2), m23 = bit_select(0x03030303u, w.z, w.w << 2);
+            auto signs4 = [](uint32_t d) {
+                uint32_t y = (d >> 7) & 0x01010101u;
                 y |= y >> 7;
-                s |= ((y | (y >> 14)) & 15u) << (4 * d);
-            }
+                return (y | (y >> 14)) & 15u;
+            };
             *(GLOBAL uint32_t *)(plane + e / 4) = bit_select(0x0f0f0f0fu, m01, m23 << 4);
-            *(GLOBAL uint16_t *)(signs + e / 8) = (uint16_t)s;
+            *(GLOBAL uint16_t *)(signs + e / 8) = (uint16_t)(signs4(w.x) | (signs4(w.y) << 4) | (signs4(w.z) << 8) | (signs4(w.w) << 12));
         }
     }
-    ((GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane] = (uint16_t)lb;
-    const uint32_t total = wave_incl_scan(lb);
-    if (lane == 63) ((GLOBAL uint64_t *)(a.blob + a.off_cb))[c + 1] = (uint64_t)total << TOTAL_AT;
-}
+    __device__ __forceinline__ uint32_t count(uint64_t c)
+    {
+        const ChunkPlace p = place_of<FMT, N>(a, c, lane);
+        uint32_t lb = 0;
+#pragma unroll
+        for (int i = 0; i < PIECES; i++) {
+            const int q = i < PIECES / 2 ? i : PIECES - 1 - (i - PIECES / 2);       // in the order in which pack asks for them
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < P; j++) lb += len[F::sym(w, j)];
+            planes(p.base + p.lane_off + q * p.stride, v[q]);
+        }
+        return lb;
+    }
+    static __device__ __forceinline__ void put2(LanePacker &out, uint32_t x0, uint32_t x1)
+    {
+        out.put((x0 & 0xffffu) | ((x1 & 0xffffu) << (x0 >> 16)), (x0 >> 16) + (x1 >> 16));
+    }
+    __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t c, bool refill)
+    {
+        LanePacker out(image, at);
+        const ChunkPlace p = place_of<FMT, N>(a, c + 1, lane);
+        const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x + (p.base + p.lane_off) * F::ELEM;
+#pragma unroll
+        for (int q = 0; q < PIECES / 2; q++) {
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = 0; j < P; j += 2) put2(out, code[0][F::sym(w, j)], code[0][F::sym(w, j + 1)]);
+            if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
+        }
+#pragma unroll
+        for (int q = PIECES - 1; q >= PIECES / 2; q--) {
+            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+            for (int j = P - 1; j > 0; j -= 2) put2(out, code[1][F::sym(w, j)], code[1][F::sym(w, j - 1)]);
+            if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
+        }
+        out.finish();
+    }
+    // any chunk, piece by piece; symbols past the tensor's end have no bits
+    __device__ __forceinline__ u32x4 piece(uint64_t e, uint32_t back, uint32_t (&s)[P]) const
+    {
+        const u32x4 v4 = load_cut((const GLOBAL uint8_t *)a.x, e * F::ELEM, a.n * F::ELEM);
+        const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w}, have = e + P <= a.n ? (uint32_t)P : e < a.n ? (uint32_t)(a.n - e) : 0u;
+#pragma unroll
+        for (int j = 0; j < P; j++) s[j] = code[back][(uint32_t)j < have ? F::sym(w, j) : (uint32_t)A];
+        return v4;
+    }
+    __device__ __forceinline__ uint32_t slow_count(uint64_t c, bool planes_)
+    {
+        const ChunkPlace p = place_of<FMT, N>(a, c, lane);
+        uint32_t lb = 0;
+#pragma unroll 1
+        for (int q = 0; q < PIECES; q++) {
+            const uint64_t e = p.base + p.lane_off + q * p.stride;
+            uint32_t s[P];
+            const u32x4 w = piece(e, 0, s);
+#pragma unroll
+            for (int j = 0; j < P; j++) lb += s[j] >> 16;
+            if (planes_) planes(e, w);
+        }
+        return lb;
+    }
+    __device__ __forceinline__ void slow_pack(uint32_t *image, uint32_t at, uint64_t c)
+    {
+        const ChunkPlace p = place_of<FMT, N>(a, c, lane);
+        LanePacker out(image, at);
+#pragma unroll 1
+        for (int i = 0; i < PIECES; i++) {
+            const bool back = i >= PIECES / 2;
+            uint32_t s[P];
+            piece(p.base + p.lane_off + (back ? PIECES - 1 - (i - PIECES / 2) : i) * p.stride, back ? 1 : 0, s);
+#pragma unroll
+            for (int j = 0; j < P; j += 2) put2(out, back ? s[P - 1 - j] : s[j], back ? s[P - 2 - j] : s[j + 1]);
+        }
+        out.finish();
+    }
+};
 
-// Stream: one wave per chunk, as in the E4M3 encoder (a lane's bits are one string: the forward run's codewords in order,
-// then the backward run's in reverse with their first bits highest).  The codewords come from the host with the launch;
-// symbols are looked up one by one (256 of them would make a pair table of 256 KiB) and packed two at a time.  58.7 M BF16
-// elements: 30 us for the 137 MB read and written (a load and two LDS atomics per symbol: 143 us).  LMAX: the longest codeword in use is at most this.
+// The container behind the code.  58.7 M elements (14336 x 4096): BF16 45 us for the 198 MB read and written, E5M2 45 for 101 MB (62 and 57 with metadata and
+// planes, prefix sum and packing as kernels of their own); bound by the look-ups, two of LDS per element.  The whole call 99 -> 80 us and
+// 85 -> 73, 16384 x 16384 in BF16 458 -> 336.
 template <int FMT, int N, int LMAX>
-__global__ __launch_bounds__(256) void w_pack_kernel(WEncArgs a, WCodeArgs ca)
+__global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeArgs ca, uint32_t per_wave)
 {
-    using F = EFmt<FMT>;
-    constexpr int P = F::P, A = F::A;
-    constexpr int STAGE = 2 * N * LMAX + 8;                 // dwords: the longest span, begun anywhere in a 16-byte unit
-    static_assert(STAGE % 4 == 0, "16-byte accesses");
-    __shared__ __attribute__((aligned(16))) uint32_t stage_all[4][STAGE];
-    __shared__ uint32_t s_code[2][A + 1];                   // code | length << 16, first bit lowest / highest; A = no symbol
-    const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
-    if (tid < A) {
+    using K = Chunk<FMT, N, LMAX>;
+    constexpr int A = K::A;
+    __shared__ __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA + 4];  // the last of the four in front is image[-1]
+    __shared__ uint32_t s_code[2][A + 1];
+    __shared__ uint32_t s_len4[64];
+    __shared__ TileShared sh;
+    const uint32_t tid = threadIdx.x;
+    const int wave = (int)uniform32(tid >> 6);
+    if (tid < (uint32_t)A) {
         const uint32_t code = ca.code[tid], l = ca.len[tid];
         s_code[0][tid] = l ? (__brev(code) >> (32 - l)) | (l << 16) : 0u;
         s_code[1][tid] = code | (l << 16);
     }
     if (tid < 2) s_code[tid][A] = 0;
-    __syncthreads();
-    uint32_t *stage = stage_all[wave];
-    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(a.blob + a.off_cb);
-    const uint64_t mask = position_mask(a.n_chunks);
-    for (uint64_t c = (uint64_t)blockIdx.x * 4 + wave; c < a.n_chunks; c += (uint64_t)gridDim.x * 4) {   // the same for the whole wave
-        const bool whole = (c + 1) * (64ull * N) <= a.n;
-        const ChunkPlace p = place_of<FMT, N>(a, c, lane);
-        u32x4 v[N / P];
-        load_pieces<FMT, N>(a, p, whole, v);
-        uint64_t b0, b1;
-        chunk_positions(cb, c, mask, lane, b0, b1);
-        const uint32_t lb = ((const GLOBAL uint16_t *)(a.blob + a.off_lb))[c * 64 + lane];
-        const uint32_t n_units = (uint32_t)(((b1 + 127) >> 7) - (b0 >> 7));
-        for (uint32_t u = lane; u < n_units && u < (uint32_t)STAGE / 4; u += 64) *(u32x4 *)(stage + 4 * u) = u32x4{0, 0, 0, 0};
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        LanePacker out(stage, (uint32_t)(b0 & 127) + (wave_incl_scan(lb) - lb));
-        auto put2 = [&](uint32_t e0, uint32_t e1) {
-            out.put((e0 & 0xffffu) | ((e1 & 0xffffu) << (e0 >> 16)), (e0 >> 16) + (e1 >> 16));
-        };
-        if (whole) {
-#pragma unroll
-            for (int q = 0; q < N / P / 2; q++) {
-                const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-                for (int j = 0; j < P; j += 2) put2(s_code[0][F::sym(w, j)], s_code[0][F::sym(w, j + 1)]);
-            }
-#pragma unroll
-            for (int q = N / P - 1; q >= N / P / 2; q--) {
-                const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-                for (int j = P - 1; j > 0; j -= 2) put2(s_code[1][F::sym(w, j)], s_code[1][F::sym(w, j - 1)]);
-            }
-        } else {
-            // the ragged last chunk: elements past the tensor's end have no bits
-            auto put_piece = [&](bool back, const u32x4 &piece, uint64_t e) {
-                const uint32_t have = e + P <= a.n ? (uint32_t)P : e < a.n ? (uint32_t)(a.n - e) : 0u;
-#pragma unroll 1
-                for (uint32_t k = 0; k < (uint32_t)P; k++) {
-                    const uint32_t j = back ? P - 1 - k : k;
-                    const uint32_t word = j * 4 / P, w = word < 2 ? (word ? piece.y : piece.x) : (word == 2 ? piece.z : piece.w);
-                    const uint32_t at = F::ELEM == 1 ? 8 * (j & 3) + 2 : 16 * (j & 1) + 7;
-                    put2(s_code[back][j < have ? (w >> at) & (uint32_t)(A - 1) : (uint32_t)A], 0u);
-                }
-            };
-            const uint64_t e0 = p.base + p.lane_off;
-#pragma unroll
-            for (int q = 0; q < N / P / 2; q++) put_piece(false, v[q], e0 + q * p.stride);
-#pragma unroll
-            for (int q = N / P - 1; q >= N / P / 2; q--) put_piece(true, v[q], e0 + q * p.stride);
-        }
-        out.finish();
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        copy_span(stage, (GLOBAL uint32_t *)(a.blob + a.off_st), b0, b1, lane);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+    if (tid < 64) s_len4[tid] = ((const uint32_t *)ca.len)[tid];
+    write_fixed(a, ca);
+    K k{a, s_code, (const uint8_t *)s_len4, (int)(tid & 63), {}};
+    encode_tiles(k, sh, images[wave] + 4, TileArgs{a.n_chunks, per_wave, (const uint32_t *)&ca.h}, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st,
+                 (int)(tid & 63), wave);
 }
 
-template <int FMT, int N>
-int launch_pass2(const WEncArgs &a, const WHeadArgs &ha, const WCodeArgs &ca, hipStream_t s)
+template <int FMT, int N, int LMAX>
+int launch_encode(const WEncArgs &a, const WCodeArgs &ca, hipStream_t s)
 {
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
-    const uint64_t chunk_blocks = (a.n_chunks + 3) / 4;
-    for (uint64_t b = 0; b < chunk_blocks; b += META_BLOCKS) {
-        const uint32_t fixed = b == 0 ? 1 : 0, blocks = (uint32_t)(chunk_blocks - b < META_BLOCKS ? chunk_blocks - b : META_BLOCKS);
-        hipLaunchKernelGGL((w_meta_kernel<FMT, N>), dim3(blocks + fixed), dim3(256), 0, s, a, ha, fixed, b);
-    }
-    // prefix sum and packing store where the metadata say: neither without what it reads
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
-    launch_scan(a.blob + a.off_cb, a.n_chunks, a.blob + a.off_st, s);
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
-    const uint64_t most = (uint64_t)cus * 8;
-    const uint32_t pg = (uint32_t)(chunk_blocks < most ? chunk_blocks : most);
-    if (ha.h.max_code_len <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_pack_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(pg), dim3(256), 0, s, a, ca);
-    else hipLaunchKernelGGL((w_pack_kernel<FMT, N, (int)ECFW_MAX_CODE_LEN>), dim3(pg), dim3(256), 0, s, a, ca);
+    using K = Chunk<FMT, N, LMAX>;
+    const TilePlan p = plan_tiles<K::AREA>(a.n_chunks, ca.h.stream_bits, (uint32_t)cus);
+    hipLaunchKernelGGL((w_encode_kernel<FMT, N, LMAX>), dim3(p.grid), dim3(p.waves * 64), 0, s, a, ca, p.per_wave);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 
@@ -340,7 +320,8 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     const uint64_t blob = (uint64_t)(uintptr_t)d_blob, x = (uint64_t)(uintptr_t)d_elems;
     // the sections in front of chunk_bit have fixed places: header 256, code_len 256, freq 8A rounded up
     const uint64_t off_freq = 512, fixed = off_freq + (8ull * A + 255) / 256 * 256;
-    if (blob_capacity < fixed) return ECF8_E_CAPACITY;
+    const uint64_t n_chunks = (n + 64ull * N - 1) / (64ull * N);
+    if (blob_capacity < fixed + 8 * (n_chunks + 1)) return ECF8_E_CAPACITY;         // no blob of this tensor is that small
 
     // pass 1: histogram, counted into the blob's freq section
     const int cus = device_cus();
@@ -348,7 +329,8 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, blob, fixed);
     const uint64_t hist_blocks = (n * EFmt<FMT>::ELEM / 4096 + 15) / 16, hist_most = (uint64_t)cus;
     hipLaunchKernelGGL(w_histogram_kernel<FMT>, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s,
-                       x, n, blob + off_freq);
+                       x, n, blob + off_freq, blob + fixed, n_chunks);
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     uint64_t freq[256] = {};
     if (!read_back(freq, blob + off_freq, 8ull * A, s)) return ECF8_E_HIP;
 
@@ -357,7 +339,7 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     if (rc) return rc;
     const ecfw_header &h = plan.hdr;
     if (h.total_size > blob_capacity) return ECF8_E_CAPACITY;
-    if (h.off_freq != off_freq || h.off_chunk_bit != fixed) return ECF8_E_FORMAT;
+    if (h.off_freq != off_freq || h.off_chunk_bit != fixed || h.n_chunks != n_chunks) return ECF8_E_FORMAT;
 
     // pass 2: the container
     WEncArgs a{};
@@ -372,14 +354,16 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     a.off_pl = h.off_plane;
     a.off_sg = h.off_sign;
     a.group = group;
-    WHeadArgs ha;
-    ha.h = h;
     WCodeArgs ca;
+    ca.h = h;
     for (int i = 0; i < 256; i++) {
-        ha.len[i] = ca.len[i] = plan.len[i];
+        ca.len[i] = plan.len[i];
         ca.code[i] = (uint16_t)plan.code[i];
     }
-    rc = N == 64 ? launch_pass2<FMT, 64>(a, ha, ca, s) : launch_pass2<FMT, 128>(a, ha, ca, s);
+    if (h.max_code_len <= ECFW_TABLE_BITS)
+        rc = N == 64 ? launch_encode<FMT, 64, (int)ECFW_TABLE_BITS>(a, ca, s) : launch_encode<FMT, 128, (int)ECFW_TABLE_BITS>(a, ca, s);
+    else
+        rc = N == 64 ? launch_encode<FMT, 64, (int)ECFW_MAX_CODE_LEN>(a, ca, s) : launch_encode<FMT, 128, (int)ECFW_MAX_CODE_LEN>(a, ca, s);
     if (rc) return rc;
     *hdr_out = h;
     return ECF8_OK;

@@ -77,8 +77,7 @@ def test_seeded_sweep_of_shapes_and_options(orc, block):
 
 @pytest.mark.parametrize("chunks,extra", [(1024, 0), (1024, 1), (2048, -1), (8192, 7), (65536, 0), (65536, 1), (65536 + 8192, 5)])
 def test_many_chunks(chunks, extra):
-    """The chunk totals are summed 1024 per workgroup up to 65536 of them, beyond that by one workgroup 8192 at a time:
-    whole and nearly whole slices and rounds, one chunk more, the first sizes past the limit."""
+    """Many tiles, each placed by what the ones before it have counted: powers of two, one chunk less and more."""
     n = chunks * 2048 + extra
     x = np.resize(_rand_bytes((1 << 20) + 12345, chunks + extra), n)
     opts = dict(lane_syms=32, max_code_len=15 if extra else 0)
@@ -107,6 +106,42 @@ def test_every_byte_of_the_blob_is_written(opts):
         assert (got[want.size:] == 0xA5).all(), n
 
 
+# One compute unit's waves take 4, 8 or 16 chunks of a tile, one each and then more each: either side of those borders, tiles of one chunk
+@pytest.mark.parametrize("chunks", [1, 4, 5, 1024, 1025, 2048, 2049, 4096, 4097, 4129, 12289])
+@pytest.mark.parametrize("extra", [0, 3])
+def test_borders_of_tiles(chunks, extra):
+    n = chunks * 2048 + extra
+    x = np.resize(_rand_bytes((1 << 20) + 4321, chunks + extra, conc=2.0), n)
+    for opts in (dict(lane_syms=32), dict(lane_syms=32, max_code_len=15, group_chunks=1)):
+        want = ecf8.ecf8_encode(x, 1, n, **opts)
+        buf = torch.full((want.size + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+        hdr, _ = ecf8.ecf8_encode_gpu(torch.from_numpy(x).to(DEV), 1, n, d_blob=buf, **opts)
+        torch.cuda.synchronize()
+        assert bytes(hdr) == bytes(want.header)
+        assert torch.equal(buf[:want.size].cpu(), torch.from_numpy(want.numpy())) and bool((buf[want.size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("lane_syms,cap,chunks,islands", [(32, 0, 40960, [(0, 170), (20011, 20400), (40930, 40960)]), (64, 15, 16500, [(2, 30), (8000, 8400), (16490, 16500)]),
+                                                          (128, 15, 6200, [(0, 1), (3104, 3105), (6199, 6200)]), (128, 15, 6200, [(17, 18), (3135, 3136), (6197, 6198)])])
+def test_chunks_that_do_not_fit_behind_the_others(lane_syms, cap, chunks, islands):
+    """A wave packs its chunks of a tile one behind the other into an image that holds the average chunk some times over.  Islands of long
+    codewords do not fit: several chunks of one wave, or a single chunk of 8192 codewords of ten bits, first, last and inside their tile."""
+    E = 64 * lane_syms
+    n = chunks * E - 37
+    rng = np.random.default_rng(chunks + lane_syms)
+    e = np.minimum(rng.geometric(0.5 if lane_syms == 128 else 0.98, n) - 1, 13).astype(np.uint8)
+    for a, b in islands:
+        e[a * E:b * E] = 14 if lane_syms == 128 else rng.integers(0, 16, e[a * E:b * E].size)
+    x = (e << 3) | (rng.integers(0, 256, n, dtype=np.uint8) & 0x87)
+    opts = dict(lane_syms=lane_syms, max_code_len=cap, group_chunks=1)
+    want = ecf8.ecf8_encode(x, 1, n, **opts)
+    assert lane_syms != 128 or want.header.code_len[14] >= 10
+    hdr, d_blob = ecf8.ecf8_encode_gpu(torch.from_numpy(x).to(DEV), 1, n, **opts)
+    torch.cuda.synchronize()
+    assert bytes(hdr) == bytes(want.header)
+    assert torch.equal(d_blob.cpu(), torch.from_numpy(want.numpy()))
+
+
 def _rows_equal(t, row):
     """Is every row of the flat tensor t (a whole number of rows) this row?  In pieces: t may be tens of GB."""
     n = row.numel()
@@ -116,9 +151,8 @@ def _rows_equal(t, row):
 
 @pytest.mark.parametrize("groups", [(1 << 17) + 3, (1 << 21) + 3])
 def test_more_chunks_than_one_launch_takes(groups):
-    """8.6 GB and 137 GB of weights, 32 symbols per lane: 2^22 and 2^26 chunks and some.  The metadata pass takes one launch per
-    2^20 workgroups; as a single launch the larger one has more than the 2^32 work-items a launch can have.  Every group of 32 chunks
-    holds the same weights, whose code bits are a whole number of 16-byte units, so each section of the container is the CPU
+    """8.6 GB and 137 GB of weights, 32 symbols per lane: 2^22 and 2^26 chunks and some, the larger one with more than the 2^32
+    work-items of a launch if each chunk had a wave of its own.  Every group of 32 chunks holds the same weights, whose code bits are a whole number of 16-byte units, so each section of the container is the CPU
     encoder's for one group over and over."""
     period = 32 * 2048
     n = groups * period

@@ -107,8 +107,7 @@ def test_full_size_matrix(orc, fmt):
 @pytest.mark.parametrize("chunks,extra", [(1024, 0), (1024, 1), (2048, -1), (65536, 0), (65536, 1), (65536 + 8192, 5)])
 @pytest.mark.parametrize("fmt", [E5M2, BF16])
 def test_many_chunks(fmt, chunks, extra):
-    """The chunk totals are summed 1024 per workgroup up to 65536 of them, beyond that by one workgroup 8192 at a time, and lie in
-    chunk_bit in another way: whole and nearly whole slices, one chunk more, the first sizes past the limit."""
+    """Many tiles, each placed by what the ones before it have counted: powers of two, one chunk less and more."""
     n = chunks * 4096 + extra
     x = np.resize(_rand_elems(fmt, (1 << 20) + 12345, chunks + extra), n)
     opts = dict(lane_syms=64, max_code_len=16 if extra else 0)
@@ -120,8 +119,27 @@ def test_many_chunks(fmt, chunks, extra):
     assert torch.equal(d_blob.cpu(), torch.from_numpy(want.numpy())) and bool((buf[want.size:] == 0xA5).all())
 
 
+@pytest.mark.parametrize("fmt,lane_syms,cap,chunks,islands", [(BF16, 64, 12, 16500, [(0, 30), (8001, 8400), (16490, 16500)]), (E5M2, 64, 12, 16500, [(3, 40), (8000, 8400), (16490, 16500)]),
+                                                              (BF16, 128, 16, 6200, [(0, 1), (3104, 3105), (6199, 6200)]), (E5M2, 128, 16, 6200, [(17, 18), (3135, 3136), (6197, 6198)])])
+def test_chunks_that_do_not_fit_behind_the_others(fmt, lane_syms, cap, chunks, islands):
+    """Islands of long codewords: chunks that a wave cannot pack behind its others, or at all, before it knows where they go."""
+    E = 64 * lane_syms
+    n = chunks * E - 37
+    rng = np.random.default_rng(chunks + lane_syms)
+    e = np.minimum(rng.geometric(0.5 if lane_syms == 128 else 0.98, n) - 1, 13).astype(np.uint16)
+    for a, b in islands:
+        e[a * E:b * E] = 14 if lane_syms == 128 else rng.integers(0, 32, e[a * E:b * E].size)
+    x = ((e + 100) << 7) | rng.integers(0, 128, n, dtype=np.uint16) if fmt == BF16 else ((e << 2) | rng.integers(0, 4, n, dtype=np.uint16)).astype(np.uint8)
+    opts = dict(lane_syms=lane_syms, max_code_len=cap, group_chunks=1)
+    want = ecfw.ecfw_encode(fmt, x, 1, n, **opts)
+    hdr, d_blob = ecfw.ecfw_encode_gpu(fmt, _to_dev(fmt, x), 1, n, **opts)
+    torch.cuda.synchronize()
+    assert bytes(hdr) == bytes(want.header)
+    assert torch.equal(d_blob[:want.size].cpu(), torch.from_numpy(want.numpy()))
+
+
 def test_more_chunks_than_one_launch_takes():
-    """17 GB of E5M2, 64 symbols per lane: 2^22 chunks and some.  The metadata pass takes one launch per 2^20 workgroups.  Every group
+    """17 GB of E5M2, 64 symbols per lane: 2^22 chunks and some.  Every group
     of 32 chunks holds the same elements, whose code bits are a whole number of 16-byte units, so each section of the
     container is the CPU encoder's for one group over and over."""
     groups, period = (1 << 17) + 3, 32 * 4096
