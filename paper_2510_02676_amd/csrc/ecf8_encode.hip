@@ -127,18 +127,20 @@ __device__ __forceinline__ void write_fixed(const EncArgs &a, const ecf8_header 
 }
 
 // A chunk on its way through encode_tiles.
-//  * Code lengths four at a time: two byte permutes of the 16 lengths held in four registers, selected by the exponents' top
-//    bits, summed by one v_sad_u8.
 //  * Plane: 8 elements -> 4 bytes, byte j = low nibble element j, high nibble element j + 4; zeros where the last chunk reaches past
 //    the tensor.
 //  * Bits: a lane's are one string, the forward run's codewords in order and then the backward run's in reverse (each with its first
 //    bit highest), packed one behind the other in a register; every finished dword is ORed into the image, where neighbouring lanes
 //    share a dword at their borders.  Symbols are looked up in pairs: 256 entries of the two codewords joined and their
-//    length, for either direction.  CAP7 (no codeword over 7 bits): two pairs are joined before they are packed.
+//    length, for either direction.
+//  * CAP7 (no codeword over 7 bits): count joins two pairs and leaves them in their dword, a one above them, and pack has nothing to
+//    look up; its OR instructions keep look-ups from moving past them.  Else count looks lengths up four at a time, by two byte
+//    permutes of the 16 lengths held in four registers, selected by the exponents' top bits and summed by one v_sad_u8.
 template <int N, bool CAP7>
 struct Chunk {
-    typedef typename std::conditional<CAP7, uint32_t, uint64_t>::type Entry;        // codewords; length from bit 26 or 32
-    static constexpr int LEN_AT = CAP7 ? 26 : 32;
+    typedef typename std::conditional<CAP7, uint32_t, uint64_t>::type Entry;        // codewords; length from bit 28 or 32
+    static constexpr int LEN_AT = CAP7 ? 28 : 32;
+    static constexpr uint32_t BITS = (1u << 28) - 1;                                // CAP7: of an entry or two joined ones
     static constexpr int AREA = ((160 * 1024 - 1024 - 512 * (int)sizeof(Entry)) / (4 * WMAX) - 4) / 4 * 4;
     static constexpr int LANE_BITS = N * (CAP7 ? 7 : 15);                           // at most
     static_assert(LANE_BITS < 32 * LATE_DWORDS && LANE_BITS * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
@@ -174,17 +176,37 @@ struct Chunk {
 #pragma unroll
         for (int i = 0; i < N / 16; i++) {
             const int q = i < N / 32 ? i : N / 16 - 1 - (i - N / 32);               // in the order in which pack asks for them
-            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+            const u32x2 plane_piece = nibbles(v[q]);
+            uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                const uint32_t low = (w[k] >> 3) & 0x07070707u;
-                const uint32_t top = ((w[k] >> 2) & 0x10101010u) - ((w[k] >> 6) & 0x01010101u);       // 0x0f in the bytes with exponents 8 .. 15
-                lb = __builtin_amdgcn_sad_u8(bit_select(top, __builtin_amdgcn_perm(len_bytes[3], len_bytes[2], low), __builtin_amdgcn_perm(len_bytes[1], len_bytes[0], low)), 0u, lb);
+                if constexpr (CAP7) {
+                    uint32_t at0, at1;
+                    pair_offsets(w[k], at0, at1);
+                    const bool back = i >= N / 32;
+                    const uint32_t e0 = entry(back ? bwd : fwd, back ? at1 : at0), e1 = entry(back ? bwd : fwd, back ? at0 : at1);
+                    const uint32_t l0 = e0 >> LEN_AT, nb = l0 + (e1 >> LEN_AT);
+                    lb += nb;
+                    w[k] = (((e1 << l0) | e0) & BITS) | (1u << nb);                 // e1's length lands above the codewords
+                } else {
+                    const uint32_t low = (w[k] >> 3) & 0x07070707u;
+                    const uint32_t top = ((w[k] >> 2) & 0x10101010u) - ((w[k] >> 6) & 0x01010101u);       // 0x0f in the bytes with exponents 8 .. 15
+                    lb = __builtin_amdgcn_sad_u8(bit_select(top, __builtin_amdgcn_perm(len_bytes[3], len_bytes[2], low), __builtin_amdgcn_perm(len_bytes[1], len_bytes[0], low)), 0u, lb);
+                }
             }
-            *(GLOBAL u32x2 *)(plane + q * (p.stride / 2)) = nibbles(v[q]);
+            if constexpr (CAP7) v[q] = u32x4{w[0], w[1], w[2], w[3]};
+            *(GLOBAL u32x2 *)(plane + q * (p.stride / 2)) = plane_piece;
         }
         return lb;
     }
+    // where the entries of a dword's two pairs of symbols are: bytes into a table of dwords
+    static __device__ __forceinline__ void pair_offsets(uint32_t w, uint32_t &at0, uint32_t &at1)
+    {
+        const uint32_t x = (w >> 1) & 0x3c3c3c3cu, u = x | (x >> 4);
+        at0 = u & 0x3fcu;
+        at1 = (u >> 16) & 0x3fcu;
+    }
+    static __device__ __forceinline__ uint32_t entry(const Entry *tab, uint32_t at) { return *(const uint32_t *)((const uint8_t *)tab + at); }
     // any chunk, piece by piece: its symbols one by one, those past the tensor's end have no bits
     __device__ __forceinline__ u32x4 piece(uint64_t e, uint32_t back, uint32_t (&s)[16]) const
     {
@@ -230,14 +252,14 @@ struct Chunk {
     template <bool BWD>
     __device__ __forceinline__ void put4(LanePacker &out, uint32_t w) const
     {
-        const Entry *tab = BWD ? bwd : fwd;
-        const uint32_t x = (w >> 3) & 0x0f0f0f0fu, u = x | (x >> 4);                // bytes 0 and 2: two exponents each
-        Entry ea = tab[u & 0xffu], eb = tab[(u >> 16) & 0xffu];
-        if (BWD) { const Entry y = ea; ea = eb; eb = y; }
-        if constexpr (CAP7) {
-            const uint32_t la = ea >> LEN_AT, lb = eb >> LEN_AT;
-            out.put((ea & ((1u << LEN_AT) - 1u)) | ((eb & ((1u << LEN_AT) - 1u)) << la), la + lb);
+        if constexpr (CAP7) {                                                       // as count has left them
+            const uint32_t nb = 31u - (uint32_t)__builtin_clz(w);
+            out.put(w ^ (1u << nb), nb);
         } else {
+            const Entry *tab = BWD ? bwd : fwd;
+            const uint32_t x = (w >> 3) & 0x0f0f0f0fu, u = x | (x >> 4);            // bytes 0 and 2: two exponents each
+            Entry ea = tab[u & 0xffu], eb = tab[(u >> 16) & 0xffu];
+            if (BWD) { const Entry y = ea; ea = eb; eb = y; }
             out.put((uint32_t)ea, (uint32_t)(ea >> LEN_AT));
             out.put((uint32_t)eb, (uint32_t)(eb >> LEN_AT));
         }
@@ -261,9 +283,10 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M weights (14336 x 4096): 32 us for the 111 MB read and written, half of it the first loads, the exchange
-// and the copy to the stream, when the compute unit waits; metadata and planes, prefix sum and packing as kernels of their own took 40, and
-// read the weights twice.  The whole call 67.7 -> 59.2 us, 16384 x 16384 242 -> 203.
+// The container behind the code.  58.7 M weights (14336 x 4096): 28 us for the 111 MB read and written (30 with two pairs looked up again for every put),
+// 17 of them bound by vector operations, the others the first loads, the exchange and the copy to the stream, when the compute unit waits;
+// metadata and planes, prefix sum and packing as kernels of their own took 40, and read the weights twice.  The whole call 67.7 -> 56.4 us,
+// 16384 x 16384 242 -> 196.
 template <int N, bool CAP7>
 __global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, ecf8_header h, uint32_t per_wave)
 {

@@ -149,21 +149,31 @@ __device__ __forceinline__ void write_fixed(const WEncArgs &a, const WCodeArgs &
     if (h.sign_bytes) zero(a.off_sg + h.sign_bytes, h.total_size);
 }
 
-// A chunk on its way through encode_tiles, as in the E4M3 encoder.  The codewords come from the host with the launch; symbols are looked up
-// one by one (256 of them would make a pair table of 256 KiB), codeword and length in one dword, and packed two at a time.
-// LMAX: the longest codeword in use is at most this.
+// A chunk on its way through encode_tiles, as in the E4M3 encoder.  The codewords come from the host with the launch.  LMAX: the longest codeword
+// in use is at most this.  Look-ups:
+//  * BF16 one symbol at a time (256 of them would make a pair table of 256 KiB), E5M2 up to 12 bits two at a time; codeword(s) and from
+//    bit 27 on their length in one dword, so that joining two of them is one operation.
+//  * QUADS (up to 12 bits): count joins four codewords and leaves them in the place of their elements, for pack to put them in one go.
+//    They are nearly always less than 32 bits; a chunk where they are not is fetched again and packed two codewords at a time.
+// What bounds it: BF16, with 38 us in the kernel for 14336 x 4096, a copy's rate; E5M2 the vector operations (45 us looked up element by element in
+// count and again in pack, 40 now; BF16 40 and 39).
 template <int FMT, int N, int LMAX>
 struct Chunk {
     using F = EFmt<FMT>;
     static constexpr int P = F::P, A = F::A, PIECES = N / P;
-    static constexpr int AREA = ((160 * 1024 - 1024 - 8 * (A + 1) - 256) / (4 * WMAX) - 4) / 4 * 4;
+    static constexpr bool QUADS = LMAX <= 12 && PIECES <= 8, PAIRS = QUADS && FMT == ECFW_FMT_E5M2;
+    static constexpr uint32_t BITS = (1u << 27) - 1;                                // of a dword that holds codewords and their length
+    static constexpr int PAIR_ENTRIES = PAIRS ? A * A : 1;
+    static constexpr int AREA = ((160 * 1024 - 1024 - 8 * (A + 1) - 256 - 8 * PAIR_ENTRIES) / (4 * WMAX) - 4) / 4 * 4;
     static_assert(N * LMAX < 32 * LATE_DWORDS && N * LMAX * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
 
     const WEncArgs &a;
-    const uint32_t (*code)[A + 1];          // code | length << 16, first bit lowest / highest; A = no symbol
+    const uint32_t (*code)[A + 1];          // code | length << 27, first bit lowest / highest; A = no symbol
+    const uint32_t (*pair)[PAIR_ENTRIES];   // two codewords and from bit 27 on their length, in order / in reverse
     const uint8_t *len;
     int lane;
     u32x4 v[PIECES];
+    bool wide;                              // QUADS: there are four codewords of 32 bits or more
 
     __device__ __forceinline__ bool whole(uint64_t c) const { return (c + 1) * (64ull * N) <= a.n; }
     __device__ __forceinline__ void fetch(uint64_t c)
@@ -197,39 +207,110 @@ struct Chunk {
     __device__ __forceinline__ uint32_t count(uint64_t c)
     {
         const ChunkPlace p = place_of<FMT, N>(a, c, lane);
-        uint32_t lb = 0;
+        uint32_t lb = 0, most = 0;
 #pragma unroll
         for (int i = 0; i < PIECES; i++) {
             const int q = i < PIECES / 2 ? i : PIECES - 1 - (i - PIECES / 2);       // in the order in which pack asks for them
-            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-            for (int j = 0; j < P; j++) lb += len[F::sym(w, j)];
             planes(p.base + p.lane_off + q * p.stride, v[q]);
+            uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+            const int back = i < PIECES / 2 ? 0 : 1;
+            if constexpr (PAIRS) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const uint32_t u = pair_index(w[k]), e0 = pair[back][u & 1023u], e1 = pair[back][(u >> 16) & 1023u];
+                    const uint32_t x0 = back ? e1 : e0, x1 = back ? e0 : e1, n0 = x0 >> 27, nb = n0 + (x1 >> 27);
+                    most |= nb;
+                    lb += nb;
+                    w[k] = (x0 & BITS) | ((x1 & BITS) << n0) | (1u << (nb & 31u));      // a one above the codewords says how many bits they are
+                }
+            } else if constexpr (QUADS) {
+                uint32_t r[4];
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    uint32_t x[4], n0, n1, nb;              // in the order in which pack puts them
+#pragma unroll
+                    for (int j = 0; j < 4; j++) x[j] = code[back][F::sym(w, back ? 7 - 4 * k - j : 4 * k + j)];
+                    const uint32_t p0 = joined(x[0], x[1], n0), p1 = joined(x[2], x[3], n1);
+                    nb = n0 + n1;
+                    r[2 * k] = p0 | (p1 << (n0 & 31u));
+                    r[2 * k + 1] = nb;
+                    most |= nb;
+                    lb += nb;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k++) w[k] = r[k];
+            } else {
+#pragma unroll
+                for (int j = 0; j < P; j++) lb += len[F::sym(w, j)];
+            }
+            if constexpr (QUADS) v[q] = u32x4{w[0], w[1], w[2], w[3]};
         }
+        wide = __ballot(most & 32u) != 0;
         return lb;
+    }
+    // two codewords (27 bits at the most) one behind the other, and the length of both
+    static __device__ __forceinline__ uint32_t joined(uint32_t x0, uint32_t x1, uint32_t &nb)
+    {
+        const uint32_t l0 = x0 >> 27;
+        nb = l0 + (x1 >> 27);
+        return (x0 | (x1 << l0)) & BITS;                    // x1's length lands above the codewords
+    }
+    // E5M2: exponents of a dword's elements 0 and 1 in bits 0 .. 9, of 2 and 3 in bits 16 .. 25, others not 0
+    static __device__ __forceinline__ uint32_t pair_index(uint32_t w)
+    {
+        const uint32_t t = (w >> 2) & 0x1f1f1f1fu;
+        return bit_select(0x001f001fu, t, t >> 3);
     }
     static __device__ __forceinline__ void put2(LanePacker &out, uint32_t x0, uint32_t x1)
     {
-        out.put((x0 & 0xffffu) | ((x1 & 0xffffu) << (x0 >> 16)), (x0 >> 16) + (x1 >> 16));
+        uint32_t nb;
+        const uint32_t x = LMAX <= 13 ? joined(x0, x1, nb) : (x0 & 0xffffu) | ((x1 & 0xffffu) << (x0 >> 27));
+        out.put(x, LMAX <= 13 ? nb : (x0 >> 27) + (x1 >> 27));
+    }
+    template <bool BACK>
+    __device__ __forceinline__ void put_piece(LanePacker &out, const u32x4 &v4) const
+    {
+        const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+        for (int j = 0; j < P; j += 2)
+            put2(out, code[BACK][F::sym(w, BACK ? P - 1 - j : j)], code[BACK][F::sym(w, BACK ? P - 2 - j : j + 1)]);
+    }
+    // what count has left of a piece
+    template <bool BACK>
+    __device__ __forceinline__ void put_quads(LanePacker &out, const u32x4 &v4) const
+    {
+        const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w};
+        if constexpr (PAIRS) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint32_t x = w[BACK ? 3 - k : k], nb = 31u - (uint32_t)__builtin_clz(x);
+                out.put(x ^ (1u << nb), nb);
+            }
+        } else {
+            out.put(w[0], w[1]);
+            out.put(w[2], w[3]);
+        }
     }
     __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t c, bool refill)
     {
         LanePacker out(image, at);
+        if (QUADS && wide) fetch(c);
         const ChunkPlace p = place_of<FMT, N>(a, c + 1, lane);
         const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x + (p.base + p.lane_off) * F::ELEM;
+        if (!QUADS || wide) {
 #pragma unroll
-        for (int q = 0; q < PIECES / 2; q++) {
-            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+            for (int i = 0; i < PIECES; i++) {
+                const int q = i < PIECES / 2 ? i : PIECES - 1 - (i - PIECES / 2);
+                if (i < PIECES / 2) put_piece<false>(out, v[q]); else put_piece<true>(out, v[q]);
+                if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
+            }
+        } else {
 #pragma unroll
-            for (int j = 0; j < P; j += 2) put2(out, code[0][F::sym(w, j)], code[0][F::sym(w, j + 1)]);
-            if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
-        }
-#pragma unroll
-        for (int q = PIECES - 1; q >= PIECES / 2; q--) {
-            const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
-#pragma unroll
-            for (int j = P - 1; j > 0; j -= 2) put2(out, code[1][F::sym(w, j)], code[1][F::sym(w, j - 1)]);
-            if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
+            for (int i = 0; i < PIECES; i++) {
+                const int q = i < PIECES / 2 ? i : PIECES - 1 - (i - PIECES / 2);
+                if (i < PIECES / 2) put_quads<false>(out, v[q]); else put_quads<true>(out, v[q]);
+                if (refill) v[q] = *(const GLOBAL u32x4 *)(x + q * p.stride * F::ELEM);
+            }
         }
         out.finish();
     }
@@ -252,7 +333,7 @@ struct Chunk {
             uint32_t s[P];
             const u32x4 w = piece(e, 0, s);
 #pragma unroll
-            for (int j = 0; j < P; j++) lb += s[j] >> 16;
+            for (int j = 0; j < P; j++) lb += s[j] >> 27;
             if (planes_) planes(e, w);
         }
         return lb;
@@ -273,9 +354,8 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M elements (14336 x 4096): BF16 45 us for the 198 MB read and written, E5M2 45 for 101 MB (62 and 57 with metadata and
-// planes, prefix sum and packing as kernels of their own); bound by the look-ups, two of LDS per element.  The whole call 99 -> 80 us and
-// 85 -> 73, 16384 x 16384 in BF16 458 -> 336.
+// The container behind the code.  58.7 M elements (14336 x 4096): BF16 39 us for the 198 MB read and written, E5M2 40 for 101 MB (62 and 57 with metadata and
+// planes, prefix sum and packing as kernels of their own).  The whole call 99 -> 79 us and 85 -> 68, 16384 x 16384 460 -> 331 and 252 -> 207.
 template <int FMT, int N, int LMAX>
 __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeArgs ca, uint32_t per_wave)
 {
@@ -283,19 +363,30 @@ __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeAr
     constexpr int A = K::A;
     __shared__ __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA + 4];  // the last of the four in front is image[-1]
     __shared__ uint32_t s_code[2][A + 1];
+    __shared__ uint32_t s_pair[2][K::PAIR_ENTRIES];
     __shared__ uint32_t s_len4[64];
     __shared__ TileShared sh;
     const uint32_t tid = threadIdx.x;
     const int wave = (int)uniform32(tid >> 6);
     if (tid < (uint32_t)A) {
         const uint32_t code = ca.code[tid], l = ca.len[tid];
-        s_code[0][tid] = l ? (__brev(code) >> (32 - l)) | (l << 16) : 0u;
-        s_code[1][tid] = code | (l << 16);
+        s_code[0][tid] = l ? (__brev(code) >> (32 - l)) | (l << 27) : 0u;
+        s_code[1][tid] = code | (l << 27);
     }
     if (tid < 2) s_code[tid][A] = 0;
     if (tid < 64) s_len4[tid] = ((const uint32_t *)ca.len)[tid];
+    if constexpr (K::PAIRS) {
+        __syncthreads();
+        for (uint32_t i = tid; i < (uint32_t)K::PAIR_ENTRIES; i += blockDim.x) {
+            const uint32_t lo = i % A, hi = i / A;          // an entry's first and second element
+            uint32_t nb;
+            s_pair[0][i] = K::joined(s_code[0][lo], s_code[0][hi], nb);
+            s_pair[1][i] = K::joined(s_code[1][hi], s_code[1][lo], nb) | (nb << 27);
+            s_pair[0][i] |= nb << 27;
+        }
+    }
     write_fixed(a, ca);
-    K k{a, s_code, (const uint8_t *)s_len4, (int)(tid & 63), {}};
+    K k{a, s_code, s_pair, (const uint8_t *)s_len4, (int)(tid & 63), {}, false};
     encode_tiles(k, sh, images[wave] + 4, TileArgs{a.n_chunks, per_wave, (const uint32_t *)&ca.h}, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st,
                  (int)(tid & 63), wave);
 }
