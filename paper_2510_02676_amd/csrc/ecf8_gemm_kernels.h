@@ -121,6 +121,20 @@ __device__ __forceinline__ void load_x_slice(const GArgs &a, int tid,
             }
 }
 
+// A lane's pieces Q and Q + 2 of the nibble plane (16 bytes of the matrix each; row l % 16, column 64 Q + 16 g, g = l / 16) out of one
+// 16-byte load.  The four lanes of a row fetch two times 32 bytes of it, lane g the (g % 2)-th half of piece Q + 2 (g / 2) for g' = 0 .. 3, and two
+// exchanges between the rows of 16 lanes give every lane what is its own.  Against 8 bytes a piece: half the load instructions, and the two of a
+// chunk are adjacent in time, so that they share their 64 bytes while the first-level cache has them (hence no nontemporal loads).
+// Eight experts, M = 4 / 16: 97.3 / 103.9 us with 8 bytes a piece, 87.8 / 93.5 with 16, 86.3 / 90.2 cached; 4096 x 14336, M = 16: 22.8, 19.4, 18.6.
+__device__ __forceinline__ uint32_t plane_lane(int lane) { return 64u * ((uint32_t)lane >> 5) + 16u * (((uint32_t)lane >> 4) & 1u); }
+__device__ __forceinline__ void deal_plane(u32x4 v, u32x2 &a, u32x2 &b)
+{
+    auto s0 = __builtin_amdgcn_permlane16_swap(v.x, v.z, false, false), s1 = __builtin_amdgcn_permlane16_swap(v.y, v.w, false, false);
+    auto t0 = __builtin_amdgcn_permlane32_swap(s0[0], s0[1], false, false), t1 = __builtin_amdgcn_permlane32_swap(s1[0], s1[1], false, false);
+    a = u32x2{t0[0], t1[0]};
+    b = u32x2{t0[1], t1[1]};
+}
+
 // The pair table the encoder embedded, if it did, on its way from the blob to LDS.
 template <int NW> constexpr int TABLE_UNITS = (TBL_ENTRIES * 2 / 16 + NW * 64 - 1) / (NW * 64);     // 16-byte units per thread
 template <int NW>
@@ -391,6 +405,60 @@ __device__ __forceinline__ void reduce_split(f32x4 *red, uint32_t *s_flag, const
     if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// 16 bytes of the stream; NT: past the caches.  A chunk's bytes are used once, but the lines at its ends belong to two chunks, and which way pays is a matter of
+// measurement: nontemporal / cached, us: M <= 16 with X in registers 14336 x 4096 19.1 / 19.3, eight experts 86.2 / 87.1; without 4096 x 14336 18.1 / 17.5;
+// more tiles of X 14336 x 4096, M = 64 30.6 / 29.3, 14336 x 7168, M = 32 43.7 / 41.8, M = 64 with group scales 90.3 / 86.8.
+template <bool NT>
+__device__ __forceinline__ u32x4 load_unit(const GLOBAL uint8_t *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load((const GLOBAL u32x4 *)p);
+    else return *(const GLOBAL u32x4 *)p;
+}
+
+// What of a chunk is needed before its bits: where it starts and ends in the stream and the bits of this lane.
+// ONE: fetched in one instruction of four bytes a lane, lanes 0 .. 31 the lanes' bits, two each, lanes 32 .. 35 the two positions (the others those
+// again); as two they are loads of 2 and 16 bytes a lane, the latter the same for all.  14336 x 7168, M = 32, scales of W: 46.5 us -> 44.2, 4096 x 14336,
+// M = 16: 19.4 -> 18.7; with four tiles of X and group scales, which crowd the registers, 94.9 -> 101.5, so not there.
+template <bool ONE>
+struct ChunkMeta {
+    uint64_t b0 = 0, b1 = 0;
+    uint32_t lb = 0;                        // ONE: as fetched
+    __device__ __forceinline__ uint64_t begin() const { return ONE ? pair(32) : uniform64(b0); }
+    __device__ __forceinline__ uint64_t end() const { return ONE ? pair(34) : uniform64(b1); }
+    __device__ __forceinline__ uint32_t lane_bits(int lane) const
+    {
+        return ONE ? ((uint32_t)__builtin_amdgcn_ds_bpermute((lane >> 1) * 4, (int)lb) >> (16 * (lane & 1))) & 0xffffu : lb;
+    }
+    __device__ __forceinline__ uint64_t pair(int l) const
+    {
+        return (uint32_t)__builtin_amdgcn_readlane((int)lb, l) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lb, l + 1) << 32;
+    }
+};
+template <bool ONE>
+struct MetaReader {
+    uint64_t at, off_lb;                    // ONE: of this lane's dword for chunk 0; else the blob's chunk_bit and lane_bits
+    uint32_t step, lane;
+    __device__ __forceinline__ MetaReader(const GArgs &a, int lane_)
+    {
+        lane = (uint32_t)lane_;
+        at = a.d_blob + (!ONE ? a.off_cb : lane < 32 ? a.off_lb + 4 * lane : a.off_cb + 4 * (lane & 3));
+        off_lb = a.d_blob + a.off_lb;
+        step = lane < 32 ? 128u : 8u;
+    }
+    __device__ __forceinline__ ChunkMeta<ONE> operator()(uint64_t c) const
+    {
+        ChunkMeta<ONE> m;
+        if constexpr (ONE) {
+            m.lb = *(const GLOBAL uint32_t *)(at + (uint64_t)(uint32_t)c * step);           // a chunk's number is below 2^32
+        } else {
+            m.b0 = ((const GLOBAL uint64_t *)at)[c];
+            m.b1 = ((const GLOBAL uint64_t *)at)[c + 1];
+            m.lb = ((const GLOBAL uint16_t *)off_lb)[c * 64 + lane];
+        }
+        return m;
+    }
+};
+
 template <int MT, int NW, int N, int SC, int ACC = 0>       // SC: 0 no scales, 1 scales of W (and one per row of X), 2 also one per row and 128 columns of X; ACC: see ECF8_MFMA_OPERANDS
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
 {
@@ -405,66 +473,51 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
     uint8_t *stage = smem + stage_off;
 
-    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(a.d_blob + a.off_cb);
-    const GLOBAL uint16_t *lane_bits = (const GLOBAL uint16_t *)(a.d_blob + a.off_lb);
     const GLOBAL uint8_t *stream = (const GLOBAL uint8_t *)(a.d_blob + a.off_st);
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
-    // this lane's piece 0 inside a chunk: row l % 16, column 16 (l / 16) of the block
-    const uint64_t lane_elem = (uint64_t)(lane & 15) * GK + (uint64_t)(lane >> 4) * 16;
 
-    struct Meta { uint64_t b0, b1; uint32_t lb; };
+    constexpr bool META1 = false;
+    using Meta = ChunkMeta<META1>;
+    const MetaReader<META1> meta(a, lane);
     const uint64_t n_blocks = a.rows / BLOCK_ROWS;
     const uint32_t wave_s = uniform32((uint32_t)wave);             // the same for every lane: chunk addresses stay in scalar registers
     // the wave's chunks in the order it meets them: step s = its (s % KPW)-th chunk of its (s / KPW)-th block
     auto block_of = [&](uint64_t s) -> uint64_t { return blockIdx.x + (s / KPW) * (uint64_t)gridDim.x; };
     auto kc_of = [&](uint64_t s) -> uint32_t { return wave_s + NW * (uint32_t)(s % KPW); };
-    auto load_meta = [&](uint64_t s) {
-        const uint64_t c = block_of(s) * KCHUNKS + kc_of(s);
-        Meta m;
-        m.b0 = chunk_bit[c];
-        m.b1 = chunk_bit[c + 1];
-        m.lb = lane_bits[c * 64 + lane];
-        return m;
-    };
+    auto load_meta = [&](uint64_t s) { return meta(block_of(s) * KCHUNKS + kc_of(s)); };
     // A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead), from the chunk's two start
     // bits: values every lane holds alike, so the arithmetic is done once, in scalar registers.
-    auto span_of = [&](const Meta &m, uint64_t &byte0) {
-        const uint64_t b0 = uniform64(m.b0), b1 = uniform64(m.b1);
-        uint64_t byte_end = ((b1 + 7) >> 3) + 8;
-        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
-        byte0 = (b0 >> 3) & ~15ull;
-        if (byte0 > byte_end) byte0 = byte_end;
-        return byte_end - byte0;
-    };
     // The span's 16-byte units into `seg` (unit lane + 64 k into seg[k]); units beyond the span keep what they
     // held: the lanes' codewords never reach into them.
     const uint32_t lane16 = (uint32_t)lane * 16;
     auto load_stream = [&](const Meta &m, u32x4 (&seg)[GSEGS], bool wanted = true) {
-        uint64_t byte0;
-        const uint32_t whole = (uint32_t)span_of(m, byte0);         // at most GSTAGE under the cap on codewords
-        const uint32_t span = wanted ? whole : 0u;
+        uint64_t byte_end = ((m.end() + 7) >> 3) + 8, byte0 = (m.begin() >> 3) & ~15ull;
+        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
+        if (byte0 > byte_end) byte0 = byte_end;
+        const uint32_t span = wanted ? (uint32_t)(byte_end - byte0) : 0u;       // at most GSTAGE under the cap on codewords
         const GLOBAL uint8_t *sp = stream + byte0;
 #pragma unroll
         for (int k = 0; k < GSEGS; k++) {
             const uint32_t i = lane16 + 1024 * k;
-            if (i < (uint32_t)GSTAGE && i < span) seg[k] = __builtin_nontemporal_load((const GLOBAL u32x4 *)(sp + i));
+            if (i < (uint32_t)GSTAGE && i < span) seg[k] = load_unit<MT == 1>(sp + i);
         }
     };
-    // nibble plane of step s: piece q of this lane at plane_of(s) + lane_plane + 32 q
-    const uint32_t lane_plane = (uint32_t)(lane_elem / 2);
+    // nibble plane of step s: this lane's part of pieces q and q + 2 at plane_of(s) + lane_plane + 32 q, see deal_plane
+    const uint32_t lane_plane = (uint32_t)(lane & 15) * (GK / 2) + plane_lane(lane);
     auto plane_of = [&](uint64_t s) -> const GLOBAL uint8_t * {
         return plane + (block_of(s) * BLOCK_ROWS * (uint64_t)GK + kc_of(s) * (uint64_t)BLOCK_COLS) / 2;
     };
 
     // start-up: the first chunks' loads and those of X are in flight while the table is set up
     const uint64_t n_steps = blockIdx.x < n_blocks ? ((n_blocks - blockIdx.x + gridDim.x - 1) / gridDim.x) * KPW : 0;
-    Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
+    Meta m_cur, m_next;
     u32x4 seg[GSEGS];
-    u32x2 pl[GPIECES];
+    static_assert(GPIECES == 4, "deal_plane");
+    u32x4 pl[2];
 #pragma unroll
     for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
+    for (int q = 0; q < 2; q++) pl[q] = u32x4{0, 0, 0, 0};
     // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
     // table first, since it is what the workgroup meets for (M = 16: 21.0 -> 20.7 us; M = 32 25.5 -> 25.2, M = 64 with scales of W
     // 34.4 -> 34.2).  Not with four tiles of X and no scales, where the metadata come first (30.0 us; in this order 30.7).
@@ -480,7 +533,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
         if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(0);
 #pragma unroll
-        for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * q));
+        for (int q = 0; q < 2; q++) pl[q] = *(const GLOBAL u32x4 *)(pp + lane_plane + 32 * q);
     }
     u32x4 areg[MT][KPW][GPIECES];
     load_x_slice<MT, NW, N>(a, tid, areg);
@@ -507,10 +560,8 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
         for (int i = 0; i < KPW; i++) {
             const uint64_t s = s0 + i;
             const Meta m = m_cur;
-            uint64_t byte0;
-            span_of(m, byte0);
-            const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
-            const uint64_t start = uniform64(m.b0);
+            const uint32_t lb = m.lane_bits(lane), rel = wave_incl_scan(lb) - lb;
+            const uint32_t start = (uint32_t)m.begin() & 127u;     // of the chunk's first bit in its image
 #pragma unroll
             for (int k = 0; k < GSEGS; k++) {
                 const uint32_t j = lane16 + 1024 * k;
@@ -524,9 +575,9 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
             load_stream(m_next, seg, more);
             const Meta m_next2 = load_meta(sn2);
             const GLOBAL uint8_t *pp = more ? plane_of(sn) : plane;
-            const uint32_t bpA = stage_off * 8 + (uint32_t)(start - byte0 * 8) + rel - 1;   // one bit off, see quad_step2
+            const uint32_t bpA = stage_off * 8 + start + rel - 1;   // one bit off, see quad_step2
             HeldRuns runs;
-            runs.begin(smem, bpA, bpA + m.lb - 30);
+            runs.begin(smem, bpA, bpA + lb - 30);
             ChunkSums<MT, SC> sums;
             sums.begin(a, block_of(s), kc_of(s));
             auto &dstA = sums.first(acc);
@@ -536,12 +587,13 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
                 uint32_t dwA[4], dwB[4];
 #pragma unroll
                 for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
-                // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
-                const u32x4 wA = merge_piece(dwA, pl[Q]);
-                pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * Q));
+                // two pieces of the nibble plane are merged, and their registers take the same pieces of the next chunk
+                u32x2 pA, pB;
+                deal_plane(pl[Q], pA, pB);
+                pl[Q] = *(const GLOBAL u32x4 *)(pp + lane_plane + 32 * Q);
+                const u32x4 wA = merge_piece(dwA, pA);
                 ECF8_MFMA_PIECE(dstA, areg, i, Q, wA);
-                const u32x4 wB = merge_piece(dwB, pl[Q + GPIECES / 2]);
-                pl[Q + GPIECES / 2] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + lane_plane + 32 * (Q + GPIECES / 2)));
+                const u32x4 wB = merge_piece(dwB, pB);
                 ECF8_MFMA_PIECE(dstB, areg, i, Q + GPIECES / 2, wB);
             }
             sums.end(acc, a, lane);
@@ -680,11 +732,12 @@ struct Place {
 
 // Chunks of a block whose share of X a wave keeps in registers for the whole matrix (0: it fetches X chunk by chunk).  One tile
 // of X only: two chunks of it are 32 registers, and with more tiles or chunks they are not there.  Two pay from the second block of
-// rows on; a workgroup with one (1024 x 7168, M = 16: 13.9 us) only waits longer for its first look-up (14.8).
-template <int MT, int NW>
+// rows on; a workgroup with one (1024 x 7168, M = 16: 13.9 us) only waits longer for its first look-up (14.8).  Not on the F16 matrix cores
+// (ACC = 1), where the converted operands beside them spill (14336 x 7168, M = 16: 45 us; fetched chunk by chunk 41).
+template <int MT, int NW, int ACC>
 __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t blocks)
 {
-    return MT != 1 ? 0u : kchunks <= NW ? 1u : kchunks <= 2 * NW && blocks > 1 ? 2u : 0u;
+    return MT != 1 ? 0u : kchunks <= NW ? 1u : ACC == 0 && kchunks <= 2 * NW && blocks > 1 ? 2u : 0u;
 }
 
 // The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units of them), table
@@ -696,10 +749,10 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 //    eighth), which costs little beside the others' work.
 //  * KRES = 0: the units' chunks form one sequence, and wave w takes every NW-th of it from the w-th on, across the units'
 //    borders; batches are rounded down to whole rounds of the waves.
-// What bounds it: the requests for the blob's bytes, the look-ups and the vector operations about equally (eight experts, M = 4: without
-// nibble loads 87 us, without stream loads 87, without look-ups 92, all 97).  Eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W,
-// M = 4 / 16 / 64: block by block with a barrier each and X fetched for every chunk 106 / 126 / 294 us, in one sequence 106 / 127 / 269,
-// now 97 / 103 / 269.
+// What bounds it: the requests for the blob's bytes, the look-ups and the vector operations about equally (eight experts, M = 4, 97 us when
+// this was asked: without nibble loads 87, without stream loads 87, without look-ups 92).  Eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales
+// of W, M = 4 / 16 / 64: block by block with a barrier each and X fetched for every chunk 106 / 126 / 294 us, in one sequence 106 / 127 / 269, with X
+// resident 97 / 103 / 269; with the fewer and wider loads of deal_plane and ChunkMeta 86 / 89 / 235.
 template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, bool PINNED, int KRES>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
                                           uint32_t my_units)
@@ -716,18 +769,17 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
     uint8_t *stage = smem + stage_off;
 
-    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(a.d_blob + a.off_cb);
-    const GLOBAL uint16_t *lane_bits = (const GLOBAL uint16_t *)(a.d_blob + a.off_lb);
     const GLOBAL uint8_t *stream = (const GLOBAL uint8_t *)(a.d_blob + a.off_st);
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
-    const uint64_t lane_elem = (uint64_t)(lane & 15) * a.K + (uint64_t)(lane >> 4) * 16;
     const uint32_t kchunks = (uint32_t)(a.K / BLOCK_COLS);
     const uint32_t unit_chunks = SPLIT ? kchunks / a.slices : kchunks;
     // split K: the grid is the units, each workgroup has one
     const uint32_t k0 = SPLIT ? (uint32_t)first_unit % a.slices * unit_chunks : 0u;
     const uint32_t block0 = SPLIT ? (uint32_t)first_unit / a.slices : (uint32_t)first_unit;
 
-    struct Meta { uint64_t b0, b1; uint32_t lb; };
+    constexpr bool META1 = !(MT == 4 && SC == 2);
+    using Meta = ChunkMeta<META1>;
+    const MetaReader<META1> meta(a, lane);
     // NW chunks on: over at most this many units and so many chunks more
     const uint32_t hop = (uint32_t)NW / unit_chunks, hop_kc = (uint32_t)NW % unit_chunks;
     const uint32_t skip = (unit_stride - 1) * unit_chunks;         // the other workgroups' chunks between one unit and the next
@@ -767,21 +819,14 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         return w;
     };
     auto valid = [&](const Place &w) { return w.b < my_units; };
-    auto load_meta = [&](const Place &w) {
-        Meta m;
-        m.b0 = chunk_bit[w.c];
-        m.b1 = chunk_bit[w.c + 1];
-        m.lb = lane_bits[(uint64_t)w.c * 64 + lane];
-        return m;
-    };
+    auto load_meta = [&](const Place &w) { return meta(w.c); };
     // A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead), from the chunk's two start
     // bits: values every lane holds alike, so the arithmetic is done once, in scalar registers.
     // The span's 16-byte units into `seg` (unit lane + 64 k into seg[k]); units beyond the span keep what they
     // held: the lanes' codewords never reach into them.
     const uint32_t lane16 = (uint32_t)lane * 16;
     auto load_stream = [&](const Meta &m, u32x4 (&seg)[GSEGS], bool wanted = true) {
-        const uint64_t b0 = uniform64(m.b0), b1 = uniform64(m.b1);
-        uint64_t byte_end = ((b1 + 7) >> 3) + 8, byte0 = (b0 >> 3) & ~15ull;
+        uint64_t byte_end = ((m.end() + 7) >> 3) + 8, byte0 = (m.begin() >> 3) & ~15ull;
         if (byte_end > a.st_bytes) byte_end = a.st_bytes;
         if (byte0 > byte_end) byte0 = byte_end;
         const uint32_t span = wanted ? (uint32_t)(byte_end - byte0) : 0u;      // at most GSTAGE under the cap on codewords
@@ -789,24 +834,25 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll
         for (int k = 0; k < GSEGS; k++) {
             const uint32_t i = lane16 + 1024 * k;
-            if (i < (uint32_t)GSTAGE && i < span) seg[k] = __builtin_nontemporal_load((const GLOBAL u32x4 *)(sp + i));
+            if (i < (uint32_t)GSTAGE && i < span) seg[k] = load_unit<MT == 1 && KRES != 0>(sp + i);
         }
     };
-    // nibble plane of a chunk: piece q of this lane at plane_of(w) + lane_plane + 32 q.  Block and column of chunk c begin at
+    // nibble plane of a chunk: this lane's part of pieces q and q + 2 at plane_of(w) + lane_plane + 32 q, see deal_plane.  Block and column of chunk c begin at
     // element 256 * (16 * block * kchunks + k), k = c - block * kchunks.
-    const uint64_t lane_plane = lane_elem / 2;
+    const uint64_t lane_plane = (uint64_t)(lane & 15) * (a.K / 2) + plane_lane(lane);
     auto plane_of = [&](const Place &w) -> const GLOBAL uint8_t * {
         return plane + ((uint64_t)(16 * w.c - 15 * (k0 + w.kc)) << 7);
     };
 
     Place cur = first_place();
-    Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
+    Meta m_cur, m_next;
     u32x4 seg[GSEGS];
-    u32x2 pl[GPIECES];
+    static_assert(GPIECES == 4, "deal_plane");
+    u32x4 pl[2];
 #pragma unroll
     for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < GPIECES; q++) pl[q] = u32x2{0, 0};
+    for (int q = 0; q < 2; q++) pl[q] = u32x4{0, 0, 0, 0};
     XPieces<MT, N> x_cur[KRES > 1 ? KRES : 1];
     // The order of ecf8_gemm_kernel, but not in groups with two tiles of X and scales of W or with two or four and no scales.
     // Metadata first / this order, us: six experts, M = 20 and scales of W 117.7 / 123.4, no scales 112.0 / 114.0; M = 32 and no scales
@@ -823,7 +869,7 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(cur) + lane_plane;
 #pragma unroll
-        for (int q = 0; q < GPIECES; q++) pl[q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * q));
+        for (int q = 0; q < 2; q++) pl[q] = *(const GLOBAL u32x4 *)(pp + 32 * q);
         load_x_chunk<MT, N>(a, lane, k0 + cur.kc, x_cur[0]);
     }
     if constexpr (EARLY) {
@@ -857,8 +903,8 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     // One chunk: decoded and multiplied by x; the wave's next one is fetched meanwhile, its share of X by fetch_x.
     auto chunk = [&](const XPieces<MT, N> &x, auto fetch_x) {
         const Meta m = m_cur;
-        const uint32_t rel = wave_incl_scan(m.lb) - m.lb;
-        const uint32_t start = uniform32((uint32_t)m.b0) & 127u;           // of the chunk's first bit in its image
+        const uint32_t lb = m.lane_bits(lane), rel = wave_incl_scan(lb) - lb;
+        const uint32_t start = (uint32_t)m.begin() & 127u;                 // of the chunk's first bit in its image
 #pragma unroll
         for (int k = 0; k < GSEGS; k++) {
             const uint32_t j = lane16 + 1024 * k;
@@ -881,7 +927,7 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         const GLOBAL uint8_t *pp = (more ? plane_of(nxt) : plane) + lane_plane;
         const uint32_t bpA = stage_off * 8 + start + rel - 1;      // one bit off, see quad_step2
         HeldRuns runs;
-        runs.begin(smem, bpA, bpA + m.lb - 30);
+        runs.begin(smem, bpA, bpA + lb - 30);
         auto &dstA = sums.first(acc);
         auto &dstB = sums.second(acc);
 #pragma unroll
@@ -889,12 +935,13 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             uint32_t dwA[4], dwB[4];
 #pragma unroll
             for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
-            // a piece of the nibble plane is merged, and its registers take the same piece of the next chunk
-            const u32x4 wA = merge_piece(dwA, pl[Q]);
-            pl[Q] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * Q));
+            // two pieces of the nibble plane are merged, and their registers take the same pieces of the next chunk
+            u32x2 pA, pB;
+            deal_plane(pl[Q], pA, pB);
+            pl[Q] = *(const GLOBAL u32x4 *)(pp + 32 * Q);
+            const u32x4 wA = merge_piece(dwA, pA);
             ECF8_MFMA_XPIECE(dstA, x, Q, wA);
-            const u32x4 wB = merge_piece(dwB, pl[Q + GPIECES / 2]);
-            pl[Q + GPIECES / 2] = __builtin_nontemporal_load((const GLOBAL u32x2 *)(pp + 32 * (Q + GPIECES / 2)));
+            const u32x4 wB = merge_piece(dwB, pB);
             ECF8_MFMA_XPIECE(dstB, x, Q + GPIECES / 2, wB);
         }
         sums.end(acc, a, lane);
@@ -1111,7 +1158,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
             else {
                 constexpr bool PINNED = !(MT == 4 && SC == 2);      // M = 64: 297 us, pinned 306
-                const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW>(kchunks, n);
+                const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW, 0>(kchunks, n);
                 if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
                 else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
                 else anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, 0>(it.a, smem, &s_flag, b0, 1, n);
@@ -1213,9 +1260,9 @@ int launch_fused(const GArgs &a, void *stream)
     // at M > 32: beside four tiles of X in registers the scales do not fit (93 us against 83 at M = 64)
     // ... and on the F16 matrix cores at M > 16, where X in registers and the converted operands do not fit together
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
-        const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
+        const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
         if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, 2>), dim3(grid), dim3(16 * 64), 0, s, a);
+        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, ACC == 0 ? 2 : 0>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // X pieces of two chunks: 8 waves' worth of registers
         else {
