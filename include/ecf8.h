@@ -179,9 +179,11 @@ uint64_t ecf8_blob_size(const ecf8_blob *blob);
  * and options (n_threads is ignored).  ecf8_encode_bound gives a capacity that
  * always suffices; ECF8_E_CAPACITY if the blob turns out larger than
  * blob_capacity (at least 256 bytes are needed in any case).  *hdr_out receives
- * the header.  The call synchronises `stream` ONCE (it reads the 16-bin
- * histogram back to build the code on the host), then queues the rest
- * asynchronously.  Uses no memory besides its input and output.
+ * the header.  The call waits for `stream` ONCE (it needs the 16-bin
+ * histogram to build the code on the host), then queues the rest
+ * asynchronously.  Uses no device memory besides its input and output, and a
+ * page of pinned host memory that later calls use again.  A stream that is
+ * being captured -> ECF8_E_HIP.
  */
 int ecf8_encode_bound(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, uint64_t *bytes);
 int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts,

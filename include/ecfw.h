@@ -133,9 +133,11 @@ int ecfw_encode(const void *elems_host, uint64_t rows, uint64_t cols, const ecfw
  * 256-byte aligned, that receives the container -- byte for byte the one ecfw_encode
  * writes for the same input and options (n_threads is ignored).  ecfw_encode_bound
  * gives a capacity that always suffices; ECF8_E_CAPACITY if the blob turns out larger
- * than blob_capacity.  *hdr_out receives the header.  The call synchronises `stream`
- * ONCE (it reads the histogram back to build the code on the host), then queues the
- * rest asynchronously.  Uses no memory besides its input and output.
+ * than blob_capacity.  *hdr_out receives the header.  The call waits for `stream`
+ * ONCE (it needs the histogram to build the code on the host), then queues the rest
+ * asynchronously.  Uses no device memory besides its input and output, and a page of
+ * pinned host memory that later calls use again.  A stream that is being captured ->
+ * ECF8_E_HIP.
  */
 int ecfw_encode_bound(uint64_t rows, uint64_t cols, const ecfw_encode_opts *opts, uint64_t *bytes);
 int ecfw_encode_gpu(const void *d_elems, uint64_t rows, uint64_t cols, const ecfw_encode_opts *opts,

@@ -4,6 +4,10 @@
 
 #include "ecf8_device.h"
 
+#include <chrono>
+#include <mutex>
+#include <vector>
+
 namespace {
 
 // The workgroups' shares of chunk_bit[] are zeroed by the histogram kernels, which run before anything reads them.
@@ -337,12 +341,106 @@ inline TilePlan plan_tiles(uint64_t n_chunks, uint64_t bits, uint32_t cus)
     return p;
 }
 
-// The encoders' one synchronisation: the histogram back to the host, when everything queued on `s` so far is done.  The
-// call returns with the bytes in place; an asynchronous copy to pageable memory waits just as long, and the
-// hipStreamSynchronize it needs for that to be certain adds a second round trip to the device.
-inline bool read_back(void *host, uint64_t device, uint64_t bytes, hipStream_t s)
+// The encoders' one synchronisation: the histogram on its way to the host.  The workgroup of the histogram kernel that adds its counts last
+// writes the sums to a page of pinned host memory and says so there, and the host looks at the page until it does.  A copy behind the
+// kernel and the call that waits for it took longer: 14336 x 4096 E4M3 56.8 us -> 53.0, BF16 89.2 -> 84.3, 256 x 256 34 -> 25.
+constexpr int MAIL_SAID = 256;              // behind the counts
+constexpr uint32_t TICKET_AT = 4;           // byte of the blob: how many workgroups have added their counts, 0 from before the histogram
+
+// By all threads of a workgroup, after their additions to `counters`.  mail: 0, or the page.  Counts, ticket and page are only touched by atomic
+// operations, which no cache answers, and each wave waits for its own to be made; a release of the whole cache in their place costs 25 us.
+template <int A>
+__device__ __forceinline__ void mail_histogram(uint64_t blob, uint64_t counters, uint64_t mail)
 {
-    return hipMemcpyWithStream(host, (const void *)(uintptr_t)device, bytes, hipMemcpyDeviceToHost, s) == hipSuccess;
+    __shared__ uint32_t s_last;
+    if (!mail) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's additions have been made ...
+    __syncthreads();                                        // ... and so have every wave's
+    if (threadIdx.x == 0) s_last = __hip_atomic_fetch_add((GLOBAL uint32_t *)(blob + TICKET_AT), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x < A)
+        __hip_atomic_store((GLOBAL uint64_t *)mail + threadIdx.x, agent_load((GLOBAL uint64_t *)counters + threadIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store((GLOBAL uint64_t *)mail + MAIL_SAID, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A page for one call.  Pages of finished calls are kept for later ones, of any thread, stream and device: KEPT of them per encoder, others are given back.
+class Mail {
+    static constexpr size_t KEPT = 16;
+    static std::mutex &lock() { static std::mutex m; return m; }
+    static std::vector<uint64_t *> &free_pages() { static auto *v = new std::vector<uint64_t *>(); return *v; }    // outlives the runtime
+    uint64_t *page = nullptr;
+    void *seen = nullptr;                   // the page as a kernel sees it
+    bool quiet = true;                      // no kernel may still write to it
+
+public:
+    Mail()
+    {
+        {
+            std::lock_guard<std::mutex> lk(lock());
+            if (!free_pages().empty()) {
+                page = free_pages().back();
+                free_pages().pop_back();
+            }
+        }
+        if (!page && hipHostMalloc((void **)&page, 4096, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            page = nullptr;
+        }
+        if (page && hipHostGetDevicePointer(&seen, page, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(page);
+            page = nullptr;
+        }
+        if (page) __atomic_store_n(page + MAIL_SAID, 0ull, __ATOMIC_RELEASE);
+    }
+    Mail(const Mail &) = delete;
+    Mail &operator=(const Mail &) = delete;
+    ~Mail()
+    {
+        if (!page || !quiet) return;        // after a failed launch or wait: lost rather than written to in another call
+        {
+            std::lock_guard<std::mutex> lk(lock());
+            if (free_pages().size() < KEPT) {
+                if (free_pages().capacity() < KEPT) free_pages().reserve(KEPT);
+                free_pages().push_back(page);
+                return;
+            }
+        }
+        (void)hipHostFree(page);
+    }
+    // for the kernel; 0: there is no page, and the histogram has to be copied
+    uint64_t device()
+    {
+        quiet = !page;
+        return page ? (uint64_t)(uintptr_t)seen : 0;
+    }
+    // The A counts, of the kernel that was given device(); without a page, from `counters`, by a copy that waits for all that is queued on s.
+    bool read(uint64_t *host, int A, uint64_t counters, hipStream_t s)
+    {
+        if (!page) return hipMemcpyWithStream(host, (const void *)(uintptr_t)counters, 8ull * A, hipMemcpyDeviceToHost, s) == hipSuccess;
+        const auto since = std::chrono::steady_clock::now();
+        for (uint32_t i = 1; !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE); i++) {
+            __builtin_ia32_pause();
+            // the stream has more to do, or it has failed
+            if (i % 256 == 0 && std::chrono::steady_clock::now() - since > std::chrono::milliseconds(1)) {
+                if (hipStreamSynchronize(s) != hipSuccess || !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE)) return false;
+                break;
+            }
+        }
+        for (int i = 0; i < A; i++) host[i] = page[i];
+        quiet = true;
+        return true;
+    }
+};
+
+// A stream that is being captured runs nothing: there is no histogram to wait for.
+inline bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
 } // namespace

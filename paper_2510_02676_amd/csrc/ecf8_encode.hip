@@ -3,11 +3,11 @@
 // trip through host memory).  Writes exactly the container the CPU encoder writes, byte for
 // byte: the code and the layout come from the same host routine, fed with the device histogram.
 //
-//   fill 0 (256 bytes) -> histogram (and zeros in chunk_bit[]) -> [host: 128 bytes back, code + layout]
+//   fill 0 (256 bytes) -> histogram (and zeros in chunk_bit[]), written to the host by its last workgroup -> [host: code + layout]
 //   -> everything else in one pass over the weights (encode_tiles): planes, lane_bits, the chunks' bits packed in LDS, their place
 //   in the stream found out between the workgroups, the stream; the workgroups also write pair table and padding, the one that
 //   finds no more work last the header.
-// The input is read twice (histogram, the rest).  No scratch memory: the histogram is counted into the header's freq[] field, tiles are
+// The input is read twice (histogram, the rest).  No scratch memory on the device: the histogram is counted into the header's freq[] field, tiles are
 // drawn from its first dword, and what the workgroups tell one another goes through chunk_bit[], all of them part of the output.
 #include "ecf8_device.h"
 #include "ecf8_enc_device.h"
@@ -48,7 +48,7 @@ __device__ __forceinline__ uint32_t piece_len(uint64_t e, uint64_t n) { return e
 // words, one per exponent bit, and each of the 16 exponents is then one AND and one population count that also adds:
 // two vector operations per element and no LDS.  58.7 M weights: 14.5 us (4 TB/s; counters private to a thread in LDS,
 // one read-modify-write per element, 37 us).  What is left is the read and its latency.
-__global__ __launch_bounds__(1024) void histogram_kernel(uint64_t x_, uint64_t n, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks)
+__global__ __launch_bounds__(1024) void histogram_kernel(uint64_t x_, uint64_t n, uint64_t blob, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks, uint64_t mail)
 {
     __shared__ uint32_t s_cnt[16];
     const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)x_;
@@ -93,6 +93,7 @@ __global__ __launch_bounds__(1024) void histogram_kernel(uint64_t x_, uint64_t n
     }
     __syncthreads();
     if (tid < 16 && s_cnt[tid]) atomicAdd((unsigned long long *)(counters + tid), (unsigned long long)s_cnt[tid]);
+    mail_histogram<16>(blob, counters_, mail);
 }
 
 // Everything of the container that is neither chunk data nor stream, but for the header, by all workgroups: pair table, zeros in the gaps between sections and behind the last dword of the stream.
@@ -285,8 +286,8 @@ struct Chunk {
 
 // The container behind the code.  58.7 M weights (14336 x 4096): 28 us for the 111 MB read and written (30 with two pairs looked up again for every put),
 // 17 of them bound by vector operations, the others the first loads, the exchange and the copy to the stream, when the compute unit waits;
-// metadata and planes, prefix sum and packing as kernels of their own took 40, and read the weights twice.  The whole call 67.7 -> 56.4 us,
-// 16384 x 16384 242 -> 196.
+// metadata and planes, prefix sum and packing as kernels of their own took 40, and read the weights twice.  The whole call 67.7 -> 56.4 us (53.0 since the
+// histogram is mailed), 16384 x 16384 242 -> 190.
 template <int N, bool CAP7>
 __global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, ecf8_header h, uint32_t per_wave)
 {
@@ -359,14 +360,16 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
     if (cus <= 0) return ECF8_E_HIP;
     const uint64_t n_chunks = (n + 64ull * N - 1) / (64ull * N), off_cb = 256 + ((tmode == 1 || (tmode == 0 && n >= (1ull << 22))) ? TBL_ENTRIES * 2 : 0);
     if (blob_capacity < off_cb + 8 * (n_chunks + 1)) return ECF8_E_CAPACITY;        // no blob of this tensor is that small
+    if (capturing(s)) return ECF8_E_HIP;
+    Mail mail;
     hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, blob, (uint64_t)256);
     // one workgroup per compute unit at the most: each ends with 16 atomic additions to one line
     const uint64_t hist_blocks = (n / 4096 + 15) / 16, hist_most = (uint64_t)cus;
     hipLaunchKernelGGL(histogram_kernel, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s, x, n,
-                       blob + 128, blob + off_cb, n_chunks);
+                       blob, blob + 128, blob + off_cb, n_chunks, mail.device());
     if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     uint64_t freq[16];
-    if (!read_back(freq, blob + 128, sizeof(freq), s)) return ECF8_E_HIP;
+    if (!mail.read(freq, 16, blob + 128, s)) return ECF8_E_HIP;
 
     ecf8_internal::Plan plan;
     rc = ecf8_internal::plan_encode(freq, rows, cols, opts, &plan);

@@ -2,9 +2,9 @@
 // for 5- and 8-bit exponent fields.  Writes exactly the container ecfw_encode writes, byte for byte:
 // the code and the layout come from the same host routine, fed with the device histogram.
 //
-//   fill 0 (header, code lengths, freq) -> histogram (and zeros in chunk_bit[]) -> [host: the histogram back, code + layout]
+//   fill 0 (header, code lengths, freq) -> histogram (and zeros in chunk_bit[]), written to the host by its last workgroup -> [host: code + layout]
 //   -> everything else in one pass over the elements, as in the E4M3 encoder (encode_tiles).
-// No scratch memory: the histogram is counted into the freq section, tiles are drawn from the header's first dword, and what the
+// No scratch memory on the device: the histogram is counted into the freq section, tiles are drawn from the header's first dword, and what the
 // workgroups tell one another goes through chunk_bit[], all of them part of the output.
 #include "ecfw.h"
 
@@ -47,7 +47,7 @@ __device__ __forceinline__ ChunkPlace place_of(const WEncArgs &a, uint64_t c, ui
 //  * BF16: LDS counters in 64 copies, lane l of every wave in copy l = bank l, so that the lanes of a wave, most of which
 //    hold one of a handful of exponents, never meet.  58.7 M elements: 21 us, 5.5 TB/s (16 copies: 47 us).
 template <int FMT>
-__global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t n, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks)
+__global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t n, uint64_t blob, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks, uint64_t mail)
 {
     constexpr int A = EFmt<FMT>::A, COPIES = FMT == ECFW_FMT_BF16 ? 64 : 1;
     __shared__ uint32_t s_cnt[A * COPIES];
@@ -122,6 +122,7 @@ __global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t
         sum += __shfl_xor(sum, 2, 64);
         if (part == 0 && sum) atomicAdd((unsigned long long *)(counters + s), (unsigned long long)sum);
     }
+    mail_histogram<A>(blob, counters_, mail);
 }
 
 struct WCodeArgs {
@@ -355,7 +356,7 @@ struct Chunk {
 };
 
 // The container behind the code.  58.7 M elements (14336 x 4096): BF16 39 us for the 198 MB read and written, E5M2 40 for 101 MB (62 and 57 with metadata and
-// planes, prefix sum and packing as kernels of their own).  The whole call 99 -> 79 us and 85 -> 68, 16384 x 16384 460 -> 331 and 252 -> 207.
+// planes, prefix sum and packing as kernels of their own).  The whole call 108 -> 84 us and 85 -> 64, 16384 x 16384 454 -> 310 and 250 -> 204.
 template <int FMT, int N, int LMAX>
 __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeArgs ca, uint32_t per_wave)
 {
@@ -417,13 +418,15 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
     // pass 1: histogram, counted into the blob's freq section
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
+    if (capturing(s)) return ECF8_E_HIP;
+    Mail mail;
     hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, blob, fixed);
     const uint64_t hist_blocks = (n * EFmt<FMT>::ELEM / 4096 + 15) / 16, hist_most = (uint64_t)cus;
     hipLaunchKernelGGL(w_histogram_kernel<FMT>, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s,
-                       x, n, blob + off_freq, blob + fixed, n_chunks);
+                       x, n, blob, blob + off_freq, blob + fixed, n_chunks, mail.device());
     if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
     uint64_t freq[256] = {};
-    if (!read_back(freq, blob + off_freq, 8ull * A, s)) return ECF8_E_HIP;
+    if (!mail.read(freq, A, blob + off_freq, s)) return ECF8_E_HIP;
 
     ecfw_internal::WPlan plan;
     int rc = ecfw_internal::plan_encode(freq, FMT, rows, cols, N, group, lmax, &plan);

@@ -250,3 +250,50 @@ def test_argument_errors():
     assert e.value.code == ecf8.E_ALIGN
     with pytest.raises(ecf8.Ecf8Error):
         ecf8.ecf8_encode_gpu(d_x, 8, 512, lane_syms=64, tile_rows=16)
+
+
+def test_histograms_of_calls_at_the_same_time():
+    """Eight threads, each on a stream of its own with a long copy queued before each call: every call gets its own histogram."""
+    import threading
+    xs = [_rand_bytes(50_000 + 8192 * i, 900 + i) for i in range(8)]
+    wants = [ecf8.ecf8_encode(x, 1, x.size) for x in xs]
+    big = torch.zeros(1 << 28, dtype=torch.uint8, device=DEV)
+    bad = []
+
+    def work(i):
+        s = torch.cuda.Stream()
+        d_x = torch.from_numpy(xs[i]).to(DEV)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            for k in range(12):
+                if k % 4 == i % 4:
+                    y = big.clone()
+                    y.add_(1)
+                hdr, d_blob = ecf8.ecf8_encode_gpu(d_x, 1, xs[i].size)
+                s.synchronize()
+                if bytes(hdr) != bytes(wants[i].header) or not np.array_equal(d_blob.cpu().numpy(), wants[i].numpy()):
+                    bad.append((i, k))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+
+
+def test_refused_while_the_stream_is_captured():
+    x = torch.from_numpy(_rand_bytes(100_000, 5)).to(DEV)
+    out = torch.empty(1 << 18, dtype=torch.uint8, device=DEV)
+    z = torch.zeros(4, device=DEV)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        z.add_(1)
+        with pytest.raises(ecf8.Ecf8Error):
+            ecf8.ecf8_encode_gpu(x, 1, x.numel(), d_blob=out)
+    for k in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((z == k + 1).all())
+    hdr, blob = ecf8.ecf8_encode_gpu(x, 1, x.numel(), d_blob=out)
+    assert np.array_equal(blob.cpu().numpy(), ecf8.ecf8_encode(x.cpu().numpy(), 1, x.numel()).numpy())
