@@ -356,11 +356,7 @@ struct HeldRuns {
 // quad_step2 over held windows, for launches whose pairs always fit the table (PAIRFIT; with a second level in
 // the way the general kernels measured faster on windows fetched per step).  It reads up to 8 bytes past the dwords of a
 // window and 4 before them: the caller's LDS map has something there.
-// PINNED: no LDS access moves across the first lookups, which keeps them in front of the next dwords' fetch; without it the
-// scheduler places that fetch among the products' other work.  Worth 1 .. 4 % to some fused products (14336 x 4096, M = 16: 21.0 -> 20.8 us;
-// 14336 x 11264, M = 64, group scales: 164.8 -> 157.7) and nothing to the decode (a layer 78.1 us, row-tiled 83.8, with and
-// without); where it costs instead, the kernel says so.
-template <bool PINNED = true>
+// No LDS access moves across the first lookups, which keeps them in front of the next dwords' fetch.
 __device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint16_t *tbl, HeldRuns &r, uint32_t &outA, uint32_t &outB)
 {
     constexpr uint32_t OFF_MASK = TBL_MASK << 1;
@@ -369,7 +365,7 @@ __device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint16
     const uint32_t wB = __brev(__builtin_amdgcn_alignbit(r.b1, r.b0, r.pb));
     const uint32_t eA1 = *(const uint16_t *)(tb + (wA & OFF_MASK));
     const uint32_t eB1 = *(const uint16_t *)(tb + (wB & OFF_MASK));
-    if constexpr (PINNED) __builtin_amdgcn_sched_barrier(0x7f);       // anything but LDS accesses may move: the lookups stay in front
+    __builtin_amdgcn_sched_barrier(0x7f);       // anything but LDS accesses may move: the lookups stay in front
     const uint32_t a2 = *(const uint32_t *)(smem + r.A + 8);
     const uint32_t bm = *(const uint32_t *)(smem + r.B);
     const uint32_t nA1 = (eA1 >> 7) & 15u;

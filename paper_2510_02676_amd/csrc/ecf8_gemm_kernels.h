@@ -18,6 +18,8 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int GK = 4096;                        // K
 constexpr int BLOCK_ROWS = 16;
 
+constexpr int X_ROW = 256 + 16;                 // bytes of a row in a turn buffer: padded so that sixteen rows fall into different banks
+
 // N symbols per lane: a chunk is 16 rows x 4N columns; NW waves per workgroup; MT blocks of 16 rows of X
 template <int MT, int NW, int N>
 struct GCfg {
@@ -25,13 +27,10 @@ struct GCfg {
     static constexpr int KCHUNKS = GK / BLOCK_COLS;        // chunks per block of rows
     static constexpr int KPW = KCHUNKS / NW;               // of which each wave takes this many
     static constexpr int PIECES = N / 16;
-    static constexpr int STAGE = 64 * N * (TB / 2) / 8 + 64;   // worst-case span of a chunk under the cap
-    static constexpr int SEGS = (STAGE / 16 + 63) / 64;
-    static_assert(STAGE % 16 == 0, "stage rows are written with 16-byte stores");
+    static_assert(N == 64, "RawRuns, X_ROW");
     static_assert(KPW * NW == KCHUNKS && KPW >= 1, "waves split the chunks of a block evenly");
     static constexpr int OFF_TBL = 0;
-    static constexpr int OFF_STAGE = OFF_TBL + TBL_ENTRIES * 2;
-    static constexpr int OFF_RED = OFF_STAGE + NW * STAGE;
+    static constexpr int OFF_RED = OFF_TBL + TBL_ENTRIES * 2;
     static constexpr int RED_BYTES = NW * MT * 64 * 16;            // one buffer of partial sums: one block of rows, every wave
     // Blocks per barrier.  Up to 16 columns of X with one chunk per wave and block, the workgroup's barrier per block
     // of rows is a fifth of the loop: there the waves park the partial sums of four blocks in a row in LDS and
@@ -39,10 +38,12 @@ struct GCfg {
     static constexpr int BPB = (MT == 1 && KPW == 1) ? 4 : 1;
     static constexpr int RED_BUFS = BPB == 1 ? 2 : BPB;
     static constexpr int TOTAL = OFF_RED + RED_BUFS * RED_BYTES;
-    // The any-K kernels give all that is left of the LDS to slots of 16 x 16 MT partial sums (see anyk_walk).
-    static constexpr uint32_t SLOTS = (160 * 1024 - 64 - OFF_RED) / (MT * 1024);
-    static constexpr int ANYK_TOTAL = OFF_RED + (int)SLOTS * MT * 1024;
-    static_assert(NW * STAGE >= 512, "table-build scratch");
+    // The any-K kernels have a turn buffer per wave (see turn_x) and give all that is left of the LDS to slots of 16 x 16 MT partial
+    // sums (see anyk_walk).
+    static constexpr int OFF_TURN = OFF_RED, ANYK_OFF_RED = OFF_TURN + NW * 16 * X_ROW;
+    static constexpr uint32_t SLOTS = (160 * 1024 - 64 - ANYK_OFF_RED) / (MT * 1024);
+    static constexpr int ANYK_TOTAL = ANYK_OFF_RED + (int)SLOTS * MT * 1024;
+    static_assert(RED_BYTES >= 512, "table-build scratch");
     static_assert(TOTAL <= 160 * 1024 && SLOTS >= NW, "LDS of one gfx950 CU");
 };
 
@@ -61,29 +62,34 @@ struct GArgs {
 
 constexpr int SCALE_BLOCK = 128;                // W carries one fp32 scale per 128 x 128 block
 
-// acc += part * s, element by element, the same operation in the fused and in the raw kernel
-// acc += part * (s * x-scale), element by element, where X carries one scale per row and 128 columns: the
-// scales of block kb for the accumulator rows of this lane (row m = 16 mt + 4 (lane / 16) + r) are
-// fetched one tile of 16 rows at a time.
+typedef float f32x2a __attribute__((ext_vector_type(2), aligned(4)));
+
+// acc += part * (s * x-scale), element by element, where X carries one scale per row and 128 columns, first the forward runs' part
+// with the scale of block kb, then the backward runs' with that of kb + 1.  The scales for the accumulator
+// rows of this lane (row m = 16 mt + 4 (lane / 16) + r) are fetched one tile of 16 rows at a time, the two of a row together.
 template <int MT>
-__device__ __forceinline__ void add_scaled_group(f32x4 (&acc)[MT], const f32x4 (&part)[MT], float s, const GArgs &a,
-                                                 int lane, uint32_t kb)
+__device__ __forceinline__ void add_scaled_groups(f32x4 (&acc)[MT], const f32x4 (&partA)[MT], const f32x4 (&partB)[MT], float sA, float sB,
+                                                  const GArgs &a, int lane, uint32_t kb)
 {
-    const GLOBAL float *xs = (const GLOBAL float *)a.d_xs;
+    const uint32_t row = 4 * (lane >> 4), at = row * a.xs_cols * 4;       // in bytes, below 2^20
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
-        float v[4];
+        f32x2a v[4];
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-            const uint32_t m = 16 * mt + 4 * (lane >> 4) + r;
-            v[r] = m < a.M ? xs[(uint64_t)m * a.xs_cols + kb] : 0.f;
+        for (uint32_t r = 0; r < 4; r++) {
+            const GLOBAL uint8_t *xs = (const GLOBAL uint8_t *)a.d_xs + ((uint64_t)((16 * mt + r) * a.xs_cols) + kb) * 4;
+            v[r] = f32x2a{0.f, 0.f};
+            if (row + 16 * mt + r < a.M) v[r] = *(const GLOBAL f32x2a *)(xs + at);
         }
 #pragma unroll
-        for (int r = 0; r < 4; r++) acc[mt][r] = __builtin_fmaf(part[mt][r], s * v[r], acc[mt][r]);
+        for (int r = 0; r < 4; r++) acc[mt][r] = __builtin_fmaf(partA[mt][r], sA * v[r].x, acc[mt][r]);
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[mt][r] = __builtin_fmaf(partB[mt][r], sB * v[r].y, acc[mt][r]);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
+// acc += part * s, element by element, the same operation in the fused and in the raw kernel
 template <int MT>
 __device__ __forceinline__ void add_scaled(f32x4 (&acc)[MT], const f32x4 (&part)[MT], float s)
 {
@@ -182,8 +188,7 @@ struct ChunkSums {
     __device__ __forceinline__ void end(f32x4 (&acc)[MT], const GArgs &a, int lane)
     {
         if constexpr (XGROUPS) {   // the scales of X are fetched here: held over the decode they would cost it registers
-            add_scaled_group<MT>(acc, partA, sA, a, lane, kbA);
-            add_scaled_group<MT>(acc, partB, sB, a, lane, kbA + 1);
+            add_scaled_groups<MT>(acc, partA, partB, sA, sB, a, lane, kbA);
         } else if constexpr (SCALED) {
             add_scaled<MT>(acc, partA, sA);
             add_scaled<MT>(acc, partB, sB);
@@ -405,20 +410,9 @@ __device__ __forceinline__ void reduce_split(f32x4 *red, uint32_t *s_flag, const
     if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// 16 bytes of the stream; NT: past the caches.  A chunk's bytes are used once, but the lines at its ends belong to two chunks, and which way pays is a matter of
-// measurement: nontemporal / cached, us: M <= 16 with X in registers 14336 x 4096 19.1 / 19.3, eight experts 86.2 / 87.1; without 4096 x 14336 18.1 / 17.5;
-// more tiles of X 14336 x 4096, M = 64 30.6 / 29.3, 14336 x 7168, M = 32 43.7 / 41.8, M = 64 with group scales 90.3 / 86.8.
-template <bool NT>
-__device__ __forceinline__ u32x4 load_unit(const GLOBAL uint8_t *p)
-{
-    if constexpr (NT) return __builtin_nontemporal_load((const GLOBAL u32x4 *)p);
-    else return *(const GLOBAL u32x4 *)p;
-}
-
 // What of a chunk is needed before its bits: where it starts and ends in the stream and the bits of this lane.
 // ONE: fetched in one instruction of four bytes a lane, lanes 0 .. 31 the lanes' bits, two each, lanes 32 .. 35 the two positions (the others those
-// again); as two they are loads of 2 and 16 bytes a lane, the latter the same for all.  14336 x 7168, M = 32, scales of W: 46.5 us -> 44.2, 4096 x 14336,
-// M = 16: 19.4 -> 18.7; with four tiles of X and group scales, which crowd the registers, 94.9 -> 101.5, so not there.
+// again); as two they are loads of 2 and 16 bytes a lane, the latter the same for all.
 template <bool ONE>
 struct ChunkMeta {
     uint64_t b0 = 0, b1 = 0;
@@ -459,6 +453,77 @@ struct MetaReader {
     }
 };
 
+// A lane's codewords of a chunk straight from memory to registers: the 8 dwords that hold its forward run from the first bit on and the 8 that hold its
+// backward run from the last bit down.  32 codewords of at most 7 bits are 224 bits; with them come the bit next to the first one, which makes a
+// masked window the byte offset of a table entry (see quad_step2), and up to 31 bits of its dword.  Positions are counted
+// in bits from 16 bytes before the chunk's span.
+// The chunk's span staged in LDS and the runs' windows read from there took a third of the LDS's time, which was busy for 61 % (14336 x 4096,
+// M = 16) and 76 % (eight experts, M = 4) of the launch, and a quarter of the vector operations.  Now the gathers are 256 accesses to the
+// first-level cache a chunk, which has the time.  us: 14336 x 4096, M = 1 / 16 / 32 / 64 17.8 / 19.1 / 22.1 / 29.2 -> 15.2 / 15.5 / 18.9 / 24.6, 14336 x 7168,
+// M = 16 31.1 -> 25.1, six experts, scales of W, M = 4 67.7 -> 55.3, eight 86.6 -> 75.8.  Cached: the lines are a lane's neighbours' too.
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
+struct RawRuns {
+    u32x4 a0, a1, b0, b1;
+    uint32_t pa, pb;            // the bit before the forward run's first; the one behind the backward run's first
+
+    // Positions beyond the stream (damaged metadata) read its end; what is read around it, 32 bytes at the most, belongs to the blob.
+    template <bool ONE>
+    __device__ __forceinline__ void fetch(const GLOBAL uint8_t *stream, uint64_t st_bytes, const ChunkMeta<ONE> &m, int lane)
+    {
+        const uint64_t begin = m.begin();
+        uint64_t byte0 = (begin >> 3) & ~15ull;
+        if (byte0 > st_bytes) byte0 = st_bytes;
+        const uint64_t room = st_bytes - byte0 + 16;
+        const uint32_t most = room < (1u << 28) ? (uint32_t)room : 1u << 28;
+        const uint32_t lb = m.lane_bits(lane), end = wave_incl_scan(lb) + ((uint32_t)begin & 127u);
+        pa = end - lb + 127;
+        pb = end + 128;
+        uint32_t atA = (pa >> 3) & ~3u, atB = (pb >> 3) & ~3u;
+        atA = atA < most ? atA : most;
+        atB = atB < most ? atB : most;
+        const GLOBAL uint8_t *base = stream + byte0 - 16;
+        a0 = *(const GLOBAL u32x4a *)(base + atA);
+        a1 = *(const GLOBAL u32x4a *)(base + atA + 16);
+        b0 = *(const GLOBAL u32x4a *)(base - 28 + atB);
+        b1 = *(const GLOBAL u32x4a *)(base - 12 + atB);
+    }
+};
+
+// The two runs as strings of bits in reading order, the next bit at bit 1 of the first dword.  A step takes four codewords, 28 bits at most, off
+// either and shifts what may still be needed: seven dwords after the first step, one less after each.
+struct ShiftedRuns {
+    uint32_t a[8], b[8];
+
+    __device__ __forceinline__ void begin(const RawRuns &r)
+    {
+        const uint32_t x[8] = {r.a0.x, r.a0.y, r.a0.z, r.a0.w, r.a1.x, r.a1.y, r.a1.z, r.a1.w};
+        const uint32_t y[8] = {__brev(r.b1.w), __brev(r.b1.z), __brev(r.b1.y), __brev(r.b1.x), __brev(r.b0.w), __brev(r.b0.z), __brev(r.b0.y), __brev(r.b0.x)};
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            a[i] = __builtin_amdgcn_alignbit(i < 7 ? x[i + 1] : 0u, x[i], r.pa);
+            b[i] = __builtin_amdgcn_alignbit(i < 7 ? y[i + 1] : 0u, y[i], ~r.pb);
+        }
+    }
+    // step t = 0 .. 7: the exponent fields of four elements of each run
+    __device__ __forceinline__ void step(const uint16_t *tbl, int t, uint32_t &outA, uint32_t &outB)
+    {
+        constexpr uint32_t OFF_MASK = TBL_MASK << 1;
+        const uint8_t *tb = (const uint8_t *)tbl;
+        const uint32_t eA1 = *(const uint16_t *)(tb + (a[0] & OFF_MASK)), eB1 = *(const uint16_t *)(tb + (b[0] & OFF_MASK));
+        const uint32_t nA1 = (eA1 >> 7) & 15u, nB1 = (eB1 >> 7) & 15u;
+        const uint32_t eA2 = *(const uint16_t *)(tb + ((a[0] >> nA1) & OFF_MASK)), eB2 = *(const uint16_t *)(tb + ((b[0] >> nB1) & OFF_MASK));
+        const uint32_t nA = nA1 + ((eA2 >> 7) & 15u), nB = nB1 + ((eB2 >> 7) & 15u);
+#pragma unroll
+        for (int i = 0; i < 7; i++)
+            if (i < 7 - t) {                                // 28 (7 - t) + 1 bits are left at most
+                a[i] = __builtin_amdgcn_alignbit(a[i + 1], a[i], nA);
+                b[i] = __builtin_amdgcn_alignbit(b[i + 1], b[i], nB);
+            }
+        outA = __builtin_amdgcn_perm(eA2, eA1, 0x05040100u);
+        outB = __builtin_amdgcn_perm(eB2, eB1, 0x05040100u);
+    }
+};
+
 template <int MT, int NW, int N, int SC, int ACC = 0>       // SC: 0 no scales, 1 scales of W (and one per row of X), 2 also one per row and 128 columns of X; ACC: see ECF8_MFMA_OPERANDS
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
 {
@@ -466,17 +531,15 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
     using C = GCfg<MT, NW, N>;
     constexpr int KPW = C::KPW, KCHUNKS = C::KCHUNKS, BLOCK_COLS = C::BLOCK_COLS;
-    constexpr int GPIECES = C::PIECES, GSTAGE = C::STAGE, GSEGS = C::SEGS;
+    constexpr int GPIECES = C::PIECES;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
-    uint8_t *stage = smem + stage_off;
 
     const GLOBAL uint8_t *stream = (const GLOBAL uint8_t *)(a.d_blob + a.off_st);
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
 
-    constexpr bool META1 = false;
+    constexpr bool META1 = MT == 4;            // M = 64 25.0 us, 24.6 with it, scales of W 28.6, 26.6; M = 16 15.5, 15.8
     using Meta = ChunkMeta<META1>;
     const MetaReader<META1> meta(a, lane);
     const uint64_t n_blocks = a.rows / BLOCK_ROWS;
@@ -485,23 +548,6 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     auto block_of = [&](uint64_t s) -> uint64_t { return blockIdx.x + (s / KPW) * (uint64_t)gridDim.x; };
     auto kc_of = [&](uint64_t s) -> uint32_t { return wave_s + NW * (uint32_t)(s % KPW); };
     auto load_meta = [&](uint64_t s) { return meta(block_of(s) * KCHUNKS + kc_of(s)); };
-    // A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead), from the chunk's two start
-    // bits: values every lane holds alike, so the arithmetic is done once, in scalar registers.
-    // The span's 16-byte units into `seg` (unit lane + 64 k into seg[k]); units beyond the span keep what they
-    // held: the lanes' codewords never reach into them.
-    const uint32_t lane16 = (uint32_t)lane * 16;
-    auto load_stream = [&](const Meta &m, u32x4 (&seg)[GSEGS], bool wanted = true) {
-        uint64_t byte_end = ((m.end() + 7) >> 3) + 8, byte0 = (m.begin() >> 3) & ~15ull;
-        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
-        if (byte0 > byte_end) byte0 = byte_end;
-        const uint32_t span = wanted ? (uint32_t)(byte_end - byte0) : 0u;       // at most GSTAGE under the cap on codewords
-        const GLOBAL uint8_t *sp = stream + byte0;
-#pragma unroll
-        for (int k = 0; k < GSEGS; k++) {
-            const uint32_t i = lane16 + 1024 * k;
-            if (i < (uint32_t)GSTAGE && i < span) seg[k] = load_unit<MT == 1>(sp + i);
-        }
-    };
     // nibble plane of step s: this lane's part of pieces q and q + 2 at plane_of(s) + lane_plane + 32 q, see deal_plane
     const uint32_t lane_plane = (uint32_t)(lane & 15) * (GK / 2) + plane_lane(lane);
     auto plane_of = [&](uint64_t s) -> const GLOBAL uint8_t * {
@@ -511,44 +557,33 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     // start-up: the first chunks' loads and those of X are in flight while the table is set up
     const uint64_t n_steps = blockIdx.x < n_blocks ? ((n_blocks - blockIdx.x + gridDim.x - 1) / gridDim.x) * KPW : 0;
     Meta m_cur, m_next;
-    u32x4 seg[GSEGS];
+    RawRuns raw = {};
     static_assert(GPIECES == 4, "deal_plane");
     u32x4 pl[2];
 #pragma unroll
-    for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
-#pragma unroll
     for (int q = 0; q < 2; q++) pl[q] = u32x4{0, 0, 0, 0};
     // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
-    // table first, since it is what the workgroup meets for (M = 16: 21.0 -> 20.7 us; M = 32 25.5 -> 25.2, M = 64 with scales of W
-    // 34.4 -> 34.2).  Not with four tiles of X and no scales, where the metadata come first (30.0 us; in this order 30.7).
-    constexpr bool EARLY = !(MT == 4 && SC == 0);
-    // lookups in front of the fetch behind them (quad_step_held): M = 16 20.7 against 21.0 us, but two tiles of X with scales of W
-    // 29.1 against 26.7
-    constexpr bool PINNED = !(MT == 2 && SC == 1);
+    // table first, since it is what the workgroup meets for.
     u32x4 tv[TABLE_UNITS<NW>];
-    if constexpr (EARLY) load_table<NW>(a, tid, tv);
+    load_table<NW>(a, tid, tv);
     if (n_steps > 0) {
         m_cur = load_meta(0);
         m_next = load_meta(n_steps > 1 ? 1 : 0);
-        if constexpr (!EARLY) load_stream(m_cur, seg);
         const GLOBAL uint8_t *pp = plane_of(0);
 #pragma unroll
         for (int q = 0; q < 2; q++) pl[q] = *(const GLOBAL u32x4 *)(pp + lane_plane + 32 * q);
     }
     u32x4 areg[MT][KPW][GPIECES];
     load_x_slice<MT, NW, N>(a, tid, areg);
-    if constexpr (EARLY) {
-        if (n_steps > 0) load_stream(m_cur, seg);
-    }
+    if (n_steps > 0) raw.fetch(stream, a.st_bytes, m_cur, lane);
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
     __builtin_memcpy(&len_hi, a.code_len + 8, 8);
     if (a.off_tbl) {
-        if constexpr (!EARLY) load_table<NW>(a, tid, tv);
         store_table<NW>(tbl, tid, tv);
     } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, (int)uniform32((uint32_t)wave));
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_RED), lane, (int)uniform32((uint32_t)wave));
     }
 
     uint32_t parity = 0;
@@ -559,25 +594,16 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
 #pragma unroll
         for (int i = 0; i < KPW; i++) {
             const uint64_t s = s0 + i;
-            const Meta m = m_cur;
-            const uint32_t lb = m.lane_bits(lane), rel = wave_incl_scan(lb) - lb;
-            const uint32_t start = (uint32_t)m.begin() & 127u;     // of the chunk's first bit in its image
-#pragma unroll
-            for (int k = 0; k < GSEGS; k++) {
-                const uint32_t j = lane16 + 1024 * k;
-                if (j < (uint32_t)GSTAGE) *(u32x4 *)(stage + j) = seg[k];
-            }
-            // The stream registers are free: fetch the next chunk's span, and the metadata of the chunk after it.
-            // The last steps have nothing to fetch and no branch around the loads either: the metadata of the last
-            // chunk again (12 bytes), a span of no bytes, and the plane's first chunk, which every wave then asks for.
+            ShiftedRuns runs;
+            runs.begin(raw);
+            // The raw registers are free: fetch the next chunk's runs, and the metadata of the chunk after it.
+            // The last steps have nothing to fetch and no branch around the loads either: the last chunk's metadata and runs
+            // again, and the plane's first chunk, which every wave then asks for.
             const bool more = s + 1 < n_steps;                 // the same for every lane
             const uint64_t sn = more ? s + 1 : s, sn2 = s + 2 < n_steps ? s + 2 : sn;
-            load_stream(m_next, seg, more);
+            raw.fetch(stream, a.st_bytes, m_next, lane);
             const Meta m_next2 = load_meta(sn2);
             const GLOBAL uint8_t *pp = more ? plane_of(sn) : plane;
-            const uint32_t bpA = stage_off * 8 + start + rel - 1;   // one bit off, see quad_step2
-            HeldRuns runs;
-            runs.begin(smem, bpA, bpA + lb - 30);
             ChunkSums<MT, SC> sums;
             sums.begin(a, block_of(s), kc_of(s));
             auto &dstA = sums.first(acc);
@@ -586,7 +612,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
             for (int Q = 0; Q < GPIECES / 2; Q++) {
                 uint32_t dwA[4], dwB[4];
 #pragma unroll
-                for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
+                for (int t = 0; t < 4; t++) runs.step(tbl, 4 * Q + t, dwA[t], dwB[t]);
                 // two pieces of the nibble plane are merged, and their registers take the same pieces of the next chunk
                 u32x2 pA, pB;
                 deal_plane(pl[Q], pA, pB);
@@ -597,7 +623,6 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
                 ECF8_MFMA_PIECE(dstB, areg, i, Q + GPIECES / 2, wB);
             }
             sums.end(acc, a, lane);
-            m_cur = m_next;
             m_next = m_next2;
         }
         if constexpr (C::BPB == 1) {
@@ -698,26 +723,40 @@ template <int NW>
 __device__ __noinline__ void build_pair_table_apart(uint64_t len_lo, uint64_t len_hi, uint8_t *smem, int lane, int wave)
 {
     using C = GCfg<1, NW, 64>;
-    build_pair_table<NW>(len_lo, len_hi, (uint16_t *)(smem + C::OFF_TBL), (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
+    build_pair_table<NW>(len_lo, len_hi, (uint16_t *)(smem + C::OFF_TBL), (uint32_t *)(smem + C::OFF_RED), lane, wave);
 }
 
 template <int MT, int N>
 struct XPieces { u32x4 v[MT][N / 16]; };
 
-// A operands for chunk kc: X[m][256 kc + 64 q + 16 g .. + 16) of lane (m = l % 16 (+ 16 mt), g = l / 16)
-template <int MT, int N>
-__device__ __forceinline__ void load_x_chunk(const GArgs &a, int lane, uint32_t kc, XPieces<MT, N> &x)
+// A operands for chunk kc: v[mt][q] = X[m][256 kc + 64 q + 16 g .. + 16) of lane (m = l % 16 (+ 16 mt), g = l / 16).
+// Kernels that fetch X for every chunk fetch it as rows as they lie in memory, 16 lanes to a row (slot j of lane l: bytes 16 (l % 16) .. of row
+// 4 j + l / 16 of each tile), and turn it into operands in LDS.  Fetched as operands, where adjacent lanes have different rows,
+// every lane is an access to the first-level cache of its own, 64 for an instruction in place of 16, and those accesses bounded
+// these kernels: 14336 x 7168, M = 64, 1400 of them a chunk, nine tenths of the time; 70.3 us -> 47.8, 16384 x 16384 145 -> 97.
+// (The nibble plane fetched and turned in the same way: M = 1, 14336 x 7168 21.7 -> 24.4, the exchange of deal_plane is cheaper.)
+// TURNED = false: slot j as the operand it is.  Rows from M on keep what they had: no output that is stored depends on them.
+template <int MT, int N, bool TURNED>
+__device__ __forceinline__ void load_x_slot(const GArgs &a, int lane, uint32_t kc, int j, XPieces<MT, N> &x)
 {
-    const GLOBAL uint8_t *X = (const GLOBAL uint8_t *)a.d_x;
-    const int n = lane & 15, g = lane >> 4;
+    const uint32_t K = (uint32_t)a.K, row = TURNED ? lane >> 4 : lane & 15, at = row * K + (TURNED ? 16 * (lane & 15) : 16 * (lane >> 4));      // 64 K <= 2^26
 #pragma unroll
-    for (int mt = 0; mt < MT; mt++)
+    for (int mt = 0; mt < MT; mt++) {
+        const uint32_t first = 16 * mt + (TURNED ? 4 * j : 0);      // row of X, of the instruction's lowest one
+        const GLOBAL uint8_t *X = (const GLOBAL uint8_t *)a.d_x + (uint64_t)(first * K) + (uint64_t)kc * (4 * N) + (TURNED ? 0 : 64 * j);
+        if (first + row < a.M) x.v[mt][j] = *(const GLOBAL u32x4 *)(X + at);
+    }
+}
+template <int MT, int N>
+__device__ __forceinline__ void turn_x(uint8_t *turn, int lane, XPieces<MT, N> &x)
+{
 #pragma unroll
-        for (int q = 0; q < N / 16; q++) {
-            const uint32_t m = 16 * mt + n;
-            x.v[mt][q] = u32x4{0, 0, 0, 0};
-            if (m < a.M) x.v[mt][q] = *(const GLOBAL u32x4 *)(X + (uint64_t)m * a.K + (uint64_t)kc * (4 * N) + 64 * q + 16 * g);
-        }
+    for (int mt = 0; mt < MT; mt++) {
+#pragma unroll
+        for (int j = 0; j < N / 16; j++) *(u32x4 *)(turn + (4 * j + (lane >> 4)) * X_ROW + 16 * (lane & 15)) = x.v[mt][j];
+#pragma unroll
+        for (int q = 0; q < N / 16; q++) x.v[mt][q] = *(const u32x4 *)(turn + (lane & 15) * X_ROW + 64 * q + 16 * (lane >> 4));
+    }
 }
 
 #define ECF8_MFMA_XPIECE(acc, xp, p, W_PIECE) ECF8_MFMA_OPERANDS(acc, xp.v[mt_][p], W_PIECE)
@@ -749,25 +788,23 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 //    eighth), which costs little beside the others' work.
 //  * KRES = 0: the units' chunks form one sequence, and wave w takes every NW-th of it from the w-th on, across the units'
 //    borders; batches are rounded down to whole rounds of the waves.
-// What bounds it: the requests for the blob's bytes, the look-ups and the vector operations about equally (eight experts, M = 4, 97 us when
-// this was asked: without nibble loads 87, without stream loads 87, without look-ups 92).  Eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales
-// of W, M = 4 / 16 / 64: block by block with a barrier each and X fetched for every chunk 106 / 126 / 294 us, in one sequence 106 / 127 / 269, with X
-// resident 97 / 103 / 269; with the fewer and wider loads of deal_plane and ChunkMeta 86 / 89 / 235.
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, bool PINNED, int KRES>
+// What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.8 us), the blobs' bytes at 4.2 TB/s, with LDS and vector
+// operations busy for 60 to 70 %; six of them, which the memory-side cache holds, 55.3.  M = 64 (215 us): two waves on a
+// SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and first-level cache busy 55 % each).
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
                                           uint32_t my_units)
 {
     constexpr bool SCALED = SC != 0;
     using C = GCfg<MT, NW, N>;
-    constexpr int BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES, GSTAGE = C::STAGE, GSEGS = C::SEGS;
+    constexpr int BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
     static_assert((NW & (NW - 1)) == 0, "places in the deal are chunk numbers modulo NW");
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
-    f32x4 *red = (f32x4 *)(smem + C::OFF_RED);
+    f32x4 *red = (f32x4 *)(smem + C::ANYK_OFF_RED);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = (int)uniform32((uint32_t)tid >> 6);           // the same for every lane: what follows from it stays in scalar registers
-    const uint32_t stage_off = C::OFF_STAGE + wave * GSTAGE;
-    uint8_t *stage = smem + stage_off;
+    uint8_t *turn = smem + C::OFF_TURN + wave * (16 * X_ROW);
 
     const GLOBAL uint8_t *stream = (const GLOBAL uint8_t *)(a.d_blob + a.off_st);
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
@@ -777,9 +814,8 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     const uint32_t k0 = SPLIT ? (uint32_t)first_unit % a.slices * unit_chunks : 0u;
     const uint32_t block0 = SPLIT ? (uint32_t)first_unit / a.slices : (uint32_t)first_unit;
 
-    constexpr bool META1 = !(MT == 4 && SC == 2);
-    using Meta = ChunkMeta<META1>;
-    const MetaReader<META1> meta(a, lane);
+    using Meta = ChunkMeta<true>;
+    const MetaReader<true> meta(a, lane);
     // NW chunks on: over at most this many units and so many chunks more
     const uint32_t hop = (uint32_t)NW / unit_chunks, hop_kc = (uint32_t)NW % unit_chunks;
     const uint32_t skip = (unit_stride - 1) * unit_chunks;         // the other workgroups' chunks between one unit and the next
@@ -820,45 +856,28 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     };
     auto valid = [&](const Place &w) { return w.b < my_units; };
     auto load_meta = [&](const Place &w) { return meta(w.c); };
-    // A chunk's span of the stream (16-byte aligned start, 8 bytes of look-ahead), from the chunk's two start
-    // bits: values every lane holds alike, so the arithmetic is done once, in scalar registers.
-    // The span's 16-byte units into `seg` (unit lane + 64 k into seg[k]); units beyond the span keep what they
-    // held: the lanes' codewords never reach into them.
-    const uint32_t lane16 = (uint32_t)lane * 16;
-    auto load_stream = [&](const Meta &m, u32x4 (&seg)[GSEGS], bool wanted = true) {
-        uint64_t byte_end = ((m.end() + 7) >> 3) + 8, byte0 = (m.begin() >> 3) & ~15ull;
-        if (byte_end > a.st_bytes) byte_end = a.st_bytes;
-        if (byte0 > byte_end) byte0 = byte_end;
-        const uint32_t span = wanted ? (uint32_t)(byte_end - byte0) : 0u;      // at most GSTAGE under the cap on codewords
-        const GLOBAL uint8_t *sp = stream + byte0;
-#pragma unroll
-        for (int k = 0; k < GSEGS; k++) {
-            const uint32_t i = lane16 + 1024 * k;
-            if (i < (uint32_t)GSTAGE && i < span) seg[k] = load_unit<MT == 1 && KRES != 0>(sp + i);
-        }
-    };
     // nibble plane of a chunk: this lane's part of pieces q and q + 2 at plane_of(w) + lane_plane + 32 q, see deal_plane.  Block and column of chunk c begin at
     // element 256 * (16 * block * kchunks + k), k = c - block * kchunks.
-    const uint64_t lane_plane = (uint64_t)(lane & 15) * (a.K / 2) + plane_lane(lane);
+    const uint32_t lane_plane = (uint32_t)(lane & 15) * (uint32_t)(a.K / 2) + plane_lane(lane);
     auto plane_of = [&](const Place &w) -> const GLOBAL uint8_t * {
         return plane + ((uint64_t)(16 * w.c - 15 * (k0 + w.kc)) << 7);
     };
 
+    auto load_x = [&](uint32_t kc, XPieces<MT, N> &x) {
+#pragma unroll
+        for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, TURNED>(a, lane, kc, j, x);
+    };
     Place cur = first_place();
     Meta m_cur, m_next;
-    u32x4 seg[GSEGS];
+    RawRuns raw = {};
     static_assert(GPIECES == 4, "deal_plane");
     u32x4 pl[2];
 #pragma unroll
-    for (int k = 0; k < GSEGS; k++) seg[k] = u32x4{0, 0, 0, 0};
-#pragma unroll
     for (int q = 0; q < 2; q++) pl[q] = u32x4{0, 0, 0, 0};
-    XPieces<MT, N> x_cur[KRES > 1 ? KRES : 1];
-    // The order of ecf8_gemm_kernel, but not in groups with two tiles of X and scales of W or with two or four and no scales.
-    // Metadata first / this order, us: six experts, M = 20 and scales of W 117.7 / 123.4, no scales 112.0 / 114.0; M = 32 and no scales
-    // 124.8 / 131.7, M = 48 163.3 / 169.3.  Elsewhere this order: M = 48 and scales of W 188.7 / 181.7, M = 32 and scales of W and X 159.9 / 153.0,
-    // M = 4 84.0 / 83.3; 512 x 7168 split in K, M = 16 and all scales 14.1 / 14.0.
-    constexpr bool EARLY = !(APART && ((MT == 2 && SC == 1) || (MT > 1 && SC == 0)));
+    XPieces<MT, N> x_cur[KRES > 1 ? KRES : 1] = {};
+    // The order of ecf8_gemm_kernel, but not in groups with two tiles of X or four and no scales.  Metadata first / this order, us: six
+    // experts M = 20 81.8 / 82.9, 48 121 / 124, eight experts M = 64 192 / 200; with scales of W no difference.
+    constexpr bool EARLY = !(APART && MT > 1 && SC == 0);
     u32x4 tv[TABLE_UNITS<NW>];
     if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (valid(cur)) {
@@ -866,16 +885,16 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         m_next = m_cur;
         const Place nxt = next_of(cur);
         if (valid(nxt)) m_next = load_meta(nxt);
-        if constexpr (!EARLY) load_stream(m_cur, seg);
-        const GLOBAL uint8_t *pp = plane_of(cur) + lane_plane;
+        if constexpr (!EARLY) raw.fetch(stream, a.st_bytes, m_cur, lane);
+        const GLOBAL uint8_t *pp = plane_of(cur);
 #pragma unroll
-        for (int q = 0; q < 2; q++) pl[q] = *(const GLOBAL u32x4 *)(pp + 32 * q);
-        load_x_chunk<MT, N>(a, lane, k0 + cur.kc, x_cur[0]);
+        for (int q = 0; q < 2; q++) pl[q] = *(const GLOBAL u32x4 *)(pp + 32 * q + lane_plane);
+        load_x(k0 + cur.kc, x_cur[0]);
     }
     if constexpr (EARLY) {
-        if (valid(cur)) load_stream(m_cur, seg);
+        if (valid(cur)) raw.fetch(stream, a.st_bytes, m_cur, lane);
     }
-    if constexpr (KRES > 1) load_x_chunk<MT, N>(a, lane, two ? kw + NW : kw, x_cur[1]);
+    if constexpr (KRES > 1) load_x(two ? kw + NW : kw, x_cur[1]);
 
     uint64_t len_lo, len_hi;
     __builtin_memcpy(&len_lo, a.code_len, 8);
@@ -886,7 +905,7 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     } else if constexpr (APART) {
         build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
     } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_STAGE), lane, wave);
+        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_RED), lane, wave);
     }
 
     // slots of a block, blocks of a batch: whole rounds of the waves where there are slots for NW / gcd(NW, chunks) blocks
@@ -900,52 +919,46 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    // One chunk: decoded and multiplied by x; the wave's next one is fetched meanwhile, its share of X by fetch_x.
-    auto chunk = [&](const XPieces<MT, N> &x, auto fetch_x) {
-        const Meta m = m_cur;
-        const uint32_t lb = m.lane_bits(lane), rel = wave_incl_scan(lb) - lb;
-        const uint32_t start = (uint32_t)m.begin() & 127u;                 // of the chunk's first bit in its image
-#pragma unroll
-        for (int k = 0; k < GSEGS; k++) {
-            const uint32_t j = lane16 + 1024 * k;
-            if (j < (uint32_t)GSTAGE) *(u32x4 *)(stage + j) = seg[k];
-        }
+    // One chunk: decoded and multiplied by x; the wave's next one is fetched meanwhile.  KRES = 0: x are its rows, turned just before the first
+    // product, and its registers take the next chunk's rows as they are used up.
+    auto chunk = [&](XPieces<MT, N> &x) {
+        ShiftedRuns runs;
+        runs.begin(raw);
         ChunkSums<MT, SC> sums;
         sums.begin(a, cur.block, k0 + cur.kc);
-        // The stream registers are free: fetch the next chunk's span and its share of X, and the metadata of the
-        // chunk after it.
+        // The raw registers are free: fetch the next chunk's runs, and the metadata of the chunk after it.
         const Place nxt = next_of(cur);
         const bool more = valid(nxt);
         Meta m_next2 = m_next;
         if (more) {
-            load_stream(m_next, seg);
-            fetch_x(nxt);
+            raw.fetch(stream, a.st_bytes, m_next, lane);
             const Place nxt2 = next_of(nxt);
             if (valid(nxt2)) m_next2 = load_meta(nxt2);
         }
         // after the last chunk the plane pieces are fetched from the plane's first chunk (every wave's last fetch: cached)
-        const GLOBAL uint8_t *pp = (more ? plane_of(nxt) : plane) + lane_plane;
-        const uint32_t bpA = stage_off * 8 + start + rel - 1;      // one bit off, see quad_step2
-        HeldRuns runs;
-        runs.begin(smem, bpA, bpA + lb - 30);
+        const GLOBAL uint8_t *pp = more ? plane_of(nxt) : plane;
         auto &dstA = sums.first(acc);
         auto &dstB = sums.second(acc);
 #pragma unroll
         for (int Q = 0; Q < GPIECES / 2; Q++) {
             uint32_t dwA[4], dwB[4];
 #pragma unroll
-            for (int t = 0; t < 4; t++) quad_step_held<PINNED>(smem, tbl, runs, dwA[t], dwB[t]);
+            for (int t = 0; t < 4; t++) runs.step(tbl, 4 * Q + t, dwA[t], dwB[t]);
             // two pieces of the nibble plane are merged, and their registers take the same pieces of the next chunk
             u32x2 pA, pB;
             deal_plane(pl[Q], pA, pB);
-            pl[Q] = *(const GLOBAL u32x4 *)(pp + 32 * Q);
+            pl[Q] = *(const GLOBAL u32x4 *)(pp + 32 * Q + lane_plane);
+            if (TURNED && Q == 0) turn_x<MT, N>(turn, lane, x);
             const u32x4 wA = merge_piece(dwA, pA);
             ECF8_MFMA_XPIECE(dstA, x, Q, wA);
             const u32x4 wB = merge_piece(dwB, pB);
             ECF8_MFMA_XPIECE(dstB, x, Q + GPIECES / 2, wB);
+            if (KRES == 0 && more) {
+                load_x_slot<MT, N, TURNED>(a, lane, k0 + nxt.kc, Q, x);
+                load_x_slot<MT, N, TURNED>(a, lane, k0 + nxt.kc, Q + GPIECES / 2, x);
+            }
         }
         sums.end(acc, a, lane);
-        m_cur = m_next;
         m_next = m_next2;
         return nxt;
     };
@@ -961,15 +974,14 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             while (cur.b < b1) {
                 const uint32_t j = cur.b - b0, place = cur.kc;
                 clear();
-                cur = chunk(x_cur[0], [](const Place &) {});
-                if (KRES > 1 && two) cur = chunk(x_cur[KRES - 1], [](const Place &) {});
+                cur = chunk(x_cur[0]);
+                if (KRES > 1 && two) cur = chunk(x_cur[KRES - 1]);
                 park(j, place);
             }
         } else {
 #pragma unroll 1
             while (cur.b < b1) {
-                const XPieces<MT, N> x = x_cur[0];
-                const Place nxt = chunk(x, [&](const Place &w) { load_x_chunk<MT, N>(a, lane, k0 + w.kc, x_cur[0]); });
+                const Place nxt = chunk(x_cur[0]);
                 if (!SPLIT && nxt.b != cur.b) {
                     park(cur.b - b0, cur.kc & (NW - 1));
                     clear();
@@ -993,12 +1005,12 @@ __device__ __forceinline__ uint64_t units_of_workgroup(uint64_t n_units)
     return blockIdx.x < n_units ? (n_units - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
 }
 
-template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, bool PINNED = true, int KRES = 0>
+template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, int KRES = 0, bool TURNED = KRES == 0>
 __global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::ANYK_TOTAL];
     __shared__ uint32_t s_flag;                   // split K: the arrival count this workgroup drew
-    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, PINNED, KRES>(a, smem, &s_flag, blockIdx.x, gridDim.x,
+    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, KRES, TURNED>(a, smem, &s_flag, blockIdx.x, gridDim.x,
                                                               (uint32_t)units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)));
 }
 
@@ -1047,10 +1059,11 @@ __device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uin
     };
     Walk cur = at_unit(0);
     u32x4 w_cur[GPIECES], w_next[GPIECES];
-    XPieces<MT, N> x_cur;
+    XPieces<MT, N> x_cur = {};
     if (valid(cur)) {
         load_w(cur, w_cur);
-        load_x_chunk<MT, N>(a, lane, kc_of(cur), x_cur);
+#pragma unroll
+        for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, false>(a, lane, kc_of(cur), j, x_cur);
     }
     for (uint64_t b = 0; b < my_blocks; b++) {
         f32x4 acc[MT];
@@ -1067,7 +1080,8 @@ __device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uin
             for (int q = 0; q < GPIECES; q++) w_next[q] = w_cur[q];
             if (valid(nxt)) {
                 load_w(nxt, w_next);
-                load_x_chunk<MT, N>(a, lane, kc_of(nxt), x_cur);
+#pragma unroll
+                for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, false>(a, lane, kc_of(nxt), j, x_cur);
             }
             auto &dstA = sums.first(acc);
             auto &dstB = sums.second(acc);
@@ -1157,11 +1171,10 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
         if (b0 < b1) {
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
             else {
-                constexpr bool PINNED = !(MT == 4 && SC == 2);      // M = 64: 297 us, pinned 306
                 const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW, 0>(kchunks, n);
-                if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
-                else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
-                else anyk_walk<MT, NW, N, SC, false, 0, true, PINNED, 0>(it.a, smem, &s_flag, b0, 1, n);
+                if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
+                else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
+                else anyk_walk<MT, NW, N, SC, false, 0, true, 0, (MT > 1)>(it.a, smem, &s_flag, b0, 1, n);
             }
         }
         pos = it.first_work + n_blocks * kchunks;       // on to the next matrix (or past `end`)
@@ -1261,22 +1274,14 @@ int launch_fused(const GArgs &a, void *stream)
     // ... and on the F16 matrix cores at M > 16, where X in registers and the converted operands do not fit together
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
         const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
-        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, true, ACC == 0 ? 2 : 0>), dim3(grid), dim3(16 * 64), 0, s, a);
+        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
+        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, ACC == 0 ? 2 : 0>), dim3(grid), dim3(16 * 64), 0, s, a);
+        // a few rows of X are few accesses either way, and the turn is time.  Operands / turned, us, M = 1 / 4 / 8 / 12 / 16: 4096 x 14336
+        // 14.1 / 14.7 / 15.4 / 16.2 / 16.8, 15.3 / 15.5 / 15.4 / 15.4 / 15.4; 14336 x 9216 29.7 / 29.9 / 31.3 / 33.0 / 35.4, 32.4 for all
+        else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // X pieces of two chunks: 8 waves' worth of registers
-        else {
-            // Four tiles of X with a scale per row and 128 columns crowd the registers: pinning the lookups (quad_step_held) pays only
-            // from seven chunks of a block per wave on, and with two blocks of rows or more per workgroup from four, or for two nearly
-            // full rounds.  us pinned / not, 14336 rows, M = 64: K = 1024 26.0 / 23.7, 2048 39.8 / 38.8, 3072 55.5 / 54.9, 3584 63.0 / 65.1,
-            // 4096 68.0 / 70.2, 4608 78.3 / 75.1, 5120 84.3 / 82.2, 6144 97.3 / 97.5, 8192 120.8 / 123.8, 11264 157.5 / 164.5, 16384 222.8 / 228.8;
-            // 4096 rows, M = 48: 1024 10.8 / 10.0, 4096 18.8 / 18.4, 5120 22.9 / 21.5, 8192 31.3 / 30.9, 14336 49.8 / 49.8; M = 64: 14336 55.8 / 56.6.
-            const uint64_t kchunks = a.K / 256;
-            const bool pinned = SCALED != 2 || ACC != 0 || kchunks >= 56 ||
-                                (a.rows / BLOCK_ROWS >= 2 * (uint64_t)grid && (kchunks >= 32 || (kchunks >= 14 && kchunks <= 16)));
-            if (pinned) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
-            else if constexpr (SCALED == 2 && ACC == 0) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC, false>), dim3(grid), dim3(8 * 64), 0, s, a);
-        }
+        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
         return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
     }
     if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_kernel<1, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);

@@ -618,6 +618,31 @@ def test_grouped_gemm_equals_the_single_calls(orc, name, scale_mode):
     _check(ys[-1].cpu().numpy(), yref, mag, "grouped, last member")
 
 
+@pytest.mark.parametrize("rows,K", [(256, 4096), (272, 4096), (8192, 4096), (1040, 256), (4112, 2048), (8192, 7168), (512, 10240), (4160, 8448)])
+def test_runs_of_the_longest_codewords(rows, K):
+    """A run is fetched as 8 dwords: 32 codewords of 7 bits and what is in front of them fill these to the last bit.  Lanes of such codewords at
+    both ends of the stream and inside, next to runs of one and two bits a codeword; X rows either side of where the kernels
+    change.  W decoded wrongly anywhere shows against the product on uncompressed W."""
+    rng = np.random.default_rng(rows + K)
+    e = (7 + np.minimum(rng.geometric(0.5, (rows, K)) - 1, 5)).astype(np.uint8)
+    chunks = [(0, 0, 0, 0), (rows // 16 - 1, K // 256 - 1, 15, 3)] + [tuple(int(rng.integers(0, k)) for k in (rows // 16, K // 256, 16, 4)) for _ in range(24)]
+    for block, kc, n, g in chunks:                                      # one lane's 64 elements
+        for q in range(4):
+            c = 256 * kc + 64 * q + 16 * g
+            e[16 * block + n, c:c + 16] = rng.integers(13, 15, 16)
+    w = (e << 3) | (rng.integers(0, 256, (rows, K), dtype=np.uint8) & 0x87)
+    blob = ecf8.ecf8_encode(w, rows, K, lane_syms=64, tile_rows=16)
+    lens = list(blob.header.code_len)
+    assert lens[7] == 1 and lens[13] == lens[14] == 7
+    d_w, d_blob = torch.from_numpy(w).to(DEV), blob.to(DEV)
+    for M in (1, 8, 9, 16, 17, 33, 64):
+        x = synth.activations(M, K, seed=M, device=DEV)
+        want, got = ecf8.ecf8_gemm_fp8_raw(d_w, x), ecf8.ecf8_gemm_fp8(blob.header, d_blob, x)
+        want_x, got_x = ecf8.ecf8_gemm_fp8_raw_exact(d_w, x), ecf8.ecf8_gemm_fp8_exact(blob.header, d_blob, x)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want) and torch.equal(got_x, want_x), M
+
+
 @pytest.mark.parametrize("M", [4, 16, 24, 64])
 def test_deals_of_chunks_to_waves(M):
     """Either side of every border of the any-K deal: as many chunks per block as fall to half the waves, one wave or two each and one
