@@ -44,7 +44,7 @@ struct BArgs {
 template <int FMT> struct Fmt;
 template <> struct Fmt<ECFW_FMT_E5M2> {
     static constexpr int P = 16, ELEM = 1, A = 32;
-    static constexpr int SYM_SHIFT = 2, LEN_SHIFT = 8;     // entry = exponent << 2 | length << 8
+    static constexpr int SYM_SHIFT = 2, LEN_SHIFT = 7;     // entry = exponent << 2 | length << 7
 };
 template <> struct Fmt<ECFW_FMT_BF16> {
     static constexpr int P = 8, ELEM = 2, A = 256;
@@ -558,15 +558,39 @@ __device__ __forceinline__ void build_pairs(const uint16_t *tbl, typename Pairs<
     using PT = Pairs<FMT>;
     constexpr uint32_t M = (1u << WTB) - 1;
     for (uint32_t lo = tid; lo <= M; lo += nthreads) {
-        const uint32_t t1 = tbl[lo], l1 = entry_len<FMT>(t1), base = t1 & PT::SYM1;
+        const uint32_t t1 = tbl[lo], l1 = entry_len<FMT>(t1), base = t1 & PT::SYM1, alone = base + (l1 << PT::FIRST_AT);
+        // E5M2: an entry's field and length, five bits up, are what a pair has of its second codeword, and a pair that does not fit is one
+        // whose sum goes past 16 bits (E5M2 has four times the entries of BF16, which were 4 us of a launch and of a change of tensors; now 2)
+        const uint32_t sum1 = l1 ? base + (l1 << PT::LEN_AT) : 1u << 16;
 #pragma unroll
         for (uint32_t hi = 0; hi < 1u << (PT::BITS - WTB); hi++) {
-            const uint32_t t2 = tbl[((lo | (hi << WTB)) >> l1) & M], l2 = entry_len<FMT>(t2), n = l1 + l2;
-            const bool pair = l1 != 0 && l2 != 0 && n <= (uint32_t)PT::BITS;
-            pairs[lo | (hi << WTB)] = (typename PT::Entry)(base + (pair ? ((t2 & PT::SYM1) << PT::SYM2_AT) + (n << PT::LEN_AT) : l1 << PT::FIRST_AT));
+            const uint32_t t2 = tbl[((lo | (hi << WTB)) >> l1) & M];
+            uint32_t e;
+            if constexpr (FMT == ECFW_FMT_E5M2) {
+                static_assert(FMT != ECFW_FMT_E5M2 || (PT::LEN_AT == Fmt<FMT>::LEN_SHIFT + 5 && PT::SYM2_AT == 5 && PT::LEN_AT + 4 == 16), "sums of entries");
+                const uint32_t sum = sum1 + (t2 << 5);
+                e = sum < 1u << 16 && t2 != 0 ? sum : alone;
+            } else {
+                const uint32_t l2 = entry_len<FMT>(t2), n = l1 + l2;
+                e = l1 != 0 && l2 != 0 && n <= (uint32_t)PT::BITS ? base + ((t2 & PT::SYM1) << PT::SYM2_AT) + (n << PT::LEN_AT) : alone;
+            }
+            pairs[lo | (hi << WTB)] = (typename PT::Entry)e;
         }
     }
     __syncthreads();
+}
+
+// The second level: e, n are the entry at bit `from` of W and its length, 0 where its pair did not fit.
+template <int FMT>
+__device__ __forceinline__ void join_pair(const uint8_t *tbl, uint64_t W, uint32_t from, uint32_t &e, uint32_t &n)
+{
+    using PT = Pairs<FMT>;
+    const uint32_t l = (e >> PT::FIRST_AT) & 15u;           // of use only where n == 0
+    const uint32_t x = *(const uint16_t *)(tbl + (((uint32_t)(W >> (from + l)) >> (PT::OFF - 1)) & WMASK2));
+    if (n == 0) {
+        e = (e & PT::SYM1) | ((x & PT::SYM1) << PT::SYM2_AT);
+        n = l + entry_len<FMT>(x);
+    }
 }
 
 // Four codewords of each run: two lookups.  pa = (next bit of the forward run) - OFF and pb = (one past the next bit of the
@@ -596,25 +620,63 @@ __device__ __forceinline__ void quad_step(const uint8_t *smem, const uint8_t *pa
         const uint32_t dA2 = *(const uint32_t *)(smem + aA + 8), dBm = *(const uint32_t *)(smem + aB - 4);
         const uint64_t WA = wA | ((uint64_t)__builtin_amdgcn_alignbit(dA2, dA1, pa) << 32);
         const uint64_t WB = wB | ((uint64_t)__brev(__builtin_amdgcn_alignbit(dB0, dBm, pb)) << 32);
-        auto join = [&](uint64_t W, uint32_t from, uint32_t &e, uint32_t &n) {       // e: the entry at bit `from` of W
-            const uint32_t l = (e >> PT::FIRST_AT) & 15u;                            // of use only where n == 0
-            const uint32_t x = *(const uint16_t *)(tbl + (((uint32_t)(W >> (from + l)) >> (PT::OFF - 1)) & WMASK2));
-            if (n == 0) {
-                e = (e & PT::SYM1) | ((x & PT::SYM1) << PT::SYM2_AT);
-                n = l + entry_len<FMT>(x);
-            }
-        };
-        join(WA, 0, eA1, nA1);                    // first pairs: at most 24 bits
-        join(WB, 0, eB1, nB1);
+        join_pair<FMT>(tbl, WA, 0, eA1, nA1);     // first pairs: at most 24 bits
+        join_pair<FMT>(tbl, WB, 0, eB1, nB1);
         eA2 = at((uint32_t)(WA >> nA1));
         eB2 = at((uint32_t)(WB >> nB1));
         nA2 = PT::len(eA2);
         nB2 = PT::len(eB2);
-        join(WA, nA1, eA2, nA2);                  // at most OFF + 24 + 15 + 12 bits from the windows' start
-        join(WB, nB1, eB2, nB2);
+        join_pair<FMT>(tbl, WA, nA1, eA2, nA2);   // at most OFF + 24 + 15 + 12 bits from the windows' start
+        join_pair<FMT>(tbl, WB, nB1, eB2, nB2);
     }
     pa += nA1 + nA2;
     pb = pb - nB1 - nB2;
+}
+
+// E5M2: quad_step over windows held in registers, as in the E4M3 decoder (HeldRuns).  Pairs that fit the table move a run by 30 bits at the most, by
+// one dword; where one does not, the run may move by two, and its dwords are fetched again.
+__device__ __forceinline__ void quad_step_held(const uint8_t *smem, const uint8_t *pairs, const uint8_t *tbl, HeldRuns &r, uint32_t &eA1, uint32_t &eA2,
+                                               uint32_t &eB1, uint32_t &eB2)
+{
+    using PT = Pairs<ECFW_FMT_E5M2>;
+    static_assert(PT::OFF == 1, "HeldRuns are one bit off");
+    auto at = [&](uint32_t w) -> uint32_t { return *(const uint16_t *)(pairs + (w & (((1u << PT::BITS) - 1) << 1))); };
+    const uint32_t wA = __builtin_amdgcn_alignbit(r.a1, r.a0, r.pa);
+    const uint32_t wB = __brev(__builtin_amdgcn_alignbit(r.b1, r.b0, r.pb));
+    eA1 = at(wA);
+    eB1 = at(wB);
+    __builtin_amdgcn_sched_barrier(0x7f);           // the look-ups stay in front of the next dwords
+    const uint32_t a2 = *(const uint32_t *)(smem + r.A + 8);
+    const uint32_t bm = *(const uint32_t *)(smem + r.B);
+    uint32_t nA1 = PT::len(eA1), nB1 = PT::len(eB1);
+    eA2 = at(wA >> nA1);
+    eB2 = at(wB >> nB1);
+    uint32_t nA2 = PT::len(eA2), nB2 = PT::len(eB2);
+    // n1 == 0 makes the second lookup repeat the first, so n2 == 0 covers both pairs of a run
+    if (__builtin_expect(nA2 == 0 || nB2 == 0, 0)) {
+        const uint64_t WA = wA | ((uint64_t)__builtin_amdgcn_alignbit(a2, r.a1, r.pa) << 32);
+        const uint64_t WB = wB | ((uint64_t)__brev(__builtin_amdgcn_alignbit(r.b0, bm, r.pb)) << 32);
+        join_pair<ECFW_FMT_E5M2>(tbl, WA, 0, eA1, nA1);
+        join_pair<ECFW_FMT_E5M2>(tbl, WB, 0, eB1, nB1);
+        eA2 = at((uint32_t)(WA >> nA1));
+        eB2 = at((uint32_t)(WB >> nB1));
+        nA2 = PT::len(eA2);
+        nB2 = PT::len(eB2);
+        join_pair<ECFW_FMT_E5M2>(tbl, WA, nA1, eA2, nA2);
+        join_pair<ECFW_FMT_E5M2>(tbl, WB, nB1, eB2, nB2);
+        r.begin(smem, r.pa + nA1 + nA2, r.pb + 32 - nB1 - nB2);
+        return;
+    }
+    r.pa += nA1 + nA2;
+    r.pb -= nB1 + nB2;
+    const uint32_t A = (r.pa >> 3) & ~3u, B = (r.pb >> 3) & ~3u;
+    const bool upA = A != r.A, downB = B != r.B;
+    r.a0 = upA ? r.a1 : r.a0;
+    r.a1 = upA ? a2 : r.a1;
+    r.b1 = downB ? r.b0 : r.b1;
+    r.b0 = downB ? bm : r.b0;
+    r.A = A;
+    r.B = B;
 }
 
 template <int FMT, int N, int WAVES>
@@ -743,6 +805,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                                 uint32_t next_stride) {
             constexpr bool RELOAD = decltype(reload)::value, CUT = decltype(cut)::value;
             uint32_t pa = first_bit - Pairs<FMT>::OFF, pb = first_bit + lb - (32 - Pairs<FMT>::OFF);                 // see quad_step
+            HeldRuns runs;
+            if constexpr (!BF) runs.begin(smem, pa, pb);
             auto piece = [&](const uint32_t (&x)[4], const Rest &r) {
                 u32x4 d;
                 if constexpr (BF) {
@@ -790,7 +854,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
 #pragma unroll
                     for (int t = 0; t < (BF ? 2 : 4); t++) {
                         uint32_t eA1, eA2, eB1, eB2;
-                        quad_step<FMT>(smem, smem + C::OFF_PAIRS, smem + C::OFF_TBL, pa, pb, eA1, eA2, eB1, eB2);
+                        if constexpr (BF) quad_step<FMT>(smem, smem + C::OFF_PAIRS, smem + C::OFF_TBL, pa, pb, eA1, eA2, eB1, eB2);
+                        else quad_step_held(smem, smem + C::OFF_PAIRS, smem + C::OFF_TBL, runs, eA1, eA2, eB1, eB2);
                         if constexpr (BF) {
                             xA[2 * t] = eA1; xA[2 * t + 1] = eA2;
                             xB[2 * t] = eB1; xB[2 * t + 1] = eB2;

@@ -97,6 +97,20 @@ def test_caps(orc, fmt, cap):
     assert blob.header.max_code_len <= cap
 
 
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+@pytest.mark.parametrize("symbols", [1, 2, 3])
+def test_codes_of_a_few_symbols(orc, fmt, symbols):
+    """One symbol has the code "0": half of the tables' entries belong to no codeword, and no pair begins or ends there."""
+    rng = np.random.default_rng(symbols)
+    n = 3 * 8192 + 17
+    e = np.array([9, 30, 17])[np.minimum(rng.geometric(0.6, n) - 1, symbols - 1)]
+    if fmt == E5M2:
+        x = ((e << 2) | (rng.integers(0, 256, n) & 0x83)).astype(np.uint8)
+    else:
+        x = ((e << 7) | (rng.integers(0, 65536, n) & 0x807f)).astype(np.uint16)
+    _check(orc, fmt, x)
+
+
 def test_long_codes_everywhere(orc):
     """BF16 with all 256 exponent fields in use and geometric frequencies: under the cap of 16 most
     fields have codewords of 13..16 bits, so the long-code branch runs in most decode steps."""
