@@ -260,7 +260,8 @@ def blob_stats(hdr):
 
 def _stream_ptr(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the object around it, which takes 2.7 us of a call's 7.4
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
