@@ -10,7 +10,7 @@
 //    pair table is built from a 2^12-entry table of single codewords, with entries that fit the format (see Pairs);
 //    pairs that do not fit it take a branch-free second level.  The launch of a layer of seven matrices (218 M elements)
 //    with one codeword per lookup and the lanes' bits moved to bank-private LDS columns first took 107.5 us for E5M2,
-//    bound by LDS and vector work; now 90 (376 MB: 4.2 TB/s, two thirds of what is left is vector work).  BF16
+//    bound by LDS and vector work; now 86 (376 MB: 4.4 TB/s; set-up of the tables, and LDS and vector work).  BF16
 //    was and is at the memory wall, 139 .. 141 us (735 MB: 5.3 TB/s);
 //  * codes with longer codewords (cap 13..16, ecfw_long_decode_kernel) keep one codeword per lookup and
 //    a canonical first-code comparison per length, in a rarely taken branch;
@@ -553,28 +553,49 @@ template <> struct Pairs<ECFW_FMT_BF16> {
 // shifted in at the top can only lengthen a codeword that does not fit anyway).  A thread keeps the low bits and
 // walks over the others.
 template <int FMT>
-__device__ __forceinline__ void build_pairs(const uint16_t *tbl, typename Pairs<FMT>::Entry *pairs, int tid, int nthreads)
+__device__ __forceinline__ void build_pairs(const uint16_t *tbl, typename Pairs<FMT>::Entry *pairs, uint16_t *tmp, int tid, int nthreads)
 {
     using PT = Pairs<FMT>;
     constexpr uint32_t M = (1u << WTB) - 1;
-    for (uint32_t lo = tid; lo <= M; lo += nthreads) {
-        const uint32_t t1 = tbl[lo], l1 = entry_len<FMT>(t1), base = t1 & PT::SYM1, alone = base + (l1 << PT::FIRST_AT);
-        // E5M2: an entry's field and length, five bits up, are what a pair has of its second codeword, and a pair that does not fit is one
-        // whose sum goes past 16 bits (E5M2 has four times the entries of BF16, which were 4 us of a launch and of a change of tensors; now 2)
-        const uint32_t sum1 = l1 ? base + (l1 << PT::LEN_AT) : 1u << 16;
+    if constexpr (FMT == ECFW_FMT_E5M2) {
+        // Two entries at a time, those of low bits 2t and 2t + 1, in the halves of a dword.  A pair's entry is the sum of two parts: of the
+        // first codeword its field and length, of the second the same five bits up, which `tmp` has for all 12-bit indices.  A pair that
+        // does not fit goes past 16 bits and saturates, and so does one of an index without a codeword, which is all ones here.
+        // (Four times the entries of BF16, per workgroup and tensor.  Made one at a time, with a sum and two compares, a launch took 0.8 us
+        // more, with lengths taken apart and compared 1.5.)
+        static_assert(PT::LEN_AT == Fmt<FMT>::LEN_SHIFT + 5 && PT::SYM2_AT == 5 && PT::LEN_AT + 4 == 16 && PT::SYM1 == 0x7cu, "sums of entries");
+        typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+        for (uint32_t i = tid; i <= M / 2; i += nthreads) {
+            const uint32_t t = ((const uint32_t *)tbl)[i], lo = t & 0xffffu, hi = t >> 16;
+            ((uint32_t *)tmp)[i] = (lo ? lo << 5 : 0xffffu) | (hi ? hi << 21 : 0xffff0000u);
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i <= M / 2; i += nthreads) {
+            const uint32_t t = ((const uint32_t *)tbl)[i], lo = t & 0xffffu, hi = t >> 16;
+            const uint32_t l0 = entry_len<FMT>(lo), l1 = entry_len<FMT>(hi);
+            const uint32_t first = (lo ? (lo & PT::SYM1) | (l0 << PT::LEN_AT) : 0xffffu) | (hi ? (hi & PT::SYM1) | (l1 << PT::LEN_AT) : 0xffffu) << 16;
+            const uint32_t alone = (lo & PT::SYM1) | (l0 << PT::FIRST_AT) | ((hi & PT::SYM1) | (l1 << PT::FIRST_AT)) << 16;
+            const uint32_t at0 = ((4 * i) >> l0) & ~1u, at1 = ((4 * i + 2) >> l1) & ~1u;       // bytes into tmp
 #pragma unroll
-        for (uint32_t hi = 0; hi < 1u << (PT::BITS - WTB); hi++) {
-            const uint32_t t2 = tbl[((lo | (hi << WTB)) >> l1) & M];
-            uint32_t e;
-            if constexpr (FMT == ECFW_FMT_E5M2) {
-                static_assert(FMT != ECFW_FMT_E5M2 || (PT::LEN_AT == Fmt<FMT>::LEN_SHIFT + 5 && PT::SYM2_AT == 5 && PT::LEN_AT + 4 == 16), "sums of entries");
-                const uint32_t sum = sum1 + (t2 << 5);
-                e = sum < 1u << 16 && t2 != 0 ? sum : alone;
-            } else {
-                const uint32_t l2 = entry_len<FMT>(t2), n = l1 + l2;
-                e = l1 != 0 && l2 != 0 && n <= (uint32_t)PT::BITS ? base + ((t2 & PT::SYM1) << PT::SYM2_AT) + (n << PT::LEN_AT) : alone;
+            for (uint32_t h = 0; h < 1u << (PT::BITS - WTB); h++) {
+                const uint32_t t0 = *(const uint16_t *)((const uint8_t *)tmp + ((((h << (WTB + 1)) >> l0) & (2 * M)) | at0));
+                const uint32_t t1 = *(const uint16_t *)((const uint8_t *)tmp + ((((h << (WTB + 1)) >> l1) & (2 * M)) | at1));
+                const uint32_t second = t0 | (t1 << 16);
+                const u16x2 sum = __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, first), __builtin_bit_cast(u16x2, second));
+                // 0xffff where it saturated: a sum that fits has its lowest two bits clear
+                const u16x2 over = __builtin_elementwise_sub_sat(sum, u16x2{0xfffc, 0xfffc}) * u16x2{0x5555, 0x5555};
+                ((uint32_t *)pairs)[i | (h << (WTB - 1))] = bit_sel(__builtin_bit_cast(uint32_t, over), alone, __builtin_bit_cast(uint32_t, sum));
             }
-            pairs[lo | (hi << WTB)] = (typename PT::Entry)e;
+        }
+    } else {
+        for (uint32_t lo = tid; lo <= M; lo += nthreads) {
+            const uint32_t t1 = tbl[lo], l1 = entry_len<FMT>(t1), base = t1 & PT::SYM1;
+#pragma unroll
+            for (uint32_t hi = 0; hi < 1u << (PT::BITS - WTB); hi++) {
+                const uint32_t t2 = tbl[((lo | (hi << WTB)) >> l1) & M], l2 = entry_len<FMT>(t2), n = l1 + l2;
+                const bool pair = l1 != 0 && l2 != 0 && n <= (uint32_t)PT::BITS;
+                pairs[lo | (hi << WTB)] = (typename PT::Entry)(base + (pair ? ((t2 & PT::SYM1) << PT::SYM2_AT) + (n << PT::LEN_AT) : l1 << PT::FIRST_AT));
+            }
         }
     }
     __syncthreads();
@@ -703,6 +724,7 @@ struct PCfg {
     static_assert(PIECES % 4 == 0, "two runs of whole pieces, in bursts of two or more");
     static_assert(TOTAL <= 160 * 1024, "LDS of one gfx950 CU");
     static_assert(WAVES >= 4, "the code set-up ranks 256 symbols with four wavefronts");
+    static_assert(WAVES * STAGE >= 2 << WTB, "scratch of build_pairs");
 };
 
 // The loop of the E4M3 decoder (ecf8_decode.hip) over these tables: metadata two chunks ahead, payload one chunk ahead in
@@ -797,7 +819,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;
         build_code<FMT>(my_len, (uint32_t *)(smem + C::OFF_WCNT), smem + C::OFF_SORTED, (uint32_t *)(smem + C::OFF_CNT),
                         (uint32_t *)(smem + C::OFF_FIRST), (uint32_t *)(smem + C::OFF_OFFS), tbl, tid, WAVES * 64);
-        build_pairs<FMT>(tbl, (typename Pairs<FMT>::Entry *)(smem + C::OFF_PAIRS), tid, WAVES * 64);
+        build_pairs<FMT>(tbl, (typename Pairs<FMT>::Entry *)(smem + C::OFF_PAIRS), (uint16_t *)(smem + C::OFF_STAGE), tid, WAVES * 64);
 
         // One chunk from LDS bit `first_bit` on.  The pieces of `rest` give their registers to the chunk whose first
         // element in this lane is next_e (RELOAD); CUT: the chunk reaches past the tensor's end.
@@ -983,7 +1005,7 @@ int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, h
     // Waves per workgroup and bursts, measured on a layer of seven matrices (218 M elements):
     //   BF16, N = 64   8 waves, a chunk's pieces in one burst 139.0 us; 10 waves 139.6, 12 waves 140.6, 6 waves 150.7; in two
     //                  bursts 8 waves 144.8, 12 waves 145, 16 waves 149
-    //   E5M2, N = 128  12 waves, two bursts 90.0 us; 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
+    //   E5M2, N = 128  12 waves, two bursts 90.0 us (before windows were held in registers; 86.2 since); 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
     // i.e. BF16 is at the memory wall and wants its stores together, E5M2 wants the waves to hide its look-ups.
     if constexpr (FMT == ECFW_FMT_BF16) {
         const uint64_t wgs = workgroups(a, max_workgroups), each = wgs ? (a.total_chunks + wgs - 1) / wgs : 0;
