@@ -23,7 +23,7 @@
  * bit goes uncoded (0.750 of the raw size against 0.726 for ECFW_FMT_E5M2 on the
  * synthetic weights), and the decoder is that of ecf8.h, whose capped codes always
  * have two symbols in one lookup: one launch over eight 14336 x 4096 matrices takes
- * 153 us against 178 us for ECFW_FMT_E5M2, 1.16 x as fast.  Use ECFW_FMT_E5M2 for the
+ * 152 us against 174 us for ECFW_FMT_E5M2, 1.15 x as fast.  Use ECFW_FMT_E5M2 for the
  * smaller blob, the FP8 container for the somewhat faster decode and for what only
  * ecf8.h has (the fused products).
  *

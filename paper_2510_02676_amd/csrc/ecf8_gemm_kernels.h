@@ -458,8 +458,8 @@ struct MetaReader {
 // masked window the byte offset of a table entry (see quad_step2), and up to 31 bits of its dword.  Positions are counted
 // in bits from 16 bytes before the chunk's span.
 // The chunk's span staged in LDS and the runs' windows read from there took a third of the LDS's time, which was busy for 61 % (14336 x 4096,
-// M = 16) and 76 % (eight experts, M = 4) of the launch, and a quarter of the vector operations.  Now the gathers are 256 accesses to the
-// first-level cache a chunk, which has the time.  us: 14336 x 4096, M = 1 / 16 / 32 / 64 17.8 / 19.1 / 22.1 / 29.2 -> 15.2 / 15.5 / 18.9 / 24.6, 14336 x 7168,
+// M = 16) and 76 % (eight experts, M = 4) of the launch.  Now the gathers are 256 accesses to the
+// first-level cache a chunk, which has the time; vector operations are as many as before.  us: 14336 x 4096, M = 1 / 16 / 32 / 64 17.8 / 19.1 / 22.1 / 29.2 -> 15.2 / 15.5 / 18.9 / 24.6, 14336 x 7168,
 // M = 16 31.1 -> 25.1, six experts, scales of W, M = 4 67.7 -> 55.3, eight 86.6 -> 75.8.  Cached: the lines are a lane's neighbours' too.
 typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
 struct RawRuns {
