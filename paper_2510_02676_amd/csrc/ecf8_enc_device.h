@@ -68,13 +68,14 @@ struct LanePacker {
     {
         if (fill) __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
+    __device__ __forceinline__ uint32_t end(const uint32_t *image) const { return (uint32_t)(d - image) * 32 + fill; }     // the bit behind the last one
 };
 
 // ---- the container behind the code: one pass over the weights ----
 // A wave takes a few chunks in a row, a workgroup as many times its waves, a tile.  Chunk by chunk the wave counts the code bits,
 // writes the planes and packs the bits into its image in LDS, one chunk behind the other; where they go is only known when
 // everything before them has been counted.  That the workgroups find out from one another, once per tile, and then copy the
-// images to the stream, shifted into place.  Tiles are drawn from a counter, so that a workgroup waits only for tiles
+// images to the stream, shifted into place.  Chunks that did not fit any more are packed after that.  Tiles are drawn from a counter, so that a workgroup waits only for tiles
 // that were drawn before its own; these wait for earlier ones only, so every wait ends whatever part of the grid is running.
 //
 // The exchange goes through chunk_bit[], which the histogram kernel has zeroed.  Of the entries of tile t, which has T chunks,
@@ -87,8 +88,8 @@ struct LanePacker {
 // has nothing else to do meanwhile; hence tiles as large as the LDS holds, and one per compute unit where that is enough.
 // 58.7 M E4M3 weights: tiles of eight chunks, two workgroups per compute unit, 52 us; of 16 chunks 42; of 32, one per compute unit, 32.
 constexpr uint64_t SAID_TOTAL = 1ull << 63, SAID_TAIL = 1ull << 62;
-constexpr int LATE_DWORDS = 68;             // end of an image: one lane's bits of a chunk that does not fit into the rest
-constexpr int LATE_LANES = 16;              // such a chunk goes out by so many lanes at a time, whose bits fit whatever they are
+constexpr int LATE_DWORDS = 20;             // end of an image: the last 32 codewords of a lane of a chunk that does not fit into the rest
+constexpr int LATE_LANES = 32;              // a chunk of more bits than an image takes goes out by so many lanes at a time, whose bits fit whatever they are
 
 __device__ __forceinline__ uint64_t agent_load(GLOBAL uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void agent_store(GLOBAL uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -199,9 +200,7 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
         if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add((GLOBAL uint32_t *)blob, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     auto first_chunk = [&](uint32_t t) { return (uint64_t)T * t + (uint64_t)ta.per_wave * wave; };
-    auto fetch_first = [&](uint32_t t) {
-        if (t < n_tiles && k.whole(first_chunk(t))) k.fetch(first_chunk(t));
-    };
+    bool fetched = false;                   // the tile's first chunk
     auto zero = [&](uint32_t dwords) {
         for (uint32_t u = lane; u * 4 < dwords; u += 64) *(u32x4 *)(image + 4 * u) = u32x4{0, 0, 0, 0};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -213,20 +212,21 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
     }
     __syncthreads();
     uint32_t t = uniform32(sh.drawn[1]);
-    fetch_first(t);
     for (uint32_t parity = 0; t < n_tiles; parity ^= 1) {
         const uint64_t first = (uint64_t)T * t, c0 = first_chunk(t);
         const bool followed = first + T < ta.n_chunks;
         const uint32_t count = c0 < ta.n_chunks ? (uint32_t)(ta.n_chunks - c0 < ta.per_wave ? ta.n_chunks - c0 : ta.per_wave) : 0u;
         uint32_t total = 0, used = 0, kept = 0, upto = 0, late_bits = 0;         // upto: lane i, bits up to the end of chunk i
+        uint32_t lb = 0, incl = 0;                                               // of the chunk counted last
+        if (!fetched && k.whole(c0)) k.fetch(c0);
         zero(K::AREA);
 #pragma unroll 1
         for (uint32_t i = 0; i < count; i++) {
             const uint64_t c = c0 + i;
             const bool whole = k.whole(c);
-            const uint32_t lb = whole ? k.count(c) : k.slow_count(c, true);
+            lb = whole ? k.count(c) : k.slow_count(c);
             lane_bits[c * 64 + lane] = (uint16_t)lb;
-            const uint32_t incl = wave_incl_scan(lb);
+            incl = wave_incl_scan(lb);
             uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             bits = bits ? bits : 1u;                            // weights that change under the call have no codes: garbage, but no tile that begins at 0
             total += bits;
@@ -243,13 +243,14 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
             // A chunk that does not fit behind the others is packed when its place is known; of the last one the last bits are needed before.
             const bool fits = kept == i && used + bits <= ROOM, refill = fits && i + 1 < count && k.whole(c + 1);
             if (fits && whole) k.pack(image, used + incl - lb, c, refill);
-            else if (fits || (i + 1 == count && lane == 63)) k.slow_pack(image + (fits ? 0 : K::AREA - LATE_DWORDS), fits ? used + incl - lb : 0u, c);
+            else if (fits || (i + 1 == count && lane == 63))
+                late_bits = k.slow_pack(image + (fits ? 0 : K::AREA - LATE_DWORDS), fits ? used + incl - lb : 0u, c, fits ? 0 : K::TAIL_FROM);
             if (i + 1 < count && !refill && k.whole(c + 1)) k.fetch(c + 1);
-            late_bits = (uint32_t)__builtin_amdgcn_readlane((int)lb, 63);
             kept += fits ? 1u : 0u;
             used += fits ? bits : 0u;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        late_bits = (uint32_t)__builtin_amdgcn_readlane((int)late_bits, 63);
         if (lane == 0) {
             sh.tail[parity][wave] = kept == count ? last32(image, total) : last32(image + K::AREA - LATE_DWORDS, late_bits);
             if (wave == 0) sh.drawn[parity] = drawn;
@@ -273,7 +274,9 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
                 sh.begin = begin;
             }
         }
-        fetch_first(next);
+        fetched = kept == count;
+        const uint64_t then = fetched ? first_chunk(next) : c0 + kept;
+        if ((fetched ? next < n_tiles : kept + 1 < count) && k.whole(then)) k.fetch(then);
         __syncthreads();
         if (count) {
             const uint64_t b0 = uniform64(sh.begin) + before;
@@ -293,25 +296,48 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
             // all but the first bit of the tile behind, which the first wave has written
             if ((uint32_t)lane < count && !(followed && wave + 1 == (int)W && (uint32_t)lane + 1 == count)) agent_store(cb + c0 + lane + 1, b0 + upto);
             if (kept < count) {
+                // The chunks that did not fit, image by image as before.  14336 x 7168 E4M3, the upper three quarters zeros: 86 us; with these chunks looked
+                // up one symbol at a time by 16 lanes after the other 222 (84 with kernels of their own for counting and packing).  16384 x
+                // 16384, half zeros: 193, 323, 222.
                 uint64_t at = b0 + used;
                 if (kept) tail = last32(image, used);
+                used = 0;
+                zero(K::AREA);
+                auto flush = [&](bool end) {
+                    if (lane == 0) image[-1] = tail;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    copy_bits(image, stream, at, at + used, end, false, lane);
+                    if (used >= 32) tail = last32(image, used);
+                    else if (used) tail = (uint32_t)((((uint64_t)image[0] << 32 | tail) >> used));
+                    at += used;
+                    used = 0;
+                    zero(K::AREA);
+                };
+#pragma unroll 1
                 for (uint32_t i = kept; i < count; i++) {
                     const uint64_t c = c0 + i;
-                    const uint32_t lb = k.slow_count(c, false), incl = wave_incl_scan(lb);
-                    for (int l0 = 0; l0 < 64; l0 += LATE_LANES) {
-                        const uint32_t from = l0 ? (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 - 1) : 0u;
-                        const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 + LATE_LANES - 1) - from;
-                        zero(K::AREA);
-                        if (lane == 0) image[-1] = tail;
-                        if (lane >= l0 && lane < l0 + LATE_LANES) k.slow_pack(image, incl - lb - from, c);
-                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                        const bool end = c + 1 == ta.n_chunks && l0 + LATE_LANES == 64;
-                        copy_bits(image, stream, at, at + bits, end, false, lane);
-                        if (bits >= 32) tail = last32(image, bits);
-                        else if (bits) tail = (uint32_t)((((uint64_t)image[0] << 32 | tail) >> bits));
-                        at += bits;
+                    const bool whole = k.whole(c), more = i + 1 < count && k.whole(c + 1);
+                    if (kept + 1 < count) {                     // else it is the chunk counted last, and as count has left it
+                        lb = whole ? k.count(c) : k.slow_count(c);
+                        incl = wave_incl_scan(lb);
                     }
+                    const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                    if (used + bits > ROOM) flush(false);
+                    if (whole && bits <= ROOM) {
+                        k.pack(image, used + incl - lb, c, false);
+                        used += bits;
+                    } else {
+                        const int lanes = bits <= ROOM ? 64 : LATE_LANES;        // at a time, if an image does not take them all
+                        for (int l0 = 0; l0 < 64; l0 += lanes) {
+                            const uint32_t from = l0 ? (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 - 1) : 0u;
+                            if (lane >= l0 && lane < l0 + lanes) k.slow_pack(image, used + incl - lb - from, c, 0);
+                            used += (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 + lanes - 1) - from;
+                            if (lanes != 64) flush(false);
+                        }
+                    }
+                    if (more) k.fetch(c + 1);
                 }
+                flush(c0 + count == ta.n_chunks);
             }
         }
         t = next;

@@ -144,7 +144,8 @@ struct Chunk {
     static constexpr uint32_t BITS = (1u << 28) - 1;                                // CAP7: of an entry or two joined ones
     static constexpr int AREA = ((160 * 1024 - 1024 - 512 * (int)sizeof(Entry)) / (4 * WMAX) - 4) / 4 * 4;
     static constexpr int LANE_BITS = N * (CAP7 ? 7 : 15);                           // at most
-    static_assert(LANE_BITS < 32 * LATE_DWORDS && LANE_BITS * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
+    static constexpr int TAIL_FROM = N / 16 - 2;                                    // a lane's last 32 codewords
+    static_assert(32 * 15 < 32 * LATE_DWORDS && LANE_BITS * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
 
     const EncArgs &a;
     const Entry *fwd, *bwd;                 // pairs of symbols
@@ -209,15 +210,14 @@ struct Chunk {
     }
     static __device__ __forceinline__ uint32_t entry(const Entry *tab, uint32_t at) { return *(const uint32_t *)((const uint8_t *)tab + at); }
     // any chunk, piece by piece: its symbols one by one, those past the tensor's end have no bits
-    __device__ __forceinline__ u32x4 piece(uint64_t e, uint32_t back, uint32_t (&s)[16]) const
+    __device__ __forceinline__ void piece(const u32x4 &v4, uint64_t e, uint32_t back, uint32_t (&s)[16]) const
     {
-        const u32x4 v4 = load_cut((const GLOBAL uint8_t *)a.x, e, a.n);
         const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w}, have = piece_len(e, a.n);
 #pragma unroll
         for (uint32_t j = 0; j < 16; j++) s[j] = one[back][j < have ? (w[j >> 2] >> (8 * (j & 3) + 3)) & 15u : 16u];
-        return v4;
     }
-    __device__ __forceinline__ uint32_t slow_count(uint64_t c, bool planes)
+    __device__ __forceinline__ u32x4 slow_fetch(uint64_t e) const { return load_cut((const GLOBAL uint8_t *)a.x, e, a.n); }
+    __device__ __forceinline__ uint32_t slow_count(uint64_t c)
     {
         const ChunkPlace p = place_of<N>(a, c, lane);
         uint32_t lb = 0;
@@ -225,22 +225,30 @@ struct Chunk {
         for (int q = 0; q < N / 16; q++) {
             const uint64_t e = p.base + p.lane_off + q * p.stride;
             uint32_t s[16];
-            const u32x4 w = piece(e, 0, s);
+            const u32x4 w = slow_fetch(e);
+            piece(w, e, 0, s);
 #pragma unroll
             for (int j = 0; j < 16; j++) lb += s[j] >> 16;
-            if (planes) *(GLOBAL u32x2 *)((GLOBAL uint8_t *)a.blob + a.off_pl + e / 2) = nibbles(w);
+            *(GLOBAL u32x2 *)((GLOBAL uint8_t *)a.blob + a.off_pl + e / 2) = nibbles(w);
         }
         return lb;
     }
-    __device__ __forceinline__ void slow_pack(uint32_t *image, uint32_t at, uint64_t c)
+    // from the lane's i0-th piece on; the image's bit behind the last one
+    __device__ __forceinline__ uint32_t slow_pack(uint32_t *image, uint32_t at, uint64_t c, int i0)
     {
         const ChunkPlace p = place_of<N>(a, c, lane);
         LanePacker out(image, at);
+        const uint64_t e0 = p.base + p.lane_off;
+        const uint32_t stride = (uint32_t)p.stride;
+        auto at_piece = [&](int i) { return e0 + (uint32_t)(i >= N / 32 ? N / 16 - 1 - (i - N / 32) : i) * stride; };
+        u32x4 next = slow_fetch(at_piece(i0));
 #pragma unroll 1
-        for (int i = 0; i < N / 16; i++) {
+        for (int i = i0; i < N / 16; i++) {
             const bool back = i >= N / 32;
+            const u32x4 w = next;
+            if (i + 1 < N / 16) next = slow_fetch(at_piece(i + 1));
             uint32_t s[16];
-            piece(p.base + p.lane_off + (back ? N / 16 - 1 - (i - N / 32) : i) * p.stride, back ? 1 : 0, s);
+            piece(w, at_piece(i), back ? 1 : 0, s);
 #pragma unroll
             for (int j = 0; j < 16; j++) {
                 const uint32_t x = back ? s[15 - j] : s[j];
@@ -248,6 +256,7 @@ struct Chunk {
             }
         }
         out.finish();
+        return out.end(image);
     }
     // the four symbols of dword w, in order (BWD = false) or in reverse
     template <bool BWD>

@@ -166,7 +166,8 @@ struct Chunk {
     static constexpr uint32_t BITS = (1u << 27) - 1;                                // of a dword that holds codewords and their length
     static constexpr int PAIR_ENTRIES = PAIRS ? A * A : 1;
     static constexpr int AREA = ((160 * 1024 - 1024 - 8 * (A + 1) - 256 - 8 * PAIR_ENTRIES) / (4 * WMAX) - 4) / 4 * 4;
-    static_assert(N * LMAX < 32 * LATE_DWORDS && N * LMAX * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
+    static constexpr int TAIL_FROM = PIECES - 32 / P;                               // a lane's last 32 codewords
+    static_assert(32 * LMAX < 32 * LATE_DWORDS && N * LMAX * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
 
     const WEncArgs &a;
     const uint32_t (*code)[A + 1];          // code | length << 27, first bit lowest / highest; A = no symbol
@@ -316,15 +317,14 @@ struct Chunk {
         out.finish();
     }
     // any chunk, piece by piece; symbols past the tensor's end have no bits
-    __device__ __forceinline__ u32x4 piece(uint64_t e, uint32_t back, uint32_t (&s)[P]) const
+    __device__ __forceinline__ void piece(const u32x4 &v4, uint64_t e, uint32_t back, uint32_t (&s)[P]) const
     {
-        const u32x4 v4 = load_cut((const GLOBAL uint8_t *)a.x, e * F::ELEM, a.n * F::ELEM);
         const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w}, have = e + P <= a.n ? (uint32_t)P : e < a.n ? (uint32_t)(a.n - e) : 0u;
 #pragma unroll
         for (int j = 0; j < P; j++) s[j] = code[back][(uint32_t)j < have ? F::sym(w, j) : (uint32_t)A];
-        return v4;
     }
-    __device__ __forceinline__ uint32_t slow_count(uint64_t c, bool planes_)
+    __device__ __forceinline__ u32x4 slow_fetch(uint64_t e) const { return load_cut((const GLOBAL uint8_t *)a.x, e * F::ELEM, a.n * F::ELEM); }
+    __device__ __forceinline__ uint32_t slow_count(uint64_t c)
     {
         const ChunkPlace p = place_of<FMT, N>(a, c, lane);
         uint32_t lb = 0;
@@ -332,26 +332,33 @@ struct Chunk {
         for (int q = 0; q < PIECES; q++) {
             const uint64_t e = p.base + p.lane_off + q * p.stride;
             uint32_t s[P];
-            const u32x4 w = piece(e, 0, s);
+            const u32x4 w = slow_fetch(e);
+            piece(w, e, 0, s);
 #pragma unroll
             for (int j = 0; j < P; j++) lb += s[j] >> 27;
-            if (planes_) planes(e, w);
+            planes(e, w);
         }
         return lb;
     }
-    __device__ __forceinline__ void slow_pack(uint32_t *image, uint32_t at, uint64_t c)
+    // from the lane's i0-th piece on; the image's bit behind the last one
+    __device__ __forceinline__ uint32_t slow_pack(uint32_t *image, uint32_t at, uint64_t c, int i0)
     {
         const ChunkPlace p = place_of<FMT, N>(a, c, lane);
         LanePacker out(image, at);
+        const uint64_t e0 = p.base + p.lane_off;
+        const uint32_t stride = (uint32_t)p.stride;
+        auto at_piece = [&](int i) { return e0 + (uint32_t)(i >= PIECES / 2 ? PIECES - 1 - (i - PIECES / 2) : i) * stride; };
 #pragma unroll 1
-        for (int i = 0; i < PIECES; i++) {
+        for (int i = i0; i < PIECES; i++) {
             const bool back = i >= PIECES / 2;
+            const u32x4 w = slow_fetch(at_piece(i));
             uint32_t s[P];
-            piece(p.base + p.lane_off + (back ? PIECES - 1 - (i - PIECES / 2) : i) * p.stride, back ? 1 : 0, s);
+            piece(w, at_piece(i), back ? 1 : 0, s);
 #pragma unroll
             for (int j = 0; j < P; j += 2) put2(out, back ? s[P - 1 - j] : s[j], back ? s[P - 2 - j] : s[j + 1]);
         }
         out.finish();
+        return out.end(image);
     }
 };
 
