@@ -446,13 +446,19 @@ public:
     // The A counts, of the kernel that was given device(); without a page, from `counters`, by a copy that waits for all that is queued on s.
     bool read(uint64_t *host, int A, uint64_t counters, hipStream_t s)
     {
-        if (!page) return hipMemcpyWithStream(host, (const void *)(uintptr_t)counters, 8ull * A, hipMemcpyDeviceToHost, s) == hipSuccess;
+        if (!page) {
+            if (hipMemcpyWithStream(host, (const void *)(uintptr_t)counters, 8ull * A, hipMemcpyDeviceToHost, s) == hipSuccess) return true;
+            (void)hipGetLastError();
+            return false;
+        }
         const auto since = std::chrono::steady_clock::now();
         for (uint32_t i = 1; !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE); i++) {
             __builtin_ia32_pause();
             // the stream has more to do, or it has failed
             if (i % 256 == 0 && std::chrono::steady_clock::now() - since > std::chrono::milliseconds(1)) {
-                if (hipStreamSynchronize(s) != hipSuccess || !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE)) return false;
+                const bool done = hipStreamSynchronize(s) == hipSuccess;
+                if (!done) (void)hipGetLastError();
+                if (!done || !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE)) return false;
                 break;
             }
         }
@@ -462,11 +468,14 @@ public:
     }
 };
 
-// A stream that is being captured runs nothing: there is no histogram to wait for.
+// A stream that is being captured runs nothing: there is no histogram to wait for.  Nor is there on the null stream while one that waits for it is
+// captured, which the question is answered with as an error: the caller has it from the return value, and the next launch's check is not to find it.
 inline bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 } // namespace

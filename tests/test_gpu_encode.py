@@ -1,6 +1,7 @@
 """GPU-side encoder (ecf8_encode_gpu, paper Section 3.1 on the device): the container it writes is
 the CPU encoder's, byte for byte; the oracle's reader decodes it to the input and agrees on the
 stream length; the GPU decoder round-trips it."""
+import ctypes
 import time
 
 import numpy as np
@@ -332,3 +333,32 @@ def test_refused_while_the_stream_is_captured():
         assert bool((z == k + 1).all())
     hdr, blob = ecf8.ecf8_encode_gpu(x, 1, x.numel(), d_blob=out)
     assert np.array_equal(blob.cpu().numpy(), ecf8.ecf8_encode(x.cpu().numpy(), 1, x.numel()).numpy())
+
+
+class _Stream:
+    """A stream by its handle, as the binding takes one."""
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+def test_refused_on_the_null_stream_while_another_is_captured():
+    """A blocking stream that is being captured keeps the null stream from being used.  The call says so, and leaves no error behind for the next one, which
+    looks for errors of its launch, nor does it spoil the capture."""
+    hip = ecf8._lib
+    x = _rand_bytes(100_000, 6)
+    want = ecf8.ecf8_encode(x, 1, x.size)
+    d_x, d_blob, out = torch.from_numpy(x).to(DEV), want.to(DEV), torch.empty(1 << 18, dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    cs, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(cs), 0) == 0
+    assert hip.hipStreamBeginCapture(cs, 2) == 0                        # hipStreamCaptureModeRelaxed
+    with pytest.raises(ecf8.Ecf8Error) as e:
+        ecf8.ecf8_encode_gpu(d_x, 1, x.size, d_blob=out, stream=_Stream(None))
+    left = hip.hipPeekAtLastError()
+    assert hip.hipStreamEndCapture(cs, ctypes.byref(graph)) == 0
+    y = ecf8.ecf8_decode(want.header, d_blob)
+    hip.hipGraphDestroy(graph)
+    hip.hipStreamDestroy(cs)
+    torch.cuda.synchronize()
+    assert e.value.code == ecf8.E_HIP and left == 0
+    assert np.array_equal(y.cpu().numpy().reshape(-1), x)
