@@ -392,11 +392,24 @@ __device__ __forceinline__ void mail_histogram(uint64_t blob, uint64_t counters,
     if (threadIdx.x == 0) __hip_atomic_store((GLOBAL uint64_t *)mail + MAIL_SAID, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// While another thread captures a stream, some calls (to allocate, to free, to wait) fail in this one and spoil that capture, unless the thread says that
+// they have nothing to do with it.  An encoder's have not: none of its pages is ever part of a graph, and it waits for no stream that is captured.
+class CaptureRelaxed {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+
+public:
+    CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    CaptureRelaxed(const CaptureRelaxed &) = delete;
+    CaptureRelaxed &operator=(const CaptureRelaxed &) = delete;
+    ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // A page for one call.  Pages of finished calls are kept for later ones, of any thread, stream and device: KEPT of them per encoder, others are given back.
 class Mail {
     static constexpr size_t KEPT = 16;
     static std::mutex &lock() { static std::mutex m; return m; }
     static std::vector<uint64_t *> &free_pages() { static auto *v = new std::vector<uint64_t *>(); return *v; }    // outlives the runtime
+    const CaptureRelaxed relaxed;           // from before the page is allocated until it is given back
     uint64_t *page = nullptr;
     void *seen = nullptr;                   // the page as a kernel sees it
     bool quiet = true;                      // no kernel may still write to it

@@ -2,6 +2,9 @@
 the CPU encoder's, byte for byte; the oracle's reader decodes it to the input and agrees on the
 stream length; the GPU decoder round-trips it."""
 import ctypes
+import os
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -12,6 +15,7 @@ from paper_2510_02676_amd import ecf8, synth
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _rand_bytes(n, seed, conc=0.4):
@@ -362,3 +366,69 @@ def test_refused_on_the_null_stream_while_another_is_captured():
     torch.cuda.synchronize()
     assert e.value.code == ecf8.E_HIP and left == 0
     assert np.array_equal(y.cpu().numpy().reshape(-1), x)
+
+
+FIRST_CALL = """
+import ctypes, sys, threading
+import numpy as np
+import torch
+from paper_2510_02676_amd import ecf8, ecfw
+hip = ecf8._lib
+xs = np.random.default_rng(7).integers(0, 256, 1 << 22, dtype=np.uint8)
+blob, wide = ecf8.ecf8_encode(xs, 1, xs.size), ecfw.ecfw_encode(ecfw.FMT_E5M2, xs, 1, xs.size)
+x = torch.from_numpy(xs).to("cuda:0")
+outs = [torch.empty(1 << 23, dtype=torch.uint8, device="cuda:0") for _ in range(2 * 20)]
+d_blob, y = blob.to("cuda:0"), torch.zeros_like(x)
+streams = [torch.cuda.Stream() for _ in range(8)]
+big = [torch.zeros(1 << 27, dtype=torch.float32, device="cuda:0") for _ in streams]
+torch.cuda.synchronize()
+
+class Stream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+for s, b in zip(streams, big):                                          # some 10 ms: the calls wait with the stream, not with their page
+    with torch.cuda.stream(s):
+        for _ in range(8):
+            b.add_(1)
+cs, graph, run = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
+assert hip.hipStreamCreateWithFlags(ctypes.byref(cs), 1) == 0
+assert hip.hipStreamBeginCapture(cs, 0) == 0                            # hipStreamCaptureModeGlobal
+ecf8.ecf8_decode(blob.header, d_blob, y, stream=Stream(cs.value))
+bad = []
+
+def work(i):
+    s = streams[i % 8]
+    try:
+        if i % 2:
+            hdr, b = ecf8.ecf8_encode_gpu(x, 1, xs.size, d_blob=outs[i], stream=s)
+        else:
+            hdr, b = ecfw.ecfw_encode_gpu(ecfw.FMT_E5M2, x, 1, xs.size, d_blob=outs[i], stream=s)
+        outs[i] = b
+    except Exception as e:
+        bad.append((i, str(e)))
+
+threads = [threading.Thread(target=work, args=(i,)) for i in range(len(outs))]      # more calls at a time than pages are kept
+for t in threads:
+    t.start()
+for t in threads:
+    t.join()
+assert not bad, bad
+assert hip.hipStreamEndCapture(cs, ctypes.byref(graph)) == 0
+assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, 0) == 0
+for k in range(3):
+    y.fill_(0xA5)
+    torch.cuda.synchronize()
+    assert hip.hipGraphLaunch(run, cs) == 0 and hip.hipStreamSynchronize(cs) == 0
+    assert torch.equal(y, x), k
+for i, b in enumerate(outs):
+    assert np.array_equal(b.cpu().numpy(), (blob if i % 2 else wide).numpy()), i
+print("capture and calls whole")
+"""
+
+
+def test_first_calls_while_another_thread_captures():
+    """In a process of its own, where no call has left a page behind: calls of other threads get their pages while this one captures a stream in the mode
+    that forbids allocations in all threads, and the graph replays."""
+    r = subprocess.run([sys.executable, "-c", FIRST_CALL], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "capture and calls whole" in r.stdout, r.stdout + r.stderr
