@@ -432,3 +432,32 @@ def test_first_calls_while_another_thread_captures():
     that forbids allocations in all threads, and the graph replays."""
     r = subprocess.run([sys.executable, "-c", FIRST_CALL], cwd=ROOT, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "capture and calls whole" in r.stdout, r.stdout + r.stderr
+
+
+NO_PAGE = """
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)                     # in front of the runtime's own
+import numpy as np
+import torch
+from paper_2510_02676_amd import ecf8, ecfw
+xs = np.random.default_rng(8).integers(0, 256, 100_000, dtype=np.uint8)
+x = torch.from_numpy(xs).to("cuda:0")
+for k in range(3):
+    hdr, b = ecf8.ecf8_encode_gpu(x, 1, xs.size)
+    want = ecf8.ecf8_encode(xs, 1, xs.size)
+    assert bytes(hdr) == bytes(want.header) and np.array_equal(b.cpu().numpy(), want.numpy())
+    hdr, b = ecfw.ecfw_encode_gpu(ecfw.FMT_BF16, x.view(torch.int16), 1, xs.size // 2)
+    want = ecfw.ecfw_encode(ecfw.FMT_BF16, xs.view(np.uint16), 1, xs.size // 2)
+    assert bytes(hdr) == bytes(want.header) and np.array_equal(b.cpu().numpy(), want.numpy())
+    assert np.array_equal(ecf8.ecf8_decode(*ecf8.ecf8_encode_gpu(x, 1, xs.size)).cpu().numpy().reshape(-1), xs)
+assert ctypes.c_int.in_dll(shim, "refused").value >= 9
+print("copied instead")
+"""
+
+
+def test_no_pinned_page(tmp_path):
+    """Where the runtime refuses a page, the histogram is copied.  In a process of its own, whose first library answers for the runtime."""
+    (tmp_path / "shim.c").write_text("int refused; int hipHostMalloc(void **p, unsigned long n, unsigned flags) { *p = 0; refused++; return 2; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.c")], check=True, timeout=60)
+    r = subprocess.run([sys.executable, "-c", NO_PAGE, str(tmp_path / "shim.so")], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "copied instead" in r.stdout, r.stdout + r.stderr
