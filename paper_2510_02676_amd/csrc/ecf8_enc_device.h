@@ -202,6 +202,7 @@ __device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *ima
     auto first_chunk = [&](uint32_t t) { return (uint64_t)T * t + (uint64_t)ta.per_wave * wave; };
     bool fetched = false;                   // the tile's first chunk
     auto zero = [&](uint32_t dwords) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes have read what this one clears
         for (uint32_t u = lane; u * 4 < dwords; u += 64) *(u32x4 *)(image + 4 * u) = u32x4{0, 0, 0, 0};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
