@@ -663,6 +663,49 @@ def test_deals_of_chunks_to_waves(M):
         assert torch.equal(y, single[i]), (i, shapes[i])
 
 
+def _device_members(shapes, M, seed, scale_mode):
+    """Products with scales, made on the device: the fused ones and their twins on uncompressed weights."""
+    fused, raw = [], []
+    for i, (rows, K) in enumerate(shapes):
+        w = synth.make_weight(rows, K, 1.7, 0.02, seed, i, "block128", DEV)
+        g = torch.Generator(device=DEV)
+        g.manual_seed(seed * 1000 + i)
+        m = {"x": synth.activations(M, K, 10 * seed + i, DEV),
+             "w_scale": torch.exp(0.7 * torch.randn((rows + 127) // 128, K // 128, generator=g, device=DEV)),
+             "x_scale": torch.exp(0.5 * torch.randn((M,) if scale_mode == 1 else (M, K // 128), generator=g, device=DEV))}
+        hdr, blob = ecf8.ecf8_encode_gpu(w, lane_syms=64, tile_rows=16, table_mode=1 + i % 2)
+        fused.append(dict(m, hdr=hdr, blob=blob))
+        raw.append(dict(m, w=w))
+    return fused, raw
+
+
+@pytest.mark.parametrize("M", [4, 16, 24, 64])
+@pytest.mark.parametrize("scale_mode", [1, 2])
+def test_deals_of_chunks_to_waves_with_scales(scale_mode, M):
+    """The shapes of the test above with scales, one per row of X and one per row and 128 columns: one chunk of X in registers, two, none; one block per
+    workgroup and several.  Bit for bit the twins on uncompressed weights and, in a group, the single calls."""
+    shapes = [(16 * b, 256 * k) for k in (1, 3, 7, 8, 9, 15, 17, 28, 31, 32, 33, 57) for b in (1, 5)] + [(16 * 700, 256 * k) for k in (3, 9, 17, 28, 32, 33)]
+    fused, raw = _device_members(shapes, M, 41, scale_mode)
+    single = [_single_call(m) for m in fused]
+    for m, y, shape in zip(raw, single, shapes):
+        assert torch.equal(_single_call(m), y), shape
+    for y, want, shape in zip(ecf8.ecf8_gemm_fp8_grouped(ecf8.GemmGroup(fused)), single, shapes):
+        assert torch.equal(y, want), shape
+
+
+@pytest.mark.parametrize("M", [4, 16, 17, 32, 64])
+@pytest.mark.parametrize("scale_mode", [1, 2])
+def test_groups_of_many_blocks_with_scales(scale_mode, M):
+    """Matrices large enough that a workgroup has several blocks of rows of each, more than one batch of slots holds where there are two tiles of X or four;
+    shares of the sequence end inside matrices."""
+    shapes = [(7168, 2048)] * 3 + [(2048, 7168)] * 2 + [(14336, 2048)] * 3 + [(8192, 7168)]
+    fused, raw = _device_members(shapes, M, 43, scale_mode)
+    group, twin = ecf8.GemmGroup(fused), ecf8.GemmGroup(raw)
+    ys = ecf8.ecf8_gemm_fp8_grouped(group)
+    for m, y, want, shape in zip(fused, ys, ecf8.ecf8_gemm_fp8_grouped(twin), shapes):
+        assert torch.equal(y, want) and torch.equal(y, _single_call(m)), shape
+
+
 def test_grouped_gemm_argument_errors():
     shapes, Ms = GROUPS["mid_M"]
     fused = _group_members(shapes, Ms, seed=3)

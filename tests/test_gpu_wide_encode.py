@@ -3,6 +3,8 @@
 The CPU encoder's container is pinned to the oracle's on the CPU (tests/test_wide_host.py); here the device
 encoder must produce that same container byte for byte, and the oracle's reader must decode it to the input.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -202,3 +204,59 @@ def test_argument_errors():
         ecfw.ecfw_encode_gpu(BF16, y, max_code_len=5)
     assert e.value.code == ecf8.E_ARG
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("fmt", [BF16, E5M2])
+def test_histograms_of_calls_at_the_same_time(fmt):
+    """Eight threads, each on a stream of its own with a long copy queued before some calls and exponents of its own, so that counts of another call, of an
+    earlier one or not yet there (BF16: 256 of them, from four waves) would give another code: every call gets its own histogram."""
+    rng = np.random.default_rng(77)
+    xs = []
+    for i in range(8):
+        n = 50_000 + 8192 * i
+        e = np.clip(np.rint(rng.normal(3 + 3.5 * i if fmt == E5M2 else 20 + 28 * i, 1.0 + 0.4 * i, n)), 0, 31 if fmt == E5M2 else 255).astype(np.uint16)
+        xs.append(((e << 2) | rng.integers(0, 4, n, dtype=np.uint16)).astype(np.uint8) if fmt == E5M2 else (e << 7) | rng.integers(0, 128, n, dtype=np.uint16))
+    wants = [ecfw.ecfw_encode(fmt, x, 1, x.size) for x in xs]
+    big = torch.zeros(1 << 28, dtype=torch.uint8, device=DEV)
+    bad = []
+
+    def work(i):
+        s = torch.cuda.Stream()
+        d_x = _to_dev(fmt, xs[i])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            for k in range(12):
+                if k % 4 == i % 4:
+                    y = big.clone()
+                    y.add_(1)
+                hdr, d_blob = ecfw.ecfw_encode_gpu(fmt, d_x, 1, xs[i].size)
+                s.synchronize()
+                if bytes(hdr) != bytes(wants[i].header) or not np.array_equal(d_blob.cpu().numpy(), wants[i].numpy()):
+                    bad.append((i, k))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+
+
+@pytest.mark.parametrize("fmt", [BF16, E5M2])
+def test_refused_while_the_stream_is_captured(fmt):
+    x = _rand_elems(fmt, 100_000, 5)
+    want = ecfw.ecfw_encode(fmt, x, 1, x.size)
+    d_x, out = _to_dev(fmt, x), torch.empty(1 << 19, dtype=torch.uint8, device=DEV)
+    z = torch.zeros(4, device=DEV)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        z.add_(1)
+        with pytest.raises(ecf8.Ecf8Error) as e:
+            ecfw.ecfw_encode_gpu(fmt, d_x, 1, x.size, d_blob=out)
+    assert e.value.code == ecf8.E_HIP
+    for k in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((z == k + 1).all())
+    hdr, blob = ecfw.ecfw_encode_gpu(fmt, d_x, 1, x.size, d_blob=out)
+    assert np.array_equal(blob.cpu().numpy(), want.numpy())
