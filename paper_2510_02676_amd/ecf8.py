@@ -18,6 +18,7 @@ if not os.path.exists(LIB_PATH):
     raise ImportError("libecf8.so is not built: run `python -m paper_2510_02676_amd.build` "
                       "(or __graft_entry__.build()) first; there is no fallback path")
 _lib = ctypes.CDLL(LIB_PATH)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 OK, E_ARG, E_FORMAT, E_CAPACITY, E_ALIGN, E_HIP, E_NOMEM = 0, -1, -2, -3, -4, -5, -6
 
@@ -260,8 +261,11 @@ def blob_stats(hdr):
 
 def _stream_ptr(stream):
     if stream is None:
-        # the handle of torch.cuda.current_stream() without the object around it, which takes 2.7 us of a call's 7.4
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        # the handle of torch.cuda.current_stream() without the object around it, which takes 2.7 us of a call's 7.4; the name is not one that
+        # PyTorch promises to keep
+        if _raw_stream is not None:
+            return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
 
 

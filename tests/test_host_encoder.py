@@ -385,3 +385,20 @@ def test_split_k_plan_is_pure_host_logic():
         with pytest.raises(ecf8.Ecf8Error) as e:
             ecf8.gemm_splitk_plan(*bad, 256)
         assert e.value.code == ecf8.E_ARG
+
+
+def test_current_stream_with_and_without_the_short_way(monkeypatch):
+    """The binding takes the current stream's handle from a function of PyTorch's that it may do without."""
+    import torch
+
+    class Current:
+        cuda_stream = 0x2222
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(ecf8, "_raw_stream", lambda device: 0x1110 + device)
+    assert ecf8._stream_ptr(None).value == 0x1113
+    monkeypatch.setattr(ecf8, "_raw_stream", None)
+    assert ecf8._stream_ptr(None).value == 0x2222
+    Current.cuda_stream = 0x3333
+    assert ecf8._stream_ptr(Current).value == 0x3333
