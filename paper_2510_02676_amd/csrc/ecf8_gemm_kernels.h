@@ -410,22 +410,20 @@ __device__ __forceinline__ void reduce_split(f32x4 *red, uint32_t *s_flag, const
     if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// What of a chunk is needed before its bits: where it starts and ends in the stream and the bits of this lane.
-// ONE: fetched in one instruction of four bytes a lane, lanes 0 .. 31 the lanes' bits, two each, lanes 32 .. 35 the two positions (the others those
-// again); as two they are loads of 2 and 16 bytes a lane, the latter the same for all.
+// What of a chunk is needed before its bits: where it starts in the stream and the bits of this lane.
+// ONE: fetched in one instruction of four bytes a lane, lanes 0 .. 31 the lanes' bits, two each, lanes 32 and 33 the position (the others that
+// again); as two they are loads of 2 and 8 bytes a lane, the latter the same for all.
 template <bool ONE>
 struct ChunkMeta {
-    uint64_t b0 = 0, b1 = 0;
+    uint64_t b0 = 0;
     uint32_t lb = 0;                        // ONE: as fetched
-    __device__ __forceinline__ uint64_t begin() const { return ONE ? pair(32) : uniform64(b0); }
-    __device__ __forceinline__ uint64_t end() const { return ONE ? pair(34) : uniform64(b1); }
+    __device__ __forceinline__ uint64_t begin() const
+    {
+        return ONE ? (uint32_t)__builtin_amdgcn_readlane((int)lb, 32) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lb, 33) << 32 : uniform64(b0);
+    }
     __device__ __forceinline__ uint32_t lane_bits(int lane) const
     {
         return ONE ? ((uint32_t)__builtin_amdgcn_ds_bpermute((lane >> 1) * 4, (int)lb) >> (16 * (lane & 1))) & 0xffffu : lb;
-    }
-    __device__ __forceinline__ uint64_t pair(int l) const
-    {
-        return (uint32_t)__builtin_amdgcn_readlane((int)lb, l) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lb, l + 1) << 32;
     }
 };
 template <bool ONE>
@@ -435,7 +433,7 @@ struct MetaReader {
     __device__ __forceinline__ MetaReader(const GArgs &a, int lane_)
     {
         lane = (uint32_t)lane_;
-        at = a.d_blob + (!ONE ? a.off_cb : lane < 32 ? a.off_lb + 4 * lane : a.off_cb + 4 * (lane & 3));
+        at = a.d_blob + (!ONE ? a.off_cb : lane < 32 ? a.off_lb + 4 * lane : a.off_cb + 4 * (lane & 1));
         off_lb = a.d_blob + a.off_lb;
         step = lane < 32 ? 128u : 8u;
     }
@@ -446,7 +444,6 @@ struct MetaReader {
             m.lb = *(const GLOBAL uint32_t *)(at + (uint64_t)(uint32_t)c * step);           // a chunk's number is below 2^32
         } else {
             m.b0 = ((const GLOBAL uint64_t *)at)[c];
-            m.b1 = ((const GLOBAL uint64_t *)at)[c + 1];
             m.lb = ((const GLOBAL uint16_t *)off_lb)[c * 64 + lane];
         }
         return m;

@@ -330,11 +330,12 @@ def test_any_k_against_oracle(orc, rows, K, M):
 
 
 @pytest.mark.parametrize("rows,K", [(256, 3328), (256, 13824), (256, 14336), (8176, 3584), (8192, 3328), (8192, 3584), (8192, 4096), (8192, 4352), (8192, 7936),
-                                    (8192, 8192)])
+                                    (8192, 8192), (8208, 3328), (8208, 3584), (12304, 2048), (16384, 1024), (16400, 1024), (28688, 768), (32784, 512), (65552, 256)])
 def test_four_tiles_of_x_with_group_scales(orc, rows, K):
-    """M > 32 with a scale per row and 128 columns of X, on either side of the sizes where the kernel with pinned lookups takes
-    over: 56 chunks of a block, and with two blocks per workgroup 14 to 16 or 32.  Bit for bit the twin on uncompressed weights; sampled
-    outputs against the oracle."""
+    """M > 32 with a scale per row and 128 columns of X, on either side of the batches in which the any-K kernel adds up its waves' sums.  There are 23
+    slots, as many of them for a block of rows as it has chunks, 8 at the most: 2 blocks from 8 chunks on, 4 at 4, 7 at 3, 8 and 16 (rounded down to
+    whole rounds of the waves) at 2 and 1.  A workgroup has one block per 4096 rows.  Bit for bit the twin on uncompressed weights;
+    sampled outputs against the oracle."""
     M = 41
     w = synth.make_weight(rows, K, 1.7, 0.02, 12, device=DEV)
     x = synth.activations(M, K, seed=rows + K, device=DEV)
