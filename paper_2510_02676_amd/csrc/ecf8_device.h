@@ -329,7 +329,7 @@ __device__ __forceinline__ void quad_step2(const uint8_t *smem, const uint16_t *
 }
 
 // The two runs of a lane with their windows held in registers: the two dwords of the LDS image that a window is made of, per
-// run.  A step moves a run by at most 28 bits, so by at most one dword; the dword it may move into is fetched inside
+// run.  A step moves a run by at most 28 bits (30 in the wide decoder's E5M2 kernel), so by at most one dword; the dword it may move into is fetched inside
 // the step, behind the first two table lookups and in their shadow, so that a step has two LDS round trips on
 // its critical path, the lookups.  Positions are kept one bit off as in quad_step2, the backward run's another 32 bits
 // down, so that the address of its window's dwords is also that of the dword below them.

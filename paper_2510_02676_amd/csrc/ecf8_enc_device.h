@@ -122,7 +122,7 @@ __device__ __forceinline__ uint64_t tile_begin(GLOBAL uint64_t *cb, uint32_t T, 
                 again = true;                                   // from this window on
                 break;
             }
-            const uint32_t sum = wave_incl_scan((uint32_t)lane < f ? (uint32_t)(said[k] >> 32) & 0x3fffffffu : 0u);      // at most 64 x 2^25, see tile_chunks
+            const uint32_t sum = wave_incl_scan((uint32_t)lane < f ? (uint32_t)(said[k] >> 32) & 0x3fffffffu : 0u);      // at most 64 x 2^25: a tile is 16 waves of 16 chunks of 2^17 bits at the most
             between += (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
             if (f < 64)
                 return between + ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(at[k] >> 32), (int)f) << 32 |

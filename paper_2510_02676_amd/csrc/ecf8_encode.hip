@@ -293,10 +293,10 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M weights (14336 x 4096): 28 us for the 111 MB read and written (30 with two pairs looked up again for every put),
-// 17 of them bound by vector operations, the others the first loads, the exchange and the copy to the stream, when the compute unit waits;
-// metadata and planes, prefix sum and packing as kernels of their own took 40, and read the weights twice.  The whole call 67.7 -> 56.4 us (53.0 since the
-// histogram is mailed), 16384 x 16384 242 -> 190.
+// The container behind the code.  58.7 M weights (14336 x 4096): 30 us in a kernel trace (the last 100 of 300 calls) for the 111 MB read and written,
+// some 17 of them bound by vector operations, the others the first loads, the exchange and the copy to the stream, when the compute unit waits.  With two
+// pairs looked up again for every put it took 2 more; metadata and planes, prefix sum and packing as kernels of their own 10 to 12 more, and
+// they read the weights twice.  The whole call 67.7 -> 56.4 us (53.0 since the histogram is mailed), 16384 x 16384 242 -> 190.
 template <int N, bool CAP7>
 __global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, ecf8_header h, uint32_t per_wave)
 {

@@ -23,11 +23,12 @@
 // ahead and the metadata two ahead.  Per block the waves' partial sums meet in
 // LDS (double buffered, one barrier per block) and 16 x M outputs are written.
 // The kernels need capped codes (no codeword over TB/2 bits: every pair is one
-// table hit, and a chunk's span always fits its stage), so they have no second
-// level and no fallback path.
+// table hit, and a lane's run always fits the dwords fetched for it), so they have
+// no second level and no fallback path.
 //
 // In this file: the K = 4096 kernels (X resident in registers) and their twins on
-// uncompressed W; the any-K kernels (X fetched chunk by chunk; at short K the waves
+// uncompressed W; the any-K kernels (up to 16 rows of X kept in registers where K is
+// short enough, else X fetched chunk by chunk and turned in LDS; at short K the waves
 // form groups with a block of rows each); scales per 128 x 128 block of W and per
 // row or 1 x 128 group of X (ChunkSums); split K for matrices of few rows
 // (reduce_split: partial sums and arrival counters in a caller-provided workspace);

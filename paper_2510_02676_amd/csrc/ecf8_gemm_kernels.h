@@ -706,12 +706,11 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_raw_kernel(GArgs a)
 }
 
 // ---- any K (a multiple of 256) ----
-// The kernels above keep the wave's slice of X in registers, which is what makes K = 4096 fast
-// and what ties them to it.  These take any K: the K / 256 chunks of a block of rows are dealt
-// round-robin to the NW waves (some waves get one chunk fewer; where a block has at most NW / 2
-// chunks the waves split into groups with a block each, see Deal), and
-// the A operands of a chunk are fetched from X (L2-resident: M x K bytes) one chunk ahead, like
-// the chunk's payload.  Same decode, same MFMA order inside a chunk, same reduction.
+// The kernels above keep the wave's slice of X in registers, which ties them to K = 4096.  These take any K: the K / 256
+// chunks of a workgroup's blocks of rows are dealt to its NW waves.  With one tile of X and at most 2 NW chunks per block
+// (see resident_chunks) a wave keeps the X of its one or two chunks in registers too, and where a block has at most NW / 2 chunks the
+// waves form groups with a block each; else X (L2-resident: M x K bytes) is fetched for every chunk, one chunk ahead, like the
+// chunk's payload.  Same decode, same MFMA order inside a chunk, and sums added in the same order.
 
 // The table's set-up out of line (APART), for the kernels that walk over several matrices: inlined there, its registers
 // cost the decode loop spills (eight experts 113.8 us inlined, 109.6 called; kernels of one matrix have the registers and
@@ -790,9 +789,11 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 //    eighth), which costs little beside the others' work.
 //  * KRES = 0: the units' chunks form one sequence, and wave w takes every NW-th of it from the w-th on, across the units'
 //    borders; batches are rounded down to whole rounds of the waves.
-// What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.8 us), the blobs' bytes at 4.2 TB/s, with LDS and vector
-// operations busy for 60 to 70 %; six of them, which the memory-side cache holds, 55.3.  M = 64 (215 us): two waves on a
-// SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and first-level cache busy 55 % each).
+// What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.8 us), the compute unit: six of them, which the memory-side
+// cache holds, take as long for a chunk (55.3 us, 462 clocks a chunk and compute unit against 472), and no unit of it is busy all of the time: vector
+// operations 67 %, LDS 61 % (72 % of that bank conflicts of the table), first-level cache 59 %, address units 55 %; a wave waits for 55 % of its life.
+// M = 64 (215 us): two waves on a SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and
+// first-level cache busy 55 % each).
 template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
                                           uint32_t my_units)
@@ -1179,6 +1180,10 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
         if (b0 < b1) {
             if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
             else {
+                // One tile of X that is fetched chunk by chunk (K > 8192, or one block) is fetched as operands, whatever its rows: one walk serves all M <= 16,
+                // and with scales of W the turned one is mostly the slower one.  Operands / turned, us, M = 1 / 9 / 16: three 4096 x 14336 37.3 / 40.6 / 46.4, 40.0 / 41.1 / 42.4, scaled
+                // 39.1 / 41.4 / 47.5, 45.2 / 47.6 / 48.9; two 1024 x 9216 12.1 / 12.8 / 14.0, 12.7 / 12.9 / 13.1, scaled 12.4 / 13.0 / 14.4, 15.3 / 15.9 / 16.3; two
+                // 14336 x 9216 48.7 / 52.7 / 68.7, 53.4 / 55.0 / 57.3, scaled 49.9 / 58.8 / 69.8, 58.4 / 61.1 / 63.1.
                 const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW, 0>(kchunks, n);
                 if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
                 else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
@@ -1270,16 +1275,17 @@ inline int scale_args(const float *d_w_scale, const float *d_x_scale, uint32_t x
 }
 
 // 16 waves (one K chunk of the block each) while X fits their registers, 8 waves of two chunks
-// at M > 32.  (16 x 512 chunks with 8 waves were measured too: slower, 37.7 us against 25.5.)
+// at M > 32.
 template <int SCALED, int ACC = 0>
 int launch_fused(const GArgs &a, void *stream)
 {
     const int grid = grid_for(a.rows / BLOCK_ROWS);
     if (grid <= 0) return ECF8_E_HIP;
     hipStream_t s = (hipStream_t)stream;
-    // any K: X does not stay in registers, fetched chunk by chunk.  Also with a scale per row and 128 columns of X
-    // at M > 32: beside four tiles of X in registers the scales do not fit (93 us against 83 at M = 64)
-    // ... and on the F16 matrix cores at M > 16, where X in registers and the converted operands do not fit together
+    // The any-K kernels also take K = 4096 where X does not fit the registers beside the rest: with a scale per row and 128 columns of X at M > 32,
+    // and on the F16 matrix cores, whose operands are converted, at M > 16.  Resident X / any K, us, rows 4096, 14336 and 28672: group scales M = 33 30.9 / 11.7,
+    // 69.6 / 35.2, 111 / 57.9, M = 64 37.5 / 13.2, 90.7 / 39.1, 146 / 64.5; F16 cores M = 33 27.2 / 11.1, 59.6 / 32.4, 95.0 / 53.7, M = 64 30.6 / 12.2, 63.4 / 34.0, 99.4 / 56.1.
+    // F16 cores at M = 17 .. 32 go with those, though there X does fit and many rows would be faster for it: M = 32 10.7 / 9.0, 20.4 / 25.0, 29.6 / 41.0.
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
         const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
         if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
@@ -1288,7 +1294,7 @@ int launch_fused(const GArgs &a, void *stream)
         // 14.1 / 14.7 / 15.4 / 16.2 / 16.8, 15.3 / 15.5 / 15.4 / 15.4 / 15.4; 14336 x 9216 29.7 / 29.9 / 31.3 / 33.0 / 35.4, 32.4 for all
         else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // X pieces of two chunks: 8 waves' worth of registers
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // two tiles of X in 16 waves spill: up to twice the time
         else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
         return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
     }
@@ -1326,7 +1332,10 @@ int launch_raw(const GArgs &a, void *stream)
 constexpr uint64_t CTR_BYTES = 4096;
 
 // Split K.  Workgroups that share a block of rows: the largest divisor of the K / 256 chunks that
-// still gives every workgroup a compute unit of its own (1 = the matrix has blocks enough).
+// still gives every workgroup a compute unit of its own (1 = the matrix has blocks enough).  It goes by the matrix
+// alone, since the workspace and the plan do; the hand-over costs some 2 us, so that it pays for long K or many rows of X.
+// Plain call / split, us, M = 1 / 16 / 64: 256 x 14336 (14 slices) 13.0 / 14.5 / 23.9, 12.8 / 13.0 / 17.5; 576 x 7168 (7) 9.0 / 9.7 / 14.3, 11.1 / 11.6 / 14.0;
+// 1536 x 7168 (2) 9.0 / 9.9 / 14.5, 10.9 / 11.1 / 14.5; 1024 x 4096 (4) 7.1 / 8.2 / 13.5, 10.1 / 10.2 / 12.5.
 inline uint32_t pick_slices(uint64_t rows, uint64_t cols, int cus)
 {
     const uint64_t n_blocks = rows / BLOCK_ROWS, kchunks = cols / 256;
@@ -1369,6 +1378,8 @@ int launch_split(const GArgs &a, void *stream)
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
         else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
     } else {
+        // X turned at any M.  Turned / as operands, us, M = 1 / 8 / 16: 2048 x 7168 11.4 / 11.5 / 11.7, 11.3 / 11.9 / 12.4; 1024 x 16384 12.3 / 12.4 / 12.7, 12.2 / 13.0 / 13.6;
+        // 256 x 4096, a chunk a workgroup, 16.0 / 16.1 / 16.1, 15.7 / 15.8 / 15.8
         if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, true>), dim3(grid), dim3(16 * 64), 0, s, a);
         else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
         else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);

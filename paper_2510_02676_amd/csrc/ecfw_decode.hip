@@ -1005,7 +1005,8 @@ int launch_fmt(const BArgs &a, uint32_t N, bool fast, uint32_t max_workgroups, h
     // Waves per workgroup and bursts, measured on a layer of seven matrices (218 M elements):
     //   BF16, N = 64   8 waves, a chunk's pieces in one burst 139.0 us; 10 waves 139.6, 12 waves 140.6, 6 waves 150.7; in two
     //                  bursts 8 waves 144.8, 12 waves 145, 16 waves 149
-    //   E5M2, N = 128  12 waves, two bursts 90.0 us (before windows were held in registers; 86.2 since); 12 waves, one burst 94.4; 16 waves, two 95.9; 8 waves, one 100.9
+    //   E5M2, N = 128  12 waves, two bursts 84.8 us; 12 waves, one burst 94.2; 16 waves, two 99.4; 10 waves, two 88.7; 8 waves, one 92.2, two 92.4.  The same order
+    //                  for one matrix of 1024 x 1024 (12.9, 15.7, 17.1, 13.6, 13.5, 13.4) up to eight of 14336 x 4096 (160.9, 166.0, 177.1, 161.1, 169.7, 169.7)
     // i.e. BF16 is at the memory wall and wants its stores together, E5M2 wants the waves to hide its look-ups.
     if constexpr (FMT == ECFW_FMT_BF16) {
         const uint64_t wgs = workgroups(a, max_workgroups), each = wgs ? (a.total_chunks + wgs - 1) / wgs : 0;

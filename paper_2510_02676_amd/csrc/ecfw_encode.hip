@@ -156,8 +156,8 @@ __device__ __forceinline__ void write_fixed(const WEncArgs &a, const WCodeArgs &
 //    bit 27 on their length in one dword, so that joining two of them is one operation.
 //  * QUADS (up to 12 bits): count joins four codewords and leaves them in the place of their elements, for pack to put them in one go.
 //    They are nearly always less than 32 bits; a chunk where they are not is fetched again and packed two codewords at a time.
-// What bounds it: BF16, with 38 us in the kernel for 14336 x 4096, a copy's rate; E5M2 the vector operations (45 us looked up element by element in
-// count and again in pack, 40 now; BF16 40 and 39).
+// What bounds it: BF16, at 4.7 TB/s, nearly a copy's rate; E5M2 the vector operations (with elements looked up one by one in count and again in
+// pack the kernel took 5 us more for 14336 x 4096, BF16's 1).
 template <int FMT, int N, int LMAX>
 struct Chunk {
     using F = EFmt<FMT>;
@@ -362,8 +362,9 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M elements (14336 x 4096): BF16 39 us for the 198 MB read and written, E5M2 40 for 101 MB (62 and 57 with metadata and
-// planes, prefix sum and packing as kernels of their own).  The whole call 108 -> 84 us and 85 -> 64, 16384 x 16384 454 -> 310 and 250 -> 204.
+// The container behind the code.  58.7 M elements (14336 x 4096): in a kernel trace (the last 100 of 300 calls) BF16 42 us for the 198 MB read and
+// written, E5M2 35 for 101 MB (some 20 more with metadata and planes, prefix sum and packing as kernels of their own).  The whole call 108 -> 84 us and
+// 85 -> 64, 16384 x 16384 454 -> 310 and 250 -> 207.
 template <int FMT, int N, int LMAX>
 __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeArgs ca, uint32_t per_wave)
 {
