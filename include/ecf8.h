@@ -183,7 +183,8 @@ uint64_t ecf8_blob_size(const ecf8_blob *blob);
  * histogram to build the code on the host), then queues the rest
  * asynchronously.  Uses no device memory besides its input and output, and a
  * page of pinned host memory that later calls use again.  A stream that is
- * being captured -> ECF8_E_HIP.
+ * being captured, or the null stream while one that waits for it is -> ECF8_E_HIP;
+ * captures of other threads are left alone.
  */
 int ecf8_encode_bound(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, uint64_t *bytes);
 int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts,

@@ -136,8 +136,9 @@ int ecfw_encode(const void *elems_host, uint64_t rows, uint64_t cols, const ecfw
  * than blob_capacity.  *hdr_out receives the header.  The call waits for `stream`
  * ONCE (it needs the histogram to build the code on the host), then queues the rest
  * asynchronously.  Uses no device memory besides its input and output, and a page of
- * pinned host memory that later calls use again.  A stream that is being captured ->
- * ECF8_E_HIP.
+ * pinned host memory that later calls use again.  A stream that is being captured, or
+ * the null stream while one that waits for it is -> ECF8_E_HIP; captures of other threads
+ * are left alone.
  */
 int ecfw_encode_bound(uint64_t rows, uint64_t cols, const ecfw_encode_opts *opts, uint64_t *bytes);
 int ecfw_encode_gpu(const void *d_elems, uint64_t rows, uint64_t cols, const ecfw_encode_opts *opts,

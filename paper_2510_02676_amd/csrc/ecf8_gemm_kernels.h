@@ -307,7 +307,7 @@ __device__ __forceinline__ void reduce_batch(const f32x4 *red, const GArgs &a, u
     }
 }
 
-// How the NW waves of a workgroup share the work of a unit in the any-K kernels.  Long K: a unit is one
+// How the NW waves of a workgroup share the work of a unit in the any-K kernels on uncompressed W.  Long K: a unit is one
 // block of rows and its chunks are dealt round-robin to all waves.  Short K (at most NW / 2 chunks per
 // block): the waves form `groups` groups of `wpb`, and each group takes a block of rows of its own --
 // blocks j, j + 1, ... of the workgroup's sequence -- so that no wave is left without work (at K = 2048,
