@@ -17,8 +17,8 @@
  * the CALLER owns (e.g. a PyTorch tensor's data_ptr()).  The library keeps no
  * device memory of its own and never allocates or frees device memory; the
  * decode calls never synchronise the device and use no global atomics (the
- * device encoder reads its histogram back once and uses atomics on its own
- * output; the split-K GEMM calls use them on the counters in their workspace).  `stream` arguments are
+ * device encoder waits once, for the blob's header; the split-K GEMM calls use
+ * atomics on the counters in their workspace).  `stream` arguments are
  * a hipStream_t passed as void* (NULL = the default stream).
  *
  * All functions return ECF8_OK (0) or a negative ECF8_E_* code; nothing throws
@@ -179,8 +179,8 @@ uint64_t ecf8_blob_size(const ecf8_blob *blob);
  * and options (n_threads is ignored).  ecf8_encode_bound gives a capacity that
  * always suffices; ECF8_E_CAPACITY if the blob turns out larger than
  * blob_capacity (at least 256 bytes are needed in any case).  *hdr_out receives
- * the header.  The call waits for `stream` ONCE (it needs the 16-bin
- * histogram to build the code on the host), then queues the rest
+ * the header.  The call queues all its work and then waits ONCE, until the
+ * header is known (histogram and code, both made on the device); the rest runs
  * asynchronously.  Uses no device memory besides its input and output, and a
  * page of pinned host memory that later calls use again.  A stream that is
  * being captured, or the null stream while one that waits for it is -> ECF8_E_HIP;

@@ -133,9 +133,9 @@ int ecfw_encode(const void *elems_host, uint64_t rows, uint64_t cols, const ecfw
  * 256-byte aligned, that receives the container -- byte for byte the one ecfw_encode
  * writes for the same input and options (n_threads is ignored).  ecfw_encode_bound
  * gives a capacity that always suffices; ECF8_E_CAPACITY if the blob turns out larger
- * than blob_capacity.  *hdr_out receives the header.  The call waits for `stream`
- * ONCE (it needs the histogram to build the code on the host), then queues the rest
- * asynchronously.  Uses no device memory besides its input and output, and a page of
+ * than blob_capacity.  *hdr_out receives the header.  The call queues all its work and
+ * then waits ONCE, until the header is known (histogram and code, both made on the
+ * device); the rest runs asynchronously.  Uses no device memory besides its input and output, and a page of
  * pinned host memory that later calls use again.  A stream that is being captured, or
  * the null stream while one that waits for it is -> ECF8_E_HIP; captures of other threads
  * are left alone.

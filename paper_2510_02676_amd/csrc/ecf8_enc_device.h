@@ -10,20 +10,6 @@
 
 namespace {
 
-// The workgroups' shares of chunk_bit[] are zeroed by the histogram kernels, which run before anything reads them.
-__device__ __forceinline__ void zero_chunk_bits(uint64_t chunk_bit, uint64_t n_chunks, uint32_t tid, uint32_t threads)
-{
-    for (uint64_t i = (uint64_t)blockIdx.x * threads + tid; i <= n_chunks; i += (uint64_t)gridDim.x * threads) ((GLOBAL uint64_t *)chunk_bit)[i] = 0;
-}
-
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint64_t dst, uint64_t bytes)   // bytes % 16 == 0
-{
-    GLOBAL u32x4 *p = (GLOBAL u32x4 *)dst;
-    const uint64_t n16 = bytes / 16;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = u32x4{0, 0, 0, 0};
-}
-
 // Where chunk c's pieces lie: piece q of lane l starts at element base + q * stride + lane_off(l) (see the container's layouts).
 struct ChunkPlace {
     uint64_t base, stride, lane_off;
@@ -46,351 +32,578 @@ __device__ __forceinline__ u32x4 load_cut(const GLOBAL uint8_t *x, uint64_t e, u
     return u32x4{w[0], w[1], w[2], w[3]};
 }
 
-// A lane's string of bits on its way into the wave's image in LDS (zeroed before): whole dwords are ORed in as they fill.
+// A lane's string of bits on its way into the wave's image in LDS (zeroed before): whole dwords are ORed in as they fill.  `acc` holds the last 32 bits, the latest on
+// top, so that a put is one funnel shift, and what a word has above its bits falls off.  ANY: puts of 32 bits occur.
+template <bool ANY>
 struct LanePacker {
     uint32_t *d;
-    uint32_t fill, acc = 0;
+    uint32_t fill, acc = 0;                 // fill: bits of the dword that is being filled, 0 .. 31
 
     __device__ __forceinline__ LanePacker(uint32_t *image, uint32_t at) : d(image + (at >> 5)), fill(at & 31) {}
-    __device__ __forceinline__ void put(uint32_t bits, uint32_t nb)          // nb <= 32, bits above nb clear
+    __device__ __forceinline__ void put(uint32_t bits, uint32_t nb)          // nb <= 31, or 32 with ANY
     {
-        const uint64_t t = (uint64_t)bits << fill;              // (two 32-bit shifts measured slower: a BF16 matrix 80 -> 83 us)
-        acc |= (uint32_t)t;
+        const uint32_t before = fill, old = acc;
         fill += nb;
+        acc = __builtin_amdgcn_alignbit(bits, old, nb);
+        if (ANY) acc = nb == 32 ? bits : acc;
         if (fill >= 32) {
-            __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            const uint32_t full = __builtin_amdgcn_alignbit(bits, old, 0u - before);
+            __hip_atomic_fetch_or(d, ANY && before == 0 ? bits : full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             d++;
             fill -= 32;
-            acc = (uint32_t)(t >> 32);
         }
     }
     __device__ __forceinline__ void finish()
     {
-        if (fill) __hip_atomic_fetch_or(d, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        if (fill) __hip_atomic_fetch_or(d, acc >> (32 - fill), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
-    __device__ __forceinline__ uint32_t end(const uint32_t *image) const { return (uint32_t)(d - image) * 32 + fill; }     // the bit behind the last one
 };
 
-// ---- the container behind the code: one pass over the weights ----
-// A wave takes a few chunks in a row, a workgroup as many times its waves, a tile.  Chunk by chunk the wave counts the code bits,
-// writes the planes and packs the bits into its image in LDS, one chunk behind the other; where they go is only known when
-// everything before them has been counted.  That the workgroups find out from one another, once per tile, and then copy the
-// images to the stream, shifted into place.  Chunks that did not fit any more are packed after that.  Tiles are drawn from a counter, so that a workgroup waits only for tiles
-// that were drawn before its own; these wait for earlier ones only, so every wait ends whatever part of the grid is running.
-//
-// The exchange goes through chunk_bit[], which the histogram kernel has zeroed.  Of the entries of tile t, which has T chunks,
-//   [T t]      holds the tile's first bit once the tile before has written it, plain and for good (it is not 0: a chunk has a bit
-//              per weight at least, and tile 0's entry is not read);
-//   [T t + 1]  holds what the tile before has to say, until tile t replaces it by its plain value: SAID_TOTAL and its length from bit 32
-//              on as soon as the code bits of its chunks are counted, SAID_TAIL and its last 32 bits once they are packed.
-//              An entry that has been replaced reads as not said; then the first bit of tile t + 1 is on its way, and is what ends the wait.
-// What bounds it: the exchange costs a tile 3 to 5 us, round trips through the memory side and waiting for the slowest wave, and the compute unit
-// has nothing else to do meanwhile; hence tiles as large as the LDS holds, and one per compute unit where that is enough.
-// 58.7 M E4M3 weights: tiles of eight chunks, two workgroups per compute unit, 52 us; of 16 chunks 42; of 32, one per compute unit, 32.
-constexpr uint64_t SAID_TOTAL = 1ull << 63, SAID_TAIL = 1ull << 62;
-constexpr int LATE_DWORDS = 20;             // end of an image: the last 32 codewords of a lane of a chunk that does not fit into the rest
-constexpr int LATE_LANES = 32;              // a chunk of more bits than an image takes goes out by so many lanes at a time, whose bits fit whatever they are
+// Sums over lanes: of a half wave and the other, of a row of 16 and its neighbour (the result in both; of two values at once, a's in the lower half or the even
+// rows and b's in the others), and over 4, 8 and 16 lanes in a row.
+__device__ __forceinline__ uint32_t add_32(uint32_t a, uint32_t b) { const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false); return r[0] + r[1]; }
+__device__ __forceinline__ uint32_t add_16(uint32_t a, uint32_t b) { const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false); return r[0] + r[1]; }
+template <int DPP> __device__ __forceinline__ uint32_t add_dpp(uint32_t v) { return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP, 0xf, 0xf, true); }
+__device__ __forceinline__ uint32_t add_quad(uint32_t v) { return add_dpp<0x4e>(add_dpp<0xb1>(v)); }       // quad_perm [1 0 3 2], [2 3 0 1]
+__device__ __forceinline__ uint32_t add_eight(uint32_t v) { return add_dpp<0x141>(add_quad(v)); }           // row_half_mirror
+__device__ __forceinline__ uint32_t add_row(uint32_t v) { return add_dpp<0x140>(add_eight(v)); }            // row_mirror
 
-__device__ __forceinline__ uint64_t agent_load(GLOBAL uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void agent_store(GLOBAL uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// One wave: the first bit of tile t, by adding up what the tiles before have said back to the nearest one whose first bit is known.
-// WINDOWS x 64 tiles are asked for at a time, about as many as there are workgroups on the chip.
-__device__ __forceinline__ uint64_t tile_begin(GLOBAL uint64_t *cb, uint32_t T, uint32_t t, int lane)
+// Counters of every lane, added up over the wave into A counters in LDS: two at a time in the wave's halves, then in its rows.
+template <int A>
+__device__ __forceinline__ void add_counts(const uint32_t (&cnt)[A], uint32_t *sums, int lane)
 {
-    constexpr int WINDOWS = 4;
-    uint64_t between = 0;
-    for (uint32_t s0 = t;;) {
-        uint64_t at[WINDOWS], said[WINDOWS];                    // of tile s0 - 64 k - lane
+    uint32_t mine = 0;
 #pragma unroll
-        for (int k = 0; k < WINDOWS; k++) {
-            at[k] = said[k] = 0;
-            if ((uint32_t)lane + 64 * k < s0) {
-                GLOBAL uint64_t *e = cb + (uint64_t)T * (s0 - 64 * k - lane);
-                at[k] = agent_load(e);
-                said[k] = agent_load(e + 1);
-            }
-        }
-        bool again = false;
-#pragma unroll
-        for (int k = 0; k < WINDOWS; k++) {
-            if (again) break;
-            const uint64_t known = __ballot((uint32_t)lane >= s0 || at[k] != 0), there = __ballot(said[k] >> 63);
-            const uint32_t f = known ? (uint32_t)__builtin_ctzll(known) : 64u;
-            const uint64_t need = f < 64 ? (1ull << f) - 1 : ~0ull;
-            if ((there & need) != need) {
-                again = true;                                   // from this window on
-                break;
-            }
-            const uint32_t sum = wave_incl_scan((uint32_t)lane < f ? (uint32_t)(said[k] >> 32) & 0x3fffffffu : 0u);      // at most 64 x 2^25: a tile is 16 waves of 16 chunks of 2^17 bits at the most
-            between += (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
-            if (f < 64)
-                return between + ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(at[k] >> 32), (int)f) << 32 |
-                                  (uint32_t)__builtin_amdgcn_readlane((int)at[k], (int)f));
-            s0 -= 64;
-        }
-        if (again) __builtin_amdgcn_s_sleep(1);
+    for (int i = 0; i < A / 4; i++) {
+        const uint32_t v = add_row(add_16(add_32(cnt[4 * i], cnt[4 * i + 1]), add_32(cnt[4 * i + 2], cnt[4 * i + 3])));
+        mine = (lane & 15) == i ? v : mine;
     }
+    if ((lane & 15) < A / 4 && mine) atomicAdd(&sums[4 * (lane & 15) + (lane >> 5) + (lane >> 4 & 1) * 2], mine);
 }
 
-// What the waves of a workgroup tell one another about the tile they are at, in two buffers used in turn.
-constexpr int WMAX = 16;                    // waves of a workgroup at the most
-struct TileShared {
-    uint64_t begin;
-    uint64_t counted[2];                    // code bits of the waves that have counted theirs, from bit 40 on how many have
-    uint32_t drawn[2];                      // the tile after it
-    uint32_t total[2][WMAX], tail[2][WMAX]; // bits of a wave's chunks, the last 32 of them
+// A chunk's last 32 bits from its last 32 codewords, in lanes 0 .. 31 from the end on: a codeword as a number, its first bit highest in a backward run
+// and lowest in a forward one, and its length.
+__device__ __forceinline__ uint32_t last_bits(uint32_t code, uint32_t len, int lane)
+{
+    const uint32_t end = wave_incl_scan(lane < 32 ? len : 0u);              // it begins so many bits below the top
+    const uint32_t start = end - len;
+    uint32_t part = 0;
+    if (lane < 32 && start < 32) part = end <= 32 ? code << (32 - end) : code >> (end - 32);
+    part = len ? part : 0u;
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(part), 63);
+}
+
+// ---- an encode: three launches and no wait between them ----
+// The chunks are dealt to the workgroups in ranges of a few to RANGE_MOST chunks in a row, the same ranges in the first and the last launch:
+//   1. range_histogram (each codec's own): the counts of the exponents of each range, a record of A u32 per range, plain stores;
+//   2. plan_kernel, one workgroup: the sum of the records, the code, from record and code lengths where each range begins in the stream
+//      (into chunk_bit[], for good), the header, which the host gets from there;
+//   3. encode_range: a workgroup knows where its range begins, its waves find out from one another in LDS where their chunks do.
+// Nothing is shared between workgroups of a launch: no counters, no waits, no atomic operations on device memory.  The records lie where the stream will
+// (RECORDS_AT); a range and its record are smaller than what the range has of the blob, and they are used up before the stream is begun.
+// Before, the workgroups of the last launch asked one another for their places (a look-back through chunk_bit[], 3 to 5 us for every tile), and
+// the host built the code between two launches.
+constexpr uint32_t RANGE_MOST = 256;        // chunks; four per lane where a wave adds up what lies before its chunk
+
+struct Ranges {
+    uint64_t chunks, each;                  // every range has `each` chunks, the first `rest` one more
+    uint32_t count, rest;
+    __device__ __forceinline__ uint64_t begin(uint32_t r) const { return r * each + (r < rest ? r : rest); }
+    __device__ __forceinline__ uint32_t size(uint32_t r) const { return (uint32_t)each + (r < rest ? 1u : 0u); }
 };
 
-// `bits` bits in front of bit number `bits` of an image: the last 32 of them, for bits >= 32.
-__device__ __forceinline__ uint32_t last32(const uint32_t *image, uint32_t bits)
+inline Ranges make_ranges(uint64_t chunks, uint32_t cus)
 {
-    return bits >= 32 ? __builtin_amdgcn_alignbit(image[bits >> 5], image[(bits >> 5) - 1], bits & 31) : 0u;
+    Ranges g;
+    g.chunks = chunks;
+    const uint64_t rounds = (chunks + (uint64_t)cus * RANGE_MOST - 1) / ((uint64_t)cus * RANGE_MOST);
+    g.count = (uint32_t)(chunks < cus ? chunks : cus * rounds);
+    g.each = chunks / g.count;
+    g.rest = (uint32_t)(chunks % g.count);
+    return g;
+}
+
+// No codeword over lmax bits: how many bits the i-th lightest of m symbols gets, as len[s[i]].  Package-merge as the CPU encoders have it: a level's
+// list is the symbols' coins and the packages of the level below, both in order, a coin before a package of its weight.  Of a level only the coins' places are
+// kept: the items taken are the first ones, so the coins among them are the first a coins, and the packages, twice as many items one level down.
+// (The CPU's E4M3 encoder asks Huffman's method first and takes its lengths where the cap does not bind.  The two agree in every tie if the one takes a leaf and
+// the other a coin first.)
+constexpr int LEVELS = 16;                  // longest codeword of any cap
+template <int A> struct CodeShared {
+    __attribute__((aligned(16))) uint64_t list[2][2 * A < 128 ? 128 : 2 * A];
+    uint64_t w[2 * A], package[2 * A];
+    uint16_t at[A > 64 ? LEVELS : 1][A];
+    uint32_t s[A], unsorted[A], rank[2][A < 64 ? 64 : A], m;
+};
+
+// m <= COINS = 16 or 64.  A coin is compared with every package at once: a lane has a coin and four packages, so COINS / 4 groups of COINS lanes have them all, one wave
+// of four groups for 16 coins, all 16 waves for 64.  A package's place in the list is a population count of a ballot, a coin's the sum of its lanes' comparisons, over
+// the groups of a wave by population counts, over waves in LDS.  One look into LDS per level and two barriers, or none, instead of a look per step of a search
+// (11 levels of 64 coins: 7.8 us in one wave with searches).
+template <int A, int COINS>
+__device__ __forceinline__ void package_merge(CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane, int wave)
+{
+    constexpr bool ONE = COINS == 16;
+    const uint32_t i = (uint32_t)lane % COINS, group = ONE ? (uint32_t)lane / COINS : (uint32_t)wave, b0 = 4 * group;
+    const uint64_t coin = i < m ? cs.w[i] : 0;
+    uint64_t at_low = i, at_high = 0;                       // wave 0: the coin's place at each level, a byte each
+    uint32_t n = m;
+    auto meet = [] {
+        if (ONE) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        else __syncthreads();
+    };
+#pragma unroll 1
+    for (uint32_t level = 1; level < lmax; level++) {
+        const uint64_t *below = cs.list[(level - 1) & 1];
+        uint64_t *here = cs.list[level & 1];
+        uint32_t *lighter = cs.rank[level & 1];             // packages lighter than the coin
+        const uint32_t packages = n / 2;
+        uint32_t mine = 0;
+        if (ONE || b0 < packages) {
+            uint64_t pw[4], heavier[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) pw[k] = below[2 * (b0 + k)] + below[2 * (b0 + k) + 1];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) heavier[k] = __ballot(pw[k] < coin && (b0 + k < packages));
+            // the k-th lane of a group puts its k-th package in its place
+            const bool k0 = i & 1, k1 = i & 2;
+            const uint64_t w = k1 ? (k0 ? pw[3] : pw[2]) : k0 ? pw[1] : pw[0];
+            if (ONE) {
+                const uint64_t same = 0x0001000100010001ull << i;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; k++) mine += (uint32_t)__builtin_popcountll(heavier[k] & same);
+                const uint64_t of = k1 ? (k0 ? heavier[3] : heavier[2]) : k0 ? heavier[1] : heavier[0];
+                if (i < 4 && b0 + i < packages) here[b0 + i + m - (uint32_t)__builtin_popcount((uint32_t)(of >> (16 * group)) & 0xffffu)] = w;
+            } else {
+                const uint32_t c0 = (uint32_t)__builtin_popcountll(heavier[0]), c1 = (uint32_t)__builtin_popcountll(heavier[1]);
+                const uint32_t c2 = (uint32_t)__builtin_popcountll(heavier[2]), c3 = (uint32_t)__builtin_popcountll(heavier[3]);
+                if (i < 4 && b0 + i < packages) here[b0 + i + m - (k1 ? (k0 ? c3 : c2) : k0 ? c1 : c0)] = w;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; k++) mine += pw[k] < coin && b0 + k < packages ? 1u : 0u;
+                if (mine) atomicAdd(&lighter[i], mine);
+            }
+        }
+        if (!ONE) meet();
+        if (ONE || wave == 0) {
+            const uint32_t place = i + (ONE ? mine : lighter[i]);
+            if (i < m && (uint32_t)lane < COINS) here[place] = coin;
+            if (level < 8) at_low |= (uint64_t)place << (level * 8);
+            else at_high |= (uint64_t)place << (level * 8 - 64);
+            if (!ONE) cs.rank[(level + 1) & 1][i] = 0;
+        }
+        n = m + packages;
+        meet();
+    }
+    if (wave != 0) return;
+    uint32_t bits = 0, taken = 2 * m - 2;
+#pragma unroll 1
+    for (uint32_t level = lmax; level-- > 0;) {
+        const uint32_t place = (uint32_t)((level < 8 ? at_low : at_high) >> (level % 8 * 8)) & 0xffu;
+        const uint32_t a = (uint32_t)__builtin_popcountll(__ballot((uint32_t)lane < m && place < taken));
+        bits += (uint32_t)lane < a ? 1u : 0u;
+        taken = 2 * (taken - a);
+    }
+    if ((uint32_t)lane < m) len[cs.s[lane]] = m == 1 ? 1u : bits;
+}
+
+// Any m, one wave: an item's place from a binary search in the other list.
+template <int A>
+__device__ __noinline__ void package_merge_any(CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane)
+{
+    constexpr int PER = (A + 63) / 64;
+    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    uint64_t coin[PER];
+#pragma unroll
+    for (int k = 0; k < PER; k++) {
+        const uint32_t i = lane + 64 * k;
+        coin[k] = i < m ? cs.w[i] : 0;
+        if (i < m) cs.list[0][i] = coin[k];
+    }
+    uint32_t n = m;
+    const uint32_t top = 1u << (31 - __builtin_clz(m));
+    fence();
+#pragma unroll 1
+    for (uint32_t level = 1; level < lmax; level++) {
+        const uint64_t *below = cs.list[(level - 1) & 1];
+        uint64_t *here = cs.list[level & 1];
+        const uint32_t packages = n / 2;
+        uint64_t pw[PER];
+        uint32_t lighter[PER], coins[PER];                  // packages lighter than the coin, coins not heavier than the package
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const uint32_t b = lane + 64 * k;
+            pw[k] = b < packages ? below[2 * b] + below[2 * b + 1] : 0;
+            if (b < packages) cs.package[b] = pw[k];
+            lighter[k] = coins[k] = 0;
+        }
+        fence();
+#pragma unroll 1
+        for (uint32_t step = top; step; step >>= 1) {
+#pragma unroll
+            for (int k = 0; k < PER; k++) {
+                const uint32_t x = lighter[k] + step, y = coins[k] + step;
+                const uint64_t px = cs.package[x - 1], cy = cs.w[y - 1];
+                if (x <= packages && px < coin[k]) lighter[k] = x;
+                if (y <= m && cy <= pw[k]) coins[k] = y;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const uint32_t i = lane + 64 * k;
+            if (i < m) {
+                here[i + lighter[k]] = coin[k];
+                cs.at[level][i] = (uint16_t)(i + lighter[k]);
+            }
+            if (i < packages) here[i + coins[k]] = pw[k];
+        }
+        n = m + packages;
+        fence();
+    }
+    uint32_t bits[PER], taken = 2 * m - 2;
+#pragma unroll
+    for (int k = 0; k < PER; k++) bits[k] = 0;
+#pragma unroll 1
+    for (uint32_t level = lmax; level-- > 0;) {
+        uint32_t a = 0;
+#pragma unroll
+        for (int k = 0; k < PER; k++) {
+            const uint32_t i = lane + 64 * k;
+            a += (uint32_t)__builtin_popcountll(__ballot(i < m && (level ? cs.at[level][i] : i) < taken));
+        }
+#pragma unroll
+        for (int k = 0; k < PER; k++) bits[k] += lane + 64 * k < a ? 1u : 0u;
+        taken = 2 * (taken - a);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; k++)
+        if (lane + 64 * k < m) len[cs.s[lane + 64 * k]] = bits[k];
+}
+
+// The code and everything that follows from it.  C: a codec: A exponents, Header, finish() (what the header holds beside the sections' places, and the
+// sections between header and chunk_bit[]).  `h` is the header as far as it does not depend on the code; where the blob would not fit, or no code of lmax bits
+// has room for the exponents that occur, nothing but a header is written: 0, and the error.
+// What bounds it: one compute unit, a chain of barriers and round trips to LDS, while the rest of the chip waits.  In a kernel trace, 256 ranges: E4M3 6.0 us, half of it
+// the lengths; E5M2 9.8; BF16 13.3, of which 3.5 are the 256 KiB of records.  On the host, between two launches, it took 8 us and, for BF16, 18.
+template <class C>
+__global__ __launch_bounds__(1024) void plan_kernel(typename C::Header h, Ranges rg, uint64_t blob_, uint64_t capacity, uint64_t records, uint32_t lmax, uint64_t mail)
+{
+    typedef typename C::Header Header;
+    constexpr int A = C::A, QUADS = A / 4, SUBSETS = 1024 / QUADS, BATCH = 256, KEEP = BATCH / SUBSETS;
+    static_assert(sizeof(Header) == 256 && (QUADS == 4 || QUADS == 8 || QUADS == 64), "64 dwords; sums over quads, eights or waves");
+    __shared__ CodeShared<A> cs;
+    __shared__ uint64_t s_part[16][A], s_freq[A], s_there[4];
+    __shared__ uint32_t s_len[A];
+    __shared__ __attribute__((aligned(16))) uint32_t s_bits[BATCH];
+    __shared__ __attribute__((aligned(16))) uint32_t s_header[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32(tid >> 6);
+    const uint32_t quad = tid % QUADS, subset = tid / QUADS;
+    GLOBAL uint8_t *blob = (GLOBAL uint8_t *)blob_;
+
+    const uint32_t frame = ((const uint32_t *)&h)[lane];
+    // a thread has four exponents of every SUBSETS-th range
+    u32x4 rec[KEEP];
+    auto load = [&](uint32_t r0) {
+#pragma unroll
+        for (int k = 0; k < KEEP; k++) {
+            const uint32_t r = r0 + subset + k * SUBSETS;
+            rec[k] = r < rg.count ? ((const GLOBAL u32x4 *)records)[(uint64_t)r * QUADS + quad] : u32x4{0, 0, 0, 0};
+        }
+    };
+    uint64_t sum[4] = {0, 0, 0, 0};
+    for (uint32_t r0 = 0; r0 < rg.count; r0 += BATCH) {
+        load(r0);
+#pragma unroll
+        for (int k = 0; k < KEEP; k++) {
+            sum[0] += rec[k].x;
+            sum[1] += rec[k].y;
+            sum[2] += rec[k].z;
+            sum[3] += rec[k].w;
+        }
+    }
+    if (wave == 0) s_header[lane] = frame;
+    if (tid < (A < 64 ? 64 : A)) cs.rank[0][tid] = cs.rank[1][tid] = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        if constexpr (QUADS < 64) {
+            // in two parts whose sums fit 32 bits: 24 bits, and the rest
+            uint32_t part[2] = {(uint32_t)sum[k] & 0xffffffu, (uint32_t)(sum[k] >> 24)};
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                part[i] = add_dpp<0x128>(part[i]);                          // row_ror:8
+                if (QUADS == 4) part[i] = add_dpp<0x124>(part[i]);          // row_ror:4
+                part[i] = add_16(part[i], part[i]);
+                part[i] = add_32(part[i], part[i]);
+            }
+            sum[k] = ((uint64_t)part[1] << 24) + part[0];
+        }
+        if (lane < QUADS) s_part[wave][4 * quad + k] = sum[k];
+    }
+    __syncthreads();
+
+    // the exponents that occur, and these in order of their counts
+    uint64_t f = 0, there = 0;
+    if (wave < (A + 63) / 64) {
+        if (tid < A) {
+#pragma unroll
+            for (int w = 0; w < 16; w++) f += s_part[w][tid];
+            s_freq[tid] = f;
+            s_len[tid] = 0;
+        }
+        there = __ballot(f != 0);
+        if (A > 64 && lane == 0) s_there[wave] = there;
+    }
+    if (A > 64) __syncthreads();
+    if (wave < (A + 63) / 64) {
+        uint32_t before = 0, m = 0;
+        if constexpr (A > 64) {
+#pragma unroll
+            for (int w = 0; w < A / 64; w++) {
+                const uint32_t in = (uint32_t)__builtin_popcountll(s_there[w]);
+                before += w < wave ? in : 0u;
+                m += in;
+            }
+        } else
+            m = (uint32_t)__builtin_popcountll(there);
+        const uint32_t i = before + (uint32_t)__builtin_popcountll(there & ((1ull << lane) - 1));
+        if (f) {
+            cs.package[i] = f;
+            cs.unsorted[i] = (uint32_t)tid;
+        }
+        if (tid == 0) cs.m = m;
+    }
+    __syncthreads();
+    const uint32_t m = uniform32(cs.m), spread = A <= 64 || m <= 64 ? 6 : 8, mine = tid & ((1u << spread) - 1u);
+    const uint64_t weight = mine < m ? cs.package[mine] : 0;
+    if (mine < m) {
+        uint32_t before = 0;
+        for (uint32_t j = tid >> spread; j < m; j += 1024u >> spread) before += cs.package[j] < weight || (cs.package[j] == weight && j < mine) ? 1u : 0u;
+        if (before) atomicAdd(&cs.rank[0][mine], before);
+    }
+    __syncthreads();
+    if (tid == (int)mine && mine < m) {
+        const uint32_t r = cs.rank[0][mine];
+        cs.w[r] = cs.list[0][r] = weight;
+        cs.s[r] = cs.unsorted[mine];
+    }
+    __syncthreads();
+    const bool code = lmax >= 1 && m <= 1u << lmax;
+    if (code) {
+        if (A == 16 && wave == 0) package_merge<A, 16>(cs, m, lmax, s_len, lane, 0);
+        else if (A != 16 && (A <= 64 || m <= 64)) package_merge<A, 64>(cs, m, lmax, s_len, lane, wave);
+        else if (A > 64 && wave == 0) package_merge_any<A>(cs, m, lmax, s_len, lane);
+    }
+    __syncthreads();
+
+    // where the ranges begin
+    GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(blob + h.off_chunk_bit);
+    const uint32_t l0 = s_len[4 * quad], l1 = s_len[4 * quad + 1], l2 = s_len[4 * quad + 2], l3 = s_len[4 * quad + 3];
+    uint64_t total = 0;
+    for (uint32_t r0 = 0; r0 < rg.count; r0 += BATCH) {
+        if (rg.count > (uint32_t)BATCH) load(r0);
+        uint32_t bits[KEEP];
+#pragma unroll
+        for (int k = 0; k < KEEP; k++) bits[k] = rec[k].x * l0 + rec[k].y * l1 + rec[k].z * l2 + rec[k].w * l3;      // a range: at most 2^25
+        if constexpr (QUADS == 64) {
+            // 16 values over a wave: two at a time in its halves, then in its rows
+#pragma unroll
+            for (int k = 0; k < KEEP / 4; k++) {
+                const uint32_t v = add_row(add_16(add_32(bits[4 * k], bits[4 * k + 1]), add_32(bits[4 * k + 2], bits[4 * k + 3])));
+                if (lane % 16 == 0) s_bits[subset + (4 * k + (lane >> 5) + (lane >> 4 & 1) * 2) * SUBSETS] = v;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < KEEP; k++) {
+                const uint32_t v = QUADS == 4 ? add_quad(bits[k]) : add_eight(bits[k]);
+                if (quad == 0) s_bits[subset + k * SUBSETS] = v;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const u32x4 v = *(const u32x4 *)(s_bits + 4 * lane);
+            const uint32_t own = v.x + v.y + v.z + v.w;
+            const uint32_t lo = wave_incl_scan(own & 0xffffu), hi = wave_incl_scan(own >> 16);  // 64 of them may need more than 32 bits
+            uint64_t at = total + (((uint64_t)hi << 16) + lo) - own;
+            total += ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, 63) << 16) + (uint32_t)__builtin_amdgcn_readlane((int)lo, 63);
+            const uint32_t each[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint32_t r = r0 + 4 * lane + k;
+                if (r < rg.count && code) cb[rg.begin(r)] = at;
+                at += each[k];
+            }
+        }
+        if (rg.count > (uint32_t)BATCH) __syncthreads();
+    }
+    if (wave != 0) return;
+
+    // the header
+    auto up = [](uint64_t v, uint64_t a) { return (v + a - 1) / a * a; };
+    Header &out = *(Header *)s_header;
+    const uint64_t stream_bytes = up((total + 7) / 8 + 8, 16), off_plane = up(h.off_stream + stream_bytes, 256), behind = up(off_plane + h.plane_bytes, 256);
+    const uint64_t size = C::size(h, behind);
+    const int err = !code ? ECF8_E_ARG : size > capacity ? ECF8_E_CAPACITY : 0;
+    if (lane == 0) {
+        out.stream_bits = total;
+        out.stream_bytes = stream_bytes;
+        out.off_plane = off_plane;
+        out.total_size = size;
+    }
+    C::finish(out, blob, behind, s_freq, s_len, m, s_len[cs.s[0]], err == 0, lane);     // the lightest symbol's codeword is the longest
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (err && lane < 2) s_header[lane] = lane ? (uint32_t)err : 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint32_t dword = s_header[lane];
+    if (mail) __hip_atomic_store((GLOBAL uint64_t *)mail + lane, 1ull << 32 | dword, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    ((GLOBAL uint32_t *)blob)[lane] = dword;
+    if (lane == 0 && !err) cb[rg.chunks] = total;
+}
+
+// The header as the kernels behind the plan read it.
+template <class Header>
+__device__ __forceinline__ const __attribute__((address_space(4))) Header &planned(uint64_t blob) { return *(const __attribute__((address_space(4))) Header *)blob; }
+
+// What the waves of a workgroup tell one another about the chunks of their range.
+constexpr int WMAX = 16;                    // waves of a workgroup at the most
+struct RangeShared {
+    __attribute__((aligned(16))) uint32_t bits[RANGE_MOST];     // of a chunk, 0: not counted yet
+    uint64_t border[RANGE_MOST + 1];        // the dword that a chunk shares with the one before: what one of the two has of it, with a 1 above
+    uint32_t next;                          // the chunk to be drawn next
+};
+__device__ __forceinline__ void range_begin(RangeShared &sh)
+{
+    for (uint32_t i = threadIdx.x; i <= RANGE_MOST; i += blockDim.x) {
+        if (i < RANGE_MOST) sh.bits[i] = 0;
+        sh.border[i] = 0;
+    }
+    if (threadIdx.x == 0) sh.next = blockDim.x >> 6;
 }
 
 typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
 
-// An image's bits to bits [b0, b1) of the stream: the dwords from the one that holds the first bit, whose lower bits are the last
-// ones of image[-1], to the last one that the bits fill, `all`: to the last one that they reach.  `skip`: not the first one.
-__device__ __forceinline__ void copy_bits(const uint32_t *image, GLOBAL uint32_t *stream, uint64_t b0, uint64_t b1, bool all, bool skip, int lane)
-{
-    const uint32_t n = (uint32_t)((b1 >> 5) - (b0 >> 5)) + (all && (b1 & 31) ? 1u : 0u), shift = (uint32_t)b0 & 31;
-    GLOBAL uint32_t *out = stream + (b0 >> 5);
-    for (uint32_t j = 4 * lane; j < n; j += 256) {
-        const u32x4 w = *(const u32x4 *)(image + j);
-        const uint32_t below = image[(int)j - 1];
-        u32x4a v = {w.x, w.y, w.z, w.w};
-        if (shift)
-            v = u32x4a{__builtin_amdgcn_alignbit(w.x, below, 32 - shift), __builtin_amdgcn_alignbit(w.y, w.x, 32 - shift),
-                       __builtin_amdgcn_alignbit(w.z, w.y, 32 - shift), __builtin_amdgcn_alignbit(w.w, w.z, 32 - shift)};
-        if (j + 4 <= n && (j || !skip)) {
-            *(GLOBAL u32x4a *)(out + j) = v;
-        } else {
-            if (j || !skip) out[j] = v.x;
-            if (j + 1 < n) out[j + 1] = v.y;
-            if (j + 2 < n) out[j + 2] = v.z;
-            if (j + 3 < n) out[j + 3] = v.w;
-        }
-    }
-}
-
-struct TileArgs {
-    uint64_t n_chunks;
-    uint32_t per_wave;                      // chunks of a wave per tile, at most 16
-    const uint32_t *header;                 // the blob's first 256 bytes
-};
-
-// The tiles of one workgroup.  K is a codec's chunk.  For chunks that lie entirely inside the tensor, fetch(c) asks for the weights, count(c) gives
-// the lane's code bits and writes the planes, pack(image, at, c, refill) packs the lane's bits from image bit `at` on and asks for the weights of
-// chunk c + 1 piece by piece as those of c are used up.  slow_count and slow_pack do the same for any chunk, from memory and rolled
-// up: the code of the common way has to stay well inside the instruction cache (with the ragged chunk's code woven in, 118 KB, it took
-// twice as long).  `image` is the wave's, K::AREA dwords, and image[-1] is there to be written.
+// The chunks of a workgroup's range, drawn in order from an LDS counter, a wave's first one by its number (already fetched, if it is whole).  K is a codec's chunk.
+// For chunks that lie entirely inside the tensor, fetch(c) asks for the weights, count(c) gives the lane's code bits and writes the planes, pack(image, at,
+// c, next, refill) packs the lane's bits from image bit `at` on and asks for the weights of chunk `next` piece by piece as its own are used up.  slow_count and
+// slow_pack do the same for any chunk, from memory and rolled up: the code of the common way has to stay well inside the instruction
+// cache.  tail(c): the last 32 bits of chunk c.  `image` is the wave's, K::AREA dwords.
+// A chunk's place is the sum of the bits of the chunks before it in the range, which are counted by the time this one is packed: a wave counts before it
+// packs and waits for chunks before its own only, so every wait ends.  The dword where two chunks meet is put together in LDS and stored by
+// whoever comes second.
 template <class K>
-__device__ __forceinline__ void encode_tiles(K &k, TileShared &sh, uint32_t *image, const TileArgs &ta, GLOBAL uint8_t *blob, uint64_t off_cb,
-                                             uint64_t off_lb, uint64_t off_st, int lane, int wave)
+__device__ __forceinline__ void encode_range(K &k, RangeShared &sh, uint32_t *image, const Ranges &rg, GLOBAL uint8_t *blob, uint64_t off_cb, uint64_t off_lb,
+                                             uint64_t off_st, uint64_t stream_dwords, int lane, int wave)
 {
-    constexpr uint32_t ROOM = (uint32_t)(K::AREA - LATE_DWORDS - 2) * 32;       // bits an image takes, zeros behind them
+    constexpr uint32_t ROOM = (uint32_t)(K::AREA - 4) * 32;     // bits an image takes
     GLOBAL uint64_t *cb = (GLOBAL uint64_t *)(blob + off_cb);
     GLOBAL uint16_t *lane_bits = (GLOBAL uint16_t *)(blob + off_lb);
     GLOBAL uint32_t *stream = (GLOBAL uint32_t *)(blob + off_st);
-    const uint32_t W = blockDim.x >> 6, T = W * ta.per_wave, n_tiles = (uint32_t)((ta.n_chunks + T - 1) / T);
-    // The counter is the header's first dword, 0 from before the histogram; whoever draws last writes the header.
-    uint32_t drawn = 0;
-    auto draw = [&]() {
-        if (threadIdx.x == 0) drawn = __hip_atomic_fetch_add((GLOBAL uint32_t *)blob, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t first = rg.begin(blockIdx.x), begin = uniform64(cb[first]);
+    const uint32_t size = rg.size(blockIdx.x), W = blockDim.x >> 6;
+    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+    auto border = [&](uint32_t i, uint32_t part, uint64_t at) {
+        const uint64_t other = atomicOr((unsigned long long *)&sh.border[i], 1ull << 32 | part);
+        if (other >> 32) stream[at] = part | (uint32_t)other;
     };
-    auto first_chunk = [&](uint32_t t) { return (uint64_t)T * t + (uint64_t)ta.per_wave * wave; };
-    bool fetched = false;                   // the tile's first chunk
-    auto zero = [&](uint32_t dwords) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes have read what this one clears
-        for (uint32_t u = lane; u * 4 < dwords; u += 64) *(u32x4 *)(image + 4 * u) = u32x4{0, 0, 0, 0};
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    };
-    draw();
-    if (threadIdx.x == 0) {
-        sh.drawn[1] = drawn;
-        sh.counted[0] = sh.counted[1] = 0;
+    for (uint32_t u = lane; u * 4 < (uint32_t)K::AREA; u += 64) *(u32x4 *)(image + 4 * u) = u32x4{0, 0, 0, 0};
+    if (wave + 1 == (int)W && begin & 31) {                     // what the range before has of the first dword
+        const uint32_t last = k.tail(first - 1) >> (32 - (begin & 31));
+        if (lane == 0 && begin >> 5 < stream_dwords) border(0, last, begin >> 5);
     }
-    __syncthreads();
-    uint32_t t = uniform32(sh.drawn[1]);
-    for (uint32_t parity = 0; t < n_tiles; parity ^= 1) {
-        const uint64_t first = (uint64_t)T * t, c0 = first_chunk(t);
-        const bool followed = first + T < ta.n_chunks;
-        const uint32_t count = c0 < ta.n_chunks ? (uint32_t)(ta.n_chunks - c0 < ta.per_wave ? ta.n_chunks - c0 : ta.per_wave) : 0u;
-        uint32_t total = 0, used = 0, kept = 0, upto = 0, late_bits = 0;         // upto: lane i, bits up to the end of chunk i
-        uint32_t lb = 0, incl = 0;                                               // of the chunk counted last
-        if (!fetched && k.whole(c0)) k.fetch(c0);
-        zero(K::AREA);
+    for (uint32_t i = wave; i < size;) {
+        const uint64_t c = first + i;
+        uint32_t drawn = 0;
+        if (lane == 0) drawn = atomicAdd(&sh.next, 1u);
+        const bool whole = k.whole(c);
+        uint32_t lb;
+        if (whole) lb = k.count(c);
+        else {
+            lb = k.slow_count(c);
+            __builtin_amdgcn_s_waitcnt(0x0f70);                 // vmcnt(0): nothing is on its way, which the compiler does not see; in pack it would wait for count's stores
+        }
+        const uint32_t incl = wave_incl_scan(lb), sum = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        const uint32_t bits = sum ? sum : 1u;                   // weights that change under the call may have no codes: garbage, but every wait ends
+        if (lane == 0) __hip_atomic_store(&sh.bits[i], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        lane_bits[c * 64 + lane] = (uint16_t)lb;
+        const uint32_t next = uniform32(drawn);
+        const bool fits = bits <= ROOM, more = next < size && k.whole(first + next), refill = more && fits && whole;
+        fence();
+        if (fits && whole) k.pack(image, incl - lb, c, first + next, refill);
+        else if (fits) k.slow_pack(image, incl - lb, c);
+        fence();
+        uint32_t before;
+        for (;;) {
+            const u32x4 e = *(volatile u32x4 *)(sh.bits + 4 * lane);
+            const uint32_t j = 4 * lane;
+            const uint32_t v0 = j < i ? e.x : 0u, v1 = j + 1 < i ? e.y : 0u, v2 = j + 2 < i ? e.z : 0u, v3 = j + 3 < i ? e.w : 0u;
+            if (!__ballot((j < i && !v0) || (j + 1 < i && !v1) || (j + 2 < i && !v2) || (j + 3 < i && !v3))) {
+                before = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v0 + v1 + v2 + v3), 63);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        uint64_t b0 = begin + before;
+        if (lane == 0 && i) cb[c] = b0;
+        // A chunk that an image does not take goes out by half its lanes at a time, whose bits fit whatever they are.
+        const uint32_t half = (uint32_t)__builtin_amdgcn_readlane((int)incl, 31);
+        uint32_t lead = 0;                                      // second half: what the first one has of its first dword
 #pragma unroll 1
-        for (uint32_t i = 0; i < count; i++) {
-            const uint64_t c = c0 + i;
-            const bool whole = k.whole(c);
-            lb = whole ? k.count(c) : k.slow_count(c);
-            lane_bits[c * 64 + lane] = (uint16_t)lb;
-            incl = wave_incl_scan(lb);
-            uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            bits = bits ? bits : 1u;                            // weights that change under the call have no codes: garbage, but no tile that begins at 0
-            total += bits;
-            upto = (uint32_t)lane == i ? total : upto;
-            // not before: a workgroup that draws twice before others have drawn at all takes their tile from them
-            if (i + 1 == count) draw();
-            if (i + 1 == count && lane == 0) {
-                // the last wave of the workgroup to have counted its chunks tells the next tile
-                sh.total[parity][wave] = total;
-                const uint64_t now = atomicAdd((unsigned long long *)&sh.counted[parity], (1ull << 40) + total) + (1ull << 40) + total;
-                if ((now >> 40) == W && followed)
-                    __hip_atomic_fetch_add(cb + first + T + 1, SAID_TOTAL | (now & ((1ull << 40) - 1)) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            // A chunk that does not fit behind the others is packed when its place is known; of the last one the last bits are needed before.
-            const bool fits = kept == i && used + bits <= ROOM, refill = fits && i + 1 < count && k.whole(c + 1);
-            if (fits && whole) k.pack(image, used + incl - lb, c, refill);
-            else if (fits || (i + 1 == count && lane == 63))
-                late_bits = k.slow_pack(image + (fits ? 0 : K::AREA - LATE_DWORDS), fits ? used + incl - lb : 0u, c, fits ? 0 : K::TAIL_FROM);
-            if (i + 1 < count && !refill && k.whole(c + 1)) k.fetch(c + 1);
-            kept += fits ? 1u : 0u;
-            used += fits ? bits : 0u;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        late_bits = (uint32_t)__builtin_amdgcn_readlane((int)late_bits, 63);
-        if (lane == 0) {
-            sh.tail[parity][wave] = kept == count ? last32(image, total) : last32(image + K::AREA - LATE_DWORDS, late_bits);
-            if (wave == 0) sh.drawn[parity] = drawn;
-        }
-        __syncthreads();
-        const uint32_t next = uniform32(sh.drawn[parity]);
-        uint32_t before = 0, all = 0;
-        for (uint32_t w = 0; w < W; w++) {
-            const uint32_t v = sh.total[parity][w];
-            before += w < (uint32_t)wave ? v : 0u;
-            all += v;
-        }
-        if (wave == 0) {
-            if (lane == 0) {
-                sh.counted[parity] = 0;
-                if (followed) __hip_atomic_fetch_add(cb + first + T + 1, SAID_TAIL | sh.tail[parity][W - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            const uint64_t begin = tile_begin(cb, T, t, lane);
-            if (lane == 0) {
-                if (followed) agent_store(cb + first + T, begin + all);
-                sh.begin = begin;
-            }
-        }
-        fetched = kept == count;
-        const uint64_t then = fetched ? first_chunk(next) : c0 + kept;
-        if ((fetched ? next < n_tiles : kept + 1 < count) && k.whole(then)) k.fetch(then);
-        __syncthreads();
-        if (count) {
-            const uint64_t b0 = uniform64(sh.begin) + before;
-            const uint32_t shift = (uint32_t)b0 & 31;
-            const bool skip = wave == 0 && shift;               // the tile's first dword comes last: it needs the end of the tile before
-            if (lane == 0 && wave != 0) image[-1] = sh.tail[parity][wave - 1];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            copy_bits(image, stream, b0, b0 + used, kept == count && c0 + count == ta.n_chunks, skip, lane);
-            uint32_t tail = wave ? sh.tail[parity][wave - 1] : 0u;
-            if (wave == 0 && t != 0) {
-                uint64_t said;                                  // all of it, before the entry is replaced
-                while (((said = agent_load(cb + first + 1)) & (SAID_TOTAL | SAID_TAIL)) != (SAID_TOTAL | SAID_TAIL)) __builtin_amdgcn_s_sleep(1);
-                tail = uniform32((uint32_t)said);
-                if (skip && lane == 0 && (b0 >> 5 != (b0 + used) >> 5 || (kept == count && c0 + count == ta.n_chunks)))
-                    stream[b0 >> 5] = __builtin_amdgcn_alignbit(image[0], tail, 32 - shift);
-            }
-            // all but the first bit of the tile behind, which the first wave has written
-            if ((uint32_t)lane < count && !(followed && wave + 1 == (int)W && (uint32_t)lane + 1 == count)) agent_store(cb + c0 + lane + 1, b0 + upto);
-            if (kept < count) {
-                // The chunks that did not fit, image by image as before.  14336 x 7168 E4M3, the upper three quarters zeros: 86 us; with these chunks looked
-                // up one symbol at a time by 16 lanes after the other 222 (84 with kernels of their own for counting and packing).  16384 x
-                // 16384, half zeros: 193, 323, 222.
-                uint64_t at = b0 + used;
-                if (kept) tail = last32(image, used);
-                used = 0;
-                zero(K::AREA);
-                auto flush = [&](bool end) {
-                    if (lane == 0) image[-1] = tail;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    copy_bits(image, stream, at, at + used, end, false, lane);
-                    if (used >= 32) tail = last32(image, used);
-                    else if (used) tail = (uint32_t)((((uint64_t)image[0] << 32 | tail) >> used));
-                    at += used;
-                    used = 0;
-                    zero(K::AREA);
-                };
-#pragma unroll 1
-                for (uint32_t i = kept; i < count; i++) {
-                    const uint64_t c = c0 + i;
-                    const bool whole = k.whole(c), more = i + 1 < count && k.whole(c + 1);
-                    if (kept + 1 < count) {                     // else it is the chunk counted last, and as count has left it
-                        lb = whole ? k.count(c) : k.slow_count(c);
-                        incl = wave_incl_scan(lb);
-                    }
-                    const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                    if (used + bits > ROOM) flush(false);
-                    if (whole && bits <= ROOM) {
-                        k.pack(image, used + incl - lb, c, false);
-                        used += bits;
-                    } else {
-                        const int lanes = bits <= ROOM ? 64 : LATE_LANES;        // at a time, if an image does not take them all
-                        for (int l0 = 0; l0 < 64; l0 += lanes) {
-                            const uint32_t from = l0 ? (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 - 1) : 0u;
-                            if (lane >= l0 && lane < l0 + lanes) k.slow_pack(image, used + incl - lb - from, c, 0);
-                            used += (uint32_t)__builtin_amdgcn_readlane((int)incl, l0 + lanes - 1) - from;
-                            if (lanes != 64) flush(false);
-                        }
-                    }
-                    if (more) k.fetch(c + 1);
+        for (int part = 0; part < (fits ? 1 : 2); part++) {
+            const uint32_t from = part ? half : 0u, here = fits ? bits : part ? bits - half : half;
+            if (!fits && (lane >> 5) == part) k.slow_pack(image, incl - lb - from, c);
+            fence();
+            const bool last = fits || part, end = last && c + 1 == rg.chunks;
+            const uint32_t shift = (uint32_t)b0 & 31, over = (uint32_t)(b0 + here) & 31, n = (uint32_t)(((b0 + here) >> 5) - (b0 >> 5));
+            const bool shared = shift && !part;                 // the first dword, with the chunk before
+            const uint64_t d0 = b0 >> 5, left = d0 < stream_dwords ? stream_dwords - d0 : 0;     // changing weights again: not past the section
+            const uint32_t full = n < left ? n : (uint32_t)left;
+            GLOBAL uint32_t *out = stream + d0;
+            uint32_t carry = 0, head = 0, tail = 0;
+            for (uint32_t j0 = 0; j0 < n + 1; j0 += 256) {
+                const uint32_t j = j0 + 4 * lane;
+                u32x4 w = {0, 0, 0, 0};
+                if (j <= n) {
+                    w = *(const u32x4 *)(image + j);
+                    *(u32x4 *)(image + j) = u32x4{0, 0, 0, 0};
                 }
-                flush(c0 + count == ta.n_chunks);
+                const uint32_t below = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)w.w, 0x138, 0xf, 0xf, false);     // wave_shr:1
+                carry = (uint32_t)__builtin_amdgcn_readlane((int)w.w, 63);
+                u32x4a v = {w.x, w.y, w.z, w.w};
+                if (shift)
+                    v = u32x4a{__builtin_amdgcn_alignbit(w.x, below, 32 - shift), __builtin_amdgcn_alignbit(w.y, w.x, 32 - shift),
+                               __builtin_amdgcn_alignbit(w.z, w.y, 32 - shift), __builtin_amdgcn_alignbit(w.w, w.z, 32 - shift)};
+                if (j == 0) v.x |= lead;
+                if (j0 == 0) head = v.x;
+                if (j + 4 <= full && (j || !shared)) {
+                    *(GLOBAL u32x4a *)(out + j) = v;
+                } else {
+                    if (j < full && (j || !shared)) out[j] = v.x;
+                    if (j + 1 < full) out[j + 1] = v.y;
+                    if (j + 2 < full) out[j + 2] = v.z;
+                    if (j + 3 < full) out[j + 3] = v.w;
+                }
+                const uint32_t t = n & 2 ? (n & 1 ? v.w : v.z) : n & 1 ? v.y : v.x;
+                tail = (uint32_t)__builtin_amdgcn_readlane((int)t, (int)(n >> 2) & 63);
             }
+            lead = over ? tail : 0u;
+            if (lane == 0) {
+                if (shared && left) border(i, head, d0);
+                if (last && over && n < left && (n || !shared)) {
+                    if (end) out[n] = tail;
+                    else border(i + 1, tail, d0 + n);
+                }
+            }
+            fence();
+            b0 += here;
         }
-        t = next;
+        if (more && !refill) k.fetch(first + next);
+        i = next;
     }
-    if (t == n_tiles + gridDim.x - 1 && threadIdx.x < 64)
-        __hip_atomic_store((GLOBAL uint32_t *)blob + threadIdx.x, ta.header[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Waves per workgroup, chunks per wave and tile, workgroups, for a stream of `bits` bits: a chunk on as many compute units as there are
-// chunks; then more waves, up to WMAX; then as many chunks per wave as gives every compute unit the same number of tiles, up to what
-// their images hold (with 15 % to spare: a chunk that does not fit is read and packed a second time).
-struct TilePlan {
-    uint32_t waves, per_wave, grid;
-};
-template <int AREA>
-inline TilePlan plan_tiles(uint64_t n_chunks, uint64_t bits, uint32_t cus)
+// Waves of a workgroup: no more than its range has chunks, as far as the tables are set up faster by more.
+inline uint32_t range_waves(const Ranges &g)
 {
-    TilePlan p;
-    p.waves = n_chunks <= 4ull * cus ? 4u : n_chunks <= 8ull * cus ? 8u : (uint32_t)WMAX;
-    const uint64_t each = (n_chunks + (uint64_t)p.waves * cus - 1) / ((uint64_t)p.waves * cus), mean = bits / n_chunks + 1;
-    uint64_t hold = (uint64_t)(AREA - LATE_DWORDS - 2) * 32 * 100 / (115 * mean);
-    hold = hold < 1 ? 1 : hold > 16 ? 16 : hold;
-    const uint64_t rounds = (each + hold - 1) / hold;
-    p.per_wave = (uint32_t)((each + rounds - 1) / rounds);
-    const uint64_t tiles = (n_chunks + (uint64_t)p.waves * p.per_wave - 1) / ((uint64_t)p.waves * p.per_wave);
-    p.grid = (uint32_t)(tiles < cus ? tiles : cus);
-    return p;
-}
-
-// The encoders' one synchronisation: the histogram on its way to the host.  The workgroup of the histogram kernel that adds its counts last
-// writes the sums to a page of pinned host memory and says so there, and the host looks at the page until it does.  A copy behind the
-// kernel and the call that waits for it took longer: 14336 x 4096 E4M3 56.8 us -> 53.0, BF16 89.2 -> 84.3, 256 x 256 34 -> 25.
-constexpr int MAIL_SAID = 256;              // behind the counts
-constexpr uint32_t TICKET_AT = 4;           // byte of the blob: how many workgroups have added their counts, 0 from before the histogram
-
-// By all threads of a workgroup, after their additions to `counters`.  mail: 0, or the page.  Counts, ticket and page are only touched by atomic
-// operations, which no cache answers, and each wave waits for its own to be made; a release of the whole cache in their place costs 25 us.
-template <int A>
-__device__ __forceinline__ void mail_histogram(uint64_t blob, uint64_t counters, uint64_t mail)
-{
-    __shared__ uint32_t s_last;
-    if (!mail) return;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's additions have been made ...
-    __syncthreads();                                        // ... and so have every wave's
-    if (threadIdx.x == 0) s_last = __hip_atomic_fetch_add((GLOBAL uint32_t *)(blob + TICKET_AT), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-    __syncthreads();
-    if (!s_last) return;
-    if (threadIdx.x < A)
-        __hip_atomic_store((GLOBAL uint64_t *)mail + threadIdx.x, agent_load((GLOBAL uint64_t *)counters + threadIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store((GLOBAL uint64_t *)mail + MAIL_SAID, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const uint64_t most = g.each + (g.rest ? 1 : 0);
+    return most <= 4 ? 4u : most <= 8 ? 8u : (uint32_t)WMAX;
 }
 
 // While another thread captures a stream, some calls (to allocate, to free, to wait) fail in this one and spoil that capture, unless the thread says that
@@ -405,6 +618,8 @@ public:
     ~CaptureRelaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
+// The encoders' one synchronisation: the header on its way to the host, on a page of pinned host memory.  A word of it is a dword of the header with a 1 above, so that
+// the host takes each as it comes and nothing has to be ordered.  (A copy behind the kernel and the call that waits for it took some 5 us longer.)
 // A page for one call.  Pages of finished calls are kept for later ones, of any thread, stream and device: KEPT of them per encoder, others are given back.
 class Mail {
     static constexpr size_t KEPT = 16;
@@ -434,7 +649,8 @@ public:
             (void)hipHostFree(page);
             page = nullptr;
         }
-        if (page) __atomic_store_n(page + MAIL_SAID, 0ull, __ATOMIC_RELEASE);
+        if (page)
+            for (int i = 0; i < 64; i++) __atomic_store_n(page + i, 0ull, i < 63 ? __ATOMIC_RELAXED : __ATOMIC_RELEASE);
     }
     Mail(const Mail &) = delete;
     Mail &operator=(const Mail &) = delete;
@@ -451,32 +667,41 @@ public:
         }
         (void)hipHostFree(page);
     }
-    // for the kernel; 0: there is no page, and the histogram has to be copied
+    // for the kernel; 0: there is no page, and the header has to be copied
     uint64_t device()
     {
         quiet = !page;
         return page ? (uint64_t)(uintptr_t)seen : 0;
     }
-    // The A counts, of the kernel that was given device(); without a page, from `counters`, by a copy that waits for all that is queued on s.
-    bool read(uint64_t *host, int A, uint64_t counters, hipStream_t s)
+    // The header, of the plan kernel that was given device(), dword by dword as they come; without a page, from the blob, by a copy that waits for all that is
+    // queued on s.
+    bool read(void *header, uint64_t blob, hipStream_t s)
     {
         if (!page) {
-            if (hipMemcpyWithStream(host, (const void *)(uintptr_t)counters, 8ull * A, hipMemcpyDeviceToHost, s) == hipSuccess) return true;
+            if (hipMemcpyWithStream(header, (const void *)(uintptr_t)blob, 256, hipMemcpyDeviceToHost, s) == hipSuccess) return true;
             (void)hipGetLastError();
             return false;
         }
         const auto since = std::chrono::steady_clock::now();
-        for (uint32_t i = 1; !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE); i++) {
+        bool done = false;
+        int got = 0;
+        for (uint32_t i = 1; got < 64; i++) {
+            const uint64_t v = __atomic_load_n(page + got, __ATOMIC_ACQUIRE);
+            if (v >> 32) {
+                ((uint32_t *)header)[got++] = (uint32_t)v;
+                continue;
+            }
+            if (done) return false;
             __builtin_ia32_pause();
             // the stream has more to do, or it has failed
             if (i % 256 == 0 && std::chrono::steady_clock::now() - since > std::chrono::milliseconds(1)) {
-                const bool done = hipStreamSynchronize(s) == hipSuccess;
-                if (!done) (void)hipGetLastError();
-                if (!done || !__atomic_load_n(page + MAIL_SAID, __ATOMIC_ACQUIRE)) return false;
-                break;
+                done = hipStreamSynchronize(s) == hipSuccess;
+                if (!done) {
+                    (void)hipGetLastError();
+                    return false;
+                }
             }
         }
-        for (int i = 0; i < A; i++) host[i] = page[i];
         quiet = true;
         return true;
     }

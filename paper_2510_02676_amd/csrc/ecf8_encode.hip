@@ -1,14 +1,11 @@
 // GPU-side ECF8 encoder for gfx950 (paper Section 3.1: histogram, code, stream, metadata and
 // nibble plane, produced on the device so that FP8 checkpoints compress at load time without a
 // trip through host memory).  Writes exactly the container the CPU encoder writes, byte for
-// byte: the code and the layout come from the same host routine, fed with the device histogram.
+// byte: the same code under every cap, ties included, and the layout of the same routine.
 //
-//   fill 0 (256 bytes) -> histogram (and zeros in chunk_bit[]), written to the host by its last workgroup -> [host: code + layout]
-//   -> everything else in one pass over the weights (encode_tiles): planes, lane_bits, the chunks' bits packed in LDS, their place
-//   in the stream found out between the workgroups, the stream; the workgroups also write pair table and padding, the one that
-//   finds no more work last the header.
-// The input is read twice (histogram, the rest).  No scratch memory on the device: the histogram is counted into the header's freq[] field, tiles are
-// drawn from its first dword, and what the workgroups tell one another goes through chunk_bit[], all of them part of the output.
+//   histograms of ranges of chunks -> code, places of the ranges in the stream, header (one workgroup; the host waits for the header) -> everything else:
+//   planes, lane_bits, the chunks' bits packed in LDS and copied to the stream, pair table and padding (encode_range).
+// The input is read twice (histogram, the rest).  No scratch memory on the device: the ranges' histograms lie where the stream will.
 #include "ecf8_device.h"
 #include "ecf8_enc_device.h"
 #include "ecf8_plan.h"
@@ -20,10 +17,9 @@ namespace {
 struct EncArgs {
     uint64_t x, blob;                     // device addresses
     uint64_t n, cols, n_chunks;
+    uint32_t kc_per_row;                  // row-tiled: chunks per block of rows
     uint64_t off_cb, off_lb, off_st, off_pl;
     uint32_t group, tiled;
-    uint64_t len_packed;                  // code length of symbol s in bits 4s..4s+3
-    uint32_t code[16], rcode[16];
 };
 
 template <int N>
@@ -31,9 +27,8 @@ __device__ __forceinline__ ChunkPlace place_of(const EncArgs &a, uint64_t c, uin
 {
     constexpr uint64_t E = 64ull * N;
     if (a.tiled) {
-        const uint64_t kc_per_row = a.cols / (4ull * N);
-        const uint64_t rb = c / kc_per_row;
-        return {rb * 16 * a.cols + (c - rb * kc_per_row) * (4ull * N), 64, (uint64_t)(lane & 15) * a.cols + 16ull * (lane >> 4)};
+        const uint32_t rb = (uint32_t)c / a.kc_per_row;     // at most 2^40 elements
+        return {(uint64_t)rb * 16 * a.cols + ((uint32_t)c - rb * a.kc_per_row) * (4ull * N), 64, (uint64_t)(lane & 15) * a.cols + 16ull * (lane >> 4)};
     }
     const uint64_t grouped = (a.n / E) & ~((uint64_t)a.group - 1);
     const uint64_t w = c & (a.group - 1);
@@ -44,25 +39,22 @@ __device__ __forceinline__ ChunkPlace place_of(const EncArgs &a, uint64_t c, uin
 // elements of the piece at e that exist
 __device__ __forceinline__ uint32_t piece_len(uint64_t e, uint64_t n) { return e + 16 <= n ? 16u : e < n ? (uint32_t)(n - e) : 0u; }
 
-// Exponent-field histogram into 16 u64 counters.  Counted with bit planes: 32 elements are turned into four 32-bit
+// Exponent-field histogram of each range into a record of 16 u32.  Counted with bit planes: 32 elements are turned into four 32-bit
 // words, one per exponent bit, and each of the 16 exponents is then one AND and one population count that also adds:
-// two vector operations per element and no LDS.  58.7 M weights: 14.5 us (4 TB/s; counters private to a thread in LDS,
-// one read-modify-write per element, 37 us).  What is left is the read and its latency.
-__global__ __launch_bounds__(1024) void histogram_kernel(uint64_t x_, uint64_t n, uint64_t blob, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks, uint64_t mail)
+// two vector operations per element and no LDS.  A range's last chunks come first: the pass behind it begins with the first ones, and finds them in the
+// second-level cache.  58.7 M weights in a kernel trace: 15.2 us when the counts were added to one record and mailed to the host by the last workgroup, each counter
+// summed over the wave by a scan of its own; 10.6 now (5.5 TB/s).  What is left is the read.
+template <int N>
+__global__ __launch_bounds__(1024) void histogram_kernel(EncArgs a, Ranges rg, uint64_t records)
 {
     __shared__ uint32_t s_cnt[16];
-    const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)x_;
-    GLOBAL unsigned long long *counters = (GLOBAL unsigned long long *)counters_;
+    const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x;
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid < 16) s_cnt[tid] = 0;
-    zero_chunk_bits(chunk_bit, n_chunks, (uint32_t)tid, 1024);
     __syncthreads();
     uint32_t cnt[16];
 #pragma unroll
     for (int s = 0; s < 16; s++) cnt[s] = 0;
-    // a wave takes 4 KiB per step: four loads of 1 KiB, of which a lane keeps the 16 bytes at 16 * lane
-    const uint64_t steps = n / 4096, stride = (uint64_t)gridDim.x * 16;
-    const GLOBAL u32x4 *p = (const GLOBAL u32x4 *)x + lane;
     auto count = [&](const u32x4 &va, const u32x4 &vb) {
         const uint32_t w[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
         uint32_t t[4];
@@ -79,25 +71,50 @@ __global__ __launch_bounds__(1024) void histogram_kernel(uint64_t x_, uint64_t n
             cnt[s] += (uint32_t)__builtin_popcount(hi & lo);
         }
     };
-    for (uint64_t i = (uint64_t)blockIdx.x * 16 + (tid >> 6); i < steps; i += stride) {
-        const u32x4 va = p[i * 256], vb = p[i * 256 + 64], vc = p[i * 256 + 128], vd = p[i * 256 + 192];
-        count(va, vb);
-        count(vc, vd);
-    }
-    if (blockIdx.x == 0)
-        for (uint64_t i = steps * 4096 + tid; i < n; i += 1024) atomicAdd(&s_cnt[(x[i] >> 3) & 15u], 1u);
+    // a wave takes four pieces of 1 KiB per step, two with 32 symbols per lane, where they are all of a chunk
+    constexpr uint32_t PIECES = N / 16, PER = PIECES < 4 ? PIECES : 4;
+    const uint64_t first = rg.begin(blockIdx.x);
+    const uint32_t size = rg.size(blockIdx.x), whole = size - ((first + size) * (64ull * N) > a.n ? 1u : 0u);
+    for (uint32_t i = uniform32(tid >> 6); i < whole * (PIECES / PER); i += 16) {
+        const uint64_t c = first + whole - 1 - i / (PIECES / PER);      // the first chunks last: the next reader begins with them
+        const uint32_t q = i % (PIECES / PER) * PER;
+        u32x4 v[PER];
+        if (a.tiled) {
+            // in the order of the rows: 256 / N of them per piece, a lane's place in them instead of the one it codes
+            const ChunkPlace p = place_of<N>(a, c, 0);
+            const uint32_t o = 16 * lane;
 #pragma unroll
-    for (int s = 0; s < 16; s++) {
-        const uint32_t sum = wave_incl_scan(cnt[s]);
-        if (lane == 63 && sum) atomicAdd(&s_cnt[s], sum);
+            for (uint32_t j = 0; j < PER; j++) v[j] = *(const GLOBAL u32x4 *)(x + p.base + (uint64_t)((q + j) * (256 / N) + o / (4 * N)) * a.cols + o % (4 * N));
+        } else {
+            const ChunkPlace p = place_of<N>(a, c, (uint32_t)lane);
+#pragma unroll
+            for (uint32_t j = 0; j < PER; j++) v[j] = *(const GLOBAL u32x4 *)(x + p.base + p.lane_off + (q + j) * p.stride);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < PER; j += 2) count(v[j], v[j + 1]);
     }
+    if (whole != size)
+        for (uint64_t i = (first + whole) * (64ull * N) + tid; i < a.n; i += 1024) atomicAdd(&s_cnt[(x[i] >> 3) & 15u], 1u);
+    add_counts<16>(cnt, s_cnt, lane);
     __syncthreads();
-    if (tid < 16 && s_cnt[tid]) atomicAdd((unsigned long long *)(counters + tid), (unsigned long long)s_cnt[tid]);
-    mail_histogram<16>(blob, counters_, mail);
+    if (tid < 16) ((GLOBAL uint32_t *)records)[(uint64_t)blockIdx.x * 16 + tid] = s_cnt[tid];
 }
 
+// What plan_kernel has to know of this codec.
+struct E4M3Codec {
+    static constexpr int A = 16;
+    typedef ecf8_header Header;
+    static __device__ __forceinline__ uint64_t size(const Header &, uint64_t behind) { return behind; }
+    static __device__ __forceinline__ void finish(Header &h, GLOBAL uint8_t *, uint64_t, const uint64_t *freq, const uint32_t *len, uint32_t, uint32_t, bool, int lane)
+    {
+        if (lane >= 16) return;
+        h.code_len[lane] = (uint8_t)len[lane];
+        h.freq[lane] = freq[lane];
+    }
+};
+
 // Everything of the container that is neither chunk data nor stream, but for the header, by all workgroups: pair table, zeros in the gaps between sections and behind the last dword of the stream.
-__device__ __forceinline__ void write_fixed(const EncArgs &a, const ecf8_header &h)
+__device__ __forceinline__ void write_fixed(const EncArgs &a, const __attribute__((address_space(4))) ecf8_header &h, uint64_t len_packed, const uint32_t (*one)[17])
 {
     const uint32_t tid = threadIdx.x, threads = blockDim.x;
     GLOBAL uint8_t *blob = (GLOBAL uint8_t *)a.blob;
@@ -111,13 +128,16 @@ __device__ __forceinline__ void write_fixed(const EncArgs &a, const ecf8_header 
         zero(a.off_pl + h.plane_bytes, h.total_size);
     }
     if (!h.table_bits) return;
+    uint32_t rcode[16];
+#pragma unroll
+    for (int s = 0; s < 16; s++) rcode[s] = uniform32(one[0][s]) & 0xffffu;
     // the first codeword at the low bits of v: symbol | length << 4, 0 if it is longer than the table's index
     auto first = [&](uint32_t v) {
         uint32_t r = 0;
 #pragma unroll
         for (int s = 0; s < 16; s++) {
-            const uint32_t l = (uint32_t)(a.len_packed >> (4 * s)) & 15u;
-            if (l != 0 && l <= (uint32_t)TB && (v & ((1u << l) - 1u)) == a.rcode[s]) r = (uint32_t)s | (l << 4);
+            const uint32_t l = (uint32_t)(len_packed >> (4 * s)) & 15u;
+            if (l != 0 && l <= (uint32_t)TB && (v & ((1u << l) - 1u)) == rcode[s]) r = (uint32_t)s | (l << 4);
         }
         return r;
     };
@@ -127,7 +147,7 @@ __device__ __forceinline__ void write_fixed(const EncArgs &a, const ecf8_header 
     }
 }
 
-// A chunk on its way through encode_tiles.
+// A chunk on its way through encode_range.
 //  * Plane: 8 elements -> 4 bytes, byte j = low nibble element j, high nibble element j + 4; zeros where the last chunk reaches past
 //    the tensor.
 //  * Bits: a lane's are one string, the forward run's codewords in order and then the backward run's in reverse (each with its first
@@ -142,10 +162,10 @@ struct Chunk {
     typedef typename std::conditional<CAP7, uint32_t, uint64_t>::type Entry;        // codewords; length from bit 28 or 32
     static constexpr int LEN_AT = CAP7 ? 28 : 32;
     static constexpr uint32_t BITS = (1u << 28) - 1;                                // CAP7: of an entry or two joined ones
-    static constexpr int AREA = ((160 * 1024 - 1024 - 512 * (int)sizeof(Entry)) / (4 * WMAX) - 4) / 4 * 4;
     static constexpr int LANE_BITS = N * (CAP7 ? 7 : 15);                           // at most
-    static constexpr int TAIL_FROM = N / 16 - 2;                                    // a lane's last 32 codewords
-    static_assert(32 * 15 < 32 * LATE_DWORDS && LANE_BITS * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
+    static constexpr int MOST = (160 * 1024 - 4096 - 512 * (int)sizeof(Entry)) / (4 * WMAX) / 4 * 4;
+    static constexpr int AREA = 2 * LANE_BITS + 4 < MOST ? 2 * LANE_BITS + 4 : MOST;  // a chunk whatever it is, if there is room
+    static_assert(LANE_BITS + 4 <= AREA && AREA % 4 == 0, "half a chunk");
 
     const EncArgs &a;
     const Entry *fwd, *bwd;                 // pairs of symbols
@@ -233,17 +253,16 @@ struct Chunk {
         }
         return lb;
     }
-    // from the lane's i0-th piece on; the image's bit behind the last one
-    __device__ __forceinline__ uint32_t slow_pack(uint32_t *image, uint32_t at, uint64_t c, int i0)
+    __device__ __forceinline__ void slow_pack(uint32_t *image, uint32_t at, uint64_t c)
     {
         const ChunkPlace p = place_of<N>(a, c, lane);
-        LanePacker out(image, at);
+        LanePacker<false> out(image, at);
         const uint64_t e0 = p.base + p.lane_off;
         const uint32_t stride = (uint32_t)p.stride;
         auto at_piece = [&](int i) { return e0 + (uint32_t)(i >= N / 32 ? N / 16 - 1 - (i - N / 32) : i) * stride; };
-        u32x4 next = slow_fetch(at_piece(i0));
+        u32x4 next = slow_fetch(at_piece(0));
 #pragma unroll 1
-        for (int i = i0; i < N / 16; i++) {
+        for (int i = 0; i < N / 16; i++) {
             const bool back = i >= N / 32;
             const u32x4 w = next;
             if (i + 1 < N / 16) next = slow_fetch(at_piece(i + 1));
@@ -256,15 +275,22 @@ struct Chunk {
             }
         }
         out.finish();
-        return out.end(image);
+    }
+    // the last 32 bits of a whole chunk: those of lane 63's last codewords, of which each lane looks up one
+    __device__ __forceinline__ uint32_t tail(uint64_t c) const
+    {
+        const ChunkPlace p = place_of<N>(a, c, 63);
+        const uint32_t t = (uint32_t)lane & 31;                 // counted from the end: the backward run from its first symbol on, then the forward run from its last
+        const uint32_t s = t < N / 2 ? N / 2 + t : N - 1 - t, back = t < N / 2 ? 1 : 0;
+        const uint32_t e = one[back][(((const GLOBAL uint8_t *)a.x)[p.base + p.lane_off + s / 16 * p.stride + s % 16] >> 3) & 15u];
+        return last_bits(e & 0xffffu, e >> 16, lane);
     }
     // the four symbols of dword w, in order (BWD = false) or in reverse
     template <bool BWD>
-    __device__ __forceinline__ void put4(LanePacker &out, uint32_t w) const
+    __device__ __forceinline__ void put4(LanePacker<false> &out, uint32_t w) const
     {
         if constexpr (CAP7) {                                                       // as count has left them
-            const uint32_t nb = 31u - (uint32_t)__builtin_clz(w);
-            out.put(w ^ (1u << nb), nb);
+            out.put(w, 31u ^ (uint32_t)__builtin_clz(w));
         } else {
             const Entry *tab = BWD ? bwd : fwd;
             const uint32_t x = (w >> 3) & 0x0f0f0f0fu, u = x | (x >> 4);            // bytes 0 and 2: two exponents each
@@ -274,10 +300,10 @@ struct Chunk {
             out.put((uint32_t)eb, (uint32_t)(eb >> LEN_AT));
         }
     }
-    __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t c, bool refill)
+    __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t, uint64_t next, bool refill)
     {
-        LanePacker out(image, at);
-        const ChunkPlace p = place_of<N>(a, c + 1, lane);
+        LanePacker<false> out(image, at);
+        const ChunkPlace p = place_of<N>(a, next, lane);
         const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x + p.base + p.lane_off;
 #pragma unroll
         for (int q = 0; q < N / 32; q++) {
@@ -293,52 +319,64 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M weights (14336 x 4096): 30 us in a kernel trace (the last 100 of 300 calls) for the 111 MB read and written,
-// some 17 of them bound by vector operations, the others the first loads, the exchange and the copy to the stream, when the compute unit waits.  With two
-// pairs looked up again for every put it took 2 more; metadata and planes, prefix sum and packing as kernels of their own 10 to 12 more, and
-// they read the weights twice.  The whole call 67.7 -> 56.4 us (53.0 since the histogram is mailed), 16384 x 16384 242 -> 190.
+// The container behind the code.  58.7 M weights (14336 x 4096): 22.7 us in a kernel trace for the 111 MB read and written; 29.8 when the workgroups had to find their
+// place in the stream from one another.  Vector operations take two thirds of it, 8.7 per weight; the rest is the first fetch and the last copy, when
+// the compute unit has nothing else to do.  The whole call 52.8 -> 42.4, 256 x 512 26 -> 18, 16384 x 16384 191 -> 154.
 template <int N, bool CAP7>
-__global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, ecf8_header h, uint32_t per_wave)
+__global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, Ranges rg)
 {
     using K = Chunk<N, CAP7>;
     typedef typename K::Entry Entry;
-    __shared__ __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA + 4];  // the last of the four in front is image[-1]
-    __shared__ Entry s_fwd[256], s_bwd[256];
-    __shared__ uint32_t s_one[2][17];
-    __shared__ TileShared sh;
+    __shared__ struct {                                     // the tables where a look-up needs no address of theirs
+        Entry fwd[256], bwd[256];
+        uint32_t one[2][17];
+        RangeShared range;
+        __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA];
+    } s;
     const uint32_t tid = threadIdx.x;
-    const int wave = (int)uniform32(tid >> 6);
-    if (tid < 256) {
-        const uint32_t lo = tid & 15, hi = tid >> 4;        // an entry's first and second element
-        const uint32_t l0 = (uint32_t)(a.len_packed >> (4 * lo)) & 15u, l1 = (uint32_t)(a.len_packed >> (4 * hi)) & 15u;
-        s_fwd[tid] = (Entry)(a.rcode[lo] | (a.rcode[hi] << l0)) | ((Entry)(l0 + l1) << K::LEN_AT);
-        s_bwd[tid] = (Entry)(a.code[hi] | (a.code[lo] << l1)) | ((Entry)(l0 + l1) << K::LEN_AT);
-        if (tid < 17) {
-            const uint32_t l = tid < 16 ? l0 : 0u;
-            s_one[0][tid] = tid < 16 ? a.rcode[lo] | (l << 16) : 0u;
-            s_one[1][tid] = tid < 16 ? a.code[lo] | (l << 16) : 0u;
-        }
-    }
-    write_fixed(a, h);
-    K k{a, s_fwd, s_bwd, s_one, (int)(tid & 63), {}, {}};
+    const int wave = (int)uniform32(tid >> 6), lane = (int)(tid & 63);
+    uint64_t len_packed = 0;                                // code length of symbol s in bits 4s..4s+3
+    K k{a, s.fwd, s.bwd, s.one, lane, {}, {}};
+    const uint64_t c0 = rg.begin(blockIdx.x) + wave;
+    if ((uint32_t)wave < rg.size(blockIdx.x) && k.whole(c0)) k.fetch(c0);
+    const auto &h = planned<ecf8_header>(a.blob);
+    if (h.magic == 0) return;                               // no blob
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-        const uint32_t l = (uint32_t)(a.len_packed >> (16 * i));
-        k.len_bytes[i] = (l & 15u) | ((l & 0xf0u) << 4) | ((l & 0xf00u) << 8) | ((l & 0xf000u) << 12);
+        k.len_bytes[i] = ((const __attribute__((address_space(4))) uint32_t *)h.code_len)[i];
+        const uint32_t l = k.len_bytes[i] | k.len_bytes[i] >> 4;
+        len_packed |= (uint64_t)((l & 0xffu) | (l >> 8 & 0xff00u)) << (16 * i);
     }
-    encode_tiles(k, sh, images[wave] + 4, TileArgs{a.n_chunks, per_wave, (const uint32_t *)&h}, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st,
-                 (int)(tid & 63), wave);
+    a.off_pl = h.off_plane;
+    range_begin(s.range);
+    if (tid < 256) {
+        const uint32_t lo = tid & 15, hi = tid >> 4;        // an entry's first and second element
+        // canonical codewords: behind those of shorter and of equally long, smaller exponents
+        uint32_t own = (uint32_t)(len_packed >> (4 * lo)) & 15u, code = 0;
+#pragma unroll
+        for (uint32_t e = 0; e < 16; e++) {
+            const uint32_t l = (uint32_t)(len_packed >> (4 * e)) & 15u;
+            if (l && (l < own || (l == own && e < lo))) code += 1u << (15 - l);
+        }
+        code = own ? code >> (15 - own) : 0u;
+        const uint32_t rcode = own ? __brev(code) >> (32 - own) : 0u, l0 = own, l1 = (uint32_t)(len_packed >> (4 * hi)) & 15u;
+        const uint32_t code_hi = (uint32_t)__shfl((int)code, (int)hi, 64), rcode_hi = (uint32_t)__shfl((int)rcode, (int)hi, 64);
+        s.fwd[tid] = (Entry)(rcode | (rcode_hi << l0)) | ((Entry)(l0 + l1) << K::LEN_AT);
+        s.bwd[tid] = (Entry)(code_hi | (code << l1)) | ((Entry)(l0 + l1) << K::LEN_AT);
+        if (tid < 17) {
+            s.one[0][tid] = tid < 16 ? rcode | (l0 << 16) : 0u;
+            s.one[1][tid] = tid < 16 ? code | (l0 << 16) : 0u;
+        }
+    }
+    __syncthreads();
+    write_fixed(a, h, len_packed, s.one);
+    encode_range(k, s.range, s.images[wave], rg, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st, h.stream_bytes / 4, lane, wave);
 }
 
 template <int N, bool CAP7>
-int launch_encode(const EncArgs &a, const ecf8_header &h, hipStream_t s)
+void launch_encode(const EncArgs &a, const Ranges &rg, hipStream_t s)
 {
-    const int cus = device_cus();
-    if (cus <= 0) return ECF8_E_HIP;
-    using K = Chunk<N, CAP7>;
-    const TilePlan p = plan_tiles<K::AREA>(h.n_chunks, h.stream_bits, (uint32_t)cus);
-    hipLaunchKernelGGL((encode_kernel<N, CAP7>), dim3(p.grid), dim3(p.waves * 64), 0, s, a, h, p.per_wave);
-    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+    hipLaunchKernelGGL((encode_kernel<N, CAP7>), dim3(rg.count), dim3(range_waves(rg) * 64), 0, s, a, rg);
 }
 
 } // namespace
@@ -359,57 +397,48 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
     int rc = ecf8_internal::check_options(rows, cols, opts, &N, &group, &lmax, &tile_rows, &tmode);
     if (rc) return rc;
     if (((uintptr_t)d_fp8 & 15) || ((uintptr_t)d_blob & 255)) return ECF8_E_ALIGN;
-    if (blob_capacity < 256) return ECF8_E_CAPACITY;
-    const uint64_t n = rows * cols;
+    ecf8_header h;
+    rc = ecf8_internal::plan_frame(rows, cols, opts, &h);
+    if (rc) return rc;
+    if (blob_capacity < h.off_stream + h.plane_bytes) return ECF8_E_CAPACITY;       // no blob of this tensor is that small, and the ranges' histograms fit
     hipStream_t s = (hipStream_t)stream;
-    const uint64_t blob = (uint64_t)(uintptr_t)d_blob, x = (uint64_t)(uintptr_t)d_fp8;
-
-    // pass 1: histogram, counted into the header's freq[] field
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
-    const uint64_t n_chunks = (n + 64ull * N - 1) / (64ull * N), off_cb = 256 + ((tmode == 1 || (tmode == 0 && n >= (1ull << 22))) ? TBL_ENTRIES * 2 : 0);
-    if (blob_capacity < off_cb + 8 * (n_chunks + 1)) return ECF8_E_CAPACITY;        // no blob of this tensor is that small
-    if (capturing(s)) return ECF8_E_HIP;
-    Mail mail;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, blob, (uint64_t)256);
-    // one workgroup per compute unit at the most: each ends with 16 atomic additions to one line
-    const uint64_t hist_blocks = (n / 4096 + 15) / 16, hist_most = (uint64_t)cus;
-    hipLaunchKernelGGL(histogram_kernel, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s, x, n,
-                       blob, blob + 128, blob + off_cb, n_chunks, mail.device());
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
-    uint64_t freq[16];
-    if (!mail.read(freq, 16, blob + 128, s)) return ECF8_E_HIP;
-
-    ecf8_internal::Plan plan;
-    rc = ecf8_internal::plan_encode(freq, rows, cols, opts, &plan);
-    if (rc) return rc;
-    const ecf8_header &h = plan.hdr;
-    if (h.total_size > blob_capacity) return ECF8_E_CAPACITY;
-    if (h.off_chunk_bit != off_cb || h.n_chunks != n_chunks) return ECF8_E_FORMAT;
 
     EncArgs a{};
-    a.x = x;
-    a.blob = blob;
-    a.n = n;
+    a.x = (uint64_t)(uintptr_t)d_fp8;
+    a.blob = (uint64_t)(uintptr_t)d_blob;
+    a.n = h.n_elem;
     a.cols = cols;
     a.n_chunks = h.n_chunks;
+    a.kc_per_row = tile_rows ? (uint32_t)(cols / (4ull * N)) : 1u;
     a.off_cb = h.off_chunk_bit;
     a.off_lb = h.off_lane_bits;
     a.off_st = h.off_stream;
-    a.off_pl = h.off_plane;
     a.group = group;
     a.tiled = tile_rows ? 1 : 0;
-    for (int i = 0; i < 16; i++) {
-        a.len_packed |= (uint64_t)h.code_len[i] << (4 * i);
-        a.code[i] = plan.code[i];
-        a.rcode[i] = plan.rcode[i];
+    const Ranges rg = make_ranges(h.n_chunks, (uint32_t)cus);
+    const uint64_t records = a.blob + h.off_stream;
+    static_assert(16 * 4 <= 32 * 32, "a record is smaller than a chunk's plane");
+
+    if (capturing(s)) return ECF8_E_HIP;
+    Mail mail;
+    if (N == 32) hipLaunchKernelGGL(histogram_kernel<32>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
+    else if (N == 64) hipLaunchKernelGGL(histogram_kernel<64>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
+    else hipLaunchKernelGGL(histogram_kernel<128>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
+    hipLaunchKernelGGL(plan_kernel<E4M3Codec>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, blob_capacity, records, lmax, mail.device());
+    if (lmax <= 7) {
+        if (N == 32) launch_encode<32, true>(a, rg, s);
+        else if (N == 64) launch_encode<64, true>(a, rg, s);
+        else launch_encode<128, true>(a, rg, s);
+    } else {
+        if (N == 32) launch_encode<32, false>(a, rg, s);
+        else if (N == 64) launch_encode<64, false>(a, rg, s);
+        else launch_encode<128, false>(a, rg, s);
     }
-    // pass 2: the container
-    uint32_t longest = 0;
-    for (int i = 0; i < 16; i++) longest = h.code_len[i] > longest ? h.code_len[i] : longest;
-    if (longest <= 7) rc = N == 32 ? launch_encode<32, true>(a, h, s) : N == 64 ? launch_encode<64, true>(a, h, s) : launch_encode<128, true>(a, h, s);
-    else rc = N == 32 ? launch_encode<32, false>(a, h, s) : N == 64 ? launch_encode<64, false>(a, h, s) : launch_encode<128, false>(a, h, s);
-    if (rc) return rc;
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
+    if (!mail.read(&h, a.blob, s)) return ECF8_E_HIP;
+    if (h.magic == 0) return (int)h.version;
     *hdr_out = h;
     return ECF8_OK;
 }

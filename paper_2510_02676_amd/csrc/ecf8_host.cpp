@@ -283,27 +283,18 @@ int check_options(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, ui
     return ECF8_OK;
 }
 
-int plan_encode(const uint64_t freq[16], uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, Plan *out)
+int plan_frame(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, ecf8_header *hdr)
 {
     uint32_t N, group, lmax, tile_rows, tmode;
     int rc = check_options(rows, cols, opts, &N, &group, &lmax, &tile_rows, &tmode);
     if (rc) return rc;
     const uint64_t n = rows * cols;
-    uint64_t fsum = 0;
-    for (int s = 0; s < 16; s++) fsum += freq[s];
-    if (fsum != n) return ECF8_E_ARG;
-    uint8_t len[16];
-    capped_lengths(freq, lmax, len);
-    if (!canonical(len, out->rcode, out->code)) return ECF8_E_FORMAT;
-    uint64_t bits = 0;
-    for (int s = 0; s < 16; s++) bits += freq[s] * len[s];
     const uint32_t table_bits = (tmode == 1 || (tmode == 0 && n >= (1ull << 22))) ? ECF8_TB : 0;
-    const Layout L = make_layout(n, bits, N, table_bits);
-    ecf8_header &h = out->hdr;
+    const Layout L = make_layout(n, 0, N, table_bits);
+    ecf8_header &h = *hdr;
     std::memset(&h, 0, sizeof(h));
     h.magic = ECF8_MAGIC;
     h.version = ECF8_VERSION;
-    h.total_size = L.total;
     h.n_elem = n;
     h.rows = rows;
     h.cols = cols;
@@ -312,14 +303,32 @@ int plan_encode(const uint64_t freq[16], uint64_t rows, uint64_t cols, const ecf
     h.group_chunks = (uint8_t)group;
     h.tile_rows = (uint8_t)tile_rows;
     h.n_chunks = L.n_chunks;
-    h.stream_bits = bits;
-    std::memcpy(h.code_len, len, 16);
     h.off_chunk_bit = L.off_cb;
     h.off_lane_bits = L.off_lb;
     h.off_stream = L.off_st;
+    h.plane_bytes = L.pl_bytes;
+    return ECF8_OK;
+}
+
+int plan_encode(const uint64_t freq[16], uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, Plan *out)
+{
+    ecf8_header &h = out->hdr;
+    int rc = plan_frame(rows, cols, opts, &h);
+    if (rc) return rc;
+    uint64_t fsum = 0;
+    for (int s = 0; s < 16; s++) fsum += freq[s];
+    if (fsum != h.n_elem) return ECF8_E_ARG;
+    uint8_t len[16];
+    capped_lengths(freq, (opts && opts->max_code_len) ? opts->max_code_len : ECF8_TB / 2, len);
+    if (!canonical(len, out->rcode, out->code)) return ECF8_E_FORMAT;
+    uint64_t bits = 0;
+    for (int s = 0; s < 16; s++) bits += freq[s] * len[s];
+    const Layout L = make_layout(h.n_elem, bits, h.lane_syms, h.table_bits);
+    h.total_size = L.total;
+    h.stream_bits = bits;
+    std::memcpy(h.code_len, len, 16);
     h.off_plane = L.off_pl;
     h.stream_bytes = L.st_bytes;
-    h.plane_bytes = L.pl_bytes;
     std::memcpy(h.freq, freq, 16 * sizeof(uint64_t));
     return ECF8_OK;
 }

@@ -25,6 +25,9 @@ struct Plan {
 int check_options(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, uint32_t *lane_syms,
                   uint32_t *group_chunks, uint32_t *max_code_len, uint32_t *tile_rows, uint32_t *table_mode);
 
+// The header as far as it does not depend on the weights: 0 in total_size, stream_bits, stream_bytes, off_plane, code_len and freq.
+int plan_frame(uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, ecf8_header *hdr);
+
 // From the exponent histogram of a rows x cols tensor: cheapest code under the cap, canonical
 // codewords, section layout, header.  Same result for the same inputs on every path.
 int plan_encode(const uint64_t freq[16], uint64_t rows, uint64_t cols, const ecf8_encode_opts *opts, Plan *out);

@@ -1,11 +1,10 @@
 // GPU-side encoder of the wide-alphabet codec (E5M2, BF16) for gfx950: Section 3.1 on the device
 // for 5- and 8-bit exponent fields.  Writes exactly the container ecfw_encode writes, byte for byte:
-// the code and the layout come from the same host routine, fed with the device histogram.
+// the same code under every cap, ties included, and the layout of the same routine.
 //
-//   fill 0 (header, code lengths, freq) -> histogram (and zeros in chunk_bit[]), written to the host by its last workgroup -> [host: code + layout]
-//   -> everything else in one pass over the elements, as in the E4M3 encoder (encode_tiles).
-// No scratch memory on the device: the histogram is counted into the freq section, tiles are drawn from the header's first dword, and what the
-// workgroups tell one another goes through chunk_bit[], all of them part of the output.
+//   histograms of ranges of chunks -> code, places of the ranges in the stream, header, code lengths, histogram (one workgroup; the host waits for the
+//   header) -> everything else, as in the E4M3 encoder (encode_range).
+// No scratch memory on the device: the ranges' histograms lie where the stream will.
 #include "ecfw.h"
 
 #include "ecf8_enc_device.h"
@@ -16,7 +15,7 @@ namespace {
 struct WEncArgs {
     uint64_t x, blob;                     // device addresses
     uint64_t n, n_chunks;
-    uint64_t off_len, off_cb, off_lb, off_st, off_pl, off_sg;
+    uint64_t off_cb, off_lb, off_st, off_pl, off_sg;
     uint32_t group;
 };
 
@@ -41,26 +40,22 @@ __device__ __forceinline__ ChunkPlace place_of(const WEncArgs &a, uint64_t c, ui
     return {c * E, 64 * P, lane * P};
 }
 
-// Histogram of the exponent field into A u64 counters, one workgroup of 16 waves per compute unit.
+// Histogram of the exponent field of each range into a record of A u32, one workgroup of 16 waves.
 //  * E5M2: bit planes.  32 elements are turned into five 32-bit words, one per exponent bit, and each of the 32 exponents
 //    is one AND and one population count that also adds: four vector operations per element, no LDS.
 //  * BF16: LDS counters in 64 copies, lane l of every wave in copy l = bank l, so that the lanes of a wave, most of which
-//    hold one of a handful of exponents, never meet.  58.7 M elements: 21 us, 5.5 TB/s (16 copies: 47 us).
-template <int FMT>
-__global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t n, uint64_t blob, uint64_t counters_, uint64_t chunk_bit, uint64_t n_chunks, uint64_t mail)
+//    hold one of a handful of exponents, never meet.  (16 copies: 47 us instead of 21 for 58.7 M elements.)
+// 58.7 M elements in a kernel trace: E5M2 18.3 us with the counts added to one record and summed by scans, 11.6 now; BF16 21.8 and 19.4, the read.
+template <int FMT, int N>
+__global__ __launch_bounds__(1024) void w_histogram_kernel(WEncArgs a, Ranges rg, uint64_t records)
 {
     constexpr int A = EFmt<FMT>::A, COPIES = FMT == ECFW_FMT_BF16 ? 64 : 1;
     __shared__ uint32_t s_cnt[A * COPIES];
-    const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)x_;
-    GLOBAL unsigned long long *counters = (GLOBAL unsigned long long *)counters_;
+    const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x;
+    GLOBAL uint32_t *record = (GLOBAL uint32_t *)records + (uint64_t)blockIdx.x * A;
     const int tid = threadIdx.x, lane = tid & 63;
     for (int i = tid; i < A * COPIES; i += 1024) s_cnt[i] = 0;
-    zero_chunk_bits(chunk_bit, n_chunks, (uint32_t)tid, 1024);
     __syncthreads();
-    // a wave takes 4 KiB per step: four loads of 1 KiB, of which a lane keeps the 16 bytes at 16 * lane
-    constexpr uint64_t PER = 4096 / EFmt<FMT>::ELEM;
-    const uint64_t steps = n / PER, stride = (uint64_t)gridDim.x * 16;
-    const GLOBAL u32x4 *p = (const GLOBAL u32x4 *)x + lane;
     uint32_t cnt[FMT == ECFW_FMT_E5M2 ? 32 : 1];
     if constexpr (FMT == ECFW_FMT_E5M2)
 #pragma unroll
@@ -93,24 +88,28 @@ __global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t
             }
         }
     };
-    for (uint64_t i = (uint64_t)blockIdx.x * 16 + (tid >> 6); i < steps; i += stride) {
-        const u32x4 va = p[i * 256], vb = p[i * 256 + 64], vc = p[i * 256 + 128], vd = p[i * 256 + 192];
-        count(va, vb);
-        count(vc, vd);
+    // a wave takes four pieces of 1 KiB per step
+    constexpr uint32_t STEPS = N / EFmt<FMT>::P / 4;
+    const uint64_t first = rg.begin(blockIdx.x);
+    const uint32_t size = rg.size(blockIdx.x), whole = size - ((first + size) * (64ull * N) > a.n ? 1u : 0u);
+    for (uint32_t i = uniform32(tid >> 6); i < whole * STEPS; i += 16) {
+        const ChunkPlace p = place_of<FMT, N>(a, first + whole - 1 - i / STEPS, (uint32_t)lane);       // the first chunks last: the next reader begins with them
+        const GLOBAL uint8_t *at = x + (p.base + p.lane_off + i % STEPS * 4 * p.stride) * EFmt<FMT>::ELEM;
+        u32x4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = *(const GLOBAL u32x4 *)(at + j * p.stride * EFmt<FMT>::ELEM);
+        count(v[0], v[1]);
+        count(v[2], v[3]);
     }
-    if (blockIdx.x == 0)
-        for (uint64_t i = steps * PER + tid; i < n; i += 1024) {
+    if (whole != size)
+        for (uint64_t i = (first + whole) * (64ull * N) + tid; i < a.n; i += 1024) {
             const uint32_t s = FMT == ECFW_FMT_E5M2 ? (x[i] >> 2) & 31u : (((const GLOBAL uint16_t *)x)[i] >> 7) & 255u;
             atomicAdd(&s_cnt[s * COPIES + (COPIES > 1 ? lane : 0)], 1u);
         }
     if constexpr (FMT == ECFW_FMT_E5M2) {
-#pragma unroll
-        for (int s = 0; s < 32; s++) {
-            const uint32_t sum = wave_incl_scan(cnt[s]);
-            if (lane == 63 && sum) atomicAdd(&s_cnt[s], sum);
-        }
+        add_counts<32>(cnt, s_cnt, lane);
         __syncthreads();
-        if (tid < A && s_cnt[tid]) atomicAdd((unsigned long long *)(counters + tid), (unsigned long long)s_cnt[tid]);
+        if (tid < A) record[tid] = s_cnt[tid];
     } else {
         __syncthreads();
         // four threads per exponent, 16 copies each, started apart so that a wave's reads fall into different banks
@@ -120,26 +119,37 @@ __global__ __launch_bounds__(1024) void w_histogram_kernel(uint64_t x_, uint64_t
         for (int k = 0; k < 16; k++) sum += s_cnt[s * COPIES + part * 16 + ((k + s) & 15)];
         sum += __shfl_xor(sum, 1, 64);
         sum += __shfl_xor(sum, 2, 64);
-        if (part == 0 && sum) atomicAdd((unsigned long long *)(counters + s), (unsigned long long)sum);
+        if (part == 0) record[s] = sum;
     }
-    mail_histogram<A>(blob, counters_, mail);
 }
 
-struct WCodeArgs {
-    ecfw_header h;
-    uint16_t code[256];                   // canonical codewords, first bit most significant
-    uint8_t len[256];
+// What plan_kernel has to know of these codecs.
+template <int FMT>
+struct WCodec {
+    static constexpr int A = EFmt<FMT>::A;
+    typedef ecfw_header Header;
+    static __device__ __forceinline__ uint64_t size(const Header &h, uint64_t behind) { return h.sign_bytes ? (behind + h.sign_bytes + 255) / 256 * 256 : behind; }
+    static __device__ __forceinline__ void finish(Header &h, GLOBAL uint8_t *blob, uint64_t behind, const uint64_t *freq, const uint32_t *len, uint32_t m, uint32_t longest, bool write, int lane)
+    {
+        if (lane == 0) {
+            h.max_code_len = longest;
+            h.n_symbols = m;
+            h.off_sign = h.sign_bytes ? behind : 0;
+        }
+        if (!write) return;
+        uint32_t four = 0;                                  // zeros behind the last
+        if (4 * lane < A) four = len[4 * lane] | len[4 * lane + 1] << 8 | len[4 * lane + 2] << 16 | len[4 * lane + 3] << 24;
+        ((GLOBAL uint32_t *)(blob + h.off_code_len))[lane] = four;
+        for (int s = lane; s < A; s += 64) ((GLOBAL uint64_t *)(blob + h.off_freq))[s] = freq[s];
+    }
 };
 
-// What of the container is neither chunk data nor stream, but for the header, by the first workgroup (the freq section already
-// holds the histogram): code lengths, zeros in the gaps between sections and behind the last dword of the stream.
-__device__ __forceinline__ void write_fixed(const WEncArgs &a, const WCodeArgs &ca)
+// What of the container is neither chunk data nor stream, header or code, by the first workgroup: zeros in the gaps between sections and behind the last dword of the stream.
+__device__ __forceinline__ void write_fixed(const WEncArgs &a, const __attribute__((address_space(4))) ecfw_header &h)
 {
     if (blockIdx.x != 0) return;
     const uint32_t tid = threadIdx.x;
     GLOBAL uint8_t *blob = (GLOBAL uint8_t *)a.blob;
-    const ecfw_header &h = ca.h;
-    if (tid * 4 < h.n_alphabet) *(GLOBAL uint32_t *)(blob + a.off_len + 4 * tid) = ((const uint32_t *)ca.len)[tid];
     auto zero = [&](uint64_t from, uint64_t to) {       // multiples of four
         for (uint64_t i = from + 4 * tid; i < to; i += 4 * blockDim.x) *(GLOBAL uint32_t *)(blob + i) = 0;
     };
@@ -150,24 +160,22 @@ __device__ __forceinline__ void write_fixed(const WEncArgs &a, const WCodeArgs &
     if (h.sign_bytes) zero(a.off_sg + h.sign_bytes, h.total_size);
 }
 
-// A chunk on its way through encode_tiles, as in the E4M3 encoder.  The codewords come from the host with the launch.  LMAX: the longest codeword
-// in use is at most this.  Look-ups:
+// A chunk on its way through encode_range, as in the E4M3 encoder.  LMAX: the longest codeword in use is at most this.  Look-ups:
 //  * BF16 one symbol at a time (256 of them would make a pair table of 256 KiB), E5M2 up to 12 bits two at a time; codeword(s) and from
 //    bit 27 on their length in one dword, so that joining two of them is one operation.
 //  * QUADS (up to 12 bits): count joins four codewords and leaves them in the place of their elements, for pack to put them in one go.
 //    They are nearly always less than 32 bits; a chunk where they are not is fetched again and packed two codewords at a time.
-// What bounds it: BF16, at 4.7 TB/s, nearly a copy's rate; E5M2 the vector operations (with elements looked up one by one in count and again in
-// pack the kernel took 5 us more for 14336 x 4096, BF16's 1).
 template <int FMT, int N, int LMAX>
 struct Chunk {
     using F = EFmt<FMT>;
     static constexpr int P = F::P, A = F::A, PIECES = N / P;
+    static constexpr bool ANY = LMAX > 15;                                          // two codewords may have 32 bits
     static constexpr bool QUADS = LMAX <= 12 && PIECES <= 8, PAIRS = QUADS && FMT == ECFW_FMT_E5M2;
     static constexpr uint32_t BITS = (1u << 27) - 1;                                // of a dword that holds codewords and their length
     static constexpr int PAIR_ENTRIES = PAIRS ? A * A : 1;
-    static constexpr int AREA = ((160 * 1024 - 1024 - 8 * (A + 1) - 256 - 8 * PAIR_ENTRIES) / (4 * WMAX) - 4) / 4 * 4;
-    static constexpr int TAIL_FROM = PIECES - 32 / P;                               // a lane's last 32 codewords
-    static_assert(32 * LMAX < 32 * LATE_DWORDS && N * LMAX * LATE_LANES <= 32 * (AREA - 4), "room for late chunks");
+    static constexpr int MOST = (160 * 1024 - 4096 - 8 * (A + 1) - 256 - 8 * PAIR_ENTRIES) / (4 * WMAX) / 4 * 4;
+    static constexpr int AREA = 2 * N * LMAX + 4 < MOST ? 2 * N * LMAX + 4 : MOST;   // a chunk whatever it is, if there is room
+    static_assert(N * LMAX + 4 <= AREA && AREA % 4 == 0, "half a chunk");
 
     const WEncArgs &a;
     const uint32_t (*code)[A + 1];          // code | length << 27, first bit lowest / highest; A = no symbol
@@ -263,14 +271,14 @@ struct Chunk {
         const uint32_t t = (w >> 2) & 0x1f1f1f1fu;
         return bit_select(0x001f001fu, t, t >> 3);
     }
-    static __device__ __forceinline__ void put2(LanePacker &out, uint32_t x0, uint32_t x1)
+    static __device__ __forceinline__ void put2(LanePacker<ANY> &out, uint32_t x0, uint32_t x1)
     {
         uint32_t nb;
         const uint32_t x = LMAX <= 13 ? joined(x0, x1, nb) : (x0 & 0xffffu) | ((x1 & 0xffffu) << (x0 >> 27));
         out.put(x, LMAX <= 13 ? nb : (x0 >> 27) + (x1 >> 27));
     }
     template <bool BACK>
-    __device__ __forceinline__ void put_piece(LanePacker &out, const u32x4 &v4) const
+    __device__ __forceinline__ void put_piece(LanePacker<ANY> &out, const u32x4 &v4) const
     {
         const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w};
 #pragma unroll
@@ -279,25 +287,25 @@ struct Chunk {
     }
     // what count has left of a piece
     template <bool BACK>
-    __device__ __forceinline__ void put_quads(LanePacker &out, const u32x4 &v4) const
+    __device__ __forceinline__ void put_quads(LanePacker<ANY> &out, const u32x4 &v4) const
     {
         const uint32_t w[4] = {v4.x, v4.y, v4.z, v4.w};
         if constexpr (PAIRS) {
 #pragma unroll
             for (int k = 0; k < 4; k++) {
-                const uint32_t x = w[BACK ? 3 - k : k], nb = 31u - (uint32_t)__builtin_clz(x);
-                out.put(x ^ (1u << nb), nb);
+                const uint32_t x = w[BACK ? 3 - k : k];
+                out.put(x, 31u ^ (uint32_t)__builtin_clz(x));
             }
         } else {
             out.put(w[0], w[1]);
             out.put(w[2], w[3]);
         }
     }
-    __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t c, bool refill)
+    __device__ __forceinline__ void pack(uint32_t *image, uint32_t at, uint64_t c, uint64_t next, bool refill)
     {
-        LanePacker out(image, at);
+        LanePacker<ANY> out(image, at);
         if (QUADS && wide) fetch(c);
-        const ChunkPlace p = place_of<FMT, N>(a, c + 1, lane);
+        const ChunkPlace p = place_of<FMT, N>(a, next, lane);
         const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x + (p.base + p.lane_off) * F::ELEM;
         if (!QUADS || wide) {
 #pragma unroll
@@ -340,16 +348,15 @@ struct Chunk {
         }
         return lb;
     }
-    // from the lane's i0-th piece on; the image's bit behind the last one
-    __device__ __forceinline__ uint32_t slow_pack(uint32_t *image, uint32_t at, uint64_t c, int i0)
+    __device__ __forceinline__ void slow_pack(uint32_t *image, uint32_t at, uint64_t c)
     {
         const ChunkPlace p = place_of<FMT, N>(a, c, lane);
-        LanePacker out(image, at);
+        LanePacker<ANY> out(image, at);
         const uint64_t e0 = p.base + p.lane_off;
         const uint32_t stride = (uint32_t)p.stride;
         auto at_piece = [&](int i) { return e0 + (uint32_t)(i >= PIECES / 2 ? PIECES - 1 - (i - PIECES / 2) : i) * stride; };
 #pragma unroll 1
-        for (int i = i0; i < PIECES; i++) {
+        for (int i = 0; i < PIECES; i++) {
             const bool back = i >= PIECES / 2;
             const u32x4 w = slow_fetch(at_piece(i));
             uint32_t s[P];
@@ -358,115 +365,131 @@ struct Chunk {
             for (int j = 0; j < P; j += 2) put2(out, back ? s[P - 1 - j] : s[j], back ? s[P - 2 - j] : s[j + 1]);
         }
         out.finish();
-        return out.end(image);
+    }
+    // the last 32 bits of a whole chunk: those of the first codewords of lane 63's backward run, of which each lane looks up one
+    __device__ __forceinline__ uint32_t tail(uint64_t c) const
+    {
+        const ChunkPlace p = place_of<FMT, N>(a, c, 63);
+        const uint32_t s = N / 2 + ((uint32_t)lane & 31);
+        const uint64_t e = p.base + p.lane_off + s / P * p.stride + s % P;
+        const GLOBAL uint8_t *x = (const GLOBAL uint8_t *)a.x;
+        const uint32_t v = code[1][FMT == ECFW_FMT_E5M2 ? (x[e] >> 2) & 31u : (((const GLOBAL uint16_t *)x)[e] >> 7) & 255u];
+        return last_bits(v & BITS, v >> 27, lane);
     }
 };
 
-// The container behind the code.  58.7 M elements (14336 x 4096): in a kernel trace (the last 100 of 300 calls) BF16 42 us for the 198 MB read and
-// written, E5M2 35 for 101 MB (some 20 more with metadata and planes, prefix sum and packing as kernels of their own).  The whole call 108 -> 84 us and
-// 85 -> 64, 16384 x 16384 454 -> 310 and 250 -> 207.
+// The container behind the code.  58.7 M elements (14336 x 4096): in a kernel trace BF16 34.7 us for the 198 MB read and written, nearly a copy's rate, and E5M2 26.6,
+// three quarters of it vector operations (42.7 and 35.6 when the workgroups had to find their place in the stream from one another).  The whole call
+// 84.8 -> 76.3 and 64 -> 48, 16384 x 16384 312 -> 274 and 204 -> 159.
 template <int FMT, int N, int LMAX>
-__global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, WCodeArgs ca, uint32_t per_wave)
+__global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, Ranges rg)
 {
     using K = Chunk<FMT, N, LMAX>;
     constexpr int A = K::A;
-    __shared__ __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA + 4];  // the last of the four in front is image[-1]
-    __shared__ uint32_t s_code[2][A + 1];
-    __shared__ uint32_t s_pair[2][K::PAIR_ENTRIES];
-    __shared__ uint32_t s_len4[64];
-    __shared__ TileShared sh;
+    __shared__ struct {                                     // the tables where a look-up needs no address of theirs
+        uint32_t pair[2][K::PAIR_ENTRIES];
+        uint32_t code[2][A + 1];
+        uint32_t len4[64];
+        RangeShared range;
+        __attribute__((aligned(16))) uint32_t images[WMAX][K::AREA];
+    } s;
     const uint32_t tid = threadIdx.x;
-    const int wave = (int)uniform32(tid >> 6);
-    if (tid < (uint32_t)A) {
-        const uint32_t code = ca.code[tid], l = ca.len[tid];
-        s_code[0][tid] = l ? (__brev(code) >> (32 - l)) | (l << 27) : 0u;
-        s_code[1][tid] = code | (l << 27);
+    const int wave = (int)uniform32(tid >> 6), lane = (int)(tid & 63);
+    // before the first chunk is asked for: loads come back in order
+    const uint32_t four = wave == 0 ? ((const GLOBAL uint32_t *)(a.blob + 256))[lane] : 0u;
+    K k{a, s.code, s.pair, (const uint8_t *)s.len4, lane, {}, false};
+    const uint64_t c0 = rg.begin(blockIdx.x) + wave;
+    if ((uint32_t)wave < rg.size(blockIdx.x) && k.whole(c0)) k.fetch(c0);
+    const auto &h = planned<ecfw_header>(a.blob);
+    if (h.magic == 0) return;                               // no blob
+    a.off_pl = h.off_plane;
+    a.off_sg = h.off_sign;
+    range_begin(s.range);
+    if (wave == 0) {
+        s.len4[lane] = four;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // canonical codewords: lane l has symbols l, l + 64, ..., ranked among those of their length
+        constexpr int PER = (A + 63) / 64;
+        uint32_t len[PER], code[PER], begin = 0;
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            len[i] = lane + 64 * i < A ? ((const uint8_t *)s.len4)[lane + 64 * i] : 0u;
+            code[i] = 0;
+        }
+#pragma unroll 1
+        for (uint32_t l = 1; l <= (uint32_t)LMAX; l++) {
+#pragma unroll
+            for (int i = 0; i < PER; i++) {
+                const uint64_t there = __ballot(len[i] == l);
+                code[i] = len[i] == l ? begin + (uint32_t)__builtin_popcountll(there & ((1ull << lane) - 1)) : code[i];
+                begin += (uint32_t)__builtin_popcountll(there);
+            }
+            begin <<= 1;
+        }
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+            if (lane + 64 * i < A) {
+                s.code[0][lane + 64 * i] = len[i] ? (__brev(code[i]) >> (32 - len[i])) | (len[i] << 27) : 0u;
+                s.code[1][lane + 64 * i] = code[i] | (len[i] << 27);
+            }
+        if (lane < 2) s.code[lane][A] = 0;
     }
-    if (tid < 2) s_code[tid][A] = 0;
-    if (tid < 64) s_len4[tid] = ((const uint32_t *)ca.len)[tid];
+    __syncthreads();
     if constexpr (K::PAIRS) {
-        __syncthreads();
         for (uint32_t i = tid; i < (uint32_t)K::PAIR_ENTRIES; i += blockDim.x) {
             const uint32_t lo = i % A, hi = i / A;          // an entry's first and second element
             uint32_t nb;
-            s_pair[0][i] = K::joined(s_code[0][lo], s_code[0][hi], nb);
-            s_pair[1][i] = K::joined(s_code[1][hi], s_code[1][lo], nb) | (nb << 27);
-            s_pair[0][i] |= nb << 27;
+            s.pair[0][i] = K::joined(s.code[0][lo], s.code[0][hi], nb);
+            s.pair[1][i] = K::joined(s.code[1][hi], s.code[1][lo], nb) | (nb << 27);
+            s.pair[0][i] |= nb << 27;
         }
+        __syncthreads();
     }
-    write_fixed(a, ca);
-    K k{a, s_code, s_pair, (const uint8_t *)s_len4, (int)(tid & 63), {}, false};
-    encode_tiles(k, sh, images[wave] + 4, TileArgs{a.n_chunks, per_wave, (const uint32_t *)&ca.h}, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st,
-                 (int)(tid & 63), wave);
+    write_fixed(a, h);
+    encode_range(k, s.range, s.images[wave], rg, (GLOBAL uint8_t *)a.blob, a.off_cb, a.off_lb, a.off_st, h.stream_bytes / 4, lane, wave);
 }
 
-template <int FMT, int N, int LMAX>
-int launch_encode(const WEncArgs &a, const WCodeArgs &ca, hipStream_t s)
+template <int FMT, int N>
+void launch(const WEncArgs &a, const ecfw_header &h, const Ranges &rg, uint64_t capacity, uint32_t lmax, uint64_t mail, hipStream_t s)
 {
-    const int cus = device_cus();
-    if (cus <= 0) return ECF8_E_HIP;
-    using K = Chunk<FMT, N, LMAX>;
-    const TilePlan p = plan_tiles<K::AREA>(a.n_chunks, ca.h.stream_bits, (uint32_t)cus);
-    hipLaunchKernelGGL((w_encode_kernel<FMT, N, LMAX>), dim3(p.grid), dim3(p.waves * 64), 0, s, a, ca, p.per_wave);
-    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+    const uint64_t records = a.blob + h.off_stream;
+    static_assert(EFmt<FMT>::A * 4 <= 16 * N, "a record is smaller than a chunk's plane");
+    const dim3 waves(range_waves(rg) * 64);
+    hipLaunchKernelGGL((w_histogram_kernel<FMT, N>), dim3(rg.count), dim3(1024), 0, s, a, rg, records);
+    hipLaunchKernelGGL(plan_kernel<WCodec<FMT>>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, capacity, records, lmax, mail);
+    if (lmax <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(rg.count), waves, 0, s, a, rg);
+    else hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_MAX_CODE_LEN>), dim3(rg.count), waves, 0, s, a, rg);
 }
 
 template <int FMT>
 int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N, uint32_t group, uint32_t lmax, void *d_blob,
                   uint64_t blob_capacity, ecfw_header *hdr_out, hipStream_t s)
 {
-    constexpr int A = EFmt<FMT>::A;
-    const uint64_t n = rows * cols;
-    const uint64_t blob = (uint64_t)(uintptr_t)d_blob, x = (uint64_t)(uintptr_t)d_elems;
-    // the sections in front of chunk_bit have fixed places: header 256, code_len 256, freq 8A rounded up
-    const uint64_t off_freq = 512, fixed = off_freq + (8ull * A + 255) / 256 * 256;
-    const uint64_t n_chunks = (n + 64ull * N - 1) / (64ull * N);
-    if (blob_capacity < fixed + 8 * (n_chunks + 1)) return ECF8_E_CAPACITY;         // no blob of this tensor is that small
-
-    // pass 1: histogram, counted into the blob's freq section
+    ecfw_header h;
+    int rc = ecfw_internal::plan_frame(FMT, rows, cols, N, group, &h);
+    if (rc) return rc;
+    if (blob_capacity < h.off_stream + h.plane_bytes + h.sign_bytes) return ECF8_E_CAPACITY;      // no blob of this tensor is that small, and the ranges' histograms fit
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
-    if (capturing(s)) return ECF8_E_HIP;
-    Mail mail;
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, blob, fixed);
-    const uint64_t hist_blocks = (n * EFmt<FMT>::ELEM / 4096 + 15) / 16, hist_most = (uint64_t)cus;
-    hipLaunchKernelGGL(w_histogram_kernel<FMT>, dim3((uint32_t)(hist_blocks < 1 ? 1 : hist_blocks < hist_most ? hist_blocks : hist_most)), dim3(1024), 0, s,
-                       x, n, blob, blob + off_freq, blob + fixed, n_chunks, mail.device());
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
-    uint64_t freq[256] = {};
-    if (!mail.read(freq, A, blob + off_freq, s)) return ECF8_E_HIP;
 
-    ecfw_internal::WPlan plan;
-    int rc = ecfw_internal::plan_encode(freq, FMT, rows, cols, N, group, lmax, &plan);
-    if (rc) return rc;
-    const ecfw_header &h = plan.hdr;
-    if (h.total_size > blob_capacity) return ECF8_E_CAPACITY;
-    if (h.off_freq != off_freq || h.off_chunk_bit != fixed || h.n_chunks != n_chunks) return ECF8_E_FORMAT;
-
-    // pass 2: the container
     WEncArgs a{};
-    a.x = x;
-    a.blob = blob;
-    a.n = n;
+    a.x = (uint64_t)(uintptr_t)d_elems;
+    a.blob = (uint64_t)(uintptr_t)d_blob;
+    a.n = h.n_elem;
     a.n_chunks = h.n_chunks;
-    a.off_len = h.off_code_len;
     a.off_cb = h.off_chunk_bit;
     a.off_lb = h.off_lane_bits;
     a.off_st = h.off_stream;
-    a.off_pl = h.off_plane;
-    a.off_sg = h.off_sign;
     a.group = group;
-    WCodeArgs ca;
-    ca.h = h;
-    for (int i = 0; i < 256; i++) {
-        ca.len[i] = plan.len[i];
-        ca.code[i] = (uint16_t)plan.code[i];
-    }
-    if (h.max_code_len <= ECFW_TABLE_BITS)
-        rc = N == 64 ? launch_encode<FMT, 64, (int)ECFW_TABLE_BITS>(a, ca, s) : launch_encode<FMT, 128, (int)ECFW_TABLE_BITS>(a, ca, s);
-    else
-        rc = N == 64 ? launch_encode<FMT, 64, (int)ECFW_MAX_CODE_LEN>(a, ca, s) : launch_encode<FMT, 128, (int)ECFW_MAX_CODE_LEN>(a, ca, s);
-    if (rc) return rc;
+    const Ranges rg = make_ranges(h.n_chunks, (uint32_t)cus);
+
+    if (capturing(s)) return ECF8_E_HIP;
+    Mail mail;
+    if (N == 64) launch<FMT, 64>(a, h, rg, blob_capacity, lmax, mail.device(), s);
+    else launch<FMT, 128>(a, h, rg, blob_capacity, lmax, mail.device(), s);
+    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
+    if (!mail.read(&h, a.blob, s)) return ECF8_E_HIP;
+    if (h.magic == 0) return (int)h.version;
     *hdr_out = h;
     return ECF8_OK;
 }

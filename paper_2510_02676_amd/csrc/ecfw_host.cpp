@@ -219,6 +219,33 @@ int check_options(const ecfw_encode_opts *opts, uint64_t rows, uint64_t cols, ui
     return ECF8_OK;
 }
 
+int plan_frame(uint32_t fmt, uint64_t rows, uint64_t cols, uint32_t N, uint32_t group, ecfw_header *hdr)
+{
+    Format f;
+    if (!format_of(fmt, &f)) return ECF8_E_ARG;
+    const Sections L = make_sections(f, rows * cols, 0, N);
+    ecfw_header &h = *hdr;
+    std::memset(&h, 0, sizeof(h));
+    h.magic = ECFW_MAGIC;
+    h.version = ECFW_VERSION;
+    h.n_elem = rows * cols;
+    h.rows = rows;
+    h.cols = cols;
+    h.fmt = fmt;
+    h.lane_syms = N;
+    h.group_chunks = group;
+    h.n_alphabet = f.alphabet;
+    h.n_chunks = L.n_chunks;
+    h.off_code_len = L.off_len;
+    h.off_freq = L.off_freq;
+    h.off_chunk_bit = L.off_cb;
+    h.off_lane_bits = L.off_lb;
+    h.off_stream = L.off_st;
+    h.plane_bytes = L.pl_bytes;
+    h.sign_bytes = L.sg_bytes;
+    return ECF8_OK;
+}
+
 int plan_encode(const uint64_t *freq, uint32_t fmt, uint64_t rows, uint64_t cols, uint32_t N, uint32_t group,
                 uint32_t lmax, WPlan *out)
 {
@@ -239,32 +266,16 @@ int plan_encode(const uint64_t *freq, uint32_t fmt, uint64_t rows, uint64_t cols
         maxlen = std::max<uint32_t>(maxlen, out->len[s]);
         nsym += freq[s] != 0;
     }
-    const Sections L = make_sections(f, n, bits, N);
     ecfw_header &h = out->hdr;
-    h.magic = ECFW_MAGIC;
-    h.version = ECFW_VERSION;
+    plan_frame(fmt, rows, cols, N, group, &h);
+    const Sections L = make_sections(f, n, bits, N);
     h.total_size = L.total;
-    h.n_elem = n;
-    h.rows = rows;
-    h.cols = cols;
-    h.fmt = fmt;
-    h.lane_syms = N;
-    h.group_chunks = group;
     h.max_code_len = maxlen;
-    h.n_alphabet = A;
     h.n_symbols = nsym;
-    h.n_chunks = L.n_chunks;
     h.stream_bits = bits;
-    h.off_code_len = L.off_len;
-    h.off_freq = L.off_freq;
-    h.off_chunk_bit = L.off_cb;
-    h.off_lane_bits = L.off_lb;
-    h.off_stream = L.off_st;
     h.off_plane = L.off_pl;
     h.off_sign = L.off_sg;
     h.stream_bytes = L.st_bytes;
-    h.plane_bytes = L.pl_bytes;
-    h.sign_bytes = L.sg_bytes;
     return ECF8_OK;
 }
 

@@ -20,6 +20,9 @@ struct WPlan {
 int check_options(const ecfw_encode_opts *opts, uint64_t rows, uint64_t cols, uint32_t *lane_syms,
                   uint32_t *group_chunks, uint32_t *max_code_len);
 
+// The header as far as it does not depend on the elements: 0 in total_size, max_code_len, n_symbols, stream_bits, stream_bytes, off_plane and off_sign.
+int plan_frame(uint32_t fmt, uint64_t rows, uint64_t cols, uint32_t lane_syms, uint32_t group_chunks, ecfw_header *hdr);
+
 // From the exponent-field histogram of a rows x cols tensor: cheapest code under the cap, canonical
 // codewords, section layout, header.  Same result for the same inputs on every path.
 int plan_encode(const uint64_t *freq, uint32_t fmt, uint64_t rows, uint64_t cols, uint32_t lane_syms,

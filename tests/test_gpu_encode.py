@@ -244,6 +244,61 @@ def test_special_histograms(orc):
             _check_same(orc, x, 1, x.size, max_code_len=cap)
 
 
+def _of_counts(counts, seed):
+    """A tensor in which exponent s occurs counts[s] times, shuffled."""
+    rng = np.random.default_rng(seed)
+    e = np.repeat(np.arange(len(counts), dtype=np.uint8), counts)
+    rng.shuffle(e)
+    return (e << 3) | (rng.integers(0, 256, e.size, dtype=np.uint8) & 0x87)
+
+
+@pytest.mark.parametrize("cap", [4, 5, 6, 7, 8, 11, 15])
+def test_codes_of_equal_counts(cap):
+    """The code is made on the device: of the many cheapest codes that equal counts and sums of counts allow it has to find the CPU encoder's."""
+    rng = np.random.default_rng(cap)
+    for i in range(40):
+        m = int(rng.integers(1, 17))
+        counts = np.zeros(16, np.int64)
+        kind = [rng.integers(1, 3, m), 2 ** rng.integers(0, 9, m), np.sort(rng.integers(1, 2000, m)), np.maximum(1, (3000 * 0.55 ** np.arange(m)).astype(np.int64)),
+                np.full(m, 7)][i % 5]
+        counts[rng.choice(16, m, replace=False)] = kind
+        x = _of_counts(counts, i)
+        want = ecf8.ecf8_encode(x, 1, x.size, max_code_len=cap)
+        hdr, blob = ecf8.ecf8_encode_gpu(torch.from_numpy(x).to(DEV), 1, x.size, max_code_len=cap)
+        assert bytes(hdr) == bytes(want.header), (cap, list(counts))
+        assert np.array_equal(blob.cpu().numpy(), want.numpy()), (cap, list(counts))
+
+
+@pytest.mark.parametrize("chunks", [255, 256, 257, 511, 65537])
+def test_borders_of_ranges(chunks):
+    """A range of chunks per compute unit, of 256 at the most: one less and more than the compute units of a whole chip, of one chunk and two, of one range and two per
+    compute unit; row-tiled, where no chunk is ragged, too."""
+    x = np.resize(_rand_bytes((1 << 20) + 77, chunks, conc=1.0), chunks * 2048)
+    for opts in (dict(lane_syms=32), dict(lane_syms=32, max_code_len=9), dict(lane_syms=32, tile_rows=16)):
+        rows, n = (16, x.size) if "tile_rows" in opts else (1, x.size - 5)
+        want = ecf8.ecf8_encode(x[:n], rows, n // rows, **opts)
+        hdr, blob = ecf8.ecf8_encode_gpu(torch.from_numpy(x[:n]).to(DEV), rows, n // rows, **opts)
+        assert bytes(hdr) == bytes(want.header)
+        assert torch.equal(blob.cpu(), torch.from_numpy(want.numpy()))
+
+
+def test_a_buffer_of_the_blobs_size_and_one_byte_less():
+    """That the blob does not fit is found on the device; the next call is none the wiser."""
+    x = _rand_bytes(300_001, 9)
+    d_x, want = torch.from_numpy(x).to(DEV), ecf8.ecf8_encode(x, 1, x.size)
+    for room in (want.size, want.size - 1, want.header.off_stream + want.header.plane_bytes, want.header.off_stream + want.header.plane_bytes - 1):
+        buf = torch.full((want.size + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+        if room == want.size:
+            hdr, blob = ecf8.ecf8_encode_gpu(d_x, 1, x.size, d_blob=buf[:room])
+            assert bytes(hdr) == bytes(want.header) and np.array_equal(blob.cpu().numpy(), want.numpy())
+        else:
+            with pytest.raises(ecf8.Ecf8Error) as e:
+                ecf8.ecf8_encode_gpu(d_x, 1, x.size, d_blob=buf[:room])
+            assert e.value.code == ecf8.E_CAPACITY
+        torch.cuda.synchronize()
+        assert bool((buf[room:] == 0xA5).all())
+
+
 def test_config0_and_a_full_size_matrix(orc):
     w = synth.make(synth.config0()[0], seed=0).numpy()
     _check_same(orc, w.reshape(-1), 1024, 1024)

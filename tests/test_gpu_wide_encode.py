@@ -187,6 +187,28 @@ def test_more_chunks_than_one_launch_takes():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("fmt,m", [(E5M2, 1), (E5M2, 2), (E5M2, 31), (E5M2, 32), (BF16, 1), (BF16, 2), (BF16, 3), (BF16, 40), (BF16, 63), (BF16, 64), (BF16, 65), (BF16, 130), (BF16, 256)])
+def test_codes_of_equal_counts(fmt, m):
+    """The code is made on the device, by all waves for up to 64 exponents and by one for more: the CPU encoder's also where counts and sums of counts are equal."""
+    rng = np.random.default_rng(m)
+    for i, cap in enumerate([5, 8, 9, 12, 12, 12, 16, 16]):
+        counts = np.zeros(32 if fmt == E5M2 else 256, np.int64)
+        kind = [rng.integers(1, 3, m), 2 ** rng.integers(0, 12, m), np.maximum(1, (20000 * 0.6 ** np.arange(m)).astype(np.int64)), np.full(m, 9)][i % 4]
+        counts[rng.choice(counts.size, m, replace=False)] = kind
+        e = np.repeat(np.arange(counts.size), counts)
+        rng.shuffle(e)
+        x = (e << 7).astype(np.uint16) if fmt == BF16 else (e << 2).astype(np.uint8)
+        if m > 1 << cap:
+            with pytest.raises(ecf8.Ecf8Error) as err:
+                ecfw.ecfw_encode_gpu(fmt, _to_dev(fmt, x), 1, x.size, max_code_len=cap)
+            assert err.value.code == ecf8.E_ARG
+            continue
+        want = ecfw.ecfw_encode(fmt, x, 1, x.size, max_code_len=cap)
+        hdr, blob = ecfw.ecfw_encode_gpu(fmt, _to_dev(fmt, x), 1, x.size, max_code_len=cap)
+        assert bytes(hdr) == bytes(want.header), (cap, kind)
+        assert np.array_equal(blob.cpu().numpy(), want.numpy()), (cap, kind)
+
+
 def test_argument_errors():
     x = torch.zeros(10000, dtype=torch.int16, device=DEV)
     with pytest.raises(ecf8.Ecf8Error) as e:
