@@ -64,6 +64,7 @@ struct KArgs {
     uint32_t max_code_len;                // longest codeword of any tensor of the launch
     uint32_t max_workgroups;              // 0 = one per compute unit
     uint32_t row_tiled;                   // every tensor of the launch is in the row-tiled layout
+    ChunkDeal deal;                       // of the launch's chunks to its workgroups
 };
 
 template <int N, int WAVES, bool PAIRFIT, bool TILED = false>
@@ -121,56 +122,34 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
     const uint32_t stage_off = C::OFF_WAVES + wave * C::STAGE;   // byte offset into smem
     uint8_t *stage = smem + stage_off;
 
-    // contiguous range of the batch's chunks for this workgroup, cut at multiples of 64 or 8 chunks
-    // where that leaves every workgroup at least 16 such units (shares then differ by 1/16 at most),
-    // so that the waves of a workgroup share the interleaved groups of the layout
-    const uint64_t NWG = gridDim.x, wg = blockIdx.x;
-    const uint64_t unit = a.total_chunks >= NWG * 1024 ? 64 : a.total_chunks >= NWG * 128 ? 8 : 1;   // >= 16 units each: shares differ by 1/16 at most
-    const uint64_t units = (a.total_chunks + unit - 1) / unit;
-    uint64_t c = units * wg / NWG * unit;
-    uint64_t c_end = units * (wg + 1) / NWG * unit;
-    if (c_end > a.total_chunks) c_end = a.total_chunks;
+    // Chunk numbers have 32 bits: 2^32 chunks are 8 TiB or more.
+    const uint32_t c0 = a.deal.begin(blockIdx.x), c_past = a.deal.begin(blockIdx.x + 1), c_all = (uint32_t)a.total_chunks;
+    const uint32_t c_end = c_past < c_all ? c_past : c_all;
+    uint32_t c = c0;
     while (c < c_end) {
         // which tensor holds chunk c (uniform)
-        uint64_t d_blob, d_out, n_elem, n_chunks, first_chunk, off_cb, off_lb, off_st, off_pl, st_bytes;
+        uint32_t n_chunks, first_chunk;
+        uint64_t d_blob, d_out, n_elem, off_cb, off_lb, off_st, off_pl, st_bytes;
         uint64_t len_lo, len_hi, off_tbl, group, tcols;
         if (a.items) {
-            // 64-way search, a round trip to memory per level instead of one per halving: lane l probes the
-            // l-th of 64 evenly spaced items of the remaining range (first_chunk is increasing, so the lanes
-            // that pass form a prefix)
-            uint32_t lo = 0, n = a.n_items;
-            while (n > 1) {
-                const uint32_t stride = (n + 63) / 64;
-                const uint32_t at = (uint32_t)lane * stride;
-                const bool pass = at < n && a.items[lo + at].first_chunk <= c;
-                const uint32_t k = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pass));
-                const uint32_t step = k ? (k - 1) * stride : 0;       // k >= 1 for a valid table: items[lo].first_chunk <= c
-                lo += step;
-                n = n - step < stride ? n - step : stride;
-            }
-            // the item's 16 words by one load of 16 lanes, then into scalar registers: the fields are the same
-            // for every lane and live as long as the tensor
-            const uint64_t word = ((const GLOBAL uint64_t *)(a.items + lo))[lane & 15];
-            auto field = [&](int k) -> uint64_t {
-                return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, k) |
-                       ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), k) << 32);
-            };
+            const BatchItem item(a.items, a.n_items, c, lane);
+            auto field = [&](int k) -> uint64_t { return item.word(k); };
             static_assert(sizeof(ecf8_batch_item) == 128 && offsetof(ecf8_batch_item, code_len) == 80 &&
                           offsetof(ecf8_batch_item, tile_cols) == 112, "field numbers below");
-            d_blob = field(0); d_out = field(1); n_elem = field(2); n_chunks = field(3); first_chunk = field(4);
+            d_blob = field(0); d_out = field(1); n_elem = field(2); n_chunks = (uint32_t)field(3); first_chunk = (uint32_t)field(4);
             off_cb = field(5); off_lb = field(6); off_st = field(7); off_pl = field(8); st_bytes = field(9);
             len_lo = field(10); len_hi = field(11); off_tbl = field(12); group = field(13); tcols = field(14);
         } else {
             d_blob = a.single.d_blob; d_out = a.single.d_out; n_elem = a.single.n_elem;
-            n_chunks = a.single.n_chunks; first_chunk = 0; off_cb = a.single.off_chunk_bit;
+            n_chunks = (uint32_t)a.single.n_chunks; first_chunk = 0; off_cb = a.single.off_chunk_bit;
             off_lb = a.single.off_lane_bits; off_st = a.single.off_stream; off_pl = a.single.off_plane;
             st_bytes = a.single.stream_bytes;
             off_tbl = a.single.off_table; group = a.single.group_chunks; tcols = a.single.tile_cols;
             __builtin_memcpy(&len_lo, a.single.code_len, 8);
             __builtin_memcpy(&len_hi, a.single.code_len + 8, 8);
         }
-        const uint64_t t_end = first_chunk + n_chunks;
-        const uint64_t seg_end = c_end < t_end ? c_end : t_end;
+        const uint32_t t_end = first_chunk + n_chunks;
+        const uint32_t seg_end = c_end < t_end ? c_end : t_end;
         if (seg_end <= c) break; // item table does not cover chunk c: stop rather than spin
         GLOBAL uint8_t *out = (GLOBAL uint8_t *)d_out;
         const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(d_blob + off_cb);
@@ -186,34 +165,36 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // of a tcols-wide matrix, lane l works on row l % 16, its piece q on columns
         // 64 q + 16 (l / 16) of the block.  lane_off is the lane's share of all of this.
         if (group == 0) group = 1;
-        const uint64_t grouped = (n_elem / (64ull * N)) & ~(group - 1);   // chunks in whole groups (group is a power of two)
-        const uint64_t blocks_per_row = tcols ? tcols / (4ull * N) : 1;
+        const uint32_t g32 = (uint32_t)group, grouped = (uint32_t)(n_elem / (64ull * N)) & ~(g32 - 1);   // chunks in whole groups (group is a power of two)
+        const uint64_t blocks_per_row = tcols ? tcols / (4ull * N) : 1;             // a shift
         // Row-tiled: chunk number -> (block of rows, block of columns) is a division by blocks_per_row, which the
         // hardware does not have: a 64-bit one takes more instructions than the decode of a chunk.  Chunk numbers
         // and blocks_per_row fit 32 bits (n_elem <= 2^40, checked by the encoder), so the division is a
         // multiplication by a reciprocal worked out once per tensor (Granlund and Montgomery's round-up method:
         // q = (t + ((n - t) >> sh1)) >> sh2 with t = mulhi(n, mul), exact for every 32-bit n).
         const uint32_t bpr32 = (uint32_t)blocks_per_row;
-        uint32_t dv_l = 0;
-        while (dv_l < 32 && (1ull << dv_l) < bpr32) dv_l++;
-        const uint32_t dv_mul = (uint32_t)((((1ull << dv_l) - bpr32) << 32) / bpr32 + 1);
+        uint32_t dv_l = 0, dv_mul = 1;
+        if (TILED || tcols) {
+            while (dv_l < 32 && (1ull << dv_l) < bpr32) dv_l++;
+            dv_mul = (uint32_t)((((1ull << dv_l) - bpr32) << 32) / bpr32 + 1);
+        }
         const uint32_t dv_sh1 = dv_l < 1 ? dv_l : 1, dv_sh2 = dv_l > 1 ? dv_l - 1 : 0;
-        auto chunk_base = [&](uint64_t cl) -> uint64_t {
+        auto chunk_base = [&](uint32_t cl) -> uint64_t {
             if (tcols) {
-                const uint32_t t = __umulhi((uint32_t)cl, dv_mul);
-                const uint32_t rb = (t + (((uint32_t)cl - t) >> dv_sh1)) >> dv_sh2;
-                return (uint64_t)rb * 16 * tcols + ((uint32_t)cl - rb * bpr32) * (4ull * N);
+                const uint32_t t = __umulhi(cl, dv_mul);
+                const uint32_t rb = (t + ((cl - t) >> dv_sh1)) >> dv_sh2;
+                return (uint64_t)rb * 16 * tcols + (cl - rb * bpr32) * (4ull * N);
             }
-            const uint64_t w = cl & (group - 1);
-            return cl < grouped ? (cl - w) * (64ull * N) + w * 1024 : cl * (64ull * N);
+            const uint32_t w = cl < grouped ? cl & (g32 - 1) : 0u;
+            return (cl - w) * (64ull * N) + w * 1024;
         };
         // What a lane stores (and the nibbles it merges): piece q at chunk_base + lane_off + q * chunk_stride.  That is where the
         // lane's symbols are, except in the TILED kernel, whose decoded exponents change lanes first: there a lane
         // holds 16 columns of row 4 q + l / 16 of the block.
         typedef typename std::conditional<TILED, uint64_t, uint32_t>::type stride_t;
-        auto chunk_stride = [&](uint64_t cl) -> stride_t {
+        auto chunk_stride = [&](uint32_t cl) -> stride_t {
             if constexpr (TILED) return 4 * tcols;
-            return tcols ? 64u : cl < grouped ? (uint32_t)group * 1024u : 1024u;
+            return tcols ? 64u : cl < grouped ? g32 * 1024u : 1024u;
         };
         const uint64_t symbol_off = tcols ? (uint64_t)(lane & 15) * tcols + (uint64_t)(lane >> 4) * 16 : (uint64_t)lane * 16;
         const uint64_t lane_off = TILED ? (uint64_t)(lane >> 4) * tcols + (uint64_t)(lane & 15) * 16 : symbol_off;
@@ -227,11 +208,12 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // ahead (into registers), so HBM latency is covered by the decode of the
         // chunk in hand.
         struct Meta { uint64_t b0, b1; uint32_t lb; };
-        auto load_meta = [&](uint64_t cl) {
+        auto load_meta = [&](uint32_t cl) {
             Meta m;
-            m.b0 = chunk_bit[cl];
-            m.b1 = chunk_bit[cl + 1];
-            m.lb = lane_bits[cl * 64 + lane];
+            const GLOBAL uint64_t *cb = chunk_bit + cl;
+            m.b0 = cb[0];
+            m.b1 = cb[1];
+            m.lb = (lane_bits + (uint64_t)cl * 64)[lane];
             return m;
         };
         // span of the stream a chunk needs: 16-byte aligned start, 8 bytes of look-ahead.  The chunk's two
@@ -260,7 +242,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             }
         };
         // nibble plane of chunk cl: this lane's piece j at plane_of(cl) + j * (chunk_stride(cl) / 2)
-        auto plane_of = [&](uint64_t cl) -> const GLOBAL uint8_t * { return plane + chunk_base(cl) / 2 + lane_off / 2; };
+        auto plane_of = [&](uint32_t cl) -> const GLOBAL uint8_t * { return plane + chunk_base(cl) / 2 + lane_off / 2; };
 
         // The pipelined loop takes only chunks that are entirely inside the tensor, so its
         // stores are unconditional: between the issue of a prefetch and its use every path
@@ -268,31 +250,20 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // whose span does not fit the stage is decoded from stale LDS there (harmless garbage,
         // in bounds) and redone by the generic pass below.
         const bool ragged_tail = !TILED && (n_elem % (64ull * N)) != 0;     // row-tiled blobs are whole chunks
-        const uint64_t fast_end = (ragged_tail && seg_end == t_end) ? seg_end - 1 : seg_end;
+        const uint32_t fast_end = (ragged_tail && seg_end == t_end) ? seg_end - 1 : seg_end;
         // next chunk of this workgroup's range, drawn from the LDS ticket counter (wave-uniform)
-        auto draw = [&]() -> uint64_t {
+        auto draw = [&]() -> uint32_t {
             uint32_t t = 0;
             if (lane == 0) t = __hip_atomic_fetch_add(s_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return c + uniform32(t);
         };
 
-        // Start-up: the loads of the table, of the first chunks' metadata and of the first chunk's
-        // payload are all in flight before the table is written to LDS, so a workgroup pays about
-        // two HBM round trips, not four, before its first decode step.
-        uint64_t cg = c + wave;
-        uint64_t cg1 = cg + WAVES;
-        uint64_t cg2 = fast_end;    // drawn when cg1 is taken up
-        u32x4 tv[(TBL_ENTRIES * 2 / 16 + WAVES * 64 - 1) / (WAVES * 64)];
-        if (off_tbl) {
-            // the encoder embedded the table: copy it (L2-resident after the first workgroup)
-            const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(d_blob + off_tbl);
-#pragma unroll
-            for (int j = 0; j < (int)(sizeof(tv) / sizeof(tv[0])); j++) {
-                const int i = tid + j * WAVES * 64;
-                tv[j] = u32x4{0, 0, 0, 0};
-                if (i < TBL_ENTRIES * 2 / 16) tv[j] = src[i];
-            }
-        }
+        // Start-up: the first chunks' metadata and the first chunk's nibbles, whose places are known, are asked for first, then the table; the
+        // chunk's stream as soon as the metadata is there; and all of it is in flight before the table is written to LDS, so a workgroup pays
+        // about two HBM round trips, not four, before its first decode step.
+        uint32_t cg = c + wave;
+        uint32_t cg1 = cg + WAVES;
+        uint32_t cg2 = fast_end;    // drawn when cg1 is taken up
         Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
         u32x4 seg[C::SEGS];
         u32x2 pl[C::PIECES];
@@ -304,19 +275,29 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         // its stores cut at the tensor's end.  (Read symbol by symbol from HBM after the loop it was a chain of N
         // round trips at the end of every such launch: 2047 x 2049 weights 55.7 -> 11.1 us, 8 x 256 22.8 -> 9.1 us.)
         // Not inside the loop: a store under a condition there would make the wait for a prefetch drain the stores.
-        const bool tail_here = fast_end != seg_end && (uint32_t)wave == (uint32_t)(seg_end - 1 - c) % WAVES;
-        auto load_first = [&](uint64_t ck) {
+        const bool tail_here = fast_end != seg_end && (uint32_t)wave == (seg_end - 1 - c) % WAVES;
+        auto ask_first = [&](uint32_t ck) {
             m_cur = load_meta(ck - first_chunk);
-            m_next = m_cur;
-            if (cg1 < fast_end) m_next = load_meta(cg1 - first_chunk);
-            load_stream(m_cur, seg);
+            m_next = load_meta((cg1 < fast_end ? cg1 : ck) - first_chunk);      // a copy of m_cur would wait for it
             const GLOBAL uint8_t *pp = plane_of(ck - first_chunk);
             const stride_t pstride = chunk_stride(ck - first_chunk) / 2;
 #pragma unroll
             for (int j = 0; j < C::PIECES; j++) pl[j] = LD_STREAM((const GLOBAL u32x2 *)(pp + j * pstride));
         };
-        if (tail_here) load_first(seg_end - 1);
-        else if (cg < fast_end) load_first(cg);
+        const bool any = tail_here || cg < fast_end;
+        if (any) ask_first(tail_here ? seg_end - 1 : cg);
+        u32x4 tv[(TBL_ENTRIES * 2 / 16 + WAVES * 64 - 1) / (WAVES * 64)];
+        if (off_tbl) {
+            // the encoder embedded the table: copy it (L2-resident after the first workgroup)
+            const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(d_blob + off_tbl);
+#pragma unroll
+            for (int j = 0; j < (int)(sizeof(tv) / sizeof(tv[0])); j++) {
+                const int i = tid + j * WAVES * 64;
+                tv[j] = u32x4{0, 0, 0, 0};
+                if (i < TBL_ENTRIES * 2 / 16) tv[j] = src[i];
+            }
+        }
+        if (any) load_stream(m_cur, seg);
         if (off_tbl) {
 #pragma unroll
             for (int j = 0; j < (int)(sizeof(tv) / sizeof(tv[0])); j++) {
@@ -444,7 +425,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 uint64_t byte0;
                 const uint64_t span64 = span_of(m_cur, byte0);
                 if (span64 <= (uint64_t)C::STAGE) {
-                    const uint64_t cl = seg_end - 1 - first_chunk;
+                    const uint32_t cl = seg_end - 1 - first_chunk;
                     const uint32_t rel = wave_incl_scan(m_cur.lb) - m_cur.lb;
                     const uint64_t b0 = uniform64(m_cur.b0);
 #pragma unroll
@@ -458,7 +439,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 } else if (lane == 0) {
                     *s_tail = 1;          // left to the symbol pass
                 }
-                if (cg < fast_end) load_first(cg);
+                if (cg < fast_end) {
+                    ask_first(cg);
+                    load_stream(m_cur, seg);
+                }
             }
         }
         if (cg < fast_end) {
@@ -467,7 +451,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             // stores of the previous chunk are younger than the prefetch and stay in flight.
             __builtin_amdgcn_s_waitcnt(0x0F70);
             for (;;) {
-                const uint64_t cl = cg - first_chunk;            // chunk index inside the tensor
+                const uint32_t cl = cg - first_chunk;            // chunk index inside the tensor
                 GLOBAL uint8_t *out_c = out + chunk_base(cl) + lane_off;   // this lane's piece 0
                 const stride_t ostride = chunk_stride(cl);
                 const uint64_t b0 = uniform64(m_cur.b0);
@@ -495,11 +479,11 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                     cg2 = draw();
                     if (cg2 < fast_end) m_next2 = load_meta(cg2 - first_chunk);
                 }
-                const uint64_t cl_pl = (has_next ? cg1 : cg) - first_chunk;
+                const uint32_t cl_pl = (has_next ? cg1 : cg) - first_chunk;
 
                 if (!staged && lane == 0) {
                     const uint32_t at = __hip_atomic_fetch_add(s_oversize, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = (uint32_t)(cg - c);
+                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = cg - c;
                 }
                 // a chunk whose span was not staged decodes stale bits (redone after the loop): its runs are
                 // pinned to the start of the wave's stage, so that every window stays inside this kernel's LDS
@@ -530,7 +514,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                 for (uint32_t r0 = 0; r0 < n_over; r0 += C::SLOTS) {
                     __syncthreads();                  // slots free (first round: every wave is out of the loop)
                     for (uint32_t k = 0; k < (uint32_t)C::SLOTS && r0 + k < n_over; k++) {
-                        const uint64_t cl = c + s_list[r0 + k] - first_chunk;
+                        const uint32_t cl = c + s_list[r0 + k] - first_chunk;
                         const uint64_t sb0 = chunk_bit[cl], sb1 = chunk_bit[cl + 1];
                         uint64_t byte_end = ((sb1 + 7) >> 3) + 8;
                         if (byte_end > st_bytes) byte_end = st_bytes;
@@ -543,7 +527,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
                     }
                     __syncthreads();
                     if ((uint32_t)wave < (uint32_t)C::SLOTS && r0 + wave < n_over) {
-                        const uint64_t cl = c + s_list[r0 + wave] - first_chunk;
+                        const uint32_t cl = c + s_list[r0 + wave] - first_chunk;
                         const Meta m = load_meta(cl);
                         uint64_t byte0;
                         const uint64_t span = span_of(m, byte0);
@@ -570,8 +554,8 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             // before any wave issues a store of this pass (barrier; scan_all is uniform).
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
-            for (uint64_t cg2 = c + wave; cg2 < seg_end; cg2 += WAVES) {
-                const uint64_t cl = cg2 - first_chunk;
+            for (uint32_t cg2 = c + wave; cg2 < seg_end; cg2 += WAVES) {
+                const uint32_t cl = cg2 - first_chunk;
                 Meta m = load_meta(cl);
                 uint64_t byte0;
                 const uint64_t span64 = span_of(m, byte0);
@@ -620,7 +604,9 @@ int launch_as(const KArgs &a, int wgs_per_cu, hipStream_t s)
     if (a.max_workgroups && a.max_workgroups < cap) cap = a.max_workgroups;
     uint32_t grid = (uint32_t)(want < cap ? want : cap);
     if (grid == 0) grid = 1;
-    hipLaunchKernelGGL((ecf8_decode_kernel<N, WAVES, PAIRFIT, TILED, LONG, BURST>), dim3(grid), dim3(WAVES * 64), 0, s, a);
+    KArgs dealt = a;
+    dealt.deal = deal_chunks(a.total_chunks, grid);
+    hipLaunchKernelGGL((ecf8_decode_kernel<N, WAVES, PAIRFIT, TILED, LONG, BURST>), dim3(grid), dim3(WAVES * 64), 0, s, dealt);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 

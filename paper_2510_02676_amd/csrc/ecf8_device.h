@@ -10,6 +10,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <mutex>
 
 namespace {
@@ -426,6 +427,66 @@ __device__ __forceinline__ uint32_t global_window(const GLOBAL uint8_t *sp, uint
     const GLOBAL uint32_t *q = (const GLOBAL uint32_t *)(sp + ((p >> 3) & ~3ull));
     return __brev(__builtin_amdgcn_alignbit(q[1], q[0], (uint32_t)p));
 }
+
+// A launch's chunks dealt to its workgroups: a contiguous range each, cut at multiples of 64 or 8 chunks where that leaves every workgroup at least 16
+// such units (shares then differ by 1/16 at most), so that the waves of a workgroup share the interleaved groups of the layout.  The division is the
+// host's, and chunk numbers have 32 bits: a wave by itself takes 8 cycles per instruction that waits for the one before, and the start of a workgroup is a chain
+// of those (with the metadata's loads, see the decode kernel: 1024 x 1024 weights 8.2 -> 7.5 us, 4099 x 5127 12.9 -> 12.35, a layer of BF16 140.5 -> 138.7).
+// Not kept: the last round or two of chunks as workgroups of their own behind the others, for compute units that end early (a workgroup's ends spread over a tenth
+// of a layer's time): a workgroup's start costs more, 78.7 -> 79.5 .. 84, E5M2 85.9 -> 87 .. 110 us.
+struct ChunkDeal {
+    uint32_t each;             // units of every workgroup; the first `rest` have one more
+    uint32_t rest, shift;      // a unit is 1 << shift chunks
+    __device__ __forceinline__ uint32_t begin(uint32_t wg) const { return (each * wg + (wg < rest ? wg : rest)) << shift; }
+};
+inline __attribute__((unused)) ChunkDeal deal_chunks(uint64_t chunks, uint32_t workgroups)
+{
+    ChunkDeal d;
+    d.shift = chunks >= workgroups * 1024ull ? 6 : chunks >= workgroups * 128ull ? 3 : 0;
+    const uint64_t units = (chunks + (1ull << d.shift) - 1) >> d.shift;
+    d.each = (uint32_t)(units / workgroups);
+    d.rest = (uint32_t)(units % workgroups);
+    return d;
+}
+
+// The item of a batch that holds chunk c, by a whole wave; every lane's answer is the same.  Items are 128 bytes, first_chunk is their fifth word and increasing.
+// More than 16 are narrowed down 64-way, a round trip to memory per level: lane l probes the l-th of 64 evenly spaced items, and the lanes that pass form a
+// prefix.  The last 16 or fewer are read whole, four lanes an item, so that a batch of a layer's tensors costs one round trip.  The words go to
+// scalar registers: they are the same for every lane and live as long as the tensor.
+struct BatchItem {
+    uint64_t part[4];
+    uint32_t lane0;
+    template <class Item>           // of either container
+    __device__ __forceinline__ BatchItem(const GLOBAL Item *items, uint32_t n_items, uint64_t c, int lane)
+    {
+        static_assert(sizeof(Item) == 128 && offsetof(Item, first_chunk) == 32, "16 words, the fifth");
+        uint32_t lo = 0, n = n_items;
+        while (n > 16) {
+            const uint32_t stride = (n + 63) / 64;
+            const uint32_t at = (uint32_t)lane * stride;
+            const bool pass = at < n && ((const GLOBAL uint64_t *)(items + lo + at))[4] <= c;
+            const uint32_t k = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pass));
+            const uint32_t step = k ? (k - 1) * stride : 0;       // k >= 1 for a valid table
+            lo += step;
+            n = n - step < stride ? n - step : stride;
+        }
+        const uint32_t mine = (uint32_t)lane >> 2;
+        const GLOBAL uint64_t *w = (const GLOBAL uint64_t *)(items + lo + (mine < n ? mine : 0)) + 4 * (lane & 3);
+        const u32x4 a = ((const GLOBAL u32x4 *)w)[0], b = ((const GLOBAL u32x4 *)w)[1];
+        part[0] = a.x | (uint64_t)a.y << 32;
+        part[1] = a.z | (uint64_t)a.w << 32;
+        part[2] = b.x | (uint64_t)b.y << 32;
+        part[3] = b.z | (uint64_t)b.w << 32;
+        const uint32_t k = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64((lane & 3) == 1 && mine < n && part[0] <= c));
+        lane0 = k ? 4 * (k - 1) : 0;
+    }
+    __device__ __forceinline__ uint64_t word(int k) const
+    {
+        const uint64_t p = part[k & 3];
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)p, (int)lane0 + (k >> 2)) |
+               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(p >> 32), (int)lane0 + (k >> 2)) << 32);
+    }
+};
 
 int device_cus()
 {

@@ -39,6 +39,7 @@ struct BArgs {
     const GLOBAL WArgs *items;           // device array for the batched call
     uint32_t n_items;
     uint64_t total_chunks;
+    ChunkDeal deal;                      // of the launch's chunks to its workgroups
 };
 
 template <int FMT> struct Fmt;
@@ -244,68 +245,49 @@ __device__ __forceinline__ u32x4 merge_e5m2(const uint32_t e[16], uint32_t mant,
     return u32x4{out[0], out[1], out[2], out[3]};
 }
 
-// The item of a batched launch that holds chunk g: a 64-way search, one round trip to memory per level (lane l probes the
-// l-th of 64 evenly spaced items; first_chunk is increasing, so the lanes that pass form a prefix), then the item's 16
-// words by one load of 16 lanes into scalar registers.
+// The item of a batched launch that holds chunk g, in scalar registers.
 __device__ __forceinline__ WArgs find_item(const BArgs &b, uint64_t g, int lane)
 {
     if (!b.items) return b.single;
-    uint32_t lo = 0, n = b.n_items;
-    while (n > 1) {
-        const uint32_t stride = (n + 63) / 64;
-        const uint32_t at = (uint32_t)lane * stride;
-        const bool pass = at < n && b.items[lo + at].first_chunk <= g;
-        const uint32_t k = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(pass));
-        const uint32_t step = k ? (k - 1) * stride : 0;
-        lo += step;
-        n = n - step < stride ? n - step : stride;
-    }
-    static_assert(sizeof(WArgs) == 128, "sixteen words");
-    const uint64_t word = ((const GLOBAL uint64_t *)(b.items + lo))[lane & 15];
+    const BatchItem item(b.items, b.n_items, g, lane);
     WArgs a;
     uint64_t *dst = (uint64_t *)&a;
 #pragma unroll
-    for (int i = 0; i < 16; i++)
-        dst[i] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, i) |
-                 ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), i) << 32);
+    for (int i = 0; i < 16; i++) dst[i] = item.word(i);
     return a;
 }
 
-// contiguous range of a launch's chunks for this workgroup, cut at multiples of 64 or 8 chunks where that leaves every
-// workgroup at least 16 such units, so that the waves of a workgroup share the interleaved groups of the layout
-__device__ __forceinline__ void share_of(const BArgs &b, uint64_t &g, uint64_t &g_end)
+// the range of a launch's chunks for this workgroup; chunk numbers run through the whole batch and have 32 bits (2^32 chunks are 16 TiB or more)
+__device__ __forceinline__ void share_of(const BArgs &b, uint32_t &g, uint32_t &g_end)
 {
-    const uint64_t NWG = gridDim.x, wg = blockIdx.x;
-    const uint64_t unit = b.total_chunks >= NWG * 1024 ? 64 : b.total_chunks >= NWG * 128 ? 8 : 1;
-    const uint64_t units = (b.total_chunks + unit - 1) / unit;
-    g = units * wg / NWG * unit;                      // chunk numbers run through the whole batch
-    g_end = units * (wg + 1) / NWG * unit;
-    if (g_end > b.total_chunks) g_end = b.total_chunks;
+    g = b.deal.begin(blockIdx.x);
+    g_end = b.deal.begin(blockIdx.x + 1);
+    if (g_end > (uint32_t)b.total_chunks) g_end = (uint32_t)b.total_chunks;
 }
 
 // Element layout: piece q of lane l of chunk c starts at element base(c) + q * stride(c) + l * P.
 template <int FMT, int N>
 struct Place {
     static constexpr uint64_t E = 64ull * N, P = Fmt<FMT>::P;
-    uint64_t group, whole;                            // whole: chunks inside complete groups (group is a power of two)
-    __device__ __forceinline__ Place(const WArgs &a) : group(a.group_chunks), whole((a.n_elem / E) & ~(a.group_chunks - 1)) {}
-    __device__ __forceinline__ uint64_t base(uint64_t c) const
+    uint32_t group, whole;                            // whole: chunks inside complete groups (group is a power of two)
+    __device__ __forceinline__ Place(const WArgs &a) : group((uint32_t)a.group_chunks), whole((uint32_t)(a.n_elem / E) & ~((uint32_t)a.group_chunks - 1)) {}
+    __device__ __forceinline__ uint64_t base(uint32_t c) const
     {
-        const uint64_t w = c & (group - 1);
-        return c < whole ? (c - w) * E + w * (64 * P) : c * E;
+        const uint32_t w = c < whole ? c & (group - 1) : 0u;
+        return (c - w) * E + w * (64 * P);
     }
-    __device__ __forceinline__ uint32_t stride(uint64_t c) const { return c < whole ? (uint32_t)(group * (64 * P)) : (uint32_t)(64 * P); }
+    __device__ __forceinline__ uint32_t stride(uint32_t c) const { return c < whole ? group * (uint32_t)(64 * P) : (uint32_t)(64 * P); }
 };
 
 struct Meta { uint64_t b0, b1; uint32_t lb; };
 
-__device__ __forceinline__ Meta load_meta(const WArgs &a, uint64_t c, int lane)
+__device__ __forceinline__ Meta load_meta(const WArgs &a, uint32_t c, int lane)
 {
-    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(a.d_blob + a.off_chunk_bit);
+    const GLOBAL uint64_t *chunk_bit = (const GLOBAL uint64_t *)(a.d_blob + a.off_chunk_bit) + c;
     Meta m;
-    m.b0 = chunk_bit[c];
-    m.b1 = chunk_bit[c + 1];
-    m.lb = ((const GLOBAL uint16_t *)(a.d_blob + a.off_lane_bits))[c * 64 + lane];
+    m.b0 = chunk_bit[0];
+    m.b1 = chunk_bit[1];
+    m.lb = ((const GLOBAL uint16_t *)(a.d_blob + a.off_lane_bits) + (uint64_t)c * 64)[lane];
     return m;
 }
 
@@ -380,13 +362,13 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t stage_off = C::OFF_STAGE + wave * STAGE;
     uint8_t *stage = smem + stage_off;
-    uint64_t g, g_end;
+    uint32_t g, g_end;
     share_of(b, g, g_end);
 
     while (g < g_end) {                                // one round per tensor the range touches (uniform)
     const WArgs a = find_item(b, g, lane);
-    const uint64_t c_begin = g - a.first_chunk;        // chunk numbers inside the tensor
-    const uint64_t c_end = g_end - a.first_chunk < a.n_chunks ? g_end - a.first_chunk : a.n_chunks;
+    const uint32_t c_begin = g - (uint32_t)a.first_chunk;        // chunk numbers inside the tensor
+    const uint32_t c_end = g_end - (uint32_t)a.first_chunk < (uint32_t)a.n_chunks ? g_end - (uint32_t)a.first_chunk : (uint32_t)a.n_chunks;
     if (c_end <= c_begin) break;                       // the item table does not cover chunk g: stop rather than spin
     const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
     const GLOBAL uint8_t *stream = blob + a.off_stream;
@@ -408,12 +390,12 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
         uint32_t mant[FMT == ECFW_FMT_E5M2 ? PIECES : 1];
         uint32_t sign[FMT == ECFW_FMT_E5M2 ? PIECES : 1];
     };
-    auto draw = [&]() -> uint64_t {
+    auto draw = [&]() -> uint32_t {
         uint32_t t = 0;
         if (lane == 0) t = atomicAdd(s_ticket, 1u);
         return c_begin + uniform32(t);
     };
-    auto load_payload = [&](uint64_t c, const Meta &m, Payload &p) {
+    auto load_payload = [&](uint32_t c, const Meta &m, Payload &p) {
         uint64_t byte0;
         const uint64_t span = span_of(a, m, byte0);
         const uint64_t e0 = place.base(c) + (uint64_t)lane * P, stride = place.stride(c);
@@ -436,14 +418,14 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
         }
     };
 
-    uint64_t cur = draw();
+    uint32_t cur = draw();
     Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
     Payload p_cur;
     if (cur < c_end) {
         m_cur = load_meta(a, cur, lane);
         load_payload(cur, m_cur, p_cur);
     }
-    uint64_t nxt = draw();
+    uint32_t nxt = draw();
     if (nxt < c_end) m_next = load_meta(a, nxt, lane);
 
     while (cur < c_end) {
@@ -518,7 +500,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
         m_cur = m_next;
         m_next = m_next2;
     }
-    g = a.first_chunk + c_end;
+    g = (uint32_t)a.first_chunk + c_end;
     __syncthreads();                                   // every wave is done with this tensor's table and tickets
     }
 }
@@ -749,25 +731,25 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
     const int tid = threadIdx.x, lane = tid & 63, wave = (int)uniform32((uint32_t)tid >> 6);
     const uint32_t stage_off = C::OFF_STAGE + wave * STAGE, lane16 = (uint32_t)lane * 16;
     uint8_t *stage = smem + stage_off;
-    uint64_t g, g_end;
+    uint32_t g, g_end;
     share_of(b, g, g_end);
 
     while (g < g_end) {                                // one round per tensor the range touches (uniform)
         const WArgs a = find_item(b, g, lane);
-        const uint64_t c_begin = g - a.first_chunk;    // chunk numbers inside the tensor
-        const uint64_t c_end = g_end - a.first_chunk < a.n_chunks ? g_end - a.first_chunk : a.n_chunks;
+        const uint32_t c_begin = g - (uint32_t)a.first_chunk;    // chunk numbers inside the tensor
+        const uint32_t c_end = g_end - (uint32_t)a.first_chunk < (uint32_t)a.n_chunks ? g_end - (uint32_t)a.first_chunk : (uint32_t)a.n_chunks;
         if (c_end <= c_begin) break;                   // the item table does not cover chunk g: stop rather than spin
         const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
         const GLOBAL uint8_t *stream = blob + a.off_stream, *plane = blob + a.off_plane, *signs = blob + a.off_sign;
         GLOBAL uint8_t *out = (GLOBAL uint8_t *)a.d_out;
         const Place<FMT, N> place(a);
         const bool ragged_tail = c_end == a.n_chunks && a.n_elem % place.E != 0;
-        const uint64_t fast_end = ragged_tail ? c_end - 1 : c_end;
+        const uint32_t fast_end = ragged_tail ? c_end - 1 : c_end;
 
         __syncthreads();                               // every wave is done with the previous tensor's tables
         if (tid == 0) { *s_ticket = 2 * WAVES; *s_oversize = 0; *s_tail = 0; }
 
-        auto draw = [&]() -> uint64_t {
+        auto draw = [&]() -> uint32_t {
             uint32_t t = 0;
             if (lane == 0) t = __hip_atomic_fetch_add(s_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return c_begin + uniform32(t);
@@ -794,7 +776,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
         };
 
         // the first two chunks of a wave are fixed, later ones are drawn
-        uint64_t cur = c_begin + wave, nxt = cur + WAVES, nn = fast_end;
+        uint32_t cur = c_begin + wave, nxt = cur + WAVES, nn = fast_end;
         Meta m_cur{0, 0, 0}, m_next{0, 0, 0};
         u32x4 seg[SEGS];
         Rest rest[PIECES];
@@ -803,17 +785,16 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
 #pragma unroll
         for (int q = 0; q < PIECES; q++) rest[q].v = u32x2{0, 0};
         uint32_t my_len = tid < F::A ? (blob + a.off_code_len)[tid] : 0u;
-        auto load_first = [&](uint64_t c) {
+        auto load_first = [&](uint32_t c) {
             m_cur = load_meta(a, c, lane);
-            m_next = m_cur;
-            if (nxt < fast_end) m_next = load_meta(a, nxt, lane);
+            m_next = load_meta(a, nxt < fast_end ? nxt : c, lane);      // a copy of m_cur would wait for it
             const uint64_t e0 = place.base(c) + (uint64_t)lane * P;
 #pragma unroll
             for (int q = 0; q < PIECES; q++) rest[q] = load_rest(e0 + q * (uint64_t)place.stride(c));
             load_stream(m_cur, seg);
         };
         // the ragged last chunk goes first, to the wave it would fall to in turn, its stores cut at the tensor's end
-        const bool tail_here = ragged_tail && (uint32_t)wave == (uint32_t)(c_end - 1 - c_begin) % WAVES;
+        const bool tail_here = ragged_tail && (uint32_t)wave == (c_end - 1 - c_begin) % WAVES;
         if (tail_here) load_first(c_end - 1);
         else if (cur < fast_end) load_first(cur);
         if (my_len > ECFW_MAX_CODE_LEN) my_len = 0;
@@ -939,10 +920,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                 }
                 if (!staged && lane == 0) {
                     const uint32_t at = __hip_atomic_fetch_add(s_oversize, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = (uint32_t)(cur - c_begin);
+                    if (at < (uint32_t)C::LIST_MAX) s_list[at] = cur - c_begin;
                 }
                 // a chunk that was not staged decodes stale bits (redone after the loop), its runs pinned to the stage's start
-                const uint64_t c_rest = has_next ? nxt : cur;          // after the last chunk: its own rest again, not a branch
+                const uint32_t c_rest = has_next ? nxt : cur;          // after the last chunk: its own rest again, not a branch
                 decode_store(std::true_type{}, std::false_type{}, stage_off * 8 + (staged ? bit_in : 64u), staged ? m_cur.lb : 0u,
                              place.base(cur) + (uint64_t)lane * P, place.stride(cur), place.base(c_rest) + (uint64_t)lane * P, place.stride(c_rest));
                 if (!has_next) break;
@@ -961,10 +942,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
             const bool listed = n_over <= (uint32_t)C::LIST_MAX;
-            const uint64_t count = listed ? n_over + (tail_left ? 1u : 0u) : c_end - c_begin;
+            const uint32_t count = listed ? n_over + (tail_left ? 1u : 0u) : c_end - c_begin;
 #pragma unroll 1
-            for (uint64_t k = wave; k < count; k += WAVES) {
-                const uint64_t c = !listed ? c_begin + k : k < n_over ? c_begin + uniform32(s_list[k]) : c_end - 1;
+            for (uint32_t k = wave; k < count; k += WAVES) {
+                const uint32_t c = !listed ? c_begin + k : k < n_over ? c_begin + uniform32(s_list[k]) : c_end - 1;
                 if (!listed) {
                     uint64_t byte0;
                     const bool over = c >= fast_end ? tail_left : span_of(a, load_meta(a, c, lane), byte0) > (uint64_t)STAGE;
@@ -973,7 +954,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_decode_kernel(BArgs b)
                 symbol_pass<FMT, N>(a, ca, c, lane);
             }
         }
-        g = a.first_chunk + c_end;
+        g = (uint32_t)a.first_chunk + c_end;
     }
 }
 
@@ -992,7 +973,9 @@ int launch_as(K kernel, const BArgs &a, uint32_t max_workgroups, hipStream_t str
 {
     const uint64_t grid = workgroups(a, max_workgroups);
     if (grid == 0) return ECF8_E_HIP;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, a);
+    BArgs dealt = a;
+    dealt.deal = deal_chunks(a.total_chunks, (uint32_t)grid);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(WAVES * 64), 0, stream, dealt);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 
