@@ -207,6 +207,13 @@ int ecf8_gemm_group_prepare(const ecf8_gemm_group_desc *descs, uint32_t n, ecf8_
         if (d.M > max_M) max_M = d.M;
         std::memcpy(&items_host[i], &it, sizeof(it));
     }
+    if (work >= 1ull << 32) return ECF8_E_ARG;                      // 16 TiB of weights
+    for (uint32_t i = 0; i < n; i++) {                              // the waves of the launch go by the largest M
+        GItem it;
+        std::memcpy(&it, &items_host[i], sizeof(it));
+        deal_waves(&it.a, max_M);
+        std::memcpy(&items_host[i], &it, sizeof(it));
+    }
     info->total_work = work;
     info->n_items = n;
     info->max_M = max_M;
@@ -221,13 +228,13 @@ int ecf8_gemm_fp8_grouped(const ecf8_gemm_group_item *d_items, const ecf8_gemm_g
         info->scale_mode > 2 || info->raw > 1)
         return ECF8_E_ARG;
     if ((uintptr_t)d_items & 7) return ECF8_E_ALIGN;
-    GGArgs g{(uint64_t)(uintptr_t)d_items, info->n_items, info->total_work};
-    const uint32_t M = info->max_M;
+    const uint64_t items = (uint64_t)(uintptr_t)d_items, work = info->total_work;
+    const uint32_t n = info->n_items, M = info->max_M;
     if (info->raw)
-        return info->scale_mode == 0 ? launch_grouped<0, true>(g, M, stream)
-             : info->scale_mode == 1 ? launch_grouped<1, true>(g, M, stream) : launch_grouped<2, true>(g, M, stream);
-    return info->scale_mode == 0 ? launch_grouped<0, false>(g, M, stream)
-         : info->scale_mode == 1 ? launch_grouped<1, false>(g, M, stream) : launch_grouped<2, false>(g, M, stream);
+        return info->scale_mode == 0 ? launch_grouped<0, true>(items, n, work, M, stream)
+             : info->scale_mode == 1 ? launch_grouped<1, true>(items, n, work, M, stream) : launch_grouped<2, true>(items, n, work, M, stream);
+    return info->scale_mode == 0 ? launch_grouped<0, false>(items, n, work, M, stream)
+         : info->scale_mode == 1 ? launch_grouped<1, false>(items, n, work, M, stream) : launch_grouped<2, false>(items, n, work, M, stream);
 }
 
 } // extern "C"

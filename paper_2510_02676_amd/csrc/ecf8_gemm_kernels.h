@@ -8,6 +8,7 @@
 #include "ecf8_device.h"
 
 #include <cstring>
+#include <numeric>
 
 namespace {
 
@@ -18,6 +19,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int GK = 4096;                        // K
 constexpr int BLOCK_ROWS = 16;
 
+// Waves of a workgroup of the any-K kernels with MT tiles of X: 4, 3 and 2 on a SIMD, which leaves 128, 168 and 256 registers to a wave.  What bounds them is
+// each wave's chain of look-ups, some 10 clocks an instruction with two waves on a SIMD.  Two tiles on 8 / 12 waves, us, M = 17 and 32: 4096 x 14336 19.1 / 16.6,
+// 20.0 / 17.1; 2048 x 7168 11.3 / 10.3, 11.9 / 10.8; 14336 x 9216 46.2 / 40.8, 49.7 / 46.4, with group scales 53.2 / 43.6, 58.1 / 52.2; 16384 x 256 5.6 / 5.1,
+// 5.7 / 5.4; eight experts with scales of W M = 20 126.4 / 117.9, M = 32 135.4 / 126.2, without 114 / 110.5, 123.7 / 122.6.  On 16 they spill: up to twice the time.
+template <int MT> constexpr int WAVES = MT == 1 ? 16 : MT == 2 ? 12 : 8;
 constexpr int X_ROW = 256 + 16;                 // bytes of a row in a turn buffer: padded so that sixteen rows fall into different banks
 
 // N symbols per lane: a chunk is 16 rows x 4N columns; NW waves per workgroup; MT blocks of 16 rows of X
@@ -28,7 +34,7 @@ struct GCfg {
     static constexpr int KPW = KCHUNKS / NW;               // of which each wave takes this many
     static constexpr int PIECES = N / 16;
     static_assert(N == 64, "RawRuns, X_ROW");
-    static_assert(KPW * NW == KCHUNKS && KPW >= 1, "waves split the chunks of a block evenly");
+    static constexpr bool EVEN = KPW * NW == KCHUNKS;              // what the kernels for K = 4096 ask for
     static constexpr int OFF_TBL = 0;
     static constexpr int OFF_RED = OFF_TBL + TBL_ENTRIES * 2;
     static constexpr int RED_BYTES = NW * MT * 64 * 16;            // one buffer of partial sums: one block of rows, every wave
@@ -58,7 +64,19 @@ struct GArgs {
     uint64_t K;                           // columns of W (a multiple of 256; 4096 for the fixed-K kernels)
     uint32_t slices;                      // split K: workgroups that share a block of rows (divides K / 256), else 1
     uint64_t d_part, d_ctr;               // split K: partial sums [block][slice][MT * 256] fp32, arrival counters [block] u32
+    // Quotients of the fused kernels' deals, from the host (deal_units, deal_waves): a division is some 25 instructions one behind the other at
+    // 8 cycles each, at the start of every workgroup
+    uint32_t units_each, units_rest;      // units (blocks of rows, times slices) of every workgroup; the first units_rest have one more
+    uint32_t unit_chunks;                 // K / 256 / slices
+    uint32_t hop, hop_kc;                 // the waves of a workgroup over unit_chunks, and the rest
+    uint32_t groups, per_group;           // waves that keep X: groups that take a unit each, waves of a group
+    uint32_t batch;                       // any K: blocks between two meetings of the workgroup
+    uint32_t by_unit, by_group;           // for small_div by unit_chunks, per_group
 };
+
+// n / d where n d < 2^20, from by = small_by(d)
+__device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t by) { return n * by >> 20; }
+inline uint32_t small_by(uint32_t d) { return (1u << 20) / d + 1; }
 
 constexpr int SCALE_BLOCK = 128;                // W carries one fp32 scale per 128 x 128 block
 
@@ -142,21 +160,27 @@ __device__ __forceinline__ void deal_plane(u32x4 v, u32x2 &a, u32x2 &b)
 }
 
 // The pair table the encoder embedded, if it did, on its way from the blob to LDS.
-template <int NW> constexpr int TABLE_UNITS = (TBL_ENTRIES * 2 / 16 + NW * 64 - 1) / (NW * 64);     // 16-byte units per thread
+constexpr int TABLE_16B = TBL_ENTRIES * 2 / 16;
+template <int NW> constexpr int TABLE_UNITS = (TABLE_16B + NW * 64 - 1) / (NW * 64);     // 16-byte units per thread
 template <int NW>
 __device__ __forceinline__ void load_table(const GArgs &a, int tid, u32x4 (&tv)[TABLE_UNITS<NW>])
 {
-    static_assert(TABLE_UNITS<NW> * NW * 64 * 16 == TBL_ENTRIES * 2, "whole rounds");
     if (!a.off_tbl) return;
     const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(a.d_blob + a.off_tbl);
 #pragma unroll
-    for (int j = 0; j < TABLE_UNITS<NW>; j++) tv[j] = src[tid + j * NW * 64];
+    for (int j = 0; j < TABLE_UNITS<NW>; j++) {
+        const int u = tid + j * NW * 64;
+        tv[j] = src[TABLE_16B % (NW * 64) == 0 || u < TABLE_16B ? u : tid];
+    }
 }
 template <int NW>
 __device__ __forceinline__ void store_table(uint16_t *tbl, int tid, const u32x4 (&tv)[TABLE_UNITS<NW>])
 {
 #pragma unroll
-    for (int j = 0; j < TABLE_UNITS<NW>; j++) ((u32x4 *)tbl)[tid + j * NW * 64] = tv[j];
+    for (int j = 0; j < TABLE_UNITS<NW>; j++) {
+        const int u = tid + j * NW * 64;
+        if (TABLE_16B % (NW * 64) == 0 || u < TABLE_16B) ((u32x4 *)tbl)[u] = tv[j];
+    }
     __syncthreads();
 }
 
@@ -283,9 +307,9 @@ __device__ __forceinline__ void reduce_parked(const f32x4 *red, const GArgs &a, 
 }
 
 // reduce_block for a batch of `count` blocks of rows first, first + stride, ...: the waves have parked block j's partial sums in
-// slots slots * j, slots * j + 1, ... of `red`, one per place of a chunk in the deal (its number modulo NW), whoever had it; the
+// slots slots * j, slots * j + 1, ... of `red`, one per place of a chunk in the deal (its number modulo PLACES), whoever had it; the
 // caller's barriers lie around this.  Summed in that order, which is reduce_block's.
-template <int MT, int NW, bool SCALED>
+template <int MT, int NW, int PLACES, bool SCALED>
 __device__ __forceinline__ void reduce_batch(const f32x4 *red, const GArgs &a, uint64_t first, uint64_t stride, uint32_t count, uint32_t slots, int tid)
 {
     GLOBAL float *Y = (GLOBAL float *)a.d_y;
@@ -293,9 +317,9 @@ __device__ __forceinline__ void reduce_batch(const f32x4 *red, const GArgs &a, u
         const uint32_t j = o / (MT * 256), mt = (o >> 8) % MT, l = (o >> 2) & 63, r = o & 3;
         const float *p = (const float *)&red[(j * slots * MT + mt) * 64 + l] + r;
         float sum = 0.f;
-        if (slots == NW) {
+        if (slots == PLACES) {
 #pragma unroll
-            for (int w = 0; w < NW; w++) sum += p[w * (MT * 256)];
+            for (int w = 0; w < PLACES; w++) sum += p[w * (MT * 256)];
         } else {
             for (uint32_t w = 0; w < slots; w++) sum += p[w * (MT * 256)];
         }
@@ -319,15 +343,16 @@ struct Deal {
 };
 
 template <int NW>
-__device__ __forceinline__ Deal deal_chunks(uint32_t unit_chunks, bool split, int wave)
+__device__ __forceinline__ Deal deal_chunks(const GArgs &a, bool split, int wave)
 {
     Deal d;
     const uint32_t w = uniform32((uint32_t)wave);       // the same for every lane: keep all of this in scalar registers
-    d.groups = (!split && 2 * unit_chunks <= (uint32_t)NW) ? (uint32_t)NW / unit_chunks : 1u;
-    d.wpb = (uint32_t)NW / d.groups;
-    d.gi = w / d.wpb;
-    d.kw = w % d.wpb;
-    d.my_chunks = (d.gi < d.groups && unit_chunks > d.kw) ? (unit_chunks - d.kw + d.wpb - 1) / d.wpb : 0u;
+    d.groups = split ? 1u : a.groups;
+    d.wpb = split ? (uint32_t)NW : a.per_group;
+    d.gi = split ? 0u : small_div(w, a.by_group);
+    d.kw = w - d.gi * d.wpb;
+    if (d.groups > 1) d.my_chunks = d.gi < d.groups && d.kw < a.unit_chunks ? 1u : 0u;
+    else d.my_chunks = a.unit_chunks > d.kw ? (a.unit_chunks - d.kw + NW - 1) / NW : 0u;
     return d;
 }
 
@@ -527,6 +552,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     constexpr bool SCALED = SC != 0;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
     using C = GCfg<MT, NW, N>;
+    static_assert(C::EVEN, "waves split the chunks of a block evenly");
     constexpr int KPW = C::KPW, KCHUNKS = C::KCHUNKS, BLOCK_COLS = C::BLOCK_COLS;
     constexpr int GPIECES = C::PIECES;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
@@ -539,20 +565,20 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     constexpr bool META1 = MT == 4;            // M = 64 25.0 us, 24.6 with it, scales of W 28.6, 26.6; M = 16 15.5, 15.8
     using Meta = ChunkMeta<META1>;
     const MetaReader<META1> meta(a, lane);
-    const uint64_t n_blocks = a.rows / BLOCK_ROWS;
     const uint32_t wave_s = uniform32((uint32_t)wave);             // the same for every lane: chunk addresses stay in scalar registers
     // the wave's chunks in the order it meets them: step s = its (s % KPW)-th chunk of its (s / KPW)-th block
-    auto block_of = [&](uint64_t s) -> uint64_t { return blockIdx.x + (s / KPW) * (uint64_t)gridDim.x; };
-    auto kc_of = [&](uint64_t s) -> uint32_t { return wave_s + NW * (uint32_t)(s % KPW); };
-    auto load_meta = [&](uint64_t s) { return meta(block_of(s) * KCHUNKS + kc_of(s)); };
+    typedef typename std::conditional<MT == 1, uint32_t, uint64_t>::type Step;     // M = 1 16.1 -> 15.0 us in 32 bits, M = 32 with group scales 22.2 -> 24.7
+    auto block_of = [&](Step s) -> Step { return blockIdx.x + (s / KPW) * (Step)gridDim.x; };
+    auto kc_of = [&](Step s) -> uint32_t { return wave_s + NW * (uint32_t)(s % KPW); };
+    auto load_meta = [&](Step s) { return meta((uint64_t)block_of(s) * KCHUNKS + kc_of(s)); };
     // nibble plane of step s: this lane's part of pieces q and q + 2 at plane_of(s) + lane_plane + 32 q, see deal_plane
     const uint32_t lane_plane = (uint32_t)(lane & 15) * (GK / 2) + plane_lane(lane);
-    auto plane_of = [&](uint64_t s) -> const GLOBAL uint8_t * {
-        return plane + (block_of(s) * BLOCK_ROWS * (uint64_t)GK + kc_of(s) * (uint64_t)BLOCK_COLS) / 2;
+    auto plane_of = [&](Step s) -> const GLOBAL uint8_t * {
+        return plane + (block_of(s) * (uint64_t)(BLOCK_ROWS * GK) + kc_of(s) * (uint64_t)BLOCK_COLS) / 2;
     };
 
     // start-up: the first chunks' loads and those of X are in flight while the table is set up
-    const uint64_t n_steps = blockIdx.x < n_blocks ? ((n_blocks - blockIdx.x + gridDim.x - 1) / gridDim.x) * KPW : 0;
+    const Step n_steps = (Step)(a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u)) * KPW;
     Meta m_cur, m_next;
     RawRuns raw = {};
     static_assert(GPIECES == 4, "deal_plane");
@@ -584,20 +610,20 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     }
 
     uint32_t parity = 0;
-    for (uint64_t s0 = 0; s0 < n_steps; s0 += KPW) {
+    for (Step s0 = 0; s0 < n_steps; s0 += KPW) {
         f32x4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < KPW; i++) {
-            const uint64_t s = s0 + i;
+            const Step s = s0 + i;
             ShiftedRuns runs;
             runs.begin(raw);
             // The raw registers are free: fetch the next chunk's runs, and the metadata of the chunk after it.
             // The last steps have nothing to fetch and no branch around the loads either: the last chunk's metadata and runs
             // again, and the plane's first chunk, which every wave then asks for.
             const bool more = s + 1 < n_steps;                 // the same for every lane
-            const uint64_t sn = more ? s + 1 : s, sn2 = s + 2 < n_steps ? s + 2 : sn;
+            const Step sn = more ? s + 1 : s, sn2 = s + 2 < n_steps ? s + 2 : sn;
             raw.fetch(stream, a.st_bytes, m_next, lane);
             const Meta m_next2 = load_meta(sn2);
             const GLOBAL uint8_t *pp = more ? plane_of(sn) : plane;
@@ -628,7 +654,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
         } else {
             // park this block's partial sums; the workgroup meets after every BPB-th block and after the last one
             f32x4 *red = (f32x4 *)(smem + C::OFF_RED);
-            const uint32_t j = (uint32_t)((s0 / KPW) % C::BPB);
+            const uint32_t j = (uint32_t)(s0 / KPW % C::BPB);
             red[(j * NW + wave_s) * 64 + lane] = acc[0];
             const bool last = s0 + KPW >= n_steps;           // the same for the whole workgroup
             if (j == C::BPB - 1 || last) {
@@ -647,13 +673,13 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_raw_kernel(GArgs a)
 {
     constexpr bool SCALED = SC != 0;
     using C = GCfg<MT, NW, N>;
+    static_assert(C::EVEN, "waves split the chunks of a block evenly");
     constexpr int KPW = C::KPW, BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::RED_BUFS * C::RED_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const GLOBAL uint8_t *W = (const GLOBAL uint8_t *)a.d_w;
     const uint64_t lane_elem = (uint64_t)(lane & 15) * GK + (uint64_t)(lane >> 4) * 16;
-    const uint64_t n_blocks = a.rows / BLOCK_ROWS;
-    const uint64_t n_steps = blockIdx.x < n_blocks ? ((n_blocks - blockIdx.x + gridDim.x - 1) / gridDim.x) * KPW : 0;
+    const uint64_t n_steps = (uint64_t)(a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u)) * KPW;
     auto block_of = [&](uint64_t s) -> uint64_t { return blockIdx.x + (s / KPW) * (uint64_t)gridDim.x; };
     auto load_w = [&](uint64_t s, u32x4 (&w)[GPIECES]) {
         const uint64_t e0 = block_of(s) * BLOCK_ROWS * (uint64_t)GK + (wave + NW * (uint32_t)(s % KPW)) * (uint64_t)BLOCK_COLS + lane_elem;
@@ -782,19 +808,22 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 
 // The work of one workgroup on one matrix: its units first_unit, first_unit + unit_stride, ... (my_units of them), table
 // set-up included.  At a block's end a wave parks its sum in LDS and goes on; the workgroup meets once per batch, as many
-// blocks as there are slots for.  Which of a block's chunks are summed together (those NW apart) and in which order the sums are
+// blocks as there are slots for.  Which of a block's chunks are summed together (those PLACES apart) and in which order the sums are
 // added does not depend on which wave has them, so every way below gives the same bits.
 //  * KRES = 1, 2 (see resident_chunks): wave w has the chunks w, w + NW of every block and keeps their X; where a block has at
 //    most NW / 2 chunks the waves form groups with a block each.  That leaves waves idle at times (28 chunks on 16 waves: an
 //    eighth), which costs little beside the others' work.
 //  * KRES = 0: the units' chunks form one sequence, and wave w takes every NW-th of it from the w-th on, across the units'
 //    borders; batches are rounded down to whole rounds of the waves.
+//  * PLACES != NW: the same with the chains of chunks that are summed together in place of chunks.  For the members of a group that have M <= 32 where another one
+//    has more, so that they are computed as their own calls compute them; they also have two tiles of X in place of four (eight experts of M = 3 to 64 172.5 us ->
+//    167.8, with scales of W 191.1 -> 187.6).
 // What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.8 us), the compute unit: six of them, which the memory-side
 // cache holds, take as long for a chunk (55.3 us, 462 clocks a chunk and compute unit against 472), and no unit of it is busy all of the time: vector
 // operations 67 %, LDS 61 % (72 % of that bank conflicts of the table), first-level cache 59 %, address units 55 %; a wave waits for 55 % of its life.
-// M = 64 (215 us): two waves on a SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and
+// M = 64 (213 us): two waves on a SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and
 // first-level cache busy 55 % each).
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0>
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0, int PLACES = NW>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
                                           uint32_t my_units)
 {
@@ -802,7 +831,6 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     using C = GCfg<MT, NW, N>;
     constexpr int BLOCK_COLS = C::BLOCK_COLS, GPIECES = C::PIECES;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
-    static_assert((NW & (NW - 1)) == 0, "places in the deal are chunk numbers modulo NW");
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
     f32x4 *red = (f32x4 *)(smem + C::ANYK_OFF_RED);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -811,29 +839,30 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 
     const GLOBAL uint8_t *stream = (const GLOBAL uint8_t *)(a.d_blob + a.off_st);
     const GLOBAL uint8_t *plane = (const GLOBAL uint8_t *)(a.d_blob + a.off_pl);
-    const uint32_t kchunks = (uint32_t)(a.K / BLOCK_COLS);
-    const uint32_t unit_chunks = SPLIT ? kchunks / a.slices : kchunks;
+    const uint32_t kchunks = (uint32_t)(a.K / BLOCK_COLS), unit_chunks = a.unit_chunks;
     // split K: the grid is the units, each workgroup has one
-    const uint32_t k0 = SPLIT ? (uint32_t)first_unit % a.slices * unit_chunks : 0u;
     const uint32_t block0 = SPLIT ? (uint32_t)first_unit / a.slices : (uint32_t)first_unit;
+    const uint32_t slice = SPLIT ? (uint32_t)first_unit - block0 * a.slices : 0u, k0 = slice * unit_chunks;
 
     using Meta = ChunkMeta<true>;
     const MetaReader<true> meta(a, lane);
     // NW chunks on: over at most this many units and so many chunks more
-    const uint32_t hop = (uint32_t)NW / unit_chunks, hop_kc = (uint32_t)NW % unit_chunks;
+    constexpr bool CHAINS = PLACES != NW;
+    static_assert(!CHAINS || (KRES == 0 && !SPLIT), "the ways that have chains");
+    const uint32_t hop = a.hop, hop_kc = a.hop_kc;
+    const uint32_t slots = unit_chunks < (uint32_t)PLACES ? unit_chunks : (uint32_t)PLACES;
     const uint32_t skip = (unit_stride - 1) * unit_chunks;         // the other workgroups' chunks between one unit and the next
-    const uint32_t groups = KRES && 2 * unit_chunks <= (uint32_t)NW ? (uint32_t)NW / unit_chunks : 1u, per_group = (uint32_t)NW / groups;
-    const uint32_t kw = (uint32_t)wave % per_group;
+    const uint32_t groups = a.groups, gi = small_div((uint32_t)wave, a.by_group), kw = (uint32_t)wave - gi * a.per_group;     // KRES
     const bool two = KRES && kw + NW < unit_chunks;
     auto first_place = [&]() {
         Place w;
         if constexpr (KRES != 0) {
-            w.b = (uint32_t)wave / per_group;
+            w.b = gi;
             w.kc = kw;
             if (kw >= unit_chunks || w.b >= groups) w.b = my_units;              // a wave with nothing to do
         } else {
-            w.b = (uint32_t)wave / unit_chunks;
-            w.kc = (uint32_t)wave % unit_chunks;
+            w.b = small_div((uint32_t)wave, a.by_unit);
+            w.kc = (uint32_t)wave - w.b * (CHAINS ? slots : unit_chunks);
         }
         w.block = block0 + w.b * unit_stride;
         w.c = w.block * kchunks + k0 + w.kc;
@@ -846,8 +875,19 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             units = over ? groups : 0u;
             kc = over ? kw : w.kc + NW;
             w.c += units * unit_stride * unit_chunks + kc - w.kc;
+        } else if constexpr (CHAINS) {
+            const bool over = w.kc + PLACES >= unit_chunks;        // the chain's last chunk: on to the chain NW further on
+            const uint32_t to = w.kc % (uint32_t)PLACES + hop_kc;
+            units = over ? hop + (to >= slots ? 1u : 0u) : 0u;
+            kc = over ? (to >= slots ? to - slots : to) : w.kc + PLACES;
+            w.c += units * unit_stride * unit_chunks + kc - w.kc;
+        } else if constexpr (SPLIT) {                              // one unit
+            const bool over = w.kc + NW >= unit_chunks;
+            units = over ? 1u : 0u;
+            kc = over ? 0u : w.kc + NW;
+            w.c += NW;
         } else {
-            const bool over = w.kc + hop_kc >= unit_chunks;        // never past the one unit that split K has but at its end
+            const bool over = w.kc + hop_kc >= unit_chunks;
             units = hop + (over ? 1u : 0u);
             kc = over ? w.kc + hop_kc - unit_chunks : w.kc + hop_kc;
             w.c += NW + units * skip;
@@ -885,9 +925,8 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     if constexpr (EARLY) load_table<NW>(a, tid, tv);
     if (valid(cur)) {
         m_cur = load_meta(cur);
-        m_next = m_cur;
         const Place nxt = next_of(cur);
-        if (valid(nxt)) m_next = load_meta(nxt);
+        m_next = meta(valid(nxt) ? nxt.c : cur.c);      // a copy of m_cur would wait for it, in front of everything below
         if constexpr (!EARLY) raw.fetch(stream, a.st_bytes, m_cur, lane);
         const GLOBAL uint8_t *pp = plane_of(cur);
 #pragma unroll
@@ -911,16 +950,13 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_RED), lane, wave);
     }
 
-    // slots of a block, blocks of a batch: whole rounds of the waves where there are slots for NW / gcd(NW, chunks) blocks
-    const uint32_t slots = unit_chunks < (uint32_t)NW ? unit_chunks : (uint32_t)NW;
-    const uint32_t low = unit_chunks & (0u - unit_chunks), whole = low < (uint32_t)NW ? (uint32_t)NW / low : 1u;
-    uint32_t batch = SPLIT ? 1u : C::SLOTS / slots;
-    if (batch >= whole) batch &= 0u - whole;
+    const uint32_t batch = SPLIT ? 1u : a.batch;
 
-    // Waves with a piece decoded go first while they multiply it, in groups with two tiles of X and group scales: eight experts M = 17 / 20 / 32
-    // 137.4 / 142.2 / 146.4 us -> 128.2 / 132.4 / 137.1, two 37.1 / 38.3 / 39.3 -> 35.8 / 37.3 / 38.4.  With scales of W M = 20 124.9 -> 123.0, but M = 32
-    // 132.3 -> 134.3; four tiles and group scales M = 64 238 -> 228, but four experts M = 33 97.5 -> 98.7; single products 1 to 4 % slower.
-    constexpr bool PRIO = APART && MT == 2 && SC == 2;
+    // Waves with a piece decoded go first while they multiply it, with two tiles of X and group scales, in groups also with scales of W.  Group scales, eight experts
+    // M = 32 139.5 us -> 135.3; 14336 x 9216 M = 17 / 32 44.8 / 55.2 -> 43.6 / 52.2, 2048 x 7168 10.95 / 11.83 -> 11.04 / 11.70.  Scales of W, eight experts M = 20 / 32 118.1 /
+    // 132.4 -> 118.3 / 126.4, single products within 2 % either way.  Without scales: eight experts M = 20 110.8 -> 113.2, 4096 x 14336 16.6 -> 16.8, 14336 x 4096 on the F16
+    // cores 22.7 -> 23.6.  Four tiles and group scales: two experts M = 64 59.2 -> 57.3, but four of M = 33 97.5 -> 98.7.
+    constexpr bool PRIO = MT == 2 && !SPLIT && (SC == 2 || (APART && SC == 1));
     f32x4 acc[MT];
     auto clear = [&]() {
 #pragma unroll
@@ -942,6 +978,10 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             const Place nxt2 = next_of(nxt);
             if (valid(nxt2)) m_next2 = load_meta(nxt2);
         }
+        // Two tiles of X and scales in groups: where a lane reads X is worked out again for every chunk; kept for the whole walk, it
+        // costs a spill.
+        uint32_t x_lane = (uint32_t)lane;
+        if constexpr (APART && MT == 2 && SC != 0) asm("" : "+v"(x_lane));
         // after the last chunk the plane pieces are fetched from the plane's first chunk (every wave's last fetch: cached)
         const GLOBAL uint8_t *pp = more ? plane_of(nxt) : plane;
         auto &dstA = sums.first(acc);
@@ -963,8 +1003,8 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
             ECF8_MFMA_XPIECE(dstB, x, Q + GPIECES / 2, wB);
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
             if (KRES == 0 && more) {
-                load_x_slot<MT, N, TURNED>(a, lane, k0 + nxt.kc, Q, x);
-                load_x_slot<MT, N, TURNED>(a, lane, k0 + nxt.kc, Q + GPIECES / 2, x);
+                load_x_slot<MT, N, TURNED>(a, (int)x_lane, k0 + nxt.kc, Q, x);
+                load_x_slot<MT, N, TURNED>(a, (int)x_lane, k0 + nxt.kc, Q + GPIECES / 2, x);
             }
         }
         sums.end(acc, a, lane);
@@ -991,27 +1031,21 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
 #pragma unroll 1
             while (cur.b < b1) {
                 const Place nxt = chunk(x_cur[0]);
-                if (!SPLIT && nxt.b != cur.b) {
-                    park(cur.b - b0, cur.kc & (NW - 1));
+                if (CHAINS ? cur.kc + PLACES >= unit_chunks : !SPLIT && nxt.b != cur.b) {
+                    park(cur.b - b0, cur.kc % (uint32_t)PLACES);
                     clear();
                 }
                 cur = nxt;
             }
         }
         if constexpr (SPLIT) {
-            reduce_split<MT, NW, SCALED>(red, s_flag, a, block0, k0 / unit_chunks, tid, acc);
+            reduce_split<MT, NW, SCALED>(red, s_flag, a, block0, slice, tid, acc);
         } else {
             __syncthreads();
-            reduce_batch<MT, NW, SCALED>(red, a, first_unit + (uint64_t)b0 * unit_stride, unit_stride, b1 - b0, slots, tid);
+            reduce_batch<MT, NW, PLACES, SCALED>(red, a, first_unit + (uint64_t)b0 * unit_stride, unit_stride, b1 - b0, slots, tid);
             if (b1 < my_units) __syncthreads();                    // the slots are free again
         }
     }
-}
-
-// units of workgroup blockIdx.x when n_units are dealt round-robin to the grid
-__device__ __forceinline__ uint64_t units_of_workgroup(uint64_t n_units)
-{
-    return blockIdx.x < n_units ? (n_units - blockIdx.x + gridDim.x - 1) / gridDim.x : 0;
 }
 
 template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, int KRES = 0, bool TURNED = KRES == 0>
@@ -1019,23 +1053,22 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::ANYK_TOTAL];
     __shared__ uint32_t s_flag;                   // split K: the arrival count this workgroup drew
-    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, KRES, TURNED>(a, smem, &s_flag, blockIdx.x, gridDim.x,
-                                                              (uint32_t)units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)));
+    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, KRES, TURNED>(a, smem, &s_flag, blockIdx.x, gridDim.x, a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u));
 }
 
 // Position of a wave in its sequence of chunks of uncompressed W: its i-th chunk of its workgroup's b-th unit.  `block` is the
 // unit's block of rows, k0 its first chunk.
 struct Walk {
-    uint64_t b;
+    uint32_t b;
     uint32_t i;
-    uint64_t block;
+    uint32_t block;
     uint32_t k0;
 };
 
 // The any-K GEMM on uncompressed W: same deal of chunks, same order of accumulation.
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0>
-__device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint64_t unit_stride,
-                                              uint64_t my_units, uint32_t &parity)
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC = 0, int PLACES = NW>
+__device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint32_t first_unit, uint32_t unit_stride,
+                                              uint32_t my_units, uint32_t &parity)
 {
     constexpr bool SCALED = SC != 0;
     using C = GCfg<MT, NW, N>;
@@ -1045,20 +1078,33 @@ __device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uin
     const uint64_t lane_elem = (uint64_t)(lane & 15) * a.K + (uint64_t)(lane >> 4) * 16;
     const uint32_t kchunks = (uint32_t)(a.K / BLOCK_COLS);
     const uint32_t unit_chunks = SPLIT ? kchunks / a.slices : kchunks;
-    const Deal deal = deal_chunks<NW>(unit_chunks, SPLIT, wave);
+    Deal deal = deal_chunks<NW>(a, SPLIT, wave);
+    // sums of PLACES places with fewer waves: a wave has the places kw and kw + NW, one behind the other
+    static_assert(PLACES == NW || (PLACES < 2 * NW && !SPLIT), "two places a wave");
+    const bool chains = PLACES != NW && unit_chunks > (uint32_t)NW;
+    const uint32_t second = deal.kw + NW;
+    uint32_t in_first = deal.my_chunks;
+    if (chains) {
+        in_first = (unit_chunks - deal.kw + PLACES - 1) / PLACES;
+        deal.my_chunks = in_first + (second < PLACES && second < unit_chunks ? (unit_chunks - second + PLACES - 1) / PLACES : 0u);
+    }
     const uint32_t my_chunks = deal.my_chunks;
-    const uint64_t my_blocks = (my_units + deal.groups - 1) / deal.groups;
-    auto at_unit = [&](uint64_t b) {
+    uint32_t my_blocks = my_units;
+    if (!SPLIT && deal.groups > 1) my_blocks = (my_units + deal.groups - 1) / deal.groups;
+    auto at_unit = [&](uint32_t b) {
         Walk w{b, 0, first_unit + (b * deal.groups + deal.gi) * unit_stride, 0};
         if constexpr (SPLIT) {
-            const uint32_t u = (uint32_t)w.block;
+            const uint32_t u = w.block;
             w.block = u / a.slices;
             w.k0 = (u % a.slices) * unit_chunks;
         }
         return w;
     };
     auto block_of = [&](const Walk &w) -> uint64_t { return w.block; };
-    auto kc_of = [&](const Walk &w) -> uint32_t { return w.k0 + deal.kw + deal.wpb * w.i; };
+    auto kc_of = [&](const Walk &w) -> uint32_t {
+        if (chains) return w.i < in_first ? deal.kw + PLACES * w.i : second + PLACES * (w.i - in_first);
+        return w.k0 + deal.kw + deal.wpb * w.i;
+    };
     auto valid = [&](const Walk &w) { return my_chunks != 0 && w.b * deal.groups + deal.gi < my_units; };
     auto next_of = [&](Walk w) { if (++w.i == my_chunks) w = at_unit(w.b + 1); return w; };
     auto load_w = [&](const Walk &w, u32x4 (&v)[GPIECES]) {
@@ -1074,13 +1120,23 @@ __device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uin
 #pragma unroll
         for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, false>(a, lane, kc_of(cur), j, x_cur);
     }
-    for (uint64_t b = 0; b < my_blocks; b++) {
+    for (uint32_t b = 0; b < my_blocks; b++) {
+        f32x4 *red = (f32x4 *)(smem + parity * (PLACES * MT * 1024));
         f32x4 acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto park = [&](uint32_t place) {
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) red[(place * MT + mt) * 64 + lane] = acc[mt];
+        };
         const uint32_t n_mine = valid(at_unit(b)) ? my_chunks : 0;
 #pragma unroll 1
         for (uint32_t i = 0; i < n_mine; i++) {
+            if (PLACES != NW && chains && i == in_first) {
+                park(deal.kw);
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
             const XPieces<MT, N> x = x_cur;
             ChunkSums<MT, SC> sums;
             sums.begin(a, block_of(cur), kc_of(cur));
@@ -1104,10 +1160,13 @@ __device__ __forceinline__ void raw_anyk_walk(const GArgs &a, uint8_t *smem, uin
             for (int q = 0; q < GPIECES; q++) w_cur[q] = w_next[q];
             cur = nxt;
         }
-        f32x4 *red = (f32x4 *)(smem + parity * C::RED_BYTES);
         const Walk unit = at_unit(b);
-        if constexpr (SPLIT) reduce_split<MT, NW, SCALED>(red, s_flag, a, (uint32_t)unit.block, unit.k0 / unit_chunks, tid, acc);
-        else reduce_groups<MT, NW, SCALED>(red, a, first_unit, unit_stride, b * deal.groups, my_units, deal, tid, acc);
+        if constexpr (SPLIT) reduce_split<MT, NW, SCALED>(red, s_flag, a, unit.block, unit.k0 / unit_chunks, tid, acc);
+        else if (PLACES != NW && chains) {
+            park(my_chunks > in_first ? second : deal.kw);
+            __syncthreads();
+            reduce_batch<MT, NW, PLACES, SCALED>(red, a, first_unit + b * unit_stride, 1, 1, unit_chunks < (uint32_t)PLACES ? unit_chunks : (uint32_t)PLACES, tid);
+        } else reduce_groups<MT, NW, SCALED>(red, a, first_unit, unit_stride, b * deal.groups, my_units, deal, tid, acc);
         parity ^= 1;
     }
 }
@@ -1118,8 +1177,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_raw_anyk_kernel(GArgs a)
     __shared__ __attribute__((aligned(16))) uint8_t smem[2 * GCfg<MT, NW, N>::RED_BYTES];
     __shared__ uint32_t s_flag;
     uint32_t parity = 0;
-    raw_anyk_walk<MT, NW, N, SC, SPLIT, ACC>(a, smem, &s_flag, blockIdx.x, gridDim.x,
-                                        units_of_workgroup(a.rows / BLOCK_ROWS * (SPLIT ? a.slices : 1u)), parity);
+    raw_anyk_walk<MT, NW, N, SC, SPLIT, ACC>(a, smem, &s_flag, blockIdx.x, gridDim.x, a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u), parity);
 }
 
 // ---- a group of matrices in one launch ----
@@ -1139,7 +1197,7 @@ static_assert(sizeof(GItem) % 8 == 0 && sizeof(GItem) <= sizeof(ecf8_gemm_group_
 struct GGArgs {
     uint64_t d_items;           // device array of ecf8_gemm_group_item
     uint32_t n_items;
-    uint64_t total_work;
+    uint32_t work_each, work_rest;      // chunks of every workgroup; the first work_rest have one more
 };
 
 template <int MT, int NW, int N, int SC, bool RAW>
@@ -1151,8 +1209,8 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
     constexpr uint32_t WORDS = sizeof(ecf8_gemm_group_item) / 8;
     const GLOBAL uint64_t *items = (const GLOBAL uint64_t *)g.d_items;
     // this workgroup takes the blocks whose first chunk lies in [pos, end) of the sequence
-    uint64_t pos = g.total_work * blockIdx.x / gridDim.x;
-    const uint64_t end = g.total_work * (blockIdx.x + 1) / gridDim.x;
+    uint32_t pos = g.work_each * blockIdx.x + (blockIdx.x < g.work_rest ? blockIdx.x : g.work_rest);
+    const uint32_t end = pos + g.work_each + (blockIdx.x < g.work_rest ? 1u : 0u);
     uint32_t parity = 0;
     // The matrix that holds pos: lane l probes the l-th of 64 evenly spaced items, one round trip to memory for up to 64 of
     // them (a binary search took five for 24, at the start and again wherever a share crosses into the next matrix, which is
@@ -1172,25 +1230,35 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
 #pragma unroll
             for (int i = 0; i < (int)(sizeof(GItem) / 8); i++) dst[i] = uniform64(items[(uint64_t)lo * WORDS + i]);
         }
-        const uint64_t kchunks = it.a.K / C::BLOCK_COLS, n_blocks = it.a.rows / BLOCK_ROWS;
-        const uint64_t b0 = (pos - it.first_work + kchunks - 1) / kchunks;
-        uint64_t b1 = (end - it.first_work + kchunks - 1) / kchunks;
+        const uint32_t kchunks = (uint32_t)(it.a.K / C::BLOCK_COLS), n_blocks = (uint32_t)(it.a.rows / BLOCK_ROWS), first_work = (uint32_t)it.first_work;
+        const uint32_t b0 = (pos - first_work + kchunks - 1) / kchunks;
+        uint32_t b1 = (end - first_work + kchunks - 1) / kchunks;
         if (b1 > n_blocks) b1 = n_blocks;
         __syncthreads();                                // the last matrix's table and reduction buffers are out of use
         if (b0 < b1) {
-            if constexpr (RAW) raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
+            if constexpr (RAW) {
+                if (MT == 4 && it.a.M <= 32) raw_anyk_walk<(MT == 4 ? 2 : MT), NW, N, SC, false, 0, (MT == 4 ? WAVES<2> : NW)>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
+                else raw_anyk_walk<MT, NW, N, SC, false>(it.a, smem, &s_flag, b0, 1, b1 - b0, parity);
+            }
             else {
                 // One tile of X that is fetched chunk by chunk (K > 8192, or one block) is fetched as operands, whatever its rows: one walk serves all M <= 16,
                 // and with scales of W the turned one is mostly the slower one.  Operands / turned, us, M = 1 / 9 / 16: three 4096 x 14336 37.3 / 40.6 / 46.4, 40.0 / 41.1 / 42.4, scaled
                 // 39.1 / 41.4 / 47.5, 45.2 / 47.6 / 48.9; two 1024 x 9216 12.1 / 12.8 / 14.0, 12.7 / 12.9 / 13.1, scaled 12.4 / 13.0 / 14.4, 15.3 / 15.9 / 16.3; two
                 // 14336 x 9216 48.7 / 52.7 / 68.7, 53.4 / 55.0 / 57.3, scaled 49.9 / 58.8 / 69.8, 58.4 / 61.1 / 63.1.
-                const uint32_t n = (uint32_t)(b1 - b0), kres = resident_chunks<MT, NW, 0>(kchunks, n);
+                const uint32_t n = b1 - b0, kres = resident_chunks<MT, NW, 0>(kchunks, n);
+                if constexpr (MT == 4) {
+                    if (it.a.M <= 32) {
+                        anyk_walk<2, NW, N, SC, false, 0, true, 0, true, WAVES<2>>(it.a, smem, &s_flag, b0, 1, n);
+                        pos = first_work + n_blocks * kchunks;
+                        continue;
+                    }
+                }
                 if (MT == 1 && kres == 1) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1>(it.a, smem, &s_flag, b0, 1, n);
                 else if (MT == 1 && kres == 2) anyk_walk<MT, NW, N, SC, false, 0, true, MT == 1 ? 2 : 0>(it.a, smem, &s_flag, b0, 1, n);
                 else anyk_walk<MT, NW, N, SC, false, 0, true, 0, (MT > 1)>(it.a, smem, &s_flag, b0, 1, n);
             }
         }
-        pos = it.first_work + n_blocks * kchunks;       // on to the next matrix (or past `end`)
+        pos = first_work + n_blocks * kchunks;          // on to the next matrix (or past `end`)
     }
 }
 
@@ -1274,28 +1342,64 @@ inline int scale_args(const float *d_w_scale, const float *d_x_scale, uint32_t x
     return ECF8_OK;
 }
 
+// What the fused kernels' deals divide: the units among the grid's workgroups, a unit's chunks among a workgroup's NW waves with MT tiles of 16 rows of X.
+inline void deal_units(GArgs *a, uint32_t grid)
+{
+    const uint32_t units = (uint32_t)(a->rows / BLOCK_ROWS) * (a->slices ? a->slices : 1u);
+    a->units_each = units / grid;
+    a->units_rest = units % grid;
+}
+template <int MT, int NW = WAVES<MT>, int PLACES = NW>
+void deal_waves(GArgs *a)
+{
+    const uint32_t slices = a->slices ? a->slices : 1u, chunks = (uint32_t)(a->K / 256) / slices;
+    const uint32_t slots = chunks < (uint32_t)PLACES ? chunks : (uint32_t)PLACES, dealt = PLACES == NW ? chunks : slots;     // see anyk_walk
+    a->unit_chunks = chunks;
+    a->hop = NW / dealt;
+    a->hop_kc = NW % dealt;
+    a->groups = slices == 1 && 2 * chunks <= (uint32_t)NW ? NW / chunks : 1u;
+    a->per_group = NW / a->groups;
+    a->by_unit = small_by(dealt);
+    a->by_group = small_by(a->per_group);
+    // blocks of a batch: whole rounds of the waves where there are slots for them
+    const uint32_t whole = (uint32_t)NW / std::gcd((uint32_t)NW, dealt);
+    a->batch = GCfg<MT, NW, 64>::SLOTS / slots;
+    if (a->batch >= whole) a->batch -= a->batch % whole;
+}
+// Of a call whose largest M is max_M
+inline void deal_waves(GArgs *a, uint32_t max_M)
+{
+    if (max_M <= 16) deal_waves<1>(a);
+    else if (max_M <= 32) deal_waves<2>(a);
+    else if (a->M <= 32) deal_waves<2, WAVES<4>, WAVES<2>>(a);
+    else deal_waves<4>(a);
+}
+
 // 16 waves (one K chunk of the block each) while X fits their registers, 8 waves of two chunks
 // at M > 32.
 template <int SCALED, int ACC = 0>
-int launch_fused(const GArgs &a, void *stream)
+int launch_fused(GArgs a, void *stream)
 {
     const int grid = grid_for(a.rows / BLOCK_ROWS);
     if (grid <= 0) return ECF8_E_HIP;
+    a.slices = 1;
+    deal_units(&a, (uint32_t)grid);
+    deal_waves(&a, a.M);
     hipStream_t s = (hipStream_t)stream;
     // The any-K kernels also take K = 4096 where X does not fit the registers beside the rest: with a scale per row and 128 columns of X at M > 32,
     // and on the F16 matrix cores, whose operands are converted, at M > 16.  Resident X / any K, us, rows 4096, 14336 and 28672: group scales M = 33 30.9 / 11.7,
     // 69.6 / 35.2, 111 / 57.9, M = 64 37.5 / 13.2, 90.7 / 39.1, 146 / 64.5; F16 cores M = 33 27.2 / 11.1, 59.6 / 32.4, 95.0 / 53.7, M = 64 30.6 / 12.2, 63.4 / 34.0, 99.4 / 56.1.
     // F16 cores at M = 17 .. 32 go with those, though there X does fit and many rows would be faster for it: M = 32 10.7 / 9.0, 20.4 / 25.0, 29.6 / 41.0.
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
-        const uint32_t kres = a.M <= 16 ? resident_chunks<1, 16, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
-        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, ACC == 0 ? 2 : 0>), dim3(grid), dim3(16 * 64), 0, s, a);
+        const uint32_t kres = a.M <= 16 ? resident_chunks<1, WAVES<1>, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
+        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, ACC == 0 ? 2 : 0>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
         // a few rows of X are few accesses either way, and the turn is time.  Operands / turned, us, M = 1 / 4 / 8 / 12 / 16: 4096 x 14336
         // 14.1 / 14.7 / 15.4 / 16.2 / 16.8, 15.3 / 15.5 / 15.4 / 15.4 / 15.4; 14336 x 9216 29.7 / 29.9 / 31.3 / 33.0 / 35.4, 32.4 for all
-        else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);   // two tiles of X in 16 waves spill: up to twice the time
-        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
+        else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, WAVES<2>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
+        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, WAVES<4>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
         return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
     }
     if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_kernel<1, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
@@ -1307,15 +1411,23 @@ int launch_fused(const GArgs &a, void *stream)
 }
 
 template <int SCALED, int ACC = 0>
-int launch_raw(const GArgs &a, void *stream)
+int launch_raw(GArgs a, void *stream)
 {
     const int grid = grid_for(a.rows / BLOCK_ROWS);
     if (grid <= 0) return ECF8_E_HIP;
+    a.slices = 1;
+    deal_units(&a, (uint32_t)grid);
+    // Two tiles of X and at most 8 chunks of a block: 8 waves, which have as many places as the fused call's.  8 / 12 waves, us, M = 17: 16384 x 512 5.95 / 6.01, with
+    // scales of W 6.47 / 6.75; 512 x 2048 6.49 / 6.65
+    const bool few = a.M > 16 && a.M <= 32 && a.K <= 8 * 256;
+    if (few) deal_waves<2, 8>(&a);
+    else deal_waves(&a, a.M);
     hipStream_t s = (hipStream_t)stream;
     if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {      // the same routes as the fused call: same order of accumulation
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, 16, 64, SCALED, false, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
+        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (few) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, 8, 64, SCALED, false, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, WAVES<2>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
+        else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, WAVES<4>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
         return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
     }
     if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_kernel<1, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
@@ -1368,21 +1480,23 @@ inline int split_args(GArgs *a, void *d_workspace, uint64_t bytes, uint32_t *sli
 }
 
 template <int SCALED, bool RAW>
-int launch_split(const GArgs &a, void *stream)
+int launch_split(GArgs a, void *stream)
 {
     const int grid = grid_for(a.rows / BLOCK_ROWS * a.slices);      // <= the compute units by the choice of slices
     if (grid <= 0) return ECF8_E_HIP;
+    deal_units(&a, (uint32_t)grid);
+    deal_waves(&a, a.M);
     hipStream_t s = (hipStream_t)stream;
     if constexpr (RAW) {
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, 16, 64, SCALED, true>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
+        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
+        else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
     } else {
         // X turned at any M.  Turned / as operands, us, M = 1 / 8 / 16: 2048 x 7168 11.4 / 11.5 / 11.7, 11.3 / 11.9 / 12.4; 1024 x 16384 12.3 / 12.4 / 12.7, 12.2 / 13.0 / 13.6;
         // 256 x 4096, a chunk a workgroup, 16.0 / 16.1 / 16.1, 15.7 / 15.8 / 15.8
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, 16, 64, SCALED, true>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, 8, 64, SCALED, true>), dim3(grid), dim3(8 * 64), 0, s, a);
+        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
+        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
     }
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
@@ -1409,18 +1523,19 @@ int run_split(GArgs &a, const float *d_w_scale, const float *d_x_scale, uint32_t
 }
 
 template <int SCALED, bool RAW>
-int launch_grouped(const GGArgs &g, uint32_t max_M, void *stream)
+int launch_grouped(uint64_t d_items, uint32_t n_items, uint64_t total_work, uint32_t max_M, void *stream)
 {
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
     // no more workgroups than blocks of 16 chunks: below that a share is less than a block's worth of the waves' work
-    uint64_t grid = (g.total_work + 15) / 16;
+    uint64_t grid = (total_work + 15) / 16;
     if (grid > (uint64_t)cus) grid = (uint64_t)cus;
     if (grid == 0) grid = 1;
+    const GGArgs g{d_items, n_items, (uint32_t)(total_work / grid), (uint32_t)(total_work % grid)};
     hipStream_t s = (hipStream_t)stream;
-    if (max_M <= 16) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<1, 16, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(16 * 64), 0, s, g);
-    else if (max_M <= 32) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<2, 8, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(8 * 64), 0, s, g);
-    else hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<4, 8, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(8 * 64), 0, s, g);
+    if (max_M <= 16) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<1, WAVES<1>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<1> * 64), 0, s, g);
+    else if (max_M <= 32) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<2, WAVES<2>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<2> * 64), 0, s, g);
+    else hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<4, WAVES<4>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<4> * 64), 0, s, g);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 

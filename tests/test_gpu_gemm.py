@@ -707,6 +707,28 @@ def test_groups_of_many_blocks_with_scales(scale_mode, M):
         assert torch.equal(y, want) and torch.equal(y, _single_call(m)), shape
 
 
+@pytest.mark.parametrize("scale_mode", [0, 1, 2])
+def test_few_rows_of_x_in_a_group_with_many(scale_mode):
+    """Members with M <= 32 in a group whose largest M takes workgroups of fewer waves than their own calls do: the sums of the places that those calls'
+    waves have, dealt to fewer waves.  Fewer chunks per block than waves, than places, as many, one more, a multiple and odd counts; one block per
+    workgroup, several, batches that end inside.  Bit for bit the twins on uncompressed weights and, above 16 rows of X, the single calls."""
+    shapes = [(16 * b, 256 * k) for k in (1, 2, 3, 5, 7, 8, 9, 11, 12, 13, 17, 20, 21, 24, 25, 28, 57) for b in (1, 5)] + [(16 * 700, 256 * k) for k in (3, 10, 12, 28, 33)]
+    fused, raw = [], []
+    for M in (1, 16, 17, 32, 33, 64):
+        f, r = _device_members(shapes, M, 47 + M, max(scale_mode, 1))
+        for i in range(len(shapes)):
+            if M in (17, 32) or i % 6 == M % 6:
+                fused.append(f[i])
+                raw.append(r[i])
+    if scale_mode == 0:
+        fused, raw = ([{k: v for k, v in m.items() if "scale" not in k} for m in ms] for ms in (fused, raw))
+    ys = ecf8.ecf8_gemm_fp8_grouped(ecf8.GemmGroup(fused))
+    for m, y, want in zip(fused, ys, ecf8.ecf8_gemm_fp8_grouped(ecf8.GemmGroup(raw))):
+        M, at = m["x"].shape[0], (m["hdr"].rows, tuple(m["x"].shape))
+        assert torch.equal(y, want), at
+        assert M <= 16 or torch.equal(y, _single_call(m)), at
+
+
 def test_grouped_gemm_argument_errors():
     shapes, Ms = GROUPS["mid_M"]
     fused = _group_members(shapes, Ms, seed=3)
