@@ -161,6 +161,25 @@ __device__ __forceinline__ void build_tables(uint64_t len_lo, uint64_t len_hi, u
     __syncthreads();
 }
 
+// The pair table from the codewords of the 128 short indices, which wave 0 has put into tmp as the second codeword of an entry.
+template <int NW>
+__device__ __forceinline__ void fill_pair_table(uint16_t *tbl, const uint32_t *tmp, int lane, int wave)
+{
+    constexpr uint32_t H = TB / 2;
+    __syncthreads();
+    const u32x2 t = *(const u32x2 *)(tmp + 2 * lane);
+    const uint32_t l0 = t.x >> 7 & 7u, l1 = t.y >> 7 & 7u;
+    const uint32_t f0 = (t.x >> 8 & 0x78u) | l0 | l0 << 7, f1 = (t.y >> 8 & 0x78u) | l1 | l1 << 7;       // as the first one
+    const uint32_t at0 = ((2u * lane) >> l0) << 2, at1 = ((2u * lane + 1u) >> l1) << 2;    // byte offsets into tmp
+#pragma unroll 4
+    for (uint32_t hi = (uint32_t)wave; hi < (1u << H); hi += NW) {
+        const uint32_t v0 = f0 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l0)) & (((1u << H) - 1) << 2)) | at0));
+        const uint32_t v1 = f1 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l1)) & (((1u << H) - 1) << 2)) | at1));
+        ((uint32_t *)tbl)[(hi << (H - 1)) + lane] = v0 | (v1 << 16);
+    }
+    __syncthreads();
+}
+
 // The pair table of a code whose codewords have at most TB/2 = 7 bits (the encoder's default cap), from the 16 code
 // lengths.  `tmp` is 128 words of scratch LDS; the workgroup has NW wavefronts and meets twice in here.
 // What bounds it: instruction issue, once per workgroup and tensor.  Under the cap an entry is the sum of two parts, the
@@ -196,21 +215,42 @@ __device__ __forceinline__ void build_pair_table(uint64_t len_lo, uint64_t len_h
         r1 += at <= x1;
     }
     const uint32_t c0 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(r0 * 4 - 4), (int)ranked), c1 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(r1 * 4 - 4), (int)ranked);
-    const uint32_t l0 = c0 >> 8, l1 = c1 >> 8, s0 = c0 & 15u, s1 = c1 & 15u;
-    if (wave == 0) {                          // as the second codeword of an entry
-        tmp[2 * lane] = (s0 << 11) | (l0 << 7);
-        tmp[2 * lane + 1] = (s1 << 11) | (l1 << 7);
+    if (wave == 0) *(u32x2 *)(tmp + 2 * lane) = u32x2{(c0 & 15u) << 11 | c0 >> 8 << 7, (c1 & 15u) << 11 | c1 >> 8 << 7};
+    fill_pair_table<NW>(tbl, tmp, lane, wave);
+}
+
+// Where a call on one tensor has its code from: the pair table lies in the blob, or the arguments end with the codewords of the 128 short indices, from the
+// host: symbol | length << 4, two for a lane.  One wave fetches these (with all 16 of 1024 workgroups' waves products took 0.1 to 0.4 us longer), and more than half of
+// the instructions above, which are one chain, are not done in every workgroup: products on blobs without a table, us, 512 x 2048 M = 1 / 16 / 64 6.8 / 7.2 / 8.8 ->
+// 5.7 / 6.3 / 7.8, split 12.9 / 13.0 / 14.9 -> 11.2 / 11.3 / 14.3, 64 x 4096 M = 16 9.3 -> 7.9, 256 x 14336 M = 16 15.6 -> 14.2.
+struct TableInBlob {};
+struct ShortCodes {
+    uint16_t two[64];
+};
+template <int NW>
+__device__ __forceinline__ void build_pair_table(uint32_t two, uint16_t *tbl, uint32_t *tmp, int lane, int wave)
+{
+    if (wave == 0) *(u32x2 *)(tmp + 2 * lane) = u32x2{(two & 15u) << 11 | (two & 0x70u) << 3, (two & 0xf00u) << 3 | (two & 0x7000u) >> 5};
+    fill_pair_table<NW>(tbl, tmp, lane, wave);
+}
+// Any 16 lengths give some codewords of 1 to 7 bits (blobs that break the promise decode to wrong bytes, in bounds).
+inline ShortCodes short_codes(const uint8_t *code_len)
+{
+    uint8_t of[128], e = 0x70;
+    uint32_t at = 0;
+    for (uint32_t l = 1; l <= TB / 2; l++)
+        for (uint32_t s = 0; s < 16; s++) {
+            if (code_len[s] != l) continue;
+            e = (uint8_t)(s | l << 4);
+            for (uint32_t k = 0; k < 128u >> l && at < 128; k++) of[at++] = e;
+        }
+    while (at < 128) of[at++] = e;
+    ShortCodes c;
+    for (uint32_t i = 0; i < 64; i++) {
+        const uint32_t x = (i & 1) << 5 | (i & 2) << 3 | (i & 4) << 1 | (i & 8) >> 1 | (i & 16) >> 3 | (i & 32) >> 5;      // the first bit most significant
+        c.two[i] = (uint16_t)(of[x] | of[x + 64] << 8);
     }
-    __syncthreads();
-    const uint32_t f0 = (s0 << 3) | l0 | (l0 << 7), f1 = (s1 << 3) | l1 | (l1 << 7);       // as the first one
-    const uint32_t at0 = ((2u * lane) >> l0) << 2, at1 = ((2u * lane + 1u) >> l1) << 2;    // byte offsets into tmp
-#pragma unroll 4
-    for (uint32_t hi = (uint32_t)wave; hi < (1u << H); hi += NW) {
-        const uint32_t v0 = f0 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l0)) & (((1u << H) - 1) << 2)) | at0));
-        const uint32_t v1 = f1 + *(const uint32_t *)((const uint8_t *)tmp + (((hi << (H + 2 - l1)) & (((1u << H) - 1) << 2)) | at1));
-        ((uint32_t *)tbl)[(hi << (H - 1)) + lane] = v0 | (v1 << 16);
-    }
-    __syncthreads();
+    return c;
 }
 
 // 32 stream bits in reading order (bit 0 = next bit to read) from LDS.

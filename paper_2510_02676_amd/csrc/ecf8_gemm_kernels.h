@@ -9,6 +9,7 @@
 
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 
 namespace {
 
@@ -123,7 +124,9 @@ __device__ __forceinline__ long hi64(u32x4 v) { return (long)(((uint64_t)v.w << 
 // A operands of a wave: for each of its chunks (K slices of 4N) and each piece q, the 16 bytes
 // X[m][4N kc + 64 q + 16 g .. + 16) of lane (m = l % 16, g = l / 16), loaded once and kept for
 // all blocks (X is M x K <= 256 KiB: half of the CU's register file at M = 64, but re-reading
-// it for each of ~900 blocks costs more than everything else).
+// it for each of ~900 blocks costs more than everything else).  Lanes of the rows from M on have the last row, no output that is stored depends on
+// them: loads under a condition are waited for one by one where the compiler joins their registers with zeros (64 x 4096 M = 1 7.2 us -> 6.3, 4096 x 4096 M = 32 / 64
+// 10.4 / 13.7 -> 9.9 / 13.0, 14336 x 4096 M = 64 24.4 -> 23.8).
 template <int MT, int NW, int N>
 __device__ __forceinline__ void load_x_slice(const GArgs &a, int tid,
                                              u32x4 (&areg)[MT][GCfg<MT, NW, N>::KPW][GCfg<MT, NW, N>::PIECES])
@@ -140,8 +143,7 @@ __device__ __forceinline__ void load_x_slice(const GArgs &a, int tid,
             for (int q = 0; q < C::PIECES; q++) {
                 const uint32_t m = 16 * mt + n;
                 const uint32_t k = (wave + NW * i) * C::BLOCK_COLS + 64 * q + 16 * g;
-                areg[mt][i][q] = u32x4{0, 0, 0, 0};
-                if (m < a.M) areg[mt][i][q] = *(const GLOBAL u32x4 *)(X + (uint64_t)m * GK + k);
+                areg[mt][i][q] = *(const GLOBAL u32x4 *)(X + (m < a.M ? m : a.M - 1) * (uint32_t)GK + k);
             }
 }
 
@@ -546,8 +548,8 @@ struct ShiftedRuns {
     }
 };
 
-template <int MT, int NW, int N, int SC, int ACC = 0>       // SC: 0 no scales, 1 scales of W (and one per row of X), 2 also one per row and 128 columns of X; ACC: see ECF8_MFMA_OPERANDS
-__global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
+template <int MT, int NW, int N, int SC, int ACC, class CODES>       // SC: 0 no scales, 1 scales of W (and one per row of X), 2 also one per row and 128 columns of X; ACC: see ECF8_MFMA_OPERANDS
+__global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a, CODES codes)
 {
     constexpr bool SCALED = SC != 0;
     static_assert(!SCALED || 4 * N == 2 * SCALE_BLOCK, "a chunk spans two scale blocks of K");
@@ -588,7 +590,13 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     // Only the first chunk's stream has to wait for anything (its metadata): the rest is asked for before that wait, and the
     // table first, since it is what the workgroup meets for.
     u32x4 tv[TABLE_UNITS<NW>];
-    load_table<NW>(a, tid, tv);
+    uint32_t two = 0;
+    constexpr bool SHORT = std::is_same<CODES, ShortCodes>::value;
+    if constexpr (!SHORT) {
+        load_table<NW>(a, tid, tv);
+    } else {
+        if (wave_s == 0) two = codes.two[lane];
+    }
     if (n_steps > 0) {
         m_cur = load_meta(0);
         m_next = load_meta(n_steps > 1 ? 1 : 0);
@@ -600,13 +608,10 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a)
     load_x_slice<MT, NW, N>(a, tid, areg);
     if (n_steps > 0) raw.fetch(stream, a.st_bytes, m_cur, lane);
 
-    uint64_t len_lo, len_hi;
-    __builtin_memcpy(&len_lo, a.code_len, 8);
-    __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) {
+    if constexpr (SHORT) {
+        build_pair_table<NW>(two, tbl, (uint32_t *)(smem + C::OFF_RED), lane, (int)wave_s);
+    } else if (a.off_tbl) {                                     // always
         store_table<NW>(tbl, tid, tv);
-    } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_RED), lane, (int)uniform32((uint32_t)wave));
     }
 
     uint32_t parity = 0;
@@ -758,7 +763,7 @@ struct XPieces { u32x4 v[MT][N / 16]; };
 // these kernels: 14336 x 7168, M = 64, 1400 of them a chunk, nine tenths of the time; 70.3 us -> 47.8, 16384 x 16384 145 -> 97.
 // (The nibble plane fetched and turned in the same way: M = 1, 14336 x 7168 21.7 -> 24.4, the exchange of deal_plane is cheaper.)
 // TURNED = false: slot j as the operand it is.  Rows from M on keep what they had: no output that is stored depends on them.
-template <int MT, int N, bool TURNED>
+template <int MT, int N, bool TURNED, bool ALL = false>
 __device__ __forceinline__ void load_x_slot(const GArgs &a, int lane, uint32_t kc, int j, XPieces<MT, N> &x)
 {
     const uint32_t K = (uint32_t)a.K, row = TURNED ? lane >> 4 : lane & 15, at = row * K + (TURNED ? 16 * (lane & 15) : 16 * (lane >> 4));      // 64 K <= 2^26
@@ -766,7 +771,10 @@ __device__ __forceinline__ void load_x_slot(const GArgs &a, int lane, uint32_t k
     for (int mt = 0; mt < MT; mt++) {
         const uint32_t first = 16 * mt + (TURNED ? 4 * j : 0);      // row of X, of the instruction's lowest one
         const GLOBAL uint8_t *X = (const GLOBAL uint8_t *)a.d_x + (uint64_t)(first * K) + (uint64_t)kc * (4 * N) + (TURNED ? 0 : 64 * j);
-        if (first + row < a.M) x.v[mt][j] = *(const GLOBAL u32x4 *)(X + at);
+        if constexpr (ALL) {
+            const uint32_t last = a.M - 1, m = first + row < last ? first + row : last;
+            x.v[mt][j] = *(const GLOBAL u32x4 *)((const GLOBAL uint8_t *)a.d_x + (uint64_t)kc * (4 * N) + (TURNED ? 0 : 64 * j) + (m * K + (TURNED ? 16 * (lane & 15) : 16 * (lane >> 4))));
+        } else if (first + row < a.M) x.v[mt][j] = *(const GLOBAL u32x4 *)(X + at);
     }
 }
 // What a lane reads here others have written, and what it writes next others have read.  A wave's LDS operations are done in order; that the compiler
@@ -823,9 +831,9 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 // operations 67 %, LDS 61 % (72 % of that bank conflicts of the table), first-level cache 59 %, address units 55 %; a wave waits for 55 % of its life.
 // M = 64 (213 us): two waves on a SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and
 // first-level cache busy 55 % each).
-template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0, int PLACES = NW>
+template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0, int PLACES = NW, class CODES = TableInBlob>
 __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_t *s_flag, uint64_t first_unit, uint32_t unit_stride,
-                                          uint32_t my_units)
+                                          uint32_t my_units, const CODES &codes = {})
 {
     constexpr bool SCALED = SC != 0;
     using C = GCfg<MT, NW, N>;
@@ -906,9 +914,13 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
         return plane + ((uint64_t)(16 * w.c - 15 * (k0 + w.kc)) << 7);
     };
 
+    // The first chunk's X without a condition, see load_x_slice, where that pays: resident X and single products of one tile or four.  With / without, us:
+    // 14336 x 7168 M = 16 24.4 / 24.9, 512 x 2048 M = 16 6.0 / 6.2, two experts M = 4 24.4 / 24.8; but eight experts M = 20 with scales of W 122.8 / 120.2, split K 1024 x 7168
+    // M = 16 10.4 / 10.2.
+    constexpr bool FIRST_ALL = KRES != 0 || (!SPLIT && !APART && MT != 2);
     auto load_x = [&](uint32_t kc, XPieces<MT, N> &x) {
 #pragma unroll
-        for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, TURNED>(a, lane, kc, j, x);
+        for (int j = 0; j < GPIECES; j++) load_x_slot<MT, N, TURNED, FIRST_ALL>(a, lane, kc, j, x);
     };
     Place cur = first_place();
     Meta m_cur, m_next;
@@ -922,7 +934,12 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     // experts M = 20 81.8 / 82.9, 48 121 / 124, eight experts M = 64 192 / 200; with scales of W no difference.
     constexpr bool EARLY = !(APART && MT > 1 && SC == 0);
     u32x4 tv[TABLE_UNITS<NW>];
-    if constexpr (EARLY) load_table<NW>(a, tid, tv);
+    constexpr bool IN_BLOB = !APART && std::is_same<CODES, TableInBlob>::value;       // APART: known for each matrix of the group
+    uint32_t codes_two = 0;
+    if constexpr (IN_BLOB) load_table<NW>(a, tid, tv);
+    else if constexpr (!APART) {
+        if (wave == 0) codes_two = codes.two[lane];
+    } else if (EARLY) load_table<NW>(a, tid, tv);
     if (valid(cur)) {
         m_cur = load_meta(cur);
         const Place nxt = next_of(cur);
@@ -938,16 +955,18 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     }
     if constexpr (KRES > 1) load_x(two ? kw + NW : kw, x_cur[1]);
 
-    uint64_t len_lo, len_hi;
-    __builtin_memcpy(&len_lo, a.code_len, 8);
-    __builtin_memcpy(&len_hi, a.code_len + 8, 8);
-    if (a.off_tbl) {
+    if constexpr (IN_BLOB) {
+        if (a.off_tbl) store_table<NW>(tbl, tid, tv);
+    } else if constexpr (!APART) {
+        build_pair_table<NW>(codes_two, tbl, (uint32_t *)(smem + C::OFF_RED), lane, wave);
+    } else if (a.off_tbl) {
         if constexpr (!EARLY) load_table<NW>(a, tid, tv);
         store_table<NW>(tbl, tid, tv);
-    } else if constexpr (APART) {
-        build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
     } else {
-        build_pair_table<NW>(len_lo, len_hi, tbl, (uint32_t *)(smem + C::OFF_RED), lane, wave);
+        uint64_t len_lo, len_hi;
+        __builtin_memcpy(&len_lo, a.code_len, 8);
+        __builtin_memcpy(&len_hi, a.code_len + 8, 8);
+        build_pair_table_apart<NW>(len_lo, len_hi, smem, lane, wave);
     }
 
     const uint32_t batch = SPLIT ? 1u : a.batch;
@@ -1048,12 +1067,12 @@ __device__ __forceinline__ void anyk_walk(const GArgs &a, uint8_t *smem, uint32_
     }
 }
 
-template <int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, int KRES = 0, bool TURNED = KRES == 0>
-__global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a)
+template <class CODES, int MT, int NW, int N, int SC, bool SPLIT = false, int ACC = 0, int KRES = 0, bool TURNED = KRES == 0>
+__global__ __launch_bounds__(NW * 64) void ecf8_gemm_anyk_kernel(GArgs a, CODES codes)
 {
     __shared__ __attribute__((aligned(16))) uint8_t smem[GCfg<MT, NW, N>::ANYK_TOTAL];
     __shared__ uint32_t s_flag;                   // split K: the arrival count this workgroup drew
-    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, KRES, TURNED>(a, smem, &s_flag, blockIdx.x, gridDim.x, a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u));
+    anyk_walk<MT, NW, N, SC, SPLIT, ACC, false, KRES, TURNED, NW, CODES>(a, smem, &s_flag, blockIdx.x, gridDim.x, a.units_each + (blockIdx.x < a.units_rest ? 1u : 0u), codes);
 }
 
 // Position of a wave in its sequence of chunks of uncompressed W: its i-th chunk of its workgroup's b-th unit.  `block` is the
@@ -1377,6 +1396,34 @@ inline void deal_waves(GArgs *a, uint32_t max_M)
 
 // 16 waves (one K chunk of the block each) while X fits their registers, 8 waves of two chunks
 // at M > 32.
+// CODES: kernels of their own where the blob holds the table and where they build it.
+template <int SCALED, int ACC, class CODES>
+int launch_fused_with(const GArgs &a, const CODES &codes, int grid, hipStream_t s)
+{
+    // The any-K kernels also take K = 4096 where X does not fit the registers beside the rest: with a scale per row and 128 columns of X at M > 32,
+    // and on the F16 matrix cores, whose operands are converted, at M > 16.  Resident X / any K, us, rows 4096, 14336 and 28672: group scales M = 33 30.9 / 11.7,
+    // 69.6 / 35.2, 111 / 57.9, M = 64 37.5 / 13.2, 90.7 / 39.1, 146 / 64.5; F16 cores M = 33 27.2 / 11.1, 59.6 / 32.4, 95.0 / 53.7, M = 64 30.6 / 12.2, 63.4 / 34.0, 99.4 / 56.1.
+    // F16 cores at M = 17 .. 32 go with those, though there X does fit and many rows would be faster for it: M = 32 10.7 / 9.0, 20.4 / 25.0, 29.6 / 41.0.
+    if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
+        const uint32_t kres = a.M <= 16 ? resident_chunks<1, WAVES<1>, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
+        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 1, WAVES<1>, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a, codes);
+        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 1, WAVES<1>, 64, SCALED, false, ACC, ACC == 0 ? 2 : 0>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a, codes);
+        // a few rows of X are few accesses either way, and the turn is time.  Operands / turned, us, M = 1 / 4 / 8 / 12 / 16: 4096 x 14336
+        // 14.1 / 14.7 / 15.4 / 16.2 / 16.8, 15.3 / 15.5 / 15.4 / 15.4 / 15.4; 14336 x 9216 29.7 / 29.9 / 31.3 / 33.0 / 35.4, 32.4 for all
+        else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 1, WAVES<1>, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a, codes);
+        else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 1, WAVES<1>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a, codes);
+        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 2, WAVES<2>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a, codes);
+        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 4, WAVES<4>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a, codes);
+        return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+    }
+    if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_kernel<1, 16, 64, SCALED, ACC, CODES>), dim3(grid), dim3(16 * 64), 0, s, a, codes);
+    else if constexpr (ACC == 0) {
+        if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_kernel<2, 16, 64, SCALED, ACC, CODES>), dim3(grid), dim3(16 * 64), 0, s, a, codes);
+        else if constexpr (SCALED != 2) hipLaunchKernelGGL((ecf8_gemm_kernel<4, 8, 64, SCALED, ACC, CODES>), dim3(grid), dim3(8 * 64), 0, s, a, codes);
+    }
+    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+}
+
 template <int SCALED, int ACC = 0>
 int launch_fused(GArgs a, void *stream)
 {
@@ -1385,29 +1432,8 @@ int launch_fused(GArgs a, void *stream)
     a.slices = 1;
     deal_units(&a, (uint32_t)grid);
     deal_waves(&a, a.M);
-    hipStream_t s = (hipStream_t)stream;
-    // The any-K kernels also take K = 4096 where X does not fit the registers beside the rest: with a scale per row and 128 columns of X at M > 32,
-    // and on the F16 matrix cores, whose operands are converted, at M > 16.  Resident X / any K, us, rows 4096, 14336 and 28672: group scales M = 33 30.9 / 11.7,
-    // 69.6 / 35.2, 111 / 57.9, M = 64 37.5 / 13.2, 90.7 / 39.1, 146 / 64.5; F16 cores M = 33 27.2 / 11.1, 59.6 / 32.4, 95.0 / 53.7, M = 64 30.6 / 12.2, 63.4 / 34.0, 99.4 / 56.1.
-    // F16 cores at M = 17 .. 32 go with those, though there X does fit and many rows would be faster for it: M = 32 10.7 / 9.0, 20.4 / 25.0, 29.6 / 41.0.
-    if (a.K != GK || (SCALED == 2 && a.M > 32) || (ACC == 1 && a.M > 16)) {
-        const uint32_t kres = a.M <= 16 ? resident_chunks<1, WAVES<1>, ACC>(a.K / 256, a.rows / BLOCK_ROWS / (uint64_t)grid) : 0u;
-        if (kres == 1) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, 1>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        else if (kres == 2) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, ACC == 0 ? 2 : 0>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        // a few rows of X are few accesses either way, and the turn is time.  Operands / turned, us, M = 1 / 4 / 8 / 12 / 16: 4096 x 14336
-        // 14.1 / 14.7 / 15.4 / 16.2 / 16.8, 15.3 / 15.5 / 15.4 / 15.4 / 15.4; 14336 x 9216 29.7 / 29.9 / 31.3 / 33.0 / 35.4, 32.4 for all
-        else if (a.M <= 8) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC, 0, false>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        else if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, WAVES<2>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, WAVES<4>, 64, SCALED, false, ACC>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
-        return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
-    }
-    if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_kernel<1, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
-    else if constexpr (ACC == 0) {
-        if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_kernel<2, 16, 64, SCALED, ACC>), dim3(grid), dim3(16 * 64), 0, s, a);
-        else if constexpr (SCALED != 2) hipLaunchKernelGGL((ecf8_gemm_kernel<4, 8, 64, SCALED, ACC>), dim3(grid), dim3(8 * 64), 0, s, a);
-    }
-    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+    return a.off_tbl ? launch_fused_with<SCALED, ACC>(a, TableInBlob{}, grid, (hipStream_t)stream)
+                     : launch_fused_with<SCALED, ACC>(a, short_codes(a.code_len), grid, (hipStream_t)stream);
 }
 
 template <int SCALED, int ACC = 0>
@@ -1479,6 +1505,17 @@ inline int split_args(GArgs *a, void *d_workspace, uint64_t bytes, uint32_t *sli
     return ECF8_OK;
 }
 
+template <int SCALED, class CODES>
+int launch_split_with(const GArgs &a, const CODES &codes, int grid, hipStream_t s)
+{
+    // X turned at any M.  Turned / as operands, us, M = 1 / 8 / 16: 2048 x 7168 11.4 / 11.5 / 11.7, 11.3 / 11.9 / 12.4; 1024 x 16384 12.3 / 12.4 / 12.7, 12.2 / 13.0 / 13.6;
+    // 256 x 4096, a chunk a workgroup, 16.0 / 16.1 / 16.1, 15.7 / 15.8 / 15.8
+    if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a, codes);
+    else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a, codes);
+    else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<CODES, 4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a, codes);
+    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+}
+
 template <int SCALED, bool RAW>
 int launch_split(GArgs a, void *stream)
 {
@@ -1487,17 +1524,10 @@ int launch_split(GArgs a, void *stream)
     deal_units(&a, (uint32_t)grid);
     deal_waves(&a, a.M);
     hipStream_t s = (hipStream_t)stream;
-    if constexpr (RAW) {
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
-    } else {
-        // X turned at any M.  Turned / as operands, us, M = 1 / 8 / 16: 2048 x 7168 11.4 / 11.5 / 11.7, 11.3 / 11.9 / 12.4; 1024 x 16384 12.3 / 12.4 / 12.7, 12.2 / 13.0 / 13.6;
-        // 256 x 4096, a chunk a workgroup, 16.0 / 16.1 / 16.1, 15.7 / 15.8 / 15.8
-        if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
-        else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
-        else hipLaunchKernelGGL((ecf8_gemm_anyk_kernel<4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
-    }
+    if constexpr (!RAW) return a.off_tbl ? launch_split_with<SCALED>(a, TableInBlob{}, grid, s) : launch_split_with<SCALED>(a, short_codes(a.code_len), grid, s);
+    if (a.M <= 16) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<1, WAVES<1>, 64, SCALED, true>), dim3(grid), dim3(WAVES<1> * 64), 0, s, a);
+    else if (a.M <= 32) hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<2, WAVES<2>, 64, SCALED, true>), dim3(grid), dim3(WAVES<2> * 64), 0, s, a);
+    else hipLaunchKernelGGL((ecf8_gemm_raw_anyk_kernel<4, WAVES<4>, 64, SCALED, true>), dim3(grid), dim3(WAVES<4> * 64), 0, s, a);
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 

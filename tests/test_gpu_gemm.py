@@ -707,6 +707,24 @@ def test_groups_of_many_blocks_with_scales(scale_mode, M):
         assert torch.equal(y, want) and torch.equal(y, _single_call(m)), shape
 
 
+@pytest.mark.parametrize("K", [4096, 2048])
+@pytest.mark.parametrize("counts", [(1,), (1, 1), (5, 1, 1), (1,) * 16, tuple(2 ** i for i in range(16)), (3, 3, 3, 1, 9)])
+def test_tables_built_from_short_codes(counts, K):
+    """One codeword, complete codes of few and of all symbols, lengths that the cap cuts: the table in the blob and the table that a workgroup builds; M on
+    either side of where the kernels change.  Bit for bit the twin on uncompressed weights; the decode gives the weights back."""
+    rng = np.random.default_rng(len(counts) + K)
+    e = rng.permutation(np.repeat(rng.permutation(16)[:len(counts)], np.maximum(1, np.array(counts) * 32 * K // sum(counts))))
+    w = (np.resize(e, (32, K)).astype(np.uint8) << 3) | (rng.integers(0, 256, (32, K), dtype=np.uint8) & 0x87)
+    d_w = torch.from_numpy(w).to(DEV)
+    for mode in (1, 2):
+        hdr, blob = ecf8.ecf8_encode_gpu(d_w, lane_syms=64, tile_rows=16, table_mode=mode)
+        assert torch.equal(ecf8.ecf8_decode(hdr, blob).view(-1), d_w.view(-1)), mode
+        for M in (3, 16, 24, 64):
+            x = synth.activations(M, K, seed=M, device=DEV)
+            got, want = ecf8.ecf8_gemm_fp8(hdr, blob, x), ecf8.ecf8_gemm_fp8_raw(d_w, x)
+            assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (mode, M)
+
+
 @pytest.mark.parametrize("scale_mode", [0, 1, 2])
 def test_few_rows_of_x_in_a_group_with_many(scale_mode):
     """Members with M <= 32 in a group whose largest M takes workgroups of fewer waves than their own calls do: the sums of the places that those calls'
