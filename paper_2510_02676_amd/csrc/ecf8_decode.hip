@@ -103,9 +103,11 @@ struct Cfg {
 // default cap), so the pipelined loop needs no second level and is one straight line.
 // LONG (general kernels only): some codeword of the launch is longer than TB bits.  BURST: 1 = a chunk's pieces are
 // held in registers and stored together at its end, 2 = half the chunk's pieces at a time, 0 = each piece as it is decoded.
-template <int N, int WAVES, bool PAIRFIT, bool TILED = false, bool LONG = !PAIRFIT, int BURST = PAIRFIT>
-__global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
+// CODES: ShortCodes for one tensor under the cap whose blob holds no table, else TableInBlob: as the tensors have it.
+template <int N, int WAVES, bool PAIRFIT, bool TILED, bool LONG, int BURST, class CODES>
+__global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a, CODES codes)
 {
+    constexpr bool SHORT = std::is_same<CODES, ShortCodes>::value;
     using C = Cfg<N, WAVES, PAIRFIT, TILED>;
     __shared__ __attribute__((aligned(16))) uint8_t smem[C::TOTAL];
     uint16_t *tbl = (uint16_t *)(smem + C::OFF_TBL);
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         uint32_t n_chunks, first_chunk;
         uint64_t d_blob, d_out, n_elem, off_cb, off_lb, off_st, off_pl, st_bytes;
         uint64_t len_lo, len_hi, off_tbl, group, tcols;
-        if (a.items) {
+        if (!SHORT && a.items) {
             const BatchItem item(a.items, a.n_items, c, lane);
             auto field = [&](int k) -> uint64_t { return item.word(k); };
             static_assert(sizeof(ecf8_batch_item) == 128 && offsetof(ecf8_batch_item, code_len) == 80 &&
@@ -287,7 +289,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
         const bool any = tail_here || cg < fast_end;
         if (any) ask_first(tail_here ? seg_end - 1 : cg);
         u32x4 tv[(TBL_ENTRIES * 2 / 16 + WAVES * 64 - 1) / (WAVES * 64)];
-        if (off_tbl) {
+        uint32_t two = 0;
+        if constexpr (SHORT) {
+            if (wave == 0) two = codes.two[lane];
+        } else if (off_tbl) {
             // the encoder embedded the table: copy it (L2-resident after the first workgroup)
             const GLOBAL u32x4 *src = (const GLOBAL u32x4 *)(d_blob + off_tbl);
 #pragma unroll
@@ -298,7 +303,9 @@ __global__ __launch_bounds__(WAVES * 64) void ecf8_decode_kernel(KArgs a)
             }
         }
         if (any) load_stream(m_cur, seg);
-        if (off_tbl) {
+        if constexpr (SHORT) {
+            build_pair_table<WAVES>(two, tbl, (uint32_t *)(smem + C::OFF_WAVES), lane, wave);
+        } else if (off_tbl) {
 #pragma unroll
             for (int j = 0; j < (int)(sizeof(tv) / sizeof(tv[0])); j++) {
                 const int i = tid + j * WAVES * 64;
@@ -606,7 +613,16 @@ int launch_as(const KArgs &a, int wgs_per_cu, hipStream_t s)
     if (grid == 0) grid = 1;
     KArgs dealt = a;
     dealt.deal = deal_chunks(a.total_chunks, grid);
-    hipLaunchKernelGGL((ecf8_decode_kernel<N, WAVES, PAIRFIT, TILED, LONG, BURST>), dim3(grid), dim3(WAVES * 64), 0, s, dealt);
+    // One tensor without a table, whose code comes from the host; the kernel has no other way in, and 20 to 30 registers less.  The same kernel for all / its own, us:
+    // 64 x 256 7.0 / 6.0, row-tiled 6.4 / 5.1, 1024 x 1024 7.5 / 6.7, row-tiled 6.9 / 5.9, 1000 x 3001 7.9 / 7.2.
+    if constexpr (PAIRFIT) {
+        if (!a.items && !a.single.off_table) {
+            hipLaunchKernelGGL((ecf8_decode_kernel<N, WAVES, PAIRFIT, TILED, LONG, BURST, ShortCodes>), dim3(grid), dim3(WAVES * 64), 0, s, dealt,
+                               short_codes(a.single.code_len));
+            return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+        }
+    }
+    hipLaunchKernelGGL((ecf8_decode_kernel<N, WAVES, PAIRFIT, TILED, LONG, BURST, TableInBlob>), dim3(grid), dim3(WAVES * 64), 0, s, dealt, TableInBlob{});
     return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
 }
 
