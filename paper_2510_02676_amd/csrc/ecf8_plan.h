@@ -1,5 +1,5 @@
-// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder share on the
-// host -- option checks, the code built from a histogram, and the container layout.
+// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder share on the host -- option checks and the container
+// layout -- and the CPU encoder's code from a histogram (the GPU encoder makes its own on the device).
 #ifndef ECF8_PLAN_H
 #define ECF8_PLAN_H
 

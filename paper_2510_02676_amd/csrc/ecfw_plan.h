@@ -1,5 +1,5 @@
-// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder of the wide-alphabet
-// codec share on the host -- option checks, the code built from a histogram, the container layout.
+// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder of the wide-alphabet codec share on the host -- option
+// checks and the container layout -- and the CPU encoder's code from a histogram (the GPU encoder makes its own on the device).
 #ifndef ECFW_PLAN_H
 #define ECFW_PLAN_H
 
