@@ -225,7 +225,7 @@ int ecf8_gemm_group_prepare(const ecf8_gemm_group_desc *descs, uint32_t n, ecf8_
 int ecf8_gemm_fp8_grouped(const ecf8_gemm_group_item *d_items, const ecf8_gemm_group_info *info, void *stream)
 {
     if (!d_items || !info || info->n_items == 0 || info->total_work == 0 || info->max_M == 0 || info->max_M > 64 ||
-        info->scale_mode > 2 || info->raw > 1)
+        info->scale_mode > 2 || info->raw > 1 || info->total_work >= 1ull << 32)
         return ECF8_E_ARG;
     if ((uintptr_t)d_items & 7) return ECF8_E_ALIGN;
     const uint64_t items = (uint64_t)(uintptr_t)d_items, work = info->total_work;
