@@ -707,7 +707,11 @@ public:
     }
 };
 
-// A stream that is being captured runs nothing: there is no histogram to wait for.  Nor is there on the null stream while one that waits for it is
+// Whether the launch just made went through.  Asked after each of an encode's three: what a kernel takes from the blob, places to store at among it, is the kernel's
+// before it, and behind a launch that failed it would be whatever the caller's buffer holds.
+inline bool launched() { return hipGetLastError() == hipSuccess; }
+
+// A stream that is being captured runs nothing: there is no header to wait for.  Nor is there on the null stream while one that waits for it is
 // captured, which the question is answered with as an error: the caller has it from the return value, and the next launch's check is not to find it.
 inline bool capturing(hipStream_t s)
 {

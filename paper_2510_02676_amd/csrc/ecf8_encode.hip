@@ -426,7 +426,9 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
     if (N == 32) hipLaunchKernelGGL(histogram_kernel<32>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
     else if (N == 64) hipLaunchKernelGGL(histogram_kernel<64>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
     else hipLaunchKernelGGL(histogram_kernel<128>, dim3(rg.count), dim3(1024), 0, s, a, rg, records);
+    if (!launched()) return ECF8_E_HIP;
     hipLaunchKernelGGL(plan_kernel<E4M3Codec>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, blob_capacity, records, lmax, mail.device());
+    if (!launched()) return ECF8_E_HIP;
     if (lmax <= 7) {
         if (N == 32) launch_encode<32, true>(a, rg, s);
         else if (N == 64) launch_encode<64, true>(a, rg, s);
@@ -436,7 +438,7 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
         else if (N == 64) launch_encode<64, false>(a, rg, s);
         else launch_encode<128, false>(a, rg, s);
     }
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
+    if (!launched()) return ECF8_E_HIP;
     if (!mail.read(&h, a.blob, s)) return ECF8_E_HIP;
     if (h.magic == 0) return (int)h.version;
     *hdr_out = h;

@@ -450,15 +450,18 @@ __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, Ranges 
 }
 
 template <int FMT, int N>
-void launch(const WEncArgs &a, const ecfw_header &h, const Ranges &rg, uint64_t capacity, uint32_t lmax, uint64_t mail, hipStream_t s)
+bool launch(const WEncArgs &a, const ecfw_header &h, const Ranges &rg, uint64_t capacity, uint32_t lmax, Mail &mail, hipStream_t s)
 {
     const uint64_t records = a.blob + h.off_stream;
     static_assert(EFmt<FMT>::A * 4 <= 16 * N, "a record is smaller than a chunk's plane");
     const dim3 waves(range_waves(rg) * 64);
     hipLaunchKernelGGL((w_histogram_kernel<FMT, N>), dim3(rg.count), dim3(1024), 0, s, a, rg, records);
-    hipLaunchKernelGGL(plan_kernel<WCodec<FMT>>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, capacity, records, lmax, mail);
+    if (!launched()) return false;
+    hipLaunchKernelGGL(plan_kernel<WCodec<FMT>>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, capacity, records, lmax, mail.device());
+    if (!launched()) return false;
     if (lmax <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(rg.count), waves, 0, s, a, rg);
     else hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_MAX_CODE_LEN>), dim3(rg.count), waves, 0, s, a, rg);
+    return launched();
 }
 
 template <int FMT>
@@ -485,9 +488,7 @@ int encode_on_gpu(const void *d_elems, uint64_t rows, uint64_t cols, uint32_t N,
 
     if (capturing(s)) return ECF8_E_HIP;
     Mail mail;
-    if (N == 64) launch<FMT, 64>(a, h, rg, blob_capacity, lmax, mail.device(), s);
-    else launch<FMT, 128>(a, h, rg, blob_capacity, lmax, mail.device(), s);
-    if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
+    if (!(N == 64 ? launch<FMT, 64>(a, h, rg, blob_capacity, lmax, mail, s) : launch<FMT, 128>(a, h, rg, blob_capacity, lmax, mail, s))) return ECF8_E_HIP;
     if (!mail.read(&h, a.blob, s)) return ECF8_E_HIP;
     if (h.magic == 0) return (int)h.version;
     *hdr_out = h;
