@@ -252,6 +252,9 @@ typedef struct ecf8_batch_info {
  * ecf8_batch_prepare: HOST.  Fills items_host[0..n) from the headers and the
  * device addresses; the caller copies the array to device memory once and
  * keeps it, together with *info.  All tensors of a batch must share lane_syms.
+ * One tensor has at most 2^31 chunks here and in ecf8_decode (4 TiB or more;
+ * the encoders take 1 TiB) -> ECF8_E_FORMAT; a batch may have more, and is then
+ * decoded by several launches.
  */
 int ecf8_batch_prepare(const ecf8_header *hdrs, const void *const *d_blobs,
                        void *const *d_outs, const uint64_t *out_capacities,

@@ -182,6 +182,8 @@ int ecfw_decode(const void *d_blob, const ecfw_header *hdr, void *d_out, uint64_
  * fills items_host[n] (the caller copies them to the device, 8-byte aligned) and
  * *info (the caller may then set info->max_workgroups, 0 = one per compute unit).
  * ecfw_decode_batched: asynchronous on `stream`; d_items is the DEVICE copy.
+ * One tensor has at most 2^31 chunks here and in ecfw_decode (8 TiB or more) ->
+ * ECF8_E_FORMAT; a batch may have more, and is then decoded by several launches.
  */
 typedef struct ecfw_batch_item {
     uint64_t d_blob, d_out;      /* device addresses                                   */

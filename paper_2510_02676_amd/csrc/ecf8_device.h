@@ -6,6 +6,7 @@
 #define ECF8_DEVICE_H
 
 #include "ecf8.h"
+#include "ecf8_plan.h"
 #include "ecf8_table.h"
 
 #include <hip/hip_runtime.h>
@@ -14,6 +15,8 @@
 #include <mutex>
 
 namespace {
+
+using ecf8_internal::LAUNCH_CHUNKS;
 
 constexpr int TB = ECF8_TB;            // table index bits
 constexpr int TBL_ENTRIES = 1 << TB;

@@ -207,7 +207,6 @@ int ecf8_gemm_group_prepare(const ecf8_gemm_group_desc *descs, uint32_t n, ecf8_
         if (d.M > max_M) max_M = d.M;
         std::memcpy(&items_host[i], &it, sizeof(it));
     }
-    if (work >= 1ull << 32) return ECF8_E_ARG;                      // 16 TiB of weights
     for (uint32_t i = 0; i < n; i++) {                              // the waves of the launch go by the largest M
         GItem it;
         std::memcpy(&it, &items_host[i], sizeof(it));
@@ -225,7 +224,7 @@ int ecf8_gemm_group_prepare(const ecf8_gemm_group_desc *descs, uint32_t n, ecf8_
 int ecf8_gemm_fp8_grouped(const ecf8_gemm_group_item *d_items, const ecf8_gemm_group_info *info, void *stream)
 {
     if (!d_items || !info || info->n_items == 0 || info->total_work == 0 || info->max_M == 0 || info->max_M > 64 ||
-        info->scale_mode > 2 || info->raw > 1 || info->total_work >= 1ull << 32)
+        info->scale_mode > 2 || info->raw > 1)
         return ECF8_E_ARG;
     if ((uintptr_t)d_items & 7) return ECF8_E_ALIGN;
     const uint64_t items = (uint64_t)(uintptr_t)d_items, work = info->total_work;

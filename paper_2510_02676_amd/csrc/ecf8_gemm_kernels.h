@@ -1215,6 +1215,7 @@ static_assert(sizeof(GItem) % 8 == 0 && sizeof(GItem) <= sizeof(ecf8_gemm_group_
 
 struct GGArgs {
     uint64_t d_items;           // device array of ecf8_gemm_group_item
+    uint64_t base;              // chunks of the group before this launch's (launch_grouped): what the kernel counts from, in 32 bits
     uint32_t n_items;
     uint32_t work_each, work_rest;      // chunks of every workgroup; the first work_rest have one more
 };
@@ -1237,7 +1238,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
     uint32_t lo = 0;
     for (uint32_t n = g.n_items; n > 1;) {
         const uint32_t step = (n + 63) / 64, at = (threadIdx.x & 63) * step;
-        const bool begun = at < n && items[(uint64_t)(lo + (at < n ? at : 0u)) * WORDS] <= pos;
+        const bool begun = at < n && items[(uint64_t)(lo + (at < n ? at : 0u)) * WORDS] <= g.base + pos;
         const uint32_t k = ((uint32_t)__popcll(__ballot(begun)) - 1u) * step;       // the first one has begun
         lo += k;
         n = n - k < step ? n - k : step;
@@ -1249,7 +1250,7 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_grouped_kernel(GGArgs g)
 #pragma unroll
             for (int i = 0; i < (int)(sizeof(GItem) / 8); i++) dst[i] = uniform64(items[(uint64_t)lo * WORDS + i]);
         }
-        const uint32_t kchunks = (uint32_t)(it.a.K / C::BLOCK_COLS), n_blocks = (uint32_t)(it.a.rows / BLOCK_ROWS), first_work = (uint32_t)it.first_work;
+        const uint32_t kchunks = (uint32_t)(it.a.K / C::BLOCK_COLS), n_blocks = (uint32_t)(it.a.rows / BLOCK_ROWS), first_work = (uint32_t)(it.first_work - g.base);
         const uint32_t b0 = (pos - first_work + kchunks - 1) / kchunks;
         uint32_t b1 = (end - first_work + kchunks - 1) / kchunks;
         if (b1 > n_blocks) b1 = n_blocks;
@@ -1292,6 +1293,7 @@ inline int check_gemm_args(uint64_t rows, uint64_t cols, const void *d_x, uint32
 {
     if (!d_x || !d_y || M == 0 || M > 64) return ECF8_E_ARG;
     if (cols == 0 || cols % 256 || cols > (1u << 20) || rows == 0 || rows % BLOCK_ROWS) return ECF8_E_ARG;
+    if (rows / BLOCK_ROWS > LAUNCH_CHUNKS / (cols / 256)) return ECF8_E_ARG;         // 8 TiB
     if (((uintptr_t)d_x & 15) || ((uintptr_t)d_y & 3)) return ECF8_E_ALIGN;
     return ECF8_OK;
 }
@@ -1557,16 +1559,20 @@ int launch_grouped(uint64_t d_items, uint32_t n_items, uint64_t total_work, uint
 {
     const int cus = device_cus();
     if (cus <= 0) return ECF8_E_HIP;
-    // no more workgroups than blocks of 16 chunks: below that a share is less than a block's worth of the waves' work
-    uint64_t grid = (total_work + 15) / 16;
-    if (grid > (uint64_t)cus) grid = (uint64_t)cus;
-    if (grid == 0) grid = 1;
-    const GGArgs g{d_items, n_items, (uint32_t)(total_work / grid), (uint32_t)(total_work % grid)};
     hipStream_t s = (hipStream_t)stream;
-    if (max_M <= 16) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<1, WAVES<1>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<1> * 64), 0, s, g);
-    else if (max_M <= 32) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<2, WAVES<2>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<2> * 64), 0, s, g);
-    else hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<4, WAVES<4>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<4> * 64), 0, s, g);
-    return hipGetLastError() == hipSuccess ? ECF8_OK : ECF8_E_HIP;
+    // As many chunks a launch as 32 bits count with room for a matrix more; 2^31 are 8 TiB of weights, so nearly always one launch
+    for (uint64_t base = 0; base < total_work; base += LAUNCH_CHUNKS) {
+        const uint64_t work = total_work - base < LAUNCH_CHUNKS ? total_work - base : LAUNCH_CHUNKS;
+        // no more workgroups than blocks of 16 chunks: below that a share is less than a block's worth of the waves' work
+        uint64_t grid = (work + 15) / 16;
+        if (grid > (uint64_t)cus) grid = (uint64_t)cus;
+        const GGArgs g{d_items, base, n_items, (uint32_t)(work / grid), (uint32_t)(work % grid)};
+        if (max_M <= 16) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<1, WAVES<1>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<1> * 64), 0, s, g);
+        else if (max_M <= 32) hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<2, WAVES<2>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<2> * 64), 0, s, g);
+        else hipLaunchKernelGGL((ecf8_gemm_grouped_kernel<4, WAVES<4>, 64, SCALED, RAW>), dim3((unsigned)grid), dim3(WAVES<4> * 64), 0, s, g);
+        if (hipGetLastError() != hipSuccess) return ECF8_E_HIP;
+    }
+    return ECF8_OK;
 }
 
 __global__ __attribute__((unused)) void gemm_fill_zero_kernel(uint64_t p, uint64_t n_dwords)

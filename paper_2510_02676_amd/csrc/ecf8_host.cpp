@@ -603,6 +603,7 @@ int ecf8_batch_prepare(const ecf8_header *hdrs, const void *const *d_blobs, void
         if (!d_blobs[i] || !d_outs[i]) return ECF8_E_ARG;
         if (((uintptr_t)d_blobs[i] | (uintptr_t)d_outs[i]) & 15) return ECF8_E_ALIGN;
         if (caps[i] < h.n_elem) return ECF8_E_CAPACITY;
+        if (h.n_chunks > ecf8_internal::LAUNCH_CHUNKS) return ECF8_E_FORMAT;
         ecf8_batch_item &it = items[i];
         std::memset(&it, 0, sizeof(it));
         it.d_blob = (uint64_t)(uintptr_t)d_blobs[i];

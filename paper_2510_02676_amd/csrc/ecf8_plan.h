@@ -1,5 +1,5 @@
-// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder share on the host -- option checks and the container
-// layout -- and the CPU encoder's code from a histogram (the GPU encoder makes its own on the device).
+// Internal (not part of the C ABI): what the CPU encoder and the GPU encoder share on the host -- option checks, the container
+// layout, limits -- and the CPU encoder's code from a histogram (the GPU encoder makes its own on the device).
 #ifndef ECF8_PLAN_H
 #define ECF8_PLAN_H
 
@@ -14,6 +14,10 @@ struct ecf8_blob {
 };
 
 namespace ecf8_internal {
+
+// Kernels number a launch's chunks in 32 bits: this many at the most, beside a tensor of as many that begins before the launch or ends behind it.  Longer
+// batches and groups are several launches; a tensor of more (4 TiB or more, the encoders take 1 TiB of E4M3) is refused.
+constexpr uint64_t LAUNCH_CHUNKS = 1ull << 31;
 
 struct Plan {
     ecf8_header hdr;              // complete header of the blob to be written

@@ -38,8 +38,9 @@ struct BArgs {
     WArgs single;                        // used when items == nullptr
     const GLOBAL WArgs *items;           // device array for the batched call
     uint32_t n_items;
-    uint64_t total_chunks;
+    uint64_t total_chunks;               // of the launch, at most LAUNCH_CHUNKS
     ChunkDeal deal;                      // of the launch's chunks to its workgroups
+    uint64_t base;                       // FAR kernels: chunks of the batch before the launch's
 };
 
 template <int FMT> struct Fmt;
@@ -245,19 +246,23 @@ __device__ __forceinline__ u32x4 merge_e5m2(const uint32_t e[16], uint32_t mant,
     return u32x4{out[0], out[1], out[2], out[3]};
 }
 
-// The item of a batched launch that holds chunk g, in scalar registers.
-__device__ __forceinline__ WArgs find_item(const BArgs &b, uint64_t g, int lane)
+// The item of a batched launch that holds chunk g, in scalar registers.  FAR: one of several launches on a batch; of a tensor that begins before it, first_chunk is
+// below 0: its low 32 bits count, and wrap.
+template <bool FAR = false>
+__device__ __forceinline__ WArgs find_item(const BArgs &b, uint32_t g, int lane)
 {
     if (!b.items) return b.single;
-    const BatchItem item(b.items, b.n_items, g, lane);
+    const uint64_t base = FAR ? b.base : 0;
+    const BatchItem item(b.items, b.n_items, base + g, lane);
     WArgs a;
     uint64_t *dst = (uint64_t *)&a;
 #pragma unroll
     for (int i = 0; i < 16; i++) dst[i] = item.word(i);
+    a.first_chunk -= base;
     return a;
 }
 
-// the range of a launch's chunks for this workgroup; chunk numbers run through the whole batch and have 32 bits (2^32 chunks are 16 TiB or more)
+// the range of a launch's chunks for this workgroup, numbered in 32 bits through all tensors from the launch's first chunk on
 __device__ __forceinline__ void share_of(const BArgs &b, uint32_t &g, uint32_t &g_end)
 {
     g = b.deal.begin(blockIdx.x);
@@ -347,7 +352,7 @@ __device__ __forceinline__ void symbol_pass(const WArgs &a, const CodeArrays &ca
 
 // Codes with codewords of more than 12 bits (caps 13 .. 16): one codeword per lookup, the longer ones by a canonical
 // first-code comparison in a rarely taken branch.
-template <int FMT, int N, int WAVES>
+template <int FMT, int N, int WAVES, bool FAR = false>
 __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
 {
     using C = WCfg<FMT, N, WAVES>;
@@ -366,9 +371,10 @@ __global__ __launch_bounds__(WAVES * 64) void ecfw_long_decode_kernel(BArgs b)
     share_of(b, g, g_end);
 
     while (g < g_end) {                                // one round per tensor the range touches (uniform)
-    const WArgs a = find_item(b, g, lane);
+    const WArgs a = find_item<FAR>(b, g, lane);
     const uint32_t c_begin = g - (uint32_t)a.first_chunk;        // chunk numbers inside the tensor
     const uint32_t c_end = g_end - (uint32_t)a.first_chunk < (uint32_t)a.n_chunks ? g_end - (uint32_t)a.first_chunk : (uint32_t)a.n_chunks;
+    if (FAR && (a.first_chunk + a.n_chunks) >> 32) break;  // it ends before the launch begins
     if (c_end <= c_begin) break;                       // the item table does not cover chunk g: stop rather than spin
     const GLOBAL uint8_t *blob = (const GLOBAL uint8_t *)a.d_blob;
     const GLOBAL uint8_t *stream = blob + a.off_stream;
@@ -1016,6 +1022,21 @@ int launch(const BArgs &a, uint32_t fmt, uint32_t N, uint32_t max_code_len, uint
                                 : launch_fmt<ECFW_FMT_E5M2>(a, N, fast, max_workgroups, s);
 }
 
+// A batch of more chunks than a launch counts (8 TiB or more), by the kernels that take every code
+int launch_far(BArgs a, uint32_t fmt, uint32_t N, uint32_t max_workgroups, hipStream_t s)
+{
+    const uint64_t all = a.total_chunks;
+    for (a.base = 0; a.base < all; a.base += LAUNCH_CHUNKS) {
+        a.total_chunks = all - a.base < LAUNCH_CHUNKS ? all - a.base : LAUNCH_CHUNKS;
+        const int rc = fmt == ECFW_FMT_BF16 ? (N == 64 ? launch_as<8>(ecfw_long_decode_kernel<ECFW_FMT_BF16, 64, 8, true>, a, max_workgroups, s)
+                                                       : launch_as<8>(ecfw_long_decode_kernel<ECFW_FMT_BF16, 128, 8, true>, a, max_workgroups, s))
+                                            : (N == 64 ? launch_as<8>(ecfw_long_decode_kernel<ECFW_FMT_E5M2, 64, 8, true>, a, max_workgroups, s)
+                                                       : launch_as<8>(ecfw_long_decode_kernel<ECFW_FMT_E5M2, 128, 8, true>, a, max_workgroups, s));
+        if (rc) return rc;
+    }
+    return ECF8_OK;
+}
+
 // Checks of one tensor's header and buffers; fills the kernel's view of it.
 int make_item(const ecfw_header *h, const void *d_blob, void *d_out, uint64_t out_capacity, WArgs *it)
 {
@@ -1026,6 +1047,7 @@ int make_item(const ecfw_header *h, const void *d_blob, void *d_out, uint64_t ou
     const uint32_t g = h->group_chunks;
     if (g < 1 || g > 64 || (g & (g - 1))) return ECF8_E_FORMAT;
     if (h->n_elem == 0 || h->n_chunks != (h->n_elem + 64ull * h->lane_syms - 1) / (64ull * h->lane_syms)) return ECF8_E_FORMAT;
+    if (h->n_chunks > LAUNCH_CHUNKS) return ECF8_E_FORMAT;
     if (h->max_code_len < 1 || h->max_code_len > ECFW_MAX_CODE_LEN || h->stream_bytes < 16 || h->stream_bytes % 16)
         return ECF8_E_FORMAT;
     const uint64_t elem = h->fmt == ECFW_FMT_BF16 ? 2 : 1;
@@ -1097,5 +1119,6 @@ extern "C" int ecfw_decode_batched(const void *d_items, uint32_t n, const ecfw_b
     a.items = (const GLOBAL WArgs *)d_items;
     a.n_items = n;
     a.total_chunks = info->total_chunks;
+    if (a.total_chunks > LAUNCH_CHUNKS) return launch_far(a, info->fmt, info->lane_syms, info->max_workgroups, (hipStream_t)stream);
     return launch(a, info->fmt, info->lane_syms, info->max_code_len, info->max_workgroups, stream);
 }

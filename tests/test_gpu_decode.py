@@ -505,3 +505,26 @@ def test_e5m2_bytes_through_this_codec(orc):
     got, guards = _gpu_decode_guarded(blob.numpy(), blob.header)
     assert guards and np.array_equal(got, _oracle_expected(orc, w)) and np.array_equal(got, w)
     assert blob.size / w.size < 0.78
+
+
+def test_batch_of_more_than_2_to_the_32_chunks():
+    """One tensor over and over into one buffer (8.8 TB of output), but for the members that hold the chunks 2^31 and 2^32, where a launch ends or 32 bits do, and
+    the last one, which have a buffer each."""
+    chunks = (1 << 17) - 1
+    n = chunks * 2048
+    w = synth.make_weight(1, n, 1.7, 0.02, 3, 0, "tensor", DEV).view(torch.uint8)
+    hdr, blob = ecf8.ecf8_encode_gpu(w, 1, n, lane_syms=32)
+    assert hdr.n_chunks == chunks
+    members = (1 << 32) // chunks + 3
+    outs = [torch.empty(n, dtype=torch.uint8, device=DEV)] * members
+    own = [(1 << 31) // chunks, (1 << 32) // chunks, members - 1]
+    for i in own:
+        outs[i] = torch.full((n,), 0xA5, dtype=torch.uint8, device=DEV)
+    batch = ecf8.Batch([hdr] * members, [blob] * members, outs)
+    assert batch.total_chunks > 1 << 32
+    ecf8.ecf8_decode_batched(batch)
+    torch.cuda.synchronize()
+    for i in own:
+        assert torch.equal(outs[i], w.view(-1)), i
+    del batch, outs, w, blob
+    torch.cuda.empty_cache()

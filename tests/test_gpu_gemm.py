@@ -823,3 +823,28 @@ def test_gemm_calls_replay_from_a_hip_graph():
         if rep:
             assert not torch.equal(want[0], first[0])
         first = want
+
+
+def test_group_of_more_than_2_to_the_32_chunks():
+    """One matrix over and over into one Y (17.6 TB of weights), but for the members that hold the chunks 2^31 and 2^32, where a launch ends or 32 bits do, and
+    the last one, which have a Y each: the single call's bits."""
+    rows, K = 16 * 1023, 256 * 255
+    chunks = 1023 * 255
+    w = synth.make_weight(rows, K, 1.7, 0.02, 3, 0, "tensor", DEV)
+    hdr, blob = ecf8.ecf8_encode_gpu(w, lane_syms=64, tile_rows=16)
+    x = synth.activations(1, K, 7, DEV)
+    want = ecf8.ecf8_gemm_fp8(hdr, blob, x)
+    members = (1 << 32) // chunks + 3
+    y = torch.empty_like(want)
+    ms = [{"hdr": hdr, "blob": blob, "x": x, "y": y}] * members
+    own = [(1 << 31) // chunks, (1 << 32) // chunks, members - 1]
+    for i in own:
+        ms[i] = dict(ms[i], y=torch.full_like(want, float("nan")))
+    group = ecf8.GemmGroup(ms)
+    assert group.info.total_work > 1 << 32
+    ecf8.ecf8_gemm_fp8_grouped(group)
+    torch.cuda.synchronize()
+    for i in own:
+        assert torch.equal(ms[i]["y"], want), i
+    del group, ms, w, blob
+    torch.cuda.empty_cache()

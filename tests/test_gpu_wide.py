@@ -400,3 +400,26 @@ def test_one_lane_of_long_codes_and_dense_islands(orc, fmt):
     lb = np.frombuffer(arr[h.off_lane_bits:h.off_lane_bits + 128 * h.n_chunks].tobytes(), "<u2").reshape(-1, 64)
     assert lb[5, 7] > 2 * np.median(lb) and lb[9].sum() > 2 * np.median(lb.sum(axis=1))    # the cases are what they claim
     _check(orc, fmt, x, lane_syms=N, group_chunks=4)
+
+
+def test_batch_of_more_than_2_to_the_32_chunks():
+    """One E5M2 tensor over and over into one buffer (17.6 TB of output), but for the members that hold the chunks 2^31 and 2^32, where a launch ends or 32 bits
+    do, and the last one, which have a buffer each."""
+    chunks = (1 << 16) - 1
+    n = chunks * 4096
+    w = synth.make_e5m2(1, n, 1.7, 0.02, 3, 0, DEV).view(torch.uint8)
+    hdr, blob = ecfw.ecfw_encode_gpu(E5M2, w, 1, n, lane_syms=64)
+    assert hdr.n_chunks == chunks
+    members = (1 << 32) // chunks + 3
+    outs = [torch.empty(n, dtype=torch.uint8, device=DEV)] * members
+    own = [(1 << 31) // chunks, (1 << 32) // chunks, members - 1]
+    for i in own:
+        outs[i] = torch.full((n,), 0xA5, dtype=torch.uint8, device=DEV)
+    batch = ecfw.WBatch([hdr] * members, [blob] * members, outs)
+    assert batch.info.total_chunks > 1 << 32
+    ecfw.ecfw_decode_batched(batch)
+    torch.cuda.synchronize()
+    for i in own:
+        assert torch.equal(outs[i], w.view(-1)), i
+    del batch, outs, w, blob
+    torch.cuda.empty_cache()

@@ -63,3 +63,47 @@ for call in (e4m3, lambda: wide(ecfw.FMT_BF16), lambda: wide(ecfw.FMT_E5M2)):
 def test_nothing_is_queued_behind_a_failed_launch(tmp_path):
     """A device encode is three kernels, each of which takes from the blob what the one before has written there, places to store at among it."""
     run_on_shim(tmp_path, FAILED_LAUNCH)
+
+
+MANY_CHUNKS = r"""
+lib = ecf8._lib
+at = 1 << 20                                                            # an address that nothing looks at
+def queued(total, call):
+    var("launches").value = 0
+    assert call(total) == 0
+    return var("launches").value
+def e4m3(total):
+    i = ecf8.BatchInfo(total_chunks=total, lane_syms=32, max_code_len=7)
+    return lib.ecf8_decode_batched(at, 7, ctypes.byref(i), None)
+def wide(total, fmt, longest):
+    i = ecfw.WBatchInfo(total_chunks=total, fmt=fmt, lane_syms=64, max_code_len=longest)
+    return lib.ecfw_decode_batched(at, 7, ctypes.byref(i), None)
+def group(total, M):
+    i = ecf8.GemmGroupInfo(total_work=total, n_items=7, max_M=M)
+    return lib.ecf8_gemm_fp8_grouped(at, ctypes.byref(i), None)
+calls = [e4m3] + [lambda t, f=f, l=l: wide(t, f, l) for f in (ecfw.FMT_BF16, ecfw.FMT_E5M2) for l in (12, 16)] + [lambda t, M=M: group(t, M) for M in (1, 20, 64)]
+for call in calls:
+    assert [queued(t, call) for t in (1, (1 << 31) - 1, 1 << 31, (1 << 31) + 1, (1 << 32) - 1, 1 << 32, (1 << 32) + 1)] == [1, 1, 1, 2, 2, 2, 3]
+# one tensor of more than that
+n = ((1 << 31) + 1) * 2048
+h = ecf8.ecf8_encode(__import__("numpy").zeros(2048, dtype="uint8"), 1, 2048, lane_syms=32).header
+def header(n):
+    g = ecf8.Header.from_buffer_copy(bytes(h))
+    g.rows, g.cols, g.n_elem, g.n_chunks, g.plane_bytes = 1, n, n, -(-n // 2048), -(-n // 2048) * 1024
+    g.total_size = g.off_plane + g.plane_bytes
+    return g
+big, most = header(n), header(1 << 42)
+assert lib.ecf8_decode(ctypes.byref(big), at, at, n, None) == ecf8.E_FORMAT
+assert queued(0, lambda _: lib.ecf8_decode(ctypes.byref(most), at, at, n, None)) == 1
+w = ecfw.ecfw_encode(ecfw.FMT_BF16, __import__("numpy").zeros(4096, dtype="uint16"), 1, 4096).header
+w.n_elem, w.n_chunks = ((1 << 31) + 1) * 4096, (1 << 31) + 1
+assert lib.ecfw_decode(at, ctypes.byref(w), at, 4 * w.n_elem, 0, None) == ecf8.E_FORMAT
+w.n_elem, w.n_chunks = (1 << 31) * 4096, 1 << 31
+assert queued(0, lambda _: lib.ecfw_decode(at, ctypes.byref(w), at, 4 * w.n_elem, 0, None)) == 1
+assert lib.ecf8_gemm_fp8_raw(at, 1 << 40, 1 << 20, at, 1, at, None) == ecf8.E_ARG
+"""
+
+
+def test_chunk_numbers_past_32_bits(tmp_path):
+    """Kernels number chunks in 32 bits: a batch or a group of more than 2^31 is several launches, a tensor of more is refused."""
+    run_on_shim(tmp_path, MANY_CHUNKS)
