@@ -515,7 +515,8 @@ struct BatchItem {
         }
         const uint32_t mine = (uint32_t)lane >> 2;
         const GLOBAL uint64_t *w = (const GLOBAL uint64_t *)(items + lo + (mine < n ? mine : 0)) + 4 * (lane & 3);
-        const u32x4 a = ((const GLOBAL u32x4 *)w)[0], b = ((const GLOBAL u32x4 *)w)[1];
+        typedef uint32_t u32x4_at_8 __attribute__((ext_vector_type(4), aligned(8)));       // the wide call's items are aligned to 8 bytes
+        const u32x4_at_8 a = ((const GLOBAL u32x4_at_8 *)w)[0], b = ((const GLOBAL u32x4_at_8 *)w)[1];
         part[0] = a.x | (uint64_t)a.y << 32;
         part[1] = a.z | (uint64_t)a.w << 32;
         part[2] = b.x | (uint64_t)b.y << 32;

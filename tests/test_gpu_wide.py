@@ -402,6 +402,28 @@ def test_one_lane_of_long_codes_and_dense_islands(orc, fmt):
     _check(orc, fmt, x, lane_syms=N, group_chunks=4)
 
 
+@pytest.mark.parametrize("members", [1, 16, 17, 70])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_batch_items_at_odd_multiples_of_8(fmt, members):
+    """The item table may lie at any multiple of 8 bytes."""
+    xs = [_rand_elems(fmt, 5000 + 1000 * i, i) for i in range(members)]
+    blobs = [ecfw.ecfw_encode(fmt, x, 1, x.size) for x in xs]
+    outs = [torch.zeros(x.nbytes, dtype=torch.uint8, device=DEV) for x in xs]
+    batch = ecfw.WBatch([b.header for b in blobs], [b.to(DEV) for b in blobs], outs)
+    room = torch.empty(batch.d_items.numel() + 16, dtype=torch.uint8, device=DEV)
+    items = room[8:8 + batch.d_items.numel()]
+    items.copy_(batch.d_items)
+    assert items.data_ptr() % 16 == 8
+    batch.d_items = items
+    ecfw.ecfw_decode_batched(batch)
+    for x, o in zip(xs, outs):
+        assert np.array_equal(o.cpu().numpy(), x.view(np.uint8))
+    batch.d_items = room[4:4 + items.numel()]
+    with pytest.raises(ecf8.Ecf8Error) as e:
+        ecfw.ecfw_decode_batched(batch)
+    assert e.value.code == ecf8.E_ALIGN
+
+
 def test_batch_of_more_than_2_to_the_32_chunks():
     """One E5M2 tensor over and over into one buffer (17.6 TB of output), but for the members that hold the chunks 2^31 and 2^32, where a launch ends or 32 bits
     do, and the last one, which have a buffer each."""
