@@ -6,6 +6,7 @@
 
 #include <chrono>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace {
@@ -127,163 +128,168 @@ inline Ranges make_ranges(uint64_t chunks, uint32_t cus)
 // list is the symbols' coins and the packages of the level below, both in order, a coin before a package of its weight.  Of a level only the coins' places are
 // kept: the items taken are the first ones, so the coins among them are the first a coins, and the packages, twice as many items one level down.
 // (The CPU's E4M3 encoder asks Huffman's method first and takes its lengths where the cap does not bind.  The two agree in every tie if the one takes a leaf and
-// the other a coin first.)
-constexpr int LEVELS = 16;                  // longest codeword of any cap
+// the other a coin first; so does a cap of m - 1, which binds nowhere.)
 template <int A> struct CodeShared {
-    __attribute__((aligned(16))) uint64_t list[2][2 * A < 128 ? 128 : 2 * A];
-    uint64_t w[2 * A], package[2 * A];
-    uint16_t at[A > 64 ? LEVELS : 1][A];
-    uint32_t s[A], unsorted[A], rank[2][A < 64 ? 64 : A], m;
+    __attribute__((aligned(16))) uint64_t key[A < 64 ? 64 : A];     // count << 8 | exponent, in the order of the exponents
+    uint64_t w[A];
+    uint32_t s[A], rank[A < 64 ? 64 : A], m;
 };
 
-// m <= COINS = 16 or 64.  A coin is compared with every package at once: a lane has a coin and four packages, so COINS / 4 groups of COINS lanes have them all, one wave
-// of four groups for 16 coins, all 16 waves for 64.  A package's place in the list is a population count of a ballot, a coin's the sum of its lanes' comparisons, over
-// the groups of a wave by population counts, over waves in LDS.  One look into LDS per level and two barriers, or none, instead of a look per step of a search
-// (11 levels of 64 coins: 7.8 us in one wave with searches).
-template <int A, int COINS>
-__device__ __forceinline__ void package_merge(CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane, int wave)
+// What lies in a at the lanes with bit D set changes place with what lies in b at the lanes D below.
+template <int D>
+__device__ __forceinline__ void exchange(uint32_t &a, uint32_t &b, int lane)
 {
-    constexpr bool ONE = COINS == 16;
-    const uint32_t i = (uint32_t)lane % COINS, group = ONE ? (uint32_t)lane / COINS : (uint32_t)wave, b0 = 4 * group;
-    const uint64_t coin = i < m ? cs.w[i] : 0;
-    uint64_t at_low = i, at_high = 0;                       // wave 0: the coin's place at each level, a byte each
-    uint32_t n = m;
-    auto meet = [] {
-        if (ONE) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        else __syncthreads();
+    auto dpp = [](uint32_t old, uint32_t v, auto ctrl, auto banks) {
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, decltype(ctrl)::value, 0xf, decltype(banks)::value, false);
     };
-#pragma unroll 1
-    for (uint32_t level = 1; level < lmax; level++) {
-        const uint64_t *below = cs.list[(level - 1) & 1];
-        uint64_t *here = cs.list[level & 1];
-        uint32_t *lighter = cs.rank[level & 1];             // packages lighter than the coin
-        const uint32_t packages = n / 2;
-        uint32_t mine = 0;
-        if (ONE || b0 < packages) {
-            uint64_t pw[4], heavier[4];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; k++) pw[k] = below[2 * (b0 + k)] + below[2 * (b0 + k) + 1];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; k++) heavier[k] = __ballot(pw[k] < coin && (b0 + k < packages));
-            // the k-th lane of a group puts its k-th package in its place
-            const bool k0 = i & 1, k1 = i & 2;
-            const uint64_t w = k1 ? (k0 ? pw[3] : pw[2]) : k0 ? pw[1] : pw[0];
-            if (ONE) {
-                const uint64_t same = 0x0001000100010001ull << i;
-#pragma unroll
-                for (uint32_t k = 0; k < 4; k++) mine += (uint32_t)__builtin_popcountll(heavier[k] & same);
-                const uint64_t of = k1 ? (k0 ? heavier[3] : heavier[2]) : k0 ? heavier[1] : heavier[0];
-                if (i < 4 && b0 + i < packages) here[b0 + i + m - (uint32_t)__builtin_popcount((uint32_t)(of >> (16 * group)) & 0xffffu)] = w;
-            } else {
-                const uint32_t c0 = (uint32_t)__builtin_popcountll(heavier[0]), c1 = (uint32_t)__builtin_popcountll(heavier[1]);
-                const uint32_t c2 = (uint32_t)__builtin_popcountll(heavier[2]), c3 = (uint32_t)__builtin_popcountll(heavier[3]);
-                if (i < 4 && b0 + i < packages) here[b0 + i + m - (k1 ? (k0 ? c3 : c2) : k0 ? c1 : c0)] = w;
-#pragma unroll
-                for (uint32_t k = 0; k < 4; k++) mine += pw[k] < coin && b0 + k < packages ? 1u : 0u;
-                if (mine) atomicAdd(&lighter[i], mine);
-            }
-        }
-        if (!ONE) meet();
-        if (ONE || wave == 0) {
-            const uint32_t place = i + (ONE ? mine : lighter[i]);
-            if (i < m && (uint32_t)lane < COINS) here[place] = coin;
-            if (level < 8) at_low |= (uint64_t)place << (level * 8);
-            else at_high |= (uint64_t)place << (level * 8 - 64);
-            if (!ONE) cs.rank[(level + 1) & 1][i] = 0;
-        }
-        n = m + packages;
-        meet();
+    uint32_t x, y;
+    if constexpr (D == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        x = r[0], y = r[1];
+    } else if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        x = r[0], y = r[1];
+    } else if constexpr (D == 8 || D == 4) {                // row_shr, row_shl, into the banks of four lanes that change
+        x = dpp(a, b, std::integral_constant<int, 0x110 + D>(), std::integral_constant<int, D == 8 ? 0xc : 0xa>());
+        y = dpp(b, a, std::integral_constant<int, 0x100 + D>(), std::integral_constant<int, D == 8 ? 0x3 : 0x5>());
+    } else {                                                // quad_perm [0 1 0 1], [2 3 2 3]; [0 0 2 2], [1 1 3 3]
+        x = dpp(a, b, std::integral_constant<int, D == 2 ? 0x44 : 0xa0>(), std::integral_constant<int, 0xf>());
+        y = dpp(b, a, std::integral_constant<int, D == 2 ? 0xee : 0xf5>(), std::integral_constant<int, 0xf>());
+        x = lane & D ? x : a;
+        y = lane & D ? b : y;
     }
-    if (wave != 0) return;
-    uint32_t bits = 0, taken = 2 * m - 2;
-#pragma unroll 1
-    for (uint32_t level = lmax; level-- > 0;) {
-        const uint32_t place = (uint32_t)((level < 8 ? at_low : at_high) >> (level % 8 * 8)) & 0xffu;
-        const uint32_t a = (uint32_t)__builtin_popcountll(__ballot((uint32_t)lane < m && place < taken));
-        bits += (uint32_t)lane < a ? 1u : 0u;
-        taken = 2 * (taken - a);
+    a = x, b = y;
+}
+template <int D>
+__device__ __forceinline__ void exchange(uint64_t &a, uint64_t &b, int lane)
+{
+    uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b, bh = (uint32_t)(b >> 32);
+    exchange<D>(al, bl, lane);
+    exchange<D>(ah, bh, lane);
+    a = al | (uint64_t)ah << 32;
+    b = bl | (uint64_t)bh << 32;
+}
+template <class T>
+__device__ __forceinline__ void in_order(T &a, T &b)
+{
+    const T x = a < b ? a : b;
+    b = a < b ? b : a;
+    a = x;
+}
+// One stage of a merge: items that differ in lane bit D only, put in order.  The bit becomes the register's (a before b), the register's the lane's.
+template <int D, int J, class T>
+__device__ __forceinline__ void merge_lanes(T (&a)[J], T (&b)[J], int lane)
+{
+#pragma unroll
+    for (int j = 0; j < J; j++) {
+        exchange<D>(a[j], b[j], lane);
+        in_order(a[j], b[j]);
     }
-    if ((uint32_t)lane < m) len[cs.s[lane]] = m == 1 ? 1u : bits;
+    if constexpr (D > 1) merge_lanes<D / 2>(a, b, lane);
 }
 
-// Any m, one wave: an item's place from a binary search in the other list.
-template <int A>
-__device__ __noinline__ void package_merge_any(CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane)
+// m <= LANES * J, by one wave, all in registers: items 2 i and 2 i + 1 of a level's list are a[j] and b[j] of lane l, i = j * LANES + l, so that package i is a sum in its
+// lane.  The coins lie there in reverse, and coins and packages, both in order, are one bitonic sequence: log2(2 LANES J) stages of minimum and maximum put it
+// in order, through which the lowest bit of an item's place comes to be the register's again (merge_lanes).  T: an item is its weight twice, and 1 more if it
+// is a package; 32 bits take 15 levels of 2^27 weights.  Where fewer than 64 lanes are enough the others do the same once more.
+// What bounds it: one wave's chain of some 8 clocks an instruction.  The plan kernel in a kernel trace, us, with coins and packages looked for in each other's list
+// in LDS (up to 64 coins by all waves, five round trips and two barriers a level, more by one wave) / now: 256 x 512 BF16 of 30 exponents 11.3 / 8.6, of 70 39.7 / 11.9,
+// of 256 50.6 / 16.6, E5M2 9.6 / 6.9, E4M3 6.0 / 5.4, cap 15 8.6 / 7.2.
+template <int A, int LANES, int J, class T>
+__device__ __forceinline__ void package_merge(const CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane)
 {
-    constexpr int PER = (A + 63) / 64;
-    auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
-    uint64_t coin[PER];
+    static_assert(LANES * J <= A || A < LANES, "coins");
+    constexpr T NONE = (T)~(T)0;
+    constexpr uint32_t N = LANES * J;
+    const uint32_t l = (uint32_t)lane % LANES;
+    if (lmax > m - 1) lmax = m - 1;
+    T a[J], b[J], coin[J];
+    uint32_t kept[J][4];                                    // lane `level`: which items of the level are coins, of a (64 lanes) and of b
 #pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const uint32_t i = lane + 64 * k;
-        coin[k] = i < m ? cs.w[i] : 0;
-        if (i < m) cs.list[0][i] = coin[k];
+    for (int j = 0; j < J; j++) {
+        const uint32_t i = j * LANES + l, back = N - 1 - i;
+        a[j] = 2 * i < m ? (T)cs.w[2 * i] << 1 : NONE;
+        b[j] = 2 * i + 1 < m ? (T)cs.w[2 * i + 1] << 1 : NONE;
+        coin[j] = back < m ? (T)cs.w[back] << 1 : NONE;
+#pragma unroll
+        for (int k = 0; k < 4; k++) kept[j][k] = 0;
     }
     uint32_t n = m;
-    const uint32_t top = 1u << (31 - __builtin_clz(m));
-    fence();
 #pragma unroll 1
     for (uint32_t level = 1; level < lmax; level++) {
-        const uint64_t *below = cs.list[(level - 1) & 1];
-        uint64_t *here = cs.list[level & 1];
         const uint32_t packages = n / 2;
-        uint64_t pw[PER];
-        uint32_t lighter[PER], coins[PER];                  // packages lighter than the coin, coins not heavier than the package
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const uint32_t b = lane + 64 * k;
-            pw[k] = b < packages ? below[2 * b] + below[2 * b + 1] : 0;
-            if (b < packages) cs.package[b] = pw[k];
-            lighter[k] = coins[k] = 0;
-        }
-        fence();
-#pragma unroll 1
-        for (uint32_t step = top; step; step >>= 1) {
-#pragma unroll
-            for (int k = 0; k < PER; k++) {
-                const uint32_t x = lighter[k] + step, y = coins[k] + step;
-                const uint64_t px = cs.package[x - 1], cy = cs.w[y - 1];
-                if (x <= packages && px < coin[k]) lighter[k] = x;
-                if (y <= m && cy <= pw[k]) coins[k] = y;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const uint32_t i = lane + 64 * k;
-            if (i < m) {
-                here[i + lighter[k]] = coin[k];
-                cs.at[level][i] = (uint16_t)(i + lighter[k]);
-            }
-            if (i < packages) here[i + coins[k]] = pw[k];
-        }
         n = m + packages;
-        fence();
-    }
-    uint32_t bits[PER], taken = 2 * m - 2;
 #pragma unroll
-    for (int k = 0; k < PER; k++) bits[k] = 0;
+        for (int j = 0; j < J; j++) {
+            T p = (T)(a[j] & ~(T)1) + (T)(b[j] | (T)1);
+            p = j * LANES + l < packages ? p : NONE;
+            a[j] = coin[j];
+            b[j] = p;
+            in_order(a[j], b[j]);
+        }
+#pragma unroll
+        for (int s = J / 2; s >= 1; s /= 2)                 // the stages between registers: what merge_lanes does, without an instruction to exchange
+#pragma unroll
+            for (int j = 0; j < J; j++) {
+                if (j & s) continue;
+                in_order(a[j], a[j + s]);
+                in_order(b[j], b[j + s]);
+                const T t = a[j + s];
+                a[j + s] = b[j];
+                b[j] = t;
+            }
+        merge_lanes<LANES / 2>(a, b, lane);
+#pragma unroll
+        for (int j = 0; j < J; j++) {
+            const uint64_t ca = __ballot(!(a[j] & 1)), cb = __ballot(!(b[j] & 1));
+            const bool here = lane == (int)level;
+            kept[j][0] = here ? (uint32_t)ca : kept[j][0];
+            kept[j][1] = here ? (uint32_t)(ca >> 32) : kept[j][1];
+            kept[j][2] = here ? (uint32_t)cb : kept[j][2];
+            kept[j][3] = here ? (uint32_t)(cb >> 32) : kept[j][3];
+        }
+    }
+    uint32_t bits[J], taken = 2 * m - 2;
+#pragma unroll
+    for (int j = 0; j < J; j++) bits[j] = 0;
 #pragma unroll 1
     for (uint32_t level = lmax; level-- > 0;) {
-        uint32_t a = 0;
+        uint32_t coins = taken < m ? taken : m;             // the lowest level has no packages
+        if (level) {
+            coins = 0;
 #pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const uint32_t i = lane + 64 * k;
-            a += (uint32_t)__builtin_popcountll(__ballot(i < m && (level ? cs.at[level][i] : i) < taken));
+            for (int j = 0; j < J; j++)
+#pragma unroll
+                for (int r = 0; r < 2; r++) {
+                    const uint64_t is = (uint32_t)__builtin_amdgcn_readlane((int)kept[j][2 * r], (int)level) |
+                                        (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)kept[j][2 * r + 1], (int)level) << 32;
+                    const int t = (int)((taken + 1 - r) / 2) - j * LANES;           // so many of a's or b's are taken
+                    const uint64_t first = t <= 0 ? 0 : t >= 64 ? ~0ull : (1ull << t) - 1;
+                    coins += (uint32_t)__builtin_popcountll(is & first);
+                }
         }
 #pragma unroll
-        for (int k = 0; k < PER; k++) bits[k] += lane + 64 * k < a ? 1u : 0u;
-        taken = 2 * (taken - a);
+        for (int j = 0; j < J; j++) bits[j] += j * LANES + l < coins ? 1u : 0u;
+        taken = 2 * (taken - coins);
     }
 #pragma unroll
-    for (int k = 0; k < PER; k++)
-        if (lane + 64 * k < m) len[cs.s[lane + 64 * k]] = bits[k];
+    for (int j = 0; j < J; j++)
+        if (lane < LANES && j * LANES + l < m) len[cs.s[j * LANES + l]] = m == 1 ? 1u : bits[j];
+}
+template <int A, class T>
+__device__ __forceinline__ void package_merge(const CodeShared<A> &cs, uint32_t m, uint32_t lmax, uint32_t *len, int lane)
+{
+    if constexpr (A <= 64) package_merge<A, A, 1, T>(cs, m, lmax, len, lane);
+    else if (m <= 64) package_merge<A, 64, 1, T>(cs, m, lmax, len, lane);
+    else if (m <= 128) package_merge<A, 64, 2, T>(cs, m, lmax, len, lane);
+    else package_merge<A, 64, A / 64, T>(cs, m, lmax, len, lane);
 }
 
 // The code and everything that follows from it.  C: a codec: A exponents, Header, finish() (what the header holds beside the sections' places, and the
 // sections between header and chunk_bit[]).  `h` is the header as far as it does not depend on the code; where the blob would not fit, or no code of lmax bits
 // has room for the exponents that occur, nothing but a header is written: 0, and the error.
-// What bounds it: one compute unit, a chain of barriers and round trips to LDS, while the rest of the chip waits.  In a kernel trace, 256 ranges: E4M3 6.0 us, half of it
-// the lengths; E5M2 9.8; BF16 13.3, of which 3.5 are the 256 KiB of records.  On the host, between two launches, it took 8 us and, for BF16, 18.
+// What bounds it: one compute unit, a chain of barriers and round trips to LDS, while the rest of the chip waits.  In a kernel trace, 256 ranges: E4M3 5.5 us, E5M2 7.1,
+// BF16 10.1, of which 3.5 are the 256 KiB of records.  On the host, between two launches, it took 8 us and, for BF16, 18.
 template <class C>
 __global__ __launch_bounds__(1024) void plan_kernel(typename C::Header h, Ranges rg, uint64_t blob_, uint64_t capacity, uint64_t records, uint32_t lmax, uint64_t mail)
 {
@@ -321,7 +327,10 @@ __global__ __launch_bounds__(1024) void plan_kernel(typename C::Header h, Ranges
         }
     }
     if (wave == 0) s_header[lane] = frame;
-    if (tid < (A < 64 ? 64 : A)) cs.rank[0][tid] = cs.rank[1][tid] = 0;
+    if (tid < (A < 64 ? 64 : A)) {
+        cs.rank[tid] = 0;
+        cs.key[tid] = ~0ull;
+    }
 #pragma unroll
     for (int k = 0; k < 4; k++) {
         if constexpr (QUADS < 64) {
@@ -365,32 +374,33 @@ __global__ __launch_bounds__(1024) void plan_kernel(typename C::Header h, Ranges
         } else
             m = (uint32_t)__builtin_popcountll(there);
         const uint32_t i = before + (uint32_t)__builtin_popcountll(there & ((1ull << lane) - 1));
-        if (f) {
-            cs.package[i] = f;
-            cs.unsorted[i] = (uint32_t)tid;
-        }
+        if (f) cs.key[i] = f << 8 | (uint32_t)tid;          // f <= 2^48
         if (tid == 0) cs.m = m;
     }
     __syncthreads();
+    // a thread compares one of them with 4 (m <= 64: each wave with others of 4) or 64 (each four waves)
     const uint32_t m = uniform32(cs.m), spread = A <= 64 || m <= 64 ? 6 : 8, mine = tid & ((1u << spread) - 1u);
-    const uint64_t weight = mine < m ? cs.package[mine] : 0;
-    if (mine < m) {
+    const uint64_t key = cs.key[mine];
+    const uint32_t others = spread == 6 ? 4 : 64, from = (tid >> spread) * others;
+    if (from < m && mine < m) {
         uint32_t before = 0;
-        for (uint32_t j = tid >> spread; j < m; j += 1024u >> spread) before += cs.package[j] < weight || (cs.package[j] == weight && j < mine) ? 1u : 0u;
-        if (before) atomicAdd(&cs.rank[0][mine], before);
+        for (uint32_t j = from; j < from + others; j += 4) {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) before += cs.key[j + k] < key ? 1u : 0u;
+        }
+        if (before) atomicAdd(&cs.rank[mine], before);
     }
     __syncthreads();
     if (tid == (int)mine && mine < m) {
-        const uint32_t r = cs.rank[0][mine];
-        cs.w[r] = cs.list[0][r] = weight;
-        cs.s[r] = cs.unsorted[mine];
+        const uint32_t r = cs.rank[mine];
+        cs.w[r] = key >> 8;
+        cs.s[r] = (uint32_t)key & 0xffu;
     }
     __syncthreads();
     const bool code = lmax >= 1 && m <= 1u << lmax;
-    if (code) {
-        if (A == 16 && wave == 0) package_merge<A, 16>(cs, m, lmax, s_len, lane, 0);
-        else if (A != 16 && (A <= 64 || m <= 64)) package_merge<A, 64>(cs, m, lmax, s_len, lane, wave);
-        else if (A > 64 && wave == 0) package_merge_any<A>(cs, m, lmax, s_len, lane);
+    if (code && wave == 0) {
+        if (h.n_elem < 1ull << 27) package_merge<A, uint32_t>(cs, m, lmax, s_len, lane);
+        else package_merge<A, uint64_t>(cs, m, lmax, s_len, lane);
     }
     __syncthreads();
 

@@ -209,6 +209,34 @@ def test_codes_of_equal_counts(fmt, m):
         assert np.array_equal(blob.cpu().numpy(), want.numpy()), (cap, kind)
 
 
+@pytest.mark.parametrize("cap", [12, 16])
+def test_many_exponents_are_coded_nearly_as_fast_as_few(cap):
+    """BF16 of 256 exponents against some 30: the same passes over memory and a longer package-merge, 1.5 times as long when the host made the code; 2.4 to 2.8 with
+    one wave's binary searches, 1.3 to 1.4 now."""
+    few = (torch.randn(1024, 1024, device=DEV) * 0.02).to(torch.bfloat16).view(torch.int16)
+    many = torch.randint(-32768, 32768, (1024, 1024), dtype=torch.int16, device=DEV)
+    buf = torch.empty(1 << 22, dtype=torch.uint8, device=DEV)
+    t_few, t_many = best_times([lambda x=x: ecfw.ecfw_encode_gpu(BF16, x, max_code_len=cap, d_blob=buf) for x in (few, many)])
+    print("%.1f us, of few exponents %.1f" % (t_many, t_few))
+    assert t_many < 1.9 * t_few
+
+
+@pytest.mark.parametrize("fmt,m", [(E5M2, 32), (BF16, 40), (BF16, 64), (BF16, 65), (BF16, 128), (BF16, 129), (BF16, 256)])
+@pytest.mark.parametrize("cap", [8, 12, 16])
+def test_codes_of_counts_past_32_bits_of_weight(fmt, m, cap):
+    """2^27 elements and more: the package-merge weighs in 64 bits.  A tensor over and over has the tensor's code."""
+    rng = np.random.default_rng(100 * m + cap)
+    counts = rng.multinomial(65536 - m, rng.dirichlet(np.ones(m) * 0.2)) + 1
+    e = np.repeat(rng.choice(32 if fmt == E5M2 else 256, m, replace=False), counts)
+    rng.shuffle(e)
+    x = (e << 7).astype(np.uint16) if fmt == BF16 else (e << 2).astype(np.uint8)
+    want = ecfw.ecfw_encode(fmt, x, 1, x.size, max_code_len=cap, lane_syms=64)
+    times = (1 << 11) + 1
+    hdr, blob = ecfw.ecfw_encode_gpu(fmt, _to_dev(fmt, x).repeat(times), 1, times * x.size, max_code_len=cap, lane_syms=64)
+    assert hdr.n_elem > 1 << 27 and hdr.stream_bits == times * want.header.stream_bits and hdr.max_code_len == want.header.max_code_len
+    assert np.array_equal(blob[hdr.off_code_len:hdr.off_code_len + 256].cpu().numpy(), want.numpy()[want.header.off_code_len:want.header.off_code_len + 256])
+
+
 def test_argument_errors():
     x = torch.zeros(10000, dtype=torch.int16, device=DEV)
     with pytest.raises(ecf8.Ecf8Error) as e:
