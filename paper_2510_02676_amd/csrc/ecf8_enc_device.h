@@ -285,9 +285,10 @@ __device__ __forceinline__ void package_merge(const CodeShared<A> &cs, uint32_t 
     else package_merge<A, 64, A / 64, T>(cs, m, lmax, len, lane);
 }
 
-// The code and everything that follows from it.  C: a codec: A exponents, Header, finish() (what the header holds beside the sections' places, and the
+// The code and everything that follows from it.  C: a codec: A exponents, Header, sign_bytes(), finish() (what the header holds beside the sections' places, and the
 // sections between header and chunk_bit[]).  `h` is the header as far as it does not depend on the code; where the blob would not fit, or no code of lmax bits
-// has room for the exponents that occur, nothing but a header is written: 0, and the error.
+// has room for the exponents that occur, the header is 0 and the error, and nothing is written behind it but what the container has no use for: the ranges' places in
+// chunk_bit[] (if there is a code), and the records, where they lie.
 // What bounds it: one compute unit, a chain of barriers and round trips to LDS, while the rest of the chip waits.  In a kernel trace, 256 ranges: E4M3 5.5 us, E5M2 7.1,
 // BF16 10.1, of which 3.5 are the 256 KiB of records.  On the host, between two launches, it took 8 us and, for BF16, 18.
 template <class C>
@@ -447,18 +448,16 @@ __global__ __launch_bounds__(1024) void plan_kernel(typename C::Header h, Ranges
     if (wave != 0) return;
 
     // the header
-    auto up = [](uint64_t v, uint64_t a) { return (v + a - 1) / a * a; };
     Header &out = *(Header *)s_header;
-    const uint64_t stream_bytes = up((total + 7) / 8 + 8, 16), off_plane = up(h.off_stream + stream_bytes, 256), behind = up(off_plane + h.plane_bytes, 256);
-    const uint64_t size = C::size(h, behind);
-    const int err = !code ? ECF8_E_ARG : size > capacity ? ECF8_E_CAPACITY : 0;
+    const ecf8_internal::LayoutEnd e = ecf8_internal::layout_end(h.off_stream, total, h.plane_bytes, C::sign_bytes(h));
+    const int err = !code ? ECF8_E_ARG : e.total > capacity ? ECF8_E_CAPACITY : 0;
     if (lane == 0) {
         out.stream_bits = total;
-        out.stream_bytes = stream_bytes;
-        out.off_plane = off_plane;
-        out.total_size = size;
+        out.stream_bytes = e.stream_bytes;
+        out.off_plane = e.off_plane;
+        out.total_size = e.total;
     }
-    C::finish(out, blob, behind, s_freq, s_len, m, s_len[cs.s[0]], err == 0, lane);     // the lightest symbol's codeword is the longest
+    C::finish(out, blob, e.off_sign, s_freq, s_len, m, s_len[cs.s[0]], err == 0, lane);     // the lightest symbol's codeword is the longest
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (err && lane < 2) s_header[lane] = lane ? (uint32_t)err : 0u;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

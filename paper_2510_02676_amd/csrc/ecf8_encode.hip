@@ -1,7 +1,7 @@
 // GPU-side ECF8 encoder for gfx950 (paper Section 3.1: histogram, code, stream, metadata and
 // nibble plane, produced on the device so that FP8 checkpoints compress at load time without a
 // trip through host memory).  Writes exactly the container the CPU encoder writes, byte for
-// byte: the same code under every cap, ties included, and the layout of the same routine.
+// byte: the same code under every cap, ties included, and the layout from the same routines.
 //
 //   histograms of ranges of chunks -> code, places of the ranges in the stream, header (one workgroup; the host waits for the header) -> everything else:
 //   planes, lane_bits, the chunks' bits packed in LDS and copied to the stream, pair table and padding (encode_range).
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(1024) void histogram_kernel(EncArgs a, Ranges rg, u
 struct E4M3Codec {
     static constexpr int A = 16;
     typedef ecf8_header Header;
-    static __device__ __forceinline__ uint64_t size(const Header &, uint64_t behind) { return behind; }
+    static __device__ __forceinline__ uint64_t sign_bytes(const Header &) { return 0; }
     static __device__ __forceinline__ void finish(Header &h, GLOBAL uint8_t *, uint64_t, const uint64_t *freq, const uint32_t *len, uint32_t, uint32_t, bool, int lane)
     {
         if (lane >= 16) return;

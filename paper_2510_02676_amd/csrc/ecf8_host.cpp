@@ -26,7 +26,7 @@
 
 namespace {
 
-inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
+using ecf8_internal::round_up;
 
 bool lane_syms_ok(uint32_t n) { return n == 32 || n == 64 || n == 128; }
 bool group_ok(uint32_t g) { return g >= 1 && g <= 64 && (g & (g - 1)) == 0; }
@@ -181,10 +181,11 @@ Layout make_layout(uint64_t n, uint64_t bits, uint32_t N, uint32_t table_bits)
     L.off_cb = 256 + (table_bits ? (2ull << table_bits) : 0);
     L.off_lb = round_up(L.off_cb + 8 * (L.n_chunks + 1), 256);
     L.off_st = round_up(L.off_lb + 2 * L.n_chunks * ECF8_LANES, 256);
-    L.st_bytes = round_up((bits + 7) / 8 + 8, 16);
-    L.off_pl = round_up(L.off_st + L.st_bytes, 256);
     L.pl_bytes = L.n_chunks * 32ull * N;
-    L.total = round_up(L.off_pl + L.pl_bytes, 256);
+    const ecf8_internal::LayoutEnd e = ecf8_internal::layout_end(L.off_st, bits, L.pl_bytes, 0);
+    L.st_bytes = e.stream_bytes;
+    L.off_pl = e.off_plane;
+    L.total = e.total;
     return L;
 }
 

@@ -19,6 +19,24 @@ namespace ecf8_internal {
 // batches and groups are several launches; a tensor of more (4 TiB or more, the encoders take 1 TiB of E4M3) is refused.
 constexpr uint64_t LAUNCH_CHUNKS = 1ull << 31;
 
+constexpr uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
+
+// The part of either container's layout that depends on the code, for the host and for the kernel that makes the code: where what follows the stream lies.
+// The stream ends with 8 bytes that a decoder may look ahead to; off_sign 0: no such section.
+struct LayoutEnd {
+    uint64_t stream_bytes, off_plane, off_sign, total;
+};
+constexpr LayoutEnd layout_end(uint64_t off_stream, uint64_t stream_bits, uint64_t plane_bytes, uint64_t sign_bytes)
+{
+    LayoutEnd e{};
+    e.stream_bytes = round_up((stream_bits + 7) / 8 + 8, 16);
+    e.off_plane = round_up(off_stream + e.stream_bytes, 256);
+    const uint64_t behind = round_up(e.off_plane + plane_bytes, 256);
+    e.off_sign = sign_bytes ? behind : 0;
+    e.total = behind + round_up(sign_bytes, 256);
+    return e;
+}
+
 struct Plan {
     ecf8_header hdr;              // complete header of the blob to be written
     uint32_t code[16];            // canonical codewords, first bit most significant

@@ -1,6 +1,6 @@
 // GPU-side encoder of the wide-alphabet codec (E5M2, BF16) for gfx950: Section 3.1 on the device
 // for 5- and 8-bit exponent fields.  Writes exactly the container ecfw_encode writes, byte for byte:
-// the same code under every cap, ties included, and the layout of the same routine.
+// the same code under every cap, ties included, and the layout from the same routines.
 //
 //   histograms of ranges of chunks -> code, places of the ranges in the stream, header, code lengths, histogram (one workgroup; the host waits for the
 //   header) -> everything else, as in the E4M3 encoder (encode_range).
@@ -128,13 +128,13 @@ template <int FMT>
 struct WCodec {
     static constexpr int A = EFmt<FMT>::A;
     typedef ecfw_header Header;
-    static __device__ __forceinline__ uint64_t size(const Header &h, uint64_t behind) { return h.sign_bytes ? (behind + h.sign_bytes + 255) / 256 * 256 : behind; }
-    static __device__ __forceinline__ void finish(Header &h, GLOBAL uint8_t *blob, uint64_t behind, const uint64_t *freq, const uint32_t *len, uint32_t m, uint32_t longest, bool write, int lane)
+    static __device__ __forceinline__ uint64_t sign_bytes(const Header &h) { return h.sign_bytes; }
+    static __device__ __forceinline__ void finish(Header &h, GLOBAL uint8_t *blob, uint64_t off_sign, const uint64_t *freq, const uint32_t *len, uint32_t m, uint32_t longest, bool write, int lane)
     {
         if (lane == 0) {
             h.max_code_len = longest;
             h.n_symbols = m;
-            h.off_sign = h.sign_bytes ? behind : 0;
+            h.off_sign = off_sign;
         }
         if (!write) return;
         uint32_t four = 0;                                  // zeros behind the last

@@ -16,7 +16,7 @@
 
 namespace {
 
-inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
+using ecf8_internal::round_up;
 
 struct Format {
     uint32_t fmt, alphabet, elem_bytes, piece;   // piece = elements per 16 output bytes
@@ -61,19 +61,13 @@ Sections make_sections(const Format &f, uint64_t n, uint64_t bits, uint32_t N)
     s.off_cb = s.off_freq + round_up(8ull * f.alphabet, 256);
     s.off_lb = s.off_cb + round_up(8 * (s.n_chunks + 1), 256);
     s.off_st = s.off_lb + round_up(128 * s.n_chunks, 256);
-    s.st_bytes = round_up((bits + 7) / 8 + 8, 16);
-    s.off_pl = s.off_st + round_up(s.st_bytes, 256);
-    if (f.fmt == ECFW_FMT_BF16) {
-        s.pl_bytes = s.n_chunks * 64 * N;
-        s.sg_bytes = 0;
-        s.off_sg = 0;
-        s.total = s.off_pl + round_up(s.pl_bytes, 256);
-    } else {
-        s.pl_bytes = s.n_chunks * 16 * N;
-        s.sg_bytes = s.n_chunks * 8 * N;
-        s.off_sg = s.off_pl + round_up(s.pl_bytes, 256);
-        s.total = s.off_sg + round_up(s.sg_bytes, 256);
-    }
+    s.pl_bytes = s.n_chunks * (f.fmt == ECFW_FMT_BF16 ? 64 : 16) * N;
+    s.sg_bytes = f.fmt == ECFW_FMT_BF16 ? 0 : s.n_chunks * 8 * N;
+    const ecf8_internal::LayoutEnd e = ecf8_internal::layout_end(s.off_st, bits, s.pl_bytes, s.sg_bytes);
+    s.st_bytes = e.stream_bytes;
+    s.off_pl = e.off_plane;
+    s.off_sg = e.off_sign;
+    s.total = e.total;
     return s;
 }
 
