@@ -511,7 +511,7 @@ print("copied instead")
 
 
 def test_no_pinned_page(tmp_path):
-    """Where the runtime refuses a page, the histogram is copied.  In a process of its own, whose first library answers for the runtime."""
+    """Where the runtime refuses a page, the header is copied.  In a process of its own, whose first library answers for the runtime."""
     (tmp_path / "shim.c").write_text("int refused; int hipHostMalloc(void **p, unsigned long n, unsigned flags) { *p = 0; refused++; return 2; }\n")
     subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.c")], check=True, timeout=60)
     r = subprocess.run([sys.executable, "-c", NO_PAGE, str(tmp_path / "shim.so")], cwd=ROOT, capture_output=True, text=True, timeout=100)

@@ -237,6 +237,28 @@ def test_codes_of_counts_past_32_bits_of_weight(fmt, m, cap):
     assert np.array_equal(blob[hdr.off_code_len:hdr.off_code_len + 256].cpu().numpy(), want.numpy()[want.header.off_code_len:want.header.off_code_len + 256])
 
 
+@pytest.mark.parametrize("lane_syms", [64, 128])
+@pytest.mark.parametrize("fmt", [E5M2, BF16])
+def test_a_buffer_of_the_blobs_size_and_one_byte_less(fmt, lane_syms):
+    """That the blob does not fit is found on the device, or by the host where it is sure; nothing is written behind the buffer, and the next call is none the wiser."""
+    x = _rand_elems(fmt, 300_001, 9)
+    d_x, want = _to_dev(fmt, x), ecfw.ecfw_encode(fmt, x, 1, x.size, lane_syms=lane_syms)
+    h = want.header
+    sure = h.off_stream + h.plane_bytes + h.sign_bytes
+    assert sure + 256 < want.size
+    for room in (want.size, want.size - 1, sure, sure - 1, 255, want.size):
+        buf = torch.full((want.size + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+        if room == want.size:
+            hdr, blob = ecfw.ecfw_encode_gpu(fmt, d_x, 1, x.size, lane_syms=lane_syms, d_blob=buf[:room])
+            assert bytes(hdr) == bytes(h) and np.array_equal(blob.cpu().numpy(), want.numpy())
+        else:
+            with pytest.raises(ecf8.Ecf8Error) as e:
+                ecfw.ecfw_encode_gpu(fmt, d_x, 1, x.size, lane_syms=lane_syms, d_blob=buf[:room])
+            assert e.value.code == ecf8.E_CAPACITY
+        torch.cuda.synchronize()
+        assert bool((buf[room:] == 0xA5).all())
+
+
 def test_argument_errors():
     x = torch.zeros(10000, dtype=torch.int16, device=DEV)
     with pytest.raises(ecf8.Ecf8Error) as e:
