@@ -210,7 +210,7 @@ def per_layer_rates(tensors, alg_total, n_total, steps=10):
 
 
 def bench_config4(a):
-    """configs[4]: W 14336 x 4096 decoded tile by tile into LDS and consumed by the FP8 matrix
+    """W 14336 x 4096 decoded tile by tile into LDS and consumed by the FP8 matrix
     cores (ecf8_gemm_fp8), against the same GEMM on uncompressed W and against decode-then-GEMM."""
     from paper_2510_02676_amd import ecf8, synth
 

@@ -43,7 +43,7 @@ def _oracle_expected(orc, x):
 @pytest.mark.parametrize("table_mode", [1, 2])
 @pytest.mark.parametrize("lane_syms", [32, 64, 128])
 def test_config0_parity(orc, lane_syms, table_mode, max_code_len):
-    """configs[0]: 1024x1024, alpha 1.8, per-128x128 scaling, seed 0; with the pair table
+    """One matrix of 1024x1024, alpha 1.8, per-128x128 scaling, seed 0; with the pair table
     embedded in the blob (1) and built in the kernel (2); with the default cap on the code
     length (the kernels' branch-free form) and with plain Huffman (second level in use)."""
     w = synth.make(synth.config0()[0], seed=0).numpy().reshape(-1)
@@ -433,7 +433,7 @@ def _full_size_case(orc, specs, oracle_checks, max_code_len=0, reader_checks=(),
 
 @pytest.mark.parametrize("max_code_len", [0, 15])
 def test_config1_full_layer(orc, max_code_len):
-    """configs[1]: one full layer of the 8B-class stack (7 matrices, 218 M weights), one launch;
+    """One full layer of the 8B-class stack (7 matrices, 218 M weights), one launch;
     under the default cap on the code length and with plain Huffman.  The oracle decodes the whole
     layer, and its reader the K projection's container."""
     specs = synth.config1(0, 1)
@@ -441,21 +441,21 @@ def test_config1_full_layer(orc, max_code_len):
 
 
 def test_config1_whole_stack_one_launch(orc):
-    """configs[1] at full size in the launch configuration and memory layout bench.py times: all 32 layers (224
+    """The 8B-class stack at full size in the launch configuration and memory layout bench.py times: all 32 layers (224
     matrices, 6.98 G weights) through ONE ecf8_decode_batched launch; every output compared with
     its input on the device, two matrices also with the oracle's own encode -> bit-serial decode."""
     _full_size_case(orc, synth.config1(0, 32), {"l17.v", "l31.k"}, gpu_encode=True, arenas=True)
 
 
 def test_config2_experts_and_attention(orc):
-    """configs[2]: six full-size expert matrices and the two attention projections in one launch,
+    """Six full-size expert matrices and the two attention projections in one launch,
     containers from the CPU encoder."""
     specs = synth.config2(0, 2)
     _full_size_case(orc, specs, {"e0.gate", "e1.down"})
 
 
 def test_config2_whole_layer_one_launch(orc):
-    """configs[2] at full size: the 768 expert matrices and the two attention projections (770 tensors,
+    """A layer of 256 experts at full size: the 768 expert matrices and the two attention projections (770 tensors,
     11.6 G weights) through ONE ecf8_decode_batched launch; every output compared with its input on the
     device; the oracle decodes one expert's three matrices and an attention projection, and its reader
     one expert container."""
@@ -464,14 +464,14 @@ def test_config2_whole_layer_one_launch(orc):
 
 
 def test_config3_full_block(orc):
-    """configs[3]: one full DiT block (11 matrices, 509 M weights, per-tensor scaling), one launch,
+    """One full DiT block (11 matrices, 509 M weights, per-tensor scaling), one launch,
     containers from the CPU encoder; the oracle decodes the whole block."""
     specs = synth.config3(1)
     _full_size_case(orc, specs, {s["name"] for s in specs}, reader_checks={"b0.sa_q"})
 
 
 def test_config3_whole_stack_one_launch(orc):
-    """configs[3] at full size: all 40 blocks (440 matrices, 20.3 G weights) through ONE
+    """The DiT stack at full size: all 40 blocks (440 matrices, 20.3 G weights) through ONE
     ecf8_decode_batched launch; every output compared with its input on the device, three matrices of
     a late block also with the oracle."""
     _full_size_case(orc, synth.config3(40), {"b33.ca_k", "b33.ffn2", "b39.sa_o"}, gpu_encode=True, arenas=True)

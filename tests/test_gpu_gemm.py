@@ -1,4 +1,4 @@
-"""Fused decode + FP8 GEMM (configs[4]) against the oracle's fp64 reference, through the C ABI.
+"""Fused decode + FP8 GEMM against the oracle's fp64 reference, through the C ABI.
 
 Tolerances, both relative to sum_k |x_k w_k| of the output in question (FP8 x FP8 products are exact; only
 the accumulation differs from the fp64 reference, so the natural yardstick is the sum of magnitudes):
@@ -111,7 +111,7 @@ def test_small_gemm_against_oracle(orc, M, table_mode):
 
 @pytest.mark.parametrize("M", [1, 16, 64])
 def test_config4_full_size(orc, M):
-    """configs[4]: W 14336 x 4096 (config-2 distribution), X = M x 4096 N(0,1) rows scaled to 448.
+    """W 14336 x 4096 (the experts' distribution), X = M x 4096 N(0,1) rows scaled to 448.
     Every output of the fused kernel equals the raw-weights kernel bit for bit, on the FP8 and on the F16
     matrix cores; a sample of output columns is checked against the oracle (decoded bytes are the
     oracle's: decode(encode(W)) == W): the exact call to the configuration's 1e-5, the FP8 matrix-core
