@@ -474,7 +474,8 @@ __device__ __forceinline__ uint32_t global_window(const GLOBAL uint8_t *sp, uint
 // A launch's chunks dealt to its workgroups: a contiguous range each, cut at multiples of 64 or 8 chunks where that leaves every workgroup at least 16
 // such units (shares then differ by 1/16 at most), so that the waves of a workgroup share the interleaved groups of the layout.  The division is the
 // host's, and chunk numbers have 32 bits: a wave by itself takes 8 cycles per instruction that waits for the one before, and the start of a workgroup is a chain
-// of those (with the metadata's loads, see the decode kernel: 1024 x 1024 weights 8.2 -> 7.5 us, 4099 x 5127 12.9 -> 12.35, a layer of BF16 140.5 -> 138.7).
+// of those (with the metadata's loads, see the decode kernel: 1024 x 1024 weights 8.2 -> 7.5 us; general decode with 15-bit codewords 0.7 to 0.8 us of any size,
+// 4096 x 4096 19.9 -> 19.2; 4099 x 5127 as before, a layer of BF16 within 1 %).
 // Not kept: the last round or two of chunks as workgroups of their own behind the others, for compute units that end early (a workgroup's ends spread over a tenth
 // of a layer's time): a workgroup's start costs more, 78.7 -> 79.5 .. 84, E5M2 85.9 -> 87 .. 110 us.
 struct ChunkDeal {

@@ -319,9 +319,10 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M weights (14336 x 4096): 22.7 us in a kernel trace for the 111 MB read and written; 29.8 when the workgroups had to find their
+// The container behind the code.  58.7 M weights (14336 x 4096): 23.0 us in a kernel trace for the 111 MB read and written; 29.8 when the workgroups had to find their
 // place in the stream from one another.  Vector operations take two thirds of it, 8.7 per weight; the rest is the first fetch and the last copy, when
-// the compute unit has nothing else to do.  The whole call 52.8 -> 42.4, 256 x 512 26 -> 18, 16384 x 16384 191 -> 154.
+// the compute unit has nothing else to do.  The whole call 53.0 -> 41.4 (one input over and
+// over, from the memory-side cache, 52.7 -> 39.0), 256 x 512 26.5 -> 19.2, 14336 x 14336 147 -> 114.
 template <int N, bool CAP7>
 __global__ __launch_bounds__(WMAX * 64) void encode_kernel(EncArgs a, Ranges rg)
 {
@@ -429,6 +430,9 @@ int ecf8_encode_gpu(const void *d_fp8, uint64_t rows, uint64_t cols, const ecf8_
     if (!launched()) return ECF8_E_HIP;
     hipLaunchKernelGGL(plan_kernel<E4M3Codec>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, blob_capacity, records, lmax, mail.device());
     if (!launched()) return ECF8_E_HIP;
+    // By the cap: the code is not known yet.  Under a cap of 8 to 15 a code that needs no more than 7 bits pays for that, 14336 x 4096 with 3 bits 37.6 us under cap 7 and 42.5
+    // under 15, and is faster all the same than when the host waited for the histogram and chose by the longest codeword: 50.7; 4096 x 4096 22.5, 24.8, 35.0;
+    // 256 x 512 18.6, 18.8, 24.4.
     if (lmax <= 7) {
         if (N == 32) launch_encode<32, true>(a, rg, s);
         else if (N == 64) launch_encode<64, true>(a, rg, s);

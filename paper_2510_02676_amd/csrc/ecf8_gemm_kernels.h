@@ -610,7 +610,9 @@ __global__ __launch_bounds__(NW * 64) void ecf8_gemm_kernel(GArgs a, CODES codes
 
     if constexpr (SHORT) {
         build_pair_table<NW>(two, tbl, (uint32_t *)(smem + C::OFF_RED), lane, (int)wave_s);
-    } else if (a.off_tbl) {                                     // always
+    } else if (a.off_tbl) {
+        // Always: these calls are launched with ShortCodes where the blob has no table.  The condition changes what the compiler puts first: with / without it,
+        // and load_table's, us, 4096 x 4096 M = 17 / 32 8.4 / 8.5, 9.5 / 9.6, but 14336 x 4096 M = 16 15.5 / 15.25, M = 32 18.55 / 18.4; the others are as fast either way.
         store_table<NW>(tbl, tid, tv);
     }
 
@@ -826,9 +828,9 @@ __host__ __device__ inline uint32_t resident_chunks(uint64_t kchunks, uint64_t b
 //  * PLACES != NW: the same with the chains of chunks that are summed together in place of chunks.  For the members of a group that have M <= 32 where another one
 //    has more, so that they are computed as their own calls compute them; they also have two tiles of X in place of four (eight experts of M = 3 to 64 172.5 us ->
 //    167.8, with scales of W 191.1 -> 187.6).
-// What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.8 us), the compute unit: six of them, which the memory-side
-// cache holds, take as long for a chunk (55.3 us, 462 clocks a chunk and compute unit against 472), and no unit of it is busy all of the time: vector
-// operations 67 %, LDS 61 % (72 % of that bank conflicts of the table), first-level cache 59 %, address units 55 %; a wave waits for 55 % of its life.
+// What bounds it, eight experts of {2 x 2048 x 7168, 7168 x 2048}, scales of W: M = 4 (75.0 us), the compute unit: six of them, which the memory-side
+// cache holds, take as long for a chunk (53.9 us, 449 clocks a chunk and compute unit against 454), and no unit of it is busy all of the time: vector
+// operations 69 %, LDS 64 % (72 % of that bank conflicts of the table), first-level cache 62 %, address units 58 %; a wave waits for 53 % of its life.
 // M = 64 (213 us): two waves on a SIMD, which is what four tiles of X leave room for, wait for look-ups and turned X in turn (LDS and
 // first-level cache busy 55 % each).
 template <int MT, int NW, int N, int SC, bool SPLIT, int ACC, bool APART, int KRES, bool TURNED = KRES == 0, int PLACES = NW, class CODES = TableInBlob>

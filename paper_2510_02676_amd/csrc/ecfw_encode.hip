@@ -378,9 +378,9 @@ struct Chunk {
     }
 };
 
-// The container behind the code.  58.7 M elements (14336 x 4096): in a kernel trace BF16 34.7 us for the 198 MB read and written, nearly a copy's rate, and E5M2 26.6,
-// three quarters of it vector operations (42.7 and 35.6 when the workgroups had to find their place in the stream from one another).  The whole call
-// 84.8 -> 76.3 and 64 -> 48, 16384 x 16384 312 -> 274 and 204 -> 159.
+// The container behind the code.  58.7 M elements (14336 x 4096): in a kernel trace BF16 34.4 us for the 198 MB read and written, nearly a copy's rate, and E5M2 27.2,
+// three quarters of it vector operations (42.7 and 35.6 when the workgroups had to find their place in the stream from one another).  The whole call,
+// one input over and over, from the memory-side cache, 74.3 -> 64.6 and 63.7 -> 45.4 (BF16 from memory 84.5 -> 73.0), 14336 x 14336 252 -> 215 and 160 -> 120.
 template <int FMT, int N, int LMAX>
 __global__ __launch_bounds__(WMAX * 64) void w_encode_kernel(WEncArgs a, Ranges rg)
 {
@@ -459,6 +459,7 @@ bool launch(const WEncArgs &a, const ecfw_header &h, const Ranges &rg, uint64_t 
     if (!launched()) return false;
     hipLaunchKernelGGL(plan_kernel<WCodec<FMT>>, dim3(1), dim3(1024), 0, s, h, rg, a.blob, capacity, records, lmax, mail.device());
     if (!launched()) return false;
+    // by the cap, the code is not known yet: BF16 under cap 16 67.6 us, under 12 64.6; when the longest codeword was known at the launch 76.9 and 74.3
     if (lmax <= ECFW_TABLE_BITS) hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_TABLE_BITS>), dim3(rg.count), waves, 0, s, a, rg);
     else hipLaunchKernelGGL((w_encode_kernel<FMT, N, (int)ECFW_MAX_CODE_LEN>), dim3(rg.count), waves, 0, s, a, rg);
     return launched();
